@@ -24,7 +24,7 @@ struct WsLayout {
   size_t select_off, select_bytes;
   size_t topk_off, topk_bytes;
   size_t sel_off, sel_bytes;
-  size_t decode_off, decode_bytes;
+  size_t part_off, part_bytes;
   size_t total;
 };
 
@@ -71,7 +71,8 @@ quoka_status check_shape(const quoka_shape* s, Dims* dm) {
   return QUOKA_OK;
 }
 
-WsLayout layout(const Dims& dm) {
+// (`part`: partials of the key-split attention kernels)
+WsLayout layout(const Dims& dm, int dtype) {
   WsLayout l;
   l.select_off = 0;
   l.select_bytes = round_up(quoka::select_queries_ws_floats(dm) * sizeof(float), kAlign);
@@ -79,9 +80,10 @@ WsLayout layout(const Dims& dm) {
   l.topk_bytes = round_up(quoka::topk_ws_words(dm) * sizeof(uint32_t), kAlign);
   l.sel_off = l.topk_off + l.topk_bytes;
   l.sel_bytes = round_up(quoka::select_keys_ws_words(dm) * sizeof(uint32_t), kAlign);
-  l.decode_off = l.sel_off + l.sel_bytes;
-  l.decode_bytes = dm.b > 0 ? round_up(quoka::attn_decode_ws_floats(dm) * sizeof(float), kAlign) : 0;
-  l.total = l.decode_off + l.decode_bytes;
+  l.part_off = l.sel_off + l.sel_bytes;
+  const size_t part_floats = dtype == QUOKA_BF16 ? quoka::attn_decode_ws_floats(dm) : quoka::attn_f32_ws_floats(dm);
+  l.part_bytes = round_up(part_floats * sizeof(float), kAlign);
+  l.total = l.part_off + l.part_bytes;
   if (l.total == 0) l.total = kAlign;
   return l;
 }
@@ -135,7 +137,7 @@ quoka_status quoka_workspace_bytes(const quoka_shape* shape, size_t* out_bytes) 
   quoka_status st = check_shape(shape, &dm);
   if (st != QUOKA_OK) return st;
   if (out_bytes == nullptr) return QUOKA_EINVAL;
-  *out_bytes = layout(dm).total;
+  *out_bytes = layout(dm, shape->dtype).total;
   return QUOKA_OK;
 }
 
@@ -146,7 +148,7 @@ quoka_status quoka_select_queries(const quoka_shape* shape, const void* q, int32
   if (st != QUOKA_OK) return st;
   if (q == nullptr || q_idx == nullptr || qbar == nullptr) return QUOKA_EINVAL;
   if (!aligned16(q) || !aligned16(qbar)) return QUOKA_EINVAL;
-  const WsLayout l = layout(dm);
+  const WsLayout l = layout(dm, shape->dtype);
   st = check_ws(l, workspace, workspace_bytes);
   if (st != QUOKA_OK) return st;
   float* ws = reinterpret_cast<float*>(static_cast<char*>(workspace) + l.select_off);
@@ -162,7 +164,7 @@ quoka_status quoka_score_keys(const quoka_shape* shape, const float* qbar, const
   if (qbar == nullptr || kv_lens == nullptr) return QUOKA_EINVAL;
   if (dm.T_max > 0 && (k_cache == nullptr || scores == nullptr)) return QUOKA_EINVAL;
   if (!aligned16(qbar) || !aligned16(k_cache)) return QUOKA_EINVAL;
-  st = check_ws(layout(dm), workspace, workspace_bytes);
+  st = check_ws(layout(dm, shape->dtype), workspace, workspace_bytes);
   if (st != QUOKA_OK) return st;
   return from_hip(
       quoka::launch_score_keys(dm, shape->dtype, qbar, k_cache, kv_lens, scores, static_cast<hipStream_t>(stream)));
@@ -177,7 +179,7 @@ quoka_status quoka_topk_keys(const quoka_shape* shape, const float* scores, cons
   if (kv_lens == nullptr || budgets == nullptr || k_cnt == nullptr) return QUOKA_EINVAL;
   if (dm.T_max > 0 && scores == nullptr) return QUOKA_EINVAL;
   if (dm.B_max > 0 && k_idx == nullptr) return QUOKA_EINVAL;
-  const WsLayout l = layout(dm);
+  const WsLayout l = layout(dm, shape->dtype);
   st = check_ws(l, workspace, workspace_bytes);
   if (st != QUOKA_OK) return st;
   uint32_t* ws = reinterpret_cast<uint32_t*>(static_cast<char*>(workspace) + l.topk_off);
@@ -200,7 +202,7 @@ static quoka_status attn_common(const quoka_shape* shape, const void* q, const v
   if (!aligned16(q) || !aligned16(k_cache) || !aligned16(v_cache) || !aligned16(k_chunk) || !aligned16(v_chunk) ||
       !aligned16(out))
     return QUOKA_EINVAL;
-  const WsLayout l = layout(dm);
+  const WsLayout l = layout(dm, shape->dtype);
   st = check_ws(l, workspace, workspace_bytes);
   if (st != QUOKA_OK) return st;
   quoka::AttnArgs a;
@@ -216,11 +218,10 @@ static quoka_status attn_common(const quoka_shape* shape, const void* q, const v
   a.out = out;
   a.lse = lse;
   hipStream_t hs = static_cast<hipStream_t>(stream);
-  if (shape->dtype == QUOKA_BF16 && quoka::attn_decode_applies(dm)) {
-    float* part = reinterpret_cast<float*>(static_cast<char*>(workspace) + l.decode_off);
-    return from_hip(quoka::launch_attn_decode_bf16(dm, a, part, hs));
-  }
-  return from_hip(shape->dtype == QUOKA_BF16 ? quoka::launch_attn_bf16(dm, a, hs) : quoka::launch_attn_f32(dm, a, hs));
+  float* part = reinterpret_cast<float*>(static_cast<char*>(workspace) + l.part_off);
+  if (shape->dtype != QUOKA_BF16) return from_hip(quoka::launch_attn_f32(dm, a, part, hs));
+  if (quoka::attn_decode_applies(dm)) return from_hip(quoka::launch_attn_decode_bf16(dm, a, part, hs));
+  return from_hip(quoka::launch_attn_bf16(dm, a, hs));
 }
 
 quoka_status quoka_sparse_attn(const quoka_shape* shape, const void* q, const void* k_cache, const void* v_cache,
@@ -268,7 +269,7 @@ quoka_status quoka_select_keys(const quoka_shape* shape, const float* qbar, cons
   if (dm.T_max > 0 && (k_cache == nullptr || scores == nullptr)) return QUOKA_EINVAL;
   if (dm.B_max > 0 && k_idx == nullptr) return QUOKA_EINVAL;
   if (!aligned16(qbar) || !aligned16(k_cache)) return QUOKA_EINVAL;
-  const WsLayout l = layout(dm);
+  const WsLayout l = layout(dm, shape->dtype);
   st = check_ws(l, workspace, workspace_bytes);
   if (st != QUOKA_OK) return st;
   return select_keys_common(dm, shape->dtype, qbar, k_cache, kv_lens, budgets, scores, k_idx, k_cnt, workspace, l,
@@ -290,7 +291,7 @@ quoka_status quoka_chunk_attn(const quoka_shape* shape, const void* q, const voi
   if (dm.T_max > 0 && (k_cache == nullptr || scores == nullptr)) return QUOKA_EINVAL;
   if (dm.B_max > 0 && k_idx == nullptr) return QUOKA_EINVAL;
   if (!aligned16(q) || !aligned16(qbar) || !aligned16(k_cache)) return QUOKA_EINVAL;
-  const WsLayout l = layout(dm);
+  const WsLayout l = layout(dm, shape->dtype);
   st = check_ws(l, workspace, workspace_bytes);
   if (st != QUOKA_OK) return st;
   hipStream_t hs = static_cast<hipStream_t>(stream);

@@ -1,100 +1,327 @@
-// Chunk attention in float32 (Alg. 2 attention step; Eq. 2-3) for the float32 storage type.
-// One wave per query row: lanes take 64 keys at a time for the logits, then own head_dim / 64 output
-// dims each for the value accumulation; online softmax in float32.  Serves the sparse path (cache
-// rows through k_idx) and the dense baseline.
+// Chunk attention in float32 (Alg. 2 attention step; Eq. 2-3) for the float32 storage type: float32 matrix
+// instructions (v_mfma_f32_32x32x2_f32: float32 operands, float32 accumulation), online softmax in float32.  Serves the
+// sparse path (cache rows through k_idx) and the dense baseline.
+//
+// What bounds it: the float32 matrix rate (64 clocks for 32x32x2, twice the rate of plain FMAs); a 32-row, 32-key unit
+// takes D such instructions and reads only 2 * 32 * D floats, so operands come straight from global memory (the cache
+// rows of one KV head stay in L2) and no key tile is staged in LDS.
+//
+// Rows: the C * g query rows of a KV head are numbered r = token * g + head-in-group, so the 32 rows of a block span few
+// tokens and decode-sized chunks of all heads fill one row block.  Keys: the cache list and the chunk are cut into
+// units of 32 keys.  A block of eight waves owns one row block; its waves take the units in turn, each with its own
+// running (m, l, O), and are merged through LDS.  Row blocks that leave compute units idle are also split over the grid
+// along the key list: such blocks write partial (m, l, O) and attn_f32_merge adds them up.
+// Measured (8/2 heads, d 128, 512 tokens over 491 + 512 keys): 423 us for one wave per row with plain FMAs, 30 + 4 us here;
+// (2/1 heads, d 64, 128 tokens over 128 + 128 keys): 47 us and 10 us.
+//
+// Operand plan (a lane is (li = lane % 32, hf = lane / 32)); the contraction index may be permuted freely:
+//   S^T[key, row]: A = K row of key li, B = Q row li from LDS; step (i, e) contracts dims 8i + e (hf 0) and 8i + 4 + e.
+//     Register v of the result holds key 8*(v/4) + 4*hf + v%4 of the unit for query row li.
+//   O^T[dim, row]: step v contracts exactly the two keys that register v holds, so B = P is that register; A = V of the
+//     lane's key, M index m of block c standing for dim DB*m + c, so one contiguous load gives all DB blocks.
 #include "common.hip.h"
 #include "kernels.h"
 
 namespace quoka {
 
-constexpr int kF32Threads = 256;
+constexpr int kFaWaves = 8;
+constexpr int kFaThreads = 64 * kFaWaves;
+constexpr int kFaMaxSplits = 64;
 
 template <int D>
-__global__ __launch_bounds__(kF32Threads) void attn_f32(Dims dm, AttnArgs a) {
-  constexpr int EPL = D / 64;
-  __shared__ float qs[kF32Threads / 64][D];
-  const int lane = threadIdx.x & 63, w = threadIdx.x >> 6;
-  const int i = blockIdx.x * (kF32Threads / 64) + w;   // chunk position of this wave's row
-  const int h = blockIdx.y, b = blockIdx.z;
-  const bool row_on = i < dm.C;
-  if (row_on) {
-    const float* qsrc = static_cast<const float*>(a.q) + b * dm.qs[0] + h * dm.qs[1] + (size_t)i * dm.qs[2];
-#pragma unroll
-    for (int e = 0; e < EPL; ++e) qs[w][lane + 64 * e] = qsrc[lane + 64 * e];
-  }
-  __syncthreads();
-  if (!row_on) return;   // wave-uniform; no barrier follows
-  const int kv = h / dm.g;
+struct FaCfg {
+  static constexpr int NI = D / 8;        // 16-byte operand loads per lane of a K row
+  static constexpr int DB = D / 32;       // dim blocks of the PV product
+  static constexpr int QLD = D + 4;       // LDS pitch of the Q rows (floats): 16 bytes of padding
+  static constexpr int OLD = D + 4;       // LDS pitch of a wave's partial output rows
+  static constexpr int REC = D + 2;       // floats per row of a partial: O[D], m, l
+  static constexpr size_t kLdsBytes =
+      (size_t)32 * QLD * 4 + (size_t)kFaWaves * 32 * OLD * 4 + (size_t)kFaWaves * 32 * 2 * 4 + (size_t)kFaWaves * 32 * 4;
+};
+
+template <int DB>
+struct FaVec;
+template <>
+struct FaVec<2> {
+  typedef float type __attribute__((ext_vector_type(2)));
+};
+template <>
+struct FaVec<4> {
+  typedef float type __attribute__((ext_vector_type(4)));
+};
+
+struct FaRow {
+  int tok, head;   // chunk token and head-in-group of a flattened row
+};
+__device__ __forceinline__ FaRow fa_row(int r, int g) { return {r / g, r % g}; }
+
+template <int D>
+__global__ __launch_bounds__(kFaThreads, 2) void attn_f32(Dims dm, AttnArgs a, float* __restrict__ part, int n_splits) {
+  using Cfg = FaCfg<D>;
+  constexpr int NI = Cfg::NI, DB = Cfg::DB, QLD = Cfg::QLD, OLD = Cfg::OLD, REC = Cfg::REC;
+  typedef typename FaVec<DB>::type vrow;
+  typedef float f32x4 __attribute__((ext_vector_type(4)));
+  extern __shared__ __align__(16) unsigned char smem[];
+  float* qs = reinterpret_cast<float*>(smem);                 // [32][QLD]
+  float* os = qs + 32 * QLD;                                    // [kFaWaves][32][OLD]
+  float* ml = os + kFaWaves * 32 * OLD;                         // [kFaWaves][32][2]
+  uint32_t* offs = reinterpret_cast<uint32_t*>(ml + kFaWaves * 64);   // [kFaWaves][32] row offsets of the wave's unit
+
+  const int tid = threadIdx.x, lane = tid & 63;
+  const int w = __builtin_amdgcn_readfirstlane(tid >> 6);
+  const int li = lane & 31, hf = lane >> 5;
+  const int rb = gridDim.x - 1 - blockIdx.x;   // longest causal ranges first
+  const int split = blockIdx.y;
+  const int kv = blockIdx.z % dm.n_kv, b = blockIdx.z / dm.n_kv;
+  const int g = dm.g, n_rows = dm.C * g, row0 = rb * 32;
+
   const bool sparse = a.k_idx != nullptr;
   int n_cache = sparse ? min(a.n_cache[b * dm.n_kv + kv], dm.B_max) : min(a.n_cache[b], dm.T_max);
   n_cache = max(n_cache, 0);
-  const int32_t* kidx = sparse ? a.k_idx + (size_t)(b * dm.n_kv + kv) * dm.B_max : nullptr;
-  const float* kcache = static_cast<const float*>(a.k_cache) + b * dm.kvs[0] + kv * dm.kvs[1];
-  const float* vcache = static_cast<const float*>(a.v_cache) + b * dm.kvs[0] + kv * dm.kvs[1];
-  const float* kchunk = static_cast<const float*>(a.k_chunk) + b * dm.cks[0] + kv * dm.cks[1];
-  const float* vchunk = static_cast<const float*>(a.v_chunk) + b * dm.cks[0] + kv * dm.cks[1];
-  const float scale = 1.0f / sqrtf((float)D);
-  const int total = n_cache + i + 1;
-  float m_run = -INFINITY, l_run = 0.f;
-  float acc[EPL];
-#pragma unroll
-  for (int e = 0; e < EPL; ++e) acc[e] = 0.f;
+  const int n_chunk = fa_row(min(row0 + 31, n_rows - 1), g).tok + 1;   // chunk keys any row of the block can see
+  const int cache_units = (n_cache + 31) / 32, units = cache_units + (n_chunk + 31) / 32;
+  const int u_begin = (int)((long long)units * split / n_splits), u_end = (int)((long long)units * (split + 1) / n_splits);
 
-  for (int j0 = 0; j0 < total; j0 += 64) {
-    const int j = j0 + lane;
-    const bool valid = j < total;
-    const int jj = valid ? j : total - 1;
-    int is_chunk, row;
-    if (jj < n_cache) {
-      is_chunk = 0;
-      row = sparse ? (int)min((uint32_t)kidx[jj], (uint32_t)(dm.T_max - 1)) : jj;   // a malformed list cannot leave the cache
-    } else {
-      is_chunk = 1;
-      row = jj - n_cache;
+  // Q rows of the block to LDS (rows past the end repeat the last one and are never stored)
+  for (int i = tid; i < 32 * (D / 4); i += kFaThreads) {
+    const int r = i / (D / 4), c4 = i % (D / 4);
+    const FaRow fr = fa_row(min(row0 + r, n_rows - 1), g);
+    const float* src = static_cast<const float*>(a.q) + b * dm.qs[0] + (size_t)(kv * g + fr.head) * dm.qs[1] +
+                       (size_t)fr.tok * dm.qs[2] + 4 * c4;
+    *reinterpret_cast<f32x4*>(qs + r * QLD + 4 * c4) = *reinterpret_cast<const f32x4*>(src);
+  }
+
+  const int32_t* kidx = sparse ? a.k_idx + (size_t)(b * dm.n_kv + kv) * dm.B_max : nullptr;
+  const char* kcache = reinterpret_cast<const char*>(static_cast<const float*>(a.k_cache) + b * dm.kvs[0] + kv * dm.kvs[1]);
+  const char* vcache = reinterpret_cast<const char*>(static_cast<const float*>(a.v_cache) + b * dm.kvs[0] + kv * dm.kvs[1]);
+  const char* kchunk = reinterpret_cast<const char*>(static_cast<const float*>(a.k_chunk) + b * dm.cks[0] + kv * dm.cks[1]);
+  const char* vchunk = reinterpret_cast<const char*>(static_cast<const float*>(a.v_chunk) + b * dm.cks[0] + kv * dm.cks[1]);
+  const uint32_t cache_rb = (uint32_t)dm.kvs[2] * 4u, chunk_rb = (uint32_t)dm.cks[2] * 4u;
+
+  // byte offset of the row that slot li of unit u names (slots past the list repeat its last row; they are masked)
+  auto row_offset = [&](int u) -> uint32_t {
+    if (u < cache_units) {
+      const int n = min(u * 32 + li, n_cache - 1);
+      const uint32_t src = sparse ? min((uint32_t)kidx[n], (uint32_t)(dm.T_max - 1)) : (uint32_t)n;   // a malformed list cannot leave the cache
+      return src * cache_rb;
     }
-    const float* kp = is_chunk ? kchunk + (size_t)row * dm.cks[2] : kcache + (size_t)row * dm.kvs[2];
-    float dot = 0.f;
-#pragma unroll 8
-    for (int d0 = 0; d0 < D; d0 += 4) {
-      const float4 kx = *reinterpret_cast<const float4*>(kp + d0);
-      dot += qs[w][d0] * kx.x;
-      dot += qs[w][d0 + 1] * kx.y;
-      dot += qs[w][d0 + 2] * kx.z;
-      dot += qs[w][d0 + 3] * kx.w;
+    return (uint32_t)min((u - cache_units) * 32 + li, n_chunk - 1) * chunk_rb;
+  };
+  f32x4 kreg[NI];
+  auto load_k = [&](int u, uint32_t off) __attribute__((always_inline)) {
+    const char* base = (u < cache_units ? kcache : kchunk) + 16 * hf;
+#pragma unroll
+    for (int i = 0; i < NI; ++i) kreg[i] = *reinterpret_cast<const f32x4*>(base + off + 32 * i);
+  };
+
+  f32x16 o[DB];
+#pragma unroll
+  for (int c = 0; c < DB; ++c)
+#pragma unroll
+    for (int v = 0; v < 16; ++v) o[c][v] = 0.f;
+  float m_run = -INFINITY, l_run = 0.f;   // of row li; l_run is this half wave's share
+  const float scale2 = 1.4426950408889634f / sqrtf((float)D);   // softmax scale and the change to base 2
+  const int tok = fa_row(min(row0 + li, n_rows - 1), g).tok;
+
+  int u = u_begin + w;
+  uint32_t off = 0;
+  if (u < u_end) {
+    off = row_offset(u);
+    load_k(u, off);
+  }
+  __syncthreads();   // Q rows are in LDS
+  uint32_t* my_offs = offs + w * 32;
+  const float* qrow = qs + li * QLD + 4 * hf;
+  for (; u < u_end; u += kFaWaves) {
+    const bool is_chunk = u >= cache_units;
+    // the rows of the unit's 16 V loads: slot 8*(v/4) + 4*hf + v%4 belongs to another lane (only this wave uses its row
+    // of `offs`, and a wave's LDS accesses stay in order)
+    if (hf == 0) my_offs[li] = off;
+    __builtin_amdgcn_wave_barrier();
+    uint32_t voff[16];
+#pragma unroll
+    for (int q4 = 0; q4 < 4; ++q4) {
+      const u32x4 t = *reinterpret_cast<const u32x4*>(my_offs + 8 * q4 + 4 * hf);
+#pragma unroll
+      for (int e = 0; e < 4; ++e) voff[4 * q4 + e] = t[e];
     }
-    const float s = valid ? dot * scale : -INFINITY;
-    const float m_new = fmaxf(m_run, wave64_max(s));   // finite: key j0 is always visible
-    const float alpha = expf(m_run - m_new);
-    const float p = valid ? expf(s - m_new) : 0.f;
-    l_run = l_run * alpha + wave64_sum(p);
-    m_run = m_new;
+    vrow vreg[16];   // in flight during the first product
+    const char* vbase = (is_chunk ? vchunk : vcache) + (DB * 4) * li;
 #pragma unroll
-    for (int e = 0; e < EPL; ++e) acc[e] *= alpha;
-    const int cnt = min(64, total - j0);
-    for (int t = 0; t < cnt; ++t) {
-      // t is wave-uniform: lane reads through the scalar path instead of LDS shuffles
-      const float pt = __int_as_float(__builtin_amdgcn_readlane(__float_as_int(p), t));
-      const int ct = __builtin_amdgcn_readlane(is_chunk, t);
-      const int rt = __builtin_amdgcn_readlane(row, t);
-      const float* vp = ct ? vchunk + (size_t)rt * dm.cks[2] : vcache + (size_t)rt * dm.kvs[2];
+    for (int v = 0; v < 16; ++v) vreg[v] = *reinterpret_cast<const vrow*>(vbase + voff[v]);
+    uint32_t off_next = 0;
+    if (u + kFaWaves < u_end) off_next = row_offset(u + kFaWaves);
+
+    f32x16 s;
 #pragma unroll
-      for (int e = 0; e < EPL; ++e) acc[e] += pt * vp[lane + 64 * e];
+    for (int v = 0; v < 16; ++v) s[v] = 0.f;
+#pragma unroll
+    for (int i = 0; i < NI; ++i) {
+      const f32x4 qv = *reinterpret_cast<const f32x4*>(qrow + 8 * i);
+#pragma unroll
+      for (int e = 0; e < 4; ++e) s = __builtin_amdgcn_mfma_f32_32x32x2f32(kreg[i][e], qv[e], s, 0, 0, 0);
+    }
+    off = off_next;
+    if (u + kFaWaves < u_end) load_k(u + kFaWaves, off);   // travels during the softmax and the second product
+
+    const int limit = is_chunk ? tok + 1 - (u - cache_units) * 32 : n_cache - u * 32;   // slots kk < limit are visible
+    float mx = -INFINITY;
+#pragma unroll
+    for (int v = 0; v < 16; ++v) {
+      const int kk = 8 * (v / 4) + 4 * hf + (v % 4);
+      if (kk >= limit) s[v] = -INFINITY;
+      mx = fmaxf(mx, s[v]);
+    }
+    mx = fmaxf(mx, other_half(mx)) * scale2;
+    // the reference point moves only when the unit's maximum exceeds it by more than 2^8
+    const bool moves = m_run == -INFINITY ? mx > -INFINITY : mx > m_run + 8.0f;
+    if (__builtin_amdgcn_ballot_w64(moves) != 0) {   // wave-uniform branch
+      const float m_new = moves ? mx : m_run;
+      const float alpha = __builtin_amdgcn_exp2f(m_run - (m_new == -INFINITY ? 0.f : m_new));
+      m_run = m_new;
+      l_run *= alpha;
+#pragma unroll
+      for (int c = 0; c < DB; ++c)
+#pragma unroll
+        for (int v = 0; v < 16; ++v) o[c][v] *= alpha;
+    }
+    const float neg_m = m_run == -INFINITY ? 0.f : -m_run;
+#pragma unroll
+    for (int v = 0; v < 16; ++v) {
+      s[v] = __builtin_amdgcn_exp2f(fmaf(s[v], scale2, neg_m));
+      l_run += s[v];
+    }
+#pragma unroll
+    for (int v = 0; v < 16; ++v)
+#pragma unroll
+      for (int c = 0; c < DB; ++c) o[c] = __builtin_amdgcn_mfma_f32_32x32x2f32(vreg[v][c], s[v], o[c], 0, 0, 0);
+  }
+
+  // ---- merge the waves: every wave leaves (m, l) and its output rows, all threads add them up ----
+  const float l_wave = l_run + other_half(l_run);
+  if (hf == 0) {
+    ml[(w * 32 + li) * 2] = m_run;
+    ml[(w * 32 + li) * 2 + 1] = l_wave;
+  }
+  float* my_os = os + (size_t)(w * 32 + li) * OLD;
+#pragma unroll
+  for (int v = 0; v < 16; ++v) {
+    const int m = 8 * (v / 4) + 4 * hf + (v % 4);
+    vrow t;
+#pragma unroll
+    for (int c = 0; c < DB; ++c) t[c] = o[c][v];
+    *reinterpret_cast<vrow*>(my_os + DB * m) = t;   // dims DB*m .. +DB
+  }
+  __syncthreads();
+  float* my_part = part + ((size_t)(blockIdx.z * gridDim.x + rb) * n_splits + split) * 32 * REC;
+  for (int i = tid; i < 32 * (D / 4); i += kFaThreads) {
+    const int r = i / (D / 4), c4 = i % (D / 4);
+    float m = -INFINITY;
+#pragma unroll
+    for (int j = 0; j < kFaWaves; ++j) m = fmaxf(m, ml[(j * 32 + r) * 2]);
+    const float m_fin = m == -INFINITY ? 0.f : m;
+    float l = 0.f;
+    f32x4 acc = {0.f, 0.f, 0.f, 0.f};
+#pragma unroll
+    for (int j = 0; j < kFaWaves; ++j) {
+      const float wgt = __builtin_amdgcn_exp2f(ml[(j * 32 + r) * 2] - m_fin);   // 0 for a wave that saw no key of this row
+      l += wgt * ml[(j * 32 + r) * 2 + 1];
+      const f32x4 x = *reinterpret_cast<const f32x4*>(os + (size_t)(j * 32 + r) * OLD + 4 * c4);
+#pragma unroll
+      for (int e = 0; e < 4; ++e) acc[e] += wgt * x[e];
+    }
+    if (n_splits > 1) {   // block-uniform
+      *reinterpret_cast<f32x4*>(my_part + r * D + 4 * c4) = acc;
+      if (c4 == 0) {
+        my_part[32 * D + r] = m;
+        my_part[32 * D + 32 + r] = l;
+      }
+    } else if (row0 + r < n_rows) {
+      const FaRow fr = fa_row(row0 + r, g);
+      const int h = kv * g + fr.head;
+      float* orow = static_cast<float*>(a.out) + b * dm.os[0] + h * dm.os[1] + (size_t)fr.tok * dm.os[2];
+#pragma unroll
+      for (int e = 0; e < 4; ++e) acc[e] /= l;
+      *reinterpret_cast<f32x4*>(orow + 4 * c4) = acc;
+      if (c4 == 0 && a.lse != nullptr)
+        a.lse[(size_t)(b * dm.n_q + h) * dm.C + fr.tok] = (m + log2f(l)) * 0.6931471805599453f;
     }
   }
-  float* orow = static_cast<float*>(a.out) + b * dm.os[0] + h * dm.os[1] + (size_t)i * dm.os[2];
-#pragma unroll
-  for (int e = 0; e < EPL; ++e) orow[lane + 64 * e] = acc[e] / l_run;
-  if (a.lse != nullptr && lane == 0) a.lse[(size_t)(b * dm.n_q + h) * dm.C + i] = m_run + logf(l_run);
 }
 
-hipError_t launch_attn_f32(const Dims& dm, const AttnArgs& a, hipStream_t st) {
-  dim3 grid((dm.C + kF32Threads / 64 - 1) / (kF32Threads / 64), dm.n_q, dm.b);
-  if (dm.d == 64) {
-    hipLaunchKernelGGL((attn_f32<64>), grid, dim3(kF32Threads), 0, st, dm, a);
-  } else {
-    hipLaunchKernelGGL((attn_f32<128>), grid, dim3(kF32Threads), 0, st, dm, a);
+// Sum of the splits' partials: one thread per (row, 4 dims), D / 4 threads per row, summed in split order.
+template <int D>
+__global__ __launch_bounds__(256) void attn_f32_merge(Dims dm, AttnArgs a, const float* __restrict__ part, int n_rb,
+                                                     int n_splits) {
+  constexpr int REC = FaCfg<D>::REC;
+  typedef float f32x4 __attribute__((ext_vector_type(4)));
+  const int row = blockIdx.x * (256 / (D / 4)) + threadIdx.x / (D / 4), c4 = threadIdx.x % (D / 4);
+  const int kv = blockIdx.y % dm.n_kv, b = blockIdx.y / dm.n_kv;
+  if (row >= dm.C * dm.g) return;
+  const float* rec = part + ((size_t)blockIdx.y * n_rb + row / 32) * n_splits * 32 * REC;
+  const int r = row % 32;
+  float m = -INFINITY;
+  for (int s = 0; s < n_splits; ++s) m = fmaxf(m, rec[(size_t)s * 32 * REC + 32 * D + r]);
+  float l = 0.f;
+  f32x4 acc = {0.f, 0.f, 0.f, 0.f};
+  for (int s = 0; s < n_splits; ++s) {
+    const float* p = rec + (size_t)s * 32 * REC;
+    const float wgt = __builtin_amdgcn_exp2f(p[32 * D + r] - m);   // (every row sees at least its own key: m is finite)
+    l += wgt * p[32 * D + 32 + r];
+    const f32x4 x = *reinterpret_cast<const f32x4*>(p + r * D + 4 * c4);
+#pragma unroll
+    for (int e = 0; e < 4; ++e) acc[e] += wgt * x[e];
+  }
+  const FaRow fr = fa_row(row, dm.g);
+  const int h = kv * dm.g + fr.head;
+  float* orow = static_cast<float*>(a.out) + b * dm.os[0] + h * dm.os[1] + (size_t)fr.tok * dm.os[2];
+#pragma unroll
+  for (int e = 0; e < 4; ++e) acc[e] /= l;
+  *reinterpret_cast<f32x4*>(orow + 4 * c4) = acc;
+  if (c4 == 0 && a.lse != nullptr)
+    a.lse[(size_t)(b * dm.n_q + h) * dm.C + fr.tok] = (m + log2f(l)) * 0.6931471805599453f;
+}
+
+// ---------------------------------------------------------------------------------------------
+// Splits of the key list: as many as give every compute unit a block, but at least one unit of 32 keys for every wave
+// of a block (a split costs 16 KiB of partials and a share of the merge launch).
+static long long f32_blocks(const Dims& dm) { return (long long)dm.b * dm.n_kv * ((dm.C * dm.g + 31) / 32); }
+static int f32_most_splits(const Dims& dm, bool sparse) {
+  const long long units = ((long long)(sparse ? dm.B_max : dm.T_max) + 31) / 32 + (dm.C + 31) / 32;
+  const long long n = (units + kFaWaves - 1) / kFaWaves;
+  return (int)(n > kFaMaxSplits ? kFaMaxSplits : n);
+}
+static int f32_splits(const Dims& dm, bool sparse) {
+  const long long blocks = f32_blocks(dm), n = (256 + blocks - 1) / blocks;
+  const int most = f32_most_splits(dm, sparse);
+  return n < most ? (int)n : most;
+}
+
+// Fewer than 256 row blocks are split into at most 2 * 256 blocks; the other bound grows with the chunk length.  So the
+// partials of a shorter chunk of the same shape (a prompt's last one) fit as well.
+size_t attn_f32_ws_floats(const Dims& dm) {
+  const long long most = f32_blocks(dm) * f32_most_splits(dm, false);
+  return (size_t)(most < 2 * 256 ? most : 2 * 256) * 32 * (dm.d + 2);
+}
+
+template <int D>
+static hipError_t launch_f32_d(const Dims& dm, const AttnArgs& a, float* part, hipStream_t st) {
+  static std::atomic<uint64_t> lds_done{0};
+  const hipError_t e = ensure_dynamic_lds(reinterpret_cast<const void*>(&attn_f32<D>), FaCfg<D>::kLdsBytes, lds_done);
+  if (e != hipSuccess) return e;
+  const int n_splits = f32_splits(dm, a.k_idx != nullptr), n_rb = (dm.C * dm.g + 31) / 32;
+  hipLaunchKernelGGL((attn_f32<D>), dim3(n_rb, n_splits, dm.b * dm.n_kv), dim3(kFaThreads), FaCfg<D>::kLdsBytes, st, dm,
+                     a, part, n_splits);
+  if (n_splits > 1) {
+    constexpr int kRows = 256 / (D / 4);
+    hipLaunchKernelGGL((attn_f32_merge<D>), dim3((dm.C * dm.g + kRows - 1) / kRows, dm.b * dm.n_kv), dim3(256), 0, st,
+                       dm, a, part, n_rb, n_splits);
   }
   return hipGetLastError();
+}
+
+hipError_t launch_attn_f32(const Dims& dm, const AttnArgs& a, float* part, hipStream_t st) {
+  return dm.d == 64 ? launch_f32_d<64>(dm, a, part, st) : launch_f32_d<128>(dm, a, part, st);
 }
 
 }  // namespace quoka

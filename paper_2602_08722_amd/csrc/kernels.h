@@ -71,7 +71,9 @@ hipError_t launch_attn_bf16(const Dims& dm, const AttnArgs& a, hipStream_t st);
 bool attn_decode_applies(const Dims& dm);
 size_t attn_decode_ws_floats(const Dims& dm);
 hipError_t launch_attn_decode_bf16(const Dims& dm, const AttnArgs& a, float* part, hipStream_t st);
-hipError_t launch_attn_f32(const Dims& dm, const AttnArgs& a, hipStream_t st);
+// (float32: partials of key-split blocks in `part`)
+size_t attn_f32_ws_floats(const Dims& dm);
+hipError_t launch_attn_f32(const Dims& dm, const AttnArgs& a, float* part, hipStream_t st);
 
 // --- measurement aids (probes.hip) ------------------------------------------------------------------
 hipError_t launch_probe_mfma(int blocks, int iters, float* sink, hipStream_t st);

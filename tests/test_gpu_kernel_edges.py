@@ -1,0 +1,86 @@
+"""Kernel variants at the sizes where they can go wrong -- edges of tiles and units, remainders, the smallest and largest
+of their range -- against the oracle, at the bars of tests/parity.py (float32 sums and bf16 operands respectively)."""
+import numpy as np
+import pytest
+import torch
+
+import gen
+from oracle import quoka_oracle as O
+from tests import parity as P
+from tests.test_gpu_stages import _buffers
+
+pytestmark = pytest.mark.gpu
+
+
+def _id(c):
+    return "-".join(f"{k}{v}" for k, v in c.items())
+
+
+def check_attention(case, rows=None, score_flags=0, tol=None):
+    """Sparse attention over seeded random index lists of the stated budgets, then dense attention, each with its
+    softmax normaliser, against the oracle (every row, or the chunk positions `rows`)."""
+    case = dict(case)
+    batch = case.setdefault("batch", 1)
+    w = gen.make_custom(n_retain=8, seed=21, **case)
+    buf = _buffers(w, score_flags=score_flags)
+    tol = tol or P.TOL_OUT[w.dtype]
+    tol_lse = 1e-4 if w.dtype == "f32" else 2e-2
+    rng = np.random.default_rng(3)
+    lists = []
+    for b in range(batch):
+        n = min(w.budgets[b], w.kv_lens[b])
+        lists.append(np.stack([np.sort(rng.choice(w.kv_lens[b], size=n, replace=False)) if n else np.zeros(0, np.int64)
+                               for _ in range(w.n_kv)]))
+    host = np.zeros(tuple(buf.k_idx.shape), dtype=np.int32)
+    for b in range(batch):
+        host[b, :, :lists[b].shape[1]] = lists[b]
+    buf.k_idx.copy_(torch.from_numpy(host))
+    buf.k_cnt.copy_(torch.from_numpy(np.array([[x.shape[1]] * w.n_kv for x in lists], dtype=np.int32)))
+    at = slice(None) if rows is None else rows
+    for name in ("sparse", "dense"):
+        buf.workspace.fill_(0xA5)
+        buf.out.fill_(float("nan"))
+        buf.lse.fill_(float("nan"))
+        (buf.sparse_attn if name == "sparse" else buf.dense_attn)()
+        torch.cuda.synchronize()
+        out, lse = gen.from_torch(buf.out), gen.from_torch(buf.lse)
+        assert not np.isnan(out).any() and not np.isnan(lse).any()
+        for b in range(batch):
+            K, V = w.K[b][:, :w.kv_lens[b]], w.V[b][:, :w.kv_lens[b]]
+            if name == "sparse":
+                want, want_lse = O.sparse_attn(w.Q[b], K, V, lists[b], w.Kc[b], w.Vc[b], True, rows=rows)
+            else:
+                want, want_lse = O.dense_attn(w.Q[b], K, V, w.Kc[b], w.Vc[b], True, rows=rows)
+            err, err_lse = P.max_abs(out[b][:, at], want), P.max_abs(lse[b][:, at], want_lse)
+            assert err <= tol and err_lse <= tol_lse, f"{name} b{b}: out {err}, lse {err_lse}"
+
+
+F32_ATTN_CASES = [
+    dict(n_q=2, n_kv=1, d=64, chunk=1, kv_lens=[1], budgets=[1]),            # one row, two keys
+    dict(n_q=3, n_kv=1, d=128, chunk=11, kv_lens=[31], budgets=[31]),        # 33 rows; one unit short of full
+    dict(n_q=2, n_kv=2, d=64, chunk=32, kv_lens=[33], budgets=[32]),         # exact units, then one key more
+    dict(n_q=2, n_kv=1, d=128, chunk=17, kv_lens=[5000], budgets=[2000]),    # 34 rows, the key list split over blocks
+    dict(n_q=4, n_kv=1, d=64, chunk=1, kv_lens=[9000], budgets=[513]),       # decode-sized, most splits
+    dict(n_q=5, n_kv=1, d=128, chunk=70, kv_lens=[300, 0, 7], budgets=[64, 3, 7], batch=3),
+    dict(n_q=16, n_kv=8, d=64, chunk=600, kv_lens=[40], budgets=[5]),        # more row blocks than compute units: no split
+]
+
+
+@pytest.mark.parametrize("case", F32_ATTN_CASES, ids=_id)
+def test_float32_attention_units_rows_and_splits(case):
+    check_attention(dict(case, dtype="f32"))
+
+
+@pytest.mark.parametrize("n_retain,kv_len,d", [(1, 1, 64), (32, 127, 128), (33, 129, 128), (64, 64, 64), (65, 1000, 128),
+                                               (128, 33, 64), (40, 70001, 64)])
+def test_float32_scores_query_blocks_and_key_tails(n_retain, kv_len, d):
+    w = gen.make_custom(dtype="f32", n_q=2, n_kv=1, d=d, chunk=140, kv_lens=[kv_len], budgets=[1], n_retain=n_retain, seed=22)
+    buf = _buffers(w)
+    qbar = O.group_mean_queries(w.Q[0], O.select_queries(w.Q[0], n_retain), 1).astype(np.float32)
+    buf.qbar.copy_(torch.from_numpy(qbar[None]))
+    buf.scores.fill_(float("nan"))
+    buf.score_keys()
+    torch.cuda.synchronize()
+    got = gen.from_torch(buf.scores)[0]
+    want = O.key_scores_preagg(qbar.astype(np.float64), w.K[0])
+    assert not np.isnan(got).any() and P.max_abs(got, want) <= P.TOL_SCORE
