@@ -81,7 +81,11 @@ WsLayout layout(const Dims& dm, int dtype) {
   l.sel_off = l.topk_off + l.topk_bytes;
   l.sel_bytes = round_up(quoka::select_keys_ws_words(dm) * sizeof(uint32_t), kAlign);
   l.part_off = l.sel_off + l.sel_bytes;
-  const size_t part_floats = dtype == QUOKA_BF16 ? quoka::attn_decode_ws_floats(dm) : quoka::attn_f32_ws_floats(dm);
+  size_t part_floats = quoka::attn_f32_ws_floats(dm);
+  if (dtype == QUOKA_BF16) {   // (a prompt's last chunk may be decode-sized when the others are not)
+    const size_t decode = quoka::attn_decode_ws_floats(dm), prefill = quoka::attn_bf16_ws_floats(dm);
+    part_floats = decode > prefill ? decode : prefill;
+  }
   l.part_bytes = round_up(part_floats * sizeof(float), kAlign);
   l.total = l.part_off + l.part_bytes;
   if (l.total == 0) l.total = kAlign;
@@ -221,7 +225,7 @@ static quoka_status attn_common(const quoka_shape* shape, const void* q, const v
   float* part = reinterpret_cast<float*>(static_cast<char*>(workspace) + l.part_off);
   if (shape->dtype != QUOKA_BF16) return from_hip(quoka::launch_attn_f32(dm, a, part, hs));
   if (quoka::attn_decode_applies(dm)) return from_hip(quoka::launch_attn_decode_bf16(dm, a, part, hs));
-  return from_hip(quoka::launch_attn_bf16(dm, a, hs));
+  return from_hip(quoka::launch_attn_bf16(dm, a, part, hs));
 }
 
 quoka_status quoka_sparse_attn(const quoka_shape* shape, const void* q, const void* k_cache, const void* v_cache,

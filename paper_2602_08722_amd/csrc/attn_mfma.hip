@@ -73,6 +73,7 @@ struct AttnCfg {
   static constexpr size_t kKTileBytes = (size_t)KT * LD * 2;
   static constexpr size_t kStageBytes = kKTileBytes + (size_t)KT * LDV * 2;   // one K tile and one V tile
   static constexpr size_t kLdsBytes = 2 * kStageBytes;                          // double buffered
+  static constexpr int kRecFloats = 32 * (D + 2);     // partial of a row block: O as the registers lie, m, l
 };
 
 // XS (QUOKA_ATTN_SCALE_F32): the softmax scale is applied to the float32 products, one fused multiply-add per score
@@ -81,7 +82,9 @@ struct AttnCfg {
 // what the exponential takes and no vector instruction is spent on either -- 4-9 % faster, at the price of rounding Q a
 // second time: an error of the logits of relative size 2^-9, which shows in the output once the logits are several
 // times those of unit-variance inputs (0.03 absolute at four times, 0.06 at eight).
-template <int D, bool SPLIT, bool XS>
+// KSPLIT: the key list is shared by a.n_splits blocks, each of which writes a partial result.  (A template parameter: as
+// a run-time switch it cost the unsplit launches 1.5-2 %.)
+template <int D, bool SPLIT, bool XS, bool KSPLIT>
 __global__ __launch_bounds__(2 * kSetThreads, 2) void attn_bf16(Dims dm, AttnArgs a) {
   using Cfg = AttnCfg<D, SPLIT>;
   constexpr int KT = Cfg::KT, KS = Cfg::KS, LD = Cfg::LD, LDV = Cfg::LDV, CG = Cfg::CG, RPI = Cfg::RPI, NLD = Cfg::NLD,
@@ -110,20 +113,22 @@ __global__ __launch_bounds__(2 * kSetThreads, 2) void attn_bf16(Dims dm, AttnArg
   // row block.  Otherwise set 0 is front, set 1 back.
   const int slot = SPLIT ? (w + 2 * set) % 4 : w + 4 * set;
   const bool back = SPLIT ? slot >= 2 : set == 1;
-  const int kf = blockIdx.y * HW + slot % HW;
+  const int yb = KSPLIT ? (int)blockIdx.y / a.n_splits : (int)blockIdx.y;   // group of row blocks
+  const int split = KSPLIT ? (int)blockIdx.y - yb * a.n_splits : 0;                               // share of its key list
+  const int kf = yb * HW + slot % HW;
   // Row blocks of a block.  Paired (a launch of one round): half from the front of the list, half from the back, so all
   // blocks take equally long.  Adjacent (a launch of several rounds): 2*HW neighbours with nearly the same causal range,
   // so no wave idles while others still have chunk keys to go, and the blocks with the longest ranges come first
   // in the grid: the compute units that finish the short blocks early pick up more of what is left.
   const bool adjacent = a.adjacent != 0;
-  const int x = adjacent ? nrb - 1 - ((int)blockIdx.y * 2 * HW + slot) : (back ? nrb - 1 - kf : kf);
+  const int x = adjacent ? nrb - 1 - (yb * 2 * HW + slot) : (back ? nrb - 1 - kf : kf);
   const bool wave_on = adjacent ? x >= 0 : (back ? (x >= half) : (x < half));
   const int xj = wave_on ? x % g : 0;
   const int tok0 = wave_on ? (x / g) * 32 : 0;
   const int h = kv * g + xj;
-  const int xb_hi = nrb - 1 - (int)blockIdx.y * HW;                                     // the block's last row block
-  const int x_hi = adjacent ? nrb - 1 - (int)blockIdx.y * 2 * HW
-                            : (xb_hi >= half ? xb_hi : min((int)blockIdx.y * HW + HW - 1, half - 1));
+  const int xb_hi = nrb - 1 - yb * HW;                                     // the block's last row block
+  const int x_hi = adjacent ? nrb - 1 - yb * 2 * HW
+                            : (xb_hi >= half ? xb_hi : min(yb * HW + HW - 1, half - 1));
   const int c_end_blk = min((x_hi / g) * 32 + 32, C);   // chunk keys any wave of this block can see
   const int sub = SPLIT ? set * kSub : 0;               // first key of this set's share of a staged tile
 
@@ -139,6 +144,8 @@ __global__ __launch_bounds__(2 * kSetThreads, 2) void attn_bf16(Dims dm, AttnArg
   const int n_cht = (c_end_blk + KT - 1) / KT;
   const int n_ct = (n_cache + KT - 1) / KT;
   const int n_tiles = n_cht + n_ct;
+  const int t_begin = KSPLIT ? (int)((long long)n_tiles * split / a.n_splits) : 0;
+  const int t_end = KSPLIT ? (int)((long long)n_tiles * (split + 1) / a.n_splits) : n_tiles;
 
   const uint16_t* qg = static_cast<const uint16_t*>(a.q);
   // The tensor this set stages (set 0: K, set 1: V) for this (batch, KV head), as byte pointers: every row is
@@ -181,7 +188,7 @@ __global__ __launch_bounds__(2 * kSetThreads, 2) void attn_bf16(Dims dm, AttnArg
 #define QUOKA_RESOLVE(IT)                                                                          \
   do {                                                                                             \
     const int it_ = (IT);                                                                          \
-    if (it_ < n_tiles) {                                                                           \
+    if (it_ < t_end) {                                                                             \
       const bool cache_ = it_ >= n_cht;                                                            \
       const int base_ = cache_ ? (it_ - n_cht) * KT : it_ * KT;                                    \
       const int last_ = cache_ ? n_cache - 1 : C - 1;                                              \
@@ -209,13 +216,18 @@ __global__ __launch_bounds__(2 * kSetThreads, 2) void attn_bf16(Dims dm, AttnArg
       R[i] = *reinterpret_cast<const u32x4*>(tb_ + (min(rows[i], row_max_) * rb_ + (uint32_t)cg * 16u)); \
   } while (0)
 
-  // tile 0 is the first chunk tile (the chunk is never empty): no index, no cache length
+  if (!KSPLIT || t_begin == 0) {
+    // tile 0 is the first chunk tile (the chunk is never empty): no index, no cache length
 #pragma unroll
-  for (int i = 0; i < NLD; ++i) {
-    rows[i] = (uint32_t)min(r0 + RPI * i, C - 1);
-    R[i] = *reinterpret_cast<const u32x4*>(chunk_base + (rows[i] * chunk_row_bytes + (uint32_t)cg * 16u));
+    for (int i = 0; i < NLD; ++i) {
+      rows[i] = (uint32_t)min(r0 + RPI * i, C - 1);
+      R[i] = *reinterpret_cast<const u32x4*>(chunk_base + (rows[i] * chunk_row_bytes + (uint32_t)cg * 16u));
+    }
+  } else if (t_begin < t_end) {
+    QUOKA_RESOLVE(t_begin);
+    QUOKA_ISSUE(t_begin);
   }
-  QUOKA_RESOLVE(1);
+  QUOKA_RESOLVE(t_begin + 1);
 
   f32x16 o[DB];
 #pragma unroll
@@ -236,7 +248,7 @@ __global__ __launch_bounds__(2 * kSetThreads, 2) void attn_bf16(Dims dm, AttnArg
   auto share_base = [&](int t) { return (t >= n_cht ? t - n_cht : t) * KT + sub; };
   // whether this wave has anything visible in its share of tile t
   auto computes = [&](int t) {
-    if (!wave_on || t < 0 || t >= n_tiles) return false;
+    if (!wave_on) return false;
     const int base = share_base(t);
     return t < n_cht ? base <= tok0 + 31 : base < n_cache;
   };
@@ -372,17 +384,17 @@ __global__ __launch_bounds__(2 * kSetThreads, 2) void attn_bf16(Dims dm, AttnArg
 #pragma unroll
     for (int i = 0; i < NLD; ++i) *reinterpret_cast<u32x4*>(dst + (r0 + RPI * i) * ld_mine + cg * 8) = R[i];
   };
-  stage_tile(0);
-  if (1 < n_tiles) {
-    QUOKA_ISSUE(1);
-    QUOKA_RESOLVE(2);
+  if (!KSPLIT || t_begin < t_end) stage_tile(t_begin);   // (a split without tiles contributes the neutral partial)
+  if (t_begin + 1 < t_end) {
+    QUOKA_ISSUE(t_begin + 1);
+    QUOKA_RESOLVE(t_begin + 2);
   }
   if (set == 1) __syncthreads();   // (with the fence: V of tile 0 is complete before set 0 passes its first barrier)
-  for (int j = 0; j < n_tiles; ++j) {
+  for (int j = t_begin; j < t_end; ++j) {
     __syncthreads();
-    if (j + 1 < n_tiles) {
+    if (j + 1 < t_end) {
       stage_tile(j + 1);
-      if (j + 2 < n_tiles) {
+      if (j + 2 < t_end) {
         QUOKA_ISSUE(j + 2);
         QUOKA_RESOLVE(j + 3);
       }
@@ -426,6 +438,21 @@ __global__ __launch_bounds__(2 * kSetThreads, 2) void attn_bf16(Dims dm, AttnArg
 
   // ---- epilogue -------------------------------------------------------------------------------
   const float l_tot = l_run + other_half(l_run);
+  if constexpr (KSPLIT) {   // the partial goes out as the registers lie, 1 KiB per store
+    if (!wave_on) return;
+    float* rec = a.part + (((size_t)(b * dm.n_kv + kv) * nrb + x) * a.n_splits + split) * Cfg::kRecFloats;
+#pragma unroll
+    for (int c = 0; c < DB; ++c)
+#pragma unroll
+      for (int v4 = 0; v4 < 4; ++v4)
+        *reinterpret_cast<float4*>(rec + ((c * 4 + v4) * 64 + lane) * 4) =
+            make_float4(o[c][4 * v4], o[c][4 * v4 + 1], o[c][4 * v4 + 2], o[c][4 * v4 + 3]);
+    if (hf == 0) {
+      rec[32 * D + li] = m_run;
+      rec[32 * D + 32 + li] = l_tot;
+    }
+    return;
+  }
   if (wave_on && tok < C) {
     const float inv = 1.0f / l_tot;
     uint16_t* orow = static_cast<uint16_t*>(a.out) + b * dm.os[0] + h * dm.os[1] + (size_t)tok * dm.os[2];
@@ -447,43 +474,141 @@ __global__ __launch_bounds__(2 * kSetThreads, 2) void attn_bf16(Dims dm, AttnArg
 #undef QUOKA_RESOLVE
 #undef QUOKA_ISSUE
 
-template <int D, bool SPLIT, bool XS>
-static hipError_t launch_dsx(const Dims& dm, const AttnArgs& a, hipStream_t st) {
+// Sum of the key splits' partials of one row block per block of four waves; wave w takes dim block w (d = 64: waves 0
+// and 1).  The lane layout is the kernel's own, so the loads are whole kilobytes; the splits are added in order.
+template <int D>
+__global__ __launch_bounds__(64 * (D / 32)) void attn_bf16_merge(Dims dm, AttnArgs a) {
+  constexpr int REC = AttnCfg<D, true>::kRecFloats;
+  const int lane = threadIdx.x & 63, c = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6);
+  const int li = lane & 31, hf = lane >> 5;
+  const int x = blockIdx.x, kv = blockIdx.y % dm.n_kv, b = blockIdx.y / dm.n_kv;
+  const float* rec = a.part + ((size_t)blockIdx.y * gridDim.x + x) * a.n_splits * REC;
+  float m = -INFINITY;
+  for (int s = 0; s < a.n_splits; ++s) m = fmaxf(m, rec[(size_t)s * REC + 32 * D + li]);
+  const float m_fin = m == -INFINITY ? 0.f : m;   // (rows past the chunk's end)
+  float l = 0.f;
+  float o[16];
+#pragma unroll
+  for (int v = 0; v < 16; ++v) o[v] = 0.f;
+#pragma unroll 2
+  for (int s = 0; s < a.n_splits; ++s) {
+    const float* p = rec + (size_t)s * REC;
+    const float wgt = __builtin_amdgcn_exp2f(p[32 * D + li] - m_fin);
+    l += wgt * p[32 * D + 32 + li];
+#pragma unroll
+    for (int v4 = 0; v4 < 4; ++v4) {
+      const float4 t = *reinterpret_cast<const float4*>(p + ((c * 4 + v4) * 64 + lane) * 4);
+      o[4 * v4] += wgt * t.x;
+      o[4 * v4 + 1] += wgt * t.y;
+      o[4 * v4 + 2] += wgt * t.z;
+      o[4 * v4 + 3] += wgt * t.w;
+    }
+  }
+  const int tok = (x / dm.g) * 32 + li, h = kv * dm.g + x % dm.g;
+  if (tok >= dm.C) return;
+  const float inv = 1.0f / l;
+  uint16_t* orow = static_cast<uint16_t*>(a.out) + b * dm.os[0] + h * dm.os[1] + (size_t)tok * dm.os[2];
+#pragma unroll
+  for (int v4 = 0; v4 < 4; ++v4) {
+    uint2 pk;
+    pk.x = f32_to_bf16_bits(o[4 * v4] * inv) | (f32_to_bf16_bits(o[4 * v4 + 1] * inv) << 16);
+    pk.y = f32_to_bf16_bits(o[4 * v4 + 2] * inv) | (f32_to_bf16_bits(o[4 * v4 + 3] * inv) << 16);
+    *reinterpret_cast<uint2*>(orow + 32 * c + 8 * v4 + 4 * hf) = pk;
+  }
+  if (a.lse != nullptr && hf == 0 && c == 0)
+    a.lse[(size_t)(b * dm.n_q + h) * dm.C + tok] = (m + log2f(l)) * 0.6931471805599453f;
+}
+
+template <int D, bool SPLIT, bool XS, bool KSPLIT>
+static hipError_t launch_variant(const Dims& dm, const AttnArgs& a, hipStream_t st) {
   using Cfg = AttnCfg<D, SPLIT>;
   constexpr size_t lds = Cfg::kLdsBytes;
   static std::atomic<uint64_t> lds_done{0};
-  const hipError_t e = ensure_dynamic_lds(reinterpret_cast<const void*>(&attn_bf16<D, SPLIT, XS>), lds, lds_done);
+  const hipError_t e =
+      ensure_dynamic_lds(reinterpret_cast<const void*>(&attn_bf16<D, SPLIT, XS, KSPLIT>), lds, lds_done);
   if (e != hipSuccess) return e;
   const int nrb = dm.g * ((dm.C + 31) / 32);
   const int half = (nrb + 1) / 2;
-  dim3 grid(dm.n_kv, (half + Cfg::HW - 1) / Cfg::HW, dm.b);
+  dim3 grid(dm.n_kv, (half + Cfg::HW - 1) / Cfg::HW * a.n_splits, dm.b);
   AttnArgs aa = a;
   // one block is resident per compute unit: from two rounds on, neighbouring row blocks and longest ranges first
   // (measured at 512 blocks, 4096-token chunk over 131072 cached tokens: 3.5 % faster than pairing; a launch of one
   // round needs the pairing, or its last block sets the time alone)
   aa.adjacent = (long long)grid.x * grid.y * grid.z >= 2 * kComputeUnits ? 1 : 0;
-  hipLaunchKernelGGL((attn_bf16<D, SPLIT, XS>), grid, dim3(2 * kSetThreads), lds, st, dm, aa);
+  hipLaunchKernelGGL((attn_bf16<D, SPLIT, XS, KSPLIT>), grid, dim3(2 * kSetThreads), lds, st, dm, aa);
+  if (KSPLIT) hipLaunchKernelGGL((attn_bf16_merge<D>), dim3(nrb, dm.b * dm.n_kv), dim3(64 * (D / 32)), 0, st, dm, aa);
   return hipGetLastError();
 }
 
 template <int D, bool SPLIT>
 static hipError_t launch_ds(const Dims& dm, const AttnArgs& a, hipStream_t st) {
-  if (dm.flags & QUOKA_ATTN_SCALE_F32) return launch_dsx<D, SPLIT, true>(dm, a, st);
-  return launch_dsx<D, SPLIT, false>(dm, a, st);
+  if (dm.flags & QUOKA_ATTN_SCALE_F32)
+    return a.n_splits > 1 ? launch_variant<D, SPLIT, true, true>(dm, a, st) : launch_variant<D, SPLIT, true, false>(dm, a, st);
+  return a.n_splits > 1 ? launch_variant<D, SPLIT, false, true>(dm, a, st) : launch_variant<D, SPLIT, false, false>(dm, a, st);
+}
+
+// ---- which variant: 8 row blocks per block or 4 (SPLIT), and over how many blocks the key list is split -----------
+constexpr int kMaxKeySplits = 32;
+constexpr long long kMaxRecords = 2048;   // partials of 32 rows (16.6 KiB each at d = 128)
+
+static int key_splits_limit(const Dims& dm, bool sparse, int keys_per_tile) {
+  const long long tiles = ((long long)(sparse ? dm.B_max : dm.T_max) + keys_per_tile - 1) / keys_per_tile +
+                          (dm.C + keys_per_tile - 1) / keys_per_tile;
+  return (int)(tiles < kMaxKeySplits ? tiles : kMaxKeySplits);
+}
+
+struct AttnPlan {
+  bool split_tile;
+  int n_splits;
+};
+// Few row blocks leave compute units idle whatever the tile mode; their key lists are split over blocks instead.
+// Measured (kernel and merge, unsplit -> split): 4 KV heads x 3 sequences, d 64, 333 tokens over 4999 keys (2 splits)
+// 60 -> 38 us; one KV head of 16 q-heads x 8 sequences, d 64, 69 tokens over 13477 keys (5 splits) 138 -> 65 us.
+// The cheapest of the variants by a model of the launch in microseconds: rounds of 256 resident blocks, each as long as
+// its share of the longest key list plus a fixed part, and for a split list the partials' traffic and the merge launch.
+static AttnPlan attn_plan(const Dims& dm, bool sparse) {
+  const long long nrb = (long long)dm.g * ((dm.C + 31) / 32), heads = (long long)dm.n_kv * dm.b;
+  const float step_us = dm.d == 128 ? 2.1f : 1.2f;   // a step is 8 row blocks x 64 keys or 4 x 128
+  AttnPlan best{false, 1};
+  float best_us = 0.f;
+  for (int mode = 0; mode < 2; ++mode) {
+    const int kt = mode == 0 ? kSub : 2 * kSub, per_block = mode == 0 ? 8 : 4;
+    const long long blocks = heads * ((nrb + per_block - 1) / per_block);
+    const int limit = key_splits_limit(dm, sparse, kt);
+    const long long tiles = ((long long)(sparse ? dm.B_max : dm.T_max) + kt - 1) / kt + (dm.C + kt - 1) / kt;
+    for (int n = 1; n <= limit; ++n) {
+      if (n > 1 && heads * nrb * n > kMaxRecords) break;
+      const long long rounds = (blocks * n + kComputeUnits - 1) / kComputeUnits, steps = (tiles + n - 1) / n;
+      float us = (float)rounds * ((float)steps * step_us + (mode == 0 ? 6.f : 8.f));
+      if (n > 1) us += 5.f + (float)(heads * nrb * n) * (float)(dm.d + 2) * (256.f / 4e6f);   // written and read at ~4 TB/s
+      if ((mode == 0 && n == 1) || us < best_us) {
+        best = AttnPlan{mode == 1, n};
+        best_us = us;
+      }
+    }
+  }
+  return best;
+}
+
+// Both factors of the first bound grow with the chunk length, so shorter chunks of the same shape fit as well.
+size_t attn_bf16_ws_floats(const Dims& dm) {
+  const long long nrb = (long long)dm.g * ((dm.C + 31) / 32), heads = (long long)dm.n_kv * dm.b;
+  const long long most = heads * nrb * key_splits_limit(dm, false, kSub);
+  return (size_t)(most < kMaxRecords ? most : kMaxRecords) * 32 * (dm.d + 2);
 }
 
 template <int D>
 static hipError_t launch_d(const Dims& dm, const AttnArgs& a, hipStream_t st) {
-  const int nrb = dm.g * ((dm.C + 31) / 32);
-  const long long blocks8 = (long long)dm.n_kv * (((nrb + 1) / 2 + 3) / 4) * dm.b;
-  // eight row blocks per block when that still gives every compute unit a block; otherwise four, with the keys of
-  // every tile split between the two wave sets
-  if (blocks8 >= kComputeUnits) return launch_ds<D, false>(dm, a, st);
-  return launch_ds<D, true>(dm, a, st);
+  const AttnPlan p = attn_plan(dm, a.k_idx != nullptr);
+  AttnArgs aa = a;
+  aa.n_splits = p.n_splits;
+  return p.split_tile ? launch_ds<D, true>(dm, aa, st) : launch_ds<D, false>(dm, aa, st);
 }
 
-hipError_t launch_attn_bf16(const Dims& dm, const AttnArgs& a, hipStream_t st) {
-  return dm.d == 64 ? launch_d<64>(dm, a, st) : launch_d<128>(dm, a, st);
+hipError_t launch_attn_bf16(const Dims& dm, const AttnArgs& a, float* part, hipStream_t st) {
+  AttnArgs aa = a;
+  aa.part = part;
+  return dm.d == 64 ? launch_d<64>(dm, aa, st) : launch_d<128>(dm, aa, st);
 }
 
 }  // namespace quoka

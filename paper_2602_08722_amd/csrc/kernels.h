@@ -64,9 +64,13 @@ struct AttnArgs {
   const int32_t* n_cache;  // k_cnt [b,n_kv] (sparse) or kv_lens [b] (dense)
   void* out;
   float* lse;              // may be nullptr
-  int adjacent = 0;        // set by the launcher: row-block assignment of the bf16 kernel (paired or adjacent)
+  // set by the launcher of the bf16 kernel:
+  int adjacent = 0;        // row-block assignment (paired or adjacent)
+  int n_splits = 1;        // blocks that share a row block's key list
+  float* part = nullptr;   // their partial results
 };
-hipError_t launch_attn_bf16(const Dims& dm, const AttnArgs& a, hipStream_t st);
+size_t attn_bf16_ws_floats(const Dims& dm);
+hipError_t launch_attn_bf16(const Dims& dm, const AttnArgs& a, float* part, hipStream_t st);
 // decode-sized chunks (g * C <= 32 query rows per KV head): split-KV kernel + merge, partials in `part`
 bool attn_decode_applies(const Dims& dm);
 size_t attn_decode_ws_floats(const Dims& dm);

@@ -84,3 +84,25 @@ def test_float32_scores_query_blocks_and_key_tails(n_retain, kv_len, d):
     got = gen.from_torch(buf.scores)[0]
     want = O.key_scores_preagg(qbar.astype(np.float64), w.K[0])
     assert not np.isnan(got).any() and P.max_abs(got, want) <= P.TOL_SCORE
+
+
+# bf16 prefill kernel with the key list split over blocks (few row blocks); the second sequence of a batch has fewer
+# tiles than there are splits, so some blocks get none
+BF16_SPLIT_CASES = [
+    dict(n_q=8, n_kv=2, d=128, chunk=9, kv_lens=[6000, 3], budgets=[1500, 3], batch=2),
+    dict(n_q=2, n_kv=1, d=64, chunk=33, kv_lens=[4097], budgets=[640]),
+    dict(n_q=7, n_kv=1, d=128, chunk=65, kv_lens=[2500], budgets=[2500]),
+    dict(n_q=2, n_kv=2, d=128, chunk=129, kv_lens=[1, 5000, 0], budgets=[1, 1100, 9], batch=3),
+]
+
+
+@pytest.mark.parametrize("scale_f32", [False, True], ids=["", "scale-f32"])
+@pytest.mark.parametrize("case", BF16_SPLIT_CASES, ids=_id)
+def test_bf16_attention_key_splits(case, scale_f32):
+    check_attention(dict(case, dtype="bf16"), score_flags=16 if scale_f32 else 0)
+
+
+def test_bf16_attention_key_splits_of_eight_row_blocks():
+    # 140 row groups of eight on 256 compute units: both tile modes and the split are in reach of the plan
+    check_attention(dict(dtype="bf16", n_q=8, n_kv=8, d=128, chunk=1341, kv_lens=[5000], budgets=[3000]),
+                    rows=[0, 1, 31, 32, 700, 1311, 1312, 1340])
