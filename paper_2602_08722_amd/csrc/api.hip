@@ -58,7 +58,7 @@ quoka_status check_shape(const quoka_shape* s, Dims* dm) {
   dm->g = s->n_q_heads / s->n_kv_heads;
   dm->d = s->head_dim;
   dm->C = s->chunk_len;
-  dm->T_max = s->max_kv_len;
+  dm->T_max = dm->T_cap = s->max_kv_len;
   dm->n_ret = s->n_retain;
   dm->B_max = s->max_budget;
   dm->flags = s->score_flags;
@@ -191,13 +191,15 @@ quoka_status quoka_topk_keys(const quoka_shape* shape, const float* scores, cons
       quoka::launch_topk_keys(dm, scores, kv_lens, budgets, k_idx, k_cnt, ws, static_cast<hipStream_t>(stream)));
 }
 
-static quoka_status attn_common(const quoka_shape* shape, const void* q, const void* k_cache, const void* v_cache,
-                                const int32_t* k_idx, const int32_t* n_cache, bool sparse, const void* k_chunk,
-                                const void* v_chunk, void* out, float* lse, void* workspace, size_t workspace_bytes,
-                                void* stream) {
+// `kv_cap`: no cache length of this call exceeds it (max_kv_len, or less where the caller knows more)
+static quoka_status attn_common(const quoka_shape* shape, int kv_cap, const void* q, const void* k_cache,
+                                const void* v_cache, const int32_t* k_idx, const int32_t* n_cache, bool sparse,
+                                const void* k_chunk, const void* v_chunk, void* out, float* lse, void* workspace,
+                                size_t workspace_bytes, void* stream) {
   Dims dm;
   quoka_status st = check_shape(shape, &dm);
   if (st != QUOKA_OK) return st;
+  dm.T_cap = kv_cap < dm.T_max ? kv_cap : dm.T_max;
   if (q == nullptr || k_chunk == nullptr || v_chunk == nullptr || out == nullptr || n_cache == nullptr)
     return QUOKA_EINVAL;
   const bool has_cache = sparse ? dm.B_max > 0 : dm.T_max > 0;
@@ -232,14 +234,14 @@ quoka_status quoka_sparse_attn(const quoka_shape* shape, const void* q, const vo
                                const int32_t* k_idx, const int32_t* k_cnt, const void* k_chunk,
                                const void* v_chunk, void* out, float* lse, void* workspace,
                                size_t workspace_bytes, void* stream) {
-  return attn_common(shape, q, k_cache, v_cache, k_idx, k_cnt, true, k_chunk, v_chunk, out, lse, workspace,
+  return attn_common(shape, kMaxKv, q, k_cache, v_cache, k_idx, k_cnt, true, k_chunk, v_chunk, out, lse, workspace,
                      workspace_bytes, stream);
 }
 
 quoka_status quoka_dense_attn(const quoka_shape* shape, const void* q, const void* k_cache, const void* v_cache,
                               const int32_t* kv_lens, const void* k_chunk, const void* v_chunk, void* out,
                               float* lse, void* workspace, size_t workspace_bytes, void* stream) {
-  return attn_common(shape, q, k_cache, v_cache, nullptr, kv_lens, false, k_chunk, v_chunk, out, lse, workspace,
+  return attn_common(shape, kMaxKv, q, k_cache, v_cache, nullptr, kv_lens, false, k_chunk, v_chunk, out, lse, workspace,
                      workspace_bytes, stream);
 }
 
@@ -255,10 +257,10 @@ static quoka_status select_keys_common(const Dims& dm, int dtype, const float* q
                                               sel_ws_is_zero));
   }
   uint32_t* topk_ws = reinterpret_cast<uint32_t*>(static_cast<char*>(workspace) + l.topk_off);
-  const size_t topk_words = quoka::topk_ws_words(dm);
-  const bool fuse_clear = dm.T_max > 0 && topk_words > 0;
+  const bool fuse_clear = quoka::topk_uses_ws(dm);
+  const size_t topk_words = fuse_clear ? quoka::topk_ws_words(dm) : 0;
   quoka_status st = from_hip(quoka::launch_score_keys(dm, dtype, qbar, k_cache, kv_lens, scores, hs,
-                                                      fuse_clear ? topk_ws : nullptr, fuse_clear ? topk_words : 0));
+                                                      fuse_clear ? topk_ws : nullptr, topk_words));
   if (st != QUOKA_OK) return st;
   return from_hip(quoka::launch_topk_keys(dm, scores, kv_lens, budgets, k_idx, k_cnt, topk_ws, hs, fuse_clear));
 }
@@ -280,16 +282,17 @@ quoka_status quoka_select_keys(const quoka_shape* shape, const float* qbar, cons
                             static_cast<hipStream_t>(stream), false);
 }
 
-quoka_status quoka_chunk_attn(const quoka_shape* shape, const void* q, const void* k_cache, const void* v_cache,
-                              const int32_t* kv_lens, const int32_t* budgets, const void* k_chunk,
-                              const void* v_chunk, int32_t* q_idx, float* qbar, float* scores, int32_t* k_idx,
-                              int32_t* k_cnt, void* out, float* lse, void* workspace, size_t workspace_bytes,
-                              void* stream) {
+static quoka_status chunk_common(const quoka_shape* shape, int kv_cap, const void* q, const void* k_cache,
+                                 const void* v_cache, const int32_t* kv_lens, const int32_t* budgets,
+                                 const void* k_chunk, const void* v_chunk, int32_t* q_idx, float* qbar, float* scores,
+                                 int32_t* k_idx, int32_t* k_cnt, void* out, float* lse, void* workspace,
+                                 size_t workspace_bytes, void* stream) {
   // The stages as in quoka_select_queries / quoka_select_keys (same checks), except that the last launch of the query
   // stage also clears the histograms and counters of the two-pass key selection, which saves that stage a launch.
   Dims dm;
   quoka_status st = check_shape(shape, &dm);
   if (st != QUOKA_OK) return st;
+  dm.T_cap = kv_cap < dm.T_max ? kv_cap : dm.T_max;
   if (q == nullptr || q_idx == nullptr || qbar == nullptr) return QUOKA_EINVAL;
   if (kv_lens == nullptr || budgets == nullptr || k_cnt == nullptr) return QUOKA_EINVAL;
   if (dm.T_max > 0 && (k_cache == nullptr || scores == nullptr)) return QUOKA_EINVAL;
@@ -308,8 +311,17 @@ quoka_status quoka_chunk_attn(const quoka_shape* shape, const void* q, const voi
   st = select_keys_common(dm, shape->dtype, qbar, k_cache, kv_lens, budgets, scores, k_idx, k_cnt, workspace, l, hs,
                           two_pass);
   if (st != QUOKA_OK) return st;
-  return quoka_sparse_attn(shape, q, k_cache, v_cache, k_idx, k_cnt, k_chunk, v_chunk, out, lse, workspace,
-                           workspace_bytes, stream);
+  return attn_common(shape, kv_cap, q, k_cache, v_cache, k_idx, k_cnt, true, k_chunk, v_chunk, out, lse, workspace,
+                     workspace_bytes, stream);
+}
+
+quoka_status quoka_chunk_attn(const quoka_shape* shape, const void* q, const void* k_cache, const void* v_cache,
+                              const int32_t* kv_lens, const int32_t* budgets, const void* k_chunk,
+                              const void* v_chunk, int32_t* q_idx, float* qbar, float* scores, int32_t* k_idx,
+                              int32_t* k_cnt, void* out, float* lse, void* workspace, size_t workspace_bytes,
+                              void* stream) {
+  return chunk_common(shape, kMaxKv, q, k_cache, v_cache, kv_lens, budgets, k_chunk, v_chunk, q_idx, qbar, scores, k_idx,
+                      k_cnt, out, lse, workspace, workspace_bytes, stream);
 }
 
 quoka_status quoka_prefill_attn(const quoka_shape* shape, int sparse, const void* q, const void* k, const void* v,
@@ -320,7 +332,11 @@ quoka_status quoka_prefill_attn(const quoka_shape* shape, int sparse, const void
   quoka_status st = check_shape(shape, &dm);
   if (st != QUOKA_OK) return st;
   if (q == nullptr || k == nullptr || v == nullptr || out == nullptr || kv_lens_all == nullptr) return QUOKA_EINVAL;
-  if (sparse && budgets_all == nullptr) return QUOKA_EINVAL;
+  if (sparse) {   // what the first chunk does not need but a later one does
+    if (budgets_all == nullptr || q_idx == nullptr || qbar == nullptr || scores == nullptr || k_cnt == nullptr)
+      return QUOKA_EINVAL;
+    if ((dm.B_max > 0 && k_idx == nullptr) || !aligned16(qbar)) return QUOKA_EINVAL;
+  }
   const int L = shape->max_kv_len, C = shape->chunk_len;
   if (L < 1) return QUOKA_EINVAL;
   const size_t es = shape->dtype == QUOKA_BF16 ? 2 : 4;
@@ -335,11 +351,13 @@ quoka_status quoka_prefill_attn(const quoka_shape* shape, int sparse, const void
     const char* vi = static_cast<const char*>(v) + tok * shape->kv_stride[2] * es;
     char* oi = static_cast<char*>(out) + tok * shape->o_stride[2] * es;
     const int32_t* lens = kv_lens_all + (size_t)i * shape->batch;
-    if (sparse) {
-      st = quoka_chunk_attn(&sh, qi, k, v, lens, budgets_all + (size_t)i * shape->batch, ki, vi, q_idx, qbar, scores,
-                            k_idx, k_cnt, oi, nullptr, workspace, workspace_bytes, stream);
+    // Chunk i's cache holds i * C rows: launches are sized for that, not for the prompt (16 chunks of 1024: 1307 ->
+    // 1222 us).  The first chunk has no cache to select from, and only the last chunk's intermediates are the caller's.
+    if (sparse && (i > 0 || n_chunks == 1)) {
+      st = chunk_common(&sh, i * C, qi, k, v, lens, budgets_all + (size_t)i * shape->batch, ki, vi, q_idx, qbar, scores,
+                        k_idx, k_cnt, oi, nullptr, workspace, workspace_bytes, stream);
     } else {
-      st = quoka_dense_attn(&sh, qi, k, v, lens, ki, vi, oi, nullptr, workspace, workspace_bytes, stream);
+      st = attn_common(&sh, i * C, qi, k, v, nullptr, lens, false, ki, vi, oi, nullptr, workspace, workspace_bytes, stream);
     }
     if (st != QUOKA_OK) return st;
   }

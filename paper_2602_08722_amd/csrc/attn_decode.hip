@@ -300,7 +300,7 @@ __global__ __launch_bounds__(kDcThreads) void attn_decode_merge(Dims dm, AttnArg
 bool attn_decode_applies(const Dims& dm) { return dm.C * dm.g <= 32; }
 
 static int decode_splits(const Dims& dm, bool sparse) {
-  const long long max_keys = (long long)(sparse ? dm.B_max : dm.T_max) + dm.C;
+  const long long max_keys = (long long)attended_cap(dm, sparse) + dm.C;
   const long long tiles = (max_keys + kDcTile - 1) / kDcTile;
   long long n = (tiles + 7) / 8;                                   // about eight tiles per split ...
   const long long fill = (256 + (long long)dm.b * dm.n_kv - 1) / ((long long)dm.b * dm.n_kv);
@@ -324,7 +324,7 @@ static hipError_t launch_decode_d(const Dims& dm, const AttnArgs& a, float* part
   if (e != hipSuccess) return e;
   const bool sparse = a.k_idx != nullptr;
   const int n_splits = decode_splits(dm, sparse);
-  const long long max_keys = (long long)(sparse ? dm.B_max : dm.T_max) + dm.C;
+  const long long max_keys = (long long)attended_cap(dm, sparse) + dm.C;
   int sps = (int)((max_keys + n_splits - 1) / n_splits);
   sps = (sps + kDcTile - 1) / kDcTile * kDcTile;
   hipLaunchKernelGGL((attn_decode_bf16<D>), dim3(n_splits, dm.n_kv, dm.b), dim3(kDcThreads), Cfg::kLdsBytes, st, dm, a,

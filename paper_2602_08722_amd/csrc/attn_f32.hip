@@ -287,7 +287,7 @@ __global__ __launch_bounds__(256) void attn_f32_merge(Dims dm, AttnArgs a, const
 // of a block (a split costs 16 KiB of partials and a share of the merge launch).
 static long long f32_blocks(const Dims& dm) { return (long long)dm.b * dm.n_kv * ((dm.C * dm.g + 31) / 32); }
 static int f32_most_splits(const Dims& dm, bool sparse) {
-  const long long units = ((long long)(sparse ? dm.B_max : dm.T_max) + 31) / 32 + (dm.C + 31) / 32;
+  const long long units = ((long long)attended_cap(dm, sparse) + 31) / 32 + (dm.C + 31) / 32;
   const long long n = (units + kFaWaves - 1) / kFaWaves;
   return (int)(n > kFaMaxSplits ? kFaMaxSplits : n);
 }

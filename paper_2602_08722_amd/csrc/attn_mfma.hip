@@ -552,7 +552,7 @@ constexpr int kMaxKeySplits = 32;
 constexpr long long kMaxRecords = 2048;   // partials of 32 rows (16.6 KiB each at d = 128)
 
 static int key_splits_limit(const Dims& dm, bool sparse, int keys_per_tile) {
-  const long long tiles = ((long long)(sparse ? dm.B_max : dm.T_max) + keys_per_tile - 1) / keys_per_tile +
+  const long long tiles = ((long long)attended_cap(dm, sparse) + keys_per_tile - 1) / keys_per_tile +
                           (dm.C + keys_per_tile - 1) / keys_per_tile;
   return (int)(tiles < kMaxKeySplits ? tiles : kMaxKeySplits);
 }
@@ -575,7 +575,7 @@ static AttnPlan attn_plan(const Dims& dm, bool sparse) {
     const int kt = mode == 0 ? kSub : 2 * kSub, per_block = mode == 0 ? 8 : 4;
     const long long blocks = heads * ((nrb + per_block - 1) / per_block);
     const int limit = key_splits_limit(dm, sparse, kt);
-    const long long tiles = ((long long)(sparse ? dm.B_max : dm.T_max) + kt - 1) / kt + (dm.C + kt - 1) / kt;
+    const long long tiles = ((long long)attended_cap(dm, sparse) + kt - 1) / kt + (dm.C + kt - 1) / kt;
     for (int n = 1; n <= limit; ++n) {
       if (n > 1 && heads * nrb * n > kMaxRecords) break;
       const long long rounds = (blocks * n + kComputeUnits - 1) / kComputeUnits, steps = (tiles + n - 1) / n;

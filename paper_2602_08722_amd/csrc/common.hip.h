@@ -17,6 +17,8 @@ typedef uint32_t u32x4 __attribute__((ext_vector_type(4)));
 // Kernel-side view of quoka_shape (plain copy; passed by value).
 struct Dims {
   int b, n_q, n_kv, g, d, C, T_max, n_ret, B_max;
+  int T_cap;   // no cache length of this call exceeds it (<= T_max; smaller inside a prompt's early chunks): sizes grids
+               // and picks variants, while T_max stays the extent of the tensors
   int flags;   // QUOKA_SCORE_* bits
   long long qs[3], kvs[3], cks[3], os[3];
 };

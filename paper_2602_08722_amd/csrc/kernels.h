@@ -39,6 +39,7 @@ hipError_t launch_score_keys(const Dims& dm, int dtype, const float* qbar, const
 
 // --- top-B key selection (topk_keys.hip) ----------------------------------------------------------
 size_t topk_ws_words(const Dims& dm);
+bool topk_uses_ws(const Dims& dm);   // whether a launch with these sizes takes the multi-block path
 // `ws_is_zero`: the workspace words (topk_ws_words) have already been cleared on this stream.
 hipError_t launch_topk_keys(const Dims& dm, const float* scores, const int32_t* kv_lens, const int32_t* budgets,
                             int32_t* k_idx, int32_t* k_cnt, uint32_t* ws, hipStream_t st, bool ws_is_zero = false);
@@ -69,6 +70,8 @@ struct AttnArgs {
   int n_splits = 1;        // blocks that share a row block's key list
   float* part = nullptr;   // their partial results
 };
+// the most cache rows any sequence of the call attends
+inline int attended_cap(const Dims& dm, bool sparse) { return sparse && dm.B_max < dm.T_cap ? dm.B_max : dm.T_cap; }
 size_t attn_bf16_ws_floats(const Dims& dm);
 hipError_t launch_attn_bf16(const Dims& dm, const AttnArgs& a, float* part, hipStream_t st);
 // decode-sized chunks (g * C <= 32 query rows per KV head): split-KV kernel + merge, partials in `part`

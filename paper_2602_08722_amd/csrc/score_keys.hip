@@ -60,7 +60,7 @@ __global__ __launch_bounds__(kScThreads, 2) void score_bf16(Dims dm, const float
     }
   };
   issue(0, RA);   // the first K tile is in flight while the length arrives and the query operands are prepared
-  const int T = min(kv_lens[b], dm.T_max);
+  const int T = min(kv_lens[b], dm.T_cap);
   if (t_begin >= T) return;  // block-uniform
   const int n_tiles = min(tiles_per_wg, (T - t_begin + kScTile - 1) / kScTile);
   if (n_tiles > 1) issue(1, RB);
@@ -139,7 +139,7 @@ __global__ __launch_bounds__(kScThreads) void score_f32(Dims dm, const float* __
   };
   int t0 = blockIdx.x * KPB;
   load_k(t0);
-  const int T = min(kv_lens[b], dm.T_max);
+  const int T = min(kv_lens[b], dm.T_cap);
   if (t0 >= T) return;   // block-uniform
   // query operand: row qb*32 + li (rows past n_keep repeat a real query, or are zero where a mean is taken)
   f32x4 qreg[NI];
@@ -196,7 +196,7 @@ static void launch_f32_d(const Dims& dm, const float* qbar, const float* kc, con
   const int qblocks = n_keep <= 32 ? 1 : (n_keep <= 64 ? 2 : 4);
   const int keys = 32 * (4 / qblocks);
   // one step per block up to four blocks a compute unit; longer caches keep the query operand over several steps
-  int gx = (dm.T_max + keys - 1) / keys;
+  int gx = (dm.T_cap + keys - 1) / keys;
   const int most = (1024 + dm.b * dm.n_kv - 1) / (dm.b * dm.n_kv);
   gx = gx < most ? gx : most;
   const dim3 grid(gx, dm.n_kv, dm.b);
@@ -221,7 +221,7 @@ static hipError_t launch_bf16(const Dims& dm, const float* qbar, const void* kc,
   const hipError_t e =
       ensure_dynamic_lds(reinterpret_cast<const void*>(&score_bf16<D, QB, EXACT>), Cfg::kLdsBytes, lds_done);
   if (e != hipSuccess) return e;
-  const int nt = (dm.T_max + kScTile - 1) / kScTile;
+  const int nt = (dm.T_cap + kScTile - 1) / kScTile;
   const int heads = dm.b * dm.n_kv;
   // two blocks per compute unit are resident at once: aim for one round of 512 blocks, so the query operands
   // (prepared once per block) are amortised over as many tiles as the launch allows
@@ -250,7 +250,7 @@ static hipError_t launch_bf16_d(const Dims& dm, const float* qbar, const void* k
 
 hipError_t launch_score_keys(const Dims& dm, int dtype, const float* qbar, const void* k_cache, const int32_t* kv_lens,
                              float* scores, hipStream_t st, uint32_t* zero, size_t zero_words_sz) {
-  if (dm.T_max <= 0) return hipSuccess;   // (then the top-k that follows takes no workspace either)
+  if (dm.T_cap <= 0) return hipSuccess;   // (then the top-k that follows takes no workspace either)
   const uint32_t zero_words = (uint32_t)zero_words_sz;
   const int n_keep = dm.n_ret < dm.C ? dm.n_ret : dm.C;
   if (dtype == QUOKA_BF16) {

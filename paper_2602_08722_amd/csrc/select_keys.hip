@@ -33,7 +33,7 @@ struct SelCtx {
 __device__ __forceinline__ SelCtx sel_ctx(const Dims& dm, float* scores, const int32_t* kv_lens,
                                           const int32_t* budgets, uint32_t* ws, int kv, int b) {
   SelCtx c;
-  c.T = max(0, min(kv_lens[b], dm.T_max));
+  c.T = max(0, min(kv_lens[b], dm.T_cap));
   c.B = max(0, min(min(budgets[b], c.T), dm.B_max));
   c.head = b * dm.n_kv + kv;
   c.sc = scores + (size_t)c.head * dm.T_max;
@@ -414,7 +414,7 @@ __global__ __launch_bounds__(kSelThreads) void sel_emit(Dims dm, float* __restri
 bool select_keys_two_pass_applies(const Dims& dm, int dtype) {
   // the error bound of the provisional pass is uniform only for cosine scores reduced by max; short caches take one
   // single-block top-k launch after the exact scores, which the longer chain of this stage cannot beat
-  return dtype == QUOKA_BF16 && dm.T_max > 32768 &&
+  return dtype == QUOKA_BF16 && dm.T_cap > 32768 &&
          (dm.flags & (QUOKA_SCORE_DOT | QUOKA_SCORE_MEAN | QUOKA_SCORE_QBAR_BF16)) == 0;
 }
 
@@ -430,7 +430,7 @@ static void launch_rescore(const Dims& dm, const float* qbar, const void* kc, co
                            const int32_t* budgets, float* scores, uint32_t* ws, int n_keep, hipStream_t st) {
   // one round of two blocks per compute unit: fewer, fatter blocks amortise the histogram scan and the query operands
   // (mixed-length batch of 8 x 8 heads: 37 us with 512 blocks, 41 with 1024, 49 with 2048)
-  const int heads = dm.b * dm.n_kv, nt = sel_tiles(dm.T_max);
+  const int heads = dm.b * dm.n_kv, nt = sel_tiles(dm.T_cap);
   const int per_head = (512 + heads - 1) / heads;
   const int tpb = (nt + per_head - 1) / per_head;
   const dim3 grid((nt + tpb - 1) / tpb, dm.n_kv, dm.b);
@@ -456,7 +456,7 @@ hipError_t launch_select_keys(const Dims& dm, const float* qbar, const void* k_c
   // provisional scores and their histogram in one streaming launch
   hipError_t e = launch_score_stream(dm, qbar, k_cache, kv_lens, scores, ws, st);
   if (e != hipSuccess) return e;
-  const dim3 grid(sel_tiles(dm.T_max), dm.n_kv, dm.b);
+  const dim3 grid(sel_tiles(dm.T_cap), dm.n_kv, dm.b);
   if (dm.d == 64) {
     launch_rescore<64>(dm, qbar, k_cache, kv_lens, budgets, scores, ws, n_keep, st);
   } else {

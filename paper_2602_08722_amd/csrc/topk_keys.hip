@@ -47,8 +47,8 @@ __global__ __launch_bounds__(kSmallThreads) void topk_small(Dims dm, const float
   // are discarded below), so the two fetches overlap instead of queueing behind each other.
   float raw[IPT];
 #pragma unroll
-  for (int j = 0; j < IPT; ++j) raw[j] = lo + 64 * j < dm.T_max ? sc[lo + 64 * j] : 0.f;
-  const int T = max(0, min(kv_lens[b], dm.T_max));
+  for (int j = 0; j < IPT; ++j) raw[j] = lo + 64 * j < dm.T_cap ? sc[lo + 64 * j] : 0.f;
+  const int T = max(0, min(kv_lens[b], dm.T_cap));
   const int B = max(0, min(min(budgets[b], T), dm.B_max));
   int32_t* out = k_idx + (size_t)(b * dm.n_kv + kv) * dm.B_max;
   if (tid == 0) k_cnt[b * dm.n_kv + kv] = B;
@@ -186,7 +186,7 @@ __device__ __forceinline__ LgCtx lg_ctx(const Dims& dm, const float* scores, con
                                         const int32_t* budgets, uint32_t* ws, int n_tiles) {
   const int kv = blockIdx.y, b = blockIdx.z;
   LgCtx c;
-  c.T = max(0, min(kv_lens[b], dm.T_max));
+  c.T = max(0, min(kv_lens[b], dm.T_cap));
   c.B = max(0, min(min(budgets[b], c.T), dm.B_max));
   const size_t head = (size_t)(b * dm.n_kv + kv);
   c.sc = scores + head * dm.T_max;
@@ -319,11 +319,13 @@ size_t topk_ws_words(const Dims& dm) {
   return (size_t)dm.b * dm.n_kv * (3 * (size_t)kBins + kCutWords + 2 * (size_t)lg_tiles(dm));
 }
 
+bool topk_uses_ws(const Dims& dm) { return dm.T_cap > kSmallMax; }
+
 hipError_t launch_topk_keys(const Dims& dm, const float* scores, const int32_t* kv_lens, const int32_t* budgets,
                             int32_t* k_idx, int32_t* k_cnt, uint32_t* ws, hipStream_t st, bool ws_is_zero) {
-  if (dm.T_max <= kSmallMax) {
+  if (!topk_uses_ws(dm)) {
     const dim3 grid(dm.n_kv, dm.b), block(kSmallThreads);
-    const int ipt = (dm.T_max + kSmallThreads - 1) / kSmallThreads;
+    const int ipt = (dm.T_cap + kSmallThreads - 1) / kSmallThreads;
     if (ipt <= 1) {
       hipLaunchKernelGGL((topk_small<1>), grid, block, 0, st, dm, scores, kv_lens, budgets, k_idx, k_cnt);
     } else if (ipt <= 2) {
@@ -342,7 +344,7 @@ hipError_t launch_topk_keys(const Dims& dm, const float* scores, const int32_t* 
   const int n_tiles = lg_tiles(dm);
   const size_t words = topk_ws_words(dm);
   if (!ws_is_zero) hipLaunchKernelGGL(topk_zero, dim3(256), dim3(256), 0, st, ws, words);
-  dim3 grid(n_tiles, dm.n_kv, dm.b);
+  dim3 grid((dm.T_cap + kLgTile - 1) / kLgTile, dm.n_kv, dm.b);
   hipLaunchKernelGGL((topk_hist<0>), grid, dim3(kLgThreads), 0, st, dm, scores, kv_lens, budgets, ws, n_tiles);
   hipLaunchKernelGGL((topk_hist<1>), grid, dim3(kLgThreads), 0, st, dm, scores, kv_lens, budgets, ws, n_tiles);
   hipLaunchKernelGGL((topk_hist<2>), grid, dim3(kLgThreads), 0, st, dm, scores, kv_lens, budgets, ws, n_tiles);
