@@ -6,8 +6,16 @@
 //
 // Rows: row r = c * g + j is chunk token c of q-head kv * g + j.  Keys: list slot n < n_cache is a cache row
 // (k_idx[n] on the sparse path, n itself on the dense path), slot n_cache + p is chunk row p, visible to token c
-// iff p <= c.  A tile is 128 list slots; wave w of the block takes slots 32 w .. 32 w + 31 of every tile of the
-// block's range and keeps its own running (m, l, O), merged through LDS at the end of the block.
+// iff p <= c.
+//
+// Bound by memory: every row of K and V is used once, by one wave.  So a wave works by itself -- it fetches 32 slots at a
+// time (index two tiles ahead, rows one tile ahead, whole rows by 16 lanes), turns them in its own piece of LDS and needs
+// no barrier until its block's four waves are merged at the end -- and two blocks share a compute unit, which keeps
+// 128 KiB of rows on the way.  The key list of a sequence is cut in proportion to its length, so the blocks of a ragged
+// batch take equally long.
+// Measured (kernel without the merge launch; 128-slot tiles that a block staged together, index and row fetched in turn,
+// equal numbers of blocks per sequence -> now): 8 sequences x 8 heads, 12 % of 13000 - 65536 tokens, 157 MB: 77 -> 37 us;
+// one sequence, 983 keys: 10.1 -> 6.1 us.
 // MFMA operand plan as in the prefill kernel: S^T = K Q^T (query rows on lanes), O^T += V^T P^T with V^T fetched
 // by the transposing LDS read.
 #include "common.hip.h"
@@ -20,51 +28,102 @@ typedef short s16x8 __attribute__((ext_vector_type(8)));
 typedef __bf16 bf16x2 __attribute__((ext_vector_type(2)));
 typedef s16x4 __attribute__((address_space(3))) * tr_ptr;
 
-constexpr int kDcThreads = 256;
-constexpr int kDcTile = 128;   // list slots per staged tile (32 per wave)
+constexpr int kDcWaves = 4;
+constexpr int kDcThreads = 64 * kDcWaves;
+constexpr int kDcTile = 32;       // list slots a wave handles at a time
+constexpr int kMaxSplits = 64;    // blocks per (sequence, KV head)
 
 template <int D>
 struct DecodeCfg {
   static constexpr int KS = D / 16;
   static constexpr int LD = D + 8;        // K rows: 16 bytes of padding (conflict-free b128 reads)
   static constexpr int LDV = D + 32;      // V rows: 64 bytes apart modulo 256 (transposing reads)
-  static constexpr int CG = D / 8;
-  static constexpr int RPI = kDcThreads / CG;
+  static constexpr int CG = D / 8;        // lanes per row (16 bytes each)
+  static constexpr int RPI = 64 / CG;     // rows per wave-wide load
   static constexpr int NLD = kDcTile / RPI;
   static constexpr int DB = D / 32;
   static constexpr size_t kKBytes = (size_t)kDcTile * LD * 2;
-  static constexpr size_t kStageBytes = kKBytes + (size_t)kDcTile * LDV * 2;
-  static constexpr size_t kLdsBytes = 2 * kStageBytes;
+  static constexpr size_t kWaveBytes = kKBytes + (size_t)kDcTile * LDV * 2;
   static constexpr int REC = 2 + D;       // floats per row of a partial: m, l, O[D]
+  static constexpr size_t kMergeBytes = (size_t)kDcWaves * 32 * REC * 4;
+  static constexpr size_t kLdsBytes = kDcWaves * kWaveBytes > kMergeBytes ? kDcWaves * kWaveBytes : kMergeBytes;
 };
 
-// part: [b, n_kv, n_splits, 32 rows, REC] float32
+// The blocks of one KV head, `n_slots` of them, over the sequences: sequence b gets 1 + floor(share * (n_slots - batch))
+// of them, share its part of all tiles (never more than there are tiles for four waves each; more than 64 sequences:
+// an equal number each).  Every wave works it out for itself; all lanes return the same.
+struct DecodeShare {
+  int n_splits;   // of sequence b
+  int first;      // its first slot
+};
+struct DecodeWork {
+  int b, split, n_splits;   // b < 0: nothing to do
+};
+__device__ __forceinline__ int decode_cache(const Dims& dm, const AttnArgs& a, int b, int kv) {
+  const int n = a.k_idx != nullptr ? min(a.n_cache[b * dm.n_kv + kv], dm.B_max) : min(a.n_cache[b], dm.T_max);
+  return max(n, 0);
+}
+__device__ __forceinline__ int decode_tiles(const Dims& dm, const AttnArgs& a, int b, int kv) {
+  return (decode_cache(dm, a, b, kv) + dm.C + kDcTile - 1) / kDcTile;
+}
+// lane i of the wave: the splits of sequence i, and the sum over the earlier ones in *before
+__device__ __forceinline__ uint32_t decode_lane_splits(const Dims& dm, const AttnArgs& a, int kv, int n_slots,
+                                                       uint32_t* before) {
+  const int lane = threadIdx.x & 63;
+  const uint32_t tiles = lane < dm.b ? (uint32_t)decode_tiles(dm, a, lane, kv) : 0u;
+  const uint32_t total = (uint32_t)__builtin_amdgcn_readlane((int)wave_incl_scan_u32(tiles), 63);
+  uint32_t n = lane < dm.b ? 1u + (uint32_t)((unsigned long long)tiles * (uint32_t)(n_slots - dm.b) / total) : 0u;
+  n = min(n, max((tiles + kDcWaves - 1) / kDcWaves, lane < dm.b ? 1u : 0u));
+  n = min(n, (uint32_t)kMaxSplits);
+  *before = wave_incl_scan_u32(n) - n;
+  return n;
+}
+__device__ __forceinline__ DecodeShare decode_share(const Dims& dm, const AttnArgs& a, int b, int kv, int n_slots) {
+  if (dm.b > 64) return {n_slots / dm.b, b * (n_slots / dm.b)};
+  uint32_t before;
+  const uint32_t n = decode_lane_splits(dm, a, kv, n_slots, &before);
+  return {__builtin_amdgcn_readlane((int)n, b), __builtin_amdgcn_readlane((int)before, b)};
+}
+__device__ __forceinline__ DecodeWork decode_work(const Dims& dm, const AttnArgs& a, int slot, int kv, int n_slots) {
+  if (dm.b == 1) {
+    const DecodeShare s = decode_share(dm, a, 0, kv, n_slots);
+    return {slot < s.n_splits ? 0 : -1, slot, s.n_splits};
+  }
+  if (dm.b > 64) {
+    const int n = n_slots / dm.b;
+    return {slot < n * dm.b ? slot / n : -1, slot % n, n};
+  }
+  uint32_t before;
+  const uint32_t n = decode_lane_splits(dm, a, kv, n_slots, &before);
+  const unsigned long long mine = __builtin_amdgcn_ballot_w64((uint32_t)slot >= before && (uint32_t)slot < before + n);
+  if (mine == 0) return {-1, 0, 0};
+  const int b = (int)__builtin_ctzll(mine);
+  return {b, slot - __builtin_amdgcn_readlane((int)before, b), __builtin_amdgcn_readlane((int)n, b)};
+}
+
+// part: [n_kv, n_slots, 32 rows, REC] float32
 template <int D>
 __global__ __launch_bounds__(kDcThreads, 2) void attn_decode_bf16(Dims dm, AttnArgs a, float* __restrict__ part,
-                                                                  int n_splits, int slots_per_split) {
+                                                                  int n_slots) {
   using Cfg = DecodeCfg<D>;
   constexpr int KS = Cfg::KS, LD = Cfg::LD, LDV = Cfg::LDV, CG = Cfg::CG, RPI = Cfg::RPI, NLD = Cfg::NLD, DB = Cfg::DB,
                 REC = Cfg::REC;
   extern __shared__ __align__(16) unsigned char smem[];
-  const int split = blockIdx.x, kv = blockIdx.y, b = blockIdx.z;
+  const int kv = blockIdx.y;
   const int tid = threadIdx.x, lane = tid & 63;
   const int w = __builtin_amdgcn_readfirstlane(tid >> 6);
   const int li = lane & 31, hf = lane >> 5;
   const int C = dm.C, g = dm.g;
   const int n_rows = C * g;   // <= 32, checked by the launcher
-
   const bool sparse = a.k_idx != nullptr;
-  int n_cache = sparse ? min(a.n_cache[b * dm.n_kv + kv], dm.B_max) : min(a.n_cache[b], dm.T_max);
-  n_cache = max(n_cache, 0);
+  const DecodeWork work = decode_work(dm, a, blockIdx.x, kv, n_slots);
+  if (work.b < 0) return;   // block-uniform
+  const int b = work.b;
+  const int n_cache = decode_cache(dm, a, b, kv);
   const int n_keys = n_cache + C;
-  const int s_begin = split * slots_per_split;
-  const int s_end = min(s_begin + slots_per_split, n_keys);
-  float* my_part = part + ((size_t)(b * dm.n_kv + kv) * n_splits + split) * 32 * REC;
-  if (s_begin >= s_end) {   // block-uniform: an empty range contributes the neutral partial
-    for (int i = tid; i < 32 * REC; i += kDcThreads) my_part[i] = (i % REC == 0) ? -INFINITY : 0.f;
-    return;
-  }
-  const int n_tiles = (s_end - s_begin + kDcTile - 1) / kDcTile;
+  const int tiles = (n_keys + kDcTile - 1) / kDcTile;
+  const int t_end = (int)((long long)tiles * (work.split + 1) / work.n_splits);
+  int t = (int)((long long)tiles * work.split / work.n_splits) + w;   // this wave's tiles: every fourth
 
   const char* kcache = reinterpret_cast<const char*>(static_cast<const uint16_t*>(a.k_cache) + b * dm.kvs[0] + kv * dm.kvs[1]);
   const char* vcache = reinterpret_cast<const char*>(static_cast<const uint16_t*>(a.v_cache) + b * dm.kvs[0] + kv * dm.kvs[1]);
@@ -75,6 +134,37 @@ __global__ __launch_bounds__(kDcThreads, 2) void attn_decode_bf16(Dims dm, AttnA
   const uint64_t k_cache_u = reinterpret_cast<uint64_t>(kcache), v_cache_u = reinterpret_cast<uint64_t>(vcache);
   const uint64_t k_chunk_delta = reinterpret_cast<uint64_t>(kchunk) - k_cache_u;   // modulo 2^64
   const uint64_t v_chunk_delta = reinterpret_cast<uint64_t>(vchunk) - v_cache_u;
+
+  const int cg = lane % CG, r0 = lane / CG;
+  uint32_t src[NLD];        // list entries of the tile whose rows are fetched next
+  u32x4 RK[NLD], RV[NLD];   // rows on the way
+  auto resolve = [&](int tt) __attribute__((always_inline)) {
+#pragma unroll
+    for (int i = 0; i < NLD; ++i) {
+      const int n = min(tt * kDcTile + r0 + RPI * i, n_keys - 1);   // tail slots repeat a real row; they are masked below
+      src[i] = (uint32_t)n;
+      if (sparse && n < n_cache) src[i] = (uint32_t)kidx[n];
+    }
+  };
+  auto issue = [&](int tt) __attribute__((always_inline)) {
+#pragma unroll
+    for (int i = 0; i < NLD; ++i) {
+      // addresses as integers (cache base, plus the distance to the chunk tensor for chunk rows): a per-lane choice
+      // between two pointers would be kept as a table in scratch memory
+      const int n = min(tt * kDcTile + r0 + RPI * i, n_keys - 1);
+      const bool from_cache = n < n_cache;
+      // (the clamp: a malformed list cannot leave the cache)
+      const uint32_t row = from_cache ? min(src[i], (uint32_t)(dm.T_max - 1)) : (uint32_t)(n - n_cache);
+      const uint64_t off = (uint64_t)(row * (from_cache ? cache_row_bytes : chunk_row_bytes) + (uint32_t)cg * 16u);
+      RK[i] = *reinterpret_cast<const u32x4*>(k_cache_u + (from_cache ? 0ull : k_chunk_delta) + off);
+      RV[i] = *reinterpret_cast<const u32x4*>(v_cache_u + (from_cache ? 0ull : v_chunk_delta) + off);
+    }
+  };
+  if (t < t_end) {
+    resolve(t);
+    issue(t);
+    if (t + kDcWaves < t_end) resolve(t + kDcWaves);
+  }
 
   // Q operand: row li -> (token li / g, head li % g); padding rows repeat row 0 and are never stored
   const int row = li < n_rows ? li : 0;
@@ -87,32 +177,6 @@ __global__ __launch_bounds__(kDcThreads, 2) void attn_decode_bf16(Dims dm, AttnA
     for (int ks = 0; ks < KS; ++ks) qreg[ks] = *reinterpret_cast<const bf16x8*>(qrow + ks * 16);
   }
 
-  const int cg = tid % CG, r0 = tid / CG;
-  u32x4 RK[NLD], RV[NLD];
-  // all rows of a tile are requested together: indices first (one latency), then the rows (one latency)
-  auto issue = [&](int t) __attribute__((always_inline)) {
-    const int base = s_begin + t * kDcTile;
-    // addresses as integers (cache base, plus the distance to the chunk tensor for chunk rows): a per-lane choice
-    // between two pointers would be kept as a table in scratch memory
-    uint64_t ka[NLD], va[NLD];
-#pragma unroll
-    for (int i = 0; i < NLD; ++i) {
-      const int n = min(base + r0 + RPI * i, s_end - 1);   // tail slots repeat a real row; they are masked below
-      const bool from_cache = n < n_cache;
-      int src = from_cache ? n : n - n_cache;
-      if (from_cache && sparse) src = (int)min((uint32_t)kidx[n], (uint32_t)(dm.T_max - 1));   // a malformed list cannot leave the cache
-      const uint64_t off = (uint64_t)((uint32_t)src * (from_cache ? cache_row_bytes : chunk_row_bytes) + (uint32_t)cg * 16u);
-      ka[i] = k_cache_u + (from_cache ? 0ull : k_chunk_delta) + off;
-      va[i] = v_cache_u + (from_cache ? 0ull : v_chunk_delta) + off;
-    }
-#pragma unroll
-    for (int i = 0; i < NLD; ++i) {
-      RK[i] = *reinterpret_cast<const u32x4*>(ka[i]);
-      RV[i] = *reinterpret_cast<const u32x4*>(va[i]);
-    }
-  };
-  issue(0);
-
   f32x16 o[DB];
 #pragma unroll
   for (int c = 0; c < DB; ++c)
@@ -120,36 +184,38 @@ __global__ __launch_bounds__(kDcThreads, 2) void attn_decode_bf16(Dims dm, AttnA
     for (int v = 0; v < 16; ++v) o[c][v] = 0.f;
   float m_run = -INFINITY, l_run = 0.f;
   const float sl2 = 1.4426950408889634f / sqrtf((float)D);
+  uint16_t* kt = reinterpret_cast<uint16_t*>(smem + (size_t)w * Cfg::kWaveBytes);
+  uint16_t* vt = reinterpret_cast<uint16_t*>(smem + (size_t)w * Cfg::kWaveBytes + Cfg::kKBytes);
 
-  for (int t = 0; t < n_tiles; ++t) {
-    uint16_t* kt = reinterpret_cast<uint16_t*>(smem + (size_t)(t & 1) * Cfg::kStageBytes);
-    uint16_t* vt = reinterpret_cast<uint16_t*>(smem + (size_t)(t & 1) * Cfg::kStageBytes + Cfg::kKBytes);
+  for (; t < t_end; t += kDcWaves) {
+    // (this wave's own piece of LDS: its accesses stay in order, no barrier)
 #pragma unroll
     for (int i = 0; i < NLD; ++i) {
       const int rl = r0 + RPI * i;
       *reinterpret_cast<u32x4*>(kt + rl * LD + cg * 8) = RK[i];
       *reinterpret_cast<u32x4*>(vt + rl * LDV + cg * 8) = RV[i];
     }
-    __syncthreads();   // tile t visible; the other stage was last read before the previous barrier
-    if (t + 1 < n_tiles) issue(t + 1);
-
-    const int slot0 = s_begin + t * kDcTile + w * 32;   // this wave's 32 slots
-    if (slot0 >= s_end) continue;                       // wave-uniform
+    __builtin_amdgcn_wave_barrier();
+    if (t + kDcWaves < t_end) {
+      issue(t + kDcWaves);
+      if (t + 2 * kDcWaves < t_end) resolve(t + 2 * kDcWaves);
+    }
+    const int slot0 = t * kDcTile;
     // ---- S^T = K Q^T ----
     f32x16 s;
 #pragma unroll
     for (int v = 0; v < 16; ++v) s[v] = 0.f;
-    const uint16_t* kp = kt + (w * 32 + li) * LD + 8 * hf;
+    const uint16_t* kp = kt + li * LD + 8 * hf;
 #pragma unroll
     for (int ks = 0; ks < KS; ++ks) {
       const bf16x8 kop = *reinterpret_cast<const bf16x8*>(kp + ks * 16);
       s = __builtin_amdgcn_mfma_f32_32x32x16_bf16(kop, qreg[ks], s, 0, 0, 0);
     }
-    // ---- mask: slots past the range; chunk rows in the token's future ----
-    // slot n is visible iff n < s_end and (it is a cache slot or its chunk position n - n_cache is <= tok),
-    // i.e. iff n < min(s_end, n_cache + tok + 1): one lane-private limit, as in the prefill kernel
-    const int limit = min(s_end, n_cache + tok + 1) - slot0;   // keys kk < limit of this wave's 32 are visible
-    if (slot0 + 32 > min(s_end, n_cache)) {   // wave-uniform: the block of 32 touches the tail or the chunk rows
+    // ---- mask: slots past the list; chunk rows in the token's future ----
+    // slot n is visible iff it is a cache slot or its chunk position n - n_cache is <= tok, i.e. iff
+    // n < n_cache + tok + 1: one lane-private limit, as in the prefill kernel
+    const int limit = n_cache + tok + 1 - slot0;   // keys kk < limit of the tile are visible
+    if (slot0 + kDcTile > n_cache) {   // wave-uniform: the tile touches the chunk rows or the end
 #pragma unroll
       for (int v = 0; v < 16; ++v) {
         const int kk = 8 * (v / 4) + 4 * hf + (v % 4);
@@ -178,7 +244,7 @@ __global__ __launch_bounds__(kDcThreads, 2) void attn_decode_bf16(Dims dm, AttnA
 #pragma unroll
     for (int v = 0; v < 16; ++v) s[v] = __builtin_amdgcn_exp2f(fmaf(s[v], sl2, -m_use));
     // ---- O^T += V^T P^T ----
-    const tr_ptr vtr = (tr_ptr)(vt + (w * 32 + 4 * hf + ((lane & 15) >> 2)) * LDV + 16 * ((lane >> 4) & 1) + 4 * (lane & 3));
+    const tr_ptr vtr = (tr_ptr)(vt + (4 * hf + ((lane & 15) >> 2)) * LDV + 16 * ((lane >> 4) & 1) + 4 * (lane & 3));
     float psum = 0.f;
 #pragma unroll
     for (int t2 = 0; t2 < 2; ++t2) {
@@ -200,13 +266,14 @@ __global__ __launch_bounds__(kDcThreads, 2) void attn_decode_bf16(Dims dm, AttnA
       }
     }
     l_run += psum;
+    __builtin_amdgcn_wave_barrier();
   }
 
-  // ---- merge the four waves' partials through LDS, then write the block's partial ----------------------------
+  // ---- merge the four waves' partials of the real rows through LDS, then write the block's partial ----
   const float l_wave = l_run + other_half(l_run);
-  __syncthreads();   // the tile buffers may be reused
+  __syncthreads();   // the waves' pieces may be reused
   float* mg = reinterpret_cast<float*>(smem);   // [4 waves][32 rows][REC]
-  {
+  if (li < n_rows) {
     float* rec = mg + ((size_t)w * 32 + li) * REC;
     if (hf == 0) {
       rec[0] = m_run;
@@ -218,19 +285,21 @@ __global__ __launch_bounds__(kDcThreads, 2) void attn_decode_bf16(Dims dm, AttnA
       for (int v = 0; v < 16; ++v) rec[2 + 32 * c + 8 * (v / 4) + 4 * hf + (v % 4)] = o[c][v];
   }
   __syncthreads();
-  for (int i = tid; i < 32 * REC; i += kDcThreads) {
+  float* my_part = part + ((size_t)kv * n_slots + blockIdx.x) * 32 * REC;
+  for (int i = tid; i < n_rows * REC; i += kDcThreads) {
     const int r = i / REC, e = i % REC;
-    float m = -INFINITY;
+    float mu[kDcWaves], m = -INFINITY;
 #pragma unroll
-    for (int u = 0; u < 4; ++u) m = fmaxf(m, mg[((size_t)u * 32 + r) * REC]);
-    float acc = 0.f;
-    if (e == 0) {
-      acc = m;
-    } else {
+    for (int u = 0; u < kDcWaves; ++u) {
+      mu[u] = mg[((size_t)u * 32 + r) * REC];
+      m = fmaxf(m, mu[u]);
+    }
+    float acc = m;
+    if (e != 0) {
+      acc = 0.f;
 #pragma unroll
-      for (int u = 0; u < 4; ++u) {
-        const float mu = mg[((size_t)u * 32 + r) * REC];
-        const float wgt = (mu == -INFINITY) ? 0.f : __builtin_amdgcn_exp2f(mu - m);
+      for (int u = 0; u < kDcWaves; ++u) {
+        const float wgt = (mu[u] == -INFINITY) ? 0.f : __builtin_amdgcn_exp2f(mu[u] - m);
         acc += wgt * mg[((size_t)u * 32 + r) * REC + e];
       }
     }
@@ -241,10 +310,9 @@ __global__ __launch_bounds__(kDcThreads, 2) void attn_decode_bf16(Dims dm, AttnA
 // One block per (row, kv, b).  The splits' (m, l) go through LDS once; then thread (dim e, split group sg) adds up the
 // O partials of its splits (independent, coalesced loads, unrolled), and the groups are combined through LDS.
 // The summation order is fixed by the indices alone, so the result does not depend on scheduling.
-constexpr int kMaxSplits = 64;
 template <int D>
 __global__ __launch_bounds__(kDcThreads) void attn_decode_merge(Dims dm, AttnArgs a, const float* __restrict__ part,
-                                                                int n_splits) {
+                                                                int n_slots) {
   constexpr int REC = DecodeCfg<D>::REC;
   constexpr int NG = kDcThreads / D;   // split groups
   __shared__ float wgt[kMaxSplits];
@@ -252,7 +320,9 @@ __global__ __launch_bounds__(kDcThreads) void attn_decode_merge(Dims dm, AttnArg
   __shared__ float s_m, s_l;
   const int r = blockIdx.x, kv = blockIdx.y, b = blockIdx.z;
   const int tid = threadIdx.x;
-  const float* base = part + ((size_t)(b * dm.n_kv + kv) * n_splits * 32 + r) * REC;   // split s is s * 32 * REC further
+  const DecodeShare share = decode_share(dm, a, b, kv, n_slots);
+  const int n_splits = share.n_splits;
+  const float* base = part + (((size_t)kv * n_slots + share.first) * 32 + r) * REC;   // split s is s * 32 * REC further
   const size_t sstride = (size_t)32 * REC;
   float m_s = -INFINITY, l_s = 0.f;
   if (tid < n_splits) {
@@ -299,21 +369,17 @@ __global__ __launch_bounds__(kDcThreads) void attn_decode_merge(Dims dm, AttnArg
 // ---------------------------------------------------------------------------------------------
 bool attn_decode_applies(const Dims& dm) { return dm.C * dm.g <= 32; }
 
-static int decode_splits(const Dims& dm, bool sparse) {
-  const long long max_keys = (long long)attended_cap(dm, sparse) + dm.C;
-  const long long tiles = (max_keys + kDcTile - 1) / kDcTile;
-  long long n = (tiles + 7) / 8;                                   // about eight tiles per split ...
-  const long long fill = (256 + (long long)dm.b * dm.n_kv - 1) / ((long long)dm.b * dm.n_kv);
-  if (n < fill) n = fill < tiles ? fill : tiles;                   // ... but enough splits to give every CU a block
-  n = n < 1 ? 1 : (n > kMaxSplits ? kMaxSplits : n);
-  return (int)n;
+// Blocks per KV head: two for every compute unit in all and one more for every sequence (see decode_share).
+static int decode_slots(const Dims& dm) {
+  const long long n = (512 + dm.n_kv - 1) / dm.n_kv, most = (long long)kMaxSplits * dm.b;
+  const long long want = dm.b > 64 ? (n + dm.b - 1) / dm.b * dm.b : n + dm.b;
+  return (int)(want < most ? want : most);
 }
 
 size_t attn_decode_ws_floats(const Dims& dm) {
   if (dm.g > 32) return 0;
-  // Independent of the chunk length (a prompt's last chunk may be decode-sized when the others are not), and sized
-  // for the dense path (the larger key list), so one workspace serves every call made with this shape.
-  return (size_t)dm.b * dm.n_kv * decode_splits(dm, false) * 32 * (2 + dm.d);
+  // independent of the chunk length (a prompt's last chunk may be decode-sized when the others are not)
+  return (size_t)dm.n_kv * decode_slots(dm) * 32 * (2 + dm.d);
 }
 
 template <int D>
@@ -322,15 +388,14 @@ static hipError_t launch_decode_d(const Dims& dm, const AttnArgs& a, float* part
   static std::atomic<uint64_t> lds_done{0};
   const hipError_t e = ensure_dynamic_lds(reinterpret_cast<const void*>(&attn_decode_bf16<D>), Cfg::kLdsBytes, lds_done);
   if (e != hipSuccess) return e;
-  const bool sparse = a.k_idx != nullptr;
-  const int n_splits = decode_splits(dm, sparse);
-  const long long max_keys = (long long)attended_cap(dm, sparse) + dm.C;
-  int sps = (int)((max_keys + n_splits - 1) / n_splits);
-  sps = (sps + kDcTile - 1) / kDcTile * kDcTile;
-  hipLaunchKernelGGL((attn_decode_bf16<D>), dim3(n_splits, dm.n_kv, dm.b), dim3(kDcThreads), Cfg::kLdsBytes, st, dm, a,
-                     part, n_splits, sps);
+  const int n_slots = decode_slots(dm);
+  // blocks that a short list leaves without work are not launched where the host can tell
+  const long long tiles = ((long long)attended_cap(dm, a.k_idx != nullptr) + dm.C + kDcTile - 1) / kDcTile;
+  const long long most = dm.b > 64 ? n_slots : dm.b * ((tiles + kDcWaves - 1) / kDcWaves);
+  hipLaunchKernelGGL((attn_decode_bf16<D>), dim3(n_slots < most ? n_slots : (int)most, dm.n_kv), dim3(kDcThreads),
+                     Cfg::kLdsBytes, st, dm, a, part, n_slots);
   hipLaunchKernelGGL((attn_decode_merge<D>), dim3(dm.C * dm.g, dm.n_kv, dm.b), dim3(kDcThreads), 0, st, dm, a, part,
-                     n_splits);
+                     n_slots);
   return hipGetLastError();
 }
 

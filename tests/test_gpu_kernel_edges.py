@@ -106,3 +106,21 @@ def test_bf16_attention_key_splits_of_eight_row_blocks():
     # 140 row groups of eight on 256 compute units: both tile modes and the split are in reach of the plan
     check_attention(dict(dtype="bf16", n_q=8, n_kv=8, d=128, chunk=1341, kv_lens=[5000], budgets=[3000]),
                     rows=[0, 1, 31, 32, 700, 1311, 1312, 1340])
+
+
+# decode kernel: single slots, tiles of 32 short of and past full, fewer tiles than waves or blocks, batches whose shares
+# of the blocks differ, batches beyond one wave's lanes
+DECODE_CASES = [
+    dict(n_q=1, n_kv=1, d=64, chunk=1, kv_lens=[0], budgets=[1]),
+    dict(n_q=4, n_kv=1, d=128, chunk=8, kv_lens=[31], budgets=[24]),
+    dict(n_q=8, n_kv=2, d=128, chunk=1, kv_lens=[4100], budgets=[127]),
+    dict(n_q=16, n_kv=1, d=64, chunk=2, kv_lens=[20000], budgets=[20000]),
+    dict(n_q=8, n_kv=4, d=128, chunk=3, kv_lens=[9000, 1, 700, 0, 3333], budgets=[1000, 1, 96, 5, 333], batch=5),
+    dict(n_q=2, n_kv=1, d=64, chunk=1, kv_lens=[(97 * i) % 1511 for i in range(66)],
+         budgets=[(97 * i) % 1511 // 4 + 1 for i in range(66)], batch=66),
+]
+
+
+@pytest.mark.parametrize("case", DECODE_CASES, ids=lambda c: _id({k: v for k, v in c.items() if k not in ("kv_lens", "budgets")}))
+def test_decode_attention_tiles_and_shares(case):
+    check_attention(dict(case, dtype="bf16"))
