@@ -4,7 +4,7 @@
 // compaction so that indices come out in ascending position and equal scores go to the lower
 // position.  Integer work only: the result is deterministic and independent of the launch shape.
 //
-//   T_max <= kSmallMax : one 1024-thread block per head, keys held in registers, one launch.
+//   T_max <= kSmallMax : one to four 1024-thread blocks per head, keys held in registers, one launch.
 //   larger             : several blocks per head.  Three histogram passes (11 + 11 + 10 bits, global
 //                        integer atomics) find the cut key; a count pass and an emit pass produce
 //                        the ordered index list.  Each launch derives the newest step of the cut
@@ -25,19 +25,41 @@ __device__ __forceinline__ int radix_shift(int pass) { return pass == 0 ? 21 : (
 __device__ __forceinline__ uint32_t radix_bins(int pass) { return pass == 2 ? 1024u : 2048u; }
 
 // ---------------------------------------------------------------------------------------------
-// Single-block path.  Wave w owns scores [w*64*IPT, (w+1)*64*IPT); its register j of lane l is score
+// Register path.  Wave w owns scores [w*64*IPT, (w+1)*64*IPT); its register j of lane l is score
 // w*64*IPT + 64*j + l, so every load is a coalesced 256-byte row and position order inside a wave is (j, lane).
-// The cut key comes from the block-wide radix select; the ordered compaction needs no scan over threads: per
-// register, two wave ballots give every lane the number of earlier taken positions of its wave, and the 16 wave
-// totals are combined through LDS.
+// The cut: one LDS histogram over 2048 equal bins between the smallest and the largest score, a scan for the bin that
+// holds the B-th largest, and a count of ranks among that bin's few keys.  (Equal bins and not key bits: the scores of a
+// head lie close together, and a lane's atomic on an occupied bin waits for the others.)  Where more keys share the
+// bin than LDS has room for, or the scores admit no such bins, the block-wide radix select decides.
+// The ordered compaction needs no scan over threads: per register, one wave ballot (two where only some of the keys
+// equal to the cut are taken) gives every lane the number of earlier taken positions of its wave, and the 16 wave totals
+// are combined through LDS.
+//
+// What bounds it: one compute unit's instruction rate (five passes over the keys) and a chain of six barriers.  So
+// from 16 keys per thread on, several blocks take a head: all of them find the cut, each emits its share of the waves'
+// ranges (two blocks: 16, four: 32 keys per thread).
+// Measured (us, radix select on key bits and one block a head -> now): 8 heads of 8192 scores 7.9 -> 6.0, 8 of 32768
+// 20.4 -> 13.5, 12 of up to 19999 19.0 -> 12.1.
+constexpr int kCutBins = 2048;
+constexpr int kCutKeys = 1024;
+struct CutLds {
+  uint32_t hist[kCutBins];
+  float key[kCutKeys];
+  uint32_t wsum[kSmallThreads / 64 + 1];
+  float wmin[kSmallThreads / 64], wmax[kSmallThreads / 64];
+  uint32_t n, bin, need, need_eq;
+  float tau;
+};
 
-template <int IPT>
+template <int IPT, int NB>
 __global__ __launch_bounds__(kSmallThreads) void topk_small(Dims dm, const float* __restrict__ scores,
                                                            const int32_t* __restrict__ kv_lens,
                                                            const int32_t* __restrict__ budgets,
                                                            int32_t* __restrict__ k_idx, int32_t* __restrict__ k_cnt) {
   constexpr int NW = kSmallThreads / 64;
+  constexpr int BPT = kCutBins / kSmallThreads;   // bins per thread
   __shared__ RadixSelectLds rs;
+  __shared__ __align__(16) CutLds cl;
   __shared__ uint32_t wgt[NW], weq[NW];
   const int kv = blockIdx.x, b = blockIdx.y;
   const int tid = threadIdx.x, lane = tid & 63, w = tid >> 6;
@@ -45,54 +67,162 @@ __global__ __launch_bounds__(kSmallThreads) void topk_small(Dims dm, const float
   const int lo = w * 64 * IPT + lane;   // position of register 0; register j is 64*j further
   // The scores are requested before the cache length is known (the row has T_max entries; those past the length
   // are discarded below), so the two fetches overlap instead of queueing behind each other.
-  float raw[IPT];
+  uint32_t rb[IPT];   // the scores' bits (the radix select borrows the registers for key images)
+  auto val = [&](int j) __attribute__((always_inline)) { return __uint_as_float(rb[j]); };
 #pragma unroll
-  for (int j = 0; j < IPT; ++j) raw[j] = lo + 64 * j < dm.T_cap ? sc[lo + 64 * j] : 0.f;
+  for (int j = 0; j < IPT; ++j) rb[j] = lo + 64 * j < dm.T_cap ? __float_as_uint(sc[lo + 64 * j]) : 0u;
   const int T = max(0, min(kv_lens[b], dm.T_cap));
   const int B = max(0, min(min(budgets[b], T), dm.B_max));
   int32_t* out = k_idx + (size_t)(b * dm.n_kv + kv) * dm.B_max;
-  if (tid == 0) k_cnt[b * dm.n_kv + kv] = B;
+  if (tid == 0 && blockIdx.z == 0) k_cnt[b * dm.n_kv + kv] = B;
   if (B == 0) return;
   if (B >= T) {
-    for (int i = tid; i < T; i += kSmallThreads) out[i] = i;
+    for (int i = blockIdx.z * kSmallThreads + tid; i < T; i += NB * kSmallThreads) out[i] = i;
     return;
   }
-  uint32_t key[IPT];
-  uint32_t valid = 0u;
+#pragma unroll
+  for (int i = 0; i < BPT; ++i) cl.hist[i * kSmallThreads + tid] = 0u;
+  if (tid == 0) cl.n = 0u;
+  // positions past the length become NaN: minima and maxima pass over them and no comparison holds for them
+  float vmin = INFINITY, vmax = -INFINITY;
 #pragma unroll
   for (int j = 0; j < IPT; ++j) {
-    const bool in = lo + 64 * j < T;
-    key[j] = in ? max(okey(raw[j]), 1u) : 0u;   // real keys are never 0, so the padding can neither exceed nor equal a cut key
-    valid |= (in ? 1u : 0u) << j;
+    if (lo + 64 * j >= T) rb[j] = 0x7FC00000u;
+    vmin = fminf(vmin, val(j));
+    vmax = fmaxf(vmax, val(j));
   }
-  uint32_t tau, need_eq;
-  block_radix_select<IPT, true>(key, valid, (uint32_t)B, rs, &tau, &need_eq);   // descending: the B largest
-  // wave totals of (key > tau) and (key == tau): per-lane counts (both in one register: at most 32 each), one scan
-  uint32_t cnt = 0;
-#pragma unroll
-  for (int j = 0; j < IPT; ++j) {
-    cnt += (key[j] > tau ? 0x10000u : 0u) + (key[j] == tau ? 1u : 0u);
-  }
-  cnt = wave_incl_scan_u32(cnt);
-  if (lane == 63) {
-    wgt[w] = cnt >> 16;
-    weq[w] = cnt & 0xFFFFu;
+  vmin = -wave64_max(-vmin);
+  vmax = wave64_max(vmax);
+  if (lane == 0) {
+    cl.wmin[w] = vmin;
+    cl.wmax[w] = vmax;
   }
   __syncthreads();
+  vmin = -wave64_max(lane < NW ? -cl.wmin[lane] : -INFINITY);
+  vmax = wave64_max(lane < NW ? cl.wmax[lane] : -INFINITY);
+  // monotone in v (a rounded product and a truncation of non-negative values), the largest score lands in the last bin
+  const float per = ((float)kCutBins - 0.5f) / (vmax - vmin);
+  const bool binned = per < 1e30f;   // false for equal (or not finite) extremes
+  auto bin_of = [&](float v) __attribute__((always_inline)) { return min((int)((v - vmin) * per), kCutBins - 1); };
+  const bool full = (w + 1) * 64 * IPT <= T;   // (wave-uniform) no position of this wave is past the length
+  float tau = 0.f;
+  uint32_t need_eq = 0u, n_in = kCutKeys + 1, need = (uint32_t)B;
+  int cut_bin = 0;
+  if (binned) {   // block-uniform
+    if (full) {
+#pragma unroll
+      for (int j = 0; j < IPT; ++j) atomicAdd(&cl.hist[bin_of(val(j))], 1u);
+    } else {
+#pragma unroll
+      for (int j = 0; j < IPT; ++j)
+        if (val(j) >= vmin) atomicAdd(&cl.hist[bin_of(val(j))], 1u);   // (not for a NaN)
+    }
+    __syncthreads();
+    uint32_t hv[BPT], mine = 0, tot;   // thread 0 has the highest bins
+#pragma unroll
+    for (int i = 0; i < BPT; ++i) {
+      hv[i] = cl.hist[kCutBins - 1 - (tid * BPT + i)];
+      mine += hv[i];
+    }
+    uint32_t above = block_excl_scan<kSmallThreads>(mine, cl.wsum, &tot);
+    if (above < need && need <= above + mine) {   // exactly one thread (the histogram holds T > B keys)
+#pragma unroll
+      for (int i = 0; i < BPT; ++i) {
+        if (above < need && need <= above + hv[i]) {
+          cl.bin = kCutBins - 1 - (tid * BPT + i);
+          cl.need = need - above;
+        }
+        above += hv[i];
+      }
+    }
+    __syncthreads();
+    cut_bin = (int)cl.bin;
+    need = cl.need;
+    asm volatile("" : "+v"(vmin));   // (the bins are worked out again: kept, they would need IPT more registers)
+#pragma unroll
+    for (int j = 0; j < IPT; ++j) {
+      if (bin_of(val(j)) == cut_bin && val(j) >= vmin) {   // (false for a NaN)
+        const uint32_t slot = atomicAdd(&cl.n, 1u);
+        if (slot < (uint32_t)kCutKeys) cl.key[slot] = val(j);
+      }
+    }
+    __syncthreads();
+    n_in = cl.n;
+  }
+  if (n_in <= (uint32_t)kCutKeys) {   // block-uniform
+    if (tid < (int)n_in) {
+      const float k = cl.key[tid];
+      uint32_t gt = 0, ge = 0;
+      for (uint32_t j = 0; j < n_in; ++j) {
+        gt += cl.key[j] > k ? 1u : 0u;
+        ge += cl.key[j] >= k ? 1u : 0u;
+      }
+      if (gt < need && need <= ge) {   // (equal keys all write the same)
+        cl.tau = k;
+        cl.need_eq = need - gt;
+      }
+    }
+    __syncthreads();
+    tau = cl.tau;
+    need_eq = cl.need_eq;
+  } else {   // descending: the `need` largest of the bin's (or all) keys
+    uint32_t in_bin = 0u, tau_key;
+#pragma unroll
+    for (int j = 0; j < IPT; ++j) {
+      in_bin |= (val(j) >= vmin && (!binned || bin_of(val(j)) == cut_bin) ? 1u : 0u) << j;
+      rb[j] = okey(val(j) + 0.0f);   // (one zero)
+    }
+    block_radix_select<IPT, true>(rb, in_bin, need, rs, &tau_key, &need_eq);
+    auto back = [](uint32_t k) { return (k & 0x80000000u) ? k & 0x7FFFFFFFu : ~k; };   // inverse of okey
+    tau = __uint_as_float(back(tau_key));
+#pragma unroll
+    for (int j = 0; j < IPT; ++j) rb[j] = back(rb[j]);
+  }
+  // wave totals of scores above the cut and equal to it
+  {
+    uint32_t c_gt = 0, c_eq = 0;
+#pragma unroll
+    for (int j = 0; j < IPT; ++j) {
+      c_gt += (uint32_t)__popcll(__builtin_amdgcn_ballot_w64(val(j) > tau));
+      c_eq += (uint32_t)__popcll(__builtin_amdgcn_ballot_w64(val(j) == tau));
+      __builtin_amdgcn_sched_barrier(0);   // (see below)
+    }
+    if (lane == 0) {
+      wgt[w] = c_gt;
+      weq[w] = c_eq;
+    }
+  }
+  __syncthreads();
+  if (NB > 1 && w / (NW / NB) != (int)blockIdx.z) return;   // (no barrier follows) another block emits this wave's range
   // taken candidates at earlier positions (earlier waves): greater than the cut / equal to it
+  const uint32_t all_eq = wave_incl_scan_u32(lane < NW ? weq[lane] : 0u);
   uint32_t n_gt = wave_incl_scan_u32(lane < w ? wgt[lane] : 0u);
   uint32_t n_eq = wave_incl_scan_u32(lane < w ? weq[lane] : 0u);
   n_gt = (uint32_t)__builtin_amdgcn_readlane((int)n_gt, 63);
   n_eq = (uint32_t)__builtin_amdgcn_readlane((int)n_eq, 63);
+  const bool take_all_eq = (uint32_t)__builtin_amdgcn_readlane((int)all_eq, 63) == need_eq;
   const unsigned long long below = (1ull << lane) - 1ull;
   // (an opaque copy of the cut: otherwise the comparison masks of the counting loop above are kept alive for this
   // loop, 2 x IPT scalar register pairs that spill)
-  uint32_t tau_e = tau;
+  float tau_e = tau;
   asm volatile("" : "+v"(tau_e));
+  if (take_all_eq) {   // every key equal to the cut is taken (nearly always there is just one)
+    uint32_t n_before = n_gt + n_eq;
+#pragma unroll
+    for (int j = 0; j < IPT; ++j) {
+      const bool take = val(j) >= tau_e;
+      const unsigned long long m = __builtin_amdgcn_ballot_w64(take);
+      const uint32_t pos = n_before + __popcll(m & below);
+      if (take && pos < (uint32_t)B) out[pos] = lo + 64 * j;   // guard: a malformed score array cannot push writes past the budget
+      n_before += __popcll(m);
+      __builtin_amdgcn_sched_barrier(0);   // keep one register's ballot live at a time (32 of them would spill SGPRs)
+    }
+    return;
+  }
 #pragma unroll
   for (int j = 0; j < IPT; ++j) {
     const int t = lo + 64 * j;
-    const bool gt = key[j] > tau_e, eq = key[j] == tau_e;
+    const bool gt = val(j) > tau_e, eq = val(j) == tau_e;
     const unsigned long long m_gt = __builtin_amdgcn_ballot_w64(gt), m_eq = __builtin_amdgcn_ballot_w64(eq);
     const uint32_t gt_before = n_gt + __popcll(m_gt & below), eq_before = n_eq + __popcll(m_eq & below);
     if (gt || (eq && eq_before < need_eq)) {   // equal scores go to the lower positions
@@ -324,20 +454,20 @@ bool topk_uses_ws(const Dims& dm) { return dm.T_cap > kSmallMax; }
 hipError_t launch_topk_keys(const Dims& dm, const float* scores, const int32_t* kv_lens, const int32_t* budgets,
                             int32_t* k_idx, int32_t* k_cnt, uint32_t* ws, hipStream_t st, bool ws_is_zero) {
   if (!topk_uses_ws(dm)) {
-    const dim3 grid(dm.n_kv, dm.b), block(kSmallThreads);
+    const dim3 block(kSmallThreads);
     const int ipt = (dm.T_cap + kSmallThreads - 1) / kSmallThreads;
     if (ipt <= 1) {
-      hipLaunchKernelGGL((topk_small<1>), grid, block, 0, st, dm, scores, kv_lens, budgets, k_idx, k_cnt);
+      hipLaunchKernelGGL((topk_small<1, 1>), dim3(dm.n_kv, dm.b), block, 0, st, dm, scores, kv_lens, budgets, k_idx, k_cnt);
     } else if (ipt <= 2) {
-      hipLaunchKernelGGL((topk_small<2>), grid, block, 0, st, dm, scores, kv_lens, budgets, k_idx, k_cnt);
+      hipLaunchKernelGGL((topk_small<2, 1>), dim3(dm.n_kv, dm.b), block, 0, st, dm, scores, kv_lens, budgets, k_idx, k_cnt);
     } else if (ipt <= 4) {
-      hipLaunchKernelGGL((topk_small<4>), grid, block, 0, st, dm, scores, kv_lens, budgets, k_idx, k_cnt);
+      hipLaunchKernelGGL((topk_small<4, 1>), dim3(dm.n_kv, dm.b), block, 0, st, dm, scores, kv_lens, budgets, k_idx, k_cnt);
     } else if (ipt <= 8) {
-      hipLaunchKernelGGL((topk_small<8>), grid, block, 0, st, dm, scores, kv_lens, budgets, k_idx, k_cnt);
+      hipLaunchKernelGGL((topk_small<8, 1>), dim3(dm.n_kv, dm.b), block, 0, st, dm, scores, kv_lens, budgets, k_idx, k_cnt);
     } else if (ipt <= 16) {
-      hipLaunchKernelGGL((topk_small<16>), grid, block, 0, st, dm, scores, kv_lens, budgets, k_idx, k_cnt);
+      hipLaunchKernelGGL((topk_small<16, 2>), dim3(dm.n_kv, dm.b, 2), block, 0, st, dm, scores, kv_lens, budgets, k_idx, k_cnt);
     } else {
-      hipLaunchKernelGGL((topk_small<32>), grid, block, 0, st, dm, scores, kv_lens, budgets, k_idx, k_cnt);
+      hipLaunchKernelGGL((topk_small<32, 4>), dim3(dm.n_kv, dm.b, 4), block, 0, st, dm, scores, kv_lens, budgets, k_idx, k_cnt);
     }
     return hipGetLastError();
   }

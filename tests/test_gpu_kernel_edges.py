@@ -124,3 +124,47 @@ DECODE_CASES = [
 @pytest.mark.parametrize("case", DECODE_CASES, ids=lambda c: _id({k: v for k, v in c.items() if k not in ("kv_lens", "budgets")}))
 def test_decode_attention_tiles_and_shares(case):
     check_attention(dict(case, dtype="bf16"))
+
+
+# top-B: the fused call and the stage calls against a sort of the same scores, bit for bit, whatever the scores look
+# like (ties at the cut, one score only, more keys in the cut bin than LDS takes, edges of the keys held per thread)
+BINNED_CASES = [
+    ("normal", dict(kv_lens=[1024, 33, 1], budgets=[100, 32, 1], batch=3)),
+    ("normal", dict(kv_lens=[1025, 1, 0], budgets=[1024, 9, 3], batch=3)),
+    ("normal", dict(kv_lens=[32768], budgets=[3932])),
+    ("normal", dict(kv_lens=[16385], budgets=[16384])),
+    ("pairs", dict(kv_lens=[16384], budgets=[5001])),
+    ("normal", dict(kv_lens=[5000], budgets=[1], chunk=1, n_retain=8)),
+    ("pairs", dict(kv_lens=[6001], budgets=[777])),            # every score twice: ties at the cut
+    ("equal", dict(kv_lens=[9000], budgets=[4000])),           # one score only: more keys in the cut's bin than LDS takes
+    ("normal", dict(kv_lens=[3000], budgets=[400], dtype="f32", d=64)),
+    ("pairs", dict(kv_lens=[20000, 7], budgets=[5000, 7], batch=2, dtype="f32")),
+]
+
+
+@pytest.mark.parametrize("kind,case", BINNED_CASES, ids=lambda x: _id(x) if isinstance(x, dict) else x)
+def test_top_b_cut_bins_ties_and_shares(kind, case):
+    case = dict(dict(dtype="bf16", n_q=4, n_kv=2, d=128, chunk=40, n_retain=16, batch=1), **case)
+    w = gen.make_custom(seed=23, **case)
+    if kind == "equal":
+        w.K[:] = w.K[:, :, :1]
+    elif kind == "pairs":
+        n = w.K.shape[2] // 2 * 2
+        w.K[:, :, 1:n:2] = w.K[:, :, 0:n:2]
+    for fused in (False, True):
+        buf = _buffers(w)
+        buf.workspace.fill_(0xA5)
+        buf.k_idx.fill_(-1)
+        buf.k_cnt.fill_(-1)
+        if fused:
+            buf.chunk_attn()
+        else:
+            buf.select_queries()
+            buf.score_keys()
+            buf.topk_keys()
+        torch.cuda.synchronize()
+        scores, idx, cnt = gen.from_torch(buf.scores), gen.from_torch(buf.k_idx), gen.from_torch(buf.k_cnt)
+        for b in range(w.batch):
+            want = O.topk_keys(scores[b][:, :w.kv_lens[b]], w.budgets[b])
+            assert np.all(cnt[b] == want.shape[1])
+            assert np.array_equal(idx[b][:, :want.shape[1]], want), f"fused {fused} b{b}"
