@@ -194,7 +194,10 @@ quoka_status quoka_chunk_attn(const quoka_shape* shape, const void* q, const voi
  *             over a whole prompt equals plain causal attention)
  *   q_idx, qbar, scores, k_idx, k_cnt   scratch for one chunk, shaped as in quoka_chunk_attn; they hold the last
  *             chunk's intermediates on return (unused when sparse == 0, may then be NULL)
- * The last chunk may be shorter than chunk_len.  Everything is enqueued on `stream`, chunk after chunk.          */
+ * The last chunk may be shorter than chunk_len.  Everything is enqueued on `stream`.  A workspace of
+ * quoka_workspace_bytes is enough to run chunk after chunk; with more, up to quoka_prefill_workspace_bytes, several
+ * chunks share each launch (as many as fit; bounded at 256 MiB unless one chunk needs more).                   */
+quoka_status quoka_prefill_workspace_bytes(const quoka_shape* shape, size_t* out_bytes);
 quoka_status quoka_prefill_attn(const quoka_shape* shape, int sparse, const void* q, const void* k, const void* v,
                                 const int32_t* kv_lens_all, const int32_t* budgets_all, int32_t* q_idx, float* qbar,
                                 float* scores, int32_t* k_idx, int32_t* k_cnt, void* out, void* workspace,

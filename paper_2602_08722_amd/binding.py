@@ -21,7 +21,8 @@ _lib: Optional[ctypes.CDLL] = None
 
 EXPORTS = (
     "quoka_workspace_bytes", "quoka_select_queries", "quoka_score_keys", "quoka_topk_keys", "quoka_select_keys",
-    "quoka_sparse_attn", "quoka_dense_attn", "quoka_chunk_attn", "quoka_prefill_attn", "quoka_topk_keys_noalloc",
+    "quoka_sparse_attn", "quoka_dense_attn", "quoka_chunk_attn", "quoka_prefill_workspace_bytes", "quoka_prefill_attn",
+    "quoka_topk_keys_noalloc",
     "quoka_probe_mfma", "quoka_probe_read", "quoka_probe_attn_mix", "quoka_status_string", "quoka_version",
 )
 _STATUS_EXPORTS = EXPORTS[:-2]   # everything that returns a quoka_status
@@ -64,6 +65,7 @@ def load_library() -> ctypes.CDLL:
     P, I32P, F32P, SZ = ctypes.c_void_p, ctypes.c_void_p, ctypes.c_void_p, ctypes.c_size_t
     SH = ctypes.POINTER(QuokaShape)
     lib.quoka_workspace_bytes.argtypes = [SH, ctypes.POINTER(ctypes.c_size_t)]
+    lib.quoka_prefill_workspace_bytes.argtypes = [SH, ctypes.POINTER(ctypes.c_size_t)]
     lib.quoka_select_queries.argtypes = [SH, P, I32P, F32P, P, SZ, P]
     lib.quoka_score_keys.argtypes = [SH, F32P, P, I32P, F32P, P, SZ, P]
     lib.quoka_topk_keys.argtypes = [SH, F32P, I32P, I32P, I32P, I32P, P, SZ, P]
@@ -140,6 +142,13 @@ def quoka_version() -> int:
 def quoka_workspace_bytes(shape: QuokaShape) -> int:
     n = ctypes.c_size_t(0)
     _check("quoka_workspace_bytes", load_library().quoka_workspace_bytes(ctypes.byref(shape), ctypes.byref(n)))
+    return int(n.value)
+
+
+def quoka_prefill_workspace_bytes(shape: QuokaShape) -> int:
+    n = ctypes.c_size_t(0)
+    _check("quoka_prefill_workspace_bytes",
+           load_library().quoka_prefill_workspace_bytes(ctypes.byref(shape), ctypes.byref(n)))
     return int(n.value)
 
 
@@ -240,7 +249,7 @@ class PrefillBuffers:
         self.scores = torch.empty((b, n_kv, L), dtype=torch.float32, device=dev)
         self.k_idx = torch.empty((b, n_kv, max(max_budget, 1)), dtype=torch.int32, device=dev)
         self.k_cnt = torch.empty((b, n_kv), dtype=torch.int32, device=dev)
-        self.workspace = torch.empty(quoka_workspace_bytes(self.shape), dtype=torch.uint8, device=dev)
+        self.workspace = torch.empty(quoka_prefill_workspace_bytes(self.shape), dtype=torch.uint8, device=dev)
 
     def run(self, sparse=True):
         quoka_prefill_attn(self.shape, sparse, self.q, self.k, self.v, self.kv_lens_all, self.budgets_all, self.q_idx,

@@ -98,14 +98,14 @@ __global__ __launch_bounds__(2 * kSetThreads, 2) void attn_bf16(Dims dm, AttnArg
   // otherwise a long sequence that happens to come last starts when most of the chip has already drained.
   int b = blockIdx.z;
   if (dm.b > 1 && dm.b <= kWave)
-    b = seq_of_rank(sparse ? a.n_cache + kv : a.n_cache, sparse ? dm.n_kv : 1, dm.b, blockIdx.z);
+    b = seq_of_rank(sparse ? a.n_cache + kv : a.n_cache, sparse ? dm.n_kv : dm.ls, dm.b, blockIdx.z);
   const int tid = threadIdx.x % kSetThreads, lane = tid & 63;                 // position inside the wave set
   // wave-uniform values are pinned to scalar registers so that everything derived from them (tile kind, base
   // pointers, branches) stays scalar too
   const int w = __builtin_amdgcn_readfirstlane(tid >> 6);
   const int set = __builtin_amdgcn_readfirstlane(threadIdx.x / kSetThreads);
   const int li = lane & 31, hf = lane >> 5;
-  const int C = dm.C, g = dm.g;
+  const int C = dm.chunk(b), g = dm.g;
   const int ntt = (C + 31) / 32;
   const int nrb = g * ntt;                       // row blocks of this KV head
   const int half = (nrb + 1) / 2;                // row blocks [0, half) are "front", [half, nrb) "back"
@@ -129,6 +129,7 @@ __global__ __launch_bounds__(2 * kSetThreads, 2) void attn_bf16(Dims dm, AttnArg
   const int xb_hi = nrb - 1 - yb * HW;                                     // the block's last row block
   const int x_hi = adjacent ? nrb - 1 - yb * 2 * HW
                             : (xb_hi >= half ? xb_hi : min(yb * HW + HW - 1, half - 1));
+  if (adjacent ? x_hi < 0 : yb * HW >= half) return;   // a short chunk has no row blocks here (block-uniform)
   const int c_end_blk = min((x_hi / g) * 32 + 32, C);   // chunk keys any wave of this block can see
   const int sub = SPLIT ? set * kSub : 0;               // first key of this set's share of a staged tile
 
@@ -136,7 +137,7 @@ __global__ __launch_bounds__(2 * kSetThreads, 2) void attn_bf16(Dims dm, AttnArg
   if (sparse) {
     n_cache = min(a.n_cache[b * dm.n_kv + kv], dm.B_max);
   } else {
-    n_cache = min(a.n_cache[b], dm.T_max);
+    n_cache = min(a.n_cache[b * dm.ls], dm.T_max);
   }
   n_cache = max(n_cache, 0);
   // Tile order: the chunk's own tiles first, then the cache tiles.  The online softmax does not care, and the first
@@ -440,7 +441,7 @@ __global__ __launch_bounds__(2 * kSetThreads, 2) void attn_bf16(Dims dm, AttnArg
   const float l_tot = l_run + other_half(l_run);
   if constexpr (KSPLIT) {   // the partial goes out as the registers lie, 1 KiB per store
     if (!wave_on) return;
-    float* rec = a.part + (((size_t)(b * dm.n_kv + kv) * nrb + x) * a.n_splits + split) * Cfg::kRecFloats;
+    float* rec = a.part + (((size_t)(b * dm.n_kv + kv) * (g * ((dm.C + 31) / 32)) + x) * a.n_splits + split) * Cfg::kRecFloats;
 #pragma unroll
     for (int c = 0; c < DB; ++c)
 #pragma unroll
@@ -466,7 +467,7 @@ __global__ __launch_bounds__(2 * kSetThreads, 2) void attn_bf16(Dims dm, AttnArg
         *reinterpret_cast<uint2*>(orow + 32 * c + 8 * v4 + 4 * hf) = pk;
       }
     if (a.lse != nullptr && hf == 0) {
-      a.lse[(size_t)(b * dm.n_q + h) * C + tok] = (m_run + log2f(l_tot)) * 0.6931471805599453f;
+      a.lse[(size_t)(b * dm.n_q + h) * dm.C + tok] = (m_run + log2f(l_tot)) * 0.6931471805599453f;
     }
   }
 }
@@ -482,6 +483,8 @@ __global__ __launch_bounds__(64 * (D / 32)) void attn_bf16_merge(Dims dm, AttnAr
   const int lane = threadIdx.x & 63, c = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6);
   const int li = lane & 31, hf = lane >> 5;
   const int x = blockIdx.x, kv = blockIdx.y % dm.n_kv, b = blockIdx.y / dm.n_kv;
+  const int C = dm.chunk(b);
+  if (x >= dm.g * ((C + 31) / 32)) return;
   const float* rec = a.part + ((size_t)blockIdx.y * gridDim.x + x) * a.n_splits * REC;
   float m = -INFINITY;
   for (int s = 0; s < a.n_splits; ++s) m = fmaxf(m, rec[(size_t)s * REC + 32 * D + li]);
@@ -505,7 +508,7 @@ __global__ __launch_bounds__(64 * (D / 32)) void attn_bf16_merge(Dims dm, AttnAr
     }
   }
   const int tok = (x / dm.g) * 32 + li, h = kv * dm.g + x % dm.g;
-  if (tok >= dm.C) return;
+  if (tok >= C) return;
   const float inv = 1.0f / l;
   uint16_t* orow = static_cast<uint16_t*>(a.out) + b * dm.os[0] + h * dm.os[1] + (size_t)tok * dm.os[2];
 #pragma unroll

@@ -60,7 +60,7 @@ __global__ __launch_bounds__(kScThreads, 2) void score_bf16(Dims dm, const float
     }
   };
   issue(0, RA);   // the first K tile is in flight while the length arrives and the query operands are prepared
-  const int T = min(kv_lens[b], dm.T_cap);
+  const int T = min(kv_lens[b * dm.ls], dm.T_cap);
   if (t_begin >= T) return;  // block-uniform
   const int n_tiles = min(tiles_per_wg, (T - t_begin + kScTile - 1) / kScTile);
   if (n_tiles > 1) issue(1, RB);
@@ -139,7 +139,7 @@ __global__ __launch_bounds__(kScThreads) void score_f32(Dims dm, const float* __
   };
   int t0 = blockIdx.x * KPB;
   load_k(t0);
-  const int T = min(kv_lens[b], dm.T_cap);
+  const int T = min(kv_lens[b * dm.ls], dm.T_cap);
   if (t0 >= T) return;   // block-uniform
   // query operand: row qb*32 + li (rows past n_keep repeat a real query, or are zero where a mean is taken)
   f32x4 qreg[NI];

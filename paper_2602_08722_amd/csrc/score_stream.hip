@@ -91,7 +91,7 @@ __global__ __launch_bounds__(kStThreads, 1) void score_stream(Dims dm, const flo
   // ---- this block's share of the flat step list ----
   long long total = 0;
   for (int b = 0; b < dm.b; ++b) {
-    const int T = max(0, min(kv_lens[b], dm.T_cap));
+    const int T = max(0, min(kv_lens[b * dm.ls], dm.T_cap));
     total += (long long)dm.n_kv * ((T + kStKeys - 1) / kStKeys);
   }
   long long cur = total * blockIdx.x / gridDim.x;
@@ -117,7 +117,7 @@ __global__ __launch_bounds__(kStThreads, 1) void score_stream(Dims dm, const flo
     // ---- locate (sequence, head, first step) of the segment and its length ----
     int T, nb;
     for (;;) {
-      T = max(0, min(kv_lens[sb], dm.T_cap));
+      T = max(0, min(kv_lens[sb * dm.ls], dm.T_cap));
       nb = (T + kStKeys - 1) / kStKeys;
       if (cur < acc_steps + (long long)dm.n_kv * nb) break;
       acc_steps += (long long)dm.n_kv * nb;

@@ -33,8 +33,8 @@ struct SelCtx {
 __device__ __forceinline__ SelCtx sel_ctx(const Dims& dm, float* scores, const int32_t* kv_lens,
                                           const int32_t* budgets, uint32_t* ws, int kv, int b) {
   SelCtx c;
-  c.T = max(0, min(kv_lens[b], dm.T_cap));
-  c.B = max(0, min(min(budgets[b], c.T), dm.B_max));
+  c.T = max(0, min(kv_lens[b * dm.ls], dm.T_cap));
+  c.B = max(0, min(min(budgets[b * dm.ls], c.T), dm.B_max));
   c.head = b * dm.n_kv + kv;
   c.sc = scores + (size_t)c.head * dm.T_max;
   c.w = sel_ws(ws, dm.b * dm.n_kv, c.head, dm.T_max);

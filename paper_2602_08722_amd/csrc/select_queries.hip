@@ -27,13 +27,14 @@ __global__ __launch_bounds__(kSqThreads) void sq_partial_sums(Dims dm, const T* 
   constexpr int CG = D / 8;              // lanes per row (8 elements each)
   constexpr int RPB = kSqThreads / CG;   // rows handled concurrently
   const int tile = blockIdx.x, h = blockIdx.y, b = blockIdx.z;
+  const int C = dm.chunk(b);
   const int cg = threadIdx.x % CG, rr = threadIdx.x / CG;
   const T* base = q + b * dm.qs[0] + h * dm.qs[1];
   float acc[8] = {0, 0, 0, 0, 0, 0, 0, 0};
   const int t0 = tile * kSqTile;
   for (int r = rr; r < kSqTile; r += RPB) {
     const int tok = t0 + r;
-    if (tok < dm.C) {
+    if (tok < C) {
       float v[8];
       Elem<T>::load8(base + tok * dm.qs[2] + cg * 8, v);
 #pragma unroll
@@ -58,6 +59,7 @@ __global__ __launch_bounds__(kSqThreads) void sq_cosine(Dims dm, const T* __rest
   constexpr int CG = D / 8;
   constexpr int RPB = kSqThreads / CG;
   const int tile = blockIdx.x, h = blockIdx.y, b = blockIdx.z;
+  const int C = dm.chunk(b);
   __shared__ float mean[D];
   __shared__ float mnorm;
   if (threadIdx.x < D) {
@@ -71,7 +73,7 @@ __global__ __launch_bounds__(kSqThreads) void sq_cosine(Dims dm, const T* __rest
       for (int u = 0; u < 8; ++u)
         if (i0 + u < n_tiles) s += t[u];
     }
-    mean[threadIdx.x] = s / (float)dm.C;
+    mean[threadIdx.x] = s / (float)C;
   }
   __syncthreads();
   if (threadIdx.x == 0) {
@@ -89,7 +91,7 @@ __global__ __launch_bounds__(kSqThreads) void sq_cosine(Dims dm, const T* __rest
   const int t0 = tile * kSqTile;
   for (int r = rr; r < kSqTile; r += RPB) {   // uniform trip count: shuffles below stay convergent
     const int tok = t0 + r;
-    const int tk = tok < dm.C ? tok : dm.C - 1;
+    const int tk = tok < C ? tok : C - 1;
     float v[8];
     Elem<T>::load8(base + tk * dm.qs[2] + cg * 8, v);
     float dot = 0.f, qq = 0.f;
@@ -105,7 +107,7 @@ __global__ __launch_bounds__(kSqThreads) void sq_cosine(Dims dm, const T* __rest
       dot = group_sum<CG>(dot);
       qq = group_sum<CG>(qq);
     }
-    if (cg == 0 && tok < dm.C) {
+    if (cg == 0 && tok < C) {
       const float qn = fmaxf(sqrtf(qq), kNormEps);
       cosv[(size_t)(b * dm.n_q + h) * dm.C + tok] = dot / (qn * mn) + 0.0f;
     }
@@ -192,8 +194,8 @@ __global__ __launch_bounds__(kSelThreads) void sq_select(Dims dm, const float* _
   __shared__ uint32_t sel_key[kMaxKeep];
   __shared__ uint32_t sel_idx[kMaxKeep];
   const int h = blockIdx.x, b = blockIdx.y;
-  const int C = dm.C;
-  const float* cv = cosv + (size_t)(b * dm.n_q + h) * C;
+  const int C = dm.chunk(b);
+  const float* cv = cosv + (size_t)(b * dm.n_q + h) * dm.C;
   const int lo = threadIdx.x * IPT;
   uint32_t key[IPT];
   uint32_t valid = 0u;
@@ -256,7 +258,7 @@ __global__ __launch_bounds__(kSelThreads) void sq_head_select(Dims dm, const T* 
   __shared__ float mnorm;
   __shared__ float buf[RPB * D];             // column partials, then the cosines (RPB * NR <= RPB * D of them)
   const int h = blockIdx.x, b = blockIdx.y;
-  const int C = dm.C;
+  const int C = dm.chunk(b);
   const int tid = threadIdx.x;
   const int cg = tid % CG, rr = tid / CG;
   const T* base = q + b * dm.qs[0] + h * dm.qs[1];
@@ -357,7 +359,7 @@ __global__ __launch_bounds__(64) void sq_qbar(Dims dm, const T* __restrict__ q, 
       if constexpr (RULE == kFromIndex) {
         tok[jj] = *slot;
       } else {
-        tok[jj] = RULE == kIdentity ? r : (int)(((int64_t)r * dm.C) / n_keep);
+        tok[jj] = RULE == kIdentity ? r : (int)(((int64_t)r * dm.chunk(b)) / n_keep);
         if (lane == 0) *slot = tok[jj];
       }
     }

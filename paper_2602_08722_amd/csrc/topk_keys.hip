@@ -71,8 +71,8 @@ __global__ __launch_bounds__(kSmallThreads) void topk_small(Dims dm, const float
   auto val = [&](int j) __attribute__((always_inline)) { return __uint_as_float(rb[j]); };
 #pragma unroll
   for (int j = 0; j < IPT; ++j) rb[j] = lo + 64 * j < dm.T_cap ? __float_as_uint(sc[lo + 64 * j]) : 0u;
-  const int T = max(0, min(kv_lens[b], dm.T_cap));
-  const int B = max(0, min(min(budgets[b], T), dm.B_max));
+  const int T = max(0, min(kv_lens[b * dm.ls], dm.T_cap));
+  const int B = max(0, min(min(budgets[b * dm.ls], T), dm.B_max));
   int32_t* out = k_idx + (size_t)(b * dm.n_kv + kv) * dm.B_max;
   if (tid == 0 && blockIdx.z == 0) k_cnt[b * dm.n_kv + kv] = B;
   if (B == 0) return;
@@ -316,8 +316,8 @@ __device__ __forceinline__ LgCtx lg_ctx(const Dims& dm, const float* scores, con
                                         const int32_t* budgets, uint32_t* ws, int n_tiles) {
   const int kv = blockIdx.y, b = blockIdx.z;
   LgCtx c;
-  c.T = max(0, min(kv_lens[b], dm.T_cap));
-  c.B = max(0, min(min(budgets[b], c.T), dm.B_max));
+  c.T = max(0, min(kv_lens[b * dm.ls], dm.T_cap));
+  c.B = max(0, min(min(budgets[b * dm.ls], c.T), dm.B_max));
   const size_t head = (size_t)(b * dm.n_kv + kv);
   c.sc = scores + head * dm.T_max;
   const size_t per_head = 3 * (size_t)kBins + kCutWords + 2 * (size_t)n_tiles;

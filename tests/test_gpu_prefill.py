@@ -67,3 +67,49 @@ def test_sparse_chunked_prefill_matches_oracle(L, chunk, n_retain, budget):
     for kv in range(K.shape[0]):
         assert cnt[kv] == min(budget, s)
         P.check_topk_set(got_idx[kv, :cnt[kv]], scores[kv], min(budget, s), what=f"last chunk kv{kv}")
+
+
+@pytest.mark.parametrize("dtype,batch,n_q,n_kv,d,L,chunk,n_retain,sparse", [
+    ("bf16", 1, 8, 2, 128, 700, 192, 32, True),      # a short last chunk goes along
+    ("bf16", 1, 8, 2, 128, 1027, 256, 16, True),     # a decode-sized one does not
+    ("bf16", 1, 6, 2, 64, 2600, 200, 48, True),      # every chunk full length, three heads a group
+    ("bf16", 2, 8, 2, 128, 2111, 128, 16, True),     # two sequences, 17 chunks each
+    ("bf16", 1, 32, 8, 128, 9000, 100, 64, True),    # 90 chunks: two groups
+    ("bf16", 1, 4, 1, 64, 36000, 2048, 32, True),    # the two-pass selection, no key splits
+    ("bf16", 1, 8, 2, 64, 800, 4, 16, True),         # decode-sized chunks
+    ("bf16", 1, 8, 2, 128, 1500, 256, 16, False),
+    ("f32", 1, 4, 2, 64, 900, 128, 16, True),        # float32: the short last chunk runs by itself
+    ("f32", 2, 4, 2, 128, 1024, 128, 16, True),
+])
+def test_chunks_that_share_launches_match_chunk_after_chunk(dtype, batch, n_q, n_kv, d, L, chunk, n_retain, sparse):
+    """The same prompt with the workspace of one chunk (chunk after chunk) and with the full one (chunks as a batch)."""
+    import paper_2602_08722_amd as pk
+    pk.load_library()
+    dt = torch.bfloat16 if dtype == "bf16" else torch.float32
+    rng = torch.Generator(device="cuda").manual_seed(5)
+    q, k, v = (torch.randn(batch, n, L, d, device="cuda", generator=rng).to(dt) for n in (n_q, n_kv, n_kv))
+    def run(full):
+        pb = pk.PrefillBuffers(q, k, v, chunk, n_retain, lambda t: t // 8)
+        if not full:
+            small = pk.quoka_workspace_bytes(pb.shape)
+            assert small < pb.workspace.numel()
+            pb.workspace = pb.workspace[:small]
+        for t in (pb.k_idx, pb.q_idx, pb.k_cnt):
+            t.fill_(-1)
+        pb.run(sparse=sparse)
+        torch.cuda.synchronize()
+        return pb
+    one, many = run(False), run(True)
+    # two roundings of the output to dt, and of the probabilities (bf16) on either side
+    tol = P.TOL_OUT["bf16"] if dtype == "bf16" else 2e-5
+    assert (one.out.float() - many.out.float()).abs().max().item() <= tol
+    if sparse:   # the last chunk's intermediates are the caller's either way
+        n_keep = min(n_retain, L - (L - 1) // chunk * chunk, chunk)
+        if n_keep == min(n_retain, chunk):
+            assert torch.equal(one.q_idx, many.q_idx)
+        assert torch.equal(one.k_cnt, many.k_cnt) and int(one.k_cnt.min()) > 0
+        cnt = int(one.k_cnt[0, 0])
+        assert torch.equal(one.k_idx[:, :, :cnt], many.k_idx[:, :, :cnt])
+        t = (L - 1) // chunk * chunk
+        assert torch.equal(one.scores[:, :, :t], many.scores[:, :, :t])
+        assert (one.qbar - many.qbar).abs().max().item() <= 1e-6 or n_keep < min(n_retain, chunk)
