@@ -85,14 +85,17 @@ __global__ __launch_bounds__(kSmallThreads) void topk_small(Dims dm, const float
   if (tid == 0) cl.n = 0u;
   // positions past the length become NaN: minima and maxima pass over them and no comparison holds for them
   float vmin = INFINITY, vmax = -INFINITY;
+  unsigned long long nan = 0;   // lanes with a NaN among their scores proper
 #pragma unroll
   for (int j = 0; j < IPT; ++j) {
-    if (lo + 64 * j >= T) rb[j] = 0x7FC00000u;
+    const bool past = lo + 64 * j >= T;
+    nan |= __builtin_amdgcn_ballot_w64(!past && val(j) != val(j));
+    if (past) rb[j] = 0x7FC00000u;
     vmin = fminf(vmin, val(j));
     vmax = fmaxf(vmax, val(j));
   }
   vmin = -wave64_max(-vmin);
-  vmax = wave64_max(vmax);
+  vmax = nan == 0 ? wave64_max(vmax) : INFINITY;   // (no bins then)
   if (lane == 0) {
     cl.wmin[w] = vmin;
     cl.wmax[w] = vmax;
@@ -102,7 +105,7 @@ __global__ __launch_bounds__(kSmallThreads) void topk_small(Dims dm, const float
   vmax = wave64_max(lane < NW ? cl.wmax[lane] : -INFINITY);
   // monotone in v (a rounded product and a truncation of non-negative values), the largest score lands in the last bin
   const float per = ((float)kCutBins - 0.5f) / (vmax - vmin);
-  const bool binned = per < 1e30f;   // false for equal (or not finite) extremes
+  const bool binned = per > 0.f && per < 1e30f;   // false for equal or infinite extremes, and where a score is NaN
   auto bin_of = [&](float v) __attribute__((always_inline)) { return min((int)((v - vmin) * per), kCutBins - 1); };
   const bool full = (w + 1) * 64 * IPT <= T;   // (wave-uniform) no position of this wave is past the length
   float tau = 0.f;
@@ -169,7 +172,13 @@ __global__ __launch_bounds__(kSmallThreads) void topk_small(Dims dm, const float
     uint32_t in_bin = 0u, tau_key;
 #pragma unroll
     for (int j = 0; j < IPT; ++j) {
-      in_bin |= (val(j) >= vmin && (!binned || bin_of(val(j)) == cut_bin) ? 1u : 0u) << j;
+      if (!binned) {   // every score proper; a NaN ranks as the infinity of its sign
+        const bool in = lo + 64 * j < T;
+        if (in && val(j) != val(j)) rb[j] = (rb[j] & 0x80000000u) | 0x7F800000u;
+        in_bin |= (in ? 1u : 0u) << j;
+      } else {
+        in_bin |= (val(j) >= vmin && bin_of(val(j)) == cut_bin ? 1u : 0u) << j;
+      }
       rb[j] = okey(val(j) + 0.0f);   // (one zero)
     }
     block_radix_select<IPT, true>(rb, in_bin, need, rs, &tau_key, &need_eq);

@@ -168,3 +168,22 @@ def test_top_b_cut_bins_ties_and_shares(kind, case):
             want = O.topk_keys(scores[b][:, :w.kv_lens[b]], w.budgets[b])
             assert np.all(cnt[b] == want.shape[1])
             assert np.array_equal(idx[b][:, :want.shape[1]], want), f"fused {fused} b{b}"
+
+
+@pytest.mark.parametrize("T,B", [(700, 90), (1024, 1023), (9001, 4500), (20011, 300), (32768, 32767)])
+def test_top_b_of_scores_that_are_not_finite(T, B):
+    """A NaN score ranks as the infinity of its sign; the list stays full, ascending and inside the cache."""
+    w = gen.make_custom(dtype="bf16", n_q=2, n_kv=2, d=64, chunk=40, n_retain=16, kv_lens=[T], budgets=[B], batch=1, seed=3)
+    rng = np.random.default_rng(11)
+    for share in (0.0, 0.001, 0.5, 1.0):
+        buf = _buffers(w)
+        s = rng.standard_normal((2, T)).astype(np.float32)
+        odd = rng.random((2, T)) < share
+        s[odd] = rng.choice(np.array([np.nan, -np.nan, np.inf, -np.inf], dtype=np.float32), size=int(odd.sum()))
+        buf.scores.copy_(torch.from_numpy(s)[None])
+        buf.k_idx.fill_(-1)
+        buf.topk_keys()
+        torch.cuda.synchronize()
+        ranked = np.where(np.isnan(s), np.copysign(np.float32(np.inf), s), s)
+        want = np.stack([np.sort(np.argsort(-r, kind="stable")[:B]) for r in ranked])
+        assert np.array_equal(gen.from_torch(buf.k_idx)[0][:, :B], want), share
