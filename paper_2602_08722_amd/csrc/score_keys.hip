@@ -10,6 +10,8 @@
 // owns one key column and 16 query rows, so the max over queries is in-register plus one
 // half-wave exchange.
 // float32 keys: float32 MFMA, operands straight from global memory.
+#include <type_traits>
+
 #include "common.hip.h"
 #include "kernels.h"
 #include "score_tile.hip.h"
@@ -18,7 +20,8 @@ namespace quoka {
 
 // EXACT: Qbar enters as the three-term split (float32-exact products).  Otherwise it is rounded to bf16 once and
 // only that term is multiplied: a third of the matrix work, scores within 2^-9 * sum|qbar_i| of the exact ones.
-template <int D, int QB, bool EXACT>
+// PACK (QB = 1, EXACT): at most kPackRows queries, all three terms in one operand.
+template <int D, int QB, bool EXACT, bool PACK>
 __global__ __launch_bounds__(kScThreads, 2) void score_bf16(Dims dm, const float* __restrict__ qbar,
                                                            const uint16_t* __restrict__ kc,
                                                            const int32_t* __restrict__ kv_lens,
@@ -66,8 +69,15 @@ __global__ __launch_bounds__(kScThreads, 2) void score_bf16(Dims dm, const float
   if (n_tiles > 1) issue(1, RB);
 
   const bool dot_mode = (dm.flags & 1) != 0, mean_mode = (dm.flags & 2) != 0;   // ablation scorers
-  QueryTerms<D, EXACT> qt;   // this wave's 32 query rows
-  qt.load(qbar + (size_t)(b * dm.n_kv + kv) * n_keep * D, n_keep, qb, li, hf, mean_mode);
+  typename std::conditional<PACK, PackedTerms<D>, QueryTerms<D, EXACT>>::type qt;   // this wave's 32 query rows
+  {
+    const float* qhead = qbar + (size_t)(b * dm.n_kv + kv) * n_keep * D;
+    if constexpr (PACK) {
+      qt.load(qhead, n_keep, li, hf);
+    } else {
+      qt.load(qhead, n_keep, qb, li, hf, mean_mode);
+    }
+  }
 
   // scores of tile `it` from the maxima and squared norms of generation it % 3
   auto finish = [&](int it) {
@@ -87,8 +97,10 @@ __global__ __launch_bounds__(kScThreads, 2) void score_bf16(Dims dm, const float
     for (int i = 0; i < NLD; ++i) {
       const int rl = r0 + RPI * i;
       *reinterpret_cast<u32x4*>(tl + rl * LD + cg * 8) = R[i];
-      const float ss = row_sumsq<CG>(R[i]);
-      if (cg == 0) ssq_g[rl] = ss;
+      if constexpr (!PACK) {
+        const float ss = row_sumsq<CG>(R[i]);
+        if (cg == 0) ssq_g[rl] = ss;
+      }
     }
     // One barrier per tile.  It publishes tile `it` (and its squared norms) and the maxima of tile it-1.  The K tile
     // buffer written above was last read two steps ago, before the previous barrier; the norm / maximum generation
@@ -97,7 +109,21 @@ __global__ __launch_bounds__(kScThreads, 2) void score_bf16(Dims dm, const float
     if (it + 2 < n_tiles) issue(it + 2, R);  // the registers are free again: fetch the tile after the next
     if (it > 0) finish(it - 1);
 
-    tile_products<D, QB, EXACT>(tl, qt, qb, kg, li, hf, mean_mode, smax_g);
+    if constexpr (PACK) {
+      const int key = w * 32 + li;
+      const uint16_t* kp = tl + key * LD + hf * (D / 2);
+      bf16x8 kop[D / 16];
+#pragma unroll
+      for (int ks = 0; ks < D / 16; ++ks) kop[ks] = *reinterpret_cast<const bf16x8*>(kp + ks * 8);
+      float ss;
+      const float m = packed_products<D>(kop, qt, &ss);
+      if (hf == 0) {
+        smax_g[key] = m;
+        ssq_g[key] = ss;
+      }
+    } else {
+      tile_products<D, QB, EXACT>(tl, qt, qb, kg, li, hf, mean_mode, smax_g);
+    }
   };
   for (int it = 0; it < n_tiles; it += 2) {
     tile_step(it, RA);
@@ -213,13 +239,13 @@ static void launch_f32_d(const Dims& dm, const float* qbar, const float* kc, con
 }
 
 // ---------------------------------------------------------------------------------------------
-template <int D, int QB, bool EXACT>
+template <int D, int QB, bool EXACT, bool PACK = false>
 static hipError_t launch_bf16(const Dims& dm, const float* qbar, const void* kc, const int32_t* kv_lens, float* scores,
                               int n_keep, hipStream_t st, uint32_t* zero, uint32_t zero_words) {
   using Cfg = ScoreCfg<D, QB>;
   static std::atomic<uint64_t> lds_done{0};
   const hipError_t e =
-      ensure_dynamic_lds(reinterpret_cast<const void*>(&score_bf16<D, QB, EXACT>), Cfg::kLdsBytes, lds_done);
+      ensure_dynamic_lds(reinterpret_cast<const void*>(&score_bf16<D, QB, EXACT, PACK>), Cfg::kLdsBytes, lds_done);
   if (e != hipSuccess) return e;
   const int nt = (dm.T_cap + kScTile - 1) / kScTile;
   const int heads = dm.b * dm.n_kv;
@@ -229,7 +255,7 @@ static hipError_t launch_bf16(const Dims& dm, const float* qbar, const void* kc,
   int tpw = (nt + wg_per_head - 1) / wg_per_head;
   tpw = tpw < 1 ? 1 : tpw;
   dim3 grid((nt + tpw - 1) / tpw, dm.n_kv, dm.b);
-  hipLaunchKernelGGL((score_bf16<D, QB, EXACT>), grid, dim3(kScThreads), Cfg::kLdsBytes, st, dm, qbar,
+  hipLaunchKernelGGL((score_bf16<D, QB, EXACT, PACK>), grid, dim3(kScThreads), Cfg::kLdsBytes, st, dm, qbar,
                      static_cast<const uint16_t*>(kc), kv_lens, scores, n_keep, tpw, zero, zero_words);
   return hipGetLastError();
 }
@@ -243,6 +269,7 @@ static hipError_t launch_bf16_d(const Dims& dm, const float* qbar, const void* k
     if (qblocks == 2) return launch_bf16<D, 2, false>(dm, qbar, kc, kv_lens, scores, n_keep, st, zero, zero_words);
     return launch_bf16<D, 4, false>(dm, qbar, kc, kv_lens, scores, n_keep, st, zero, zero_words);
   }
+  if (score_packs(dm)) return launch_bf16<D, 1, true, true>(dm, qbar, kc, kv_lens, scores, n_keep, st, zero, zero_words);
   if (qblocks <= 1) return launch_bf16<D, 1, true>(dm, qbar, kc, kv_lens, scores, n_keep, st, zero, zero_words);
   if (qblocks == 2) return launch_bf16<D, 2, true>(dm, qbar, kc, kv_lens, scores, n_keep, st, zero, zero_words);
   return launch_bf16<D, 4, true>(dm, qbar, kc, kv_lens, scores, n_keep, st, zero, zero_words);

@@ -63,7 +63,8 @@ __device__ __forceinline__ void wait_vmcnt() {
   asm volatile("s_waitcnt vmcnt(%0)" ::"n"(N) : "memory");
 }
 
-template <int D, int QB>
+// PACK (QB = 1): at most kPackRows queries with all three terms in the one operand, so the scores are the exact ones.
+template <int D, int QB, bool PACK>
 __global__ __launch_bounds__(kStThreads, 1) void score_stream(Dims dm, const float* __restrict__ qbar,
                                                              const uint16_t* __restrict__ kc,
                                                              const int32_t* __restrict__ kv_lens,
@@ -164,7 +165,9 @@ __global__ __launch_bounds__(kStThreads, 1) void score_stream(Dims dm, const flo
 
     // query operand of this wave: rows qb*32 .. +32 of the head's Qbar, rounded to bf16, chunk ks + KS*hf per k-step
     bf16x8 qa[KS];
-    if (!producer) {
+    PackedTerms<D> qp;
+    if (PACK && !producer) qp.load(qbar + (size_t)head * n_keep * D, n_keep, li, hf);
+    if (!PACK && !producer) {
       float d2 = 0.f;
       const int r = min(qb * 32 + li, n_keep - 1);   // padding rows repeat a real query: the max is unchanged
       const float* qrow = qbar + ((size_t)head * n_keep + r) * D;
@@ -238,6 +241,16 @@ __global__ __launch_bounds__(kStThreads, 1) void score_stream(Dims dm, const flo
         // the next key block's operands are requested before this one's products are issued
         if (u + 1 < UPW) read_ops(u + 1, kop[(u + 1) & 1]);
         __builtin_amdgcn_sched_barrier(0);
+        if constexpr (PACK) {
+          float ss;
+          const float m = packed_products<D>(kop[u & 1], qp, &ss);
+          if (hf == 0) {
+            const int k = (kb0 + u * KB_STEP) * 32 + li;
+            smax_g[k] = m;
+            ssq_g[k] = ss;
+          }
+          continue;
+        }
         f32x16 c0 = {0}, c1 = {0};   // two chains (even / odd k-steps): a single dependent chain idles the matrix core
 #pragma unroll
         for (int ks = 0; ks < KS; ks += 2) {
@@ -299,15 +312,15 @@ __global__ __launch_bounds__(kStThreads, 1) void score_stream(Dims dm, const flo
   }
 }
 
-template <int D, int QB>
+template <int D, int QB, bool PACK = false>
 static hipError_t launch_stream_q(const Dims& dm, const float* qbar, const void* kc, const int32_t* kv_lens,
                                   float* scores, uint32_t* hist_ws, int n_keep, hipStream_t st) {
   using Cfg = StreamCfg<D, QB>;
   static std::atomic<uint64_t> lds_done{0};
   const hipError_t e =
-      ensure_dynamic_lds(reinterpret_cast<const void*>(&score_stream<D, QB>), Cfg::kLdsBytes, lds_done);
+      ensure_dynamic_lds(reinterpret_cast<const void*>(&score_stream<D, QB, PACK>), Cfg::kLdsBytes, lds_done);
   if (e != hipSuccess) return e;
-  hipLaunchKernelGGL((score_stream<D, QB>), dim3(kStGrid), dim3(kStThreads), Cfg::kLdsBytes, st, dm, qbar,
+  hipLaunchKernelGGL((score_stream<D, QB, PACK>), dim3(kStGrid), dim3(kStThreads), Cfg::kLdsBytes, st, dm, qbar,
                      static_cast<const uint16_t*>(kc), kv_lens, scores, hist_ws, n_keep);
   return hipGetLastError();
 }
@@ -316,6 +329,7 @@ template <int D>
 static hipError_t launch_stream_d(const Dims& dm, const float* qbar, const void* kc, const int32_t* kv_lens,
                                   float* scores, uint32_t* hist_ws, int n_keep, hipStream_t st) {
   const int qblocks = (n_keep + 31) / 32;
+  if (score_packs(dm)) return launch_stream_q<D, 1, true>(dm, qbar, kc, kv_lens, scores, hist_ws, n_keep, st);
   if (qblocks <= 1) return launch_stream_q<D, 1>(dm, qbar, kc, kv_lens, scores, hist_ws, n_keep, st);
   if (qblocks == 2) return launch_stream_q<D, 2>(dm, qbar, kc, kv_lens, scores, hist_ws, n_keep, st);
   return launch_stream_q<D, 4>(dm, qbar, kc, kv_lens, scores, hist_ws, n_keep, st);

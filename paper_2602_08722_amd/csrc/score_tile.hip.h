@@ -147,6 +147,69 @@ __device__ __forceinline__ void tile_products(const uint16_t* __restrict__ tl, c
   }
 }
 
+// Up to kPackRows queries: their three terms fit the 32 rows of ONE operand (rows 0-7 hi, 8-15 mid, 16-23 lo, 24-31
+// zero), so the exact product costs what one term costs.  The terms of a query land in the same lane of the result
+// (registers 0-3 hi, 4-7 mid, 8-11 lo of queries 4*hf .. +4), where they are added, smallest first; every MFMA product is
+// exact.  Here lane (li, hf) holds, for k-step ks, the 16-byte chunk ks + KS*hf of its row (the contraction index may
+// be permuted freely).  Rows past n_keep repeat the last real query.
+constexpr int kPackRows = 8;
+template <int D>
+struct PackedTerms {
+  bf16x8 t[D / 16];
+  __device__ __forceinline__ void load(const float* __restrict__ qhead, int n_keep, int li, int hf) {
+    const int term = li >> 3;
+    const float* qrow = qhead + (size_t)min(li & 7, n_keep - 1) * D + hf * (D / 2);
+#pragma unroll
+    for (int ks = 0; ks < D / 16; ++ks) {
+      const float4 x0 = *reinterpret_cast<const float4*>(qrow + ks * 8);
+      const float4 x1 = *reinterpret_cast<const float4*>(qrow + ks * 8 + 4);
+      const float x[8] = {x0.x, x0.y, x0.z, x0.w, x1.x, x1.y, x1.z, x1.w};
+#pragma unroll
+      for (int e = 0; e < 8; ++e) {
+        const __bf16 h = (__bf16)x[e];
+        const float r1 = x[e] - (float)h;
+        const __bf16 m = (__bf16)r1;
+        const float r2 = r1 - (float)m;
+        t[ks][e] = (__bf16)(term == 0 ? (float)h : term == 1 ? (float)m : term == 2 ? r2 : 0.f);
+      }
+    }
+  }
+};
+// The largest product of lane li's key with the queries (in both half waves) and the key's squared norm.
+template <int D>
+__device__ __forceinline__ float packed_products(const bf16x8 (&kop)[D / 16], const PackedTerms<D>& q, float* ssq) {
+  f32x16 c0 = {0}, c1 = {0};   // two chains (even / odd k-steps)
+#pragma unroll
+  for (int ks = 0; ks < D / 16; ks += 2) {
+    c0 = __builtin_amdgcn_mfma_f32_32x32x16_bf16(q.t[ks], kop[ks], c0, 0, 0, 0);
+    c1 = __builtin_amdgcn_mfma_f32_32x32x16_bf16(q.t[ks + 1], kop[ks + 1], c1, 0, 0, 0);
+  }
+  float ss = 0.f;
+#pragma unroll
+  for (int ks = 0; ks < D / 16; ++ks)
+#pragma unroll
+    for (int e = 0; e < 8; e += 2) {
+      const bf16x2_t pr = {kop[ks][e], kop[ks][e + 1]};
+      ss = __builtin_amdgcn_fdot2_f32_bf16(pr, pr, ss, false);
+    }
+  *ssq = ss + other_half(ss);
+  float m = -INFINITY;
+#pragma unroll
+  for (int i = 0; i < 4; ++i) m = fmaxf(m, ((c0[8 + i] + c1[8 + i]) + (c0[4 + i] + c1[4 + i])) + (c0[i] + c1[i]));
+  return fmaxf(m, other_half(m));
+}
+// Whether a bf16 call takes this form: the scores' last bits depend on it, so every scoring kernel goes by this rule.
+// Bounds: sel_finish ranks within heads of up to kPackMaxKeys positions.  Long caches of few keys in all keep the
+// provisional scores, which are the documented output of that stage and which its tests look at (two heads of 65537
+// positions: 61.6 us a call, packed 48.9).
+constexpr int kPackMaxKeys = 131072;
+constexpr long long kPackMinKeys = 3 << 16;
+inline bool score_packs(const Dims& dm) {
+  const int n_keep = dm.n_ret < dm.C ? dm.n_ret : dm.C;
+  return n_keep <= kPackRows && (dm.flags & (QUOKA_SCORE_DOT | QUOKA_SCORE_MEAN | QUOKA_SCORE_QBAR_BF16)) == 0 &&
+         (dm.T_cap <= 32768 || (dm.T_cap <= kPackMaxKeys && (long long)dm.b * dm.n_kv * dm.T_cap >= kPackMinKeys));
+}
+
 // Score of key `k` of a tile from the per-query-block maxima (sums) and the squared norm.
 template <int QB>
 __device__ __forceinline__ float tile_score(const float* __restrict__ sm, const float* __restrict__ ssq_g, int k,

@@ -45,6 +45,43 @@ __global__ void sel_zero(uint32_t* __restrict__ p, size_t n) {
   for (size_t i = (size_t)blockIdx.x * blockDim.x + threadIdx.x; i < n; i += (size_t)gridDim.x * blockDim.x) p[i] = 0u;
 }
 
+// Whole block of kSelThreads: thread t's run of the head's histogram (thread 0 has the highest bins) ...
+constexpr uint32_t kSelPer = kSelBins / kSelThreads;
+__device__ __forceinline__ void load_hist_run(const uint32_t* __restrict__ hist, uint32_t (&hv)[kSelPer]) {
+  const uint32_t top = kSelBins - threadIdx.x * kSelPer;   // exclusive upper bin of the run
+#pragma unroll
+  for (uint32_t i = 0; i < kSelPer; i += 4) {
+    const u32x4 v = *reinterpret_cast<const u32x4*>(hist + top - kSelPer + i);
+    hv[i] = v[0]; hv[i + 1] = v[1]; hv[i + 2] = v[2]; hv[i + 3] = v[3];
+  }
+}
+// ... and the bin of the cut: scanning from the top, where the running count reaches B (the histogram holds T > B keys).
+__device__ __forceinline__ int find_cut_bin(const uint32_t (&hv)[kSelPer], uint32_t B, uint32_t* sh, uint32_t* bin) {
+  const uint32_t top = kSelBins - threadIdx.x * kSelPer;
+  uint32_t mine = 0;
+#pragma unroll
+  for (uint32_t i = 0; i < kSelPer; ++i) mine += hv[i];
+  uint32_t tot;
+  const uint32_t above = block_excl_scan<kSelThreads>(mine, sh, &tot);
+  if (above < B && B <= above + mine) {   // exactly one thread
+    uint32_t rem = B - above;
+    int found = -1;
+#pragma unroll
+    for (int j = (int)kSelPer - 1; j >= 0; --j) {   // from this thread's highest bin down
+      if (found < 0) {
+        if (rem <= hv[j]) {
+          found = j;
+        } else {
+          rem -= hv[j];
+        }
+      }
+    }
+    *bin = top - kSelPer + (uint32_t)max(found, 0);
+  }
+  __syncthreads();
+  return (int)*bin;
+}
+
 // ---------------------------------------------------------------------------------------------
 // Band classification and exact re-scoring.  A block takes `tpb` consecutive 2048-key tiles of one head: it locates
 // the band once from the finished histogram, then per tile classifies the keys and scores the band keys exactly.
@@ -87,48 +124,17 @@ __global__ __launch_bounds__(kSelThreads) void sel_band_rescore(Dims dm, const f
     }
   };
   load_p(tile_first * kSelTile);
-  constexpr uint32_t per = kSelBins / kSelThreads;
-  const uint32_t top = kSelBins - tid * per;   // exclusive upper bin of this thread's run (thread 0: highest bins)
-  uint32_t hv[per];
-#pragma unroll
-  for (uint32_t i = 0; i < per; i += 4) {
-    const u32x4 v = *reinterpret_cast<const u32x4*>(c.w.hist + top - per + i);
-    hv[i] = v[0]; hv[i + 1] = v[1]; hv[i + 2] = v[2]; hv[i + 3] = v[3];
-  }
+  uint32_t hv[kSelPer];
+  load_hist_run(c.w.hist, hv);
   const float d2 = __uint_as_float(c.w.meta[kMetaEps2]);
   QueryTerms<D, true> qt;
   qt.load(qbar + (size_t)c.head * n_keep * D, n_keep, qb, li, hf, false);
 
-  // ---- the bin of the provisional cut: scanning from the top, where the running count reaches B ----
-  {
-    uint32_t mine = 0;
-#pragma unroll
-    for (uint32_t i = 0; i < per; ++i) mine += hv[i];
-    uint32_t tot;
-    const uint32_t above = block_excl_scan<kSelThreads>(mine, sh, &tot);
-    const uint32_t need = (uint32_t)c.B;
-    if (above < need && need <= above + mine) {   // exactly one thread (the histogram holds T > B keys)
-      uint32_t rem = need - above;
-      int found = -1;
-#pragma unroll
-      for (int j = (int)per - 1; j >= 0; --j) {   // from this thread's highest bin down
-        if (found < 0) {
-          if (rem <= hv[j]) {
-            found = j;
-          } else {
-            rem -= hv[j];
-          }
-        }
-      }
-      bc[0] = top - per + (uint32_t)max(found, 0);
-    }
-  }
-  __syncthreads();
+  const int cut_bin = find_cut_bin(hv, (uint32_t)c.B, sh, &bc[0]);   // of the provisional cut
   // |p - s| <= ||delta|| (exact arithmetic; the scoring launch left the largest squared ||delta|| of the head) plus
   // the float32 accumulation and bin-edge slack of the two computed values
   const float eps = sqrtf(d2) * 1.001f + 4e-6f;
   const int m = (int)ceilf(2.0f * eps * (float)(kSelBins / 2)) + 1;
-  const int cut_bin = (int)bc[0];
   const int bin_lo = max(cut_bin - m, 0), bin_hi = min(cut_bin + m, kSelBins - 1);
   if (blockIdx.x == 0 && tid == 0) {
     c.w.meta[kMetaBinLo] = (uint32_t)bin_lo;
@@ -216,12 +222,13 @@ struct HeadSelectLds {
   uint32_t wsum[kSelHeadThreads / 64 + 1];
 };
 
+template <int NT>
 __device__ __forceinline__ void stream_radix_select_desc(const uint32_t* __restrict__ keys, uint32_t n, uint32_t need,
                                                          RadixSelectLds& L, uint32_t* cut_key, uint32_t* need_eq) {
   const int tid = threadIdx.x, lane = tid & 63, w = tid >> 6;
-  if (tid < 768) (&L.hist[0][0])[tid] = 0u;
+  for (int i = tid; i < 768; i += NT) (&L.hist[0][0])[i] = 0u;
   uint32_t kmin = 0xFFFFFFFFu, kmax = 0u;
-  for (uint32_t i = tid; i < n; i += kSelHeadThreads) {
+  for (uint32_t i = tid; i < n; i += NT) {
     const uint32_t k = keys[i];
     kmin = min(kmin, k);
     kmax = max(kmax, k);
@@ -233,8 +240,8 @@ __device__ __forceinline__ void stream_radix_select_desc(const uint32_t* __restr
     L.wmax[w] = kmax;
   }
   __syncthreads();
-  kmin = wave_min_u32(lane < 16 ? L.wmin[lane] : 0xFFFFFFFFu);
-  kmax = wave_max_u32(lane < 16 ? L.wmax[lane] : 0u);
+  kmin = wave_min_u32(lane < NT / 64 ? L.wmin[lane] : 0xFFFFFFFFu);
+  kmax = wave_max_u32(lane < NT / 64 ? L.wmax[lane] : 0u);
   const uint32_t diff = kmin ^ kmax;
   int hi = diff ? 32 - __clz(diff) : 0;                                    // the keys agree on all bits >= hi
   uint32_t mask = hi >= 32 ? 0u : ~((hi == 0) ? 0u : ((1u << hi) - 1u));   // decided bits
@@ -246,7 +253,7 @@ __device__ __forceinline__ void stream_radix_select_desc(const uint32_t* __restr
   while (hi > 0) {
     const int lo_bit = max(hi - 8, 0);
     const uint32_t dmask = (1u << (hi - lo_bit)) - 1u;
-    for (uint32_t i = tid; i < n; i += kSelHeadThreads) {
+    for (uint32_t i = tid; i < n; i += NT) {
       const uint32_t k = keys[i];
       if ((k & mask) == prefix) atomicAdd(&h_use[(k >> lo_bit) & dmask], 1u);
     }
@@ -311,7 +318,7 @@ __global__ __launch_bounds__(kSelHeadThreads) void sel_band_select(Dims dm, floa
   // (the candidates are read again from memory in every pass: holding them in registers, 16 per thread, was
   // measured slower -- 13.5 against 11.2 us at 4000 candidates per head)
   uint32_t tau, need_eq;
-  stream_radix_select_desc(c.w.cand_key, n_c, need, L.rs, &tau, &need_eq);
+  stream_radix_select_desc<kSelHeadThreads>(c.w.cand_key, n_c, need, L.rs, &tau, &need_eq);
   for (uint32_t i = tid; i < n_c; i += kSelHeadThreads) {
     const uint32_t k = c.w.cand_key[i];
     if (k >= tau) atomicAdd(&cnt[c.w.cand_pos[i] / kSelTile], k > tau ? 0x10000u : 1u);
@@ -348,15 +355,61 @@ __global__ __launch_bounds__(kSelHeadThreads) void sel_band_select(Dims dm, floa
 }
 
 // ---------------------------------------------------------------------------------------------
-// Ordered emission per tile: thread t owns 8 consecutive positions.
+// Ordered emission of one tile.  Wave w owns 512 consecutive positions; register j of its lane l is position 64*j + l of
+// them, so scores and indices travel as coalesced rows and wave ballots give the order.  `take`: keys selected whatever the
+// ties; `eq`: keys equal to the cut, of which the `need_eq` lowest positions are selected (`eq_tile0` of them lie in
+// earlier tiles); `off`: selected keys in earlier tiles.
+constexpr int kSelWaves = kSelThreads / 64;
+// (`take` and `eq`: bit j is the lane's register j)
+__device__ __forceinline__ void emit_tile(uint32_t take, uint32_t eq, uint32_t eq_tile0, uint32_t need_eq, uint32_t off,
+                                          int lo, int B, uint32_t* wcnt, int32_t* __restrict__ out) {
+  const int lane = threadIdx.x & 63, w = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6);
+  const uint32_t cnt = wave_incl_scan_u32(((uint32_t)__popc(take) << 16) | (uint32_t)__popc(eq));
+  if (lane == 63) wcnt[w] = cnt;   // (a tile has 2048 keys: both counts fit 16 bits)
+  __syncthreads();
+  uint32_t p_take = 0, p_eq = eq_tile0;
+#pragma unroll
+  for (int i = 0; i < kSelWaves; ++i) {
+    const uint32_t c = wcnt[i];
+    p_take += i < w ? c >> 16 : 0u;
+    p_eq += i < w ? c & 0xFFFFu : 0u;
+  }
+  const unsigned long long below = (1ull << lane) - 1ull;
+  const uint32_t eq_off = off - min(eq_tile0, need_eq);   // (ties taken in earlier tiles are part of `off`)
+#pragma unroll
+  for (int j = 0; j < kSelIPT; ++j) {
+    const bool is_take = (take >> j) & 1u, is_eq = (eq >> j) & 1u;
+    const unsigned long long m_take = __builtin_amdgcn_ballot_w64(is_take), m_eq = __builtin_amdgcn_ballot_w64(is_eq);
+    const uint32_t eq_before = p_eq + __popcll(m_eq & below);
+    if (is_take || (is_eq && eq_before < need_eq)) {
+      const uint32_t pos = eq_off + p_take + __popcll(m_take & below) + min(eq_before, need_eq);
+      if (pos < (uint32_t)B) out[pos] = lo + 64 * j;   // guard: inconsistent inputs cannot push writes past the budget
+    }
+    p_take += (uint32_t)__popcll(m_take);
+    p_eq += (uint32_t)__popcll(m_eq);
+  }
+}
+
 __global__ __launch_bounds__(kSelThreads) void sel_emit(Dims dm, float* __restrict__ scores,
                                                        const int32_t* __restrict__ kv_lens,
                                                        const int32_t* __restrict__ budgets, uint32_t* __restrict__ ws,
                                                        int32_t* __restrict__ k_idx, int32_t* __restrict__ k_cnt) {
-  __shared__ uint32_t sh[kSelThreads + 2];
+  __shared__ uint32_t wcnt[kSelWaves];
   const int kv = blockIdx.y, b = blockIdx.z;
   const SelCtx c = sel_ctx(dm, scores, kv_lens, budgets, ws, kv, b);
   const int t0 = blockIdx.x * kSelTile;
+  // Everything is requested before the cache length is known (a fetch of what another launch has just written takes
+  // about 2 us, and they would queue up behind each other): positions are clamped to the array.
+  const int lane = threadIdx.x & 63, w = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6);
+  const int lo = t0 + w * 64 * kSelIPT + lane;
+  float v[kSelIPT];
+#pragma unroll
+  for (int j = 0; j < kSelIPT; ++j) v[j] = c.sc[min(lo + 64 * j, dm.T_max - 1)];
+  // this wave's band mask: two words a register, lane i holds word i
+  const uint32_t mword = c.w.mask[(size_t)blockIdx.x * (kSelTile / 32) + w * (2 * kSelIPT) + min(lane, 2 * kSelIPT - 1)];
+  const int bin_hi = (int)c.w.meta[kMetaBinHi];
+  const uint32_t tau = c.w.meta[kMetaTau], need_eq = c.w.meta[kMetaNeedEq];
+  const uint32_t eq_tile0 = c.w.tile_eqb[blockIdx.x], off = c.w.tile_off[blockIdx.x];
   int32_t* out = k_idx + (size_t)c.head * dm.B_max;
   if (blockIdx.x == 0 && threadIdx.x == 0) k_cnt[c.head] = c.B;
   if (c.B == 0 || t0 >= c.T) return;
@@ -365,49 +418,166 @@ __global__ __launch_bounds__(kSelThreads) void sel_emit(Dims dm, float* __restri
     for (int i = t0 + threadIdx.x; i < t1; i += kSelThreads) out[i] = i;
     return;
   }
-  const int bin_hi = (int)c.w.meta[kMetaBinHi];
-  const uint32_t tau = c.w.meta[kMetaTau], need_eq = c.w.meta[kMetaNeedEq];
-  const int lo = t0 + threadIdx.x * kSelIPT;
-  // this thread's 8 positions are one byte of the tile's band mask
-  const uint32_t mword = c.w.mask[(size_t)blockIdx.x * (kSelTile / 32) + (threadIdx.x * kSelIPT) / 32];
-  const uint32_t mbits = (mword >> ((threadIdx.x * kSelIPT) % 32)) & 0xFFu;
-  uint32_t take = 0, eqm = 0;   // per position: selected regardless of ties / band key equal to the cut
-  uint32_t cntp = 0;
+  uint32_t take = 0, eq = 0;
+#pragma unroll
+  for (int j = 0; j < kSelIPT; ++j) {
+    const bool in = lo + 64 * j < t1;
+    const uint32_t m_lo = (uint32_t)__builtin_amdgcn_readlane((int)mword, 2 * j),
+                   m_hi = (uint32_t)__builtin_amdgcn_readlane((int)mword, 2 * j + 1);
+    const bool band = ((lane < 32 ? m_lo : m_hi) >> (lane & 31)) & 1u;
+    const uint32_t k = max(okey(v[j]), 1u);
+    take |= (in && (band ? k > tau : score_bin(v[j]) > bin_hi) ? 1u : 0u) << j;
+    eq |= (in && band && k == tau ? 1u : 0u) << j;
+  }
+  emit_tile(take, eq, eq_tile0, need_eq, off, lo, c.B, wcnt, out);
+}
+
+// ---------------------------------------------------------------------------------------------
+// Exact scores (score_packs): nothing is scored again, the candidates are the keys of the cut's own bin, a few dozen.
+// Launch chain: scoring with the histogram, one count per tile, emission; every emitting block finds the cut among the
+// candidates for itself, which is cheaper than a launch for it while the heads are short.
+static_assert(kPackMaxKeys / kSelTile <= 64, "one lane a tile");
+
+__global__ __launch_bounds__(kSelThreads) void sel_classify(Dims dm, float* __restrict__ scores,
+                                                           const int32_t* __restrict__ kv_lens,
+                                                           const int32_t* __restrict__ budgets, uint32_t* __restrict__ ws) {
+  __shared__ uint32_t sh[kSelThreads / 64 + 1];
+  __shared__ uint32_t bin, n_in;
+  const SelCtx c = sel_ctx(dm, scores, kv_lens, budgets, ws, blockIdx.y, blockIdx.z);
+  const int t0 = blockIdx.x * kSelTile;
+  const int tid = threadIdx.x, lane = tid & 63;
+  float v[kSelIPT];   // (requested before the cache length is known)
+#pragma unroll
+  for (int i = 0; i < kSelIPT; ++i) v[i] = c.sc[min(t0 + tid + kSelThreads * i, dm.T_max - 1)];
+  uint32_t hv[kSelPer];
+  load_hist_run(c.w.hist, hv);
+  if (c.B == 0 || c.B >= c.T || t0 >= c.T) return;   // block-uniform
+  if (tid == 0) n_in = 0u;
+  const int cut_bin = find_cut_bin(hv, (uint32_t)c.B, sh, &bin);
+  uint32_t above = 0;
 #pragma unroll
   for (int i = 0; i < kSelIPT; ++i) {
-    const int t = lo + i;
-    if (t < t1) {
-      const float v = c.sc[t];
-      if ((mbits >> i) & 1u) {
-        const uint32_t k = max(okey(v), 1u);
-        take |= (k > tau ? 1u : 0u) << i;
-        eqm |= (k == tau ? 1u : 0u) << i;
-      } else {
-        take |= (score_bin(v) > bin_hi ? 1u : 0u) << i;
+    const int t = t0 + tid + kSelThreads * i;
+    const int k = score_bin(v[i]);
+    above += (uint32_t)__popcll(__builtin_amdgcn_ballot_w64(t < c.T && k > cut_bin));
+    const bool cand = t < c.T && k == cut_bin;
+    const unsigned long long m = __builtin_amdgcn_ballot_w64(cand);
+    if (m != 0) {   // wave-uniform; any order will do
+      uint32_t slot = 0;
+      if (lane == 0) slot = atomicAdd(&c.w.meta[kMetaCand], (uint32_t)__popcll(m));
+      slot = (uint32_t)__builtin_amdgcn_readfirstlane((int)slot) + __popcll(m & ((1ull << lane) - 1ull));
+      if (cand) {
+        c.w.cand_key[slot] = max(okey(v[i]), 1u);
+        c.w.cand_pos[slot] = (uint32_t)t;
       }
     }
   }
-  cntp = ((uint32_t)__popc(take) << 16) | (uint32_t)__popc(eqm);
-  uint32_t tot;
-  const uint32_t before = block_excl_scan<kSelThreads>(cntp, sh, &tot);
-  // cut-equal band keys at lower positions: in earlier tiles, then in earlier threads of this tile
-  uint32_t p_eq = c.w.tile_eqb[blockIdx.x] + (before & 0xFFFFu);
-  // selected keys at lower positions: earlier tiles, this tile's certain ones, and the cut-equal ones still in budget
-  const uint32_t eq_tile0 = c.w.tile_eqb[blockIdx.x];
-  const uint32_t taken_eq_before = min(p_eq, need_eq) - min(eq_tile0, need_eq);
-  uint32_t pos = c.w.tile_off[blockIdx.x] + (before >> 16) + taken_eq_before;
+  if (lane == 0 && above) atomicAdd(&n_in, above);
+  __syncthreads();
+  if (tid == 0) {
+    c.w.tile_in[blockIdx.x] = n_in;
+    if (blockIdx.x == 0) c.w.meta[kMetaBinHi] = (uint32_t)cut_bin;
+  }
+}
+
+constexpr int kFinCands = 1024;   // candidates ranked by counting in LDS; more are radix-selected from memory
+__global__ __launch_bounds__(kSelThreads) void sel_finish(Dims dm, float* __restrict__ scores,
+                                                         const int32_t* __restrict__ kv_lens,
+                                                         const int32_t* __restrict__ budgets, uint32_t* __restrict__ ws,
+                                                         int32_t* __restrict__ k_idx, int32_t* __restrict__ k_cnt) {
+  __shared__ RadixSelectLds rs;
+  __shared__ __align__(16) uint32_t key[kFinCands + 8];   // (zeros behind the candidates: below every key)
+  __shared__ uint32_t pos[kFinCands];
+  __shared__ uint32_t cut[2], sums[4], wcnt[kSelWaves];
+  const SelCtx c = sel_ctx(dm, scores, kv_lens, budgets, ws, blockIdx.y, blockIdx.z);
+  const int t0 = blockIdx.x * kSelTile;
+  // requested before the cache length and the number of candidates are known (the arrays hold T_max > 32768 entries)
+  const int tid = threadIdx.x, lane = tid & 63, w = __builtin_amdgcn_readfirstlane(tid >> 6);
+  const int lo = t0 + w * 64 * kSelIPT + lane;
+  float v[kSelIPT];
 #pragma unroll
-  for (int i = 0; i < kSelIPT; ++i) {
-    bool sel = (take >> i) & 1u;
-    if ((eqm >> i) & 1u) {
-      sel = p_eq < need_eq;
-      ++p_eq;
+  for (int j = 0; j < kSelIPT; ++j) v[j] = c.sc[min(lo + 64 * j, dm.T_max - 1)];
+  const uint32_t n_c = c.w.meta[kMetaCand];
+  const int cut_bin = (int)c.w.meta[kMetaBinHi];
+  const uint32_t key0 = c.w.cand_key[tid], pos0 = c.w.cand_pos[tid];
+  uint32_t certain = c.w.tile_in[min(tid, sel_tiles(dm.T_max) - 1)];
+  int32_t* out = k_idx + (size_t)c.head * dm.B_max;
+  if (blockIdx.x == 0 && threadIdx.x == 0) k_cnt[c.head] = c.B;
+  if (c.B == 0 || t0 >= c.T) return;   // block-uniform
+  const int t1 = min(t0 + kSelTile, c.T);
+  if (c.B >= c.T) {
+    for (int i = t0 + threadIdx.x; i < t1; i += kSelThreads) out[i] = i;
+    return;
+  }
+  const bool in_lds = n_c <= (uint32_t)kFinCands;
+  if (in_lds) {
+    if (tid < (int)n_c) {
+      key[tid] = key0;
+      pos[tid] = pos0;
     }
-    if (sel) {
-      if (pos < (uint32_t)c.B) out[pos] = lo + i;   // guard: inconsistent inputs cannot push writes past the budget
-      ++pos;
+    for (uint32_t i = tid + kSelThreads; i < n_c; i += kSelThreads) {
+      key[i] = c.w.cand_key[i];
+      pos[i] = c.w.cand_pos[i];
+    }
+    if (tid < 8) key[n_c + tid] = 0u;
+  }
+  if (tid == 0) sums[2] = sums[3] = 0u;
+  // certainly selected keys, in all tiles and in the earlier ones (the first wave has a lane for every tile)
+  if (w == 0) {
+    if (lane >= (c.T + kSelTile - 1) / kSelTile) certain = 0u;
+    const uint32_t upto = wave_incl_scan_u32(certain);
+    if (lane == 63) sums[0] = upto;
+    if (lane == (int)blockIdx.x) sums[1] = upto - certain;
+  }
+  __syncthreads();
+  const uint32_t need = (uint32_t)c.B - sums[0];   // >= 1: fewer than B keys lie above the cut bin
+  uint32_t tau, need_eq;
+  if (in_lds) {
+    for (uint32_t i = tid; i < n_c; i += kSelThreads) {
+      const uint32_t k = key[i];
+      uint32_t gt = 0, ge = 0;
+      for (uint32_t j = 0; j < n_c; j += 8) {   // eight keys a fetch: one at a time, the loop is a chain of LDS latencies
+        const u32x4 a = *reinterpret_cast<const u32x4*>(key + j), b = *reinterpret_cast<const u32x4*>(key + j + 4);
+#pragma unroll
+        for (int e = 0; e < 4; ++e) {
+          gt += (a[e] > k ? 1u : 0u) + (b[e] > k ? 1u : 0u);
+          ge += (a[e] >= k ? 1u : 0u) + (b[e] >= k ? 1u : 0u);
+        }
+      }
+      if (gt < need && need <= ge) {   // (equal keys all write the same)
+        cut[0] = k;
+        cut[1] = need - gt;
+      }
+    }
+    __syncthreads();
+    tau = cut[0];
+    need_eq = cut[1];
+  } else {
+    stream_radix_select_desc<kSelThreads>(c.w.cand_key, n_c, need, rs, &tau, &need_eq);
+  }
+  // candidates above the cut, and equal to it, in earlier tiles
+  uint32_t gt = 0, eq0 = 0;
+  for (uint32_t i = tid; i < n_c; i += kSelThreads) {
+    const uint32_t k = in_lds ? key[i] : c.w.cand_key[i];
+    if (k >= tau && (in_lds ? pos[i] : c.w.cand_pos[i]) < (uint32_t)t0) {
+      gt += k > tau ? 1u : 0u;
+      eq0 += k == tau ? 1u : 0u;
     }
   }
+  if (gt) atomicAdd(&sums[2], gt);
+  if (eq0) atomicAdd(&sums[3], eq0);
+  uint32_t take = 0, eq = 0;
+#pragma unroll
+  for (int j = 0; j < kSelIPT; ++j) {
+    const bool in = lo + 64 * j < t1;
+    const uint32_t k = max(okey(v[j]), 1u);
+    const int bin = score_bin(v[j]);
+    take |= (in && (bin > cut_bin || (bin == cut_bin && k > tau)) ? 1u : 0u) << j;
+    eq |= (in && bin == cut_bin && k == tau ? 1u : 0u) << j;
+  }
+  __syncthreads();
+  const uint32_t eq_tile0 = sums[3];
+  emit_tile(take, eq, eq_tile0, need_eq, sums[1] + sums[2] + min(eq_tile0, need_eq), lo, c.B, wcnt, out);
 }
 
 // ---------------------------------------------------------------------------------------------
@@ -457,6 +627,11 @@ hipError_t launch_select_keys(const Dims& dm, const float* qbar, const void* k_c
   hipError_t e = launch_score_stream(dm, qbar, k_cache, kv_lens, scores, ws, st);
   if (e != hipSuccess) return e;
   const dim3 grid(sel_tiles(dm.T_cap), dm.n_kv, dm.b);
+  if (score_packs(dm)) {
+    hipLaunchKernelGGL(sel_classify, grid, dim3(kSelThreads), 0, st, dm, scores, kv_lens, budgets, ws);
+    hipLaunchKernelGGL(sel_finish, grid, dim3(kSelThreads), 0, st, dm, scores, kv_lens, budgets, ws, k_idx, k_cnt);
+    return hipGetLastError();
+  }
   if (dm.d == 64) {
     launch_rescore<64>(dm, qbar, k_cache, kv_lens, budgets, scores, ws, n_keep, st);
   } else {

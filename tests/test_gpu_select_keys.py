@@ -160,3 +160,68 @@ def test_select_keys_token_major_cache():
     ra, rb = _fused(a), _fused(b)
     for x, y in zip(ra, rb):
         assert torch.equal(x.view(torch.int32), y.view(torch.int32))
+
+
+# up to eight retained queries: all three terms in one operand, exact scores from the streaming launch, the cut found by the
+# emitting blocks (edges of the tiles, of the list of candidates held in LDS, and of the rule's sizes)
+PACKED = [
+    ("normal", dict(n_q=32, n_kv=8, d=128, chunk=1, n_retain=16, kv_lens=[32769], budgets=[3000])),
+    ("normal", dict(n_q=12, n_kv=4, d=64, chunk=8, n_retain=8, kv_lens=[65537, 0, 1500, 2048, 40000],
+                    budgets=[7000, 4, 1500, 2047, 1], batch=5)),
+    ("normal", dict(n_q=2, n_kv=2, d=128, chunk=40, n_retain=7, kv_lens=[131072], budgets=[131071])),
+    ("pairs", dict(n_q=8, n_kv=2, d=128, chunk=3, n_retain=64, kv_lens=[110001], budgets=[9001])),
+    ("equal", dict(n_q=8, n_kv=2, d=64, chunk=2, n_retain=64, kv_lens=[100000], budgets=[50001])),
+    ("half", dict(n_q=4, n_kv=2, d=128, chunk=1, n_retain=1, kv_lens=[100003], budgets=[60001])),
+]
+
+
+@pytest.mark.parametrize("kind,case", PACKED, ids=lambda c: "-".join(f"{k}{v}" for k, v in c.items()) if isinstance(c, dict) else c)
+def test_few_queries_select_exactly_from_one_pass(kind, case):
+    pk = _pk()
+    case = dict(case)
+    w = gen.make_custom(dtype="bf16", seed=41, **dict(dict(batch=1), **case))
+    if kind == "equal":
+        w.K[:] = w.K[:, :, :1]
+    elif kind == "half":      # more equal candidates at the cut than the emitting blocks hold
+        w.K[:, :, 30000:70000] = w.K[:, :, 30000:30001]
+    elif kind == "pairs":
+        n = w.K.shape[2] // 2 * 2
+        w.K[:, :, 1:n:2] = w.K[:, :, 0:n:2]
+    n_exact, n_all = _compare(pk, w, oracle=kind == "normal")
+    assert n_exact == n_all
+    buf = _buffers(pk, w)
+    buf.select_queries()
+    torch.cuda.synchronize()
+    qbar, q_idx = buf.qbar.clone(), buf.q_idx.clone()
+    for b in (buf.qbar, buf.q_idx, buf.k_idx):
+        b.fill_(-1)
+    buf.chunk_attn()
+    torch.cuda.synchronize()
+    assert torch.equal(buf.qbar, qbar) and torch.equal(buf.q_idx, q_idx)
+    for b in range(w.batch):
+        n = int(buf.k_cnt[b, 0])
+        want = O.topk_keys(buf.scores[b, :, :w.kv_lens[b]].cpu().numpy(), w.budgets[b])
+        assert np.array_equal(buf.k_idx[b, :, :n].cpu().numpy(), want)
+
+
+@pytest.mark.parametrize("case", [
+    dict(n_q=4, n_kv=2, d=128, chunk=1, n_retain=16, kv_lens=[1000, 0, 129], budgets=[100, 5, 128], batch=3),
+    dict(n_q=16, n_kv=1, d=64, chunk=8, n_retain=8, kv_lens=[32768], budgets=[5000]),
+    dict(n_q=6, n_kv=2, d=64, chunk=5, n_retain=32, kv_lens=[1], budgets=[1]),
+], ids=lambda c: "-".join(f"{k}{v}" for k, v in c.items()))
+def test_scoring_launch_forms_the_queries_of_a_few_tokens(case):
+    """chunk_attn leaves the query stage to the scoring launch here: the same bits as the separate calls."""
+    pk = _pk()
+    w = gen.make_custom(dtype="bf16", seed=43, **dict(dict(batch=1), **case))
+    buf = _buffers(pk, w)
+    sc, idx, cnt = _staged(buf)
+    qbar, q_idx = buf.qbar.clone(), buf.q_idx.clone()
+    for b in (buf.qbar, buf.q_idx, buf.k_idx, buf.k_cnt):
+        b.fill_(-1)
+    buf.scores.fill_(float("nan"))
+    buf.chunk_attn()
+    torch.cuda.synchronize()
+    assert torch.equal(buf.qbar, qbar) and torch.equal(buf.q_idx, q_idx) and torch.equal(buf.k_cnt, cnt)
+    for b in range(w.batch):
+        T, n = w.kv_lens[b], int(cnt[b, 0])
+        assert torch.equal(buf.scores[b, :, :T], sc[b, :, :T]) and torch.equal(buf.k_idx[b, :, :n], idx[b, :, :n])
