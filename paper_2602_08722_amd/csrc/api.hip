@@ -345,7 +345,7 @@ quoka_status quoka_dense_attn(const quoka_shape* shape, const void* q, const voi
 static quoka_status select_keys_common(const Dims& dm, int dtype, const float* qbar, const void* k_cache,
                                        const int32_t* kv_lens, const int32_t* budgets, float* scores, int32_t* k_idx,
                                        int32_t* k_cnt, void* workspace, const WsLayout& l, hipStream_t hs,
-                                       bool sel_ws_is_zero) {
+                                       bool sel_ws_is_zero, const quoka::FusedQbar& fq = {}) {
   if (dm.T_max > 0 && quoka::select_keys_two_pass_applies(dm, dtype)) {
     uint32_t* sel_ws = reinterpret_cast<uint32_t*>(static_cast<char*>(workspace) + l.sel_off);
     return from_hip(quoka::launch_select_keys(dm, qbar, k_cache, kv_lens, budgets, scores, k_idx, k_cnt, sel_ws, hs,
@@ -355,7 +355,7 @@ static quoka_status select_keys_common(const Dims& dm, int dtype, const float* q
   const bool fuse_clear = quoka::topk_uses_ws(dm);
   const size_t topk_words = fuse_clear ? quoka::topk_ws_words(dm) : 0;
   quoka_status st = from_hip(quoka::launch_score_keys(dm, dtype, qbar, k_cache, kv_lens, scores, hs,
-                                                      fuse_clear ? topk_ws : nullptr, topk_words));
+                                                      fuse_clear ? topk_ws : nullptr, topk_words, fq));
   if (st != QUOKA_OK) return st;
   return from_hip(quoka::launch_topk_keys(dm, scores, kv_lens, budgets, k_idx, k_cnt, topk_ws, hs, fuse_clear));
 }
@@ -400,11 +400,16 @@ static quoka_status chunk_common(const quoka_shape* shape, const CallInfo& info,
   const bool two_pass = dm.T_max > 0 && quoka::select_keys_two_pass_applies(dm, shape->dtype);
   uint32_t* sel_ws = reinterpret_cast<uint32_t*>(static_cast<char*>(workspace) + l.sel_off);
   float* sq_ws = reinterpret_cast<float*>(static_cast<char*>(workspace) + l.select_off);
-  st = from_hip(quoka::launch_select_queries(dm, shape->dtype, q, q_idx, qbar, sq_ws, hs, two_pass ? sel_ws : nullptr,
-                                             two_pass ? quoka::select_keys_zero_words(dm) : 0));
-  if (st != QUOKA_OK) return st;
+  quoka::FusedQbar fq;
+  if (!two_pass && quoka::score_forms_qbar(dm, shape->dtype)) {   // a few tokens: one launch less
+    fq = quoka::FusedQbar{q, q_idx, qbar};
+  } else {
+    st = from_hip(quoka::launch_select_queries(dm, shape->dtype, q, q_idx, qbar, sq_ws, hs, two_pass ? sel_ws : nullptr,
+                                               two_pass ? quoka::select_keys_zero_words(dm) : 0));
+    if (st != QUOKA_OK) return st;
+  }
   st = select_keys_common(dm, shape->dtype, qbar, k_cache, kv_lens, budgets, scores, k_idx, k_cnt, workspace, l, hs,
-                          two_pass);
+                          two_pass, fq);
   if (st != QUOKA_OK) return st;
   return attn_common(shape, info, q, k_cache, v_cache, k_idx, k_cnt, true, k_chunk, v_chunk, out, lse, workspace,
                      workspace_bytes, stream);

@@ -34,8 +34,16 @@ hipError_t launch_select_queries(const Dims& dm, int dtype, const void* q, int32
 // --- key scoring (score_keys.hip) ---------------------------------------------------------------
 // `zero` / `zero_words`: optional side job for the fused call -- the scoring blocks clear that many 32-bit words (the
 // histograms the multi-block top-k that follows would otherwise clear with a launch of its own).
+// `fq` (where score_forms_qbar): the query stage has not run; the launch forms Qbar and q_idx itself.
+struct FusedQbar {
+  const void* q = nullptr;
+  int32_t* q_idx = nullptr;
+  float* qbar = nullptr;
+};
+bool score_forms_qbar(const Dims& dm, int dtype);
 hipError_t launch_score_keys(const Dims& dm, int dtype, const float* qbar, const void* k_cache, const int32_t* kv_lens,
-                             float* scores, hipStream_t st, uint32_t* zero = nullptr, size_t zero_words = 0);
+                             float* scores, hipStream_t st, uint32_t* zero = nullptr, size_t zero_words = 0,
+                             const FusedQbar& fq = {});
 
 // --- top-B key selection (topk_keys.hip) ----------------------------------------------------------
 size_t topk_ws_words(const Dims& dm);

@@ -14,6 +14,7 @@
 
 #include "common.hip.h"
 #include "kernels.h"
+#include "qbar_row.hip.h"
 #include "score_tile.hip.h"
 
 namespace quoka {
@@ -21,12 +22,15 @@ namespace quoka {
 // EXACT: Qbar enters as the three-term split (float32-exact products).  Otherwise it is rounded to bf16 once and
 // only that term is multiplied: a third of the matrix work, scores within 2^-9 * sum|qbar_i| of the exact ones.
 // PACK (QB = 1, EXACT): at most kPackRows queries, all three terms in one operand.
-template <int D, int QB, bool EXACT, bool PACK>
+// FUSE (PACK, every query retained): Qbar is not there yet.  Every block works its head's few rows out for itself, in
+// place of reading them (8 heads, 8192 keys, one query: FIGURE).
+template <int D, int QB, bool EXACT, bool PACK, bool FUSE>
 __global__ __launch_bounds__(kScThreads, 2) void score_bf16(Dims dm, const float* __restrict__ qbar,
                                                            const uint16_t* __restrict__ kc,
                                                            const int32_t* __restrict__ kv_lens,
                                                            float* __restrict__ scores, int n_keep, int tiles_per_wg,
-                                                           uint32_t* __restrict__ zero, uint32_t zero_words) {
+                                                           uint32_t* __restrict__ zero, uint32_t zero_words,
+                                                           FusedQbar fq) {
   using Cfg = ScoreCfg<D, QB>;
   clear_words(zero, zero_words);
   constexpr int LD = Cfg::LD, CG = Cfg::CG, RPI = Cfg::RPI, NLD = Cfg::NLD;
@@ -64,19 +68,34 @@ __global__ __launch_bounds__(kScThreads, 2) void score_bf16(Dims dm, const float
   };
   issue(0, RA);   // the first K tile is in flight while the length arrives and the query operands are prepared
   const int T = min(kv_lens[b * dm.ls], dm.T_cap);
+  const float* qhead = qbar + (size_t)(b * dm.n_kv + kv) * n_keep * D;
+  if constexpr (FUSE) {
+    __shared__ float qrows[kPackRows * D];
+    if (t_begin >= T && blockIdx.x != 0) return;   // block-uniform
+    constexpr int EPL = D / 64;
+    for (int r = w; r < n_keep; r += kScThreads / 64) {
+      float row[EPL];
+      qbar_row<uint16_t, D, kIdentity>(dm, static_cast<const uint16_t*>(fq.q), fq.q_idx, n_keep, r, kv, b, lane,
+                                       blockIdx.x == 0, row);
+#pragma unroll
+      for (int e = 0; e < EPL; ++e) {
+        qrows[r * D + lane * EPL + e] = row[e];
+        if (blockIdx.x == 0) fq.qbar[((size_t)(b * dm.n_kv + kv) * n_keep + r) * D + lane * EPL + e] = row[e];
+      }
+    }
+    __syncthreads();
+    qhead = qrows;
+  }
   if (t_begin >= T) return;  // block-uniform
   const int n_tiles = min(tiles_per_wg, (T - t_begin + kScTile - 1) / kScTile);
   if (n_tiles > 1) issue(1, RB);
 
   const bool dot_mode = (dm.flags & 1) != 0, mean_mode = (dm.flags & 2) != 0;   // ablation scorers
   typename std::conditional<PACK, PackedTerms<D>, QueryTerms<D, EXACT>>::type qt;   // this wave's 32 query rows
-  {
-    const float* qhead = qbar + (size_t)(b * dm.n_kv + kv) * n_keep * D;
-    if constexpr (PACK) {
-      qt.load(qhead, n_keep, li, hf);
-    } else {
-      qt.load(qhead, n_keep, qb, li, hf, mean_mode);
-    }
+  if constexpr (PACK) {
+    qt.load(qhead, n_keep, li, hf);
+  } else {
+    qt.load(qhead, n_keep, qb, li, hf, mean_mode);
   }
 
   // scores of tile `it` from the maxima and squared norms of generation it % 3
@@ -239,13 +258,13 @@ static void launch_f32_d(const Dims& dm, const float* qbar, const float* kc, con
 }
 
 // ---------------------------------------------------------------------------------------------
-template <int D, int QB, bool EXACT, bool PACK = false>
+template <int D, int QB, bool EXACT, bool PACK = false, bool FUSE = false>
 static hipError_t launch_bf16(const Dims& dm, const float* qbar, const void* kc, const int32_t* kv_lens, float* scores,
-                              int n_keep, hipStream_t st, uint32_t* zero, uint32_t zero_words) {
+                              int n_keep, hipStream_t st, uint32_t* zero, uint32_t zero_words, const FusedQbar& fq = {}) {
   using Cfg = ScoreCfg<D, QB>;
   static std::atomic<uint64_t> lds_done{0};
   const hipError_t e =
-      ensure_dynamic_lds(reinterpret_cast<const void*>(&score_bf16<D, QB, EXACT, PACK>), Cfg::kLdsBytes, lds_done);
+      ensure_dynamic_lds(reinterpret_cast<const void*>(&score_bf16<D, QB, EXACT, PACK, FUSE>), Cfg::kLdsBytes, lds_done);
   if (e != hipSuccess) return e;
   const int nt = (dm.T_cap + kScTile - 1) / kScTile;
   const int heads = dm.b * dm.n_kv;
@@ -255,34 +274,41 @@ static hipError_t launch_bf16(const Dims& dm, const float* qbar, const void* kc,
   int tpw = (nt + wg_per_head - 1) / wg_per_head;
   tpw = tpw < 1 ? 1 : tpw;
   dim3 grid((nt + tpw - 1) / tpw, dm.n_kv, dm.b);
-  hipLaunchKernelGGL((score_bf16<D, QB, EXACT, PACK>), grid, dim3(kScThreads), Cfg::kLdsBytes, st, dm, qbar,
-                     static_cast<const uint16_t*>(kc), kv_lens, scores, n_keep, tpw, zero, zero_words);
+  hipLaunchKernelGGL((score_bf16<D, QB, EXACT, PACK, FUSE>), grid, dim3(kScThreads), Cfg::kLdsBytes, st, dm, qbar,
+                     static_cast<const uint16_t*>(kc), kv_lens, scores, n_keep, tpw, zero, zero_words, fq);
   return hipGetLastError();
 }
 
 template <int D>
 static hipError_t launch_bf16_d(const Dims& dm, const float* qbar, const void* kc, const int32_t* kv_lens,
-                                float* scores, int n_keep, hipStream_t st, uint32_t* zero, uint32_t zero_words) {
+                                float* scores, int n_keep, hipStream_t st, uint32_t* zero, uint32_t zero_words,
+                                const FusedQbar& fq) {
   const int qblocks = (n_keep + 31) / 32;
   if (dm.flags & QUOKA_SCORE_QBAR_BF16) {
     if (qblocks <= 1) return launch_bf16<D, 1, false>(dm, qbar, kc, kv_lens, scores, n_keep, st, zero, zero_words);
     if (qblocks == 2) return launch_bf16<D, 2, false>(dm, qbar, kc, kv_lens, scores, n_keep, st, zero, zero_words);
     return launch_bf16<D, 4, false>(dm, qbar, kc, kv_lens, scores, n_keep, st, zero, zero_words);
   }
+  if (fq.q != nullptr)
+    return launch_bf16<D, 1, true, true, true>(dm, qbar, kc, kv_lens, scores, n_keep, st, zero, zero_words, fq);
   if (score_packs(dm)) return launch_bf16<D, 1, true, true>(dm, qbar, kc, kv_lens, scores, n_keep, st, zero, zero_words);
   if (qblocks <= 1) return launch_bf16<D, 1, true>(dm, qbar, kc, kv_lens, scores, n_keep, st, zero, zero_words);
   if (qblocks == 2) return launch_bf16<D, 2, true>(dm, qbar, kc, kv_lens, scores, n_keep, st, zero, zero_words);
   return launch_bf16<D, 4, true>(dm, qbar, kc, kv_lens, scores, n_keep, st, zero, zero_words);
 }
 
+bool score_forms_qbar(const Dims& dm, int dtype) {
+  return dtype == QUOKA_BF16 && dm.T_cap > 0 && dm.C <= dm.n_ret && score_packs(dm);
+}
+
 hipError_t launch_score_keys(const Dims& dm, int dtype, const float* qbar, const void* k_cache, const int32_t* kv_lens,
-                             float* scores, hipStream_t st, uint32_t* zero, size_t zero_words_sz) {
+                             float* scores, hipStream_t st, uint32_t* zero, size_t zero_words_sz, const FusedQbar& fq) {
   if (dm.T_cap <= 0) return hipSuccess;   // (then the top-k that follows takes no workspace either)
   const uint32_t zero_words = (uint32_t)zero_words_sz;
   const int n_keep = dm.n_ret < dm.C ? dm.n_ret : dm.C;
   if (dtype == QUOKA_BF16) {
-    return dm.d == 64 ? launch_bf16_d<64>(dm, qbar, k_cache, kv_lens, scores, n_keep, st, zero, zero_words)
-                      : launch_bf16_d<128>(dm, qbar, k_cache, kv_lens, scores, n_keep, st, zero, zero_words);
+    return dm.d == 64 ? launch_bf16_d<64>(dm, qbar, k_cache, kv_lens, scores, n_keep, st, zero, zero_words, fq)
+                      : launch_bf16_d<128>(dm, qbar, k_cache, kv_lens, scores, n_keep, st, zero, zero_words, fq);
   }
   const float* kf = static_cast<const float*>(k_cache);
   if (dm.d == 64) {

@@ -13,6 +13,7 @@
 //                     group and average                                                 -> qbar
 #include "common.hip.h"
 #include "kernels.h"
+#include "qbar_row.hip.h"
 #include "score_tile.hip.h"
 
 namespace quoka {
@@ -332,13 +333,7 @@ __global__ __launch_bounds__(kSelThreads) void sq_head_select(Dims dm, const T* 
 }
 
 // ---------------------------------------------------------------------------------------------
-// One wave per (r, kv, b): lanes own D/64 consecutive elements each.  The group's rows are all requested before
-// any is used, so the kernel pays one index latency and one row latency, not g of each.
-constexpr int kGroupUnroll = 8;
-// RULE: where the retained positions come from.  kFromIndex: q_idx as written by the selection kernel.  The other two
-// are known in closed form, so this kernel writes q_idx itself and no separate launch is needed: kIdentity keeps every
-// query (C <= N_Q), kUniform takes the even stride floor(r * C / N') of the query-sampling baseline of Sec. 4.
-enum { kFromIndex = 0, kIdentity = 1, kUniform = 2 };
+// One wave per (r, kv, b).
 template <typename T, int D, int RULE>
 __global__ __launch_bounds__(64) void sq_qbar(Dims dm, const T* __restrict__ q, int32_t* __restrict__ q_idx,
                                              float* __restrict__ qbar, int n_keep, uint32_t* __restrict__ zero,
@@ -347,46 +342,11 @@ __global__ __launch_bounds__(64) void sq_qbar(Dims dm, const T* __restrict__ q, 
   clear_words(zero, zero_words);   // side job of the fused call: histograms and counters of the key-selection stage
   const int r = blockIdx.x, kv = blockIdx.y, b = blockIdx.z;
   const int lane = threadIdx.x;
-  float acc[EPL];
-#pragma unroll
-  for (int e = 0; e < EPL; ++e) acc[e] = 0.f;
-  for (int j0 = 0; j0 < dm.g; j0 += kGroupUnroll) {
-    int tok[kGroupUnroll];
-#pragma unroll
-    for (int jj = 0; jj < kGroupUnroll; ++jj) {
-      const int j = min(j0 + jj, dm.g - 1);
-      int32_t* slot = q_idx + (size_t)(b * dm.n_q + kv * dm.g + j) * n_keep + r;
-      if constexpr (RULE == kFromIndex) {
-        tok[jj] = *slot;
-      } else {
-        tok[jj] = RULE == kIdentity ? r : (int)(((int64_t)r * dm.chunk(b)) / n_keep);
-        if (lane == 0) *slot = tok[jj];
-      }
-    }
-    float v[kGroupUnroll][EPL];
-#pragma unroll
-    for (int jj = 0; jj < kGroupUnroll; ++jj) {
-      const int j = min(j0 + jj, dm.g - 1);
-      const T* row = q + b * dm.qs[0] + (size_t)(kv * dm.g + j) * dm.qs[1] + (size_t)tok[jj] * dm.qs[2];
-#pragma unroll
-      for (int e = 0; e < EPL; ++e) v[jj][e] = Elem<T>::load1(row + lane * EPL + e);
-    }
-#pragma unroll
-    for (int jj = 0; jj < kGroupUnroll; ++jj) {
-      float ss = 0.f;
-#pragma unroll
-      for (int e = 0; e < EPL; ++e) ss += v[jj][e] * v[jj][e];
-      ss = wave64_sum(ss);
-      const float nrm = (dm.flags & 1) ? 1.0f : fmaxf(sqrtf(ss), kNormEps);   // dot-product ablation: no normalisation
-      if (j0 + jj < dm.g) {   // wave-uniform; heads are accumulated in ascending order
-#pragma unroll
-        for (int e = 0; e < EPL; ++e) acc[e] += v[jj][e] / nrm;
-      }
-    }
-  }
+  float row[EPL];
+  qbar_row<T, D, RULE>(dm, q, q_idx, n_keep, r, kv, b, lane, true, row);
   float* out = qbar + ((size_t)(b * dm.n_kv + kv) * n_keep + r) * D;
 #pragma unroll
-  for (int e = 0; e < EPL; ++e) out[lane * EPL + e] = acc[e] / (float)dm.g;
+  for (int e = 0; e < EPL; ++e) out[lane * EPL + e] = row[e];
 }
 
 // ---------------------------------------------------------------------------------------------
