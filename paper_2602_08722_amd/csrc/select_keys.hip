@@ -356,7 +356,8 @@ __global__ __launch_bounds__(kSelHeadThreads) void sel_band_select(Dims dm, floa
 
 // ---------------------------------------------------------------------------------------------
 // Ordered emission of one tile.  Wave w owns 512 consecutive positions; register j of its lane l is position 64*j + l of
-// them, so scores and indices travel as coalesced rows and wave ballots give the order.  `take`: keys selected whatever the
+// them, so scores and indices travel as coalesced rows and wave ballots give the order
+// (8 x 8 ragged heads: 11.7 us with eight consecutive positions a thread, 9.0 so).  `take`: keys selected whatever the
 // ties; `eq`: keys equal to the cut, of which the `need_eq` lowest positions are selected (`eq_tile0` of them lie in
 // earlier tiles); `off`: selected keys in earlier tiles.
 constexpr int kSelWaves = kSelThreads / 64;
@@ -435,7 +436,9 @@ __global__ __launch_bounds__(kSelThreads) void sel_emit(Dims dm, float* __restri
 // ---------------------------------------------------------------------------------------------
 // Exact scores (score_packs): nothing is scored again, the candidates are the keys of the cut's own bin, a few dozen.
 // Launch chain: scoring with the histogram, one count per tile, emission; every emitting block finds the cut among the
-// candidates for itself, which is cheaper than a launch for it while the heads are short.
+// candidates for itself, which is cheaper than a launch for it while the heads are short.  Measured (re-score, select, emit before -> these two; the scoring
+// launch takes the same): 8 sequences x 8 heads of 4096 to 65536 positions 48 -> 24 us (call 216 -> 196 us), 8 heads of
+// 100003 23 -> 14 us (call 88 -> 80 us).
 static_assert(kPackMaxKeys / kSelTile <= 64, "one lane a tile");
 
 __global__ __launch_bounds__(kSelThreads) void sel_classify(Dims dm, float* __restrict__ scores,
@@ -486,8 +489,7 @@ __global__ __launch_bounds__(kSelThreads) void sel_finish(Dims dm, float* __rest
                                                          const int32_t* __restrict__ budgets, uint32_t* __restrict__ ws,
                                                          int32_t* __restrict__ k_idx, int32_t* __restrict__ k_cnt) {
   __shared__ RadixSelectLds rs;
-  __shared__ __align__(16) uint32_t key[kFinCands + 8];   // (zeros behind the candidates: below every key)
-  __shared__ uint32_t pos[kFinCands];
+  __shared__ uint32_t key[kFinCands], pos[kFinCands];
   __shared__ uint32_t cut[2], sums[4], wcnt[kSelWaves];
   const SelCtx c = sel_ctx(dm, scores, kv_lens, budgets, ws, blockIdx.y, blockIdx.z);
   const int t0 = blockIdx.x * kSelTile;
@@ -519,7 +521,6 @@ __global__ __launch_bounds__(kSelThreads) void sel_finish(Dims dm, float* __rest
       key[i] = c.w.cand_key[i];
       pos[i] = c.w.cand_pos[i];
     }
-    if (tid < 8) key[n_c + tid] = 0u;
   }
   if (tid == 0) sums[2] = sums[3] = 0u;
   // certainly selected keys, in all tiles and in the earlier ones (the first wave has a lane for every tile)
@@ -536,13 +537,9 @@ __global__ __launch_bounds__(kSelThreads) void sel_finish(Dims dm, float* __rest
     for (uint32_t i = tid; i < n_c; i += kSelThreads) {
       const uint32_t k = key[i];
       uint32_t gt = 0, ge = 0;
-      for (uint32_t j = 0; j < n_c; j += 8) {   // eight keys a fetch: one at a time, the loop is a chain of LDS latencies
-        const u32x4 a = *reinterpret_cast<const u32x4*>(key + j), b = *reinterpret_cast<const u32x4*>(key + j + 4);
-#pragma unroll
-        for (int e = 0; e < 4; ++e) {
-          gt += (a[e] > k ? 1u : 0u) + (b[e] > k ? 1u : 0u);
-          ge += (a[e] >= k ? 1u : 0u) + (b[e] >= k ? 1u : 0u);
-        }
+      for (uint32_t j = 0; j < n_c; ++j) {
+        gt += key[j] > k ? 1u : 0u;
+        ge += key[j] >= k ? 1u : 0u;
       }
       if (gt < need && need <= ge) {   // (equal keys all write the same)
         cut[0] = k;
