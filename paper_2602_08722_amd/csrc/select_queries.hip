@@ -21,6 +21,33 @@ namespace quoka {
 constexpr int kSqTile = 64;     // tokens per tile
 constexpr int kSqThreads = 256;
 
+template <typename T>
+struct Raw8;   // eight consecutive elements as loaded
+template <>
+struct Raw8<uint16_t> {
+  u32x4 r;
+  __device__ __forceinline__ void load(const uint16_t* p) { r = *reinterpret_cast<const u32x4*>(p); }
+  __device__ __forceinline__ void widen(float (&v)[8]) const {
+#pragma unroll
+    for (int i = 0; i < 4; ++i) {
+      v[2 * i] = __uint_as_float(r[i] << 16);
+      v[2 * i + 1] = __uint_as_float(r[i] & 0xFFFF0000u);
+    }
+  }
+};
+template <>
+struct Raw8<float> {
+  float4 a, b;
+  __device__ __forceinline__ void load(const float* p) {
+    a = *reinterpret_cast<const float4*>(p);
+    b = *reinterpret_cast<const float4*>(p + 4);
+  }
+  __device__ __forceinline__ void widen(float (&v)[8]) const {
+    v[0] = a.x; v[1] = a.y; v[2] = a.z; v[3] = a.w;
+    v[4] = b.x; v[5] = b.y; v[6] = b.z; v[7] = b.w;
+  }
+};
+
 // ---------------------------------------------------------------------------------------------
 template <typename T, int D>
 __global__ __launch_bounds__(kSqThreads) void sq_partial_sums(Dims dm, const T* __restrict__ q, float* __restrict__ part,
@@ -33,11 +60,14 @@ __global__ __launch_bounds__(kSqThreads) void sq_partial_sums(Dims dm, const T* 
   const T* base = q + b * dm.qs[0] + h * dm.qs[1];
   float acc[8] = {0, 0, 0, 0, 0, 0, 0, 0};
   const int t0 = tile * kSqTile;
-  for (int r = rr; r < kSqTile; r += RPB) {
-    const int tok = t0 + r;
-    if (tok < C) {
-      float v[8];
-      Elem<T>::load8(base + tok * dm.qs[2] + cg * 8, v);
+  Raw8<T> rows[kSqTile / RPB];   // all requested before the first is used
+#pragma unroll
+  for (int u = 0; u < kSqTile / RPB; ++u) rows[u].load(base + (size_t)min(t0 + u * RPB + rr, C - 1) * dm.qs[2] + cg * 8);
+#pragma unroll
+  for (int u = 0; u < kSqTile / RPB; ++u) {
+    float v[8];
+    rows[u].widen(v);
+    if (t0 + u * RPB + rr < C) {
 #pragma unroll
       for (int e = 0; e < 8; ++e) acc[e] += v[e];
     }
@@ -63,6 +93,9 @@ __global__ __launch_bounds__(kSqThreads) void sq_cosine(Dims dm, const T* __rest
   const int C = dm.chunk(b);
   __shared__ float mean[D];
   __shared__ float mnorm;
+  const int cg = threadIdx.x % CG, rr = threadIdx.x / CG;
+  const T* base = q + b * dm.qs[0] + h * dm.qs[1];
+  const int t0 = tile * kSqTile;
   if (threadIdx.x < D) {
     const float* p = part + (size_t)(b * dm.n_q + h) * n_tiles * D + threadIdx.x;
     float s = 0.f;
@@ -76,25 +109,26 @@ __global__ __launch_bounds__(kSqThreads) void sq_cosine(Dims dm, const T* __rest
     }
     mean[threadIdx.x] = s / (float)C;
   }
+  Raw8<T> rows[kSqTile / RPB];   // travel while the mean's norm is formed
+#pragma unroll
+  for (int u = 0; u < kSqTile / RPB; ++u) rows[u].load(base + (size_t)min(t0 + u * RPB + rr, C - 1) * dm.qs[2] + cg * 8);
   __syncthreads();
-  if (threadIdx.x == 0) {
+  if (threadIdx.x < 64) {   // one wave: squared norm of the mean
     float ss = 0.f;
-    for (int i = 0; i < D; ++i) ss += mean[i] * mean[i];
-    mnorm = fmaxf(sqrtf(ss), kNormEps);
+    for (int i = threadIdx.x; i < D; i += 64) ss += mean[i] * mean[i];
+    ss = wave64_sum(ss);
+    if (threadIdx.x == 0) mnorm = fmaxf(sqrtf(ss), kNormEps);
   }
   __syncthreads();
-  const int cg = threadIdx.x % CG, rr = threadIdx.x / CG;
   float m[8];
 #pragma unroll
   for (int e = 0; e < 8; ++e) m[e] = mean[cg * 8 + e];
   const float mn = mnorm;
-  const T* base = q + b * dm.qs[0] + h * dm.qs[1];
-  const int t0 = tile * kSqTile;
-  for (int r = rr; r < kSqTile; r += RPB) {   // uniform trip count: shuffles below stay convergent
-    const int tok = t0 + r;
-    const int tk = tok < C ? tok : C - 1;
+#pragma unroll
+  for (int u = 0; u < kSqTile / RPB; ++u) {
+    const int tok = t0 + u * RPB + rr;
     float v[8];
-    Elem<T>::load8(base + tk * dm.qs[2] + cg * 8, v);
+    rows[u].widen(v);
     float dot = 0.f, qq = 0.f;
 #pragma unroll
     for (int e = 0; e < 8; ++e) {
@@ -217,33 +251,6 @@ __global__ __launch_bounds__(kSelThreads) void sq_select(Dims dm, const float* _
 // Column sums are formed per group of concurrently handled rows and the groups added in a fixed order, so the mean is
 // bit-reproducible here too (its rounding differs from the tiled kernels' in the last bits: the two routes are
 // never mixed within one call).
-template <typename T>
-struct Raw8;   // eight consecutive elements as loaded
-template <>
-struct Raw8<uint16_t> {
-  u32x4 r;
-  __device__ __forceinline__ void load(const uint16_t* p) { r = *reinterpret_cast<const u32x4*>(p); }
-  __device__ __forceinline__ void widen(float (&v)[8]) const {
-#pragma unroll
-    for (int i = 0; i < 4; ++i) {
-      v[2 * i] = __uint_as_float(r[i] << 16);
-      v[2 * i + 1] = __uint_as_float(r[i] & 0xFFFF0000u);
-    }
-  }
-};
-template <>
-struct Raw8<float> {
-  float4 a, b;
-  __device__ __forceinline__ void load(const float* p) {
-    a = *reinterpret_cast<const float4*>(p);
-    b = *reinterpret_cast<const float4*>(p + 4);
-  }
-  __device__ __forceinline__ void widen(float (&v)[8]) const {
-    v[0] = a.x; v[1] = a.y; v[2] = a.z; v[3] = a.w;
-    v[4] = b.x; v[5] = b.y; v[6] = b.z; v[7] = b.w;
-  }
-};
-
 template <typename T, int D, int NR>   // NR: rows per thread (all held in registers)
 __global__ __launch_bounds__(kSelThreads) void sq_head_select(Dims dm, const T* __restrict__ q,
                                                              int32_t* __restrict__ q_idx, int n_keep) {
