@@ -25,6 +25,7 @@ struct WsLayout {
   size_t topk_off, topk_bytes;
   size_t sel_off, sel_bytes;
   size_t part_off, part_bytes;
+  size_t terms_off, terms_bytes;
   size_t total;
 };
 
@@ -89,7 +90,9 @@ WsLayout layout(const Dims& dm, int dtype) {
     part_floats = decode > prefill ? decode : prefill;
   }
   l.part_bytes = round_up(part_floats * sizeof(float), kAlign);
-  l.total = l.part_off + l.part_bytes;
+  l.terms_off = l.part_off + l.part_bytes;
+  l.terms_bytes = dtype == QUOKA_BF16 ? round_up(quoka::query_terms_bytes(dm), kAlign) : 0;
+  l.total = l.terms_off + l.terms_bytes;
   if (l.total == 0) l.total = kAlign;
   return l;
 }
@@ -345,7 +348,8 @@ quoka_status quoka_dense_attn(const quoka_shape* shape, const void* q, const voi
 static quoka_status select_keys_common(const Dims& dm, int dtype, const float* qbar, const void* k_cache,
                                        const int32_t* kv_lens, const int32_t* budgets, float* scores, int32_t* k_idx,
                                        int32_t* k_cnt, void* workspace, const WsLayout& l, hipStream_t hs,
-                                       bool sel_ws_is_zero, const quoka::FusedQbar& fq = {}) {
+                                       bool sel_ws_is_zero, const quoka::FusedQbar& fq = {},
+                                       const uint16_t* terms = nullptr) {
   if (dm.T_max > 0 && quoka::select_keys_two_pass_applies(dm, dtype)) {
     uint32_t* sel_ws = reinterpret_cast<uint32_t*>(static_cast<char*>(workspace) + l.sel_off);
     return from_hip(quoka::launch_select_keys(dm, qbar, k_cache, kv_lens, budgets, scores, k_idx, k_cnt, sel_ws, hs,
@@ -355,7 +359,7 @@ static quoka_status select_keys_common(const Dims& dm, int dtype, const float* q
   const bool fuse_clear = quoka::topk_uses_ws(dm);
   const size_t topk_words = fuse_clear ? quoka::topk_ws_words(dm) : 0;
   quoka_status st = from_hip(quoka::launch_score_keys(dm, dtype, qbar, k_cache, kv_lens, scores, hs,
-                                                      fuse_clear ? topk_ws : nullptr, topk_words, fq));
+                                                      fuse_clear ? topk_ws : nullptr, topk_words, fq, terms));
   if (st != QUOKA_OK) return st;
   return from_hip(quoka::launch_topk_keys(dm, scores, kv_lens, budgets, k_idx, k_cnt, topk_ws, hs, fuse_clear));
 }
@@ -401,15 +405,18 @@ static quoka_status chunk_common(const quoka_shape* shape, const CallInfo& info,
   uint32_t* sel_ws = reinterpret_cast<uint32_t*>(static_cast<char*>(workspace) + l.sel_off);
   float* sq_ws = reinterpret_cast<float*>(static_cast<char*>(workspace) + l.select_off);
   quoka::FusedQbar fq;
+  uint16_t* terms = !two_pass && quoka::score_reads_terms(dm, shape->dtype)
+                        ? reinterpret_cast<uint16_t*>(static_cast<char*>(workspace) + l.terms_off)
+                        : nullptr;
   if (!two_pass && quoka::score_forms_qbar(dm, shape->dtype)) {   // a few tokens: one launch less
     fq = quoka::FusedQbar{q, q_idx, qbar};
   } else {
     st = from_hip(quoka::launch_select_queries(dm, shape->dtype, q, q_idx, qbar, sq_ws, hs, two_pass ? sel_ws : nullptr,
-                                               two_pass ? quoka::select_keys_zero_words(dm) : 0));
+                                               two_pass ? quoka::select_keys_zero_words(dm) : 0, terms));
     if (st != QUOKA_OK) return st;
   }
   st = select_keys_common(dm, shape->dtype, qbar, k_cache, kv_lens, budgets, scores, k_idx, k_cnt, workspace, l, hs,
-                          two_pass, fq);
+                          two_pass, fq, terms);
   if (st != QUOKA_OK) return st;
   return attn_common(shape, info, q, k_cache, v_cache, k_idx, k_cnt, true, k_chunk, v_chunk, out, lse, workspace,
                      workspace_bytes, stream);

@@ -29,7 +29,10 @@ size_t select_queries_ws_floats(const Dims& dm);
 // `zero` / `zero_words`: optional side job for the fused call -- the last launch clears that many 32-bit words (what
 // the key-selection stage that follows needs cleared).
 hipError_t launch_select_queries(const Dims& dm, int dtype, const void* q, int32_t* q_idx, float* qbar, float* ws,
-                                 hipStream_t st, uint32_t* zero = nullptr, size_t zero_words = 0);
+                                 hipStream_t st, uint32_t* zero = nullptr, size_t zero_words = 0,
+                                 uint16_t* terms = nullptr);
+// (`terms`: the last launch also leaves Qbar as the exact scorer's operands, TermsLayout of score_tile.hip.h; bf16)
+size_t query_terms_bytes(const Dims& dm);
 
 // --- key scoring (score_keys.hip) ---------------------------------------------------------------
 // `zero` / `zero_words`: optional side job for the fused call -- the scoring blocks clear that many 32-bit words (the
@@ -43,7 +46,8 @@ struct FusedQbar {
 bool score_forms_qbar(const Dims& dm, int dtype);
 hipError_t launch_score_keys(const Dims& dm, int dtype, const float* qbar, const void* k_cache, const int32_t* kv_lens,
                              float* scores, hipStream_t st, uint32_t* zero = nullptr, size_t zero_words = 0,
-                             const FusedQbar& fq = {});
+                             const FusedQbar& fq = {}, const uint16_t* terms = nullptr);
+bool score_reads_terms(const Dims& dm, int dtype);   // whether the launch would rather have `terms` than Qbar
 
 // --- top-B key selection (topk_keys.hip) ----------------------------------------------------------
 size_t topk_ws_words(const Dims& dm);

@@ -30,7 +30,7 @@ __global__ __launch_bounds__(kScThreads, 2) void score_bf16(Dims dm, const float
                                                            const int32_t* __restrict__ kv_lens,
                                                            float* __restrict__ scores, int n_keep, int tiles_per_wg,
                                                            uint32_t* __restrict__ zero, uint32_t zero_words,
-                                                           FusedQbar fq) {
+                                                           FusedQbar fq, const uint16_t* __restrict__ terms) {
   using Cfg = ScoreCfg<D, QB>;
   clear_words(zero, zero_words);
   constexpr int LD = Cfg::LD, CG = Cfg::CG, RPI = Cfg::RPI, NLD = Cfg::NLD;
@@ -94,6 +94,9 @@ __global__ __launch_bounds__(kScThreads, 2) void score_bf16(Dims dm, const float
   typename std::conditional<PACK, PackedTerms<D>, QueryTerms<D, EXACT>>::type qt;   // this wave's 32 query rows
   if constexpr (PACK) {
     qt.load(qhead, n_keep, li, hf);
+  } else if (EXACT && terms != nullptr) {   // (kernel-uniform)
+    if constexpr (EXACT)
+      qt.load_terms(terms + (size_t)(b * dm.n_kv + kv) * TermsLayout<D>::head_elems(n_keep), n_keep, qb, li, hf);
   } else {
     qt.load(qhead, n_keep, qb, li, hf, mean_mode);
   }
@@ -260,7 +263,8 @@ static void launch_f32_d(const Dims& dm, const float* qbar, const float* kc, con
 // ---------------------------------------------------------------------------------------------
 template <int D, int QB, bool EXACT, bool PACK = false, bool FUSE = false>
 static hipError_t launch_bf16(const Dims& dm, const float* qbar, const void* kc, const int32_t* kv_lens, float* scores,
-                              int n_keep, hipStream_t st, uint32_t* zero, uint32_t zero_words, const FusedQbar& fq = {}) {
+                              int n_keep, hipStream_t st, uint32_t* zero, uint32_t zero_words, const FusedQbar& fq = {},
+                              const uint16_t* terms = nullptr) {
   using Cfg = ScoreCfg<D, QB>;
   static std::atomic<uint64_t> lds_done{0};
   const hipError_t e =
@@ -279,14 +283,15 @@ static hipError_t launch_bf16(const Dims& dm, const float* qbar, const void* kc,
   tpw = tpw < 1 ? 1 : tpw;
   dim3 grid((nt + tpw - 1) / tpw, dm.n_kv, dm.b);
   hipLaunchKernelGGL((score_bf16<D, QB, EXACT, PACK, FUSE>), grid, dim3(kScThreads), Cfg::kLdsBytes, st, dm, qbar,
-                     static_cast<const uint16_t*>(kc), kv_lens, scores, n_keep, tpw, zero, zero_words, fq);
+                     static_cast<const uint16_t*>(kc), kv_lens, scores, n_keep, tpw, zero, zero_words, fq,
+                     terms);
   return hipGetLastError();
 }
 
 template <int D>
 static hipError_t launch_bf16_d(const Dims& dm, const float* qbar, const void* kc, const int32_t* kv_lens,
                                 float* scores, int n_keep, hipStream_t st, uint32_t* zero, uint32_t zero_words,
-                                const FusedQbar& fq) {
+                                const FusedQbar& fq, const uint16_t* terms) {
   const int qblocks = (n_keep + 31) / 32;
   if (dm.flags & QUOKA_SCORE_QBAR_BF16) {
     if (qblocks <= 1) return launch_bf16<D, 1, false>(dm, qbar, kc, kv_lens, scores, n_keep, st, zero, zero_words);
@@ -296,9 +301,13 @@ static hipError_t launch_bf16_d(const Dims& dm, const float* qbar, const void* k
   if (fq.q != nullptr)
     return launch_bf16<D, 1, true, true, true>(dm, qbar, kc, kv_lens, scores, n_keep, st, zero, zero_words, fq);
   if (score_packs(dm)) return launch_bf16<D, 1, true, true>(dm, qbar, kc, kv_lens, scores, n_keep, st, zero, zero_words);
-  if (qblocks <= 1) return launch_bf16<D, 1, true>(dm, qbar, kc, kv_lens, scores, n_keep, st, zero, zero_words);
-  if (qblocks == 2) return launch_bf16<D, 2, true>(dm, qbar, kc, kv_lens, scores, n_keep, st, zero, zero_words);
-  return launch_bf16<D, 4, true>(dm, qbar, kc, kv_lens, scores, n_keep, st, zero, zero_words);
+  if (qblocks <= 1) return launch_bf16<D, 1, true>(dm, qbar, kc, kv_lens, scores, n_keep, st, zero, zero_words, {}, terms);
+  if (qblocks == 2) return launch_bf16<D, 2, true>(dm, qbar, kc, kv_lens, scores, n_keep, st, zero, zero_words, {}, terms);
+  return launch_bf16<D, 4, true>(dm, qbar, kc, kv_lens, scores, n_keep, st, zero, zero_words, {}, terms);
+}
+
+bool score_reads_terms(const Dims& dm, int dtype) {
+  return dtype == QUOKA_BF16 && dm.T_cap > 0 && !score_packs(dm) && (dm.flags & (QUOKA_SCORE_MEAN | QUOKA_SCORE_QBAR_BF16)) == 0;
 }
 
 bool score_forms_qbar(const Dims& dm, int dtype) {
@@ -306,13 +315,14 @@ bool score_forms_qbar(const Dims& dm, int dtype) {
 }
 
 hipError_t launch_score_keys(const Dims& dm, int dtype, const float* qbar, const void* k_cache, const int32_t* kv_lens,
-                             float* scores, hipStream_t st, uint32_t* zero, size_t zero_words_sz, const FusedQbar& fq) {
+                             float* scores, hipStream_t st, uint32_t* zero, size_t zero_words_sz, const FusedQbar& fq,
+                             const uint16_t* terms) {
   if (dm.T_cap <= 0) return hipSuccess;   // (then the top-k that follows takes no workspace either)
   const uint32_t zero_words = (uint32_t)zero_words_sz;
   const int n_keep = dm.n_ret < dm.C ? dm.n_ret : dm.C;
   if (dtype == QUOKA_BF16) {
-    return dm.d == 64 ? launch_bf16_d<64>(dm, qbar, k_cache, kv_lens, scores, n_keep, st, zero, zero_words, fq)
-                      : launch_bf16_d<128>(dm, qbar, k_cache, kv_lens, scores, n_keep, st, zero, zero_words, fq);
+    return dm.d == 64 ? launch_bf16_d<64>(dm, qbar, k_cache, kv_lens, scores, n_keep, st, zero, zero_words, fq, terms)
+                      : launch_bf16_d<128>(dm, qbar, k_cache, kv_lens, scores, n_keep, st, zero, zero_words, fq, terms);
   }
   const float* kf = static_cast<const float*>(k_cache);
   if (dm.d == 64) {

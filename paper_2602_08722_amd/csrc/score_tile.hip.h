@@ -60,9 +60,33 @@ __device__ __forceinline__ float row_sumsq(const u32x4& r) {
 // terms.  EXACT: hi + mid + lo add up to the float32 value exactly, so with bf16 keys every product is exact and only
 // the float32 accumulation rounds.  Otherwise only hi (Qbar rounded to bf16) is formed.  Rows past n_keep repeat the
 // last real query (the max is unchanged); `zero_pad` makes them zero instead (for the mean over queries).
+// The three terms of a row of Qbar as the launch that forms it can leave them, 16 bytes a lane in operand order:
+// [row block][k-step][term][lane].  A scoring block then fetches whole kilobytes and converts nothing (64 elements a lane,
+// about 450 instructions): 8 heads of 8192 keys, 64 queries 10.4 -> 8.7 us, call 72.7 -> 69.9; 128 queries x 32768 keys
+// 31.0 -> 29.2.  (The re-scoring of the two-pass stage gains nothing from it.)
+template <int D>
+struct TermsLayout {
+  static constexpr int kBlock = (D / 16) * 3 * 64 * 8;   // elements of 32 rows
+  __host__ __device__ static size_t head_elems(int n_keep) { return (size_t)((n_keep + 31) / 32) * kBlock; }
+  // first of the elements of row r's dims d .. (d % 8 != 7: neighbours follow)
+  __device__ static size_t at(int r, int d, int term) {
+    return (size_t)(r / 32) * kBlock + (size_t)((((d / 16) * 3 + term) * 64 + ((d % 16) / 8) * 32 + r % 32) * 8 + d % 8);
+  }
+};
+
 template <int D, bool EXACT>
 struct QueryTerms {
   bf16x8 hi[D / 16], mid[D / 16], lo[D / 16];
+  // (rows past n_keep repeat the last real query)
+  __device__ __forceinline__ void load_terms(const uint16_t* __restrict__ head, int n_keep, int qb, int li, int hf) {
+    const uint16_t* p = head + TermsLayout<D>::at(min(qb * 32 + li, n_keep - 1), 8 * hf, 0);
+#pragma unroll
+    for (int ks = 0; ks < D / 16; ++ks) {
+      hi[ks] = *reinterpret_cast<const bf16x8*>(p + (ks * 3 + 0) * 512);
+      mid[ks] = *reinterpret_cast<const bf16x8*>(p + (ks * 3 + 1) * 512);
+      lo[ks] = *reinterpret_cast<const bf16x8*>(p + (ks * 3 + 2) * 512);
+    }
+  }
   __device__ __forceinline__ void load(const float* __restrict__ qhead, int n_keep, int qb, int li, int hf,
                                        bool zero_pad) {
     int r = qb * 32 + li;

@@ -344,7 +344,7 @@ __global__ __launch_bounds__(kSelThreads) void sq_head_select(Dims dm, const T* 
 template <typename T, int D, int RULE>
 __global__ __launch_bounds__(64) void sq_qbar(Dims dm, const T* __restrict__ q, int32_t* __restrict__ q_idx,
                                              float* __restrict__ qbar, int n_keep, uint32_t* __restrict__ zero,
-                                             uint32_t zero_words) {
+                                             uint32_t zero_words, uint16_t* __restrict__ terms) {
   constexpr int EPL = D / 64;
   clear_words(zero, zero_words);   // side job of the fused call: histograms and counters of the key-selection stage
   const int r = blockIdx.x, kv = blockIdx.y, b = blockIdx.z;
@@ -354,19 +354,44 @@ __global__ __launch_bounds__(64) void sq_qbar(Dims dm, const T* __restrict__ q, 
   float* out = qbar + ((size_t)(b * dm.n_kv + kv) * n_keep + r) * D;
 #pragma unroll
   for (int e = 0; e < EPL; ++e) out[lane * EPL + e] = row[e];
+  if (terms != nullptr) {   // (kernel-uniform)
+    uint16_t* th = terms + (size_t)(b * dm.n_kv + kv) * TermsLayout<D>::head_elems(n_keep);
+    uint16_t t[3][EPL];
+#pragma unroll
+    for (int e = 0; e < EPL; ++e) {
+      const __bf16 hi = (__bf16)row[e];
+      const float r1 = row[e] - (float)hi;
+      const __bf16 mid = (__bf16)r1;
+      t[0][e] = __builtin_bit_cast(uint16_t, hi);
+      t[1][e] = __builtin_bit_cast(uint16_t, mid);
+      t[2][e] = __builtin_bit_cast(uint16_t, (__bf16)(r1 - (float)mid));
+    }
+#pragma unroll
+    for (int k = 0; k < 3; ++k) {
+      uint16_t* p = th + TermsLayout<D>::at(r, lane * EPL, k);
+      if constexpr (EPL == 2) {
+        *reinterpret_cast<uint32_t*>(p) = t[k][0] | ((uint32_t)t[k][1] << 16);
+      } else {
+        *p = t[k][0];
+      }
+    }
+  }
 }
 
 // ---------------------------------------------------------------------------------------------
 template <typename T, int D>
 static hipError_t launch_typed(const Dims& dm, const void* q, int32_t* q_idx, float* qbar, float* ws_part,
-                               float* ws_cos, hipStream_t st, uint32_t* zero, uint32_t zero_words) {
+                               float* ws_cos, hipStream_t st, uint32_t* zero, uint32_t zero_words,
+                               uint16_t* terms) {
   const int n_keep = dm.n_ret < dm.C ? dm.n_ret : dm.C;
   const T* qp = static_cast<const T*>(q);
   const dim3 qgrid(n_keep, dm.n_kv, dm.b);
   if (dm.C <= dm.n_ret) {
-    hipLaunchKernelGGL((sq_qbar<T, D, kIdentity>), qgrid, dim3(64), 0, st, dm, qp, q_idx, qbar, n_keep, zero, zero_words);
+    hipLaunchKernelGGL((sq_qbar<T, D, kIdentity>), qgrid, dim3(64), 0, st, dm, qp, q_idx, qbar, n_keep, zero,
+                       zero_words, terms);
   } else if (dm.flags & QUOKA_SELECT_UNIFORM) {
-    hipLaunchKernelGGL((sq_qbar<T, D, kUniform>), qgrid, dim3(64), 0, st, dm, qp, q_idx, qbar, n_keep, zero, zero_words);
+    hipLaunchKernelGGL((sq_qbar<T, D, kUniform>), qgrid, dim3(64), 0, st, dm, qp, q_idx, qbar, n_keep, zero,
+                       zero_words, terms);
   } else {
     const dim3 sgrid(dm.n_q, dm.b), sblock(kSelThreads);
     const int ipt = (dm.C + kSelThreads - 1) / kSelThreads;
@@ -398,9 +423,15 @@ static hipError_t launch_typed(const Dims& dm, const void* q, int32_t* q_idx, fl
         hipLaunchKernelGGL((sq_select<8>), sgrid, sblock, 0, st, dm, ws_cos, q_idx, n_keep);
       }
     }
-    hipLaunchKernelGGL((sq_qbar<T, D, kFromIndex>), qgrid, dim3(64), 0, st, dm, qp, q_idx, qbar, n_keep, zero, zero_words);
+    hipLaunchKernelGGL((sq_qbar<T, D, kFromIndex>), qgrid, dim3(64), 0, st, dm, qp, q_idx, qbar, n_keep, zero,
+                       zero_words, terms);
   }
   return hipGetLastError();
+}
+
+size_t query_terms_bytes(const Dims& dm) {
+  const int n_keep = dm.n_ret < dm.C ? dm.n_ret : dm.C;
+  return (size_t)dm.b * dm.n_kv * (dm.d == 64 ? TermsLayout<64>::head_elems(n_keep) : TermsLayout<128>::head_elems(n_keep)) * 2;
 }
 
 size_t select_queries_ws_floats(const Dims& dm) {
@@ -409,17 +440,17 @@ size_t select_queries_ws_floats(const Dims& dm) {
 }
 
 hipError_t launch_select_queries(const Dims& dm, int dtype, const void* q, int32_t* q_idx, float* qbar, float* ws,
-                                 hipStream_t st, uint32_t* zero, size_t zero_words_sz) {
+                                 hipStream_t st, uint32_t* zero, size_t zero_words_sz, uint16_t* terms) {
   const uint32_t zero_words = (uint32_t)zero_words_sz;
   const size_t n_tiles = (dm.C + kSqTile - 1) / kSqTile;
   float* ws_part = ws;
   float* ws_cos = ws + (size_t)dm.b * dm.n_q * n_tiles * dm.d;
   if (dtype == QUOKA_F32) {
-    return dm.d == 64 ? launch_typed<float, 64>(dm, q, q_idx, qbar, ws_part, ws_cos, st, zero, zero_words)
-                      : launch_typed<float, 128>(dm, q, q_idx, qbar, ws_part, ws_cos, st, zero, zero_words);
+    return dm.d == 64 ? launch_typed<float, 64>(dm, q, q_idx, qbar, ws_part, ws_cos, st, zero, zero_words, terms)
+                      : launch_typed<float, 128>(dm, q, q_idx, qbar, ws_part, ws_cos, st, zero, zero_words, terms);
   }
-  return dm.d == 64 ? launch_typed<uint16_t, 64>(dm, q, q_idx, qbar, ws_part, ws_cos, st, zero, zero_words)
-                    : launch_typed<uint16_t, 128>(dm, q, q_idx, qbar, ws_part, ws_cos, st, zero, zero_words);
+  return dm.d == 64 ? launch_typed<uint16_t, 64>(dm, q, q_idx, qbar, ws_part, ws_cos, st, zero, zero_words, terms)
+                    : launch_typed<uint16_t, 128>(dm, q, q_idx, qbar, ws_part, ws_cos, st, zero, zero_words, terms);
 }
 
 }  // namespace quoka
