@@ -133,6 +133,9 @@ BINNED_CASES = [
     ("normal", dict(kv_lens=[1025, 1, 0], budgets=[1024, 9, 3], batch=3)),
     ("normal", dict(kv_lens=[32768], budgets=[3932])),
     ("normal", dict(kv_lens=[16385], budgets=[16384])),
+    ("pairs", dict(kv_lens=[20480, 20000], budgets=[2481, 19999], batch=2)),   # 20, 24, 28 keys a thread, full and not
+    ("normal", dict(kv_lens=[20481], budgets=[700])),
+    ("normal", dict(kv_lens=[24576, 24577], budgets=[24575, 3], batch=2)),
     ("pairs", dict(kv_lens=[16384], budgets=[5001])),
     ("normal", dict(kv_lens=[5000], budgets=[1], chunk=1, n_retain=8)),
     ("pairs", dict(kv_lens=[6001], budgets=[777])),            # every score twice: ties at the cut
