@@ -47,6 +47,7 @@ __global__ void sel_zero(uint32_t* __restrict__ p, size_t n) {
 
 // Whole block of kSelThreads: thread t's run of the head's histogram (thread 0 has the highest bins) ...
 constexpr uint32_t kSelPer = kSelBins / kSelThreads;
+constexpr int kBandCap = 2 * kSelTile;   // band keys a block lists before it scores them
 __device__ __forceinline__ void load_hist_run(const uint32_t* __restrict__ hist, uint32_t (&hv)[kSelPer]) {
   const uint32_t top = kSelBins - threadIdx.x * kSelPer;   // exclusive upper bin of the run
 #pragma unroll
@@ -84,7 +85,9 @@ __device__ __forceinline__ int find_cut_bin(const uint32_t (&hv)[kSelPer], uint3
 
 // ---------------------------------------------------------------------------------------------
 // Band classification and exact re-scoring.  A block takes `tpb` consecutive 2048-key tiles of one head: it locates
-// the band once from the finished histogram, then per tile classifies the keys and scores the band keys exactly.
+// the band once from the finished histogram, classifies the keys tile after tile and scores the listed band keys exactly.
+// (Listing a whole block first and fetching the next rows during the products: 8 x 8 ragged heads 34.5 -> 32.9 us; an
+// operand load placed beside the first rows instead of up front costs the second wave per SIMD, 48 us.)
 template <int D, int QB>
 __global__ __launch_bounds__(kSelThreads) void sel_band_rescore(Dims dm, const float* __restrict__ qbar,
                                                                const uint16_t* __restrict__ kc,
@@ -95,38 +98,36 @@ __global__ __launch_bounds__(kSelThreads) void sel_band_rescore(Dims dm, const f
   using Cfg = ScoreCfg<D, QB>;
   constexpr int LD = Cfg::LD, CG = Cfg::CG, RPI = Cfg::RPI, NLD = Cfg::NLD;
   __shared__ __align__(16) uint16_t tile[kScTile * LD];
-  __shared__ float ssq[kScTile];
-  __shared__ float smax[QB * kScTile];
-  __shared__ uint32_t band_loc[kSelTile];        // positions (relative to the tile) of the band keys, any order
+  __shared__ float ssq[2][kScTile];
+  __shared__ float smax[2][QB * kScTile];
+  __shared__ uint32_t band_loc[kBandCap];        // positions (relative to the block's first key) of the band keys, any order
   __shared__ uint32_t sh[kSelThreads + 2];
   __shared__ uint32_t bc[2];                     // cut bin, candidate slot base
-  __shared__ uint32_t cnt2[2][2];                // per tile parity: band count, sure-in count
+  __shared__ uint32_t n_band;                    // keys in band_loc
+  __shared__ uint32_t n_sure[2];                 // per tile parity: keys that are certainly selected
 
   const int kv = blockIdx.y, b = blockIdx.z;
   const SelCtx c = sel_ctx(dm, scores, kv_lens, budgets, ws, kv, b);
   const int tile_first = blockIdx.x * tpb;
-  if (c.B == 0 || c.B >= c.T || tile_first * kSelTile >= c.T) return;   // block-uniform
-  const int tile_end = min(tile_first + tpb, (c.T + kSelTile - 1) / kSelTile);
   const int tid = threadIdx.x, lane = tid & 63;
   const int w = __builtin_amdgcn_readfirstlane(tid >> 6);
   const int qb = w % QB, kg = w / QB;
   const int li = lane & 31, hf = lane >> 5;
-  if (tid < 4) (&cnt2[0][0])[tid] = 0u;
 
-  // Everything the block needs from memory before it can classify is requested up front: the first tile's
-  // provisional scores, the histogram, the error bound, and the query operands of the exact product.
+  // What the block needs from memory before it can classify is requested up front, before the cache length is known: the
+  // first tile's provisional scores, the histogram and the error bound.
   float p[kSelIPT];
-  auto load_p = [&](int t0) __attribute__((always_inline)) {
+  auto load_p = [&](int t0) __attribute__((always_inline)) {   // positions are clamped to the array
 #pragma unroll
-    for (int i = 0; i < kSelIPT; ++i) {
-      const int t = t0 + tid + kSelThreads * i;   // coalesced rows
-      p[i] = t < c.T ? c.sc[t] : 0.f;
-    }
+    for (int i = 0; i < kSelIPT; ++i) p[i] = c.sc[min(t0 + tid + kSelThreads * i, dm.T_max - 1)];   // coalesced rows
   };
   load_p(tile_first * kSelTile);
   uint32_t hv[kSelPer];
   load_hist_run(c.w.hist, hv);
   const float d2 = __uint_as_float(c.w.meta[kMetaEps2]);
+  if (c.B == 0 || c.B >= c.T || tile_first * kSelTile >= c.T) return;   // block-uniform
+  const int tile_end = min(tile_first + tpb, (c.T + kSelTile - 1) / kSelTile);
+  if (tid == 0) n_band = n_sure[0] = n_sure[1] = 0u;
   QueryTerms<D, true> qt;
   qt.load(qbar + (size_t)c.head * n_keep * D, n_keep, qb, li, hf, false);
 
@@ -143,6 +144,47 @@ __global__ __launch_bounds__(kSelThreads) void sel_band_rescore(Dims dm, const f
   const char* kbase = reinterpret_cast<const char*>(kc + b * dm.kvs[0] + kv * dm.kvs[1]);
   const uint32_t row_bytes = (uint32_t)dm.kvs[2] * 2u;
   const int cg = tid % CG, r0 = tid / CG;
+
+  // ---- exact scores of the listed keys, 128 at a time, by the tile arithmetic of the streaming kernel; the rows of the
+  // next 128 travel during the products ----
+  const int first_key = tile_first * kSelTile;
+  auto rescore = [&](int n) __attribute__((always_inline)) {
+    uint32_t slot = 0;
+    if (tid == 0) slot = atomicAdd(&c.w.meta[kMetaCand], (uint32_t)n);   // slots in the head's candidate list
+    u32x4 R[NLD];
+    auto load_rows = [&](int j0) __attribute__((always_inline)) {
+#pragma unroll
+      for (int i = 0; i < NLD; ++i) {
+        const int j = min(j0 + r0 + RPI * i, n - 1);   // tail slots repeat a real row; their scores are not used
+        const uint32_t row = (uint32_t)first_key + band_loc[j];
+        R[i] = *reinterpret_cast<const u32x4*>(kbase + (row * row_bytes + (uint32_t)cg * 16u));
+      }
+    };
+    load_rows(0);
+    for (int j0 = 0; j0 < n; j0 += kScTile) {
+      float* ssq_g = ssq[(j0 / kScTile) & 1];     // (a batch's norms and maxima are read while the next one is staged)
+      float* smax_g = smax[(j0 / kScTile) & 1];
+#pragma unroll
+      for (int i = 0; i < NLD; ++i) {
+        const int rl = r0 + RPI * i;
+        *reinterpret_cast<u32x4*>(tile + rl * LD + cg * 8) = R[i];
+        const float ss = row_sumsq<CG>(R[i]);
+        if (cg == 0) ssq_g[rl] = ss;
+      }
+      __syncthreads();
+      if (j0 + kScTile < n) load_rows(j0 + kScTile);
+      tile_products<D, QB, true>(tile, qt, qb, kg, li, hf, false, smax_g);
+      if (j0 == 0 && tid == 0) bc[1] = slot;
+      __syncthreads();
+      if (tid < kScTile && j0 + tid < n) {
+        const float s = tile_score<QB>(smax_g, ssq_g, tid, false, false, n_keep);
+        const uint32_t pos = (uint32_t)first_key + band_loc[j0 + tid], at = bc[1] + j0 + tid;
+        c.sc[pos] = s;
+        c.w.cand_key[at] = max(okey(s), 1u);
+        c.w.cand_pos[at] = pos;
+      }
+    }
+  };
 
   for (int tile_i = tile_first; tile_i < tile_end; ++tile_i) {
     const int t0 = tile_i * kSelTile;
@@ -163,53 +205,25 @@ __global__ __launch_bounds__(kSelThreads) void sel_band_rescore(Dims dm, const f
         mw[1] = (uint32_t)(bal >> 32);
       }
       uint32_t base = 0;
-      if (lane == 0 && bal != 0) base = atomicAdd(&cnt2[tile_i & 1][0], (uint32_t)__popcll(bal));
+      if (lane == 0 && bal != 0) base = atomicAdd(&n_band, (uint32_t)__popcll(bal));
       base = (uint32_t)__builtin_amdgcn_readfirstlane((int)base);
-      if (inb) band_loc[base + __popcll(bal & ((1ull << lane) - 1ull))] = (uint32_t)tl;
+      if (inb) band_loc[base + __popcll(bal & ((1ull << lane) - 1ull))] = (uint32_t)(t0 - first_key + tl);
     }
-    if (tile_i + 1 < tile_end) load_p(t0 + kSelTile);   // the next tile's scores travel during the re-scoring
+    if (tile_i + 1 < tile_end) load_p(t0 + kSelTile);   // the next tile's scores travel
     n_in = wave_incl_scan_u32(n_in);
-    if (lane == 63 && n_in) atomicAdd(&cnt2[tile_i & 1][1], n_in);
+    if (lane == 63 && n_in) atomicAdd(&n_sure[tile_i & 1], n_in);
     __syncthreads();
-    const int n_band = (int)cnt2[tile_i & 1][0];
+    const int n = (int)n_band;
     if (tid == 0) {
-      c.w.tile_in[tile_i] = cnt2[tile_i & 1][1];
-      if (n_band > 0) bc[1] = atomicAdd(&c.w.meta[kMetaCand], (uint32_t)n_band);   // slots in the head's candidate list
-      // the other parity's counters serve the next tile: their last readers passed the previous tile's second barrier
-      cnt2[(tile_i + 1) & 1][0] = 0u;
-      cnt2[(tile_i + 1) & 1][1] = 0u;
+      c.w.tile_in[tile_i] = n_sure[tile_i & 1];
+      n_sure[tile_i & 1] = 0u;   // (serves the tile after the next, a barrier away)
     }
-    __syncthreads();
-    const uint32_t slot0 = bc[1];
-
-    // ---- exact scores of the band keys, 128 at a time, by the tile arithmetic of the streaming kernel ----
-    for (int j0 = 0; j0 < n_band; j0 += kScTile) {
-      u32x4 R[NLD];
-#pragma unroll
-      for (int i = 0; i < NLD; ++i) {
-        const int j = min(j0 + r0 + RPI * i, n_band - 1);   // tail slots repeat a real row; their scores are not used
-        const uint32_t row = (uint32_t)t0 + band_loc[j];
-        R[i] = *reinterpret_cast<const u32x4*>(kbase + (row * row_bytes + (uint32_t)cg * 16u));
-      }
-#pragma unroll
-      for (int i = 0; i < NLD; ++i) {
-        const int rl = r0 + RPI * i;
-        *reinterpret_cast<u32x4*>(tile + rl * LD + cg * 8) = R[i];
-        const float ss = row_sumsq<CG>(R[i]);
-        if (cg == 0) ssq[rl] = ss;
-      }
+    if (n > kBandCap - kSelTile || (tile_i + 1 == tile_end && n > 0)) {   // block-uniform: the list may overflow, or it is complete
+      rescore(n);
       __syncthreads();
-      tile_products<D, QB, true>(tile, qt, qb, kg, li, hf, false, smax);
-      __syncthreads();
-      if (tid < kScTile && j0 + tid < n_band) {
-        const float s = tile_score<QB>(smax, ssq, tid, false, false, n_keep);
-        const uint32_t pos = (uint32_t)t0 + band_loc[j0 + tid];
-        c.sc[pos] = s;
-        c.w.cand_key[slot0 + j0 + tid] = max(okey(s), 1u);
-        c.w.cand_pos[slot0 + j0 + tid] = pos;
-      }
-      __syncthreads();   // the tile, norms and maxima are overwritten by the next batch (and band_loc by the next tile)
+      if (tid == 0) n_band = 0u;
     }
+    __syncthreads();   // (n_band has been read, or cleared)
   }
 }
 
