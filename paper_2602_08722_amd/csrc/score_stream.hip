@@ -90,10 +90,21 @@ __global__ __launch_bounds__(kStThreads, 1) void score_stream(Dims dm, const flo
   for (int i = tid; i < kSelBins / 2; i += kStThreads) lh[i] = 0u;
 
   // ---- this block's share of the flat step list ----
+  // Up to 64 sequences: lane i holds the length of sequence i and the steps up to its end (a loop over the lengths waits
+  // for each of them: prompt of 39000 in 56 chunks, whole call 349.7 -> 341.9 us; 8 sequences 0.4 us).
+  const bool by_lane = dm.b <= kWave;
+  int T_lane = 0;
+  uint32_t upto = 0;
   long long total = 0;
-  for (int b = 0; b < dm.b; ++b) {
-    const int T = max(0, min(kv_lens[b * dm.ls], dm.T_cap));
-    total += (long long)dm.n_kv * ((T + kStKeys - 1) / kStKeys);
+  if (by_lane) {
+    T_lane = lane < dm.b ? max(0, min(kv_lens[lane * dm.ls], dm.T_cap)) : 0;
+    upto = wave_incl_scan_u32((uint32_t)dm.n_kv * (uint32_t)((T_lane + kStKeys - 1) / kStKeys));   // (a card's memory holds fewer than 2^32 steps)
+    total = (uint32_t)__builtin_amdgcn_readlane((int)upto, kWave - 1);
+  } else {
+    for (int b = 0; b < dm.b; ++b) {
+      const int T = max(0, min(kv_lens[b * dm.ls], dm.T_cap));
+      total += (long long)dm.n_kv * ((T + kStKeys - 1) / kStKeys);
+    }
   }
   long long cur = total * blockIdx.x / gridDim.x;
   const long long end = total * (blockIdx.x + 1) / gridDim.x;
@@ -117,7 +128,13 @@ __global__ __launch_bounds__(kStThreads, 1) void score_stream(Dims dm, const flo
   while (cur < end) {
     // ---- locate (sequence, head, first step) of the segment and its length ----
     int T, nb;
-    for (;;) {
+    if (by_lane) {
+      sb = (int)__builtin_ctzll(__builtin_amdgcn_ballot_w64((uint32_t)cur < upto));   // (cur < total: some lane's)
+      T = __builtin_amdgcn_readlane(T_lane, sb);
+      nb = (T + kStKeys - 1) / kStKeys;
+      acc_steps = (uint32_t)__builtin_amdgcn_readlane((int)upto, sb) - (long long)dm.n_kv * nb;
+    }
+    while (!by_lane) {
       T = max(0, min(kv_lens[sb * dm.ls], dm.T_cap));
       nb = (T + kStKeys - 1) / kStKeys;
       if (cur < acc_steps + (long long)dm.n_kv * nb) break;
