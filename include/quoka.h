@@ -141,8 +141,9 @@ quoka_status quoka_topk_keys(const quoka_shape* shape, const float* scores, cons
  *                      within the proven error bound of the provisional cut; `scores` then holds the exact value
  *                      (as quoka_score_keys computes it, bit for bit) for those keys -- at least every key within
  *                      2^-11 of the cut -- and elsewhere the provisional value, which differs from the exact one by at
- *                      most max_r ||qbar_r - bf16(qbar_r)||_2 + 4e-6 (<= 2^-9).  In every other case the stage is the
- *                      two separate calls and `scores` is exact everywhere.                                          */
+ *                      most max_r ||qbar_r - bf16(qbar_r)||_2 + 4e-6 (<= 2^-9).  With at most eight retained queries,
+ *                      up to 131072 positions and at least 196608 of them over all heads, one pass is exact and so is
+ *                      `scores`.  In every other case the stage is the two separate calls and `scores` is exact.      */
 quoka_status quoka_select_keys(const quoka_shape* shape, const float* qbar, const void* k_cache,
                                const int32_t* kv_lens, const int32_t* budgets, float* scores, int32_t* k_idx,
                                int32_t* k_cnt, void* workspace, size_t workspace_bytes, void* stream);

@@ -573,7 +573,11 @@ static AttnPlan attn_plan(const Dims& dm, bool sparse) {
   const long long nrb = (long long)dm.g * ((dm.C + 31) / 32), heads = (long long)dm.n_kv * dm.b;
   const float step_us = dm.d == 128 ? 2.1f : 1.2f;   // a step is 8 row blocks x 64 keys or 4 x 128
   AttnPlan best{false, 1};
-  float best_us = 0.f;
+  float best_us = INFINITY;
+  // Whole key lists of a batch: the lengths may differ, which the model cannot know, and then smaller blocks fill up the
+  // second round where eight row blocks alone would be one (2 sequences of 2153 tokens, 14/2 heads, 5546 and 2547 keys: 240
+  // blocks of eight 255 us a call, 476 of four 244).
+  const bool few = heads * ((nrb + 7) / 8) < kComputeUnits;
   for (int mode = 0; mode < 2; ++mode) {
     const int kt = mode == 0 ? kSub : 2 * kSub, per_block = mode == 0 ? 8 : 4;
     const long long blocks = heads * ((nrb + per_block - 1) / per_block);
@@ -581,10 +585,11 @@ static AttnPlan attn_plan(const Dims& dm, bool sparse) {
     const long long tiles = ((long long)attended_cap(dm, sparse) + kt - 1) / kt + (dm.C + kt - 1) / kt;
     for (int n = 1; n <= limit; ++n) {
       if (n > 1 && heads * nrb * n > kMaxRecords) break;
+      if (n == 1 && dm.b > 1 && few != (mode == 1)) continue;
       const long long rounds = (blocks * n + kComputeUnits - 1) / kComputeUnits, steps = (tiles + n - 1) / n;
       float us = (float)rounds * ((float)steps * step_us + (mode == 0 ? 6.f : 8.f));
       if (n > 1) us += 5.f + (float)(heads * nrb * n) * (float)(dm.d + 2) * (256.f / 4e6f);   // written and read at ~4 TB/s
-      if ((mode == 0 && n == 1) || us < best_us) {
+      if (us < best_us) {
         best = AttnPlan{mode == 1, n};
         best_us = us;
       }
