@@ -64,6 +64,7 @@ quoka_status check_shape(const quoka_shape* s, Dims* dm) {
   dm->B_max = s->max_budget;
   dm->flags = s->score_flags;
   dm->ls = 1;
+  dm->prompt_chunks = 0;
   dm->C_last = dm->C;
   for (int i = 0; i < 3; ++i) {
     dm->qs[i] = s->q_stride[i];
@@ -113,9 +114,11 @@ struct CallInfo {
   int kv_cap = kMaxKv;   // no cache length of this call exceeds it
   int len_stride = 1;    // entries between the cache lengths (budgets) of neighbouring batch entries
   int last_len = 0;      // tokens of the last batch entry where it is shorter than the others
+  bool prompt_chunks = false;   // the batch entries are chunks of one prompt
   void apply(Dims* dm) const {
     dm->T_cap = kv_cap < dm->T_max ? kv_cap : dm->T_max;
     dm->ls = len_stride;
+    dm->prompt_chunks = prompt_chunks;
     if (last_len > 0) dm->C_last = last_len;
   }
 };
@@ -473,6 +476,7 @@ quoka_status quoka_prefill_attn(const quoka_shape* shape, int sparse, const void
         CallInfo info;
         info.kv_cap = (i0 + n - 1) * C;
         info.len_stride = shape->batch;
+        info.prompt_chunks = true;
         const bool holds_last = i0 + n == n_chunks;
         if (holds_last) info.last_len = last_len;
         const size_t first = (size_t)i0 * C;

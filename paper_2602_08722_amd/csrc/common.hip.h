@@ -21,9 +21,9 @@ struct Dims {
                // and picks variants, while T_max stays the extent of the tensors
   int flags;   // QUOKA_SCORE_* bits
   long long qs[3], kvs[3], cks[3], os[3];
-  // Several chunks of one prompt as the batch of one launch: their lengths and budgets lie `ls` entries apart, and the
+  // Several chunks of one prompt as the batch of one launch (prompt_chunks): their lengths and budgets lie `ls` entries apart, and the
   // last one may be shorter than the others (C_last; array layouts go by C).  Otherwise ls == 1 and C_last == C.
-  int ls, C_last;
+  int ls, C_last, prompt_chunks;
   __host__ __device__ int chunk(int bi) const { return bi + 1 == b ? C_last : C; }   // tokens of batch entry bi
 };
 

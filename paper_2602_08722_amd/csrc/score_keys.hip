@@ -277,8 +277,7 @@ static hipError_t launch_bf16(const Dims& dm, const float* qbar, const void* kc,
   // -- except where the batch entries are chunks of a prompt, which share one cache of which the earlier ones see little:
   // four rounds of shorter blocks even that out (prompt of 16000 in chunks of 1024, this launch 84 -> 57 us; 1024 blocks
   // 84, 4096 64; for caches of one length each, 2048 blocks cost 10-17 %).
-  const bool shared_cache = dm.b > 1 && dm.kvs[0] == 0;
-  const int wg_per_head = ((shared_cache ? 2048 : 512) + heads - 1) / heads;
+  const int wg_per_head = ((dm.prompt_chunks ? 2048 : 512) + heads - 1) / heads;
   int tpw = (nt + wg_per_head - 1) / wg_per_head;
   tpw = tpw < 1 ? 1 : tpw;
   dim3 grid((nt + tpw - 1) / tpw, dm.n_kv, dm.b);

@@ -7,8 +7,8 @@
 //                     result is bit-reproducible), then CosSim(q_i, M_Q) for the tile   -> ws.cos
 //   sq_select       : per (b, q-head) the N' lowest cosines in rank order (radix select on register-held
 //                     keys + rank by counting)                                          -> q_idx
-//   sq_head_select  : the three steps above in one block per (b, q-head), for short chunks (the rows of a head fit the
-//                     block's registers)
+//   sq_head_select  : the three steps above in one block per (b, q-head), for batches of short chunks (the rows of
+//                     a head fit the block's registers and the heads alone fill the chip)
 //   sq_qbar         : per (b, KV head, r) unit-normalise the r-th retained query of each head of the
 //                     group and average                                                 -> qbar
 #include "common.hip.h"
@@ -113,11 +113,10 @@ __global__ __launch_bounds__(kSqThreads) void sq_cosine(Dims dm, const T* __rest
 #pragma unroll
   for (int u = 0; u < kSqTile / RPB; ++u) rows[u].load(base + (size_t)min(t0 + u * RPB + rr, C - 1) * dm.qs[2] + cg * 8);
   __syncthreads();
-  if (threadIdx.x < 64) {   // one wave: squared norm of the mean
+  if (threadIdx.x == 0) {
     float ss = 0.f;
-    for (int i = threadIdx.x; i < D; i += 64) ss += mean[i] * mean[i];
-    ss = wave64_sum(ss);
-    if (threadIdx.x == 0) mnorm = fmaxf(sqrtf(ss), kNormEps);
+    for (int i = 0; i < D; ++i) ss += mean[i] * mean[i];
+    mnorm = fmaxf(sqrtf(ss), kNormEps);
   }
   __syncthreads();
   float m[8];
@@ -395,19 +394,18 @@ static hipError_t launch_typed(const Dims& dm, const void* q, int32_t* q_idx, fl
   } else {
     const dim3 sgrid(dm.n_q, dm.b), sblock(kSelThreads);
     const int ipt = (dm.C + kSelThreads - 1) / kSelThreads;
-    // One block per head for everything when the block can hold the head's queries in registers, 8 rows of 8 elements per
-    // thread.  Measured with sq_qbar (us, the three launches below -> one): 2 float32 heads of 128 x 64 16.9 -> 10.4, 36 of
-    // 333 x 64 16.1 -> 12.0, 32 of 512 x 128 16.7 -> 14.4, 256 of 512 x 128 24 -> 15.  With 16 rows per thread one compute
-    // unit pulls too little (32 heads of 1024 x 128 17.9 -> 21.9, 512 of them 63 -> 71), so longer chunks spread the two
-    // reads of Q over the whole chip.
+    // One block per head for everything when the block can hold the head's queries in registers (8 rows of 8 elements
+    // per thread) AND the heads alone give half the compute units a block (batches).  Measured: 256 heads of 512 tokens
+    // 14.8 us against 24 us for the three launches below; with only 32 heads (1024 tokens each) one compute unit per
+    // head is the slower way (20.7 against 16.5 us), so single sequences spread the two reads of Q over the whole chip.
+    // (Fewer heads of short chunks would gain 2-6 us, but the means of the two routes differ in the last bits, and cosines
+    // that differ in theirs only then change ranks: a sequence's route does not depend on what runs beside it, so the
+    // chunks of a prompt count as one sequence.)
+    constexpr int kRowsPerThread = 8;
     constexpr int kRowsAtOnce = kSelThreads / (D / 8);
-    const int rows_per_thread = (dm.C + kRowsAtOnce - 1) / kRowsAtOnce;
-    if (rows_per_thread <= 2) {
-      hipLaunchKernelGGL((sq_head_select<T, D, 2>), sgrid, sblock, 0, st, dm, qp, q_idx, n_keep);
-    } else if (rows_per_thread <= 4) {
-      hipLaunchKernelGGL((sq_head_select<T, D, 4>), sgrid, sblock, 0, st, dm, qp, q_idx, n_keep);
-    } else if (rows_per_thread <= 8) {
-      hipLaunchKernelGGL((sq_head_select<T, D, 8>), sgrid, sblock, 0, st, dm, qp, q_idx, n_keep);
+    const int sequences = dm.prompt_chunks ? 1 : dm.b;
+    if (dm.C <= kRowsAtOnce * kRowsPerThread && sequences * dm.n_q >= 128) {
+      hipLaunchKernelGGL((sq_head_select<T, D, kRowsPerThread>), sgrid, sblock, 0, st, dm, qp, q_idx, n_keep);
     } else {
       const int n_tiles = (dm.C + kSqTile - 1) / kSqTile;
       dim3 grid(n_tiles, dm.n_q, dm.b);
