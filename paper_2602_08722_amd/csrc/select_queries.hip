@@ -400,10 +400,10 @@ static hipError_t launch_typed(const Dims& dm, const void* q, int32_t* q_idx, fl
     // head is the slower way (20.7 against 16.5 us), so single sequences spread the two reads of Q over the whole chip.
     // (Fewer heads of short chunks would gain 2-6 us, but the means of the two routes differ in the last bits, and cosines
     // that differ in theirs only then change ranks: a sequence's route does not depend on what runs beside it, so the
-    // chunks of a prompt count as one sequence.)
+    // chunks of a prompt do not count.)
     constexpr int kRowsPerThread = 8;
     constexpr int kRowsAtOnce = kSelThreads / (D / 8);
-    const int sequences = dm.prompt_chunks ? 1 : dm.b;
+    const int sequences = dm.prompt_chunks ? dm.ls : dm.b;   // (ls: the batch of the whole call)
     if (dm.C <= kRowsAtOnce * kRowsPerThread && sequences * dm.n_q >= 128) {
       hipLaunchKernelGGL((sq_head_select<T, D, kRowsPerThread>), sgrid, sblock, 0, st, dm, qp, q_idx, n_keep);
     } else {
