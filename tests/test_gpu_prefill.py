@@ -113,3 +113,35 @@ def test_chunks_that_share_launches_match_chunk_after_chunk(dtype, batch, n_q, n
         t = (L - 1) // chunk * chunk
         assert torch.equal(one.scores[:, :, :t], many.scores[:, :, :t])
         assert (one.qbar - many.qbar).abs().max().item() <= 1e-6 or n_keep < min(n_retain, chunk)
+
+
+def _prompt_on_device(batch, n_q, n_kv, d, L, q_scale=1.0, seed=5):
+    rng = torch.Generator(device="cuda").manual_seed(seed)
+    q, k, v = (torch.randn(batch, n, L, d, device="cuda", generator=rng) for n in (n_q, n_kv, n_kv))
+    return (q * q_scale).bfloat16(), k.bfloat16(), v.bfloat16()
+
+
+@pytest.mark.parametrize("n_q,n_kv,d,L,chunk,n_retain,sparse", [
+    (2, 2, 64, 212, 64, 16, True),       # one head a group, last chunk of 20 tokens
+    (8, 2, 128, 1029, 256, 4, True),     # four heads a group, last chunk of 5
+    (8, 2, 128, 1029, 256, 4, False),
+])
+def test_decode_sized_last_chunk_is_scaled_in_float32(n_q, n_kv, d, L, chunk, n_retain, sparse):
+    """A last chunk that retains as many queries as the others but fits the decode kernel takes that kernel, which leaves Q
+    alone: logits of eight times unit variance, at the usual bar (the kernel for larger chunks is off by 0.06 there)."""
+    import paper_2602_08722_amd as pk
+    pk.load_library()
+    q, k, v = _prompt_on_device(1, n_q, n_kv, d, L, q_scale=8.0)
+    outs = []
+    for full in (False, True):
+        pb = pk.PrefillBuffers(q, k, v, chunk, n_retain, lambda t: t // 8)
+        if not full:
+            pb.workspace = pb.workspace[:pk.quoka_workspace_bytes(pb.shape)]
+        pb.run(sparse=sparse)
+        torch.cuda.synchronize()
+        outs.append(pb.out)
+    tail = (L - 1) // chunk * chunk
+    assert torch.equal(outs[0][:, :, tail:], outs[1][:, :, tail:])   # the same launches
+    if not sparse:
+        want = _full_causal(gen.from_torch(q)[0], gen.from_torch(k)[0], gen.from_torch(v)[0])[:, tail:]
+        assert P.max_abs(gen.from_torch(outs[1])[0][:, tail:], want) <= P.TOL_OUT["bf16"]
