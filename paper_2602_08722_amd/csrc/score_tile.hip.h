@@ -222,7 +222,9 @@ __device__ __forceinline__ float packed_products(const bf16x8 (&kop)[D / 16], co
   for (int i = 0; i < 4; ++i) m = fmaxf(m, ((c0[8 + i] + c1[8 + i]) + (c0[4 + i] + c1[4 + i])) + (c0[i] + c1[i]));
   return fmaxf(m, other_half(m));
 }
-// Whether a bf16 call takes this form: the scores' last bits depend on it, so every scoring kernel goes by this rule.
+// Whether a bf16 call takes this form: the scores' last bits depend on it, so every scoring kernel goes by this rule, and
+// in a prompt it goes by the prompt's length and the batch of the whole call: how many chunks share a launch, and how
+// much cache they have come to, must not decide between two nearly equal keys.
 // Bounds: sel_finish ranks within heads of up to kPackMaxKeys positions.  Long caches of few keys in all keep the
 // provisional scores, which are the documented output of that stage and which its tests look at (two heads of 65537
 // positions: 61.6 us a call, packed 48.9).
@@ -230,8 +232,9 @@ constexpr int kPackMaxKeys = 131072;
 constexpr long long kPackMinKeys = 3 << 16;
 inline bool score_packs(const Dims& dm) {
   const int n_keep = dm.n_ret < dm.C ? dm.n_ret : dm.C;
+  const long long sequences = dm.prompt_chunks ? dm.ls : dm.b;   // (ls: the batch of the whole call)
   return n_keep <= kPackRows && (dm.flags & (QUOKA_SCORE_DOT | QUOKA_SCORE_MEAN | QUOKA_SCORE_QBAR_BF16)) == 0 &&
-         (dm.T_cap <= 32768 || (dm.T_cap <= kPackMaxKeys && (long long)dm.b * dm.n_kv * dm.T_cap >= kPackMinKeys));
+         (dm.T_max <= 32768 || (dm.T_max <= kPackMaxKeys && sequences * dm.n_kv * dm.T_max >= kPackMinKeys));
 }
 
 // Score of key `k` of a tile from the per-query-block maxima (sums) and the squared norm.

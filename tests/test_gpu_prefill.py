@@ -80,6 +80,8 @@ def test_sparse_chunked_prefill_matches_oracle(L, chunk, n_retain, budget):
     ("bf16", 1, 8, 2, 128, 1500, 256, 16, False),
     ("f32", 1, 4, 2, 64, 900, 128, 16, True),        # float32: the short last chunk runs by itself
     ("f32", 2, 4, 2, 128, 1024, 128, 16, True),
+    ("bf16", 1, 4, 2, 64, 60000, 1024, 8, True),     # few queries, few keys in all: no packed scoring in any group
+    ("bf16", 1, 8, 8, 64, 36000, 600, 8, True),      # few queries, packed scoring in chunks of every length
 ])
 def test_chunks_that_share_launches_match_chunk_after_chunk(dtype, batch, n_q, n_kv, d, L, chunk, n_retain, sparse):
     """The same prompt with the workspace of one chunk (chunk after chunk) and with the full one (chunks as a batch)."""
