@@ -455,14 +455,14 @@ quoka_status quoka_prefill_attn(const quoka_shape* shape, int sparse, const void
   // Groups of chunks per sequence, as long as that takes fewer launches than chunk after chunk of the whole batch.
   // 32/8 heads, d 128, 16000 tokens in chunks of 1024: 106 launches, 1197 us -> 8 launches, 573 us: the short launches
   // of the selection run once, and the attention blocks of all chunks fill the chip together.  A short last chunk goes
-  // along where it keeps as many queries as the others and would take the same kernels by itself (a decode-sized one is
-  // attended by attn_decode_bf16, which rounds Q no second time).
+  // along where it selects as many queries as the others (up to n_retain tokens it keeps all, in position order) and would
+  // take the same kernels by itself (a decode-sized one is attended by attn_decode_bf16, which rounds Q no second time).
   const int last_len = L - (n_chunks - 1) * C;
   Dims last = dm;   // the last chunk by itself
   last.C = last.C_last = last_len;
-  const int keep = dm.n_ret < C ? dm.n_ret : C, keep_last = dm.n_ret < last_len ? dm.n_ret : last_len;
+  const int keep = dm.n_ret < C ? dm.n_ret : C;
   const bool last_along =
-      last_len == C || (shape->dtype == QUOKA_BF16 && !quoka::attn_decode_applies(last) && keep_last == keep);
+      last_len == C || (shape->dtype == QUOKA_BF16 && !quoka::attn_decode_applies(last) && last_len > dm.n_ret);
   const int n_grouped = last_along ? n_chunks : n_chunks - 1;
   const int most = group_chunks(*shape, dm, n_grouped, workspace_bytes);
   const int n_groups = n_grouped > 0 ? (n_grouped + most - 1) / most : 0;

@@ -147,3 +147,26 @@ def test_decode_sized_last_chunk_is_scaled_in_float32(n_q, n_kv, d, L, chunk, n_
     if not sparse:
         want = _full_causal(gen.from_torch(q)[0], gen.from_torch(k)[0], gen.from_torch(v)[0])[:, tail:]
         assert P.max_abs(gen.from_torch(outs[1])[0][:, tail:], want) <= P.TOL_OUT["bf16"]
+
+
+@pytest.mark.parametrize("n_retain", [15, 16, 17])
+def test_last_chunk_of_as_many_tokens_as_are_retained(n_retain):
+    """Up to n_retain tokens all are kept, in position order (16 tokens of four heads a group: not decode-sized)."""
+    import paper_2602_08722_amd as pk
+    pk.load_library()
+    q, k, v = _prompt_on_device(1, 8, 2, 64, 3 * 256 + 16)
+    got = []
+    for full in (False, True):
+        pb = pk.PrefillBuffers(q, k, v, 256, n_retain, lambda t: t // 8)
+        if not full:
+            pb.workspace = pb.workspace[:pk.quoka_workspace_bytes(pb.shape)]
+        pb.run()
+        torch.cuda.synchronize()
+        n = min(n_retain, 16)
+        # (where the last chunk retains fewer queries than the others, its arrays are packed by its own number)
+        q_idx, qbar = pb.q_idx.flatten()[:8 * n].view(8, n), pb.qbar.flatten()[:2 * n * 64]
+        got.append((q_idx, qbar, pb.k_cnt, pb.k_idx[:, :, :int(pb.k_cnt[0, 0])]))
+        if n == 16:
+            assert torch.equal(q_idx, torch.arange(16, device="cuda", dtype=torch.int32).expand(8, 16))
+    for a, b in zip(*got):
+        assert torch.equal(a, b)
