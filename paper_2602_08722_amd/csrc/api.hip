@@ -456,13 +456,15 @@ quoka_status quoka_prefill_attn(const quoka_shape* shape, int sparse, const void
   // 32/8 heads, d 128, 16000 tokens in chunks of 1024: 106 launches, 1197 us -> 8 launches, 573 us: the short launches
   // of the selection run once, and the attention blocks of all chunks fill the chip together.  A short last chunk goes
   // along where it selects as many queries as the others (up to n_retain tokens it keeps all, in position order) and would
-  // take the same kernels by itself (a decode-sized one is attended by attn_decode_bf16, which rounds Q no second time).
+  // take the same kernels by itself (a decode-sized one is attended by attn_decode_bf16, which rounds Q no second time;
+  // the query stage's two routes round the mean differently).
   const int last_len = L - (n_chunks - 1) * C;
   Dims last = dm;   // the last chunk by itself
   last.C = last.C_last = last_len;
   const int keep = dm.n_ret < C ? dm.n_ret : C;
   const bool last_along =
-      last_len == C || (shape->dtype == QUOKA_BF16 && !quoka::attn_decode_applies(last) && last_len > dm.n_ret);
+      last_len == C || (shape->dtype == QUOKA_BF16 && !quoka::attn_decode_applies(last) && last_len > dm.n_ret &&
+                        quoka::select_queries_one_block(last) == quoka::select_queries_one_block(dm));
   const int n_grouped = last_along ? n_chunks : n_chunks - 1;
   const int most = group_chunks(*shape, dm, n_grouped, workspace_bytes);
   const int n_groups = n_grouped > 0 ? (n_grouped + most - 1) / most : 0;

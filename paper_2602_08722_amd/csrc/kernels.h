@@ -33,6 +33,7 @@ hipError_t launch_select_queries(const Dims& dm, int dtype, const void* q, int32
                                  uint16_t* terms = nullptr);
 // (`terms`: the last launch also leaves Qbar as the exact scorer's operands, TermsLayout of score_tile.hip.h; bf16)
 size_t query_terms_bytes(const Dims& dm);
+bool select_queries_one_block(const Dims& dm);   // which of its two routes (C > n_ret) the launch takes
 
 // --- key scoring (score_keys.hip) ---------------------------------------------------------------
 // `zero` / `zero_words`: optional side job for the fused call -- the scoring blocks clear that many 32-bit words (the

@@ -378,6 +378,20 @@ __global__ __launch_bounds__(64) void sq_qbar(Dims dm, const T* __restrict__ q, 
 }
 
 // ---------------------------------------------------------------------------------------------
+// One block per head for everything when the block can hold the head's queries in registers (8 rows of 8 elements
+// per thread) AND the heads alone give half the compute units a block (batches).  Measured: 256 heads of 512 tokens
+// 14.8 us against 24 us for the three launches below; with only 32 heads (1024 tokens each) one compute unit per
+// head is the slower way (20.7 against 16.5 us), so single sequences spread the two reads of Q over the whole chip.
+// (Fewer heads of short chunks would gain 2-6 us, but the means of the two routes differ in the last bits, and cosines
+// that differ in theirs only then change ranks, so the line stays where it is.  The route goes by the batch of the whole
+// call and the chunk's own length; how many chunks of a prompt share a launch does not count.)
+constexpr int kRowsPerThread = 8;
+bool select_queries_one_block(const Dims& dm) {
+  const int rows_at_once = kSelThreads / (dm.d / 8);
+  const int sequences = dm.prompt_chunks ? dm.ls : dm.b;   // (ls: the batch of the whole call)
+  return dm.C <= rows_at_once * kRowsPerThread && sequences * dm.n_q >= 128;
+}
+
 template <typename T, int D>
 static hipError_t launch_typed(const Dims& dm, const void* q, int32_t* q_idx, float* qbar, float* ws_part,
                                float* ws_cos, hipStream_t st, uint32_t* zero, uint32_t zero_words,
@@ -394,17 +408,7 @@ static hipError_t launch_typed(const Dims& dm, const void* q, int32_t* q_idx, fl
   } else {
     const dim3 sgrid(dm.n_q, dm.b), sblock(kSelThreads);
     const int ipt = (dm.C + kSelThreads - 1) / kSelThreads;
-    // One block per head for everything when the block can hold the head's queries in registers (8 rows of 8 elements
-    // per thread) AND the heads alone give half the compute units a block (batches).  Measured: 256 heads of 512 tokens
-    // 14.8 us against 24 us for the three launches below; with only 32 heads (1024 tokens each) one compute unit per
-    // head is the slower way (20.7 against 16.5 us), so single sequences spread the two reads of Q over the whole chip.
-    // (Fewer heads of short chunks would gain 2-6 us, but the means of the two routes differ in the last bits, and cosines
-    // that differ in theirs only then change ranks: a sequence's route does not depend on what runs beside it, so the
-    // chunks of a prompt do not count.)
-    constexpr int kRowsPerThread = 8;
-    constexpr int kRowsAtOnce = kSelThreads / (D / 8);
-    const int sequences = dm.prompt_chunks ? dm.ls : dm.b;   // (ls: the batch of the whole call)
-    if (dm.C <= kRowsAtOnce * kRowsPerThread && sequences * dm.n_q >= 128) {
+    if (select_queries_one_block(dm)) {
       hipLaunchKernelGGL((sq_head_select<T, D, kRowsPerThread>), sgrid, sblock, 0, st, dm, qp, q_idx, n_keep);
     } else {
       const int n_tiles = (dm.C + kSqTile - 1) / kSqTile;

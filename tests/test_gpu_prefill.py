@@ -170,3 +170,25 @@ def test_last_chunk_of_as_many_tokens_as_are_retained(n_retain):
             assert torch.equal(q_idx, torch.arange(16, device="cuda", dtype=torch.int32).expand(8, 16))
     for a, b in zip(*got):
         assert torch.equal(a, b)
+
+
+def test_short_last_chunk_keeps_its_query_route():
+    """128 heads, full chunks beyond what one block per head holds, a last chunk within: cosines so close together that the
+    last bits of the mean decide ranks."""
+    import paper_2602_08722_amd as pk
+    pk.load_library()
+    L, chunk = 6 * 1024 + 300, 1024
+    q, k, v = _prompt_on_device(4, 32, 8, 128, L)
+    rng = torch.Generator(device="cuda").manual_seed(6)
+    lean = 30.0 * torch.randn(4, 32, 1, 128, device="cuda", generator=rng)
+    q = (lean + q.float()).bfloat16()
+    got = []
+    for full in (False, True):
+        pb = pk.PrefillBuffers(q, k, v, chunk, 64, lambda t: t // 8)
+        if not full:
+            pb.workspace = pb.workspace[:pk.quoka_workspace_bytes(pb.shape)]
+        pb.run()
+        torch.cuda.synchronize()
+        got.append((pb.q_idx, pb.qbar, pb.k_cnt, pb.k_idx[:, :, :int(pb.k_cnt[0, 0])]))
+    for a, b in zip(*got):
+        assert torch.equal(a, b)
