@@ -192,3 +192,32 @@ def test_short_last_chunk_keeps_its_query_route():
         got.append((pb.q_idx, pb.qbar, pb.k_cnt, pb.k_idx[:, :, :int(pb.k_cnt[0, 0])]))
     for a, b in zip(*got):
         assert torch.equal(a, b)
+
+
+@pytest.mark.parametrize("dtype,n_q,n_kv,L,chunk,sparse", [
+    ("bf16", 4, 1, 300, 8, False),      # decode kernel
+    ("bf16", 4, 1, 300, 8, True),
+    ("bf16", 4, 2, 900, 64, False),     # key lists split over blocks
+    ("f32", 4, 2, 500, 32, False),
+])
+@pytest.mark.parametrize("full", [False, True], ids=["chunk-after-chunk", "grouped"])
+def test_cache_lengths_beyond_the_prompt_position_are_cut(dtype, n_q, n_kv, L, chunk, sparse, full):
+    """No chunk sees cache rows that its launch was not sized for (every partial result that is added up has been written:
+    the workspace holds NaN).  Chunk after chunk that is the chunk's own position."""
+    import paper_2602_08722_amd as pk
+    pk.load_library()
+    q, k, v = (x if dtype == "bf16" else x.float() for x in _prompt_on_device(1, n_q, n_kv, 64, L))
+    outs = []
+    for beyond in (False, True):
+        pb = pk.PrefillBuffers(q, k, v, chunk, 4, lambda t: t // 4)
+        if beyond:
+            pb.kv_lens_all.fill_(L)
+        if not full:
+            pb.workspace = pb.workspace[:pk.quoka_workspace_bytes(pb.shape)]
+        pb.workspace.fill_(0xFF)
+        pb.run(sparse=sparse)
+        torch.cuda.synchronize()
+        outs.append(pb.out)
+    assert not torch.isnan(outs[1].float()).any()
+    if not full:
+        assert torch.equal(outs[0], outs[1])
