@@ -1,10 +1,12 @@
 // Top-B key selection per (sequence, KV head) (Alg. 1: I = topk(S-hat, B_SA); Eq. 3).
 //
-// Exact radix select on order-preserving uint32 images of the float scores, then an ordered
-// compaction so that indices come out in ascending position and equal scores go to the lower
-// position.  Integer work only: the result is deterministic and independent of the launch shape.
+// The cut (the B-th largest score) is found exactly, and an ordered compaction emits the positions of the scores above it
+// and of the first ones equal to it: ascending, equal scores to the lower position.  Scores are compared as floats (-0
+// equals +0, a NaN ranks as the infinity of its sign), or as order-preserving images that compare alike, so the result is
+// deterministic and does not depend on the launch shape.
 //
-//   T_max <= kSmallMax : one to four 1024-thread blocks per head, keys held in registers, one launch.
+//   T_max <= kSmallMax : one to four 1024-thread blocks per head, scores held in registers, one launch; the cut from a
+//                        histogram over equal score bins and a count of ranks in the cut's bin.
 //   larger             : several blocks per head.  Three histogram passes (11 + 11 + 10 bits, global
 //                        integer atomics) find the cut key; a count pass and an emit pass produce
 //                        the ordered index list.  Each launch derives the newest step of the cut
@@ -308,6 +310,12 @@ __device__ __forceinline__ Cut derive_cut(const uint32_t* __restrict__ hist, uin
   return c;
 }
 
+// A score's key image in the multi-block path: one zero, and a NaN as the infinity of its sign, as in the register path.
+__device__ __forceinline__ uint32_t score_key(float s) {
+  const uint32_t inf = (__float_as_uint(s) & 0x80000000u) | 0x7F800000u;
+  return okey(s != s ? __uint_as_float(inf) : s + 0.0f);
+}
+
 __global__ void topk_zero(uint32_t* __restrict__ p, size_t n) {
   for (size_t i = (size_t)blockIdx.x * blockDim.x + threadIdx.x; i < n; i += (size_t)gridDim.x * blockDim.x) p[i] = 0u;
 }
@@ -353,7 +361,7 @@ __global__ __launch_bounds__(kLgThreads) void topk_hist(Dims dm, const float* __
   const uint32_t bm = radix_bins(PASS) - 1u;
   const int t1 = min(t0 + kLgTile, c.T);
   for (int i = t0 + threadIdx.x; i < t1; i += kLgThreads) {
-    const uint32_t k = okey(c.sc[i]);
+    const uint32_t k = score_key(c.sc[i]);
     if ((k & cut.mask) == cut.prefix) atomicAdd(&lh[(k >> sft) & bm], 1u);
   }
   __syncthreads();
@@ -394,7 +402,7 @@ __global__ __launch_bounds__(kLgThreads) void topk_finish(Dims dm, const float* 
 #pragma unroll
   for (int i = 0; i < IPT; ++i) {
     const int t = lo + i;
-    const uint32_t k = t < t1 ? okey(c.sc[t]) : 0u;   // 0 is below every real key image except okey(-NaN); never > tau
+    const uint32_t k = t < t1 ? score_key(c.sc[t]) : 0u;   // 0 is below every key image
     kreg[i] = k;
     cnt += ((t < t1) && (k > tau) ? 0x10000u : 0u) + ((t < t1) && (k == tau) ? 1u : 0u);
   }

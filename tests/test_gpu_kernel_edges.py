@@ -190,3 +190,27 @@ def test_top_b_of_scores_that_are_not_finite(T, B):
         ranked = np.where(np.isnan(s), np.copysign(np.float32(np.inf), s), s)
         want = np.stack([np.sort(np.argsort(-r, kind="stable")[:B]) for r in ranked])
         assert np.array_equal(gen.from_torch(buf.k_idx)[0][:, :B], want), share
+
+
+@pytest.mark.parametrize("T,B", [(9001, 4500), (32768, 20000), (32769, 20000), (70001, 30000)])
+def test_top_b_ties_of_signed_zeros_and_nan_on_both_sides_of_the_register_path(T, B):
+    """Equal scores go to the lower position, whatever the sign of a zero, and a NaN ranks as the infinity of its sign:
+    the register path (up to 32768 scores) and the multi-block path alike."""
+    w = gen.make_custom(dtype="bf16", n_q=2, n_kv=2, d=64, chunk=40, n_retain=16, kv_lens=[T], budgets=[B], batch=1, seed=3)
+    rng = np.random.default_rng(12)
+    zeros = rng.choice(np.array([0.0, -0.0], dtype=np.float32), size=(2, T))
+    zeros[:, ::9] = rng.choice(np.array([1.5, -1.5], dtype=np.float32), size=zeros[:, ::9].shape)
+    odd = rng.standard_normal((2, T)).astype(np.float32)
+    at = rng.random((2, T)) < 0.5 * B / T   # (the cut lies among the infinities where B is small)
+    odd[at] = rng.choice(np.array([np.nan, -np.nan, np.inf, -np.inf], dtype=np.float32), size=int(at.sum()))
+    odd[:, 5:T:max(1, 2 * T // (3 * B))] = np.inf
+    for s in (zeros, odd):
+        buf = _buffers(w)
+        buf.scores.copy_(torch.from_numpy(s)[None])
+        buf.workspace.fill_(0xA5)
+        buf.k_idx.fill_(-1)
+        buf.topk_keys()
+        torch.cuda.synchronize()
+        ranked = np.where(np.isnan(s), np.copysign(np.float32(np.inf), s), s)
+        want = np.stack([np.sort(np.argsort(-r, kind="stable")[:B]) for r in ranked])
+        assert np.array_equal(gen.from_torch(buf.k_idx)[0][:, :B], want)
