@@ -178,10 +178,11 @@ __device__ __forceinline__ uint32_t block_excl_scan(uint32_t x, uint32_t* wsum, 
 // range and would otherwise pile into one or two bins of the first passes).  One block barrier per pass: the
 // histograms rotate through three LDS buffers (the buffer of pass p is cleared during pass p+2's predecessor), and
 // every wave locates the cut bin for itself from the finished histogram, so nothing is handed around through LDS.
-struct RadixSelectLds {
+struct __align__(16) RadixSelectLds {
   uint32_t hist[3][256];
   uint32_t wmin[16], wmax[16];
 };
+static_assert(alignof(RadixSelectLds) >= sizeof(u32x4), "the histograms are read 16 bytes at a time");
 
 template <int IPT, bool DESC>
 __device__ __forceinline__ void block_radix_select(const uint32_t (&key)[IPT], uint32_t valid, uint32_t need,

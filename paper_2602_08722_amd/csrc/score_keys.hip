@@ -70,7 +70,7 @@ __global__ __launch_bounds__(kScThreads, 2) void score_bf16(Dims dm, const float
   const int T = min(kv_lens[b * dm.ls], dm.T_cap);
   const float* qhead = qbar + (size_t)(b * dm.n_kv + kv) * n_keep * D;
   if constexpr (FUSE) {
-    __shared__ float qrows[kPackRows * D];
+    __shared__ __align__(16) float qrows[kPackRows * D];   // (read 16 bytes at a time)
     if (t_begin >= T && blockIdx.x != 0) return;   // block-uniform
     constexpr int EPL = D / 64;
     for (int r = w; r < n_keep; r += kScThreads / 64) {
