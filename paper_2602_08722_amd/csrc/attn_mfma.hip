@@ -564,37 +564,81 @@ struct AttnPlan {
   bool split_tile;
   int n_splits;
 };
+
+// Whole key lists: eight row blocks per block, or four.
+// A batch: eight where that gives every compute unit a block.  (The lengths may differ, which the host cannot know, and then
+// smaller blocks fill up the second round where eight row blocks alone would be one: 2 sequences of 2153 tokens, 14/2
+// heads, 5546 and 2547 keys: 240 blocks of eight 255 us a call, 476 of four 235.)
+// One sequence: blocks of four take two rounds where eight take one, and each costs more per key, but in the second round
+// the blocks with the shortest causal ranges follow each other, so up to 128 groups of eight four is the faster, from
+// there on it depends on how much of the list is the chunk's own.  The bound is a fit of the two times' difference, in us,
+// to 172 measured pairs (groups 130 - 250, chunks 1056 - 4096, 0 - 4096 keys; rms 1.5 %), less 0.5 - 1 us.  Attention, eight
+// against four, d 128: 32/8 heads, 1312 tokens over 983 keys 62 / 72 us, over 3932 134 / 164; 12/4 heads, 3000 tokens over
+// 983 92 / 96, over none 66.9 / 65.4; d 64: 12/4 heads, 2752 tokens over none 43 / 37, over 2048 78.4 / 76.8.
+// Above 256 groups the rounds decide: 32/8 heads, d 128, 2400 tokens over 983 keys, 304 groups 140 / 123 us; 3072 tokens, 384
+// groups 164 / 155; 4096 tokens, 512 groups 200 / 232.
+static bool eight_row_blocks(const Dims& dm, bool sparse, long long groups) {
+  if (dm.b > 1 || groups == kComputeUnits) return groups >= kComputeUnits;
+  if (groups > kComputeUnits) {   // two rounds of four blocks a unit and more: a step of four row blocks takes as long
+    const long long rounds8 = (groups + kComputeUnits - 1) / kComputeUnits;
+    return 2 * rounds8 <= (2 * groups + kComputeUnits - 1) / kComputeUnits;
+  }
+  if (groups <= kComputeUnits / 2) return false;
+  const float c = (float)attended_cap(dm, sparse) / kSub, r = (float)dm.C / kSub, n = (float)groups;
+  return dm.d == 128 ? 6.2f + 0.36f * c + r * (0.147f - 47.4f / n) > 0.f : 4.8f + 0.114f * c + r * (0.093f - 41.1f / n) > 0.f;
+}
+
 // Few row blocks leave compute units idle whatever the tile mode; their key lists are split over blocks instead.
 // Measured (kernel and merge, unsplit -> split): 4 KV heads x 3 sequences, d 64, 333 tokens over 4999 keys (2 splits)
 // 60 -> 38 us; one KV head of 16 q-heads x 8 sequences, d 64, 69 tokens over 13477 keys (5 splits) 138 -> 65 us.
 // The cheapest of the variants by a model of the launch in microseconds: rounds of 256 resident blocks, each as long as
 // its share of the longest key list plus a fixed part, and for a split list the partials' traffic and the merge launch.
+// Lists of a few steps are then left whole where that is the faster after all: the model has no term for a merge that adds
+// up one split after the other, and takes a short launch for longer than it is.  The two times are fits to measured calls
+// (33 - 660 tokens over 0 - 3000 keys, 229 split and 888 whole; rms 0.3 us split at d 64, 0.5 at d 128).  Whole against the
+// model's splits: 2 KV heads of 2, d 64, 332 tokens over 132 keys 11.7 / 14.5 us (9 splits); 8 heads, d 128, 33 tokens over
+// 200 12.6 / 13.4 (5); 14/2 heads, d 64, 59 tokens over 448 11.5 / 12.9 (8).
+static bool whole_is_faster(const Dims& dm, const AttnPlan& split, long long split_steps, float partials_us,
+                            long long whole_steps) {
+  struct Fit {
+    float fixed, step, merge;
+  };
+  constexpr Fit kFits[2][2] = {{{8.4f, 0.95f, 0.38f}, {7.9f, 1.30f, 0.36f}},    // d 64: eight row blocks, four
+                               {{9.5f, 1.35f, 0.41f}, {9.8f, 1.97f, 0.46f}}};   // d 128
+  const Fit& f = kFits[dm.d == 128][split.split_tile];
+  const float whole = dm.d == 128 ? 7.6f + 1.99f * (float)whole_steps : 6.8f + 1.10f * (float)whole_steps;
+  return whole < f.fixed + f.step * (float)split_steps + f.merge * (float)split.n_splits + partials_us + 0.6f;
+}
+
 static AttnPlan attn_plan(const Dims& dm, bool sparse) {
   const long long nrb = (long long)dm.g * ((dm.C + 31) / 32), heads = (long long)dm.n_kv * dm.b;
+  if (heads * nrb * 2 > kMaxRecords) return AttnPlan{!eight_row_blocks(dm, sparse, heads * ((nrb + 7) / 8)), 1};
+  // (from here on there are at most 128 blocks of eight row blocks: a whole list takes blocks of four, in one round)
   const float step_us = dm.d == 128 ? 2.1f : 1.2f;   // a step is 8 row blocks x 64 keys or 4 x 128
-  AttnPlan best{false, 1};
-  float best_us = INFINITY;
-  // Whole key lists of a batch: the lengths may differ, which the model cannot know, and then smaller blocks fill up the
-  // second round where eight row blocks alone would be one (2 sequences of 2153 tokens, 14/2 heads, 5546 and 2547 keys: 240
-  // blocks of eight 255 us a call, 476 of four 244).
-  const bool few = heads * ((nrb + 7) / 8) < kComputeUnits;
+  AttnPlan best{true, 1};
+  float best_us = INFINITY, partials_us = 0.f;
+  long long split_steps = 0, whole_steps = 0;
   for (int mode = 0; mode < 2; ++mode) {
     const int kt = mode == 0 ? kSub : 2 * kSub, per_block = mode == 0 ? 8 : 4;
     const long long blocks = heads * ((nrb + per_block - 1) / per_block);
     const int limit = key_splits_limit(dm, sparse, kt);
     const long long tiles = ((long long)attended_cap(dm, sparse) + kt - 1) / kt + (dm.C + kt - 1) / kt;
-    for (int n = 1; n <= limit; ++n) {
-      if (n > 1 && heads * nrb * n > kMaxRecords) break;
-      if (n == 1 && dm.b > 1 && few != (mode == 1)) continue;
+    whole_steps = tiles;   // (of the last mode)
+    for (int n = 1; n <= limit && heads * nrb * n <= kMaxRecords; ++n) {
+      if (n == 1 && dm.b > 1 && mode == 0) continue;
       const long long rounds = (blocks * n + kComputeUnits - 1) / kComputeUnits, steps = (tiles + n - 1) / n;
+      const float partials = (float)(heads * nrb * n) * (float)(dm.d + 2) * (256.f / 4e6f);   // written and read at ~4 TB/s
       float us = (float)rounds * ((float)steps * step_us + (mode == 0 ? 6.f : 8.f));
-      if (n > 1) us += 5.f + (float)(heads * nrb * n) * (float)(dm.d + 2) * (256.f / 4e6f);   // written and read at ~4 TB/s
+      if (n > 1) us += 5.f + partials;
       if (us < best_us) {
         best = AttnPlan{mode == 1, n};
         best_us = us;
+        partials_us = partials;
+        split_steps = rounds * steps;
       }
     }
   }
+  if (best.n_splits == 1 || whole_is_faster(dm, best, split_steps, partials_us, whole_steps)) return AttnPlan{true, 1};
   return best;
 }
 

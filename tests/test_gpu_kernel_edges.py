@@ -108,6 +108,18 @@ def test_bf16_attention_key_splits_of_eight_row_blocks():
                     rows=[0, 1, 31, 32, 700, 1311, 1312, 1340])
 
 
+# whole key lists of one sequence: one round of blocks of eight row blocks (130 of them, the last one not full; long lists
+# and none), and two rounds of blocks of four (264 of eight)
+@pytest.mark.parametrize("case", [
+    dict(n_q=16, n_kv=1, d=64, chunk=2070, kv_lens=[3000], budgets=[2500]),
+    dict(n_q=16, n_kv=1, d=64, chunk=2070, kv_lens=[0], budgets=[1]),
+    dict(n_q=7, n_kv=1, d=128, chunk=4803, kv_lens=[700], budgets=[129]),
+    dict(n_q=32, n_kv=8, d=64, chunk=2081, kv_lens=[100], budgets=[65]),
+], ids=_id)
+def test_bf16_attention_whole_lists_of_one_sequence(case):
+    check_attention(dict(case, dtype="bf16"), rows=[0, 31, 32, 1000, case["chunk"] - 33, case["chunk"] - 1])
+
+
 # decode kernel: single slots, tiles of 32 short of and past full, fewer tiles than waves or blocks, batches whose shares
 # of the blocks differ, batches beyond one wave's lanes
 DECODE_CASES = [
