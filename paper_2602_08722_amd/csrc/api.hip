@@ -454,7 +454,8 @@ quoka_status quoka_prefill_attn(const quoka_shape* shape, int sparse, const void
 
   // Groups of chunks per sequence, as long as that takes fewer launches than chunk after chunk of the whole batch.
   // 32/8 heads, d 128, 16000 tokens in chunks of 1024: 106 launches, 1197 us -> 8 launches, 573 us: the short launches
-  // of the selection run once, and the attention blocks of all chunks fill the chip together.  A short last chunk goes
+  // of the selection run once, and the attention blocks of all chunks fill the chip together.  (Batches: 2 sequences of
+  // 16000 1777 -> 1099 us, 8 of them 5125 -> 4389, 8 of 20000 in chunks of 500, 8/2 heads 3844 -> 2104.)  A short last chunk goes
   // along where it selects as many queries as the others (up to n_retain tokens it keeps all, in position order) and would
   // take the same kernels by itself (a decode-sized one is attended by attn_decode_bf16, which rounds Q no second time;
   // the query stage's two routes round the mean differently).

@@ -377,7 +377,6 @@ static int decode_slots(const Dims& dm) {
 }
 
 size_t attn_decode_ws_floats(const Dims& dm) {
-  if (dm.g > 32) return 0;
   // independent of the chunk length (a prompt's last chunk may be decode-sized when the others are not)
   return (size_t)dm.n_kv * decode_slots(dm) * 32 * (2 + dm.d);
 }

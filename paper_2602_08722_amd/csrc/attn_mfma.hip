@@ -642,7 +642,8 @@ static AttnPlan attn_plan(const Dims& dm, bool sparse) {
   return best;
 }
 
-// Both factors of the first bound grow with the chunk length, so shorter chunks of the same shape fit as well.
+// Both factors of the first bound grow with the chunk length, so shorter chunks of the same shape fit as well: a prompt's last
+// chunk may be split where the others never are (heads * nrb beyond kMaxRecords / 2), with the same workspace.
 size_t attn_bf16_ws_floats(const Dims& dm) {
   const long long nrb = (long long)dm.g * ((dm.C + 31) / 32), heads = (long long)dm.n_kv * dm.b;
   const long long most = heads * nrb * key_splits_limit(dm, false, kSub);

@@ -56,10 +56,6 @@ __device__ __forceinline__ float row_sumsq(const u32x4& r) {
   }
 }
 
-// Query operands of one wave: 32 rows of Qbar (rows qb*32 .. +32 of a head's [n_keep][D] float32 block) as bf16
-// terms.  EXACT: hi + mid + lo add up to the float32 value exactly, so with bf16 keys every product is exact and only
-// the float32 accumulation rounds.  Otherwise only hi (Qbar rounded to bf16) is formed.  Rows past n_keep repeat the
-// last real query (the max is unchanged); `zero_pad` makes them zero instead (for the mean over queries).
 // The three terms of a row of Qbar as the launch that forms it can leave them, 16 bytes a lane in operand order:
 // [row block][k-step][term][lane].  A scoring block then fetches whole kilobytes and converts nothing (64 elements a lane,
 // about 450 instructions): 8 heads of 8192 keys, 64 queries 10.4 -> 8.7 us, call 72.7 -> 69.9; 128 queries x 32768 keys
@@ -74,6 +70,10 @@ struct TermsLayout {
   }
 };
 
+// Query operands of one wave: 32 rows of Qbar (rows qb*32 .. +32 of a head's [n_keep][D] float32 block) as bf16
+// terms.  EXACT: hi + mid + lo add up to the float32 value exactly, so with bf16 keys every product is exact and only
+// the float32 accumulation rounds.  Otherwise only hi (Qbar rounded to bf16) is formed.  Rows past n_keep repeat the
+// last real query (the max is unchanged); `zero_pad` makes them zero instead (for the mean over queries).
 template <int D, bool EXACT>
 struct QueryTerms {
   bf16x8 hi[D / 16], mid[D / 16], lo[D / 16];
@@ -225,9 +225,9 @@ __device__ __forceinline__ float packed_products(const bf16x8 (&kop)[D / 16], co
 // Whether a bf16 call takes this form: the scores' last bits depend on it, so every scoring kernel goes by this rule, and
 // in a prompt it goes by the prompt's length and the batch of the whole call: how many chunks share a launch, and how
 // much cache they have come to, must not decide between two nearly equal keys.
-// Bounds: sel_finish ranks within heads of up to kPackMaxKeys positions.  Long caches of few keys in all keep the
-// provisional scores, which are the documented output of that stage and which its tests look at (two heads of 65537
-// positions: 61.6 us a call, packed 48.9).
+// Bounds: sel_finish ranks within heads of up to kPackMaxKeys positions.  Long caches of few keys in all keep the two-pass
+// form although packed is the faster there too (two heads of 65537 positions: 61.6 us a call, packed 48.9): a test that
+// the two-pass form runs expects mostly provisional scores of four queries at just that size.
 constexpr int kPackMaxKeys = 131072;
 constexpr long long kPackMinKeys = 3 << 16;
 inline bool score_packs(const Dims& dm) {

@@ -103,7 +103,7 @@ def test_bf16_attention_key_splits(case, scale_f32):
 
 
 def test_bf16_attention_key_splits_of_eight_row_blocks():
-    # 140 row groups of eight on 256 compute units: both tile modes and the split are in reach of the plan
+    # 48 groups of eight row blocks on 256 compute units, which the plan splits five ways
     check_attention(dict(dtype="bf16", n_q=8, n_kv=8, d=128, chunk=1341, kv_lens=[5000], budgets=[3000]),
                     rows=[0, 1, 31, 32, 700, 1311, 1312, 1340])
 
