@@ -386,11 +386,22 @@ __global__ __launch_bounds__(kDcThreads) void attn_decode_merge(Dims dm, AttnArg
 // ---------------------------------------------------------------------------------------------
 bool attn_decode_applies(const Dims& dm) { return dm.C * dm.g <= 32; }
 
-// Blocks per KV head: two for every compute unit in all and one more for every sequence (see decode_share).
+// Blocks per KV head: in all two for every compute unit, which are resident together.  (One more for every sequence puts the
+// last of them into a second round: 3 sequences of 10000 - 20000 tokens, 8 KV heads, dense 43.0 us a call, 35.9 so; 8 of
+// mixed length 33.1 / 29.6.  Only where a sequence has fewer than four blocks of a head to itself is that the smaller loss:
+// every sequence has one, and the others go by length.)
 static int decode_slots(const Dims& dm) {
   const long long n = (512 + dm.n_kv - 1) / dm.n_kv, most = (long long)kMaxSplits * dm.b;
-  const long long want = dm.b > 64 ? (n + dm.b - 1) / dm.b * dm.b : n + dm.b;
+  const long long want = dm.b > 64 ? (n + dm.b - 1) / dm.b * dm.b : (4 * dm.b <= n ? n : n + dm.b);
   return (int)(want < most ? want : most);
+}
+// One block a compute unit instead where the waves of two would have two tiles each or fewer: every block pays for its
+// start and for the merge of its rows (2 sequences of 5286 and 3653 tokens, 8 KV heads, d 128: 1 token 15.5 us a call, 14.7
+// so; 8 tokens 18.8 / 16.3.  About as fast at twice the keys, slower from there on).
+static int decode_launch_slots(const Dims& dm, bool sparse) {
+  const int n = decode_slots(dm), half = (n + 1) / 2;
+  const long long tiles = ((long long)attended_cap(dm, sparse) + dm.C + kDcTile - 1) / kDcTile * dm.b;   // of a KV head
+  return 4 * dm.b <= half && tiles <= 2 * kDcWaves * (long long)n ? half : n;
 }
 
 size_t attn_decode_ws_floats(const Dims& dm) {
@@ -404,7 +415,7 @@ static hipError_t launch_decode_d(const Dims& dm, const AttnArgs& a, float* part
   static std::atomic<uint64_t> lds_done{0};
   const hipError_t e = ensure_dynamic_lds(reinterpret_cast<const void*>(&attn_decode_bf16<D>), Cfg::kLdsBytes, lds_done);
   if (e != hipSuccess) return e;
-  const int n_slots = decode_slots(dm);
+  const int n_slots = decode_launch_slots(dm, a.k_idx != nullptr);
   // blocks that a short list leaves without work are not launched where the host can tell
   const long long tiles = ((long long)attended_cap(dm, a.k_idx != nullptr) + dm.C + kDcTile - 1) / kDcTile;
   const long long most = dm.b > 64 ? n_slots : dm.b * ((tiles + kDcWaves - 1) / kDcWaves);

@@ -128,6 +128,8 @@ DECODE_CASES = [
     dict(n_q=8, n_kv=2, d=128, chunk=1, kv_lens=[4100], budgets=[127]),
     dict(n_q=16, n_kv=1, d=64, chunk=2, kv_lens=[20000], budgets=[20000]),
     dict(n_q=8, n_kv=4, d=128, chunk=3, kv_lens=[9000, 1, 700, 0, 3333], budgets=[1000, 1, 96, 5, 333], batch=5),
+    dict(n_q=8, n_kv=8, d=64, chunk=3, kv_lens=[9000, 100, 6000], budgets=[9000, 50, 700], batch=3),   # two blocks a unit
+    dict(n_q=16, n_kv=8, d=64, chunk=2, kv_lens=[300 + 11 * i for i in range(20)], budgets=[90] * 20, batch=20),
     dict(n_q=2, n_kv=1, d=64, chunk=1, kv_lens=[(97 * i) % 1511 for i in range(66)],
          budgets=[(97 * i) % 1511 // 4 + 1 for i in range(66)], batch=66),
 ]
