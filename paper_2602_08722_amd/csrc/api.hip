@@ -452,7 +452,11 @@ quoka_status quoka_prefill_attn(const quoka_shape* shape, int sparse, const void
   const size_t es = shape->dtype == QUOKA_BF16 ? 2 : 4;
   const int n_chunks = (L + C - 1) / C;
 
-  // Groups of chunks per sequence, as long as that takes fewer launches than chunk after chunk of the whole batch.
+  // Groups of chunks per sequence, where that takes at most three quarters (dense: three fifths) of the calls of chunk after
+  // chunk of the whole batch: beyond, the batch fills a launch as well, with chunks of one length.  (Grouped against chunk
+  // after chunk, 8 sequences of 5000 in chunks of 500, 32/8 heads, d 64, sparse 707 / 621 us; 8 of 3214 in chunks of 333,
+  // 8/8 heads, dense 458 / 357.  220 measured batches: 0.6 of the time and less up to a third of the calls, 0.8 up to three
+  // fifths, 0.85 up to three quarters, 0.99 above.)
   // 32/8 heads, d 128, 16000 tokens in chunks of 1024: 106 launches, 1197 us -> 8 launches, 573 us: the short launches
   // of the selection run once, and the attention blocks of all chunks fill the chip together.  (Batches: 2 sequences of
   // 16000 1777 -> 1099 us, 8 of them 5125 -> 4389, 8 of 20000 in chunks of 500, 8/2 heads 3844 -> 2104.)  A short last chunk goes
@@ -471,7 +475,7 @@ quoka_status quoka_prefill_attn(const quoka_shape* shape, int sparse, const void
   const int n_groups = n_grouped > 0 ? (n_grouped + most - 1) / most : 0;
   int done = 0;   // chunks enqueued
   if (workspace != nullptr && reinterpret_cast<uintptr_t>(workspace) % kAlign == 0 && most > 1 &&
-      (long long)n_groups * shape->batch < n_grouped) {
+      (sparse ? 4LL : 5LL) * n_groups * shape->batch <= 3LL * n_grouped) {
     const int per_group = (n_grouped + n_groups - 1) / n_groups;
     char* ws = static_cast<char*>(workspace);
     for (int s = 0; s < shape->batch; ++s) {
