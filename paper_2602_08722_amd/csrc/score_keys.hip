@@ -9,7 +9,7 @@
 // accumulation rounds.  Queries are the M side of v_mfma_f32_32x32x16_bf16, keys the N side: a lane
 // owns one key column and 16 query rows, so the max over queries is in-register plus one
 // half-wave exchange.
-// float32 keys: float32 MFMA, operands straight from global memory.
+// float32 keys: float32 MFMA, operands straight from global memory; few queries: plain FMAs, one key per thread.
 #include <type_traits>
 
 #include "common.hip.h"
@@ -238,9 +238,72 @@ __global__ __launch_bounds__(kScThreads) void score_f32(Dims dm, const float* __
   }
 }
 
+// The same for few queries, of which a matrix instruction would hold 32 whatever their number: one key per thread, its row in
+// registers, Qbar from LDS.  Bound by the fetch of the rows, and by D FMAs a query where the keys are few.  Measured,
+// matrix instructions -> this kernel: 8 x 8 heads of 4000 keys, d 128, 2 queries 39.2 -> 22.3 us, 16 queries 40.9 -> 33.4;
+// 8 of 100000, d 64, 4 queries 58.6 -> 33.3; 2 of 4096, d 64, 2 queries 4.7 -> 4.2.
+constexpr int kFewQueries = 26;
+template <int D>
+__global__ __launch_bounds__(kScThreads) void score_f32_few(Dims dm, const float* __restrict__ qbar,
+                                                           const float* __restrict__ kc,
+                                                           const int32_t* __restrict__ kv_lens,
+                                                           float* __restrict__ scores, int n_keep,
+                                                           uint32_t* __restrict__ zero, uint32_t zero_words) {
+  __shared__ float qs[kFewQueries * D];
+  clear_words(zero, zero_words);
+  const int kv = blockIdx.y, b = blockIdx.z;
+  const int T = min(kv_lens[b * dm.ls], dm.T_cap);
+  if ((int)(blockIdx.x * kScThreads) >= T) return;   // block-uniform
+  const float* qhead = qbar + (size_t)(b * dm.n_kv + kv) * n_keep * D;
+  const bool round_q = (dm.flags & QUOKA_SCORE_QBAR_BF16) != 0;   // reduced-precision scorer: Qbar as bf16 values
+  for (int i = threadIdx.x; i < n_keep * D; i += kScThreads)
+    qs[i] = round_q ? bf16_bits_to_f32(f32_to_bf16_bits(qhead[i])) : qhead[i];
+  __syncthreads();
+  const int t = blockIdx.x * kScThreads + threadIdx.x;
+  if (t >= T) return;
+  const float* krow = kc + b * dm.kvs[0] + kv * dm.kvs[1] + (size_t)t * dm.kvs[2];
+  float k[D];
+  float ss = 0.f;
+#pragma unroll
+  for (int i = 0; i < D; i += 4) {
+    const float4 x = *reinterpret_cast<const float4*>(krow + i);
+    k[i] = x.x; k[i + 1] = x.y; k[i + 2] = x.z; k[i + 3] = x.w;
+    ss += x.x * x.x; ss += x.y * x.y; ss += x.z * x.z; ss += x.w * x.w;
+  }
+  const bool dot_mode = (dm.flags & 1) != 0, mean_mode = (dm.flags & 2) != 0;   // ablation scorers
+  float m = mean_mode ? 0.f : -INFINITY;
+  for (int r = 0; r < n_keep; ++r) {
+    const float* qr = qs + r * D;
+    float dot = 0.f;
+#pragma unroll
+    for (int i = 0; i < D; ++i) dot += qr[i] * k[i];
+    m = mean_mode ? m + dot : fmaxf(m, dot);
+  }
+  if (mean_mode) m /= (float)n_keep;
+  scores[(size_t)(b * dm.n_kv + kv) * dm.T_max + t] = m / (dot_mode ? 1.0f : fmaxf(sqrtf(ss), kNormEps)) + 0.0f;
+}
+
+// Which of the two: the more keys, the more of the matrix instructions' time is not hidden, so the line rises with the keys
+// (both sides equal at 3 - 4 queries up to 16384 keys over all heads, 8 - 11 at 65536, from 262144 on 26 - 28 at d 64 and
+// 22 - 25 at d 128).  The last
+// bits of the scores depend on it: in a prompt it goes by the prompt's length and the batch of the whole call, like
+// score_packs.
+static bool score_f32_by_key(const Dims& dm, int n_keep) {
+  const long long keys = (long long)(dm.prompt_chunks ? dm.ls : dm.b) * dm.n_kv * dm.T_max;
+  const long long line = keys / 8192;
+  const int most = dm.d == 64 ? kFewQueries : 23;
+  return n_keep <= (line < 3 ? 3 : line < most ? line : most);
+}
+
 template <int D>
 static void launch_f32_d(const Dims& dm, const float* qbar, const float* kc, const int32_t* kv_lens, float* scores,
                          int n_keep, hipStream_t st, uint32_t* zero, uint32_t zero_words) {
+  if (score_f32_by_key(dm, n_keep)) {
+    const dim3 grid((dm.T_cap + kScThreads - 1) / kScThreads, dm.n_kv, dm.b);
+    hipLaunchKernelGGL((score_f32_few<D>), grid, dim3(kScThreads), 0, st, dm, qbar, kc, kv_lens, scores, n_keep, zero,
+                       zero_words);
+    return;
+  }
   const int qblocks = n_keep <= 32 ? 1 : (n_keep <= 64 ? 2 : 4);
   const int keys = 32 * (4 / qblocks);
   // one step per block up to four blocks a compute unit; longer caches keep the query operand over several steps

@@ -7,6 +7,7 @@ import torch
 import gen
 from oracle import quoka_oracle as O
 from tests import parity as P
+from tests.bf16_round import round_to_bf16
 from tests.test_gpu_stages import _buffers
 
 pytestmark = pytest.mark.gpu
@@ -84,6 +85,32 @@ def test_float32_scores_query_blocks_and_key_tails(n_retain, kv_len, d):
     got = gen.from_torch(buf.scores)[0]
     want = O.key_scores_preagg(qbar.astype(np.float64), w.K[0])
     assert not np.isnan(got).any() and P.max_abs(got, want) <= P.TOL_SCORE
+
+
+# few queries: plain FMAs up to a number of queries that rises with the keys (3 at first, 26 at most), either side of the line
+@pytest.mark.parametrize("score_flags", [0, 1, 2, 8])
+@pytest.mark.parametrize("n_q,n_retain,kv_lens,d", [(2, 3, [1, 255, 257], 64), (2, 4, [255], 128), (4, 26, [70001], 64),
+                                                    (4, 17, [70001, 0], 64), (4, 27, [70001], 64), (4, 23, [70001], 128), (2, 1, [513], 128)])
+def test_float32_scores_of_few_queries(n_q, n_retain, kv_lens, d, score_flags):
+    n_kv = 1 if n_q == 2 else 4
+    w = gen.make_custom(dtype="f32", n_q=n_q, n_kv=n_kv, d=d, chunk=140, kv_lens=kv_lens, budgets=[1] * len(kv_lens),
+                        n_retain=n_retain, batch=len(kv_lens), seed=24)
+    buf = _buffers(w, score_flags=score_flags)
+    qbar = np.stack([O.group_mean_queries(w.Q[b], O.select_queries(w.Q[b], n_retain), n_kv) for b in range(w.batch)]).astype(np.float32)
+    buf.qbar.copy_(torch.from_numpy(qbar))
+    buf.scores.fill_(float("nan"))
+    buf.score_keys()
+    torch.cuda.synchronize()
+    q = round_to_bf16(qbar) if score_flags & 8 else qbar
+    for b in range(w.batch):
+        got = gen.from_torch(buf.scores)[b][:, :w.kv_lens[b]]
+        K = w.K[b][:, :w.kv_lens[b]].astype(np.float64)
+        dots = np.einsum("hrd,htd->hrt", q[b].astype(np.float64), K)
+        want = dots.mean(axis=1) if score_flags & 2 else dots.max(axis=1)
+        if not score_flags & 1:
+            want = want / np.maximum(np.linalg.norm(K, axis=-1), 1e-8)
+        # (float32 sums of d products: about sqrt(d) 2^-24 of |q| |k|, and |k| is about sqrt(d))
+        assert not np.isnan(got).any() and (not got.size or P.max_abs(got, want) <= P.TOL_SCORE * (np.sqrt(d) * 1.5 if score_flags & 1 else 1))
 
 
 # bf16 prefill kernel with the key list split over blocks (few row blocks); the second sequence of a batch has fewer
