@@ -310,10 +310,10 @@ __device__ __forceinline__ Cut derive_cut(const uint32_t* __restrict__ hist, uin
   return c;
 }
 
-// A score's key image in the multi-block path: one zero, and a NaN as the infinity of its sign, as in the register path.
+// A score's key image in the multi-block path: one zero, and a NaN as the infinity of its sign, as in the register path
+// (NaN images lie beyond those of the infinities, and the sum keeps the sign).
 __device__ __forceinline__ uint32_t score_key(float s) {
-  const uint32_t inf = (__float_as_uint(s) & 0x80000000u) | 0x7F800000u;
-  return okey(s != s ? __uint_as_float(inf) : s + 0.0f);
+  return min(max(okey(s + 0.0f), 0x007FFFFFu), 0xFF800000u);
 }
 
 __global__ void topk_zero(uint32_t* __restrict__ p, size_t n) {
@@ -360,9 +360,13 @@ __global__ __launch_bounds__(kLgThreads) void topk_hist(Dims dm, const float* __
   const int sft = radix_shift(PASS);
   const uint32_t bm = radix_bins(PASS) - 1u;
   const int t1 = min(t0 + kLgTile, c.T);
-  for (int i = t0 + threadIdx.x; i < t1; i += kLgThreads) {
-    const uint32_t k = score_key(c.sc[i]);
-    if ((k & cut.mask) == cut.prefix) atomicAdd(&lh[(k >> sft) & bm], 1u);
+  float v[kLgTile / kLgThreads];   // all requested before the first is used
+#pragma unroll
+  for (int j = 0; j < kLgTile / kLgThreads; ++j) v[j] = c.sc[min(t0 + (int)threadIdx.x + kLgThreads * j, t1 - 1)];
+#pragma unroll
+  for (int j = 0; j < kLgTile / kLgThreads; ++j) {
+    const uint32_t k = score_key(v[j]);
+    if (t0 + (int)threadIdx.x + kLgThreads * j < t1 && (k & cut.mask) == cut.prefix) atomicAdd(&lh[(k >> sft) & bm], 1u);
   }
   __syncthreads();
   uint32_t* gh = c.hist + PASS * kBins;
