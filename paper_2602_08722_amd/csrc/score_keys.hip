@@ -24,7 +24,9 @@ namespace quoka {
 // PACK (QB = 1, EXACT): at most kPackRows queries, all three terms in one operand.
 // FUSE (PACK, every query retained): Qbar is not there yet.  Every block works its head's few rows out for itself, in
 // place of reading them (8 heads, 8192 keys, one query: a launch of 3.4 us saved, 1 us added here; call 26.1 -> 25.0 us).
-template <int D, int QB, bool EXACT, bool PACK, bool FUSE>
+// TERMS: the query operands lie ready in `terms`.  (A template parameter: as a run-time choice it cost the calls that
+// convert Qbar themselves 1.5 us, 2 x 8 heads of 8337 keys 12.0 -> 13.7.)
+template <int D, int QB, bool EXACT, bool PACK, bool FUSE, bool TERMS>
 __global__ __launch_bounds__(kScThreads, 2) void score_bf16(Dims dm, const float* __restrict__ qbar,
                                                            const uint16_t* __restrict__ kc,
                                                            const int32_t* __restrict__ kv_lens,
@@ -94,9 +96,8 @@ __global__ __launch_bounds__(kScThreads, 2) void score_bf16(Dims dm, const float
   typename std::conditional<PACK, PackedTerms<D>, QueryTerms<D, EXACT>>::type qt;   // this wave's 32 query rows
   if constexpr (PACK) {
     qt.load(qhead, n_keep, li, hf);
-  } else if (EXACT && terms != nullptr) {   // (kernel-uniform)
-    if constexpr (EXACT)
-      qt.load_terms(terms + (size_t)(b * dm.n_kv + kv) * TermsLayout<D>::head_elems(n_keep), n_keep, qb, li, hf);
+  } else if constexpr (TERMS) {
+    qt.load_terms(terms + (size_t)(b * dm.n_kv + kv) * TermsLayout<D>::head_elems(n_keep), n_keep, qb, li, hf);
   } else {
     qt.load(qhead, n_keep, qb, li, hf, mean_mode);
   }
@@ -324,14 +325,14 @@ static void launch_f32_d(const Dims& dm, const float* qbar, const float* kc, con
 }
 
 // ---------------------------------------------------------------------------------------------
-template <int D, int QB, bool EXACT, bool PACK = false, bool FUSE = false>
+template <int D, int QB, bool EXACT, bool PACK = false, bool FUSE = false, bool TERMS = false>
 static hipError_t launch_bf16(const Dims& dm, const float* qbar, const void* kc, const int32_t* kv_lens, float* scores,
                               int n_keep, hipStream_t st, uint32_t* zero, uint32_t zero_words, const FusedQbar& fq = {},
                               const uint16_t* terms = nullptr) {
   using Cfg = ScoreCfg<D, QB>;
   static std::atomic<uint64_t> lds_done{0};
   const hipError_t e =
-      ensure_dynamic_lds(reinterpret_cast<const void*>(&score_bf16<D, QB, EXACT, PACK, FUSE>), Cfg::kLdsBytes, lds_done);
+      ensure_dynamic_lds(reinterpret_cast<const void*>(&score_bf16<D, QB, EXACT, PACK, FUSE, TERMS>), Cfg::kLdsBytes, lds_done);
   if (e != hipSuccess) return e;
   const int nt = (dm.T_cap + kScTile - 1) / kScTile;
   const int heads = dm.b * dm.n_kv;
@@ -346,7 +347,7 @@ static hipError_t launch_bf16(const Dims& dm, const float* qbar, const void* kc,
   int tpw = (nt + wg_per_head - 1) / wg_per_head;
   tpw = tpw < 1 ? 1 : tpw;
   dim3 grid((nt + tpw - 1) / tpw, dm.n_kv, dm.b);
-  hipLaunchKernelGGL((score_bf16<D, QB, EXACT, PACK, FUSE>), grid, dim3(kScThreads), Cfg::kLdsBytes, st, dm, qbar,
+  hipLaunchKernelGGL((score_bf16<D, QB, EXACT, PACK, FUSE, TERMS>), grid, dim3(kScThreads), Cfg::kLdsBytes, st, dm, qbar,
                      static_cast<const uint16_t*>(kc), kv_lens, scores, n_keep, tpw, zero, zero_words, fq,
                      terms);
   return hipGetLastError();
@@ -365,9 +366,16 @@ static hipError_t launch_bf16_d(const Dims& dm, const float* qbar, const void* k
   if (fq.q != nullptr)
     return launch_bf16<D, 1, true, true, true>(dm, qbar, kc, kv_lens, scores, n_keep, st, zero, zero_words, fq);
   if (score_packs(dm)) return launch_bf16<D, 1, true, true>(dm, qbar, kc, kv_lens, scores, n_keep, st, zero, zero_words);
-  if (qblocks <= 1) return launch_bf16<D, 1, true>(dm, qbar, kc, kv_lens, scores, n_keep, st, zero, zero_words, {}, terms);
-  if (qblocks == 2) return launch_bf16<D, 2, true>(dm, qbar, kc, kv_lens, scores, n_keep, st, zero, zero_words, {}, terms);
-  return launch_bf16<D, 4, true>(dm, qbar, kc, kv_lens, scores, n_keep, st, zero, zero_words, {}, terms);
+  if (terms != nullptr) {
+    if (qblocks <= 1)
+      return launch_bf16<D, 1, true, false, false, true>(dm, qbar, kc, kv_lens, scores, n_keep, st, zero, zero_words, {}, terms);
+    if (qblocks == 2)
+      return launch_bf16<D, 2, true, false, false, true>(dm, qbar, kc, kv_lens, scores, n_keep, st, zero, zero_words, {}, terms);
+    return launch_bf16<D, 4, true, false, false, true>(dm, qbar, kc, kv_lens, scores, n_keep, st, zero, zero_words, {}, terms);
+  }
+  if (qblocks <= 1) return launch_bf16<D, 1, true>(dm, qbar, kc, kv_lens, scores, n_keep, st, zero, zero_words);
+  if (qblocks == 2) return launch_bf16<D, 2, true>(dm, qbar, kc, kv_lens, scores, n_keep, st, zero, zero_words);
+  return launch_bf16<D, 4, true>(dm, qbar, kc, kv_lens, scores, n_keep, st, zero, zero_words);
 }
 
 bool score_reads_terms(const Dims& dm, int dtype) {
