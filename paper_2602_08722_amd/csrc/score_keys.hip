@@ -284,16 +284,15 @@ __global__ __launch_bounds__(kScThreads) void score_f32_few(Dims dm, const float
   scores[(size_t)(b * dm.n_kv + kv) * dm.T_max + t] = m / (dot_mode ? 1.0f : fmaxf(sqrtf(ss), kNormEps)) + 0.0f;
 }
 
-// Which of the two: the more keys, the more of the matrix instructions' time is not hidden, so the line rises with the keys
-// (both sides equal at 3 - 4 queries up to 16384 keys over all heads, 8 - 11 at 65536, from 262144 on 26 - 28 at d 64 and
-// 22 - 25 at d 128).  The last
-// bits of the scores depend on it: in a prompt it goes by the prompt's length and the batch of the whole call, like
-// score_packs.
+// Which of the two: the more keys, the more of the matrix instructions' time is not hidden, so the line rises with the keys.
+// Both sides equal at 3 - 4 queries up to 32768 keys over all heads (one block of 128 for each compute unit); d 64: at 8 - 9 up
+// to 98304, 26 - 28 from 262144 on; d 128: at 10 - 12 up to 65536, 18 - 20 at 98304, 22 - 25 from 262144 on.  The last bits of
+// the scores depend on it: in a prompt it goes by the prompt's length and the batch of the whole call, like score_packs.
 static bool score_f32_by_key(const Dims& dm, int n_keep) {
   const long long keys = (long long)(dm.prompt_chunks ? dm.ls : dm.b) * dm.n_kv * dm.T_max;
-  const long long line = keys / 8192;
-  const int most = dm.d == 64 ? kFewQueries : 23;
-  return n_keep <= (line < 3 ? 3 : line < most ? line : most);
+  if (keys <= 32768) return n_keep <= 3;
+  if (dm.d == 64) return n_keep <= (keys <= 81920 ? 8 : keys < 10240 * kFewQueries ? keys / 10240 : kFewQueries);
+  return n_keep <= (keys <= 65536 ? 10 : keys < 10240 * 13 ? 10 + keys / 10240 : 23);
 }
 
 template <int D>
