@@ -61,7 +61,7 @@ struct DecodeWork {
   int b, split, n_splits;   // b < 0: nothing to do
 };
 __device__ __forceinline__ int decode_cache(const Dims& dm, const AttnArgs& a, int b, int kv) {
-  const int n = a.k_idx != nullptr ? min(a.n_cache[b * dm.n_kv + kv], dm.B_max) : min(a.n_cache[b * dm.ls], dm.T_cap);
+  const int n = a.k_idx != nullptr ? min(a.n_cache[b * dm.n_kv + kv], dm.B_max) : min(a.n_cache[b * dm.ls], dm.T_max);
   return max(n, 0);
 }
 __device__ __forceinline__ int decode_tiles(const Dims& dm, const AttnArgs& a, int b, int kv) {

@@ -76,7 +76,7 @@ __global__ __launch_bounds__(kFaThreads, 2) void attn_f32(Dims dm, AttnArgs a, f
   const int g = dm.g, n_rows = dm.C * g, row0 = rb * 32;
 
   const bool sparse = a.k_idx != nullptr;
-  int n_cache = sparse ? min(a.n_cache[b * dm.n_kv + kv], dm.B_max) : min(a.n_cache[b * dm.ls], dm.T_cap);
+  int n_cache = sparse ? min(a.n_cache[b * dm.n_kv + kv], dm.B_max) : min(a.n_cache[b * dm.ls], dm.T_max);
   n_cache = max(n_cache, 0);
   const int n_chunk = fa_row(min(row0 + 31, n_rows - 1), g).tok + 1;   // chunk keys any row of the block can see
   const int cache_units = (n_cache + 31) / 32, units = cache_units + (n_chunk + 31) / 32;

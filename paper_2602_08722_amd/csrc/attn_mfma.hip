@@ -137,7 +137,7 @@ __global__ __launch_bounds__(2 * kSetThreads, 2) void attn_bf16(Dims dm, AttnArg
   if (sparse) {
     n_cache = min(a.n_cache[b * dm.n_kv + kv], dm.B_max);
   } else {
-    n_cache = min(a.n_cache[b * dm.ls], dm.T_cap);
+    n_cache = min(a.n_cache[b * dm.ls], dm.T_max);
   }
   n_cache = max(n_cache, 0);
   // Tile order: the chunk's own tiles first, then the cache tiles.  The online softmax does not care, and the first

@@ -72,8 +72,8 @@ hipError_t launch_select_keys(const Dims& dm, const float* qbar, const void* k_c
 
 // --- attention (attn_mfma.hip for bf16, attn_f32.hip for float32) ---------------------------------
 // Cache rows attended: sparse (k_idx != nullptr): k_idx[b,kv,0..k_cnt[b,kv]); dense: 0..kv_lens[b].  The kernels cut
-// the list at B_max (in a prompt the top-B launch has cut it at T_cap) and the length at T_cap, for which the launch is
-// sized: a merge adds up only partials that some block has written.
+// the list at B_max (in a prompt the top-B launch has cut it at T_cap) and the length at T_max, which a dense launch has set
+// to the T_cap that it is sized for: a merge adds up only partials that some block has written.
 struct AttnArgs {
   const void *q, *k_cache, *v_cache, *k_chunk, *v_chunk;
   const int32_t* k_idx;    // nullptr for dense
