@@ -2,6 +2,7 @@
 """Turns rocprofv3 CSV output of bench.py runs into the short text summaries kept under profiles/.
 
     python3 profile_summary.py trace <workload> <rocprofv3 output dir> <bench.py stdout file>
+    python3 profile_summary.py cases <dir holding one rocprofv3 output dir per case, named like it>
     python3 profile_summary.py traffic <workload> <dir holding one rocprofv3 output dir per pass>
     python3 profile_summary.py counters <title> <kernel substring> <rocprofv3 output dir> [<dir> ...]
 
@@ -83,10 +84,42 @@ def trace(workload, out_dir, bench_log):
     print("\n".join(out))
 
 
-def _pmc(out_dir):
+def cases(base):
+    """Kernel traces of perf/cases.py's cases: every pass launches the same kernels, the first tenth is left out."""
+    out = ["# rocprofv3 kernel traces of the timed cases (perf/cases.py), one pass after another", "",
+           "Commands (run from /tmp with TMPDIR=/tmp, repository root = $R, one run per case):",
+           "    rocprofv3 --kernel-trace --stats --output-format csv -d <base>/<case> -o kt -- python3 -c \"import sys, torch; "
+           "sys.path.insert(0, '$R'); from perf import cases as c; s = c.prepare(next(x for x in c.listed() if x['name'] == "
+           "'<case>'), 1); [c.run(s) for _ in range(40)]; torch.cuda.synchronize()\"",
+           "    python3 $R/profile_summary.py cases <base>", "",
+           "Launches per pass, and durations in us (the gaps between the launches of a pass are not in them)."]
+    for d in sorted(x for x in os.listdir(base) if os.path.isdir(os.path.join(base, x))):
+        rows = [r for r in csv.DictReader(open(_find(os.path.join(base, d), "*kernel_trace.csv"))) if _is_ours(r["Kernel_Name"])]
+        rows.sort(key=lambda r: int(r["Start_Timestamp"]))
+        rows = rows[len(rows) // 10:]
+        dur = collections.defaultdict(list)
+        for r in rows:
+            dur[_short(r["Kernel_Name"])].append((int(r["End_Timestamp"]) - int(r["Start_Timestamp"])) / 1e3)
+        per_pass = min(len(v) for v in dur.values())
+        total = sum(sum(v) for v in dur.values()) / per_pass
+        out += ["", f"## {d}: {total:.1f} us in kernels per pass", "",
+                f"{'kernel':54s} {'a pass':>6s} {'avg_us':>9s} {'min_us':>9s} {'max_us':>9s}"]
+        for n, v in sorted(dur.items(), key=lambda kv: -sum(kv[1])):
+            out.append(f"{n[:54]:54s} {round(len(v) / per_pass):6d} {sum(v) / len(v):9.2f} {min(v):9.2f} {max(v):9.2f}")
+    print("\n".join(out))
+
+
+def _pmc(out_dir, last_step=False):
+    """Counter values per kernel and counter, in dispatch order; `last_step`: only of the kernels that are among this
+    library's last dispatches (a pass sets its buffers up with whole calls, which may launch other variants)."""
+    rows = list(csv.DictReader(open(_find(out_dir, "*counter_collection.csv"))))
+    rows.sort(key=lambda r: int(r["Dispatch_Id"]))
+    ours = sorted({int(r["Dispatch_Id"]) for r in rows if _is_ours(r["Kernel_Name"])})[-6:]   # (a stage has up to six launches)
+    late = {r["Kernel_Name"] for r in rows if int(r["Dispatch_Id"]) in ours}
     agg = collections.defaultdict(lambda: collections.defaultdict(list))
-    for r in csv.DictReader(open(_find(out_dir, "*counter_collection.csv"))):
-        agg[r["Kernel_Name"]][r["Counter_Name"]].append(float(r["Counter_Value"]))
+    for r in rows:
+        if not last_step or r["Kernel_Name"] in late:
+            agg[r["Kernel_Name"]][r["Counter_Name"]].append(float(r["Counter_Value"]))
     return agg
 
 
@@ -128,7 +161,7 @@ def traffic(workload, base):
         fd, wd = os.path.join(base, f"{stage}_FETCH_SIZE"), os.path.join(base, f"{stage}_WRITE_SIZE")
         if not (os.path.isdir(fd) and os.path.isdir(wd)):
             continue
-        fa, wa = _pmc(fd), _pmc(wd)
+        fa, wa = _pmc(fd, last_step=True), _pmc(wd, last_step=True)
         rd_tot = wr_tot = 0.0
         for k in fa:
             if not (_is_ours(k) and any(p in k for p in pats)) or k not in wa:
@@ -190,6 +223,8 @@ def main():
     mode = sys.argv[1]
     if mode == "trace" and len(sys.argv) == 5:
         trace(sys.argv[2], sys.argv[3], sys.argv[4])
+    elif mode == "cases" and len(sys.argv) == 3:
+        cases(sys.argv[2])
     elif mode == "traffic" and len(sys.argv) == 4:
         traffic(sys.argv[2], sys.argv[3])
     elif mode == "counters" and len(sys.argv) >= 5:
