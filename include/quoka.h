@@ -124,8 +124,8 @@ quoka_status quoka_score_keys(const quoka_shape* shape, const float* qbar, const
 /* Key selection (Alg. 1: I = topk(S-hat, B_SA); Eq. 3).
  *   scores   in   [b, n_KV, T_max] float32
  *   kv_lens  in   [b] int32;  budgets in [b] int32 (B_SA per sequence, >= 0)
- *   k_idx    out  [b, n_KV, B_max] int32: the k_cnt best positions, ASCENDING; equal scores go to the
- *                 lower position; entries past k_cnt unspecified
+ *   k_idx    out  [b, n_KV, B_max] int32: the k_cnt best positions, ASCENDING; equal scores (a zero's sign
+ *                 does not count) go to the lower position; entries past k_cnt unspecified
  *   k_cnt    out  [b, n_KV] int32 = min(budgets[b], kv_lens[b], B_max)                             */
 quoka_status quoka_topk_keys(const quoka_shape* shape, const float* scores, const int32_t* kv_lens,
                              const int32_t* budgets, int32_t* k_idx, int32_t* k_cnt, void* workspace,
@@ -197,7 +197,8 @@ quoka_status quoka_chunk_attn(const quoka_shape* shape, const void* q, const voi
  *             chunk's intermediates on return (unused when sparse == 0, may then be NULL)
  * The last chunk may be shorter than chunk_len.  Everything is enqueued on `stream`.  A workspace of
  * quoka_workspace_bytes is enough to run chunk after chunk; with more, up to quoka_prefill_workspace_bytes, several
- * chunks share each launch (as many as fit; bounded at 256 MiB unless one chunk needs more).                   */
+ * chunks of a sequence share each launch where that pays (as many as fit; bounded at 256 MiB unless one chunk needs
+ * more); retained queries, scores and key lists do not depend on how many do.                                     */
 quoka_status quoka_prefill_workspace_bytes(const quoka_shape* shape, size_t* out_bytes);
 quoka_status quoka_prefill_attn(const quoka_shape* shape, int sparse, const void* q, const void* k, const void* v,
                                 const int32_t* kv_lens_all, const int32_t* budgets_all, int32_t* q_idx, float* qbar,
