@@ -14,6 +14,8 @@
 // Measured (8/2 heads, d 128, 512 tokens over 491 + 512 keys): 423 us for one wave per row with plain FMAs, 30 + 4 us here;
 // (2/1 heads, d 64, 128 tokens over 128 + 128 keys): 47 us and 10 us.
 //
+// Short lists of a few tokens keep one wave per row (attn_f32_short).
+//
 // Operand plan (a lane is (li = lane % 32, hf = lane / 32)); the contraction index may be permuted freely:
 //   S^T[key, row]: A = K row of key li, B = Q row li from LDS; step (i, e) contracts dims 8i + e (hf 0) and 8i + 4 + e.
 //     Register v of the result holds key 8*(v/4) + 4*hf + v%4 of the unit for query row li.
@@ -283,6 +285,97 @@ __global__ __launch_bounds__(256) void attn_f32_merge(Dims dm, AttnArgs a, const
 }
 
 // ---------------------------------------------------------------------------------------------
+// Short lists of a few tokens: one wave per query row, lanes take 64 keys at a time for the logits and own head_dim / 64
+// output dims each for the values; no unit of 32 rows and 32 keys is formed, which takes a wave of attn_f32 5 us at d 128
+// whatever there is in it.  Bound by a chain of three fetches and one step a key.  Measured (attn_f32 -> this kernel): 32/8
+// heads, d 128, 1 token over 8 keys 8.8 -> 4.8 us, 8 tokens over 16 keys 9.4 -> 7.5; d 64, 1 token over 16 keys 6.3 -> 5.3.
+constexpr int kFsThreads = 256;
+
+template <int D>
+__global__ __launch_bounds__(kFsThreads) void attn_f32_short(Dims dm, AttnArgs a) {
+  constexpr int EPL = D / 64;
+  __shared__ float qs[kFsThreads / 64][D];
+  const int lane = threadIdx.x & 63, w = threadIdx.x >> 6;
+  const int i = blockIdx.x * (kFsThreads / 64) + w;   // chunk position of this wave's row
+  const int h = blockIdx.y, b = blockIdx.z;
+  const bool row_on = i < dm.C;
+  if (row_on) {
+    const float* qsrc = static_cast<const float*>(a.q) + b * dm.qs[0] + h * dm.qs[1] + (size_t)i * dm.qs[2];
+#pragma unroll
+    for (int e = 0; e < EPL; ++e) qs[w][lane + 64 * e] = qsrc[lane + 64 * e];
+  }
+  __syncthreads();
+  if (!row_on) return;   // wave-uniform; no barrier follows
+  const int kv = h / dm.g;
+  const bool sparse = a.k_idx != nullptr;
+  int n_cache = sparse ? min(a.n_cache[b * dm.n_kv + kv], dm.B_max) : min(a.n_cache[b * dm.ls], dm.T_max);
+  n_cache = max(n_cache, 0);
+  const int32_t* kidx = sparse ? a.k_idx + (size_t)(b * dm.n_kv + kv) * dm.B_max : nullptr;
+  const float* kcache = static_cast<const float*>(a.k_cache) + b * dm.kvs[0] + kv * dm.kvs[1];
+  const float* vcache = static_cast<const float*>(a.v_cache) + b * dm.kvs[0] + kv * dm.kvs[1];
+  const float* kchunk = static_cast<const float*>(a.k_chunk) + b * dm.cks[0] + kv * dm.cks[1];
+  const float* vchunk = static_cast<const float*>(a.v_chunk) + b * dm.cks[0] + kv * dm.cks[1];
+  const float scale = 1.0f / sqrtf((float)D);
+  const int total = n_cache + i + 1;
+  float m_run = -INFINITY, l_run = 0.f;
+  float acc[EPL];
+#pragma unroll
+  for (int e = 0; e < EPL; ++e) acc[e] = 0.f;
+
+  for (int j0 = 0; j0 < total; j0 += 64) {
+    const int j = j0 + lane;
+    const bool valid = j < total;
+    const int jj = valid ? j : total - 1;
+    int is_chunk, row;
+    if (jj < n_cache) {
+      is_chunk = 0;
+      row = sparse ? (int)min((uint32_t)kidx[jj], (uint32_t)(dm.T_max - 1)) : jj;   // a malformed list cannot leave the cache
+    } else {
+      is_chunk = 1;
+      row = jj - n_cache;
+    }
+    const float* kp = is_chunk ? kchunk + (size_t)row * dm.cks[2] : kcache + (size_t)row * dm.kvs[2];
+    float dot = 0.f;
+#pragma unroll 8
+    for (int d0 = 0; d0 < D; d0 += 4) {
+      const float4 kx = *reinterpret_cast<const float4*>(kp + d0);
+      dot += qs[w][d0] * kx.x;
+      dot += qs[w][d0 + 1] * kx.y;
+      dot += qs[w][d0 + 2] * kx.z;
+      dot += qs[w][d0 + 3] * kx.w;
+    }
+    const float s = valid ? dot * scale : -INFINITY;
+    const float m_new = fmaxf(m_run, wave64_max(s));   // finite: key j0 is always visible
+    const float alpha = expf(m_run - m_new);
+    const float p = valid ? expf(s - m_new) : 0.f;
+    l_run = l_run * alpha + wave64_sum(p);
+    m_run = m_new;
+#pragma unroll
+    for (int e = 0; e < EPL; ++e) acc[e] *= alpha;
+    const int cnt = min(64, total - j0);
+    for (int t = 0; t < cnt; ++t) {
+      // t is wave-uniform: lane reads through the scalar path instead of LDS shuffles
+      const float pt = __int_as_float(__builtin_amdgcn_readlane(__float_as_int(p), t));
+      const int ct = __builtin_amdgcn_readlane(is_chunk, t);
+      const int rt = __builtin_amdgcn_readlane(row, t);
+      const float* vp = ct ? vchunk + (size_t)rt * dm.cks[2] : vcache + (size_t)rt * dm.kvs[2];
+#pragma unroll
+      for (int e = 0; e < EPL; ++e) acc[e] += pt * vp[lane + 64 * e];
+    }
+  }
+  float* orow = static_cast<float*>(a.out) + b * dm.os[0] + h * dm.os[1] + (size_t)i * dm.os[2];
+#pragma unroll
+  for (int e = 0; e < EPL; ++e) orow[lane + 64 * e] = acc[e] / l_run;
+  if (a.lse != nullptr && lane == 0) a.lse[(size_t)(b * dm.n_q + h) * dm.C + i] = m_run + logf(l_run);
+}
+
+// Both sides equal at 24 (C = 1) to 16 (C = 8) cached keys at d 64, 46 to 26 at d 128 and about 10 at C = 16 (32/8 heads, no
+// cached key: 9.4 -> 6.3); longer chunks have the rows for attn_f32.
+static bool attn_f32_is_short(const Dims& dm, bool sparse) {
+  return dm.C <= 16 && attended_cap(dm, sparse) + 2 * dm.C <= (dm.d == 64 ? 26 : 42);
+}
+
+// ---------------------------------------------------------------------------------------------
 // Splits of the key list: as many as give every compute unit a block, but at least one unit of 32 keys for every wave
 // of a block (a split costs 16 KiB of partials and a share of the merge launch).
 static long long f32_blocks(const Dims& dm) { return (long long)dm.b * dm.n_kv * ((dm.C * dm.g + 31) / 32); }
@@ -306,6 +399,11 @@ size_t attn_f32_ws_floats(const Dims& dm) {
 
 template <int D>
 static hipError_t launch_f32_d(const Dims& dm, const AttnArgs& a, float* part, hipStream_t st) {
+  if (attn_f32_is_short(dm, a.k_idx != nullptr)) {
+    const dim3 grid((dm.C + kFsThreads / 64 - 1) / (kFsThreads / 64), dm.n_q, dm.b);
+    hipLaunchKernelGGL((attn_f32_short<D>), grid, dim3(kFsThreads), 0, st, dm, a);
+    return hipGetLastError();
+  }
   static std::atomic<uint64_t> lds_done{0};
   const hipError_t e = ensure_dynamic_lds(reinterpret_cast<const void*>(&attn_f32<D>), FaCfg<D>::kLdsBytes, lds_done);
   if (e != hipSuccess) return e;

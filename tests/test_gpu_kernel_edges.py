@@ -64,6 +64,11 @@ F32_ATTN_CASES = [
     dict(n_q=4, n_kv=1, d=64, chunk=1, kv_lens=[9000], budgets=[513]),       # decode-sized, most splits
     dict(n_q=5, n_kv=1, d=128, chunk=70, kv_lens=[300, 0, 7], budgets=[64, 3, 7], batch=3),
     dict(n_q=16, n_kv=8, d=64, chunk=600, kv_lens=[40], budgets=[5]),        # more row blocks than compute units: no split
+    dict(n_q=8, n_kv=2, d=128, chunk=8, kv_lens=[26, 0, 3], budgets=[26, 1, 9], batch=3),   # short lists: one wave per row, up to
+    dict(n_q=3, n_kv=3, d=64, chunk=1, kv_lens=[24], budgets=[24]),                          # the line, and one key beyond it
+    dict(n_q=3, n_kv=3, d=64, chunk=1, kv_lens=[25], budgets=[25]),
+    dict(n_q=4, n_kv=1, d=128, chunk=5, kv_lens=[33], budgets=[32]),
+    dict(n_q=4, n_kv=2, d=128, chunk=16, kv_lens=[10], budgets=[3]),
 ]
 
 
