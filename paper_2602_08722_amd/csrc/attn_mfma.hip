@@ -575,14 +575,12 @@ struct AttnPlan {
 // to 172 measured pairs (groups 130 - 250, chunks 1056 - 4096, 0 - 4096 keys; rms 1.5 %), less 0.5 - 1 us.  Attention, eight
 // against four, d 128: 32/8 heads, 1312 tokens over 983 keys 62 / 72 us, over 3932 134 / 164; 12/4 heads, 3000 tokens over
 // 983 92 / 96, over none 66.9 / 65.4; d 64: 12/4 heads, 2752 tokens over none 43 / 37, over 2048 78.4 / 76.8.
-// Above 256 groups the rounds decide: 32/8 heads, d 128, 2400 tokens over 983 keys, 304 groups 140 / 123 us; 3072 tokens, 384
-// groups 164 / 155; 4096 tokens, 512 groups 200 / 232.
+// Above 256 groups blocks of four take three rounds where those of eight take two, 32/8 heads, d 128, 2400 tokens over 983
+// keys, 304 groups 140 / 123 us; 3072 tokens, 384 groups 164 / 155.  From two full rounds on the longest ranges come first
+// and even the rounds out, whatever the rest: 4096 tokens, 512 groups 200 / 232; 6200, 776 groups 412 / 473.
 static bool eight_row_blocks(const Dims& dm, bool sparse, long long groups) {
   if (dm.b > 1 || groups == kComputeUnits) return groups >= kComputeUnits;
-  if (groups > kComputeUnits) {   // two rounds of four blocks a unit and more: a step of four row blocks takes as long
-    const long long rounds8 = (groups + kComputeUnits - 1) / kComputeUnits;
-    return 2 * rounds8 <= (2 * groups + kComputeUnits - 1) / kComputeUnits;
-  }
+  if (groups > kComputeUnits) return 2 * groups > 3 * kComputeUnits;
   if (groups <= kComputeUnits / 2) return false;
   const float c = (float)attended_cap(dm, sparse) / kSub, r = (float)dm.C / kSub, n = (float)groups;
   return dm.d == 128 ? 6.2f + 0.36f * c + r * (0.147f - 47.4f / n) > 0.f : 4.8f + 0.114f * c + r * (0.093f - 41.1f / n) > 0.f;
