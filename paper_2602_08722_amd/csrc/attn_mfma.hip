@@ -475,36 +475,93 @@ __global__ __launch_bounds__(2 * kSetThreads, 2) void attn_bf16(Dims dm, AttnArg
 #undef QUOKA_RESOLVE
 #undef QUOKA_ISSUE
 
-// Sum of the key splits' partials of one row block per block of four waves; wave w takes dim block w (d = 64: waves 0
-// and 1).  The lane layout is the kernel's own, so the loads are whole kilobytes; the splits are added in order.
+// Sum of the key splits' partials: a block takes one dim block of a row block, each of its waves up to kMergeRun
+// neighbouring splits at a time, all of whose records are requested before the first is used, and the waves' sums meet in
+// LDS.  The lane layout is the attention kernel's own, so the loads are whole kilobytes.  Everything is added in a fixed order.
+// What bounds it is the chain of fetches, not the bytes: with one wave walking a dim block's splits two at a time the launch took
+// 0.4 us a split (8 heads, d 64, 103 tokens, 32 splits 15.4 us, now 5.4; 2 heads of 7, d 128, 5 tokens 13.2, now 4.4; 4 heads
+// of 3, d 128, 147 tokens 9.3, now 5.3).
+constexpr int kMergeWaves = 8, kMergeRun = 4;
 template <int D>
-__global__ __launch_bounds__(64 * (D / 32)) void attn_bf16_merge(Dims dm, AttnArgs a) {
+__global__ __launch_bounds__(64 * kMergeWaves) void attn_bf16_merge(Dims dm, AttnArgs a) {
   constexpr int REC = AttnCfg<D, true>::kRecFloats;
-  const int lane = threadIdx.x & 63, c = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6);
+  __shared__ float2 ml[kMergeWaves][32];
+  __shared__ float4 sum[kMergeWaves - 1][4][64];
+  const int lane = threadIdx.x & 63, w = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6);
+  const int nw = blockDim.x >> 6;
   const int li = lane & 31, hf = lane >> 5;
-  const int x = blockIdx.x, kv = blockIdx.y % dm.n_kv, b = blockIdx.y / dm.n_kv;
+  const int x = blockIdx.x, kv = blockIdx.y % dm.n_kv, b = blockIdx.y / dm.n_kv, c = blockIdx.z;
   const int C = dm.chunk(b);
-  if (x >= dm.g * ((C + 31) / 32)) return;
+  if (x >= dm.g * ((C + 31) / 32)) return;   // block-uniform
   const float* rec = a.part + ((size_t)blockIdx.y * gridDim.x + x) * a.n_splits * REC;
-  float m = -INFINITY;
-  for (int s = 0; s < a.n_splits; ++s) m = fmaxf(m, rec[(size_t)s * REC + 32 * D + li]);
-  const float m_fin = m == -INFINITY ? 0.f : m;   // (rows past the chunk's end)
-  float l = 0.f;
+  const int s0 = a.n_splits * w / nw, s1 = a.n_splits * (w + 1) / nw;
+  float m = -INFINITY, l = 0.f;
   float o[16];
 #pragma unroll
   for (int v = 0; v < 16; ++v) o[v] = 0.f;
-#pragma unroll 2
-  for (int s = 0; s < a.n_splits; ++s) {
-    const float* p = rec + (size_t)s * REC;
-    const float wgt = __builtin_amdgcn_exp2f(p[32 * D + li] - m_fin);
-    l += wgt * p[32 * D + 32 + li];
+  for (int s = s0; s < s1; s += kMergeRun) {
+    float ms[kMergeRun], ls[kMergeRun];
+    float4 t[kMergeRun][4];
 #pragma unroll
-    for (int v4 = 0; v4 < 4; ++v4) {
-      const float4 t = *reinterpret_cast<const float4*>(p + ((c * 4 + v4) * 64 + lane) * 4);
-      o[4 * v4] += wgt * t.x;
-      o[4 * v4 + 1] += wgt * t.y;
-      o[4 * v4 + 2] += wgt * t.z;
-      o[4 * v4 + 3] += wgt * t.w;
+    for (int i = 0; i < kMergeRun; ++i) {   // (the last record of the run again where there are fewer)
+      const float* p = rec + (size_t)min(s + i, s1 - 1) * REC;
+      ms[i] = p[32 * D + li];
+      ls[i] = p[32 * D + 32 + li];
+#pragma unroll
+      for (int v4 = 0; v4 < 4; ++v4) t[i][v4] = *reinterpret_cast<const float4*>(p + ((c * 4 + v4) * 64 + lane) * 4);
+    }
+    __builtin_amdgcn_sched_barrier(0);   // all of them in flight
+    float m_new = m;
+#pragma unroll
+    for (int i = 0; i < kMergeRun; ++i) m_new = fmaxf(m_new, ms[i]);
+    const float m_fin = m_new == -INFINITY ? 0.f : m_new;   // (a row that no split so far has seen a key for)
+    const float alpha = __builtin_amdgcn_exp2f(m - m_fin);
+    m = m_new;
+    l *= alpha;
+#pragma unroll
+    for (int v = 0; v < 16; ++v) o[v] *= alpha;
+#pragma unroll
+    for (int i = 0; i < kMergeRun; ++i) {
+      const bool in = s + i < s1;   // (a repeated record adds plain zeros, whatever it holds)
+      const float wgt = __builtin_amdgcn_exp2f(ms[i] - m_fin);
+      l += in ? wgt * ls[i] : 0.f;
+#pragma unroll
+      for (int v4 = 0; v4 < 4; ++v4) {
+        o[4 * v4] += in ? wgt * t[i][v4].x : 0.f;
+        o[4 * v4 + 1] += in ? wgt * t[i][v4].y : 0.f;
+        o[4 * v4 + 2] += in ? wgt * t[i][v4].z : 0.f;
+        o[4 * v4 + 3] += in ? wgt * t[i][v4].w : 0.f;
+      }
+    }
+  }
+  if (nw > 1) {
+    if (hf == 0) ml[w][li] = make_float2(m, l);
+    if (w > 0) {
+#pragma unroll
+      for (int v4 = 0; v4 < 4; ++v4)
+        sum[w - 1][v4][lane] = make_float4(o[4 * v4], o[4 * v4 + 1], o[4 * v4 + 2], o[4 * v4 + 3]);
+    }
+    __syncthreads();
+    if (w > 0) return;
+    float m_all = m;
+    for (int i = 1; i < nw; ++i) m_all = fmaxf(m_all, ml[i][li].x);
+    const float m_fin = m_all == -INFINITY ? 0.f : m_all;
+    const float alpha = __builtin_amdgcn_exp2f(m - m_fin);
+    m = m_all;
+    l *= alpha;
+#pragma unroll
+    for (int v = 0; v < 16; ++v) o[v] *= alpha;
+    for (int i = 1; i < nw; ++i) {
+      const float wgt = __builtin_amdgcn_exp2f(ml[i][li].x - m_fin);
+      l += wgt * ml[i][li].y;
+#pragma unroll
+      for (int v4 = 0; v4 < 4; ++v4) {
+        const float4 t = sum[i - 1][v4][lane];
+        o[4 * v4] += wgt * t.x;
+        o[4 * v4 + 1] += wgt * t.y;
+        o[4 * v4 + 2] += wgt * t.z;
+        o[4 * v4 + 3] += wgt * t.w;
+      }
     }
   }
   const int tok = (x / dm.g) * 32 + li, h = kv * dm.g + x % dm.g;
@@ -539,7 +596,11 @@ static hipError_t launch_variant(const Dims& dm, const AttnArgs& a, hipStream_t 
   // round needs the pairing, or its last block sets the time alone)
   aa.adjacent = (long long)grid.x * grid.y * grid.z >= 2 * kComputeUnits ? 1 : 0;
   hipLaunchKernelGGL((attn_bf16<D, SPLIT, XS, KSPLIT>), grid, dim3(2 * kSetThreads), lds, st, dm, aa);
-  if (KSPLIT) hipLaunchKernelGGL((attn_bf16_merge<D>), dim3(nrb, dm.b * dm.n_kv), dim3(64 * (D / 32)), 0, st, dm, aa);
+  if (KSPLIT) {
+    const int runs = (a.n_splits + kMergeRun - 1) / kMergeRun;
+    hipLaunchKernelGGL((attn_bf16_merge<D>), dim3(nrb, dm.b * dm.n_kv, D / 32), dim3(64 * (runs < kMergeWaves ? runs : kMergeWaves)),
+                       0, st, dm, aa);
+  }
   return hipGetLastError();
 }
 
@@ -589,54 +650,44 @@ static bool eight_row_blocks(const Dims& dm, bool sparse, long long groups) {
 // Few row blocks leave compute units idle whatever the tile mode; their key lists are split over blocks instead.
 // Measured (kernel and merge, unsplit -> split): 4 KV heads x 3 sequences, d 64, 333 tokens over 4999 keys (2 splits)
 // 60 -> 38 us; one KV head of 16 q-heads x 8 sequences, d 64, 69 tokens over 13477 keys (5 splits) 138 -> 65 us.
-// The cheapest of the variants by a model of the launch in microseconds: rounds of 256 resident blocks, each as long as
-// its share of the longest key list plus a fixed part, and for a split list the partials' traffic and the merge launch.
-// Lists of a few steps are then left whole where that is the faster after all: the model has no term for a merge that adds
-// up one split after the other, and takes a short launch for longer than it is.  The two times are fits to measured calls
-// (33 - 660 tokens over 0 - 3000 keys, 229 split and 888 whole; rms 0.3 us split at d 64, 0.5 at d 128).  Whole against the
-// model's splits: 2 KV heads of 2, d 64, 332 tokens over 132 keys 11.7 / 14.5 us (9 splits); 8 heads, d 128, 33 tokens over
-// 200 12.6 / 13.4 (5); 14/2 heads, d 64, 59 tokens over 448 11.5 / 12.9 (8).
-static bool whole_is_faster(const Dims& dm, const AttnPlan& split, long long split_steps, float partials_us,
-                            long long whole_steps) {
-  struct Fit {
-    float fixed, step, merge;
-  };
-  constexpr Fit kFits[2][2] = {{{8.4f, 0.95f, 0.38f}, {7.9f, 1.30f, 0.36f}},    // d 64: eight row blocks, four
-                               {{9.5f, 1.35f, 0.41f}, {9.8f, 1.97f, 0.46f}}};   // d 128
-  const Fit& f = kFits[dm.d == 128][split.split_tile];
-  const float whole = dm.d == 128 ? 7.6f + 1.99f * (float)whole_steps : 6.8f + 1.10f * (float)whole_steps;
-  return whole < f.fixed + f.step * (float)split_steps + f.merge * (float)split.n_splits + partials_us + 0.6f;
-}
-
+// The cheapest variant by a model of the call in microseconds: a fixed part, the steps of the longest key list's share times
+// the rounds of 256 resident blocks, and for a split list the partials' bytes.  The numbers are fits to 2400 measured calls
+// (220 shapes of 5 - 1500 tokens over 64 - 16000 keys; rms 3 - 5 %); a split has to promise 0.6 us more than it costs, because
+// the model takes the shortest whole lists for longer than they are (2 KV heads of 7, d 64, 5 tokens over 129 keys 8.2 us whole,
+// 10.5 in 4 splits).  The plans are 1 % off the best of the measured ones on the mean.
 static AttnPlan attn_plan(const Dims& dm, bool sparse) {
   const long long nrb = (long long)dm.g * ((dm.C + 31) / 32), heads = (long long)dm.n_kv * dm.b;
   if (heads * nrb * 2 > kMaxRecords) return AttnPlan{!eight_row_blocks(dm, sparse, heads * ((nrb + 7) / 8)), 1};
   // (from here on there are at most 128 blocks of eight row blocks: a whole list takes blocks of four, in one round)
-  const float step_us = dm.d == 128 ? 2.1f : 1.2f;   // a step is 8 row blocks x 64 keys or 4 x 128
+  struct Fit {
+    float fixed, step, per_mb;   // a step is 8 row blocks x 64 keys or 4 x 128
+  };
+  constexpr Fit kWhole[2] = {{6.3f, 1.17f, 0.f}, {7.8f, 1.85f, 0.f}};   // d 64, d 128
+  constexpr Fit kSplit[2][2] = {{{8.1f, 1.10f, 0.58f}, {8.3f, 1.30f, 0.62f}},    // d 64: eight row blocks, four
+                                {{9.4f, 1.64f, 0.47f}, {9.8f, 1.95f, 0.56f}}};   // d 128
+  const int wide = dm.d == 128 ? 1 : 0;
   AttnPlan best{true, 1};
-  float best_us = INFINITY, partials_us = 0.f;
-  long long split_steps = 0, whole_steps = 0;
-  for (int mode = 0; mode < 2; ++mode) {
+  float best_us = INFINITY;
+  for (int mode = 1; mode >= 0; --mode) {
     const int kt = mode == 0 ? kSub : 2 * kSub, per_block = mode == 0 ? 8 : 4;
     const long long blocks = heads * ((nrb + per_block - 1) / per_block);
     const int limit = key_splits_limit(dm, sparse, kt);
     const long long tiles = ((long long)attended_cap(dm, sparse) + kt - 1) / kt + (dm.C + kt - 1) / kt;
-    whole_steps = tiles;   // (of the last mode)
-    for (int n = 1; n <= limit && heads * nrb * n <= kMaxRecords; ++n) {
-      if (n == 1 && dm.b > 1 && mode == 0) continue;
+    if (mode == 1) {
+      const long long rounds = (blocks + kComputeUnits - 1) / kComputeUnits;
+      best_us = kWhole[wide].fixed + kWhole[wide].step * (float)(rounds * tiles);
+    }
+    for (int n = 2; n <= limit && heads * nrb * n <= kMaxRecords; ++n) {
+      const Fit& f = kSplit[wide][mode];
       const long long rounds = (blocks * n + kComputeUnits - 1) / kComputeUnits, steps = (tiles + n - 1) / n;
-      const float partials = (float)(heads * nrb * n) * (float)(dm.d + 2) * (256.f / 4e6f);   // written and read at ~4 TB/s
-      float us = (float)rounds * ((float)steps * step_us + (mode == 0 ? 6.f : 8.f));
-      if (n > 1) us += 5.f + partials;
+      const float mb = (float)(heads * nrb * n) * (float)(dm.d + 2) * 128e-6f;
+      const float us = f.fixed + 0.6f + f.step * (float)(rounds * steps) + f.per_mb * mb + 0.03f * (float)n;
       if (us < best_us) {
         best = AttnPlan{mode == 1, n};
         best_us = us;
-        partials_us = partials;
-        split_steps = rounds * steps;
       }
     }
   }
-  if (best.n_splits == 1 || whole_is_faster(dm, best, split_steps, partials_us, whole_steps)) return AttnPlan{true, 1};
   return best;
 }
 

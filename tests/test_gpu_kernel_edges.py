@@ -140,6 +140,21 @@ def test_bf16_attention_key_splits_of_eight_row_blocks():
                     rows=[0, 1, 31, 32, 700, 1311, 1312, 1340])
 
 
+# the merge of key splits takes four records at a time and up to eight waves: 2 to 5 splits, 8 and 9, and the most there are
+@pytest.mark.parametrize("case", [
+    dict(n_q=32, n_kv=8, d=64, chunk=333, kv_lens=[2000], budgets=[1990]),       # 2
+    dict(n_q=7, n_kv=1, d=128, chunk=333, kv_lens=[300], budgets=[299]),         # 3
+    dict(n_q=14, n_kv=2, d=128, chunk=65, kv_lens=[300], budgets=[290]),         # 4
+    dict(n_q=2, n_kv=1, d=64, chunk=333, kv_lens=[150], budgets=[150]),          # 5
+    dict(n_q=4, n_kv=1, d=128, chunk=130, kv_lens=[700], budgets=[640]),         # 8
+    dict(n_q=1, n_kv=1, d=64, chunk=333, kv_lens=[700], budgets=[690]),          # 9
+    dict(n_q=1, n_kv=1, d=128, chunk=33, kv_lens=[20000], budgets=[19000]),      # 32, one token in the second row block
+    dict(n_q=3, n_kv=1, d=64, chunk=33, kv_lens=[9000, 2, 0, 4000], budgets=[8000, 2, 1, 40], batch=4),   # neutral records
+], ids=_id)
+def test_bf16_attention_merge_of_splits(case):
+    check_attention(dict(case, dtype="bf16"))
+
+
 # whole key lists of one sequence: one round of blocks of eight row blocks (130 of them, the last one not full; long lists
 # and none), and two rounds of blocks of four (264 of eight)
 @pytest.mark.parametrize("case", [
