@@ -5,10 +5,10 @@
 //   sq_partial_sums : per (b, q-head, token tile) column sums of Q                     -> ws.part
 //   sq_cosine       : per (b, q-head, token tile) mean query from the partials (fixed order, so the
 //                     result is bit-reproducible), then CosSim(q_i, M_Q) for the tile   -> ws.cos
-//   sq_select       : per (b, q-head) the N' lowest cosines in rank order (radix select on register-held
+//   sq_select       : per (b, q-head) the N' lowest cosines in rank order (histogram of register-held
 //                     keys + rank by counting)                                          -> q_idx
-//   sq_head_select  : the three steps above in one block per (b, q-head), for batches of short chunks (the rows of
-//                     a head fit the block's registers and the heads alone fill the chip)
+//   sq_head_select  : the three steps above in one block per (b, q-head), for short chunks (the rows of a head fit the
+//                     block's registers)
 //   sq_qbar         : per (b, KV head, r) unit-normalise the r-th retained query of each head of the
 //                     group and average                                                 -> qbar
 #include "common.hip.h"
@@ -83,6 +83,21 @@ __global__ __launch_bounds__(kSqThreads) void sq_partial_sums(Dims dm, const T* 
   }
 }
 
+// Norm of the mean by one thread, summed in order.
+template <int D>
+__device__ __forceinline__ float norm_in_order(const float* mean) {   // 16-byte aligned
+  float ss = 0.f;
+#pragma unroll
+  for (int i = 0; i < D; i += 4) {
+    const float4 v = *reinterpret_cast<const float4*>(mean + i);
+    ss += v.x * v.x;
+    ss += v.y * v.y;
+    ss += v.z * v.z;
+    ss += v.w * v.w;
+  }
+  return fmaxf(sqrtf(ss), kNormEps);
+}
+
 // ---------------------------------------------------------------------------------------------
 template <typename T, int D>
 __global__ __launch_bounds__(kSqThreads) void sq_cosine(Dims dm, const T* __restrict__ q, const float* __restrict__ part,
@@ -91,7 +106,7 @@ __global__ __launch_bounds__(kSqThreads) void sq_cosine(Dims dm, const T* __rest
   constexpr int RPB = kSqThreads / CG;
   const int tile = blockIdx.x, h = blockIdx.y, b = blockIdx.z;
   const int C = dm.chunk(b);
-  __shared__ float mean[D];
+  __shared__ __align__(16) float mean[D];
   __shared__ float mnorm;
   const int cg = threadIdx.x % CG, rr = threadIdx.x / CG;
   const T* base = q + b * dm.qs[0] + h * dm.qs[1];
@@ -113,19 +128,13 @@ __global__ __launch_bounds__(kSqThreads) void sq_cosine(Dims dm, const T* __rest
 #pragma unroll
   for (int u = 0; u < kSqTile / RPB; ++u) rows[u].load(base + (size_t)min(t0 + u * RPB + rr, C - 1) * dm.qs[2] + cg * 8);
   __syncthreads();
-  if (threadIdx.x == 0) {
-    float ss = 0.f;
-    for (int i = 0; i < D; ++i) ss += mean[i] * mean[i];
-    mnorm = fmaxf(sqrtf(ss), kNormEps);
-  }
-  __syncthreads();
+  if (threadIdx.x == kSqThreads - kWave) mnorm = norm_in_order<D>(mean);
   float m[8];
 #pragma unroll
   for (int e = 0; e < 8; ++e) m[e] = mean[cg * 8 + e];
-  const float mn = mnorm;
+  float dots[kSqTile / RPB], qn[kSqTile / RPB];   // (the norm of the mean is needed last)
 #pragma unroll
   for (int u = 0; u < kSqTile / RPB; ++u) {
-    const int tok = t0 + u * RPB + rr;
     float v[8];
     rows[u].widen(v);
     float dot = 0.f, qq = 0.f;
@@ -141,92 +150,169 @@ __global__ __launch_bounds__(kSqThreads) void sq_cosine(Dims dm, const T* __rest
       dot = group_sum<CG>(dot);
       qq = group_sum<CG>(qq);
     }
-    if (cg == 0 && tok < C) {
-      const float qn = fmaxf(sqrtf(qq), kNormEps);
-      cosv[(size_t)(b * dm.n_q + h) * dm.C + tok] = dot / (qn * mn) + 0.0f;
-    }
+    dots[u] = dot;
+    qn[u] = fmaxf(sqrtf(qq), kNormEps);
+  }
+  __syncthreads();
+  const float mn = mnorm;
+#pragma unroll
+  for (int u = 0; u < kSqTile / RPB; ++u) {
+    const int tok = t0 + u * RPB + rr;
+    if (cg == 0 && tok < C) cosv[(size_t)(b * dm.n_q + h) * dm.C + tok] = dots[u] / (qn[u] * mn) + 0.0f;
   }
 }
 
 // ---------------------------------------------------------------------------------------------
-// One block per (b, q-head): the N' lowest cosines in rank order.  Thread t keeps cosines t*IPT .. t*IPT+IPT-1
-// in registers as order-preserving keys; LDS radix select (8 bits per pass, ties to the lower position) that
-// starts below the leading bits all keys share (cosines to the mean sit in a narrow range), then the rank of
-// every retained query among the retained ones by counting, spread over the whole block.
-constexpr int kMaxKeep = 128;
 constexpr int kSelThreads = 1024;
 
-// The N' lowest keys of a block's register-held order-preserving keys, in rank order, to out[0..n_keep): radix select,
-// compaction of the retained ones in position order, rank by counting.  Thread t holds positions lo .. lo+IPT-1.
+// The N' lowest keys of a block's register-held order-preserving keys, in rank order, to out[0..n_keep).  Thread t holds
+// positions lo .. lo+IPT-1.  A histogram over 1024 equal bins of the cosines' range finds the bin that holds the N'-th lowest;
+// the keys up to that bin, a few more than N', are listed in any order, and the rank of each among them is counted: one
+// barrier for the range, one for the histogram, one for the list.  Where they do not fit the list (many equal cosines,
+// or nearly so) or a cosine is not finite, the exact cut is found by radix select first.
+// (Radix select and an ordered compaction for every head, three to four passes: sq_select 5.5 -> 4.0 us at 8 to 32 heads of 64 to
+// 1024 cosines, 9.3 -> 6.8 at 4096.)
+constexpr int kSqBins = 1024, kSqRowPitch = 20;   // 16 bins a lane; the pitch spreads 16-byte reads over the banks
+constexpr int kMaxCands = 256;
+struct __align__(16) RankLds {
+  uint32_t hist[kWave * kSqRowPitch];
+  unsigned long long cand[kMaxCands];   // key in the high half, position in the low one
+  uint32_t wmin[kSelThreads / kWave], wmax[kSelThreads / kWave];
+  uint32_t n_listed;
+  RadixSelectLds rs;
+  uint32_t wsum[kSelThreads / kWave + 1];
+};
+static_assert(alignof(RankLds) >= sizeof(u32x4), "the histogram is read 16 bytes at a time");
+
+__device__ __forceinline__ float okey_value(uint32_t k) { return __uint_as_float(k & 0x80000000u ? k ^ 0x80000000u : ~k); }
+
+// (before the first barrier of the caller, or with one between this and the selection)
+__device__ __forceinline__ void clear_rank_lds(RankLds& L) {
+  for (int i = threadIdx.x; i < kWave * kSqRowPitch; i += kSelThreads) L.hist[i] = 0u;
+  if (threadIdx.x == 0) L.n_listed = 0u;
+}
+
 template <int IPT>
 __device__ __forceinline__ void select_lowest_ranked(const uint32_t (&key)[IPT], uint32_t valid, int lo, int n_keep,
-                                                     RadixSelectLds& rs, uint32_t* wsum, uint32_t* sel_key,
-                                                     uint32_t* sel_idx, int32_t* __restrict__ out) {
+                                                     RankLds& L, int32_t* __restrict__ out) {
   const int tid = threadIdx.x, lane = tid & 63, w = tid >> 6;
-  // tau: key of the n_keep-th smallest cosine; need_eq: how many elements equal to it are kept (lowest positions first)
-  uint32_t tau, need_eq;
-  block_radix_select<IPT, false>(key, valid, (uint32_t)n_keep, rs, &tau, &need_eq);
-  // Retained queries go to LDS in position order.  One block scan carries both counts a thread needs (elements below
-  // the cut in the high half, elements equal to it in the low half; both fit 16 bits since C <= 8192).
-  uint32_t cnt = 0;
-#pragma unroll
-  for (int j = 0; j < IPT; ++j) {
-    const bool in = (valid >> j) & 1u;
-    cnt += (in && key[j] == tau ? 1u : 0u) + (in && key[j] < tau ? 0x10000u : 0u);
-  }
-  uint32_t tot;
-  const uint32_t before = block_excl_scan<kSelThreads>(cnt, wsum, &tot);
-  uint32_t eq_rank = before & 0xFFFFu, lt_rank = before >> 16;
+  uint32_t kmin = 0xFFFFFFFFu, kmax = 0u;
 #pragma unroll
   for (int j = 0; j < IPT; ++j) {
     if ((valid >> j) & 1u) {
-      const uint32_t k = key[j];
-      const bool lt = k < tau, eq = k == tau;
-      if (lt || (eq && eq_rank < need_eq)) {   // equal cosines go to the lower positions
-        const uint32_t slot = lt_rank + min(eq_rank, need_eq);
-        if (slot < (uint32_t)kMaxKeep) {
-          sel_key[slot] = k;
-          sel_idx[slot] = (uint32_t)(lo + j);
-        }
-      }
-      lt_rank += lt ? 1u : 0u;
-      eq_rank += eq ? 1u : 0u;
+      kmin = min(kmin, key[j]);
+      kmax = max(kmax, key[j]);
     }
+  }
+  kmin = wave_min_u32(kmin);
+  kmax = wave_max_u32(kmax);
+  if (lane == 0) {
+    L.wmin[w] = kmin;
+    L.wmax[w] = kmax;
   }
   __syncthreads();
-  // rank by counting: P consecutive lanes share one retained query and split the comparisons
-  int nk2 = 1;
-  while (nk2 < n_keep) nk2 <<= 1;
-  const int P = kSelThreads / nk2;         // 8 .. 1024, a power of two
+  constexpr int NW = kSelThreads / kWave;
+  kmin = wave_min_u32(L.wmin[lane % NW]);
+  kmax = wave_max_u32(L.wmax[lane % NW]);
+  if (kmin == kmax) {   // all cosines are equal: the lowest positions, in order (block-uniform)
+#pragma unroll
+    for (int j = 0; j < IPT; ++j)
+      if (lo + j < n_keep) out[lo + j] = lo + j;
+    return;
+  }
+  const float fmin_ = okey_value(kmin), range = okey_value(kmax) - fmin_;
+  // (infinities and NaN have the outermost keys, so a finite range means that every cosine is finite)
+  bool listed = range < INFINITY;   // wave-uniform, and the same in every wave
+  int bin[IPT];
+  int cut_bin = 0;
+  uint32_t n_c = 0;
+  if (listed) {
+    const float per = fminf((float)(kSqBins - 1) / range, 3.0e38f);   // monotone in the cosine, whatever it rounds to
+#pragma unroll
+    for (int j = 0; j < IPT; ++j) {
+      bin[j] = min(max((int)((okey_value(key[j]) - fmin_) * per), 0), kSqBins - 1);
+      if ((valid >> j) & 1u) atomicAdd(&L.hist[bin[j] + (bin[j] >> 4) * (kSqRowPitch - 16)], 1u);
+    }
+    __syncthreads();
+    // every wave finds the cut's bin for itself; lane l has bins 16 l .. 16 l + 15
+    uint32_t c[16];
+    uint32_t sum = 0;
+#pragma unroll
+    for (int i = 0; i < 4; ++i) {
+      const u32x4 v = *reinterpret_cast<const u32x4*>(&L.hist[lane * kSqRowPitch + 4 * i]);
+#pragma unroll
+      for (int e = 0; e < 4; ++e) {
+        c[4 * i + e] = v[e];
+        sum += v[e];
+      }
+    }
+    const uint32_t upto = wave_incl_scan_u32(sum), need = (uint32_t)n_keep;
+    uint32_t run = upto - sum;
+    int found = 0;
+    uint32_t at = upto;
+#pragma unroll
+    for (int i = 0; i < 16; ++i) {   // the lane's first bin with which the running count reaches n_keep
+      run += c[i];
+      const bool before = run < need;
+      found += before ? 1 : 0;
+      at = !before && at > run ? run : at;
+    }
+    const unsigned long long hit = __builtin_amdgcn_ballot_w64(upto - sum < need && need <= upto);   // exactly one lane
+    const int src = hit ? (int)__builtin_ctzll(hit) : 63;
+    cut_bin = __builtin_amdgcn_readlane(16 * lane + min(found, 15), src);
+    n_c = (uint32_t)__builtin_amdgcn_readlane((int)at, src);
+    listed = n_c <= (uint32_t)kMaxCands;
+  }
+  if (listed) {
+#pragma unroll
+    for (int j = 0; j < IPT; ++j) {
+      const bool in = ((valid >> j) & 1u) && bin[j] <= cut_bin;
+      const unsigned long long m = __builtin_amdgcn_ballot_w64(in);
+      if (m != 0) {   // wave-uniform; any order will do
+        uint32_t slot = 0;
+        if (lane == 0) slot = atomicAdd(&L.n_listed, (uint32_t)__popcll(m));
+        slot = (uint32_t)__builtin_amdgcn_readfirstlane((int)slot) + (uint32_t)__popcll(m & ((1ull << lane) - 1ull));
+        if (in && slot < (uint32_t)kMaxCands) L.cand[slot] = ((unsigned long long)key[j] << 32) | (uint32_t)(lo + j);
+      }
+    }
+  } else {
+    // key of the n_keep-th smallest cosine; need_eq: how many elements equal to it are kept (lowest positions first)
+    uint32_t tau, need_eq;
+    block_radix_select<IPT, false>(key, valid, (uint32_t)n_keep, L.rs, &tau, &need_eq);
+    uint32_t eq = 0, tot;
+#pragma unroll
+    for (int j = 0; j < IPT; ++j) eq += ((valid >> j) & 1u) && key[j] == tau ? 1u : 0u;
+    uint32_t eq_rank = block_excl_scan<kSelThreads>(eq, L.wsum, &tot);
+#pragma unroll
+    for (int j = 0; j < IPT; ++j) {
+      const bool is_eq = ((valid >> j) & 1u) && key[j] == tau;
+      if (((valid >> j) & 1u) && (key[j] < tau || (is_eq && eq_rank < need_eq))) {
+        const uint32_t slot = atomicAdd(&L.n_listed, 1u);
+        if (slot < (uint32_t)kMaxCands) L.cand[slot] = ((unsigned long long)key[j] << 32) | (uint32_t)(lo + j);
+      }
+      eq_rank += is_eq ? 1u : 0u;
+    }
+    n_c = (uint32_t)n_keep;
+  }
+  __syncthreads();
+  // rank by counting: P consecutive lanes share one listed query and split the comparisons (equal cosines: the lower
+  // position first, as the low halves say)
+  int e_cap = 16;
+  while (e_cap < (int)n_c) e_cap <<= 1;
+  const int P = kSelThreads / e_cap;         // 4 .. 64
   const int e = tid / P, part = tid % P;
   int rank = 0;
-  if (e < n_keep) {
-    const uint32_t k = sel_key[e], id = sel_idx[e];
-    for (int jj = part; jj < n_keep; jj += P) {
-      const uint32_t kj = sel_key[jj], ij = sel_idx[jj];
-      rank += (kj < k) || (kj == k && ij < id);
-    }
-  }
-  for (int o = 1; o < P && o < 64; o <<= 1) rank += __shfl_xor(rank, o, kWave);
-  if (P > 64) {   // n_keep < 16: the lanes of one query span waves; let lane 0 of each wave add through LDS
-    __syncthreads();
-    if (lane == 0) wsum[w] = (uint32_t)rank;
-    __syncthreads();
-    rank = 0;
-    const int w0 = (e * P) >> 6;
-    for (int i = 0; i < P / 64; ++i) rank += (int)wsum[w0 + i];
-  }
-  if (e < n_keep && part == 0) out[rank] = (int32_t)sel_idx[e];
+  const unsigned long long mine = L.cand[min(e, (int)n_c - 1)];
+  if (e < (int)n_c)
+    for (int jj = part; jj < (int)n_c; jj += P) rank += L.cand[jj] < mine ? 1 : 0;
+  for (int o = 1; o < P; o <<= 1) rank += __shfl_xor(rank, o, kWave);
+  if (e < (int)n_c && part == 0 && rank < n_keep) out[rank] = (int32_t)(uint32_t)mine;
 }
 
 template <int IPT>
 __global__ __launch_bounds__(kSelThreads) void sq_select(Dims dm, const float* __restrict__ cosv,
                                                         int32_t* __restrict__ q_idx, int n_keep) {
-  constexpr int NW = kSelThreads / 64;
-  __shared__ RadixSelectLds rs;
-  __shared__ uint32_t wsum[NW + 1];
-  __shared__ uint32_t sel_key[kMaxKeep];
-  __shared__ uint32_t sel_idx[kMaxKeep];
+  __shared__ RankLds L;
   const int h = blockIdx.x, b = blockIdx.y;
   const int C = dm.chunk(b);
   const float* cv = cosv + (size_t)(b * dm.n_q + h) * dm.C;
@@ -239,71 +325,106 @@ __global__ __launch_bounds__(kSelThreads) void sq_select(Dims dm, const float* _
     key[j] = in ? okey(cv[lo + j]) : 0xFFFFFFFFu;
     valid |= (in ? 1u : 0u) << j;
   }
-  select_lowest_ranked<IPT>(key, valid, lo, n_keep, rs, wsum, sel_key, sel_idx,
-                            q_idx + (size_t)(b * dm.n_q + h) * n_keep);
+  clear_rank_lds(L);   // (the selection's first barrier comes before it counts)
+  select_lowest_ranked<IPT>(key, valid, lo, n_keep, L, q_idx + (size_t)(b * dm.n_q + h) * n_keep);
 }
 
 // ---------------------------------------------------------------------------------------------
 // Mean, cosines and selection of one (b, q-head) in one block, for chunks short enough that the block can hold the
 // head's queries in registers: every row is requested at once (one memory latency; a compute unit that fetches a
 // few rows per thread at a time pulls only a few tens of GB/s) and read only once.
-// Column sums are formed per group of concurrently handled rows and the groups added in a fixed order, so the mean is
-// bit-reproducible here too (its rounding differs from the tiled kernels' in the last bits: the two routes are
-// never mixed within one call).
-template <typename T, int D, int NR>   // NR: rows per thread (all held in registers)
+// Column sums, two orders.  TILED: the very sums of the tiled kernels -- the rows of a 64-token tile by the same groups, the
+// groups of a tile in order, the tiles in order, the norm in order -- so a call may take either route, bit for bit.
+// Otherwise (batches, see select_queries_one_block): per group of concurrently handled rows over the whole chunk, the groups in
+// order; its rounding differs from the tiled one's in the last bits, and the two are never mixed within one call.
+template <typename T, int D, int NR, bool TILED>   // NR: rows per thread (all held in registers)
 __global__ __launch_bounds__(kSelThreads) void sq_head_select(Dims dm, const T* __restrict__ q,
                                                              int32_t* __restrict__ q_idx, int n_keep) {
   constexpr int CG = D / 8;                  // lanes per row (8 elements each)
   constexpr int RPB = kSelThreads / CG;      // rows handled concurrently
   constexpr int IPT = (RPB * NR + kSelThreads - 1) / kSelThreads;   // cosines per thread in the selection
-  constexpr int NW = kSelThreads / 64;
-  __shared__ RadixSelectLds rs;
-  __shared__ uint32_t wsum[NW + 1];
-  __shared__ uint32_t sel_key[kMaxKeep];
-  __shared__ uint32_t sel_idx[kMaxKeep];
-  __shared__ float mean[D];
+  constexpr int RT = kSqThreads / CG;        // TILED: rows of a tile handled concurrently, as in sq_partial_sums ...
+  constexpr int UT = kSqTile / RT;           // ... and rows of a tile per thread
+  constexpr int TB = kSelThreads / kSqThreads;   // TILED: tiles handled concurrently
+  static_assert(!TILED || NR % UT == 0, "whole tiles");
+  constexpr int NT = TILED ? NR / UT * TB : 1;
+  __shared__ RankLds L;
+  __shared__ __align__(16) float mean[D];
   __shared__ float mnorm;
   __shared__ float buf[RPB * D];             // column partials, then the cosines (RPB * NR <= RPB * D of them)
+  __shared__ float tsum[NT * D];
   const int h = blockIdx.x, b = blockIdx.y;
   const int C = dm.chunk(b);
   const int tid = threadIdx.x;
-  const int cg = tid % CG, rr = tid / CG;
+  const int cg = tid % CG, rr = TILED ? (tid / CG) % RT : tid / CG;
+  // token of a thread's register u
+  auto token = [&](int u) __attribute__((always_inline)) {
+    if constexpr (TILED) return (tid / kSqThreads + TB * (u / UT)) * kSqTile + (u % UT) * RT + rr;
+    return u * RPB + rr;
+  };
   const T* base = q + b * dm.qs[0] + h * dm.qs[1];
   Raw8<T> rows[NR];
 #pragma unroll
-  for (int u = 0; u < NR; ++u) rows[u].load(base + (size_t)min(u * RPB + rr, C - 1) * dm.qs[2] + cg * 8);
-  // ---- column sums, mean, its norm ----
-  float acc[8] = {0, 0, 0, 0, 0, 0, 0, 0};
+  for (int u = 0; u < NR; ++u) rows[u].load(base + (size_t)min(token(u), C - 1) * dm.qs[2] + cg * 8);
+  clear_rank_lds(L);
+  // ---- column sums, mean ----
+  float acc[8];
 #pragma unroll
   for (int u = 0; u < NR; ++u) {
+    if (u == 0 || (TILED && u % UT == 0)) {
+#pragma unroll
+      for (int e = 0; e < 8; ++e) acc[e] = 0.f;
+    }
     float v[8];
     rows[u].widen(v);
-    if (u * RPB + rr < C) {
+    if (token(u) < C) {
 #pragma unroll
       for (int e = 0; e < 8; ++e) acc[e] += v[e];
     }
-  }
+    if (TILED && u % UT == UT - 1) {   // four tiles at a time through the buffer
+      if (u >= UT) __syncthreads();    // (the sums of the four before have been read)
 #pragma unroll
-  for (int e = 0; e < 8; ++e) buf[rr * D + cg * 8 + e] = acc[e];
+      for (int e = 0; e < 8; ++e) buf[(tid / CG) * D + cg * 8 + e] = acc[e];
+      __syncthreads();
+      if (tid < TB * D) {
+        const float* p = buf + (tid / D) * RT * D + tid % D;
+        float s = 0.f;
+#pragma unroll
+        for (int i = 0; i < RT; ++i) s += p[i * D];
+        tsum[(u / UT * TB) * D + tid] = s;
+      }
+    }
+  }
+  if constexpr (!TILED) {
+#pragma unroll
+    for (int e = 0; e < 8; ++e) buf[rr * D + cg * 8 + e] = acc[e];
+  }
   __syncthreads();
   if (tid < D) {
     float s = 0.f;
-    for (int i = 0; i < RPB; ++i) s += buf[i * D + tid];
+    if constexpr (TILED) {
+#pragma unroll
+      for (int i = 0; i < NT; ++i) s += tsum[i * D + tid];
+    } else {
+      for (int i = 0; i < RPB; ++i) s += buf[i * D + tid];
+    }
     mean[tid] = s / (float)C;
   }
-  __syncthreads();
-  if (tid < 64) {   // one wave: squared norm of the mean
-    float ss = 0.f;
-    for (int i = tid; i < D; i += 64) ss += mean[i] * mean[i];
-    ss = wave64_sum(ss);
-    if (tid == 0) mnorm = fmaxf(sqrtf(ss), kNormEps);
-  }
   __syncthreads();   // (also: the partials in buf are dead from here on)
+  if constexpr (TILED) {
+    if (tid == kSelThreads - kWave) mnorm = norm_in_order<D>(mean);
+  } else if (tid >= kSelThreads - kWave) {   // one wave: squared norm of the mean
+    const int lane = tid & 63;
+    float ss = 0.f;
+    for (int i = lane; i < D; i += 64) ss += mean[i] * mean[i];
+    ss = wave64_sum(ss);
+    if (lane == 0) mnorm = fmaxf(sqrtf(ss), kNormEps);
+  }
   float m[8];
 #pragma unroll
   for (int e = 0; e < 8; ++e) m[e] = mean[cg * 8 + e];
-  const float mn = mnorm;
-  // ---- cosines of the rows held in registers ----
+  // ---- cosines of the rows held in registers (the norm of the mean is needed last) ----
+  float dots[NR], qn[NR];
 #pragma unroll
   for (int u = 0; u < NR; ++u) {
     float v[8];
@@ -321,8 +442,14 @@ __global__ __launch_bounds__(kSelThreads) void sq_head_select(Dims dm, const T* 
       dot = group_sum<CG>(dot);
       qq = group_sum<CG>(qq);
     }
-    const int tok = u * RPB + rr;
-    if (cg == 0 && tok < C) buf[tok] = dot / (fmaxf(sqrtf(qq), kNormEps) * mn) + 0.0f;
+    dots[u] = dot;
+    qn[u] = fmaxf(sqrtf(qq), kNormEps);
+  }
+  __syncthreads();
+  const float mn = mnorm;
+#pragma unroll
+  for (int u = 0; u < NR; ++u) {
+    if (cg == 0 && token(u) < C) buf[token(u)] = dots[u] / (qn[u] * mn) + 0.0f;
   }
   __syncthreads();
   const int lo = tid * IPT;
@@ -334,8 +461,7 @@ __global__ __launch_bounds__(kSelThreads) void sq_head_select(Dims dm, const T* 
     key[j] = in ? okey(buf[in ? lo + j : 0]) : 0xFFFFFFFFu;
     valid |= (in ? 1u : 0u) << j;
   }
-  select_lowest_ranked<IPT>(key, valid, lo, n_keep, rs, wsum, sel_key, sel_idx,
-                            q_idx + (size_t)(b * dm.n_q + h) * n_keep);
+  select_lowest_ranked<IPT>(key, valid, lo, n_keep, L, q_idx + (size_t)(b * dm.n_q + h) * n_keep);
 }
 
 // ---------------------------------------------------------------------------------------------
@@ -378,13 +504,15 @@ __global__ __launch_bounds__(64) void sq_qbar(Dims dm, const T* __restrict__ q, 
 }
 
 // ---------------------------------------------------------------------------------------------
-// One block per head for everything when the block can hold the head's queries in registers (8 rows of 8 elements
-// per thread) AND the heads alone give half the compute units a block (batches).  Measured: 256 heads of 512 tokens
-// 14.8 us against 24 us for the three launches below; with only 32 heads (1024 tokens each) one compute unit per
-// head is the slower way (20.7 against 16.5 us), so single sequences spread the two reads of Q over the whole chip.
-// (Fewer heads of short chunks would gain 2-6 us, but the means of the two routes differ in the last bits, and cosines
-// that differ in theirs only then change ranks, so the line stays where it is.  The route goes by the batch of the whole
-// call and the chunk's own length; how many chunks of a prompt share a launch does not count.)
+// One block per head for everything where that is the faster, one launch instead of three.  Short chunks, whatever the heads, in
+// the sums of the tiled kernels: up to kHeadTokens tokens (query stage, bf16, d 128: 12 heads of 128 tokens 15.2 -> 10.2 us, 32 of
+// 423 15.8 -> 13.0; float32 8 of 464 15.3 -> 13.8).  From there on one compute unit per head pulls too little (32 heads of 1024
+// tokens 20.7 against 16.5 us, d 64 even), so single sequences spread the two reads of Q over the whole chip.
+// Batches, where the heads alone give half the compute units a block and the block can hold the head (8 rows of 8 elements per
+// thread): 256 heads of 512 tokens 14.8 us against 24 us.  Their sums differ in the last bits, and cosines that differ in theirs
+// only can change ranks, so that line stays where it is.  (It goes by the batch of the whole call and the chunk's own length; how
+// many chunks of a prompt share a launch does not count.)
+constexpr int kHeadTokens = 512;
 constexpr int kRowsPerThread = 8;
 bool select_queries_one_block(const Dims& dm) {
   const int rows_at_once = kSelThreads / (dm.d / 8);
@@ -409,7 +537,13 @@ static hipError_t launch_typed(const Dims& dm, const void* q, int32_t* q_idx, fl
     const dim3 sgrid(dm.n_q, dm.b), sblock(kSelThreads);
     const int ipt = (dm.C + kSelThreads - 1) / kSelThreads;
     if (select_queries_one_block(dm)) {
-      hipLaunchKernelGGL((sq_head_select<T, D, kRowsPerThread>), sgrid, sblock, 0, st, dm, qp, q_idx, n_keep);
+      hipLaunchKernelGGL((sq_head_select<T, D, kRowsPerThread, false>), sgrid, sblock, 0, st, dm, qp, q_idx, n_keep);
+    } else if (dm.C <= kHeadTokens / 2) {
+      hipLaunchKernelGGL((sq_head_select<T, D, kHeadTokens / 2 * D / 8 / kSelThreads, true>), sgrid, sblock, 0, st, dm, qp, q_idx,
+                         n_keep);
+    } else if (dm.C <= kHeadTokens) {
+      hipLaunchKernelGGL((sq_head_select<T, D, kHeadTokens * D / 8 / kSelThreads, true>), sgrid, sblock, 0, st, dm, qp, q_idx,
+                         n_keep);
     } else {
       const int n_tiles = (dm.C + kSqTile - 1) / kSqTile;
       dim3 grid(n_tiles, dm.n_q, dm.b);

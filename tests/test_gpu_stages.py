@@ -117,6 +117,41 @@ def test_select_queries_with_repeated_zero_and_rescaled_rows(case):
         assert P.max_abs(qbar[b], want) <= P.TOL_QBAR * max(1.0, float(np.abs(want).max()))
 
 
+# one block per head: tiles of 64 tokens just short of, at and past full, the two sizes of the block's share and the first
+# chunk beyond them; one query more than is retained
+@pytest.mark.parametrize("dtype,d", [("bf16", 128), ("bf16", 64), ("f32", 128), ("f32", 64)])
+@pytest.mark.parametrize("chunk,n_retain", [(2, 1), (17, 16), (63, 5), (64, 63), (65, 64), (256, 128), (257, 16), (511, 100), (512, 128), (513, 64)])
+def test_select_queries_of_short_chunks(dtype, d, chunk, n_retain):
+    w = gen.make_custom(dtype=dtype, n_q=4, n_kv=2, d=d, chunk=chunk, n_retain=n_retain, batch=2, kv_lens=[8, 8], budgets=[2, 2],
+                        seed=19)
+    buf = _buffers(w)
+    buf.q_idx.fill_(-1)
+    buf.select_queries()
+    torch.cuda.synchronize()
+    q_idx, qbar = gen.from_torch(buf.q_idx), gen.from_torch(buf.qbar)
+    for b in range(w.batch):
+        cos = O.cos_to_mean(w.Q[b])
+        for h in range(w.n_q):
+            P.check_query_ranking(q_idx[b, h], cos[h], n_retain, what=f"b{b} h{h}")
+        assert P.max_abs(qbar[b], O.group_mean_queries(w.Q[b], q_idx[b], w.n_kv)) <= P.TOL_QBAR
+
+
+@pytest.mark.parametrize("chunk,equal", [(300, 300), (512, 200), (512, 400), (1500, 255), (1500, 257), (1500, 1500)])
+def test_select_queries_with_more_equal_cosines_than_are_listed(chunk, equal):
+    """`equal` identical queries pull away from the others: they have the lowest cosines, equal bit for bit, and the first
+    positions among them are retained in order, whether or not they all fit the list that is ranked."""
+    w = gen.make_custom(dtype="bf16", n_q=4, n_kv=2, d=128, chunk=chunk, n_retain=100, kv_lens=[8], budgets=[2], seed=20)
+    rng = np.random.default_rng(5)
+    at = np.sort(rng.choice(chunk, size=equal, replace=False))
+    u = np.sign(rng.standard_normal(128)) * 0.5
+    w.Q[0] = w.Q[0] * 0.25 + 4.0 * u          # (away from the others even where most of the queries are the equal ones)
+    w.Q[0][:, at] = -u if equal < chunk else u
+    buf = _buffers(w)
+    buf.select_queries()
+    torch.cuda.synchronize()
+    assert np.array_equal(gen.from_torch(buf.q_idx)[0], np.tile(at[:100], (4, 1)))
+
+
 SCORE_CASES = [
     dict(dtype="f32", n_q=2, n_kv=1, d=64, chunk=128, n_retain=16, kv_lens=[1000]),
     dict(dtype="bf16", n_q=8, n_kv=2, d=128, chunk=256, n_retain=64, kv_lens=[1500]),          # ragged tail tile
