@@ -465,8 +465,10 @@ __global__ __launch_bounds__(kSelThreads) void sq_head_select(Dims dm, const T* 
 }
 
 // ---------------------------------------------------------------------------------------------
-// One wave per (r, kv, b).
-template <typename T, int D, int RULE>
+// One wave per (r, kv, b); GU: heads of the group whose rows travel, and whose norms form, side by side (all of them: with the
+// positions in one vector load and no branch per head, the query stage of one KV head of 16, d 128, 600 tokens takes 15.8 us
+// instead of 18.6, of 8 KV heads of 4 14.2 instead of 14.9).
+template <typename T, int D, int RULE, int GU>
 __global__ __launch_bounds__(64) void sq_qbar(Dims dm, const T* __restrict__ q, int32_t* __restrict__ q_idx,
                                              float* __restrict__ qbar, int n_keep, uint32_t* __restrict__ zero,
                                              uint32_t zero_words, uint16_t* __restrict__ terms) {
@@ -475,7 +477,7 @@ __global__ __launch_bounds__(64) void sq_qbar(Dims dm, const T* __restrict__ q, 
   const int r = blockIdx.x, kv = blockIdx.y, b = blockIdx.z;
   const int lane = threadIdx.x;
   float row[EPL];
-  qbar_row<T, D, RULE>(dm, q, q_idx, n_keep, r, kv, b, lane, true, row);
+  qbar_row<T, D, RULE, GU>(dm, q, q_idx, n_keep, r, kv, b, lane, true, row);
   float* out = qbar + ((size_t)(b * dm.n_kv + kv) * n_keep + r) * D;
 #pragma unroll
   for (int e = 0; e < EPL; ++e) out[lane * EPL + e] = row[e];
@@ -520,19 +522,29 @@ bool select_queries_one_block(const Dims& dm) {
   return dm.C <= rows_at_once * kRowsPerThread && sequences * dm.n_q >= 128;
 }
 
+template <typename T, int D, int RULE>
+static void launch_qbar(const Dims& dm, const T* q, int32_t* q_idx, float* qbar, int n_keep, hipStream_t st, uint32_t* zero,
+                        uint32_t zero_words, uint16_t* terms) {
+  const dim3 grid(n_keep, dm.n_kv, dm.b);
+  if (dm.g <= 4) {
+    hipLaunchKernelGGL((sq_qbar<T, D, RULE, 4>), grid, dim3(64), 0, st, dm, q, q_idx, qbar, n_keep, zero, zero_words, terms);
+  } else if (dm.g <= 8) {
+    hipLaunchKernelGGL((sq_qbar<T, D, RULE, 8>), grid, dim3(64), 0, st, dm, q, q_idx, qbar, n_keep, zero, zero_words, terms);
+  } else {
+    hipLaunchKernelGGL((sq_qbar<T, D, RULE, 16>), grid, dim3(64), 0, st, dm, q, q_idx, qbar, n_keep, zero, zero_words, terms);
+  }
+}
+
 template <typename T, int D>
 static hipError_t launch_typed(const Dims& dm, const void* q, int32_t* q_idx, float* qbar, float* ws_part,
                                float* ws_cos, hipStream_t st, uint32_t* zero, uint32_t zero_words,
                                uint16_t* terms) {
   const int n_keep = dm.n_ret < dm.C ? dm.n_ret : dm.C;
   const T* qp = static_cast<const T*>(q);
-  const dim3 qgrid(n_keep, dm.n_kv, dm.b);
   if (dm.C <= dm.n_ret) {
-    hipLaunchKernelGGL((sq_qbar<T, D, kIdentity>), qgrid, dim3(64), 0, st, dm, qp, q_idx, qbar, n_keep, zero,
-                       zero_words, terms);
+    launch_qbar<T, D, kIdentity>(dm, qp, q_idx, qbar, n_keep, st, zero, zero_words, terms);
   } else if (dm.flags & QUOKA_SELECT_UNIFORM) {
-    hipLaunchKernelGGL((sq_qbar<T, D, kUniform>), qgrid, dim3(64), 0, st, dm, qp, q_idx, qbar, n_keep, zero,
-                       zero_words, terms);
+    launch_qbar<T, D, kUniform>(dm, qp, q_idx, qbar, n_keep, st, zero, zero_words, terms);
   } else {
     const dim3 sgrid(dm.n_q, dm.b), sblock(kSelThreads);
     const int ipt = (dm.C + kSelThreads - 1) / kSelThreads;
@@ -559,8 +571,7 @@ static hipError_t launch_typed(const Dims& dm, const void* q, int32_t* q_idx, fl
         hipLaunchKernelGGL((sq_select<8>), sgrid, sblock, 0, st, dm, ws_cos, q_idx, n_keep);
       }
     }
-    hipLaunchKernelGGL((sq_qbar<T, D, kFromIndex>), qgrid, dim3(64), 0, st, dm, qp, q_idx, qbar, n_keep, zero,
-                       zero_words, terms);
+    launch_qbar<T, D, kFromIndex>(dm, qp, q_idx, qbar, n_keep, st, zero, zero_words, terms);
   }
   return hipGetLastError();
 }
