@@ -86,6 +86,30 @@ __device__ __forceinline__ float row16_sum(float x) {
   return x;
 }
 
+// The same for unsigned integers: sum, minimum, maximum.
+#define QUOKA_ROW16(x, OP)                                                                         \
+  do {                                                                                             \
+    x = OP(x, (uint32_t)__builtin_amdgcn_update_dpp((int)x, (int)x, 0x128, 0xF, 0xF, false));      \
+    x = OP(x, (uint32_t)__builtin_amdgcn_update_dpp((int)x, (int)x, 0x124, 0xF, 0xF, false));      \
+    x = OP(x, (uint32_t)__builtin_amdgcn_update_dpp((int)x, (int)x, 0x122, 0xF, 0xF, false));      \
+    x = OP(x, (uint32_t)__builtin_amdgcn_update_dpp((int)x, (int)x, 0x121, 0xF, 0xF, false));      \
+  } while (0)
+__device__ __forceinline__ uint32_t op_add_u32(uint32_t a, uint32_t b) { return a + b; }
+__device__ __forceinline__ uint32_t op_min_u32(uint32_t a, uint32_t b) { return a < b ? a : b; }
+__device__ __forceinline__ uint32_t op_max_u32(uint32_t a, uint32_t b) { return a > b ? a : b; }
+__device__ __forceinline__ uint32_t row16_sum_u32(uint32_t x) {
+  QUOKA_ROW16(x, op_add_u32);
+  return x;
+}
+__device__ __forceinline__ uint32_t row16_min_u32(uint32_t x) {
+  QUOKA_ROW16(x, op_min_u32);
+  return x;
+}
+__device__ __forceinline__ uint32_t row16_max_u32(uint32_t x) {
+  QUOKA_ROW16(x, op_max_u32);
+  return x;
+}
+
 // Cross-lane steps on the VALU's DPP path (no LDS crossbar, a few clocks each instead of a ds_bpermute round trip).
 // CTRL: row_shr:n = 0x110 + n (lane i reads lane i-n of its 16-lane row), row_bcast:15 = 0x142 (lane 15 of every row to
 // the next row), row_bcast:31 = 0x143 (lane 31 to rows 2 and 3).  A lane without a source, or in a row that ROW_MASK
@@ -107,9 +131,6 @@ __device__ __forceinline__ uint32_t dpp_take(uint32_t idle, uint32_t v) {
     x = OP(x, dpp_take<0x143, 0xC>(IDLE, x));                          \
   } while (0)
 
-__device__ __forceinline__ uint32_t op_add_u32(uint32_t a, uint32_t b) { return a + b; }
-__device__ __forceinline__ uint32_t op_min_u32(uint32_t a, uint32_t b) { return a < b ? a : b; }
-__device__ __forceinline__ uint32_t op_max_u32(uint32_t a, uint32_t b) { return a > b ? a : b; }
 __device__ __forceinline__ uint32_t op_add_f32(uint32_t a, uint32_t b) {
   return __float_as_uint(__uint_as_float(a) + __uint_as_float(b));
 }
@@ -170,7 +191,7 @@ __device__ __forceinline__ uint32_t block_excl_scan(uint32_t x, uint32_t* wsum, 
   return wsum[w] + inc - x;
 }
 
-// Block-wide radix select over keys held in registers (blocks of 1024 threads, every thread calls it).
+// Block-wide radix select over keys held in registers (blocks of NT threads, at most 1024; every thread calls it).
 // key[j] is an order-preserving uint32 image; bit j of `valid` says whether key[j] is a real element.  Finds the key
 // of the element of rank `need` (1-based; counted from the largest if DESC, else from the smallest; the caller
 // guarantees need <= number of valid elements) and how many elements equal to that key belong to the first `need`.
@@ -184,11 +205,11 @@ struct __align__(16) RadixSelectLds {
 };
 static_assert(alignof(RadixSelectLds) >= sizeof(u32x4), "the histograms are read 16 bytes at a time");
 
-template <int IPT, bool DESC>
+template <int IPT, bool DESC, int NT = 1024>
 __device__ __forceinline__ void block_radix_select(const uint32_t (&key)[IPT], uint32_t valid, uint32_t need,
                                                    RadixSelectLds& L, uint32_t* cut_key, uint32_t* need_eq) {
   const int tid = threadIdx.x, lane = tid & 63, w = tid >> 6;
-  if (tid < 768) (&L.hist[0][0])[tid] = 0u;
+  for (int i = tid; i < 768; i += NT) (&L.hist[0][0])[i] = 0u;
   uint32_t kmin = 0xFFFFFFFFu, kmax = 0u;
 #pragma unroll
   for (int j = 0; j < IPT; ++j) {
@@ -204,8 +225,8 @@ __device__ __forceinline__ void block_radix_select(const uint32_t (&key)[IPT], u
     L.wmax[w] = kmax;
   }
   __syncthreads();
-  kmin = wave_min_u32(lane < 16 ? L.wmin[lane] : 0xFFFFFFFFu);
-  kmax = wave_max_u32(lane < 16 ? L.wmax[lane] : 0u);
+  kmin = wave_min_u32(lane < NT / 64 ? L.wmin[lane] : 0xFFFFFFFFu);
+  kmax = wave_max_u32(lane < NT / 64 ? L.wmax[lane] : 0u);
   const uint32_t diff = kmin ^ kmax;
   int hi = diff ? 32 - __clz(diff) : 0;                                    // valid keys agree on all bits >= hi
   uint32_t mask = hi >= 32 ? 0u : ~((hi == 0) ? 0u : ((1u << hi) - 1u));   // decided bits

@@ -5,7 +5,7 @@
 // equals +0, a NaN ranks as the infinity of its sign), or as order-preserving images that compare alike, so the result is
 // deterministic and does not depend on the launch shape.
 //
-//   T_max <= kSmallMax : one to four 1024-thread blocks per head, scores held in registers, one launch; the cut from a
+//   T_max <= kSmallMax : one to four blocks per head, scores held in registers, one launch; the cut from a
 //                        histogram over equal score bins and a count of ranks in the cut's bin.
 //   larger             : several blocks per head.  Three histogram passes (11 + 11 + 10 bits, global
 //                        integer atomics) find the cut key; a count pass and an emit pass produce
@@ -18,7 +18,6 @@
 namespace quoka {
 
 constexpr int kSmallMax = 32768;   // beyond this one compute unit is slower than the multi-block path
-constexpr int kSmallThreads = 1024;
 constexpr int kLgThreads = 256;
 constexpr int kLgTile = 2048;          // scores per block in the multi-block path
 constexpr int kBins = 2048;            // bins per histogram pass (11 bits; last pass uses 1024)
@@ -34,102 +33,128 @@ __device__ __forceinline__ uint32_t radix_bins(int pass) { return pass == 2 ? 10
 // head lie close together, and a lane's atomic on an occupied bin waits for the others.)  Where more keys share the
 // bin than LDS has room for, or the scores admit no such bins, the block-wide radix select decides.
 // The ordered compaction needs no scan over threads: per register, one wave ballot (two where only some of the keys
-// equal to the cut are taken) gives every lane the number of earlier taken positions of its wave, and the 16 wave totals
-// are combined through LDS.
+// equal to the cut are taken) gives every lane the number of earlier taken positions of its wave; how many earlier waves
+// take follows from their counts above the cut's bin and from the positions in the list of that bin's keys.
 //
-// What bounds it: one compute unit's instruction rate (five passes over the keys) and a chain of six barriers.  So
-// from 16 keys per thread on, several blocks take a head: all of them find the cut, each emits its share of the waves'
-// ranges (two blocks: 16, four: 32 keys per thread).
-// Measured (us, radix select on key bits and one block a head -> now): 8 heads of 8192 scores 7.9 -> 6.0, 8 of 32768
-// 20.4 -> 13.5, 12 of up to 19999 19.0 -> 12.1.
+// What bounds it: one compute unit's instruction rate (four passes over the keys, and 16 waves that each do what is done per
+// wave: letting every wave scan the histogram for itself to save two barriers took 1 - 2 us more).  So from 8 keys per
+// thread on, several blocks take a head: all of them find the cut, each emits its share of the waves' ranges.
+// Measured (us, radix select on key bits and one block a head -> histogram -> now: wave reductions on integer images, bins kept,
+// counts in the pass that lists the candidates): 8 heads of 8192 scores 7.9 -> 6.4 -> 6.1, 8 of 32768 20.4 -> 13.2 -> 12.0, of
+// 12000 8.1 -> 7.0.
 constexpr int kCutBins = 2048;
-constexpr int kCutKeys = 1024;
+constexpr int kCutKeys = 256;          // candidates a block ranks; more are radix-selected
+template <int NT>
 struct CutLds {
   uint32_t hist[kCutBins];
   float key[kCutKeys];
-  uint32_t wsum[kSmallThreads / 64 + 1];
-  float wmin[kSmallThreads / 64], wmax[kSmallThreads / 64];
+  int pos[kCutKeys];
+  uint32_t wmin[NT / 64], wmax[NT / 64], wsum[NT / 64];
+  uint32_t above[NT / 64];             // a wave's scores in the bins above the cut's
   uint32_t n, bin, need, need_eq;
   float tau;
 };
 
-template <int IPT, int NB>
-__global__ __launch_bounds__(kSmallThreads) void topk_small(Dims dm, const float* __restrict__ scores,
-                                                           const int32_t* __restrict__ kv_lens,
-                                                           const int32_t* __restrict__ budgets,
-                                                           int32_t* __restrict__ k_idx, int32_t* __restrict__ k_cnt) {
-  constexpr int NW = kSmallThreads / 64;
-  constexpr int BPT = kCutBins / kSmallThreads;   // bins per thread
+// Inverse of okey.
+__device__ __forceinline__ float okey_value(uint32_t k) {
+  return __uint_as_float((k & 0x80000000u) ? k & 0x7FFFFFFFu : ~k);
+}
+
+template <int NT, int IPT, int NB>
+__global__ __launch_bounds__(NT) void topk_small(Dims dm, const float* __restrict__ scores,
+                                                const int32_t* __restrict__ kv_lens,
+                                                const int32_t* __restrict__ budgets,
+                                                int32_t* __restrict__ k_idx, int32_t* __restrict__ k_cnt) {
+  constexpr int NW = NT / 64;
+  constexpr int BPT = kCutBins / NT;   // bins per thread
+  constexpr bool kKeepBins = IPT <= 16;
   __shared__ RadixSelectLds rs;
-  __shared__ __align__(16) CutLds cl;
+  __shared__ __align__(16) CutLds<NT> cl;
   __shared__ uint32_t wgt[NW], weq[NW];
   const int kv = blockIdx.x, b = blockIdx.y;
-  const int tid = threadIdx.x, lane = tid & 63, w = tid >> 6;
+  const int tid = threadIdx.x, lane = tid & 63, w = __builtin_amdgcn_readfirstlane(tid >> 6);
   const float* sc = scores + (size_t)(b * dm.n_kv + kv) * dm.T_max;
-  const int lo = w * 64 * IPT + lane;   // position of register 0; register j is 64*j further
+  const int w_lo = w * 64 * IPT, lo = w_lo + lane;   // positions of the wave, of register 0; register j is 64*j further
   // The scores are requested before the cache length is known (the row has T_max entries; those past the length
   // are discarded below), so the two fetches overlap instead of queueing behind each other.
   uint32_t rb[IPT];   // the scores' bits (the radix select borrows the registers for key images)
   auto val = [&](int j) __attribute__((always_inline)) { return __uint_as_float(rb[j]); };
 #pragma unroll
-  for (int j = 0; j < IPT; ++j) rb[j] = lo + 64 * j < dm.T_cap ? __float_as_uint(sc[lo + 64 * j]) : 0u;
+  for (int j = 0; j < IPT; ++j) rb[j] = 0u;
+  if (w_lo < dm.T_cap) {   // (wave-uniform)
+#pragma unroll
+    for (int j = 0; j < IPT; ++j) rb[j] = __float_as_uint(sc[min(lo + 64 * j, dm.T_cap - 1)]);
+  }
   const int T = max(0, min(kv_lens[b * dm.ls], dm.T_cap));
   const int B = max(0, min(min(budgets[b * dm.ls], T), dm.B_max));
   int32_t* out = k_idx + (size_t)(b * dm.n_kv + kv) * dm.B_max;
   if (tid == 0 && blockIdx.z == 0) k_cnt[b * dm.n_kv + kv] = B;
   if (B == 0) return;
   if (B >= T) {
-    for (int i = blockIdx.z * kSmallThreads + tid; i < T; i += NB * kSmallThreads) out[i] = i;
+    for (int i = blockIdx.z * NT + tid; i < T; i += NB * NT) out[i] = i;
     return;
   }
 #pragma unroll
-  for (int i = 0; i < BPT; ++i) cl.hist[i * kSmallThreads + tid] = 0u;
+  for (int i = 0; i < BPT; ++i) cl.hist[i * NT + tid] = 0u;
   if (tid == 0) cl.n = 0u;
   // positions past the length become NaN: minima and maxima pass over them and no comparison holds for them
+  const bool full = w_lo + 64 * IPT <= T;   // (wave-uniform) no position of this wave is past the length
   float vmin = INFINITY, vmax = -INFINITY;
-  unsigned long long nan = 0;   // lanes with a NaN among their scores proper
+  bool nan = false;   // among the scores proper
+  if (full) {
 #pragma unroll
-  for (int j = 0; j < IPT; ++j) {
-    const bool past = lo + 64 * j >= T;
-    nan |= __builtin_amdgcn_ballot_w64(!past && val(j) != val(j));
-    if (past) rb[j] = 0x7FC00000u;
-    vmin = fminf(vmin, val(j));
-    vmax = fmaxf(vmax, val(j));
+    for (int j = 0; j < IPT; ++j) {
+      nan |= val(j) != val(j);
+      vmin = fminf(vmin, val(j));
+      vmax = fmaxf(vmax, val(j));
+    }
+  } else {
+#pragma unroll
+    for (int j = 0; j < IPT; ++j) {
+      const bool past = lo + 64 * j >= T;
+      nan |= !past && val(j) != val(j);
+      if (past) rb[j] = 0x7FC00000u;
+      vmin = fminf(vmin, val(j));
+      vmax = fmaxf(vmax, val(j));
+    }
   }
-  vmin = -wave64_max(-vmin);
-  vmax = nan == 0 ? wave64_max(vmax) : INFINITY;   // (no bins then)
-  if (lane == 0) {
-    cl.wmin[w] = vmin;
-    cl.wmax[w] = vmax;
+  {   // (as order-preserving images, whose reductions take one instruction a step; a NaN has the largest: no bins then)
+    const uint32_t kmin = wave_min_u32(okey(vmin)), kmax = wave_max_u32(nan ? 0xFFFFFFFFu : okey(vmax));
+    if (lane == 0) {
+      cl.wmin[w] = kmin;
+      cl.wmax[w] = kmax;
+    }
   }
   __syncthreads();
-  vmin = -wave64_max(lane < NW ? -cl.wmin[lane] : -INFINITY);
-  vmax = wave64_max(lane < NW ? cl.wmax[lane] : -INFINITY);
+  vmin = okey_value(row16_min_u32(cl.wmin[lane % NW]));
+  vmax = okey_value(row16_max_u32(cl.wmax[lane % NW]));
   // monotone in v (a rounded product and a truncation of non-negative values), the largest score lands in the last bin
   const float per = ((float)kCutBins - 0.5f) / (vmax - vmin);
   const bool binned = per > 0.f && per < 1e30f;   // false for equal or infinite extremes, and where a score is NaN
   auto bin_of = [&](float v) __attribute__((always_inline)) { return min((int)((v - vmin) * per), kCutBins - 1); };
-  const bool full = (w + 1) * 64 * IPT <= T;   // (wave-uniform) no position of this wave is past the length
   float tau = 0.f;
   uint32_t need_eq = 0u, n_in = kCutKeys + 1, need = (uint32_t)B;
   int cut_bin = 0;
   if (binned) {   // block-uniform
-    if (full) {
+    int bins[kKeepBins ? IPT : 1];   // (more of them would not fit the registers: they are worked out again)
 #pragma unroll
-      for (int j = 0; j < IPT; ++j) atomicAdd(&cl.hist[bin_of(val(j))], 1u);
-    } else {
-#pragma unroll
-      for (int j = 0; j < IPT; ++j)
-        if (val(j) >= vmin) atomicAdd(&cl.hist[bin_of(val(j))], 1u);   // (not for a NaN)
+    for (int j = 0; j < IPT; ++j) {
+      const int bin = bin_of(val(j));
+      if constexpr (kKeepBins) bins[j] = full || val(j) >= vmin ? bin : -1;
+      if (full || val(j) >= vmin) atomicAdd(&cl.hist[bin], 1u);   // (not for a NaN)
     }
     __syncthreads();
-    uint32_t hv[BPT], mine = 0, tot;   // thread 0 has the highest bins
+    uint32_t hv[BPT], mine = 0;   // thread 0 has the highest bins
 #pragma unroll
     for (int i = 0; i < BPT; ++i) {
       hv[i] = cl.hist[kCutBins - 1 - (tid * BPT + i)];
       mine += hv[i];
     }
-    uint32_t above = block_excl_scan<kSmallThreads>(mine, cl.wsum, &tot);
+    const uint32_t upto = wave_incl_scan_u32(mine);
+    if (lane == 63) cl.wsum[w] = upto;
+    __syncthreads();
+    const uint32_t earlier = lane % 16 < NW && lane % 16 < w ? cl.wsum[lane % 16] : 0u;
+    uint32_t above = row16_sum_u32(earlier) + upto - mine;
     if (above < need && need <= above + mine) {   // exactly one thread (the histogram holds T > B keys)
 #pragma unroll
       for (int i = 0; i < BPT; ++i) {
@@ -143,33 +168,63 @@ __global__ __launch_bounds__(kSmallThreads) void topk_small(Dims dm, const float
     __syncthreads();
     cut_bin = (int)cl.bin;
     need = cl.need;
-    asm volatile("" : "+v"(vmin));   // (the bins are worked out again: kept, they would need IPT more registers)
+    if constexpr (!kKeepBins) asm volatile("" : "+v"(vmin));
+    uint32_t n_above = 0;
 #pragma unroll
     for (int j = 0; j < IPT; ++j) {
-      if (bin_of(val(j)) == cut_bin && val(j) >= vmin) {   // (false for a NaN)
+      int bin;
+      if constexpr (kKeepBins) {
+        bin = bins[j];
+      } else {
+        bin = full || val(j) >= vmin ? bin_of(val(j)) : -1;
+      }
+      n_above += bin > cut_bin ? 1u : 0u;
+      if (bin == cut_bin) {
         const uint32_t slot = atomicAdd(&cl.n, 1u);
-        if (slot < (uint32_t)kCutKeys) cl.key[slot] = val(j);
+        if (slot < (uint32_t)kCutKeys) {
+          cl.key[slot] = val(j);
+          cl.pos[slot] = lo + 64 * j;
+        }
       }
     }
+    n_above = wave_incl_scan_u32(n_above);
+    if (lane == 63) cl.above[w] = n_above;
     __syncthreads();
     n_in = cl.n;
   }
+  uint32_t n_gt, n_eq, all_eq;     // taken candidates at earlier positions, above the cut / equal to it; all that are equal to it
   if (n_in <= (uint32_t)kCutKeys) {   // block-uniform
-    if (tid < (int)n_in) {
-      const float k = cl.key[tid];
-      uint32_t gt = 0, ge = 0;
-      for (uint32_t j = 0; j < n_in; ++j) {
-        gt += cl.key[j] > k ? 1u : 0u;
-        ge += cl.key[j] >= k ? 1u : 0u;
-      }
-      if (gt < need && need <= ge) {   // (equal keys all write the same)
-        cl.tau = k;
-        cl.need_eq = need - gt;
-      }
+    // the cut: `need` of the bin's keys are taken, the largest.  P neighbouring lanes rank one key.
+    int cap = NT / 16;
+    while (cap < (int)n_in) cap <<= 1;
+    const int P = NT / cap;   // 16 .. 2
+    const int e = tid / P, part = tid % P;
+    const float k = cl.key[min(e, (int)n_in - 1)];
+    uint32_t cnt = 0;   // keys greater (low half), greater or equal (high half)
+    for (int j = part; j < (int)n_in; j += P) {
+      const float o = cl.key[j];
+      cnt += (o > k ? 1u : 0u) + (o >= k ? 0x10000u : 0u);
+    }
+    for (int o = 1; o < P; o <<= 1) cnt += (uint32_t)__shfl_xor((int)cnt, o, kWave);
+    if (e < (int)n_in && (cnt & 0xFFFFu) < need && need <= (cnt >> 16)) {   // (equal keys all write the same)
+      cl.tau = k;
+      cl.need_eq = need - (cnt & 0xFFFFu);
     }
     __syncthreads();
+    if (NB > 1 && w / (NW / NB) != (int)blockIdx.z) return;   // (no barrier follows) another block emits this wave's range
     tau = cl.tau;
     need_eq = cl.need_eq;
+    uint32_t gt = lane < w ? cl.above[min(lane, NW - 1)] : 0u, eq = 0;
+    for (int i = lane; i < (int)n_in; i += kWave) {
+      const float k = cl.key[i];
+      const bool earlier = cl.pos[i] < w_lo;
+      gt += earlier && k > tau ? 1u : 0u;
+      eq += (earlier && k == tau ? 1u : 0u) + (k == tau ? 0x10000u : 0u);   // (at most kCutKeys each)
+    }
+    n_gt = (uint32_t)__builtin_amdgcn_readlane((int)wave_incl_scan_u32(gt), 63);
+    eq = (uint32_t)__builtin_amdgcn_readlane((int)wave_incl_scan_u32(eq), 63);
+    n_eq = eq & 0xFFFFu;
+    all_eq = eq >> 16;
   } else {   // descending: the `need` largest of the bin's (or all) keys
     uint32_t in_bin = 0u, tau_key;
 #pragma unroll
@@ -183,14 +238,11 @@ __global__ __launch_bounds__(kSmallThreads) void topk_small(Dims dm, const float
       }
       rb[j] = okey(val(j) + 0.0f);   // (one zero)
     }
-    block_radix_select<IPT, true>(rb, in_bin, need, rs, &tau_key, &need_eq);
-    auto back = [](uint32_t k) { return (k & 0x80000000u) ? k & 0x7FFFFFFFu : ~k; };   // inverse of okey
-    tau = __uint_as_float(back(tau_key));
+    block_radix_select<IPT, true, NT>(rb, in_bin, need, rs, &tau_key, &need_eq);
+    tau = okey_value(tau_key);
 #pragma unroll
-    for (int j = 0; j < IPT; ++j) rb[j] = back(rb[j]);
-  }
-  // wave totals of scores above the cut and equal to it
-  {
+    for (int j = 0; j < IPT; ++j) rb[j] = __float_as_uint(okey_value(rb[j]));
+    // wave totals of scores above the cut and equal to it
     uint32_t c_gt = 0, c_eq = 0;
 #pragma unroll
     for (int j = 0; j < IPT; ++j) {
@@ -202,16 +254,16 @@ __global__ __launch_bounds__(kSmallThreads) void topk_small(Dims dm, const float
       wgt[w] = c_gt;
       weq[w] = c_eq;
     }
+    __syncthreads();
+    if (NB > 1 && w / (NW / NB) != (int)blockIdx.z) return;   // (as above)
+    all_eq = wave_incl_scan_u32(lane < NW ? weq[lane] : 0u);
+    n_gt = wave_incl_scan_u32(lane < w ? wgt[lane] : 0u);
+    n_eq = wave_incl_scan_u32(lane < w ? weq[lane] : 0u);
+    all_eq = (uint32_t)__builtin_amdgcn_readlane((int)all_eq, 63);
+    n_gt = (uint32_t)__builtin_amdgcn_readlane((int)n_gt, 63);
+    n_eq = (uint32_t)__builtin_amdgcn_readlane((int)n_eq, 63);
   }
-  __syncthreads();
-  if (NB > 1 && w / (NW / NB) != (int)blockIdx.z) return;   // (no barrier follows) another block emits this wave's range
-  // taken candidates at earlier positions (earlier waves): greater than the cut / equal to it
-  const uint32_t all_eq = wave_incl_scan_u32(lane < NW ? weq[lane] : 0u);
-  uint32_t n_gt = wave_incl_scan_u32(lane < w ? wgt[lane] : 0u);
-  uint32_t n_eq = wave_incl_scan_u32(lane < w ? weq[lane] : 0u);
-  n_gt = (uint32_t)__builtin_amdgcn_readlane((int)n_gt, 63);
-  n_eq = (uint32_t)__builtin_amdgcn_readlane((int)n_eq, 63);
-  const bool take_all_eq = (uint32_t)__builtin_amdgcn_readlane((int)all_eq, 63) == need_eq;
+  const bool take_all_eq = all_eq == need_eq;
   const unsigned long long below = (1ull << lane) - 1ull;
   // (an opaque copy of the cut: otherwise the comparison masks of the counting loop above are kept alive for this
   // loop, 2 x IPT scalar register pairs that spill)
@@ -475,31 +527,36 @@ bool topk_uses_ws(const Dims& dm) { return dm.T_cap > kSmallMax; }
 hipError_t launch_topk_keys(const Dims& dm, const float* scores, const int32_t* kv_lens, const int32_t* budgets,
                             int32_t* k_idx, int32_t* k_cnt, uint32_t* ws, hipStream_t st, bool ws_is_zero) {
   if (!topk_uses_ws(dm)) {
-    const dim3 block(kSmallThreads);
-    const int ipt = (dm.T_cap + kSmallThreads - 1) / kSmallThreads;
-    auto launch = [&](auto kernel, int blocks_per_head) {
-      hipLaunchKernelGGL(kernel, dim3(dm.n_kv, dm.b, blocks_per_head), block, 0, st, dm, scores, kv_lens, budgets, k_idx, k_cnt);
+    auto launch = [&](auto kernel, int threads, int blocks_per_head) {
+      hipLaunchKernelGGL(kernel, dim3(dm.n_kv, dm.b, blocks_per_head), dim3(threads), 0, st, dm, scores, kv_lens, budgets, k_idx,
+                         k_cnt);
     };
-    // (The time goes with the keys a thread holds, so above 16 the variants lie close together: 12 heads of up to 19999
-    // scores 12.3 -> 9.3 us, 8 of 24000 12.4 -> 10.3 against 32 keys a thread.  12 instead of 16 gave 0.2 us only.)
-    if (ipt <= 1) {
-      launch(topk_small<1, 1>, 1);
-    } else if (ipt <= 2) {
-      launch(topk_small<2, 1>, 1);
-    } else if (ipt <= 4) {
-      launch(topk_small<4, 1>, 1);
-    } else if (ipt <= 8) {
-      launch(topk_small<8, 1>, 1);
-    } else if (ipt <= 16) {
-      launch(topk_small<16, 2>, 2);
-    } else if (ipt <= 20) {
-      launch(topk_small<20, 4>, 4);
-    } else if (ipt <= 24) {
-      launch(topk_small<24, 4>, 4);
-    } else if (ipt <= 28) {
-      launch(topk_small<28, 4>, 4);
+    // (The time goes with the keys a thread holds, so above 8 the variants lie close together: 8 heads of 12000 scores 7.6 us with
+    // 16 keys a thread, 7.0 with 12; 8 of 24000 11.0 with 32, 9.9 with 24.  Half the threads for short heads: 8 of 512 4.5 -> 4.2,
+    // of 2048 4.9 -> 4.7; longer ones want the other half back, 8 of 8192 6.0 against 6.6.)
+    const int T = dm.T_cap;
+    if (T <= 512) {
+      launch(topk_small<512, 1, 1>, 512, 1);
+    } else if (T <= 1024) {
+      launch(topk_small<512, 2, 1>, 512, 1);
+    } else if (T <= 2048) {
+      launch(topk_small<512, 4, 1>, 512, 1);
+    } else if (T <= 4096) {
+      launch(topk_small<1024, 4, 1>, 1024, 1);
+    } else if (T <= 8192) {
+      launch(topk_small<1024, 8, 1>, 1024, 1);
+    } else if (T <= 12288) {
+      launch(topk_small<1024, 12, 2>, 1024, 2);
+    } else if (T <= 16384) {
+      launch(topk_small<1024, 16, 2>, 1024, 2);
+    } else if (T <= 20480) {
+      launch(topk_small<1024, 20, 4>, 1024, 4);
+    } else if (T <= 24576) {
+      launch(topk_small<1024, 24, 4>, 1024, 4);
+    } else if (T <= 28672) {
+      launch(topk_small<1024, 28, 4>, 1024, 4);
     } else {
-      launch(topk_small<32, 4>, 4);
+      launch(topk_small<1024, 32, 4>, 1024, 4);
     }
     return hipGetLastError();
   }

@@ -275,3 +275,28 @@ def test_top_b_ties_of_signed_zeros_and_nan_on_both_sides_of_the_register_path(T
         ranked = np.where(np.isnan(s), np.copysign(np.float32(np.inf), s), s)
         want = np.stack([np.sort(np.argsort(-r, kind="stable")[:B]) for r in ranked])
         assert np.array_equal(gen.from_torch(buf.k_idx)[0][:, :B], want)
+
+
+# threads and keys a thread: the sizes on either side of every line; scores that fill one bin with few, up to 256 (ranked) or more
+# (radix-selected) keys
+@pytest.mark.parametrize("T", [2, 63, 511, 512, 513, 1024, 1025, 2048, 2049, 4096, 4097, 8192, 8193, 12288, 12289, 16384, 28672, 28673])
+@pytest.mark.parametrize("crowd", [0, 200, 256, 257])
+def test_top_b_threads_keys_and_crowded_bins(T, crowd):
+    if crowd >= T:
+        pytest.skip("fewer scores than that")
+    rng = np.random.default_rng(T + crowd)
+    s = rng.standard_normal((2, T)).astype(np.float32)
+    B = max(1, T // 3)
+    if crowd:   # `crowd` keys within a thousandth of a bin around the cut, a third of them equal
+        at = np.stack([rng.choice(T, size=crowd, replace=False) for _ in range(2)])
+        cut = np.sort(s, axis=1)[:, T - B][:, None]
+        near = (cut + rng.choice(np.array([0, 0, 1, 2, 3, 4], dtype=np.float32), size=at.shape) * np.float32(1e-7)).astype(np.float32)
+        np.put_along_axis(s, at, near, axis=1)
+    w = gen.make_custom(dtype="bf16", n_q=2, n_kv=2, d=64, chunk=40, n_retain=16, kv_lens=[T], budgets=[B], batch=1, seed=3)
+    buf = _buffers(w)
+    buf.scores.copy_(torch.from_numpy(s)[None])
+    buf.k_idx.fill_(-1)
+    buf.topk_keys()
+    torch.cuda.synchronize()
+    want = np.stack([np.sort(np.argsort(-r, kind="stable")[:B]) for r in s])
+    assert np.array_equal(gen.from_torch(buf.k_idx)[0][:, :B], want)
