@@ -46,29 +46,30 @@ __global__ void sel_zero(uint32_t* __restrict__ p, size_t n) {
 }
 
 // Whole block of kSelThreads: thread t's run of the head's histogram (thread 0 has the highest bins) ...
-constexpr uint32_t kSelPer = kSelBins / kSelThreads;
 constexpr int kBandCap = 2 * kSelTile;   // band keys a block lists before it scores them
-__device__ __forceinline__ void load_hist_run(const uint32_t* __restrict__ hist, uint32_t (&hv)[kSelPer]) {
-  const uint32_t top = kSelBins - threadIdx.x * kSelPer;   // exclusive upper bin of the run
+template <uint32_t PER>
+__device__ __forceinline__ void load_hist_run(const uint32_t* __restrict__ hist, uint32_t (&hv)[PER]) {
+  const uint32_t top = PER * (kSelThreads - threadIdx.x);   // exclusive upper bin of the run
 #pragma unroll
-  for (uint32_t i = 0; i < kSelPer; i += 4) {
-    const u32x4 v = *reinterpret_cast<const u32x4*>(hist + top - kSelPer + i);
+  for (uint32_t i = 0; i < PER; i += 4) {
+    const u32x4 v = *reinterpret_cast<const u32x4*>(hist + top - PER + i);
     hv[i] = v[0]; hv[i + 1] = v[1]; hv[i + 2] = v[2]; hv[i + 3] = v[3];
   }
 }
 // ... and the bin of the cut: scanning from the top, where the running count reaches B (the histogram holds T > B keys).
-__device__ __forceinline__ int find_cut_bin(const uint32_t (&hv)[kSelPer], uint32_t B, uint32_t* sh, uint32_t* bin) {
-  const uint32_t top = kSelBins - threadIdx.x * kSelPer;
+template <uint32_t PER>
+__device__ __forceinline__ int find_cut_bin(const uint32_t (&hv)[PER], uint32_t B, uint32_t* sh, uint32_t* bin) {
+  const uint32_t top = PER * (kSelThreads - threadIdx.x);
   uint32_t mine = 0;
 #pragma unroll
-  for (uint32_t i = 0; i < kSelPer; ++i) mine += hv[i];
+  for (uint32_t i = 0; i < PER; ++i) mine += hv[i];
   uint32_t tot;
   const uint32_t above = block_excl_scan<kSelThreads>(mine, sh, &tot);
   if (above < B && B <= above + mine) {   // exactly one thread
     uint32_t rem = B - above;
     int found = -1;
 #pragma unroll
-    for (int j = (int)kSelPer - 1; j >= 0; --j) {   // from this thread's highest bin down
+    for (int j = (int)PER - 1; j >= 0; --j) {   // from this thread's highest bin down
       if (found < 0) {
         if (rem <= hv[j]) {
           found = j;
@@ -77,7 +78,7 @@ __device__ __forceinline__ int find_cut_bin(const uint32_t (&hv)[kSelPer], uint3
         }
       }
     }
-    *bin = top - kSelPer + (uint32_t)max(found, 0);
+    *bin = top - PER + (uint32_t)max(found, 0);
   }
   __syncthreads();
   return (int)*bin;
@@ -122,7 +123,7 @@ __global__ __launch_bounds__(kSelThreads) void sel_band_rescore(Dims dm, const f
     for (int i = 0; i < kSelIPT; ++i) p[i] = c.sc[min(t0 + tid + kSelThreads * i, dm.T_max - 1)];   // coalesced rows
   };
   load_p(tile_first * kSelTile);
-  uint32_t hv[kSelPer];
+  uint32_t hv[kSelBins / kSelThreads];
   load_hist_run(c.w.hist, hv);
   const float d2 = __uint_as_float(c.w.meta[kMetaEps2]);
   if (c.B == 0 || c.B >= c.T || tile_first * kSelTile >= c.T) return;   // block-uniform
@@ -231,10 +232,97 @@ __global__ __launch_bounds__(kSelThreads) void sel_band_rescore(Dims dm, const f
 // One block per head: the exact cut among the band candidates, then the output offset of every tile.
 // Radix select (descending) over keys that are read again from memory in every pass (the candidate list of a head is
 // a few tens of KiB and stays in cache; there is no bound on its length, so registers cannot hold it in general).
+// The cut among n candidates held in registers (thread t's k[i] is number t + NT*i): the `need`-th largest key, and how many
+// candidates equal to it are among the `need` largest.  A histogram over 256 equal parts of the keys' range, then the ranks of the
+// few keys in the cut's part: three barriers whatever n is, where radix passes need one each for every 8 bits.  False (block-
+// uniform) where more than 64 keys share that part.  L.hist and L.n are zero, with a barrier since.
+struct __align__(16) CutListLds {
+  uint32_t hist[256];
+  uint32_t list[kWave];
+  uint32_t wmin[16], wmax[16];
+  uint32_t n;
+};
+static_assert(alignof(CutListLds) >= sizeof(u32x4), "the histogram is read 16 bytes at a time");
+
+template <int NT, int R>
+__device__ __forceinline__ bool cut_among(const uint32_t (&k)[R], uint32_t n, uint32_t need, CutListLds& L, uint32_t* tau,
+                                          uint32_t* need_eq) {
+  const int tid = threadIdx.x, lane = tid & 63, w = tid >> 6;
+  uint32_t n_list = n;
+  if (n > (uint32_t)kWave) {   // block-uniform
+    uint32_t kmin = 0xFFFFFFFFu, kmax = 0u;
+#pragma unroll
+    for (int i = 0; i < R; ++i) {
+      const bool in = (uint32_t)(tid + NT * i) < n;
+      kmin = in ? min(kmin, k[i]) : kmin;
+      kmax = in ? max(kmax, k[i]) : kmax;
+    }
+    kmin = wave_min_u32(kmin);
+    kmax = wave_max_u32(kmax);
+    if (lane == 0) {
+      L.wmin[w] = kmin;
+      L.wmax[w] = kmax;
+    }
+    __syncthreads();
+    kmin = row16_min_u32(L.wmin[lane % (NT / 64)]);
+    kmax = row16_max_u32(L.wmax[lane % (NT / 64)]);
+    const uint32_t range = kmax - kmin;
+    const int shift = range < 256u ? 0 : 24 - __clz(range);   // range >> shift is 255 at most
+#pragma unroll
+    for (int i = 0; i < R; ++i)
+      if ((uint32_t)(tid + NT * i) < n) atomicAdd(&L.hist[(k[i] - kmin) >> shift], 1u);
+    __syncthreads();
+    // every wave locates the cut's part for itself; scan position o = 4 * lane + i is part 255 - o
+    const u32x4 raw = *reinterpret_cast<const u32x4*>(L.hist + 4 * (63 - lane));
+    const uint32_t cc[4] = {raw[3], raw[2], raw[1], raw[0]};
+    const uint32_t sum = cc[0] + cc[1] + cc[2] + cc[3];
+    const uint32_t inc = wave_incl_scan_u32(sum);
+    uint32_t rem = need - (inc - sum);
+    const bool hit = inc - sum < need && need <= inc;   // exactly one lane (need <= n)
+    int i0 = 0;
+#pragma unroll
+    for (; i0 < 3; ++i0) {
+      if (rem <= cc[i0]) break;
+      rem -= cc[i0];
+    }
+    const unsigned long long bal = __builtin_amdgcn_ballot_w64(hit);
+    const int src = bal ? (int)__builtin_ctzll(bal) : 0;
+    const uint32_t part = (uint32_t)__builtin_amdgcn_readlane(255 - (4 * lane + i0), src);
+    need = (uint32_t)__builtin_amdgcn_readlane((int)rem, src);
+#pragma unroll
+    for (int i = 0; i < R; ++i) {
+      if ((uint32_t)(tid + NT * i) < n && (k[i] - kmin) >> shift == part) {
+        const uint32_t slot = atomicAdd(&L.n, 1u);
+        if (slot < (uint32_t)kWave) L.list[slot] = k[i];
+      }
+    }
+    __syncthreads();
+    n_list = L.n;
+    if (n_list > (uint32_t)kWave) return false;
+  } else {
+    if (tid < (int)n) L.list[tid] = k[0];
+    __syncthreads();
+  }
+  const uint32_t mine = L.list[min(lane, (int)n_list - 1)];
+  uint32_t gt = 0, ge = 0;
+  for (uint32_t j = 0; j < n_list; ++j) {
+    const uint32_t o = L.list[j];
+    gt += o > mine ? 1u : 0u;
+    ge += o >= mine ? 1u : 0u;
+  }
+  const unsigned long long bal = __builtin_amdgcn_ballot_w64(gt < need && need <= ge);   // (equal keys all say the same)
+  const int src = bal ? (int)__builtin_ctzll(bal) : 0;
+  *tau = (uint32_t)__builtin_amdgcn_readlane((int)mine, src);
+  *need_eq = need - (uint32_t)__builtin_amdgcn_readlane((int)gt, src);
+  return true;
+}
+
 struct HeadSelectLds {
   RadixSelectLds rs;
+  CutListLds cut;
   uint32_t wsum[kSelHeadThreads / 64 + 1];
 };
+constexpr int kHeadCands = 4;   // candidates a thread of the head's block holds in registers
 
 template <int NT>
 __device__ __forceinline__ void stream_radix_select_desc(const uint32_t* __restrict__ keys, uint32_t n, uint32_t need,
@@ -317,25 +405,44 @@ __global__ __launch_bounds__(kSelHeadThreads) void sel_band_select(Dims dm, floa
   if (c.B == 0 || c.B >= c.T) return;   // block-uniform
   const int tid = threadIdx.x;
   const int nt = (c.T + kSelTile - 1) / kSelTile;   // tiles of this head that the per-tile kernels worked on
-  // keys that are certainly selected: everything in the bins above the band
+  // requested together: the histogram, the number of candidates, and the first of these (the arrays hold T_max > 32768 entries)
   const u32x4 hv = *reinterpret_cast<const u32x4*>(c.w.hist + 4 * tid);
   const uint32_t bin_hi = c.w.meta[kMetaBinHi];
   const uint32_t n_c = c.w.meta[kMetaCand];
+  uint32_t ck[kHeadCands], cp[kHeadCands];
+#pragma unroll
+  for (int i = 0; i < kHeadCands; ++i) {
+    ck[i] = c.w.cand_key[tid + kSelHeadThreads * i];
+    cp[i] = c.w.cand_pos[tid + kSelHeadThreads * i];
+  }
+  for (int i = tid; i < nt; i += kSelHeadThreads) cnt[i] = 0u;
+  if (tid < 256) L.cut.hist[tid] = 0u;
+  if (tid == 0) L.cut.n = 0u;
+  // keys that are certainly selected: everything in the bins above the band
   uint32_t n_in = 0;
 #pragma unroll
   for (int i = 0; i < 4; ++i) n_in += (uint32_t)(4 * tid + i) > bin_hi ? hv[i] : 0u;
-  uint32_t tot_in;
-  block_excl_scan<kSelHeadThreads>(n_in, L.wsum, &tot_in);
-  const uint32_t need = (uint32_t)c.B - tot_in;   // >= 1: fewer than B keys lie above the cut bin, let alone the band
-  for (int i = tid; i < nt; i += kSelHeadThreads) cnt[i] = 0u;
+  n_in = wave_incl_scan_u32(n_in);
+  if ((tid & 63) == 63) L.wsum[tid >> 6] = n_in;
   __syncthreads();
-  // (the candidates are read again from memory in every pass: holding them in registers, 16 per thread, was
-  // measured slower -- 13.5 against 11.2 us at 4000 candidates per head)
+  const uint32_t tot_in = row16_sum_u32(L.wsum[tid & 15]);
+  const uint32_t need = (uint32_t)c.B - tot_in;   // >= 1: fewer than B keys lie above the cut bin, let alone the band
   uint32_t tau, need_eq;
-  stream_radix_select_desc<kSelHeadThreads>(c.w.cand_key, n_c, need, L.rs, &tau, &need_eq);
-  for (uint32_t i = tid; i < n_c; i += kSelHeadThreads) {
-    const uint32_t k = c.w.cand_key[i];
-    if (k >= tau) atomicAdd(&cnt[c.w.cand_pos[i] / kSelTile], k > tau ? 0x10000u : 1u);
+  const bool held = n_c <= (uint32_t)(kSelHeadThreads * kHeadCands);   // block-uniform
+  // (radix select over memory, four passes of the candidates: 8 sequences x 8 heads of 4096 to 65536 positions 12.8 us, 8.5 so; 4 heads
+  // of 39853 7.8, 6.4 so)
+  if (!held || !cut_among<kSelHeadThreads, kHeadCands>(ck, n_c, need, L.cut, &tau, &need_eq))
+    stream_radix_select_desc<kSelHeadThreads>(c.w.cand_key, n_c, need, L.rs, &tau, &need_eq);
+  if (held) {
+#pragma unroll
+    for (int i = 0; i < kHeadCands; ++i)
+      if ((uint32_t)(tid + kSelHeadThreads * i) < n_c && ck[i] >= tau)
+        atomicAdd(&cnt[cp[i] / kSelTile], ck[i] > tau ? 0x10000u : 1u);
+  } else {
+    for (uint32_t i = tid; i < n_c; i += kSelHeadThreads) {
+      const uint32_t k = c.w.cand_key[i];
+      if (k >= tau) atomicAdd(&cnt[c.w.cand_pos[i] / kSelTile], k > tau ? 0x10000u : 1u);
+    }
   }
   __syncthreads();
   // Output offsets.  Thread t owns tiles t*tpt .. +tpt; first the number of cut-equal band keys before every tile
@@ -455,6 +562,7 @@ __global__ __launch_bounds__(kSelThreads) void sel_emit(Dims dm, float* __restri
 // 100003 23 -> 14 us (call 88 -> 80 us).
 static_assert(kPackMaxKeys / kSelTile <= 64, "one lane a tile");
 
+template <int BINS>
 __global__ __launch_bounds__(kSelThreads) void sel_classify(Dims dm, float* __restrict__ scores,
                                                            const int32_t* __restrict__ kv_lens,
                                                            const int32_t* __restrict__ budgets, uint32_t* __restrict__ ws) {
@@ -466,7 +574,7 @@ __global__ __launch_bounds__(kSelThreads) void sel_classify(Dims dm, float* __re
   float v[kSelIPT];   // (requested before the cache length is known)
 #pragma unroll
   for (int i = 0; i < kSelIPT; ++i) v[i] = c.sc[min(t0 + tid + kSelThreads * i, dm.T_max - 1)];
-  uint32_t hv[kSelPer];
+  uint32_t hv[BINS / kSelThreads];
   load_hist_run(c.w.hist, hv);
   if (c.B == 0 || c.B >= c.T || t0 >= c.T) return;   // block-uniform
   if (tid == 0) n_in = 0u;
@@ -475,7 +583,7 @@ __global__ __launch_bounds__(kSelThreads) void sel_classify(Dims dm, float* __re
 #pragma unroll
   for (int i = 0; i < kSelIPT; ++i) {
     const int t = t0 + tid + kSelThreads * i;
-    const int k = score_bin(v[i]);
+    const int k = coarse_bin<BINS>(v[i]);
     above += (uint32_t)__popcll(__builtin_amdgcn_ballot_w64(t < c.T && k > cut_bin));
     const bool cand = t < c.T && k == cut_bin;
     const unsigned long long m = __builtin_amdgcn_ballot_w64(cand);
@@ -497,25 +605,31 @@ __global__ __launch_bounds__(kSelThreads) void sel_classify(Dims dm, float* __re
   }
 }
 
-constexpr int kFinCands = 1024;   // candidates ranked by counting in LDS; more are radix-selected from memory
+constexpr int kFinCands = 4;   // candidates a thread holds in registers; more are radix-selected from memory
+template <int BINS>
 __global__ __launch_bounds__(kSelThreads) void sel_finish(Dims dm, float* __restrict__ scores,
                                                          const int32_t* __restrict__ kv_lens,
                                                          const int32_t* __restrict__ budgets, uint32_t* __restrict__ ws,
                                                          int32_t* __restrict__ k_idx, int32_t* __restrict__ k_cnt) {
   __shared__ RadixSelectLds rs;
-  __shared__ uint32_t key[kFinCands], pos[kFinCands];
-  __shared__ uint32_t cut[2], sums[4], wcnt[kSelWaves];
+  __shared__ CutListLds cl;
+  __shared__ uint32_t sums[4], wcnt[kSelWaves];
   const SelCtx c = sel_ctx(dm, scores, kv_lens, budgets, ws, blockIdx.y, blockIdx.z);
   const int t0 = blockIdx.x * kSelTile;
   // requested before the cache length and the number of candidates are known (the arrays hold T_max > 32768 entries)
-  const int tid = threadIdx.x, lane = tid & 63, w = __builtin_amdgcn_readfirstlane(tid >> 6);
+  const int tid = threadIdx.x, lane = tid & 63, w = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6);
   const int lo = t0 + w * 64 * kSelIPT + lane;
   float v[kSelIPT];
 #pragma unroll
   for (int j = 0; j < kSelIPT; ++j) v[j] = c.sc[min(lo + 64 * j, dm.T_max - 1)];
   const uint32_t n_c = c.w.meta[kMetaCand];
   const int cut_bin = (int)c.w.meta[kMetaBinHi];
-  const uint32_t key0 = c.w.cand_key[tid], pos0 = c.w.cand_pos[tid];
+  uint32_t ck[kFinCands], cp[kFinCands];
+#pragma unroll
+  for (int i = 0; i < kFinCands; ++i) {
+    ck[i] = c.w.cand_key[tid + kSelThreads * i];
+    cp[i] = c.w.cand_pos[tid + kSelThreads * i];
+  }
   uint32_t certain = c.w.tile_in[min(tid, sel_tiles(dm.T_max) - 1)];
   int32_t* out = k_idx + (size_t)c.head * dm.B_max;
   if (blockIdx.x == 0 && threadIdx.x == 0) k_cnt[c.head] = c.B;
@@ -525,18 +639,8 @@ __global__ __launch_bounds__(kSelThreads) void sel_finish(Dims dm, float* __rest
     for (int i = t0 + threadIdx.x; i < t1; i += kSelThreads) out[i] = i;
     return;
   }
-  const bool in_lds = n_c <= (uint32_t)kFinCands;
-  if (in_lds) {
-    if (tid < (int)n_c) {
-      key[tid] = key0;
-      pos[tid] = pos0;
-    }
-    for (uint32_t i = tid + kSelThreads; i < n_c; i += kSelThreads) {
-      key[i] = c.w.cand_key[i];
-      pos[i] = c.w.cand_pos[i];
-    }
-  }
-  if (tid == 0) sums[2] = sums[3] = 0u;
+  cl.hist[tid] = 0u;
+  if (tid == 0) cl.n = sums[2] = sums[3] = 0u;
   // certainly selected keys, in all tiles and in the earlier ones (the first wave has a lane for every tile)
   if (w == 0) {
     if (lane >= (c.T + kSelTile - 1) / kSelTile) certain = 0u;
@@ -547,32 +651,26 @@ __global__ __launch_bounds__(kSelThreads) void sel_finish(Dims dm, float* __rest
   __syncthreads();
   const uint32_t need = (uint32_t)c.B - sums[0];   // >= 1: fewer than B keys lie above the cut bin
   uint32_t tau, need_eq;
-  if (in_lds) {
-    for (uint32_t i = tid; i < n_c; i += kSelThreads) {
-      const uint32_t k = key[i];
-      uint32_t gt = 0, ge = 0;
-      for (uint32_t j = 0; j < n_c; ++j) {
-        gt += key[j] > k ? 1u : 0u;
-        ge += key[j] >= k ? 1u : 0u;
-      }
-      if (gt < need && need <= ge) {   // (equal keys all write the same)
-        cut[0] = k;
-        cut[1] = need - gt;
-      }
-    }
-    __syncthreads();
-    tau = cut[0];
-    need_eq = cut[1];
-  } else {
+  // (every candidate against every other in 256 threads: 4 heads of 124502, 2 queries, budget 17 % 18.0 us, 6.5 so; 64 heads of 4096 to
+  // 65536 14.3, 11.2 so)
+  const bool held = n_c <= (uint32_t)(kSelThreads * kFinCands);   // block-uniform
+  if (!held || !cut_among<kSelThreads, kFinCands>(ck, n_c, need, cl, &tau, &need_eq))
     stream_radix_select_desc<kSelThreads>(c.w.cand_key, n_c, need, rs, &tau, &need_eq);
-  }
   // candidates above the cut, and equal to it, in earlier tiles
   uint32_t gt = 0, eq0 = 0;
-  for (uint32_t i = tid; i < n_c; i += kSelThreads) {
-    const uint32_t k = in_lds ? key[i] : c.w.cand_key[i];
-    if (k >= tau && (in_lds ? pos[i] : c.w.cand_pos[i]) < (uint32_t)t0) {
-      gt += k > tau ? 1u : 0u;
-      eq0 += k == tau ? 1u : 0u;
+  if (held) {
+#pragma unroll
+    for (int i = 0; i < kFinCands; ++i) {
+      const bool earlier = (uint32_t)(tid + kSelThreads * i) < n_c && cp[i] < (uint32_t)t0;
+      gt += earlier && ck[i] > tau ? 1u : 0u;
+      eq0 += earlier && ck[i] == tau ? 1u : 0u;
+    }
+  } else {
+    for (uint32_t i = tid; i < n_c; i += kSelThreads) {
+      const uint32_t k = c.w.cand_key[i];
+      const bool earlier = c.w.cand_pos[i] < (uint32_t)t0;
+      gt += earlier && k > tau ? 1u : 0u;
+      eq0 += earlier && k == tau ? 1u : 0u;
     }
   }
   if (gt) atomicAdd(&sums[2], gt);
@@ -582,7 +680,7 @@ __global__ __launch_bounds__(kSelThreads) void sel_finish(Dims dm, float* __rest
   for (int j = 0; j < kSelIPT; ++j) {
     const bool in = lo + 64 * j < t1;
     const uint32_t k = max(okey(v[j]), 1u);
-    const int bin = score_bin(v[j]);
+    const int bin = coarse_bin<BINS>(v[j]);
     take |= (in && (bin > cut_bin || (bin == cut_bin && k > tau)) ? 1u : 0u) << j;
     eq |= (in && bin == cut_bin && k == tau ? 1u : 0u) << j;
   }
@@ -639,8 +737,8 @@ hipError_t launch_select_keys(const Dims& dm, const float* qbar, const void* k_c
   if (e != hipSuccess) return e;
   const dim3 grid(sel_tiles(dm.T_cap), dm.n_kv, dm.b);
   if (score_packs(dm)) {
-    hipLaunchKernelGGL(sel_classify, grid, dim3(kSelThreads), 0, st, dm, scores, kv_lens, budgets, ws);
-    hipLaunchKernelGGL(sel_finish, grid, dim3(kSelThreads), 0, st, dm, scores, kv_lens, budgets, ws, k_idx, k_cnt);
+    hipLaunchKernelGGL((sel_classify<kSelBins>), grid, dim3(kSelThreads), 0, st, dm, scores, kv_lens, budgets, ws);
+    hipLaunchKernelGGL((sel_finish<kSelBins>), grid, dim3(kSelThreads), 0, st, dm, scores, kv_lens, budgets, ws, k_idx, k_cnt);
     return hipGetLastError();
   }
   if (dm.d == 64) {

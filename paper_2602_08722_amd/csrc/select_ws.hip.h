@@ -20,6 +20,13 @@ __device__ __forceinline__ int score_bin(float p) {
   return min(max((int)floorf(x), 0), kSelBins - 1);
 }
 
+// The same in BINS (kSelBins or half of them) bins.
+template <int BINS>
+__device__ __forceinline__ int coarse_bin(float p) {
+  static_assert(BINS == kSelBins || 2 * BINS == kSelBins, "");
+  return score_bin(p) >> (BINS == kSelBins ? 0 : 1);
+}
+
 // Workspace of the stage.  The words that must be zero when the chain starts (histograms and candidate counters of
 // all heads) come first, in one contiguous run, so that an earlier launch can clear them as a side job.
 struct SelWs {

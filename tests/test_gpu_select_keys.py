@@ -225,3 +225,28 @@ def test_scoring_launch_forms_the_queries_of_a_few_tokens(case):
     for b in range(w.batch):
         T, n = w.kv_lens[b], int(cnt[b, 0])
         assert torch.equal(buf.scores[b, :, :T], sc[b, :, :T]) and torch.equal(buf.k_idx[b, :, :n], idx[b, :, :n])
+
+
+@pytest.mark.parametrize("crowd", [0, 40, 64, 300, 900, 1100, 3000])
+@pytest.mark.parametrize("n_q,chunk", [(4, 2), (4, 60)], ids=["one-pass", "two-pass"])
+def test_select_keys_with_many_candidates_near_the_cut(n_q, chunk, crowd):
+    """`crowd` keys differ from the one at the cut by a few bf16 steps of some elements, so that they share its bin, or its part of
+    a bin: more or fewer than a block holds in registers or ranks one by one.  The list is that of the scores themselves."""
+    pk = _pk()
+    T, B = 100000, 9000
+    w = gen.make_custom(dtype="bf16", n_q=n_q, n_kv=2, d=128, chunk=chunk, n_retain=32, kv_lens=[T], budgets=[B], seed=47)
+    rng = np.random.default_rng(6)
+    sc = O.key_scores(w.Q[0], O.select_queries(w.Q[0], w.n_retain), w.K[0], w.n_kv)
+    for kv in range(w.n_kv):
+        src = np.argsort(-sc[kv], kind="stable")[B - crowd // 3]
+        dst = rng.choice(T, size=crowd, replace=False)
+        rows = np.repeat(w.K[0, kv, src:src + 1], crowd, axis=0)
+        rows *= 1.0 + (rng.integers(-1, 2, size=rows.shape) * (rng.random(rows.shape) < 0.05)) * 2.0 ** -7
+        w.K[0, kv, dst] = rows
+    t = gen.to_torch(w, "cuda:0")     # (rounds the rows to bf16)
+    buf = _buffers(pk, w, t)
+    _, idx_s, cnt_s = _staged(buf)
+    exact = gen.from_torch(buf.scores)[0]
+    _, idx_f, cnt_f = _fused(buf)
+    assert torch.equal(cnt_f, cnt_s) and torch.equal(idx_f, idx_s)
+    assert np.array_equal(gen.from_torch(idx_f)[0], O.topk_keys(exact, B))
