@@ -174,7 +174,8 @@ quoka_status quoka_dense_attn(const quoka_shape* shape, const void* q, const voi
 
 /* The sparse stages back to back on one stream (Alg. 2, select-then-attend for one chunk): quoka_select_queries,
  * quoka_select_keys, quoka_sparse_attn.  Intermediates are returned to the caller: q_idx, qbar, k_idx, k_cnt as
- * above, scores as quoka_select_keys leaves them. */
+ * above, scores as quoka_select_keys leaves them, or, where that is the faster way to the same lists, as
+ * quoka_score_keys does (exact for every key). */
 quoka_status quoka_chunk_attn(const quoka_shape* shape, const void* q, const void* k_cache, const void* v_cache,
                               const int32_t* kv_lens, const int32_t* budgets, const void* k_chunk,
                               const void* v_chunk, int32_t* q_idx, float* qbar, float* scores, int32_t* k_idx,

@@ -353,9 +353,12 @@ static quoka_status select_keys_common(const Dims& dm, int dtype, const float* q
                                        const int32_t* kv_lens, const int32_t* budgets, float* scores, int32_t* k_idx,
                                        int32_t* k_cnt, void* workspace, const WsLayout& l, hipStream_t hs,
                                        bool sel_ws_is_zero, const quoka::FusedQbar& fq = {},
-                                       const uint16_t* terms = nullptr) {
+                                       const uint16_t* terms = nullptr, bool exact = false) {
   if (dm.T_max > 0 && quoka::select_keys_two_pass_applies(dm, dtype)) {
     uint32_t* sel_ws = reinterpret_cast<uint32_t*>(static_cast<char*>(workspace) + l.sel_off);
+    if (exact)
+      return from_hip(quoka::launch_select_keys_exact(dm, qbar, k_cache, kv_lens, budgets, scores, k_idx, k_cnt, sel_ws, terms,
+                                                      hs));
     return from_hip(quoka::launch_select_keys(dm, qbar, k_cache, kv_lens, budgets, scores, k_idx, k_cnt, sel_ws, hs,
                                               sel_ws_is_zero));
   }
@@ -406,10 +409,11 @@ static quoka_status chunk_common(const quoka_shape* shape, const CallInfo& info,
   if (st != QUOKA_OK) return st;
   hipStream_t hs = static_cast<hipStream_t>(stream);
   const bool two_pass = dm.T_max > 0 && quoka::select_keys_two_pass_applies(dm, shape->dtype);
+  const bool exact = two_pass && quoka::select_keys_exact_pays(dm, shape->dtype);   // (the same lists)
   uint32_t* sel_ws = reinterpret_cast<uint32_t*>(static_cast<char*>(workspace) + l.sel_off);
   float* sq_ws = reinterpret_cast<float*>(static_cast<char*>(workspace) + l.select_off);
   quoka::FusedQbar fq;
-  uint16_t* terms = !two_pass && quoka::score_reads_terms(dm, shape->dtype)
+  uint16_t* terms = (!two_pass || exact) && quoka::score_reads_terms(dm, shape->dtype)
                         ? reinterpret_cast<uint16_t*>(static_cast<char*>(workspace) + l.terms_off)
                         : nullptr;
   if (!two_pass && quoka::score_forms_qbar(dm, shape->dtype)) {   // a few tokens: one launch less
@@ -420,7 +424,7 @@ static quoka_status chunk_common(const quoka_shape* shape, const CallInfo& info,
     if (st != QUOKA_OK) return st;
   }
   st = select_keys_common(dm, shape->dtype, qbar, k_cache, kv_lens, budgets, scores, k_idx, k_cnt, workspace, l, hs,
-                          two_pass, fq, terms);
+                          two_pass, fq, terms, exact);
   if (st != QUOKA_OK) return st;
   return attn_common(shape, info, q, k_cache, v_cache, k_idx, k_cnt, true, k_chunk, v_chunk, out, lse, workspace,
                      workspace_bytes, stream);

@@ -64,6 +64,14 @@ hipError_t launch_topk_keys(const Dims& dm, const float* scores, const int32_t* 
 hipError_t launch_score_stream(const Dims& dm, const float* qbar, const void* k_cache, const int32_t* kv_lens,
                                float* scores, uint32_t* hist_ws, hipStream_t st);
 bool select_keys_two_pass_applies(const Dims& dm, int dtype);
+// The same lists from exact scores and their histogram (launch_score_hist), which is the faster up to a size; `terms` as
+// launch_select_queries leaves them, the workspace cleared as for launch_select_keys.
+bool select_keys_exact_pays(const Dims& dm, int dtype);
+hipError_t launch_score_hist(const Dims& dm, const float* qbar, const void* k_cache, const int32_t* kv_lens, float* scores,
+                             hipStream_t st, const uint16_t* terms, uint32_t* hist_ws);
+hipError_t launch_select_keys_exact(const Dims& dm, const float* qbar, const void* k_cache, const int32_t* kv_lens,
+                                    const int32_t* budgets, float* scores, int32_t* k_idx, int32_t* k_cnt, uint32_t* ws,
+                                    const uint16_t* terms, hipStream_t st);
 size_t select_keys_ws_words(const Dims& dm);
 size_t select_keys_zero_words(const Dims& dm);
 hipError_t launch_select_keys(const Dims& dm, const float* qbar, const void* k_cache, const int32_t* kv_lens,

@@ -16,6 +16,7 @@
 #include "kernels.h"
 #include "qbar_row.hip.h"
 #include "score_tile.hip.h"
+#include "select_ws.hip.h"
 
 namespace quoka {
 
@@ -24,23 +25,30 @@ namespace quoka {
 // PACK (QB = 1, EXACT): at most kPackRows queries, all three terms in one operand.
 // FUSE (PACK, every query retained): Qbar is not there yet.  Every block works its head's few rows out for itself, in
 // place of reading them (8 heads, 8192 keys, one query: a launch of 3.4 us saved, 1 us added here; call 26.1 -> 25.0 us).
+// HIST: the scores are also counted in the head's histogram of kScoreBins bins (hist_ws: the zeroed head of the selection's
+// workspace), in LDS first, so that the selection starts from the finished histogram.
 // TERMS: the query operands lie ready in `terms`.  (A template parameter: as a run-time choice it cost the calls that
 // convert Qbar themselves 1.5 us, 2 x 8 heads of 8337 keys 12.0 -> 13.7.)
-template <int D, int QB, bool EXACT, bool PACK, bool FUSE, bool TERMS>
+template <int D, int QB, bool EXACT, bool PACK, bool FUSE, bool TERMS, bool HIST>
 __global__ __launch_bounds__(kScThreads, 2) void score_bf16(Dims dm, const float* __restrict__ qbar,
                                                            const uint16_t* __restrict__ kc,
                                                            const int32_t* __restrict__ kv_lens,
                                                            float* __restrict__ scores, int n_keep, int tiles_per_wg,
                                                            uint32_t* __restrict__ zero, uint32_t zero_words,
-                                                           FusedQbar fq, const uint16_t* __restrict__ terms) {
+                                                           FusedQbar fq, const uint16_t* __restrict__ terms,
+                                                           uint32_t* __restrict__ hist_ws) {
   using Cfg = ScoreCfg<D, QB>;
-  clear_words(zero, zero_words);
+  if constexpr (!HIST) clear_words(zero, zero_words);
   constexpr int LD = Cfg::LD, CG = Cfg::CG, RPI = Cfg::RPI, NLD = Cfg::NLD;
   extern __shared__ __align__(16) unsigned char smem[];
   uint16_t* tile0p = reinterpret_cast<uint16_t*>(smem);
   uint16_t* tile1p = reinterpret_cast<uint16_t*>(smem + Cfg::kTileBytes);
   float* ssq = reinterpret_cast<float*>(smem + 2 * Cfg::kTileBytes);   // [3][kScTile]
   float* smax = ssq + 3 * kScTile;                                       // [3][QB][kScTile]
+  uint32_t* bins = reinterpret_cast<uint32_t*>(smem + Cfg::kLdsBytes);   // HIST: two bins a word
+  if constexpr (HIST) {
+    for (int i = threadIdx.x; i < kScoreBins / 2; i += kScThreads) bins[i] = 0u;   // (a barrier follows before the first count)
+  }
 
   const int kv = blockIdx.y, b = blockIdx.z;
   const int t_begin = blockIdx.x * tiles_per_wg * kScTile;
@@ -110,9 +118,15 @@ __global__ __launch_bounds__(kScThreads, 2) void score_bf16(Dims dm, const float
   auto finish = [&](int it) {
     if (tid < kScTile) {
       const int key = t_begin + it * kScTile + tid;
-      if (key < T)
-        sc[key] = tile_score<QB>(smax + (it % 3) * QB * kScTile, ssq + (it % 3) * kScTile, tid, dot_mode, mean_mode,
-                                 n_keep);
+      if (key < T) {
+        const float s = tile_score<QB>(smax + (it % 3) * QB * kScTile, ssq + (it % 3) * kScTile, tid, dot_mode, mean_mode,
+                                       n_keep);
+        sc[key] = s;
+        if constexpr (HIST) {
+          const int bin = coarse_bin<kScoreBins>(s);
+          atomicAdd(&bins[bin >> 1], 1u << (16 * (bin & 1)));
+        }
+      }
     }
   };
 
@@ -158,6 +172,15 @@ __global__ __launch_bounds__(kScThreads, 2) void score_bf16(Dims dm, const float
   }
   __syncthreads();
   finish(n_tiles - 1);
+  if constexpr (HIST) {
+    __syncthreads();
+    uint32_t* hist = hist_ws + (size_t)(b * dm.n_kv + kv) * (kSelBins + kSelMeta);
+    for (int i = tid; i < kScoreBins / 2; i += kScThreads) {
+      const uint32_t c = bins[i];
+      if (c & 0xFFFFu) atomicAdd(&hist[2 * i], c & 0xFFFFu);
+      if (c >> 16) atomicAdd(&hist[2 * i + 1], c >> 16);
+    }
+  }
 }
 
 // ---------------------------------------------------------------------------------------------
@@ -328,31 +351,37 @@ static void launch_f32_d(const Dims& dm, const float* qbar, const float* kc, con
 }
 
 // ---------------------------------------------------------------------------------------------
-template <int D, int QB, bool EXACT, bool PACK = false, bool FUSE = false, bool TERMS = false>
-static hipError_t launch_bf16(const Dims& dm, const float* qbar, const void* kc, const int32_t* kv_lens, float* scores,
-                              int n_keep, hipStream_t st, uint32_t* zero, uint32_t zero_words, const FusedQbar& fq = {},
-                              const uint16_t* terms = nullptr) {
-  using Cfg = ScoreCfg<D, QB>;
-  static std::atomic<uint64_t> lds_done{0};
-  const hipError_t e =
-      ensure_dynamic_lds(reinterpret_cast<const void*>(&score_bf16<D, QB, EXACT, PACK, FUSE, TERMS>), Cfg::kLdsBytes, lds_done);
-  if (e != hipSuccess) return e;
+// Tiles of a block, and blocks of a head.  Two blocks per compute unit are resident at once: aim for one round of 512 blocks, so
+// the query operands (prepared once per block) are amortised over as many tiles as the launch allows
+// -- except where the batch entries are chunks of a prompt, which share one cache of which the earlier ones see little:
+// four rounds of shorter blocks even that out (prompt of 16000 in chunks of 1024, this launch 84 -> 57 us; 1024 blocks
+// 84, 4096 64; for caches of one length each, 2048 blocks cost 10-17 %).  Whole calls, 512 -> 2048 blocks: 2 such prompts
+// 1133 -> 1088 us, 30000 tokens, d 64 956 -> 923, 24000 in chunks of 2048 446 -> 432, 20000 in chunks of 500, 14/2 heads
+// 364 -> 355, 9000 in chunks of 333, 12/4 heads 131 -> 124; 3000 - 6000 tokens within 0.5 %.
+static int tiles_per_block(const Dims& dm) {
   const int nt = (dm.T_cap + kScTile - 1) / kScTile;
   const int heads = dm.b * dm.n_kv;
-  // two blocks per compute unit are resident at once: aim for one round of 512 blocks, so the query operands
-  // (prepared once per block) are amortised over as many tiles as the launch allows
-  // -- except where the batch entries are chunks of a prompt, which share one cache of which the earlier ones see little:
-  // four rounds of shorter blocks even that out (prompt of 16000 in chunks of 1024, this launch 84 -> 57 us; 1024 blocks
-  // 84, 4096 64; for caches of one length each, 2048 blocks cost 10-17 %).  Whole calls, 512 -> 2048 blocks: 2 such prompts
-  // 1133 -> 1088 us, 30000 tokens, d 64 956 -> 923, 24000 in chunks of 2048 446 -> 432, 20000 in chunks of 500, 14/2 heads
-  // 364 -> 355, 9000 in chunks of 333, 12/4 heads 131 -> 124; 3000 - 6000 tokens within 0.5 %.
   const int wg_per_head = ((dm.prompt_chunks ? 2048 : 512) + heads - 1) / heads;
-  int tpw = (nt + wg_per_head - 1) / wg_per_head;
-  tpw = tpw < 1 ? 1 : tpw;
+  const int tpw = (nt + wg_per_head - 1) / wg_per_head;
+  return tpw < 1 ? 1 : tpw;
+}
+
+template <int D, int QB, bool EXACT, bool PACK = false, bool FUSE = false, bool TERMS = false, bool HIST = false>
+static hipError_t launch_bf16(const Dims& dm, const float* qbar, const void* kc, const int32_t* kv_lens, float* scores,
+                              int n_keep, hipStream_t st, uint32_t* zero, uint32_t zero_words, const FusedQbar& fq = {},
+                              const uint16_t* terms = nullptr, uint32_t* hist_ws = nullptr) {
+  using Cfg = ScoreCfg<D, QB>;
+  constexpr size_t lds = Cfg::kLdsBytes + (HIST ? kScoreBins / 2 * sizeof(uint32_t) : 0);
+  static_assert(lds <= 81920, "two blocks a compute unit");
+  static std::atomic<uint64_t> lds_done{0};
+  const hipError_t e =
+      ensure_dynamic_lds(reinterpret_cast<const void*>(&score_bf16<D, QB, EXACT, PACK, FUSE, TERMS, HIST>), lds, lds_done);
+  if (e != hipSuccess) return e;
+  const int nt = (dm.T_cap + kScTile - 1) / kScTile, tpw = tiles_per_block(dm);
   dim3 grid((nt + tpw - 1) / tpw, dm.n_kv, dm.b);
-  hipLaunchKernelGGL((score_bf16<D, QB, EXACT, PACK, FUSE, TERMS>), grid, dim3(kScThreads), Cfg::kLdsBytes, st, dm, qbar,
+  hipLaunchKernelGGL((score_bf16<D, QB, EXACT, PACK, FUSE, TERMS, HIST>), grid, dim3(kScThreads), lds, st, dm, qbar,
                      static_cast<const uint16_t*>(kc), kv_lens, scores, n_keep, tpw, zero, zero_words, fq,
-                     terms);
+                     terms, hist_ws);
   return hipGetLastError();
 }
 
@@ -379,6 +408,25 @@ static hipError_t launch_bf16_d(const Dims& dm, const float* qbar, const void* k
   if (qblocks <= 1) return launch_bf16<D, 1, true>(dm, qbar, kc, kv_lens, scores, n_keep, st, zero, zero_words);
   if (qblocks == 2) return launch_bf16<D, 2, true>(dm, qbar, kc, kv_lens, scores, n_keep, st, zero, zero_words);
   return launch_bf16<D, 4, true>(dm, qbar, kc, kv_lens, scores, n_keep, st, zero, zero_words);
+}
+
+// The exact scores and their histogram, from `terms`.
+template <int D>
+static hipError_t launch_hist_d(const Dims& dm, const float* qbar, const void* kc, const int32_t* kv_lens, float* scores,
+                                int n_keep, hipStream_t st, const uint16_t* terms, uint32_t* ws) {
+  const int qblocks = (n_keep + 31) / 32;
+  if (qblocks <= 1)
+    return launch_bf16<D, 1, true, false, false, true, true>(dm, qbar, kc, kv_lens, scores, n_keep, st, nullptr, 0, {}, terms, ws);
+  if (qblocks == 2)
+    return launch_bf16<D, 2, true, false, false, true, true>(dm, qbar, kc, kv_lens, scores, n_keep, st, nullptr, 0, {}, terms, ws);
+  return launch_bf16<D, 4, true, false, false, true, true>(dm, qbar, kc, kv_lens, scores, n_keep, st, nullptr, 0, {}, terms, ws);
+}
+
+hipError_t launch_score_hist(const Dims& dm, const float* qbar, const void* k_cache, const int32_t* kv_lens, float* scores,
+                             hipStream_t st, const uint16_t* terms, uint32_t* hist_ws) {
+  const int n_keep = dm.n_ret < dm.C ? dm.n_ret : dm.C;
+  return dm.d == 64 ? launch_hist_d<64>(dm, qbar, k_cache, kv_lens, scores, n_keep, st, terms, hist_ws)
+                    : launch_hist_d<128>(dm, qbar, k_cache, kv_lens, scores, n_keep, st, terms, hist_ws);
 }
 
 bool score_reads_terms(const Dims& dm, int dtype) {

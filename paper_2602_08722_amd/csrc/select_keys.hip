@@ -15,6 +15,9 @@
 // The selected set is therefore exactly the top-B of the exact scores, as the separate scoring and top-B calls
 // produce it; the `scores` array ends up holding exact values inside the band and provisional values elsewhere.
 //
+// Up to a size the fused call takes a shorter way to the same lists: exact scores of every key with their histogram
+// (score_bf16), then sel_classify and sel_finish, see select_keys_exact_pays.
+//
 // Launch chain (no block ever waits for another block of its launch): provisional scoring with the histogram
 // (score_stream.hip), band classification + exact re-scoring per 2048-key tile, one block per head that selects
 // among the band candidates and lays out the tiles' output offsets, ordered emission per tile.
@@ -695,6 +698,32 @@ bool select_keys_two_pass_applies(const Dims& dm, int dtype) {
   // single-block top-k launch after the exact scores, which the longer chain of this stage cannot beat
   return dtype == QUOKA_BF16 && dm.T_cap > 32768 &&
          (dm.flags & (QUOKA_SCORE_DOT | QUOKA_SCORE_MEAN | QUOKA_SCORE_QBAR_BF16)) == 0;
+}
+
+// Exact scores of every key (three terms, score_bf16) with their histogram, and no key scored twice: two short launches follow
+// instead of three, for up to three times the matrix work.  Whole calls with a small attention part, caches not in any cache
+// memory (us, two-pass -> exact): up to 64 queries 1 head of 72294 61.0 -> 41.7, 2 of 56209 61.3 -> 48.8, 8 of 43636, d 64 54.5 ->
+// 48.3, 8 of 96413 94.6 -> 88.8, 3 x 8 of 46562 119.8 -> 111.2 (245 MB of keys), 8 x 8 of 49927 230.7 -> 233.4 (820 MB); up to 128
+// queries 1 of 45681 66.3 -> 52.7, 4 of 47821 69.7 -> 65.2, 8 of 49594 78.9 -> 80.3 (100 MB), 8 of 95165 109.7 -> 116.4, 8 x 8 of
+// 44597 262 -> 329.  150 sizes measured; the lines lie where the two sides meet.  Packed calls score exactly either way and the
+// streaming launch is the faster for them; a prompt's chunks share one cache, 12 prompts 0.96 - 1.15 of the time, no line to draw.
+// (At these sizes a scoring block has far fewer than the 65536 keys that its 16-bit counters hold.)
+constexpr long long kExactBytes = 300'000'000, kExactBytesWide = 72'000'000;
+bool select_keys_exact_pays(const Dims& dm, int dtype) {
+  if (!select_keys_two_pass_applies(dm, dtype) || dm.T_max > kPackMaxKeys || dm.prompt_chunks || score_packs(dm)) return false;
+  const int n_keep = dm.n_ret < dm.C ? dm.n_ret : dm.C;
+  return (long long)dm.b * dm.n_kv * dm.T_cap * dm.d * 2 <= (n_keep <= 64 ? kExactBytes : kExactBytesWide);
+}
+
+hipError_t launch_select_keys_exact(const Dims& dm, const float* qbar, const void* k_cache, const int32_t* kv_lens,
+                                    const int32_t* budgets, float* scores, int32_t* k_idx, int32_t* k_cnt, uint32_t* ws,
+                                    const uint16_t* terms, hipStream_t st) {
+  const hipError_t e = launch_score_hist(dm, qbar, k_cache, kv_lens, scores, st, terms, ws);
+  if (e != hipSuccess) return e;
+  const dim3 grid(sel_tiles(dm.T_cap), dm.n_kv, dm.b);
+  hipLaunchKernelGGL((sel_classify<kScoreBins>), grid, dim3(kSelThreads), 0, st, dm, scores, kv_lens, budgets, ws);
+  hipLaunchKernelGGL((sel_finish<kScoreBins>), grid, dim3(kSelThreads), 0, st, dm, scores, kv_lens, budgets, ws, k_idx, k_cnt);
+  return hipGetLastError();
 }
 
 size_t select_keys_ws_words(const Dims& dm) {

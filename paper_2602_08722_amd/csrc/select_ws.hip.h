@@ -5,6 +5,7 @@
 namespace quoka {
 
 constexpr int kSelBins = 4096;        // equal bins over [-1, 1]
+constexpr int kScoreBins = 2048;      // of the exact scorer's histogram: half of them (its LDS has room for no more)
 constexpr int kSelTile = 2048;        // keys per block in the per-tile kernels
 constexpr int kSelThreads = 256;
 constexpr int kSelIPT = kSelTile / kSelThreads;

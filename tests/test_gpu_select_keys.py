@@ -250,3 +250,35 @@ def test_select_keys_with_many_candidates_near_the_cut(n_q, chunk, crowd):
     _, idx_f, cnt_f = _fused(buf)
     assert torch.equal(cnt_f, cnt_s) and torch.equal(idx_f, idx_s)
     assert np.array_equal(gen.from_torch(idx_f)[0], O.topk_keys(exact, B))
+
+
+# chunk_attn, in sizes where it scores every key exactly and selects from the histogram of the exact scores
+@pytest.mark.parametrize("kind", ["normal", "pairs", "equal"])
+@pytest.mark.parametrize("case", [
+    dict(n_q=4, n_kv=1, d=128, chunk=40, n_retain=9, kv_lens=[32769], budgets=[1]),                  # one query block; a tile of one key
+    dict(n_q=4, n_kv=2, d=64, chunk=70, n_retain=64, kv_lens=[40960], budgets=[40959]),              # two; full tiles; all but one
+    dict(n_q=4, n_kv=2, d=128, chunk=200, n_retain=100, kv_lens=[131072], budgets=[9000]),           # four; the longest cache
+    dict(n_q=2, n_kv=2, d=128, chunk=3, n_retain=16, kv_lens=[65537], budgets=[8000]),               # all queries kept, few positions
+    dict(n_q=8, n_kv=2, d=128, chunk=128, n_retain=32, kv_lens=[45000, 0, 1500, 33333, 70000], budgets=[5000, 10, 150, 33333, 99999],
+         batch=5),
+], ids=lambda c: "-".join(f"{k}{v}" for k, v in c.items()))
+def test_chunk_attn_selects_from_exact_scores(kind, case):
+    pk = _pk()
+    w = gen.make_custom(dtype="bf16", seed=44, **dict(dict(batch=1), **case))
+    if kind == "equal":
+        w.K[:] = w.K[:, :, :1]
+    elif kind == "pairs":
+        n = w.K.shape[2] // 2 * 2
+        w.K[:, :, 1:n:2] = w.K[:, :, 0:n:2]
+    buf = _buffers(pk, w)
+    sc, idx, cnt = _staged(buf)
+    buf.scores.fill_(float("nan"))
+    buf.k_idx.fill_(-1)
+    buf.k_cnt.fill_(-1)
+    buf.workspace.fill_(0x5A)
+    buf.chunk_attn()
+    torch.cuda.synchronize()
+    assert torch.equal(buf.k_cnt, cnt)
+    for b in range(w.batch):
+        T, n = w.kv_lens[b], int(cnt[b, 0])
+        assert torch.equal(buf.scores[b, :, :T], sc[b, :, :T]) and torch.equal(buf.k_idx[b, :, :n], idx[b, :, :n])
