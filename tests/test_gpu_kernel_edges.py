@@ -77,6 +77,20 @@ def test_float32_attention_units_rows_and_splits(case):
     check_attention(dict(case, dtype="f32"))
 
 
+# the merge of key splits takes four records at a time, in one group of threads or eight: 2, 4, 5 and 9 splits, the most there are,
+# and sequences with fewer units than splits
+@pytest.mark.parametrize("case", [
+    dict(n_q=2, n_kv=1, d=128, chunk=33, kv_lens=[400], budgets=[300]),
+    dict(n_q=2, n_kv=1, d=64, chunk=40, kv_lens=[1000], budgets=[960]),
+    dict(n_q=2, n_kv=1, d=128, chunk=3, kv_lens=[1200], budgets=[1100]),
+    dict(n_q=5, n_kv=1, d=64, chunk=31, kv_lens=[2300], budgets=[2200]),
+    dict(n_q=1, n_kv=1, d=128, chunk=1, kv_lens=[17000], budgets=[16500]),
+    dict(n_q=4, n_kv=2, d=64, chunk=9, kv_lens=[4000, 1, 0, 270], budgets=[3900, 1, 2, 40], batch=4),
+], ids=_id)
+def test_float32_attention_merge_of_splits(case):
+    check_attention(dict(case, dtype="f32"))
+
+
 @pytest.mark.parametrize("n_retain,kv_len,d", [(1, 1, 64), (32, 127, 128), (33, 129, 128), (64, 64, 64), (65, 1000, 128),
                                                (128, 33, 64), (40, 70001, 64)])
 def test_float32_scores_query_blocks_and_key_tails(n_retain, kv_len, d):
