@@ -341,34 +341,39 @@ __global__ __launch_bounds__(kDcThreads) void attn_decode_merge(Dims dm, AttnArg
   const int n_splits = share.n_splits;
   constexpr size_t sstride = DecodeCfg<D>::kRec;   // split s is s * sstride further
   const float* base = part + ((size_t)kv * n_slots + share.first) * sstride;
+  // a thread's first eight outputs are requested together with (m, l), the next eight before these are used
+  const int e = tid % D, sg = tid / D;
+  float v[8];
+  auto load_v = [&](int s0) __attribute__((always_inline)) {
+#pragma unroll
+    for (int u = 0; u < 8; ++u) v[u] = base[min(s0 + u * NG, n_splits - 1) * sstride + r * D + e];
+  };
   float m_s = -INFINITY, l_s = 0.f;
   if (tid < n_splits) {
     m_s = base[tid * sstride + 32 * D + r];
     l_s = base[tid * sstride + 32 * D + 32 + r];
   }
+  load_v(sg);
   if (tid < 64) {   // n_splits <= 64: one wave holds all of them
     const float m = wave64_max(m_s);
     const float w = (m_s == -INFINITY) ? 0.f : __builtin_amdgcn_exp2f(m_s - m);
     const float l = wave64_sum(w * l_s);
-    if (tid < n_splits) wgt[tid] = w;
+    wgt[tid] = w;
     if (tid == 0) {
       s_m = m;
       s_l = l;
     }
   }
   __syncthreads();
-  const int e = tid % D, sg = tid / D;
   float acc = 0.f;
   for (int s0 = sg; s0 < n_splits; s0 += 8 * NG) {
-    float v[8];
+    float x[8];
 #pragma unroll
-    for (int u = 0; u < 8; ++u) {
-      const int sp = min(s0 + u * NG, n_splits - 1);
-      v[u] = base[sp * sstride + r * D + e];
-    }
+    for (int u = 0; u < 8; ++u) x[u] = v[u];
+    if (s0 + 8 * NG < n_splits) load_v(s0 + 8 * NG);
 #pragma unroll
     for (int u = 0; u < 8; ++u)
-      if (s0 + u * NG < n_splits) acc += wgt[s0 + u * NG] * v[u];
+      if (s0 + u * NG < n_splits) acc += wgt[s0 + u * NG] * x[u];
   }
   red[sg][e] = acc;
   __syncthreads();
