@@ -115,6 +115,7 @@ struct CallInfo {
   int len_stride = 1;    // entries between the cache lengths (budgets) of neighbouring batch entries
   int last_len = 0;      // tokens of the last batch entry where it is shorter than the others
   bool prompt_chunks = false;   // the batch entries are chunks of one prompt
+  bool of_prompt = false;       // a chunk of a prompt, by itself or among others: leaves the same `scores` either way
   void apply(Dims* dm) const {
     dm->T_cap = kv_cap < dm->T_max ? kv_cap : dm->T_max;
     dm->ls = len_stride;
@@ -409,7 +410,7 @@ static quoka_status chunk_common(const quoka_shape* shape, const CallInfo& info,
   if (st != QUOKA_OK) return st;
   hipStream_t hs = static_cast<hipStream_t>(stream);
   const bool two_pass = dm.T_max > 0 && quoka::select_keys_two_pass_applies(dm, shape->dtype);
-  const bool exact = two_pass && quoka::select_keys_exact_pays(dm, shape->dtype);   // (the same lists)
+  const bool exact = two_pass && !info.of_prompt && quoka::select_keys_exact_pays(dm, shape->dtype);   // (the same lists)
   uint32_t* sel_ws = reinterpret_cast<uint32_t*>(static_cast<char*>(workspace) + l.sel_off);
   float* sq_ws = reinterpret_cast<float*>(static_cast<char*>(workspace) + l.select_off);
   quoka::FusedQbar fq;
@@ -491,7 +492,7 @@ quoka_status quoka_prefill_attn(const quoka_shape* shape, int sparse, const void
         CallInfo info;
         info.kv_cap = (i0 + n - 1) * C;
         info.len_stride = shape->batch;
-        info.prompt_chunks = true;
+        info.prompt_chunks = info.of_prompt = true;
         const bool holds_last = i0 + n == n_chunks;
         if (holds_last) info.last_len = last_len;
         const size_t first = (size_t)i0 * C;
@@ -557,6 +558,7 @@ quoka_status quoka_prefill_attn(const quoka_shape* shape, int sparse, const void
     // 1222 us).  The first chunk has no cache to select from, and only the last chunk's intermediates are the caller's.
     CallInfo info;
     info.kv_cap = i * C;
+    info.of_prompt = true;
     if (sparse && (i > 0 || n_chunks == 1)) {
       st = chunk_common(&sh, info, qi, k, v, lens, budgets_all + (size_t)i * shape->batch, ki, vi, q_idx, qbar, scores,
                         k_idx, k_cnt, oi, nullptr, workspace, workspace_bytes, stream);

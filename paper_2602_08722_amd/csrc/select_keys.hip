@@ -710,7 +710,7 @@ bool select_keys_two_pass_applies(const Dims& dm, int dtype) {
 // (At these sizes a scoring block has far fewer than the 65536 keys that its 16-bit counters hold.)
 constexpr long long kExactBytes = 300'000'000, kExactBytesWide = 72'000'000;
 bool select_keys_exact_pays(const Dims& dm, int dtype) {
-  if (!select_keys_two_pass_applies(dm, dtype) || dm.T_max > kPackMaxKeys || dm.prompt_chunks || score_packs(dm)) return false;
+  if (!select_keys_two_pass_applies(dm, dtype) || dm.T_max > kPackMaxKeys || score_packs(dm)) return false;
   const int n_keep = dm.n_ret < dm.C ? dm.n_ret : dm.C;
   return (long long)dm.b * dm.n_kv * dm.T_cap * dm.d * 2 <= (n_keep <= 64 ? kExactBytes : kExactBytesWide);
 }
