@@ -454,43 +454,71 @@ __global__ __launch_bounds__(2 * kSetThreads, 2) void attn_bf16(Dims dm, AttnArg
     }
     return;
   }
-  if (wave_on && tok < C) {
-    const float inv = 1.0f / l_tot;
-    uint16_t* orow = static_cast<uint16_t*>(a.out) + b * dm.os[0] + h * dm.os[1] + (size_t)tok * dm.os[2];
+  if constexpr (D == 64 && !SPLIT) {   // (here rows that go out whole cost 1 - 1.5 % in launches of many rounds)
+    if (wave_on && tok < C) {
+      const float inv = 1.0f / l_tot;
+      uint16_t* orow = static_cast<uint16_t*>(a.out) + b * dm.os[0] + h * dm.os[1] + (size_t)tok * dm.os[2];
 #pragma unroll
-    for (int c = 0; c < DB; ++c)
+      for (int c = 0; c < DB; ++c)
 #pragma unroll
-      for (int v4 = 0; v4 < 4; ++v4) {   // registers 4*v4 .. 4*v4+3 are four consecutive dims
-        uint2 pk;
-        pk.x = f32_to_bf16_bits(o[c][4 * v4] * inv) | (f32_to_bf16_bits(o[c][4 * v4 + 1] * inv) << 16);
-        pk.y = f32_to_bf16_bits(o[c][4 * v4 + 2] * inv) | (f32_to_bf16_bits(o[c][4 * v4 + 3] * inv) << 16);
-        *reinterpret_cast<uint2*>(orow + 32 * c + 8 * v4 + 4 * hf) = pk;
-      }
-    if (a.lse != nullptr && hf == 0) {
-      a.lse[(size_t)(b * dm.n_q + h) * dm.C + tok] = (m_run + log2f(l_tot)) * 0.6931471805599453f;
+        for (int v4 = 0; v4 < 4; ++v4) {   // registers 4*v4 .. 4*v4+3 are four consecutive dims
+          uint2 pk;
+          pk.x = f32_to_bf16_bits(o[c][4 * v4] * inv) | (f32_to_bf16_bits(o[c][4 * v4 + 1] * inv) << 16);
+          pk.y = f32_to_bf16_bits(o[c][4 * v4 + 2] * inv) | (f32_to_bf16_bits(o[c][4 * v4 + 3] * inv) << 16);
+          *reinterpret_cast<uint2*>(orow + 32 * c + 8 * v4 + 4 * hf) = pk;
+        }
+      if (a.lse != nullptr && hf == 0)
+        a.lse[(size_t)(b * dm.n_q + h) * dm.C + tok] = (m_run + log2f(l_tot)) * 0.6931471805599453f;
     }
+    return;
+  }
+  // Rows go out whole, 16 bytes a lane, through the wave's own piece of LDS; as the registers lie, a store covers 16 bytes of
+  // each of 32 rows (32/8 heads, d 128, 1024 tokens over 983 keys 40.6 -> 39.4 us, 443 over 43 17.3 -> 16.7).
+  constexpr int OLD = D + 8;   // pitch (elements)
+  if constexpr (!SPLIT) __syncthreads();   // all tiles consumed (SPLIT: the piece is the one this wave has just read)
+  uint16_t* ot = reinterpret_cast<uint16_t*>(smem) + (SPLIT ? (size_t)slot * 64 * (2 + DB * 16) * 2 : (size_t)slot * 32 * OLD);
+  if (!wave_on) return;
+  const float inv = 1.0f / l_tot;
+#pragma unroll
+  for (int c = 0; c < DB; ++c)
+#pragma unroll
+    for (int v4 = 0; v4 < 4; ++v4) {   // registers 4*v4 .. 4*v4+3 are four consecutive dims
+      uint2 pk;
+      pk.x = f32_to_bf16_bits(o[c][4 * v4] * inv) | (f32_to_bf16_bits(o[c][4 * v4 + 1] * inv) << 16);
+      pk.y = f32_to_bf16_bits(o[c][4 * v4 + 2] * inv) | (f32_to_bf16_bits(o[c][4 * v4 + 3] * inv) << 16);
+      *reinterpret_cast<uint2*>(ot + li * OLD + 32 * c + 8 * v4 + 4 * hf) = pk;
+    }
+  if (a.lse != nullptr && hf == 0 && tok < C)
+    a.lse[(size_t)(b * dm.n_q + h) * dm.C + tok] = (m_run + log2f(l_tot)) * 0.6931471805599453f;
+  __builtin_amdgcn_wave_barrier();
+  uint16_t* obase = static_cast<uint16_t*>(a.out) + b * dm.os[0] + h * dm.os[1] + (size_t)tok0 * dm.os[2] + (lane % CG) * 8;
+#pragma unroll
+  for (int i = 0; i < 32 * CG / 64; ++i) {
+    const int r = i * (64 / CG) + lane / CG;
+    const u32x4 x = *reinterpret_cast<const u32x4*>(ot + r * OLD + (lane % CG) * 8);
+    if (tok0 + r < C) *reinterpret_cast<u32x4*>(obase + (size_t)r * dm.os[2]) = x;
   }
 }
 
 #undef QUOKA_RESOLVE
 #undef QUOKA_ISSUE
 
-// Sum of the key splits' partials: a block takes one dim block of a row block, each of its waves up to kMergeRun
-// neighbouring splits at a time, all of whose records are requested before the first is used, and the waves' sums meet in
-// LDS.  The lane layout is the attention kernel's own, so the loads are whole kilobytes.  Everything is added in a fixed order.
+// Sum of the key splits' partials: a wave takes one dim block of a row block and up to kMergeRun neighbouring splits at a
+// time, all of whose records are requested before the first is used, and the sums of the waves that share a dim block meet in
+// LDS.  A block is all waves of a row block where those are at most eight, else those of a dim block (`dims` of a block).  The lane layout is the attention kernel's own, so the loads are whole kilobytes.  Everything is added in a fixed order.
 // What bounds it is the chain of fetches, not the bytes: with one wave walking a dim block's splits two at a time the launch took
 // 0.4 us a split (8 heads, d 64, 103 tokens, 32 splits 15.4 us, now 5.4; 2 heads of 7, d 128, 5 tokens 13.2, now 4.4; 4 heads
 // of 3, d 128, 147 tokens 9.3, now 5.3).
 constexpr int kMergeWaves = 8, kMergeRun = 4;
 template <int D>
-__global__ __launch_bounds__(64 * kMergeWaves) void attn_bf16_merge(Dims dm, AttnArgs a) {
+__global__ __launch_bounds__(64 * kMergeWaves) void attn_bf16_merge(Dims dm, AttnArgs a, int dims) {
   constexpr int REC = AttnCfg<D, true>::kRecFloats;
   __shared__ float2 ml[kMergeWaves][32];
-  __shared__ float4 sum[kMergeWaves - 1][4][64];
-  const int lane = threadIdx.x & 63, w = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6);
-  const int nw = blockDim.x >> 6;
+  __shared__ float4 sum[kMergeWaves][4][64];
+  const int lane = threadIdx.x & 63, wave = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6);
+  const int w = wave / dims, nw = (int)(blockDim.x >> 6) / dims;   // of the dim block
   const int li = lane & 31, hf = lane >> 5;
-  const int x = blockIdx.x, kv = blockIdx.y % dm.n_kv, b = blockIdx.y / dm.n_kv, c = blockIdx.z;
+  const int x = blockIdx.x, kv = blockIdx.y % dm.n_kv, b = blockIdx.y / dm.n_kv, c = (int)blockIdx.z * dims + wave % dims;
   const int C = dm.chunk(b);
   if (x >= dm.g * ((C + 31) / 32)) return;   // block-uniform
   const float* rec = a.part + ((size_t)blockIdx.y * gridDim.x + x) * a.n_splits * REC;
@@ -503,12 +531,19 @@ __global__ __launch_bounds__(64 * kMergeWaves) void attn_bf16_merge(Dims dm, Att
     float ms[kMergeRun], ls[kMergeRun];
     float4 t[kMergeRun][4];
 #pragma unroll
-    for (int i = 0; i < kMergeRun; ++i) {   // (the last record of the run again where there are fewer)
-      const float* p = rec + (size_t)min(s + i, s1 - 1) * REC;
-      ms[i] = p[32 * D + li];
-      ls[i] = p[32 * D + 32 + li];
+    for (int i = 0; i < kMergeRun; ++i) {
+      if (s + i < s1) {   // (wave-uniform)
+        const float* p = rec + (size_t)(s + i) * REC;
+        ms[i] = p[32 * D + li];
+        ls[i] = p[32 * D + 32 + li];
 #pragma unroll
-      for (int v4 = 0; v4 < 4; ++v4) t[i][v4] = *reinterpret_cast<const float4*>(p + ((c * 4 + v4) * 64 + lane) * 4);
+        for (int v4 = 0; v4 < 4; ++v4) t[i][v4] = *reinterpret_cast<const float4*>(p + ((c * 4 + v4) * 64 + lane) * 4);
+      } else {   // adds zeros
+        ms[i] = -INFINITY;
+        ls[i] = 0.f;
+#pragma unroll
+        for (int v4 = 0; v4 < 4; ++v4) t[i][v4] = make_float4(0.f, 0.f, 0.f, 0.f);
+      }
     }
     __builtin_amdgcn_sched_barrier(0);   // all of them in flight
     float m_new = m;
@@ -522,29 +557,28 @@ __global__ __launch_bounds__(64 * kMergeWaves) void attn_bf16_merge(Dims dm, Att
     for (int v = 0; v < 16; ++v) o[v] *= alpha;
 #pragma unroll
     for (int i = 0; i < kMergeRun; ++i) {
-      const bool in = s + i < s1;   // (a repeated record adds plain zeros, whatever it holds)
       const float wgt = __builtin_amdgcn_exp2f(ms[i] - m_fin);
-      l += in ? wgt * ls[i] : 0.f;
+      l += wgt * ls[i];
 #pragma unroll
       for (int v4 = 0; v4 < 4; ++v4) {
-        o[4 * v4] += in ? wgt * t[i][v4].x : 0.f;
-        o[4 * v4 + 1] += in ? wgt * t[i][v4].y : 0.f;
-        o[4 * v4 + 2] += in ? wgt * t[i][v4].z : 0.f;
-        o[4 * v4 + 3] += in ? wgt * t[i][v4].w : 0.f;
+        o[4 * v4] += wgt * t[i][v4].x;
+        o[4 * v4 + 1] += wgt * t[i][v4].y;
+        o[4 * v4 + 2] += wgt * t[i][v4].z;
+        o[4 * v4 + 3] += wgt * t[i][v4].w;
       }
     }
   }
   if (nw > 1) {
-    if (hf == 0) ml[w][li] = make_float2(m, l);
+    if (hf == 0) ml[wave][li] = make_float2(m, l);
     if (w > 0) {
 #pragma unroll
       for (int v4 = 0; v4 < 4; ++v4)
-        sum[w - 1][v4][lane] = make_float4(o[4 * v4], o[4 * v4 + 1], o[4 * v4 + 2], o[4 * v4 + 3]);
+        sum[wave][v4][lane] = make_float4(o[4 * v4], o[4 * v4 + 1], o[4 * v4 + 2], o[4 * v4 + 3]);
     }
     __syncthreads();
     if (w > 0) return;
     float m_all = m;
-    for (int i = 1; i < nw; ++i) m_all = fmaxf(m_all, ml[i][li].x);
+    for (int i = 1; i < nw; ++i) m_all = fmaxf(m_all, ml[i * dims + wave][li].x);   // (w is 0: wave is the dim block's place)
     const float m_fin = m_all == -INFINITY ? 0.f : m_all;
     const float alpha = __builtin_amdgcn_exp2f(m - m_fin);
     m = m_all;
@@ -552,11 +586,11 @@ __global__ __launch_bounds__(64 * kMergeWaves) void attn_bf16_merge(Dims dm, Att
 #pragma unroll
     for (int v = 0; v < 16; ++v) o[v] *= alpha;
     for (int i = 1; i < nw; ++i) {
-      const float wgt = __builtin_amdgcn_exp2f(ml[i][li].x - m_fin);
-      l += wgt * ml[i][li].y;
+      const float wgt = __builtin_amdgcn_exp2f(ml[i * dims + wave][li].x - m_fin);
+      l += wgt * ml[i * dims + wave][li].y;
 #pragma unroll
       for (int v4 = 0; v4 < 4; ++v4) {
-        const float4 t = sum[i - 1][v4][lane];
+        const float4 t = sum[i * dims + wave][v4][lane];
         o[4 * v4] += wgt * t.x;
         o[4 * v4 + 1] += wgt * t.y;
         o[4 * v4 + 2] += wgt * t.z;
@@ -597,9 +631,9 @@ static hipError_t launch_variant(const Dims& dm, const AttnArgs& a, hipStream_t 
   aa.adjacent = (long long)grid.x * grid.y * grid.z >= 2 * kComputeUnits ? 1 : 0;
   hipLaunchKernelGGL((attn_bf16<D, SPLIT, XS, KSPLIT>), grid, dim3(2 * kSetThreads), lds, st, dm, aa);
   if (KSPLIT) {
-    const int runs = (a.n_splits + kMergeRun - 1) / kMergeRun;
-    hipLaunchKernelGGL((attn_bf16_merge<D>), dim3(nrb, dm.b * dm.n_kv, D / 32), dim3(64 * (runs < kMergeWaves ? runs : kMergeWaves)),
-                       0, st, dm, aa);
+    const int runs = (a.n_splits + kMergeRun - 1) / kMergeRun, waves = runs < kMergeWaves ? runs : kMergeWaves;
+    const int dims = waves * (D / 32) <= kMergeWaves ? D / 32 : 1;
+    hipLaunchKernelGGL((attn_bf16_merge<D>), dim3(nrb, dm.b * dm.n_kv, D / 32 / dims), dim3(64 * waves * dims), 0, st, dm, aa, dims);
   }
   return hipGetLastError();
 }
