@@ -421,7 +421,7 @@ static quoka_status chunk_common(const quoka_shape* shape, const CallInfo& info,
     fq = quoka::FusedQbar{q, q_idx, qbar};
   } else {
     st = from_hip(quoka::launch_select_queries(dm, shape->dtype, q, q_idx, qbar, sq_ws, hs, two_pass ? sel_ws : nullptr,
-                                               two_pass ? quoka::select_keys_zero_words(dm) : 0, terms));
+                                               two_pass ? quoka::select_keys_zero_words(dm, exact) : 0, terms));
     if (st != QUOKA_OK) return st;
   }
   st = select_keys_common(dm, shape->dtype, qbar, k_cache, kv_lens, budgets, scores, k_idx, k_cnt, workspace, l, hs,

@@ -73,7 +73,7 @@ hipError_t launch_select_keys_exact(const Dims& dm, const float* qbar, const voi
                                     const int32_t* budgets, float* scores, int32_t* k_idx, int32_t* k_cnt, uint32_t* ws,
                                     const uint16_t* terms, hipStream_t st);
 size_t select_keys_ws_words(const Dims& dm);
-size_t select_keys_zero_words(const Dims& dm);
+size_t select_keys_zero_words(const Dims& dm, bool exact);   // (`exact`: for launch_select_keys_exact)
 hipError_t launch_select_keys(const Dims& dm, const float* qbar, const void* k_cache, const int32_t* kv_lens,
                               const int32_t* budgets, float* scores, int32_t* k_idx, int32_t* k_cnt, uint32_t* ws,
                               hipStream_t st, bool ws_is_zero = false);

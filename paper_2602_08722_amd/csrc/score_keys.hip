@@ -174,7 +174,8 @@ __global__ __launch_bounds__(kScThreads, 2) void score_bf16(Dims dm, const float
   finish(n_tiles - 1);
   if constexpr (HIST) {
     __syncthreads();
-    uint32_t* hist = hist_ws + (size_t)(b * dm.n_kv + kv) * (kSelBins + kSelMeta);
+    const int heads = dm.b * dm.n_kv;
+    uint32_t* hist = exact_hist(hist_ws, heads, b * dm.n_kv + kv, (int)blockIdx.x % exact_hist_copies(heads));
     for (int i = tid; i < kScoreBins / 2; i += kScThreads) {
       const uint32_t c = bins[i];
       if (c & 0xFFFFu) atomicAdd(&hist[2 * i], c & 0xFFFFu);

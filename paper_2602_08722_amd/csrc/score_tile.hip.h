@@ -249,12 +249,14 @@ __device__ __forceinline__ float tile_score(const float* __restrict__ sm, const 
   return m / nrm + 0.0f;
 }
 
-// Side job of a fused call: all blocks of the launch together clear `words` 32-bit words.
+// Side job of a fused call: all blocks of the launch together clear `words` 32-bit words (p is 16-byte aligned).
 __device__ __forceinline__ void clear_words(uint32_t* __restrict__ p, uint32_t words) {
   if (p == nullptr) return;
   const uint32_t nblk = gridDim.x * gridDim.y * gridDim.z;
   const uint32_t blk = blockIdx.x + gridDim.x * (blockIdx.y + gridDim.y * blockIdx.z);
-  for (uint32_t i = blk * blockDim.x + threadIdx.x; i < words; i += nblk * blockDim.x) p[i] = 0u;
+  const uint32_t i0 = blk * blockDim.x + threadIdx.x, step = nblk * blockDim.x;
+  for (uint32_t i = i0; i < words / 4; i += step) reinterpret_cast<u32x4*>(p)[i] = u32x4{0u, 0u, 0u, 0u};
+  if (i0 < words % 4) p[words / 4 * 4 + i0] = 0u;
 }
 
 }  // namespace quoka

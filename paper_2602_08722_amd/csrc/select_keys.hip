@@ -569,42 +569,71 @@ template <int BINS>
 __global__ __launch_bounds__(kSelThreads) void sel_classify(Dims dm, float* __restrict__ scores,
                                                            const int32_t* __restrict__ kv_lens,
                                                            const int32_t* __restrict__ budgets, uint32_t* __restrict__ ws) {
+  constexpr int PER = BINS / kSelThreads;
   __shared__ uint32_t sh[kSelThreads / 64 + 1];
-  __shared__ uint32_t bin, n_in;
+  __shared__ uint32_t bin, n_in, n_cand, slot0;
   const SelCtx c = sel_ctx(dm, scores, kv_lens, budgets, ws, blockIdx.y, blockIdx.z);
   const int t0 = blockIdx.x * kSelTile;
   const int tid = threadIdx.x, lane = tid & 63;
   float v[kSelIPT];   // (requested before the cache length is known)
 #pragma unroll
   for (int i = 0; i < kSelIPT; ++i) v[i] = c.sc[min(t0 + tid + kSelThreads * i, dm.T_max - 1)];
-  uint32_t hv[BINS / kSelThreads];
-  load_hist_run(c.w.hist, hv);
+  uint32_t hv[PER];
+  if constexpr (BINS == kSelBins) {
+    load_hist_run(c.w.hist, hv);
+  } else {   // the copies of the exact scorer's histogram, four at a time
+    const int heads = dm.b * dm.n_kv, copies = exact_hist_copies(heads);
+#pragma unroll
+    for (int i = 0; i < PER; ++i) hv[i] = 0u;
+    for (int j0 = 0; j0 < copies; j0 += 4) {
+      uint32_t h[4][PER];
+#pragma unroll
+      for (int j = 0; j < 4; ++j) load_hist_run(exact_hist(ws, heads, c.head, min(j0 + j, copies - 1)), h[j]);
+#pragma unroll
+      for (int j = 0; j < 4; ++j)
+#pragma unroll
+        for (int i = 0; i < PER; ++i) hv[i] += j0 + j < copies ? h[j][i] : 0u;
+    }
+  }
   if (c.B == 0 || c.B >= c.T || t0 >= c.T) return;   // block-uniform
-  if (tid == 0) n_in = 0u;
+  if (tid == 0) n_in = n_cand = 0u;
   const int cut_bin = find_cut_bin(hv, (uint32_t)c.B, sh, &bin);
-  uint32_t above = 0;
+  // The candidates get slots inside the block first, and the block one piece of the head's list: waves that each asked for
+  // theirs queued up at the head's counter (one head of 130664 positions: 14.7 us, 6.6 so; 4 heads of 39853 7.0, 4.8 so).
+  uint32_t above = 0, mine = 0, cand = 0;
 #pragma unroll
   for (int i = 0; i < kSelIPT; ++i) {
     const int t = t0 + tid + kSelThreads * i;
     const int k = coarse_bin<BINS>(v[i]);
-    above += (uint32_t)__popcll(__builtin_amdgcn_ballot_w64(t < c.T && k > cut_bin));
-    const bool cand = t < c.T && k == cut_bin;
-    const unsigned long long m = __builtin_amdgcn_ballot_w64(cand);
-    if (m != 0) {   // wave-uniform; any order will do
-      uint32_t slot = 0;
-      if (lane == 0) slot = atomicAdd(&c.w.meta[kMetaCand], (uint32_t)__popcll(m));
-      slot = (uint32_t)__builtin_amdgcn_readfirstlane((int)slot) + __popcll(m & ((1ull << lane) - 1ull));
-      if (cand) {
-        c.w.cand_key[slot] = max(okey(v[i]), 1u);
-        c.w.cand_pos[slot] = (uint32_t)t;
-      }
-    }
+    above += t < c.T && k > cut_bin ? 1u : 0u;
+    const bool is_cand = t < c.T && k == cut_bin;
+    cand |= is_cand ? 1u << i : 0u;
+    mine += is_cand ? 1u : 0u;
   }
-  if (lane == 0 && above) atomicAdd(&n_in, above);
+  // (one scan for both counts: a tile has 2048 keys)
+  const uint32_t upto = wave_incl_scan_u32((above << 16) | mine);
+  uint32_t at = 0;
+  if (lane == 63) {
+    if (upto >> 16) atomicAdd(&n_in, upto >> 16);
+    if (upto & 0xFFFFu) at = atomicAdd(&n_cand, upto & 0xFFFFu);
+  }
+  at = (uint32_t)__builtin_amdgcn_readlane((int)at, 63) + (upto & 0xFFFFu) - mine;   // any order of the waves will do
   __syncthreads();
   if (tid == 0) {
+    if (n_cand) slot0 = atomicAdd(&c.w.meta[kMetaCand], n_cand);
     c.w.tile_in[blockIdx.x] = n_in;
     if (blockIdx.x == 0) c.w.meta[kMetaBinHi] = (uint32_t)cut_bin;
+  }
+  __syncthreads();
+  if (n_cand == 0) return;
+  at += slot0;
+#pragma unroll
+  for (int i = 0; i < kSelIPT; ++i) {
+    if ((cand >> i) & 1u) {
+      c.w.cand_key[at] = max(okey(v[i]), 1u);
+      c.w.cand_pos[at] = (uint32_t)(t0 + tid + kSelThreads * i);
+      ++at;
+    }
   }
 }
 
@@ -728,10 +757,14 @@ hipError_t launch_select_keys_exact(const Dims& dm, const float* qbar, const voi
 
 size_t select_keys_ws_words(const Dims& dm) {
   if (dm.T_max <= 32768) return 0;
-  return sel_zero_words(dm.b * dm.n_kv) + (size_t)dm.b * dm.n_kv * sel_head_words(dm.T_max);
+  const int heads = dm.b * dm.n_kv;
+  return sel_zero_words(heads) + exact_hist_words(heads) + (size_t)heads * sel_head_words(dm.T_max);
 }
 
-size_t select_keys_zero_words(const Dims& dm) { return sel_zero_words(dm.b * dm.n_kv); }
+size_t select_keys_zero_words(const Dims& dm, bool exact) {
+  const int heads = dm.b * dm.n_kv;
+  return sel_zero_words(heads) + (exact ? exact_hist_words(heads) : 0);
+}
 
 template <int D>
 static void launch_rescore(const Dims& dm, const float* qbar, const void* kc, const int32_t* kv_lens,
@@ -760,7 +793,7 @@ hipError_t launch_select_keys(const Dims& dm, const float* qbar, const void* k_c
                               const int32_t* budgets, float* scores, int32_t* k_idx, int32_t* k_cnt, uint32_t* ws,
                               hipStream_t st, bool ws_is_zero) {
   const int n_keep = dm.n_ret < dm.C ? dm.n_ret : dm.C;
-  if (!ws_is_zero) hipLaunchKernelGGL(sel_zero, dim3(64), dim3(256), 0, st, ws, select_keys_zero_words(dm));
+  if (!ws_is_zero) hipLaunchKernelGGL(sel_zero, dim3(64), dim3(256), 0, st, ws, select_keys_zero_words(dm, false));
   // provisional scores and their histogram in one streaming launch
   hipError_t e = launch_score_stream(dm, qbar, k_cache, kv_lens, scores, ws, st);
   if (e != hipSuccess) return e;

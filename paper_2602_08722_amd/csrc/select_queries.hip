@@ -476,6 +476,7 @@ __global__ __launch_bounds__(64) void sq_qbar(Dims dm, const T* __restrict__ q, 
   clear_words(zero, zero_words);   // side job of the fused call: histograms and counters of the key-selection stage
   const int r = blockIdx.x, kv = blockIdx.y, b = blockIdx.z;
   const int lane = threadIdx.x;
+  if (r >= n_keep) return;   // (such a block only clears)
   float row[EPL];
   qbar_row<T, D, RULE, GU>(dm, q, q_idx, n_keep, r, kv, b, lane, true, row);
   float* out = qbar + ((size_t)(b * dm.n_kv + kv) * n_keep + r) * D;
@@ -525,7 +526,9 @@ bool select_queries_one_block(const Dims& dm) {
 template <typename T, int D, int RULE>
 static void launch_qbar(const Dims& dm, const T* q, int32_t* q_idx, float* qbar, int n_keep, hipStream_t st, uint32_t* zero,
                         uint32_t zero_words, uint16_t* terms) {
-  const dim3 grid(n_keep, dm.n_kv, dm.b);
+  // (what is cleared, 128 to 260 KiB for up to 16 heads, wants more than the blocks of a few queries)
+  const int heads = dm.n_kv * dm.b, least = zero != nullptr ? (64 + heads - 1) / heads : 0;
+  const dim3 grid(n_keep > least ? n_keep : least, dm.n_kv, dm.b);
   if (dm.g <= 4) {
     hipLaunchKernelGGL((sq_qbar<T, D, RULE, 4>), grid, dim3(64), 0, st, dm, q, q_idx, qbar, n_keep, zero, zero_words, terms);
   } else if (dm.g <= 8) {

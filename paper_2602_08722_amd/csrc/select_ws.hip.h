@@ -36,6 +36,15 @@ struct SelWs {
 __host__ __device__ inline int sel_tiles(int T_max) { return (T_max + kSelTile - 1) / kSelTile; }
 __host__ __device__ inline size_t sel_mask_words(int T_max) { return (size_t)sel_tiles(T_max) * (kSelTile / 32); }
 __host__ __device__ inline size_t sel_zero_words(int heads) { return (size_t)heads * (kSelBins + kSelMeta); }
+// The exact scorer's histogram comes in several copies, shared out over its blocks: with one for all, the blocks of few heads queue
+// up at the same few bins (one head of 130664 positions: scoring launch 27.9 us, 12.4 so).  The first two lie where the
+// streaming scorer has its histogram, the others behind the run above (they are cleared with it where they are used).
+__host__ __device__ inline int exact_hist_copies(int heads) { return heads >= 8 ? 2 : heads >= 4 ? 4 : heads >= 2 ? 8 : 16; }
+__host__ __device__ inline size_t exact_hist_words(int heads) { return (size_t)heads * (exact_hist_copies(heads) - 2) * kScoreBins; }
+__device__ __forceinline__ uint32_t* exact_hist(uint32_t* ws, int heads, int head, int copy) {
+  return copy < 2 ? ws + (size_t)head * (kSelBins + kSelMeta) + copy * kScoreBins
+                  : ws + sel_zero_words(heads) + ((size_t)head * (exact_hist_copies(heads) - 2) + copy - 2) * kScoreBins;
+}
 __host__ __device__ inline size_t sel_head_words(int T_max) {
   return 3 * (size_t)sel_tiles(T_max) + sel_mask_words(T_max) + 2 * (size_t)T_max;
 }
@@ -43,7 +52,7 @@ __device__ __forceinline__ SelWs sel_ws(uint32_t* ws, int heads, int head, int T
   SelWs s;
   s.hist = ws + (size_t)head * (kSelBins + kSelMeta);
   s.meta = s.hist + kSelBins;
-  uint32_t* p = ws + sel_zero_words(heads) + (size_t)head * sel_head_words(T_max);
+  uint32_t* p = ws + sel_zero_words(heads) + exact_hist_words(heads) + (size_t)head * sel_head_words(T_max);
   const int nt = sel_tiles(T_max);
   s.tile_in = p;
   s.tile_off = p + nt;
