@@ -731,13 +731,13 @@ bool select_keys_two_pass_applies(const Dims& dm, int dtype) {
 
 // Exact scores of every key (three terms, score_bf16) with their histogram, and no key scored twice: two short launches follow
 // instead of three, for up to three times the matrix work.  Whole calls with a small attention part, caches not in any cache
-// memory (us, two-pass -> exact): up to 64 queries 1 head of 72294 61.0 -> 41.7, 2 of 56209 61.3 -> 48.8, 8 of 43636, d 64 54.5 ->
-// 48.3, 8 of 96413 94.6 -> 88.8, 3 x 8 of 46562 119.8 -> 111.2 (245 MB of keys), 8 x 8 of 49927 230.7 -> 233.4 (820 MB); up to 128
-// queries 1 of 45681 66.3 -> 52.7, 4 of 47821 69.7 -> 65.2, 8 of 49594 78.9 -> 80.3 (100 MB), 8 of 95165 109.7 -> 116.4, 8 x 8 of
-// 44597 262 -> 329.  150 sizes measured; the lines lie where the two sides meet.  Packed calls score exactly either way and the
+// memory (us, two-pass -> exact): up to 64 queries 1 head of 72294 61.0 -> 41.7, 2 of 99086 75.7 -> 66.2, 8 of 55226 79.1 -> 72.3,
+// 8 of 92109 90.8 -> 84.7, 3 x 8 of 53300 120.0 -> 116.8 (246 MB of keys), 8 x 8 of 49927 230.7 -> 233.4 (820 MB); up to 128
+// queries 2 of 88869 76.5 -> 63.6, 4 of 58639 74.3 -> 69.0, 8 of 83522, d 64 76.8 -> 74.7 (86 MB), 8 of 47311 82.3 -> 83.0 (97 MB),
+// 8 x 8 of 36611, d 64 138 -> 156.  260 sizes measured; the lines lie where the two sides meet.  Packed calls score exactly either way and the
 // streaming launch is the faster for them; a prompt's chunks share one cache, 12 prompts 0.96 - 1.15 of the time, no line to draw.
 // (At these sizes a scoring block has far fewer than the 65536 keys that its 16-bit counters hold.)
-constexpr long long kExactBytes = 300'000'000, kExactBytesWide = 72'000'000;
+constexpr long long kExactBytes = 300'000'000, kExactBytesWide = 80'000'000;
 bool select_keys_exact_pays(const Dims& dm, int dtype) {
   if (!select_keys_two_pass_applies(dm, dtype) || dm.T_max > kPackMaxKeys || score_packs(dm)) return false;
   const int n_keep = dm.n_ret < dm.C ? dm.n_ret : dm.C;
