@@ -67,6 +67,10 @@ __device__ __forceinline__ int decode_cache(const Dims& dm, const AttnArgs& a, i
 __device__ __forceinline__ int decode_tiles(const Dims& dm, const AttnArgs& a, int b, int kv) {
   return (decode_cache(dm, a, b, kv) + dm.C + kDcTile - 1) / kDcTile;
 }
+// the splits of a call's only sequence
+__device__ __forceinline__ int decode_splits_of_one(int tiles, int n_slots) {
+  return min(min(n_slots, (tiles + kDcWaves - 1) / kDcWaves), kMaxSplits);
+}
 // lane i of the wave: the splits of sequence i, and the sum over the earlier ones in *before
 __device__ __forceinline__ uint32_t decode_lane_splits(const Dims& dm, const AttnArgs& a, int kv, int n_slots,
                                                        uint32_t* before) {
@@ -80,16 +84,13 @@ __device__ __forceinline__ uint32_t decode_lane_splits(const Dims& dm, const Att
   return n;
 }
 __device__ __forceinline__ DecodeShare decode_share(const Dims& dm, const AttnArgs& a, int b, int kv, int n_slots) {
+  if (dm.b == 1) return {decode_splits_of_one(decode_tiles(dm, a, 0, kv), n_slots), 0};
   if (dm.b > 64) return {n_slots / dm.b, b * (n_slots / dm.b)};
   uint32_t before;
   const uint32_t n = decode_lane_splits(dm, a, kv, n_slots, &before);
   return {__builtin_amdgcn_readlane((int)n, b), __builtin_amdgcn_readlane((int)before, b)};
 }
 __device__ __forceinline__ DecodeWork decode_work(const Dims& dm, const AttnArgs& a, int slot, int kv, int n_slots) {
-  if (dm.b == 1) {
-    const DecodeShare s = decode_share(dm, a, 0, kv, n_slots);
-    return {slot < s.n_splits ? 0 : -1, slot, s.n_splits};
-  }
   if (dm.b > 64) {
     const int n = n_slots / dm.b;
     return {slot < n * dm.b ? slot / n : -1, slot % n, n};
@@ -103,7 +104,11 @@ __device__ __forceinline__ DecodeWork decode_work(const Dims& dm, const AttnArgs
 }
 
 // part: [n_kv, n_slots, kRec] float32
-template <int D>
+// ONE: one sequence and a list.  The list mostly has the B_max entries that there is room for, so the first tile of such a list is
+// looked up while the list's length travels: one fetch less in the chain, here and in the merge (32/8 heads, d 128, whole calls: 1 token
+// over 983 keys 23.6 -> 22.6 us, this kernel alone 22.7; 5 over 4000 75.4 -> 74.5; batches, whose shares go by all the lengths,
+// lost 1.4 % to it and stay as they were).
+template <int D, bool ONE>
 __global__ __launch_bounds__(kDcThreads, 2) void attn_decode_bf16(Dims dm, AttnArgs a, float* __restrict__ part,
                                                                   int n_slots) {
   using Cfg = DecodeCfg<D>;
@@ -117,14 +122,23 @@ __global__ __launch_bounds__(kDcThreads, 2) void attn_decode_bf16(Dims dm, AttnA
   const int C = dm.C, g = dm.g;
   const int n_rows = C * g;   // <= 32, checked by the launcher
   const bool sparse = a.k_idx != nullptr;
-  const DecodeWork work = decode_work(dm, a, blockIdx.x, kv, n_slots);
-  if (work.b < 0) return;   // block-uniform
+  DecodeWork work{0, (int)blockIdx.x, 0};
+  if constexpr (!ONE) {
+    work = decode_work(dm, a, blockIdx.x, kv, n_slots);
+    if (work.b < 0) return;   // block-uniform
+  }
   const int b = work.b;
-  const int n_cache = decode_cache(dm, a, b, kv);
-  const int n_keys = n_cache + C;
-  const int tiles = (n_keys + kDcTile - 1) / kDcTile;
-  const int t_end = (int)((long long)tiles * (work.split + 1) / work.n_splits);
-  int t = (int)((long long)tiles * work.split / work.n_splits) + w;   // this wave's tiles: every fourth
+  int n_cache, n_keys, t_end, t;   // cache slots and all slots of the list; this wave's tiles: every fourth
+  auto share_out = [&](int n) __attribute__((always_inline)) {
+    n_cache = n;
+    n_keys = n + C;
+    const int tiles = (n_keys + kDcTile - 1) / kDcTile;
+    if constexpr (ONE) work.n_splits = decode_splits_of_one(tiles, n_slots);
+    t_end = (int)((long long)tiles * (work.split + 1) / work.n_splits);
+    t = ONE && work.split >= work.n_splits ? t_end : (int)((long long)tiles * work.split / work.n_splits) + w;
+  };
+  const int n_given = decode_cache(dm, a, b, kv), n_most = min(dm.B_max, dm.T_max);
+  share_out(ONE ? n_most : n_given);
 
   const char* kcache = reinterpret_cast<const char*>(static_cast<const uint16_t*>(a.k_cache) + b * dm.kvs[0] + kv * dm.kvs[1]);
   const char* vcache = reinterpret_cast<const char*>(static_cast<const uint16_t*>(a.v_cache) + b * dm.kvs[0] + kv * dm.kvs[1]);
@@ -161,8 +175,15 @@ __global__ __launch_bounds__(kDcThreads, 2) void attn_decode_bf16(Dims dm, AttnA
       RV[i] = *reinterpret_cast<const u32x4*>(v_cache_u + (from_cache ? 0ull : v_chunk_delta) + off);
     }
   };
+  if (t < t_end) resolve(t);
+  if constexpr (ONE) {
+    if (n_given != n_most) {   // block-uniform
+      share_out(n_given);
+      if (t < t_end) resolve(t);
+    }
+    if (work.split >= work.n_splits) return;   // block-uniform
+  }
   if (t < t_end) {
-    resolve(t);
     issue(t);
     if (t + kDcWaves < t_end) resolve(t + kDcWaves);
   }
@@ -328,7 +349,8 @@ __global__ __launch_bounds__(kDcThreads, 2) void attn_decode_bf16(Dims dm, AttnA
 // One block per (row, kv, b).  The splits' (m, l) go through LDS once; then thread (dim e, split group sg) adds up the
 // O partials of its splits (independent, coalesced loads, unrolled), and the groups are combined through LDS.
 // The summation order is fixed by the indices alone, so the result does not depend on scheduling.
-template <int D>
+// ONE: as in attn_decode_bf16; the first partials are requested while the list's length travels.
+template <int D, bool ONE>
 __global__ __launch_bounds__(kDcThreads) void attn_decode_merge(Dims dm, AttnArgs a, const float* __restrict__ part,
                                                                 int n_slots) {
   constexpr int NG = kDcThreads / D;   // split groups
@@ -337,8 +359,16 @@ __global__ __launch_bounds__(kDcThreads) void attn_decode_merge(Dims dm, AttnArg
   __shared__ float s_m, s_l;
   const int r = blockIdx.x, kv = blockIdx.y, b = blockIdx.z;
   const int tid = threadIdx.x;
-  const DecodeShare share = decode_share(dm, a, b, kv, n_slots);
-  const int n_splits = share.n_splits;
+  DecodeShare share{0, 0};
+  int n_splits;
+  const int n_given = ONE ? decode_cache(dm, a, 0, kv) : 0, n_most = min(dm.B_max, dm.T_max);
+  auto splits_of = [&](int n) __attribute__((always_inline)) { return decode_splits_of_one((n + dm.C + kDcTile - 1) / kDcTile, n_slots); };
+  if constexpr (ONE) {
+    n_splits = splits_of(n_most);
+  } else {
+    share = decode_share(dm, a, b, kv, n_slots);
+    n_splits = share.n_splits;
+  }
   constexpr size_t sstride = DecodeCfg<D>::kRec;   // split s is s * sstride further
   const float* base = part + ((size_t)kv * n_slots + share.first) * sstride;
   // a thread's first eight outputs are requested together with (m, l), the next eight before these are used
@@ -348,12 +378,22 @@ __global__ __launch_bounds__(kDcThreads) void attn_decode_merge(Dims dm, AttnArg
 #pragma unroll
     for (int u = 0; u < 8; ++u) v[u] = base[min(s0 + u * NG, n_splits - 1) * sstride + r * D + e];
   };
-  float m_s = -INFINITY, l_s = 0.f;
-  if (tid < n_splits) {
-    m_s = base[tid * sstride + 32 * D + r];
-    l_s = base[tid * sstride + 32 * D + 32 + r];
-  }
+  float m_s, l_s;
+  auto load_ml = [&]() __attribute__((always_inline)) {
+    m_s = -INFINITY;
+    l_s = 0.f;
+    if (tid < n_splits) {
+      m_s = base[tid * sstride + 32 * D + r];
+      l_s = base[tid * sstride + 32 * D + 32 + r];
+    }
+  };
+  load_ml();
   load_v(sg);
+  if (ONE && n_given != n_most) {   // block-uniform
+    n_splits = splits_of(n_given);
+    load_ml();
+    load_v(sg);
+  }
   if (tid < 64) {   // n_splits <= 64: one wave holds all of them
     const float m = wave64_max(m_s);
     const float w = (m_s == -INFINITY) ? 0.f : __builtin_amdgcn_exp2f(m_s - m);
@@ -414,25 +454,27 @@ size_t attn_decode_ws_floats(const Dims& dm) {
   return (size_t)dm.n_kv * decode_slots(dm) * 32 * (2 + dm.d);
 }
 
-template <int D>
+template <int D, bool ONE>
 static hipError_t launch_decode_d(const Dims& dm, const AttnArgs& a, float* part, hipStream_t st) {
   using Cfg = DecodeCfg<D>;
   static std::atomic<uint64_t> lds_done{0};
-  const hipError_t e = ensure_dynamic_lds(reinterpret_cast<const void*>(&attn_decode_bf16<D>), Cfg::kLdsBytes, lds_done);
+  const hipError_t e = ensure_dynamic_lds(reinterpret_cast<const void*>(&attn_decode_bf16<D, ONE>), Cfg::kLdsBytes, lds_done);
   if (e != hipSuccess) return e;
   const int n_slots = decode_launch_slots(dm, a.k_idx != nullptr);
   // blocks that a short list leaves without work are not launched where the host can tell
   const long long tiles = ((long long)attended_cap(dm, a.k_idx != nullptr) + dm.C + kDcTile - 1) / kDcTile;
   const long long most = dm.b > 64 ? n_slots : dm.b * ((tiles + kDcWaves - 1) / kDcWaves);
-  hipLaunchKernelGGL((attn_decode_bf16<D>), dim3(n_slots < most ? n_slots : (int)most, dm.n_kv), dim3(kDcThreads),
+  hipLaunchKernelGGL((attn_decode_bf16<D, ONE>), dim3(n_slots < most ? n_slots : (int)most, dm.n_kv), dim3(kDcThreads),
                      Cfg::kLdsBytes, st, dm, a, part, n_slots);
-  hipLaunchKernelGGL((attn_decode_merge<D>), dim3(dm.C * dm.g, dm.n_kv, dm.b), dim3(kDcThreads), 0, st, dm, a, part,
+  hipLaunchKernelGGL((attn_decode_merge<D, ONE>), dim3(dm.C * dm.g, dm.n_kv, dm.b), dim3(kDcThreads), 0, st, dm, a, part,
                      n_slots);
   return hipGetLastError();
 }
 
 hipError_t launch_attn_decode_bf16(const Dims& dm, const AttnArgs& a, float* part, hipStream_t st) {
-  return dm.d == 64 ? launch_decode_d<64>(dm, a, part, st) : launch_decode_d<128>(dm, a, part, st);
+  if (dm.b == 1 && a.k_idx != nullptr)
+    return dm.d == 64 ? launch_decode_d<64, true>(dm, a, part, st) : launch_decode_d<128, true>(dm, a, part, st);
+  return dm.d == 64 ? launch_decode_d<64, false>(dm, a, part, st) : launch_decode_d<128, false>(dm, a, part, st);
 }
 
 }  // namespace quoka

@@ -201,6 +201,30 @@ def test_decode_attention_tiles_and_shares(case):
     check_attention(dict(case, dtype="bf16"))
 
 
+# one sequence: the kernels look a full list up before they know its length; lists that are full, one short of it, of fewer tiles or
+# splits, and empty, in arrays whose unused entries are out of range, and partials left by a longer list
+@pytest.mark.parametrize("count", [1600, 1599, 1500, 400, 127, 32, 1, 0])
+@pytest.mark.parametrize("d,chunk", [(128, 1), (64, 8), (128, 5)])
+def test_decode_attention_lists_of_one_sequence_shorter_than_their_array(d, chunk, count):
+    w = gen.make_custom(dtype="bf16", n_q=8, n_kv=2, d=d, chunk=chunk, n_retain=8, kv_lens=[2000], budgets=[1600], batch=1, seed=4)
+    buf = _buffers(w)
+    rng = np.random.default_rng(count)
+    lists = np.stack([np.sort(rng.choice(2000, size=1600, replace=False)) for _ in range(w.n_kv)]).astype(np.int32)
+    full = np.full(tuple(buf.k_idx.shape), 0x7FFFFFFF, dtype=np.int32)
+    for n in (1600, count):   # (the full list first: its partials are still there when the short one is merged)
+        host = full.copy()
+        host[0, :, :n] = lists[:, :n]
+        buf.k_idx.copy_(torch.from_numpy(host))
+        buf.k_cnt.fill_(n)
+        buf.out.fill_(float("nan"))
+        buf.lse.fill_(float("nan"))
+        buf.sparse_attn()
+        torch.cuda.synchronize()
+        want, want_lse = O.sparse_attn(w.Q[0], w.K[0], w.V[0], lists[:, :n], w.Kc[0], w.Vc[0], True)
+        assert P.max_abs(gen.from_torch(buf.out[0]), want) <= P.TOL_OUT["bf16"]
+        assert P.max_abs(gen.from_torch(buf.lse[0]), want_lse) <= 2e-2
+
+
 # top-B: the fused call and the stage calls against a sort of the same scores, bit for bit, whatever the scores look
 # like (ties at the cut, one score only, more keys in the cut bin than LDS takes, edges of the keys held per thread)
 BINNED_CASES = [
