@@ -475,7 +475,14 @@ __global__ __launch_bounds__(2 * kSetThreads, 2) void attn_bf16(Dims dm, AttnArg
   // Rows go out whole, 16 bytes a lane, through the wave's own piece of LDS; as the registers lie, a store covers 16 bytes of
   // each of 32 rows (32/8 heads, d 128, 1024 tokens over 983 keys 40.6 -> 39.4 us, 443 over 43 17.3 -> 16.7).
   constexpr int OLD = D + 8;   // pitch (elements)
-  if constexpr (!SPLIT) __syncthreads();   // all tiles consumed (SPLIT: the piece is the one this wave has just read)
+  // SPLIT: the piece is the one whose records this wave's lanes have just read, each its own; a lane's stores go to the
+  // others' records, so the reads of all lanes come first.  (A wave's LDS accesses stay in the order they are issued in: the
+  // fence orders the compiler and costs no instruction.)
+  if constexpr (SPLIT) {
+    wave_fence();
+  } else {
+    __syncthreads();   // all tiles consumed
+  }
   uint16_t* ot = reinterpret_cast<uint16_t*>(smem) + (SPLIT ? (size_t)slot * 64 * (2 + DB * 16) * 2 : (size_t)slot * 32 * OLD);
   if (!wave_on) return;
   const float inv = 1.0f / l_tot;
@@ -490,7 +497,7 @@ __global__ __launch_bounds__(2 * kSetThreads, 2) void attn_bf16(Dims dm, AttnArg
     }
   if (a.lse != nullptr && hf == 0 && tok < C)
     a.lse[(size_t)(b * dm.n_q + h) * dm.C + tok] = (m_run + log2f(l_tot)) * 0.6931471805599453f;
-  __builtin_amdgcn_wave_barrier();
+  wave_fence();   // (the rows are read back by other lanes)
   uint16_t* obase = static_cast<uint16_t*>(a.out) + b * dm.os[0] + h * dm.os[1] + (size_t)tok0 * dm.os[2] + (lane % CG) * 8;
 #pragma unroll
   for (int i = 0; i < 32 * CG / 64; ++i) {

@@ -171,6 +171,14 @@ __device__ __forceinline__ float other_half(float x) {
   return __uint_as_float((threadIdx.x & 32) ? lo : hi);
 }
 
+// Orders the memory accesses of one wave's lanes to each other: none is moved across it by the compiler.  (LDS accesses of a wave
+// are carried out in the order they are issued in.)
+__device__ __forceinline__ void wave_fence() {
+  __builtin_amdgcn_fence(__ATOMIC_ACQ_REL, "wavefront");
+  __builtin_amdgcn_wave_barrier();
+  __builtin_amdgcn_fence(__ATOMIC_ACQ_REL, "wavefront");
+}
+
 // Exclusive prefix sum of one uint per thread over a block of NT threads (NT multiple of 64, <= 1024).
 // `wsum` is LDS scratch of at least NT/64 + 1 uints.  Returns the exclusive prefix; *total gets the block sum.
 template <int NT>

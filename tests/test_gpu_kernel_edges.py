@@ -181,6 +181,31 @@ def test_bf16_attention_whole_lists_of_one_sequence(case):
     check_attention(dict(case, dtype="bf16"), rows=[0, 31, 32, 1000, case["chunk"] - 33, case["chunk"] - 1])
 
 
+# rows go out through LDS, which the waves' hand-over records (blocks of four) or the tiles (blocks of eight) held before: every row,
+# the last row block not full, into contiguous outputs and into rows that lie apart, whose gaps stay as they are
+@pytest.mark.parametrize("scale_f32", [False, True], ids=["", "scale-f32"])
+@pytest.mark.parametrize("case", [
+    dict(n_q=16, n_kv=2, d=128, chunk=2070, kv_lens=[50], budgets=[40]),        # blocks of four
+    dict(n_q=16, n_kv=2, d=64, chunk=2070, kv_lens=[50], budgets=[40]),
+    dict(n_q=14, n_kv=2, d=64, chunk=5, kv_lens=[129], budgets=[129]),          # one row block a head
+    dict(n_q=16, n_kv=2, d=128, chunk=2070, kv_lens=[3000], budgets=[2500]),    # blocks of eight
+], ids=_id)
+def test_bf16_attention_rows_of_whole_lists(case, scale_f32):
+    flags, rows = 16 if scale_f32 else 0, sorted({0, 1, case["chunk"] // 2, case["chunk"] - 2, case["chunk"] - 1})
+    check_attention(dict(case, dtype="bf16"), rows=rows, score_flags=flags)
+    w = gen.make_custom(dtype="bf16", n_retain=8, seed=22, batch=1, **case)
+    buf = _buffers(w, score_flags=flags)
+    n, d = w.budgets[0], w.d
+    buf.k_idx.copy_(torch.arange(n, dtype=torch.int32).expand(1, w.n_kv, n))
+    buf.k_cnt.fill_(n)
+    buf.sparse_attn()
+    wide = torch.full((1, w.n_q, w.chunk, d + 24), 7.0, dtype=torch.bfloat16, device="cuda:0")
+    buf.shape.o_stride[:] = wide.stride()[:3]
+    buf.sparse_attn(out=wide[..., :d])
+    torch.cuda.synchronize()
+    assert torch.equal(wide[..., :d], buf.out) and bool((wide[..., d:] == 7.0).all())
+
+
 # decode kernel: single slots, tiles of 32 short of and past full, fewer tiles than waves or blocks, batches whose shares
 # of the blocks differ, batches beyond one wave's lanes
 DECODE_CASES = [
