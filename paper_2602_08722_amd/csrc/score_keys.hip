@@ -26,7 +26,12 @@ namespace quoka {
 // FUSE (PACK, every query retained): Qbar is not there yet.  Every block works its head's few rows out for itself, in
 // place of reading them (8 heads, 8192 keys, one query: a launch of 3.4 us saved, 1 us added here; call 26.1 -> 25.0 us).
 // HIST: the scores are also counted in the head's histogram of kScoreBins bins (hist_ws: the zeroed head of the selection's
-// workspace), in LDS first, so that the selection starts from the finished histogram.
+// workspace), in LDS first, so that the selection starts from the finished histogram.  Its blocks share out what the caches
+// hold, not what there is room for: a sequence's blocks its tiles, and in a batch a KV head's blocks the tiles of all sequences
+// (with a fixed share of T_cap most had nothing to do in a long cache that is not full yet, or in the shorter ones of a batch).
+// Whole calls, fixed share -> this: 8 heads, room for 131072 keys, 64 queries, over 8000 keys 74.6 -> 42.1 us, 33000 74.1 -> 53.9,
+// 131072 93.4 -> 92.9; 2 heads of 13 sequences, one of 42306 keys and twelve of 2000 82.5 -> 56.9; batches of equal lengths
+// 0.99 - 1.02 of the time.
 // TERMS: the query operands lie ready in `terms`.  (A template parameter: as a run-time choice it cost the calls that
 // convert Qbar themselves 1.5 us, 2 x 8 heads of 8337 keys 12.0 -> 13.7.)
 template <int D, int QB, bool EXACT, bool PACK, bool FUSE, bool TERMS, bool HIST>
@@ -50,13 +55,30 @@ __global__ __launch_bounds__(kScThreads, 2) void score_bf16(Dims dm, const float
     for (int i = threadIdx.x; i < kScoreBins / 2; i += kScThreads) bins[i] = 0u;   // (a barrier follows before the first count)
   }
 
-  const int kv = blockIdx.y, b = blockIdx.z;
-  const int t_begin = blockIdx.x * tiles_per_wg * kScTile;
-
   const int tid = threadIdx.x, lane = tid & 63;
   const int w = __builtin_amdgcn_readfirstlane(tid >> 6);
   const int qb = w % QB, kg = w / QB;
   const int li = lane & 31, hf = lane >> 5;
+
+  const int kv = blockIdx.y;
+  int b = blockIdx.z;
+  int t_begin = blockIdx.x * tiles_per_wg * kScTile;
+  // (HIST: `zero_words` is the number of blocks of a KV head, or with tiles_per_wg == 0 of all its sequences together, among which
+  // they are shared out; as grid sizes these would be fetched by a load of their own, a call of one head 1 us longer)
+  const bool shared = HIST && tiles_per_wg == 0;
+  const int blocks = (int)zero_words;
+  if (shared) {
+    const uint32_t tiles = lane < dm.b ? (uint32_t)(max(min(kv_lens[lane * dm.ls], dm.T_cap), 0) + kScTile - 1) / kScTile : 0u;
+    const uint32_t total = max((uint32_t)__builtin_amdgcn_readlane((int)wave_incl_scan_u32(tiles), 63), 1u);
+    const uint32_t n = min(tiles, 1u + tiles * (uint32_t)(blocks - dm.b) / total);   // (2^17 keys and 512 blocks at most)
+    const uint32_t upto = wave_incl_scan_u32(n);
+    const unsigned long long mine = __builtin_amdgcn_ballot_w64(blockIdx.x >= upto - n && blockIdx.x < upto);
+    if (mine == 0) return;   // block-uniform
+    b = (int)__builtin_ctzll(mine);
+    const int nb = __builtin_amdgcn_readlane((int)n, b), first = __builtin_amdgcn_readlane((int)(upto - n), b);
+    tiles_per_wg = (__builtin_amdgcn_readlane((int)tiles, b) + nb - 1) / nb;
+    t_begin = ((int)blockIdx.x - first) * tiles_per_wg * kScTile;
+  }
 
   // rows of this (batch, KV head) are addressed as base + 32-bit byte offset (the host checks the 4 GiB span)
   const char* kbase = reinterpret_cast<const char*>(kc + b * dm.kvs[0] + kv * dm.kvs[1]);
@@ -76,8 +98,16 @@ __global__ __launch_bounds__(kScThreads, 2) void score_bf16(Dims dm, const float
       R[i] = *reinterpret_cast<const u32x4*>(kbase + ((uint32_t)row * row_bytes + (uint32_t)cg * 16u));
     }
   };
-  issue(0, RA);   // the first K tile is in flight while the length arrives and the query operands are prepared
+  if constexpr (!HIST) issue(0, RA);   // the first K tile is in flight while the length arrives and the query operands are prepared
   const int T = min(kv_lens[b * dm.ls], dm.T_cap);
+  if constexpr (HIST) {
+    if (!shared && T != dm.T_cap) {   // the cache is not full
+      tiles_per_wg = (max(T, 0) + kScTile * blocks - 1) / (kScTile * blocks);
+      t_begin = blockIdx.x * tiles_per_wg * kScTile;
+    }
+    if (t_begin >= T) return;   // block-uniform
+    issue(0, RA);
+  }
   const float* qhead = qbar + (size_t)(b * dm.n_kv + kv) * n_keep * D;
   if constexpr (FUSE) {
     __shared__ __align__(16) float qrows[kPackRows * D];   // (read 16 bytes at a time)
@@ -378,8 +408,16 @@ static hipError_t launch_bf16(const Dims& dm, const float* qbar, const void* kc,
   const hipError_t e =
       ensure_dynamic_lds(reinterpret_cast<const void*>(&score_bf16<D, QB, EXACT, PACK, FUSE, TERMS, HIST>), lds, lds_done);
   if (e != hipSuccess) return e;
-  const int nt = (dm.T_cap + kScTile - 1) / kScTile, tpw = tiles_per_block(dm);
+  const int nt = (dm.T_cap + kScTile - 1) / kScTile;
+  int tpw = tiles_per_block(dm);
   dim3 grid((nt + tpw - 1) / tpw, dm.n_kv, dm.b);
+  if (HIST) {
+    if (dm.b > 1 && dm.b <= kWave && 512 / dm.n_kv >= 2 * dm.b) {
+      grid = dim3(512 / dm.n_kv, dm.n_kv, 1);
+      tpw = 0;
+    }
+    zero_words = grid.x;
+  }
   hipLaunchKernelGGL((score_bf16<D, QB, EXACT, PACK, FUSE, TERMS, HIST>), grid, dim3(kScThreads), lds, st, dm, qbar,
                      static_cast<const uint16_t*>(kc), kv_lens, scores, n_keep, tpw, zero, zero_words, fq,
                      terms, hist_ws);

@@ -282,3 +282,33 @@ def test_chunk_attn_selects_from_exact_scores(kind, case):
     for b in range(w.batch):
         T, n = w.kv_lens[b], int(cnt[b, 0])
         assert torch.equal(buf.scores[b, :, :T], sc[b, :, :T]) and torch.equal(buf.k_idx[b, :, :n], idx[b, :, :n])
+
+
+# The exact route's scoring blocks share out what the caches hold: caches with room to spare, with nothing, one key, and tiles of 128
+# just short of, at and past full; batches with one long sequence, with empty ones, and with more than a wave has lanes
+@pytest.mark.parametrize("n_kv,d,T_max,lens", [
+    (2, 128, 70000, [0]), (2, 128, 70000, [1]), (2, 64, 70000, [127]), (2, 128, 70000, [128]), (1, 64, 131072, [129]),
+    (8, 128, 40000, [8000]), (2, 128, 70000, [69999]),
+    (2, 64, 70000, [70000, 0, 1, 128, 129, 5000]), (1, 128, 50000, [0, 0, 50000]), (2, 64, 33000, [0, 0, 0]),
+    (4, 64, 33000, [3, 33000, 0, 77, 20000]),
+    (1, 64, 33000, [33000 - 517 * i for i in range(64)]), (1, 64, 32800, [32800 - 499 * i for i in range(65)]),
+], ids=lambda v: f"{len(v)}x{v[0]}" if isinstance(v, list) else str(v))
+def test_chunk_attn_of_caches_with_room_to_spare(n_kv, d, T_max, lens):
+    pk = _pk()
+    b, C = len(lens), 40
+    g = torch.Generator(device="cuda").manual_seed(50)
+    q, k, v, kc, vc = (torch.randn(b, n, t, d, device="cuda", generator=g, dtype=torch.float32).bfloat16()
+                       for n, t in ((2 * n_kv, C), (n_kv, T_max), (n_kv, T_max), (n_kv, C), (n_kv, C)))
+    buf = pk.ChunkBuffers(q, k, v, kc, vc, lens, [t // 9 + 1 for t in lens], 16, max_budget=T_max // 8)
+    sc, idx, cnt = _staged(buf)
+    buf.scores.fill_(float("nan"))
+    buf.k_idx.fill_(-1)
+    buf.k_cnt.fill_(-1)
+    buf.workspace.fill_(0x5A)
+    buf.chunk_attn()
+    torch.cuda.synchronize()
+    assert torch.equal(buf.k_cnt, cnt)
+    for i, T in enumerate(lens):
+        n = int(cnt[i, 0])
+        assert n == min(T // 9 + 1, T)
+        assert torch.equal(buf.scores[i, :, :T], sc[i, :, :T]) and torch.equal(buf.k_idx[i, :, :n], idx[i, :, :n])
