@@ -327,17 +327,46 @@ struct HeadSelectLds {
 };
 constexpr int kHeadCands = 4;   // candidates a thread of the head's block holds in registers
 
+// use(number, value...) for each of n entries of one or two arrays in memory, by a block of NT threads.  Eight of a thread's are
+// requested at a time: one by one, the list of a head whose scores all share a bin is 512 fetches in a row, in every emitting block
+// (8 heads of 131072 equal keys, whole calls, 64 queries 408 -> 195 us, 2 queries 384 -> 173; eight different keys 143 -> 122).
+constexpr int kListRun = 8;
+template <int NT, typename F>
+__device__ __forceinline__ void for_each_listed(const uint32_t* __restrict__ a, uint32_t n, F use) {
+  for (uint32_t i0 = threadIdx.x; i0 < n; i0 += kListRun * NT) {
+    uint32_t v[kListRun];
+#pragma unroll
+    for (int j = 0; j < kListRun; ++j) v[j] = a[min(i0 + NT * j, n - 1)];
+#pragma unroll
+    for (int j = 0; j < kListRun; ++j)
+      if (i0 + NT * j < n) use(v[j]);
+  }
+}
+template <int NT, typename F>
+__device__ __forceinline__ void for_each_listed(const uint32_t* __restrict__ a, const uint32_t* __restrict__ b, uint32_t n, F use) {
+  for (uint32_t i0 = threadIdx.x; i0 < n; i0 += kListRun * NT) {
+    uint32_t v[kListRun], u[kListRun];
+#pragma unroll
+    for (int j = 0; j < kListRun; ++j) {
+      v[j] = a[min(i0 + NT * j, n - 1)];
+      u[j] = b[min(i0 + NT * j, n - 1)];
+    }
+#pragma unroll
+    for (int j = 0; j < kListRun; ++j)
+      if (i0 + NT * j < n) use(v[j], u[j]);
+  }
+}
+
 template <int NT>
 __device__ __forceinline__ void stream_radix_select_desc(const uint32_t* __restrict__ keys, uint32_t n, uint32_t need,
                                                          RadixSelectLds& L, uint32_t* cut_key, uint32_t* need_eq) {
   const int tid = threadIdx.x, lane = tid & 63, w = tid >> 6;
   for (int i = tid; i < 768; i += NT) (&L.hist[0][0])[i] = 0u;
   uint32_t kmin = 0xFFFFFFFFu, kmax = 0u;
-  for (uint32_t i = tid; i < n; i += NT) {
-    const uint32_t k = keys[i];
+  for_each_listed<NT>(keys, n, [&](uint32_t k) {
     kmin = min(kmin, k);
     kmax = max(kmax, k);
-  }
+  });
   kmin = wave_min_u32(kmin);
   kmax = wave_max_u32(kmax);
   if (lane == 0) {
@@ -358,10 +387,9 @@ __device__ __forceinline__ void stream_radix_select_desc(const uint32_t* __restr
   while (hi > 0) {
     const int lo_bit = max(hi - 8, 0);
     const uint32_t dmask = (1u << (hi - lo_bit)) - 1u;
-    for (uint32_t i = tid; i < n; i += NT) {
-      const uint32_t k = keys[i];
+    for_each_listed<NT>(keys, n, [&](uint32_t k) {
       if ((k & mask) == prefix) atomicAdd(&h_use[(k >> lo_bit) & dmask], 1u);
-    }
+    });
     __syncthreads();
     // h_clear was last read before this barrier (during the previous pass) and is next written after the next one
     if (!first && tid < 256) h_clear[tid] = 0u;
@@ -442,10 +470,9 @@ __global__ __launch_bounds__(kSelHeadThreads) void sel_band_select(Dims dm, floa
       if ((uint32_t)(tid + kSelHeadThreads * i) < n_c && ck[i] >= tau)
         atomicAdd(&cnt[cp[i] / kSelTile], ck[i] > tau ? 0x10000u : 1u);
   } else {
-    for (uint32_t i = tid; i < n_c; i += kSelHeadThreads) {
-      const uint32_t k = c.w.cand_key[i];
-      if (k >= tau) atomicAdd(&cnt[c.w.cand_pos[i] / kSelTile], k > tau ? 0x10000u : 1u);
-    }
+    for_each_listed<kSelHeadThreads>(c.w.cand_key, c.w.cand_pos, n_c, [&](uint32_t k, uint32_t pos) {
+      if (k >= tau) atomicAdd(&cnt[pos / kSelTile], k > tau ? 0x10000u : 1u);
+    });
   }
   __syncthreads();
   // Output offsets.  Thread t owns tiles t*tpt .. +tpt; first the number of cut-equal band keys before every tile
@@ -698,12 +725,11 @@ __global__ __launch_bounds__(kSelThreads) void sel_finish(Dims dm, float* __rest
       eq0 += earlier && ck[i] == tau ? 1u : 0u;
     }
   } else {
-    for (uint32_t i = tid; i < n_c; i += kSelThreads) {
-      const uint32_t k = c.w.cand_key[i];
-      const bool earlier = c.w.cand_pos[i] < (uint32_t)t0;
+    for_each_listed<kSelThreads>(c.w.cand_key, c.w.cand_pos, n_c, [&](uint32_t k, uint32_t pos) {
+      const bool earlier = pos < (uint32_t)t0;
       gt += earlier && k > tau ? 1u : 0u;
       eq0 += earlier && k == tau ? 1u : 0u;
-    }
+    });
   }
   if (gt) atomicAdd(&sums[2], gt);
   if (eq0) atomicAdd(&sums[3], eq0);

@@ -312,3 +312,28 @@ def test_chunk_attn_of_caches_with_room_to_spare(n_kv, d, T_max, lens):
         n = int(cnt[i, 0])
         assert n == min(T // 9 + 1, T)
         assert torch.equal(buf.scores[i, :, :T], sc[i, :, :T]) and torch.equal(buf.k_idx[i, :, :n], idx[i, :, :n])
+
+
+# More candidates than a block holds in registers, listed in memory and fetched in runs of 2048 (8192 where one block selects for a
+# head): lists just short of, at and past whole runs; all scores equal, or eight values of which the cut's is an eighth
+@pytest.mark.parametrize("values", [1, 8])
+@pytest.mark.parametrize("call,chunk", [("chunk_attn", 40), ("chunk_attn", 2), ("select_keys", 40)], ids=["exact", "one-pass", "two-pass"])
+def test_candidates_listed_in_memory(call, chunk, values):
+    pk = _pk()
+    lens = [1025, 2047, 2048, 2049, 4096 * 8 + 1, 8191, 8192, 8193] if values == 1 else [33000, 16384, 16392, 8200, 40, 20000, 30000, 24576]
+    g = torch.Generator(device="cuda").manual_seed(51)
+    q, k, v, kc, vc = (torch.randn(8, n, t, 64, device="cuda", generator=g).bfloat16()
+                       for n, t in ((2, chunk), (1, 33000), (1, 33000), (1, chunk), (1, chunk)))
+    k = k[:, :, torch.randint(0, values, (33000,), device="cuda", generator=g)].contiguous()
+    buf = pk.ChunkBuffers(q, k, v, kc, vc, lens, [t // 2 + 1 for t in lens], 16)
+    sc, idx, cnt = _staged(buf)
+    buf.select_queries()
+    buf.k_idx.fill_(-1)
+    buf.k_cnt.fill_(-1)
+    getattr(buf, call)()
+    torch.cuda.synchronize()
+    assert torch.equal(buf.k_cnt, cnt)
+    for i, T in enumerate(lens):
+        n = int(cnt[i, 0])
+        want = O.topk_keys(gen.from_torch(sc)[i][:, :T], n)
+        assert np.array_equal(gen.from_torch(idx)[i][:, :n], want) and np.array_equal(gen.from_torch(buf.k_idx)[i][:, :n], want)
