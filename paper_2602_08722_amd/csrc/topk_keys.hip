@@ -31,7 +31,7 @@ __device__ __forceinline__ uint32_t radix_bins(int pass) { return pass == 2 ? 10
 // The cut: one LDS histogram over 2048 equal bins between the smallest and the largest score, a scan for the bin that
 // holds the B-th largest, and a count of ranks among that bin's few keys.  (Equal bins and not key bits: the scores of a
 // head lie close together, and a lane's atomic on an occupied bin waits for the others.)  Where more keys share the
-// bin than LDS has room for, or the scores admit no such bins, the block-wide radix select decides.
+// bin than are ranked (cut_keys), or the scores admit no such bins, the block-wide radix select decides.
 // The ordered compaction needs no scan over threads: per register, one wave ballot (two where only some of the keys
 // equal to the cut are taken) gives every lane the number of earlier taken positions of its wave; how many earlier waves
 // take follows from their counts above the cut's bin and from the positions in the list of that bin's keys.
@@ -43,12 +43,16 @@ __device__ __forceinline__ uint32_t radix_bins(int pass) { return pass == 2 ? 10
 // counts in the pass that lists the candidates): 8 heads of 8192 scores 7.9 -> 6.4 -> 6.1, 8 of 32768 20.4 -> 13.2 -> 12.0, of
 // 12000 8.1 -> 7.0.
 constexpr int kCutBins = 2048;
-constexpr int kCutKeys = 256;          // candidates a block ranks; more are radix-selected
-template <int NT>
-struct CutLds {
+// Candidates a block ranks; more are radix-selected, which goes over all keys of a thread again.  Ranking takes NT / (their number,
+// rounded up) lanes a key.  Measured (us, ranked / radix-selected): 512 threads, 1000 scores, 96 candidates 4.7 / 5.3, 160 5.9 / 5.4;
+// 1024 threads, 4 keys each, 200 7.3 / 7.6, 300 11.1 / 7.7; 16 keys 256 14.3 / 15.1, 350 16.3 / 15.3; 24 keys 400 19.5 / 20.3; 32 keys
+// 460 23.4 / 25.7.
+constexpr int cut_keys(int nt, int ipt) { return nt == 512 ? 128 : ipt <= 12 ? 256 : ipt <= 28 ? 64 + 16 * ipt : 512; }
+template <int NT, int KEYS>
+struct __align__(16) CutLds {
   uint32_t hist[kCutBins];
-  float key[kCutKeys];
-  int pos[kCutKeys];
+  float key[KEYS];                     // (read 16 bytes at a time)
+  int pos[KEYS];
   uint32_t wmin[NT / 64], wmax[NT / 64], wsum[NT / 64];
   uint32_t above[NT / 64];             // a wave's scores in the bins above the cut's
   uint32_t n, bin, need, need_eq;
@@ -69,7 +73,8 @@ __global__ __launch_bounds__(NT) void topk_small(Dims dm, const float* __restric
   constexpr int BPT = kCutBins / NT;   // bins per thread
   constexpr bool kKeepBins = IPT <= 16;
   __shared__ RadixSelectLds rs;
-  __shared__ __align__(16) CutLds<NT> cl;
+  constexpr int kCutKeys = cut_keys(NT, IPT);
+  __shared__ CutLds<NT, kCutKeys> cl;
   __shared__ uint32_t wgt[NW], weq[NW];
   const int kv = blockIdx.x, b = blockIdx.y;
   const int tid = threadIdx.x, lane = tid & 63, w = __builtin_amdgcn_readfirstlane(tid >> 6);
@@ -198,13 +203,20 @@ __global__ __launch_bounds__(NT) void topk_small(Dims dm, const float* __restric
     int cap = NT / 16;
     while (cap < (int)n_in) cap <<= 1;
     const int P = NT / cap;   // 16 .. 2
+    static_assert(kCutKeys <= NT / 2 && kCutKeys % 4 == 0, "");
     const int e = tid / P, part = tid % P;
     const float k = cl.key[min(e, (int)n_in - 1)];
     uint32_t cnt = 0;   // keys greater (low half), greater or equal (high half)
-    for (int j = part; j < (int)n_in; j += P) {
-      const float o = cl.key[j];
-      cnt += (o > k ? 1u : 0u) + (o >= k ? 0x10000u : 0u);
+    auto count = [&](float o) __attribute__((always_inline)) { cnt += (o > k ? 1u : 0u) + (o >= k ? 0x10000u : 0u); };
+    int j = part;
+    if (n_in > NT / 16u) {   // four at a time
+      for (j = 4 * part; j + 3 < (int)n_in; j += 4 * P) {
+        const float4 o = *reinterpret_cast<const float4*>(&cl.key[j]);
+        count(o.x); count(o.y); count(o.z); count(o.w);
+      }
+      j = ((int)n_in & ~3) + part;
     }
+    for (; j < (int)n_in; j += P) count(cl.key[j]);
     for (int o = 1; o < P; o <<= 1) cnt += (uint32_t)__shfl_xor((int)cnt, o, kWave);
     if (e < (int)n_in && (cnt & 0xFFFFu) < need && need <= (cnt >> 16)) {   // (equal keys all write the same)
       cl.tau = k;

@@ -340,17 +340,12 @@ def test_top_b_ties_of_signed_zeros_and_nan_on_both_sides_of_the_register_path(T
         assert np.array_equal(gen.from_torch(buf.k_idx)[0][:, :B], want)
 
 
-# threads and keys a thread: the sizes on either side of every line; scores that fill one bin with few, up to 256 (ranked) or more
-# (radix-selected) keys
-@pytest.mark.parametrize("T", [2, 63, 511, 512, 513, 1024, 1025, 2048, 2049, 4096, 4097, 8192, 8193, 12288, 12289, 16384, 28672, 28673])
-@pytest.mark.parametrize("crowd", [0, 200, 256, 257])
-def test_top_b_threads_keys_and_crowded_bins(T, crowd):
-    if crowd >= T:
-        pytest.skip("fewer scores than that")
+def check_crowded_top_b(T, crowd):
+    """Two heads of T scores, `crowd` of them within a thousandth of a bin around the cut, a third of these equal."""
     rng = np.random.default_rng(T + crowd)
     s = rng.standard_normal((2, T)).astype(np.float32)
     B = max(1, T // 3)
-    if crowd:   # `crowd` keys within a thousandth of a bin around the cut, a third of them equal
+    if crowd:
         at = np.stack([rng.choice(T, size=crowd, replace=False) for _ in range(2)])
         cut = np.sort(s, axis=1)[:, T - B][:, None]
         near = (cut + rng.choice(np.array([0, 0, 1, 2, 3, 4], dtype=np.float32), size=at.shape) * np.float32(1e-7)).astype(np.float32)
@@ -362,4 +357,22 @@ def test_top_b_threads_keys_and_crowded_bins(T, crowd):
     buf.topk_keys()
     torch.cuda.synchronize()
     want = np.stack([np.sort(np.argsort(-r, kind="stable")[:B]) for r in s])
-    assert np.array_equal(gen.from_torch(buf.k_idx)[0][:, :B], want)
+    assert np.array_equal(gen.from_torch(buf.k_idx)[0][:, :B], want), f"{crowd} keys"
+
+
+# threads and keys a thread: the sizes on either side of every line; scores that fill one bin with few, up to 256 or more keys
+@pytest.mark.parametrize("T,crowd", [
+    (T, crowd) for T in (2, 63, 511, 512, 513, 1024, 1025, 2048, 2049, 4096, 4097, 8192, 8193, 12288, 12289, 16384, 28672, 28673)
+    for crowd in (0, 200, 256, 257) if crowd < T])
+def test_top_b_threads_keys_and_crowded_bins(T, crowd):
+    check_crowded_top_b(T, crowd)
+
+
+# how many keys of the cut's bin are ranked (`line`; the bin holds a few more than the crowd), one or four at a time, and how many are
+# radix-selected
+@pytest.mark.parametrize("T,line", [(500, 128), (2048, 128), (2049, 256), (12288, 256), (16384, 320), (20480, 384), (24576, 448),
+                                    (28672, 512), (32768, 512)])
+def test_top_b_ranked_and_radix_selected_bins(T, line):
+    few = 32 if line == 128 else 64
+    for crowd in [few - 2, few - 1, few, few + 1, few + 2, few + 3, 2 * few - 1] + [line + i for i in range(-12, 3)]:
+        check_crowded_top_b(T, min(crowd, T - 1))
