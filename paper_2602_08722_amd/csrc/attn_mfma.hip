@@ -84,7 +84,11 @@ struct AttnCfg {
 // times those of unit-variance inputs (0.03 absolute at four times, 0.06 at eight).
 // KSPLIT: the key list is shared by a.n_splits blocks, each of which writes a partial result.  (A template parameter: as
 // a run-time switch it cost the unsplit launches 1.5-2 %.)
-template <int D, bool SPLIT, bool XS, bool KSPLIT>
+// WHOLE (not KSPLIT): rows go out whole, 16 bytes a lane, through the wave's own piece of LDS; as the registers lie, a store covers
+// 16 bytes of each of 32 rows (32/8 heads, d 128, 1024 tokens over 983 keys 40.6 -> 39.2 us, 443 over 43 17.3 -> 16.6, 32 over 40
+// 10.9 -> 10.0).  Blocks of fewer than 64 rows in all are the faster without (2 KV heads of 2, d 64, 17 tokens 6.4 / 6.6 us), and so are
+// blocks of eight at d 64 (1 - 1.5 % in launches of many rounds).  (As a run-time choice it cost all others 2 - 5 %.)
+template <int D, bool SPLIT, bool XS, bool KSPLIT, bool WHOLE>
 __global__ __launch_bounds__(2 * kSetThreads, 2) void attn_bf16(Dims dm, AttnArgs a) {
   using Cfg = AttnCfg<D, SPLIT>;
   constexpr int KT = Cfg::KT, KS = Cfg::KS, LD = Cfg::LD, LDV = Cfg::LDV, CG = Cfg::CG, RPI = Cfg::RPI, NLD = Cfg::NLD,
@@ -454,7 +458,7 @@ __global__ __launch_bounds__(2 * kSetThreads, 2) void attn_bf16(Dims dm, AttnArg
     }
     return;
   }
-  if constexpr (D == 64 && !SPLIT) {   // (here rows that go out whole cost 1 - 1.5 % in launches of many rounds)
+  if constexpr (!WHOLE) {
     if (wave_on && tok < C) {
       const float inv = 1.0f / l_tot;
       uint16_t* orow = static_cast<uint16_t*>(a.out) + b * dm.os[0] + h * dm.os[1] + (size_t)tok * dm.os[2];
@@ -472,8 +476,6 @@ __global__ __launch_bounds__(2 * kSetThreads, 2) void attn_bf16(Dims dm, AttnArg
     }
     return;
   }
-  // Rows go out whole, 16 bytes a lane, through the wave's own piece of LDS; as the registers lie, a store covers 16 bytes of
-  // each of 32 rows (32/8 heads, d 128, 1024 tokens over 983 keys 40.6 -> 39.4 us, 443 over 43 17.3 -> 16.7).
   constexpr int OLD = D + 8;   // pitch (elements)
   // SPLIT: the piece is the one whose records this wave's lanes have just read, each its own; a lane's stores go to the
   // others' records, so the reads of all lanes come first.  (A wave's LDS accesses stay in the order they are issued in: the
@@ -499,11 +501,15 @@ __global__ __launch_bounds__(2 * kSetThreads, 2) void attn_bf16(Dims dm, AttnArg
     a.lse[(size_t)(b * dm.n_q + h) * dm.C + tok] = (m_run + log2f(l_tot)) * 0.6931471805599453f;
   wave_fence();   // (the rows are read back by other lanes)
   uint16_t* obase = static_cast<uint16_t*>(a.out) + b * dm.os[0] + h * dm.os[1] + (size_t)tok0 * dm.os[2] + (lane % CG) * 8;
+  u32x4 rows_out[32 * CG / 64];   // all read before the first goes out
+#pragma unroll
+  for (int i = 0; i < 32 * CG / 64; ++i)
+    rows_out[i] = *reinterpret_cast<const u32x4*>(ot + (i * (64 / CG) + lane / CG) * OLD + (lane % CG) * 8);
+  __builtin_amdgcn_sched_barrier(0);
 #pragma unroll
   for (int i = 0; i < 32 * CG / 64; ++i) {
     const int r = i * (64 / CG) + lane / CG;
-    const u32x4 x = *reinterpret_cast<const u32x4*>(ot + r * OLD + (lane % CG) * 8);
-    if (tok0 + r < C) *reinterpret_cast<u32x4*>(obase + (size_t)r * dm.os[2]) = x;
+    if (tok0 + r < C) *reinterpret_cast<u32x4*>(obase + (size_t)r * dm.os[2]) = rows_out[i];
   }
 }
 
@@ -620,13 +626,13 @@ __global__ __launch_bounds__(64 * kMergeWaves) void attn_bf16_merge(Dims dm, Att
     a.lse[(size_t)(b * dm.n_q + h) * dm.C + tok] = (m + log2f(l)) * 0.6931471805599453f;
 }
 
-template <int D, bool SPLIT, bool XS, bool KSPLIT>
+template <int D, bool SPLIT, bool XS, bool KSPLIT, bool WHOLE>
 static hipError_t launch_variant(const Dims& dm, const AttnArgs& a, hipStream_t st) {
   using Cfg = AttnCfg<D, SPLIT>;
   constexpr size_t lds = Cfg::kLdsBytes;
   static std::atomic<uint64_t> lds_done{0};
   const hipError_t e =
-      ensure_dynamic_lds(reinterpret_cast<const void*>(&attn_bf16<D, SPLIT, XS, KSPLIT>), lds, lds_done);
+      ensure_dynamic_lds(reinterpret_cast<const void*>(&attn_bf16<D, SPLIT, XS, KSPLIT, WHOLE>), lds, lds_done);
   if (e != hipSuccess) return e;
   const int nrb = dm.g * ((dm.C + 31) / 32);
   const int half = (nrb + 1) / 2;
@@ -636,7 +642,7 @@ static hipError_t launch_variant(const Dims& dm, const AttnArgs& a, hipStream_t 
   // (measured at 512 blocks, 4096-token chunk over 131072 cached tokens: 3.5 % faster than pairing; a launch of one
   // round needs the pairing, or its last block sets the time alone)
   aa.adjacent = (long long)grid.x * grid.y * grid.z >= 2 * kComputeUnits ? 1 : 0;
-  hipLaunchKernelGGL((attn_bf16<D, SPLIT, XS, KSPLIT>), grid, dim3(2 * kSetThreads), lds, st, dm, aa);
+  hipLaunchKernelGGL((attn_bf16<D, SPLIT, XS, KSPLIT, WHOLE>), grid, dim3(2 * kSetThreads), lds, st, dm, aa);
   if (KSPLIT) {
     const int runs = (a.n_splits + kMergeRun - 1) / kMergeRun, waves = runs < kMergeWaves ? runs : kMergeWaves;
     const int dims = waves * (D / 32) <= kMergeWaves ? D / 32 : 1;
@@ -645,11 +651,18 @@ static hipError_t launch_variant(const Dims& dm, const AttnArgs& a, hipStream_t 
   return hipGetLastError();
 }
 
+template <int D, bool SPLIT, bool XS>
+static hipError_t launch_dsx(const Dims& dm, const AttnArgs& a, hipStream_t st) {
+  if (a.n_splits > 1) return launch_variant<D, SPLIT, XS, true, false>(dm, a, st);
+  if constexpr (SPLIT) {
+    if (dm.g * ((dm.C + 31) / 32) * (dm.C < 32 ? dm.C : 32) < 64) return launch_variant<D, SPLIT, XS, false, false>(dm, a, st);
+  }
+  return launch_variant<D, SPLIT, XS, false, SPLIT || D == 128>(dm, a, st);
+}
+
 template <int D, bool SPLIT>
 static hipError_t launch_ds(const Dims& dm, const AttnArgs& a, hipStream_t st) {
-  if (dm.flags & QUOKA_ATTN_SCALE_F32)
-    return a.n_splits > 1 ? launch_variant<D, SPLIT, true, true>(dm, a, st) : launch_variant<D, SPLIT, true, false>(dm, a, st);
-  return a.n_splits > 1 ? launch_variant<D, SPLIT, false, true>(dm, a, st) : launch_variant<D, SPLIT, false, false>(dm, a, st);
+  return dm.flags & QUOKA_ATTN_SCALE_F32 ? launch_dsx<D, SPLIT, true>(dm, a, st) : launch_dsx<D, SPLIT, false>(dm, a, st);
 }
 
 // ---- which variant: 8 row blocks per block or 4 (SPLIT), and over how many blocks the key list is split -----------

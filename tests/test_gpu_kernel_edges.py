@@ -187,7 +187,10 @@ def test_bf16_attention_whole_lists_of_one_sequence(case):
 @pytest.mark.parametrize("case", [
     dict(n_q=16, n_kv=2, d=128, chunk=2070, kv_lens=[50], budgets=[40]),        # blocks of four
     dict(n_q=16, n_kv=2, d=64, chunk=2070, kv_lens=[50], budgets=[40]),
-    dict(n_q=14, n_kv=2, d=64, chunk=5, kv_lens=[129], budgets=[129]),          # one row block a head
+    dict(n_q=14, n_kv=2, d=64, chunk=5, kv_lens=[129], budgets=[129]),          # few rows: stored as the registers lie; 63 of them,
+    dict(n_q=14, n_kv=2, d=128, chunk=9, kv_lens=[60], budgets=[50]),           # and 64, which go out whole
+    dict(n_q=16, n_kv=2, d=128, chunk=8, kv_lens=[60], budgets=[50]),
+    dict(n_q=4, n_kv=2, d=64, chunk=31, kv_lens=[60], budgets=[50]),            # 62, one head a row block
     dict(n_q=16, n_kv=2, d=128, chunk=2070, kv_lens=[3000], budgets=[2500]),    # blocks of eight
 ], ids=_id)
 def test_bf16_attention_rows_of_whole_lists(case, scale_f32):
