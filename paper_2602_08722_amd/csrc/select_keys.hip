@@ -327,34 +327,38 @@ struct HeadSelectLds {
 };
 constexpr int kHeadCands = 4;   // candidates a thread of the head's block holds in registers
 
-// use(number, value...) for each of n entries of one or two arrays in memory, by a block of NT threads.  Eight of a thread's are
-// requested at a time: one by one, the list of a head whose scores all share a bin is 512 fetches in a row, in every emitting block
-// (8 heads of 131072 equal keys, whole calls, 64 queries 408 -> 195 us, 2 queries 384 -> 173; eight different keys 143 -> 122).
+// use(value...) for each of n entries of one or two arrays in memory, by a block of NT threads.  Eight loads of a thread are in flight:
+// one by one, the list of a head whose scores all share a bin is 512 fetches in a row, in every emitting block (8 heads of
+// 131072 equal keys, whole calls, 64 queries 403 -> 187 us, 2 queries 381 -> 164; eight different keys 138 -> 116).  The rest
+// goes one by one: with runs that reach past the end, clamped, sel_finish took 88 registers instead of 62, and 8 x 8 ragged heads
+// of one query, whole calls, 189 us instead of 180.
 constexpr int kListRun = 8;
 template <int NT, typename F>
 __device__ __forceinline__ void for_each_listed(const uint32_t* __restrict__ a, uint32_t n, F use) {
-  for (uint32_t i0 = threadIdx.x; i0 < n; i0 += kListRun * NT) {
+  uint32_t i = threadIdx.x;
+  for (; i + (kListRun - 1) * NT < n; i += kListRun * NT) {
     uint32_t v[kListRun];
 #pragma unroll
-    for (int j = 0; j < kListRun; ++j) v[j] = a[min(i0 + NT * j, n - 1)];
+    for (int j = 0; j < kListRun; ++j) v[j] = a[i + NT * j];
 #pragma unroll
-    for (int j = 0; j < kListRun; ++j)
-      if (i0 + NT * j < n) use(v[j]);
+    for (int j = 0; j < kListRun; ++j) use(v[j]);
   }
+  for (; i < n; i += NT) use(a[i]);
 }
 template <int NT, typename F>
 __device__ __forceinline__ void for_each_listed(const uint32_t* __restrict__ a, const uint32_t* __restrict__ b, uint32_t n, F use) {
-  for (uint32_t i0 = threadIdx.x; i0 < n; i0 += kListRun * NT) {
-    uint32_t v[kListRun], u[kListRun];
+  uint32_t i = threadIdx.x;
+  for (; i + (kListRun / 2 - 1) * NT < n; i += kListRun / 2 * NT) {
+    uint32_t v[kListRun / 2], u[kListRun / 2];
 #pragma unroll
-    for (int j = 0; j < kListRun; ++j) {
-      v[j] = a[min(i0 + NT * j, n - 1)];
-      u[j] = b[min(i0 + NT * j, n - 1)];
+    for (int j = 0; j < kListRun / 2; ++j) {
+      v[j] = a[i + NT * j];
+      u[j] = b[i + NT * j];
     }
 #pragma unroll
-    for (int j = 0; j < kListRun; ++j)
-      if (i0 + NT * j < n) use(v[j], u[j]);
+    for (int j = 0; j < kListRun / 2; ++j) use(v[j], u[j]);
   }
+  for (; i < n; i += NT) use(a[i], b[i]);
 }
 
 template <int NT>
