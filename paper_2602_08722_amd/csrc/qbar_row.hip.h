@@ -9,23 +9,25 @@ namespace quoka {
 // RULE: where the retained positions come from.  kFromIndex: q_idx as written by the selection kernel.  The other two
 // are known in closed form, so q_idx is written here (`write_idx`) and no separate launch is needed: kIdentity keeps
 // every query (C <= N_Q), kUniform takes the even stride floor(r * C / N') of the query-sampling baseline of Sec. 4.
-// GU: heads requested at a time.
+// GU: heads requested at a time.  SIDE: their norms form side by side, without a branch a head, which is the faster as long as the chip is
+// not full (query stage of one KV head of 16, d 128, 600 tokens 18.6 -> 15.8 us); in the scoring launch that forms Qbar itself, whose every
+// block does this, groups of more than four go one head after the other (24 x 8 KV heads of 7, d 64, 8 tokens over 1500 keys, whole
+// calls 36.2 / 37.4 us; one sequence 19.2 / 18.9).  The same bits.
 enum { kFromIndex = 0, kIdentity = 1, kUniform = 2 };
-template <typename T, int D, int RULE, int GU>
+template <typename T, int D, int RULE, int GU, bool SIDE>
 __device__ __forceinline__ void qbar_row(const Dims& dm, const T* __restrict__ q, int32_t* __restrict__ q_idx, int n_keep,
                                          int r, int kv, int b, int lane, bool write_idx, float (&row)[D / 64]) {
   constexpr int EPL = D / 64;
   float acc[EPL];
 #pragma unroll
   for (int e = 0; e < EPL; ++e) acc[e] = 0.f;
-  // lane j has the position in head j of the group (at most 16), in one vector load: as scalar loads they would be waited for
-  // one by one
+  // kFromIndex: lane j has the position in head j of the group (at most 16), in one vector load: as scalar loads they would be waited
+  // for one by one
   int32_t* slot = q_idx + (size_t)(b * dm.n_q + kv * dm.g + min(lane, dm.g - 1)) * n_keep + r;
-  int my_tok;
+  int my_tok = RULE == kIdentity ? r : (int)(((int64_t)r * dm.chunk(b)) / n_keep);
   if constexpr (RULE == kFromIndex) {
     my_tok = *slot;
   } else {
-    my_tok = RULE == kIdentity ? r : (int)(((int64_t)r * dm.chunk(b)) / n_keep);
     if (write_idx && lane < dm.g) *slot = my_tok;
   }
   for (int j0 = 0; j0 < dm.g; j0 += GU) {
@@ -33,29 +35,43 @@ __device__ __forceinline__ void qbar_row(const Dims& dm, const T* __restrict__ q
 #pragma unroll
     for (int jj = 0; jj < GU; ++jj) {
       const int j = min(j0 + jj, dm.g - 1);
-      const int tok = __builtin_amdgcn_readlane(my_tok, j);
+      const int tok = RULE == kFromIndex ? __builtin_amdgcn_readlane(my_tok, j) : my_tok;
       const T* src = q + b * dm.qs[0] + (size_t)(kv * dm.g + j) * dm.qs[1] + (size_t)tok * dm.qs[2];
 #pragma unroll
       for (int e = 0; e < EPL; ++e) v[jj][e] = Elem<T>::load1(src + lane * EPL + e);
     }
-    // (no branches, so that the chains of the group's heads run side by side: a row beyond the group is made zero, and adds
-    // zero; without normalisation (dot-product ablation) every norm is made one)
+    if constexpr (SIDE) {
+      // (a row beyond the group is made zero, and adds zero; without normalisation (dot-product ablation) every norm is made one)
 #pragma unroll
-    for (int jj = 0; jj < GU; ++jj) {
-      ss[jj] = 0.f;
+      for (int jj = 0; jj < GU; ++jj) {
+        ss[jj] = 0.f;
 #pragma unroll
-      for (int e = 0; e < EPL; ++e) {
-        v[jj][e] = j0 + jj < dm.g ? v[jj][e] : 0.f;
-        ss[jj] += v[jj][e] * v[jj][e];
+        for (int e = 0; e < EPL; ++e) {
+          v[jj][e] = j0 + jj < dm.g ? v[jj][e] : 0.f;
+          ss[jj] += v[jj][e] * v[jj][e];
+        }
       }
-    }
 #pragma unroll
-    for (int jj = 0; jj < GU; ++jj) ss[jj] = wave64_sum(ss[jj]);
+      for (int jj = 0; jj < GU; ++jj) ss[jj] = wave64_sum(ss[jj]);
 #pragma unroll
-    for (int jj = 0; jj < GU; ++jj) {
-      const float nrm = fmaxf(sqrtf((dm.flags & 1) ? 1.0f : ss[jj]), kNormEps);
+      for (int jj = 0; jj < GU; ++jj) {
+        const float nrm = fmaxf(sqrtf((dm.flags & 1) ? 1.0f : ss[jj]), kNormEps);
 #pragma unroll
-      for (int e = 0; e < EPL; ++e) acc[e] += v[jj][e] / nrm;   // heads are accumulated in ascending order
+        for (int e = 0; e < EPL; ++e) acc[e] += v[jj][e] / nrm;   // heads are accumulated in ascending order
+      }
+    } else {
+#pragma unroll
+      for (int jj = 0; jj < GU; ++jj) {
+        ss[jj] = 0.f;
+#pragma unroll
+        for (int e = 0; e < EPL; ++e) ss[jj] += v[jj][e] * v[jj][e];
+        ss[jj] = wave64_sum(ss[jj]);
+        const float nrm = (dm.flags & 1) ? 1.0f : fmaxf(sqrtf(ss[jj]), kNormEps);
+        if (j0 + jj < dm.g) {   // wave-uniform
+#pragma unroll
+          for (int e = 0; e < EPL; ++e) acc[e] += v[jj][e] / nrm;
+        }
+      }
     }
   }
 #pragma unroll

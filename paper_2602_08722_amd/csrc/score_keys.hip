@@ -117,9 +117,9 @@ __global__ __launch_bounds__(kScThreads, 2) void score_bf16(Dims dm, const float
       float row[EPL];
       const uint16_t* q = static_cast<const uint16_t*>(fq.q);
       if (dm.g <= 4) {
-        qbar_row<uint16_t, D, kIdentity, 4>(dm, q, fq.q_idx, n_keep, r, kv, b, lane, blockIdx.x == 0, row);
+        qbar_row<uint16_t, D, kIdentity, 4, true>(dm, q, fq.q_idx, n_keep, r, kv, b, lane, blockIdx.x == 0, row);
       } else {
-        qbar_row<uint16_t, D, kIdentity, 8>(dm, q, fq.q_idx, n_keep, r, kv, b, lane, blockIdx.x == 0, row);
+        qbar_row<uint16_t, D, kIdentity, 8, false>(dm, q, fq.q_idx, n_keep, r, kv, b, lane, blockIdx.x == 0, row);
       }
 #pragma unroll
       for (int e = 0; e < EPL; ++e) {

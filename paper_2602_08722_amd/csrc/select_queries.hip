@@ -478,7 +478,7 @@ __global__ __launch_bounds__(64) void sq_qbar(Dims dm, const T* __restrict__ q, 
   const int lane = threadIdx.x;
   if (r >= n_keep) return;   // (such a block only clears)
   float row[EPL];
-  qbar_row<T, D, RULE, GU>(dm, q, q_idx, n_keep, r, kv, b, lane, true, row);
+  qbar_row<T, D, RULE, GU, true>(dm, q, q_idx, n_keep, r, kv, b, lane, true, row);
   float* out = qbar + ((size_t)(b * dm.n_kv + kv) * n_keep + r) * D;
 #pragma unroll
   for (int e = 0; e < EPL; ++e) out[lane * EPL + e] = row[e];
