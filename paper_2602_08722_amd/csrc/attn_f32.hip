@@ -252,17 +252,21 @@ __global__ __launch_bounds__(kFaThreads, 2) void attn_f32(Dims dm, AttnArgs a, f
 }
 
 // Sum of the splits' partials: D / 4 threads per row, four dims each, the splits of a row shared by G such groups (neighbouring
-// splits each, four requested at a time), whose sums meet in LDS.  Added in a fixed order.  What bounds it is the chain of
-// fetches: with one group that walked the splits one by one, after a pass for the
-// maximum, two KV heads of one, d 128, 2 tokens over 7362 keys took 33 us in all, and take 19; 4 heads, d 64, 48 tokens 27 and 14.
+// splits each), whose sums meet in LDS.  All of a thread's records, at most eight, are requested before the first is used.  The maximum
+// over all splits comes first, so that every partial is weighted once and added by one fused multiply-add, in a fixed order; the
+// groups' sums are added in pairs.  (Sums rescaled to a running maximum, products rounded before they are added: 0.1 - 0.5 % further
+// from float64.)  What bounds it is the chain of fetches: with one group that walked the splits one by one two KV heads of one,
+// d 128, 2 tokens over 7362 keys took 33 us in all, and take 19; 4 heads, d 64, 48 tokens 27 and 14.
 constexpr int kFmThreads = 256, kFmRun = 4;
 template <int D, int G>
 __global__ __launch_bounds__(kFmThreads) void attn_f32_merge(Dims dm, AttnArgs a, const float* __restrict__ part, int n_rb,
                                                             int n_splits) {
   constexpr int REC = FaCfg<D>::REC, TPR = D / 4, ROWS = kFmThreads / (TPR * G);
+  constexpr int RUNS = G > 1 ? kFaMaxSplits / (G * kFmRun) : 1;   // (G == 1: at most kFmRun splits)
+  static_assert(G == 1 || RUNS * G * kFmRun == kFaMaxSplits, "");
   typedef float f32x4 __attribute__((ext_vector_type(4)));
   __shared__ __align__(16) f32x4 sum[G > 1 ? kFmThreads : 1];
-  __shared__ float2 ml[G > 1 ? kFmThreads : 1];
+  __shared__ float ms_all[G > 1 ? kFmThreads : 1], ls_all[G > 1 ? kFmThreads : 1];
   const int c4 = threadIdx.x % TPR, grp = threadIdx.x / TPR % G;
   const int row = blockIdx.x * ROWS + threadIdx.x / (TPR * G);
   const int kv = blockIdx.y % dm.n_kv, b = blockIdx.y / dm.n_kv;
@@ -270,56 +274,61 @@ __global__ __launch_bounds__(kFmThreads) void attn_f32_merge(Dims dm, AttnArgs a
   const int r = row % 32, rb = row_on ? row / 32 : 0;
   const float* rec = part + ((size_t)blockIdx.y * n_rb + rb) * n_splits * 32 * REC;
   const int s0 = n_splits * grp / G, s1 = n_splits * (grp + 1) / G;
-  float m = -INFINITY, l = 0.f;
-  f32x4 acc = {0.f, 0.f, 0.f, 0.f};
-  for (int s = s0; s < s1; s += kFmRun) {
-    float ms[kFmRun], ls[kFmRun];
-    f32x4 x[kFmRun];
+  float ms[RUNS * kFmRun], ls[RUNS * kFmRun];
+  f32x4 x[RUNS * kFmRun];
 #pragma unroll
-    for (int i = 0; i < kFmRun; ++i) {   // (the last record of the run again where there are fewer)
-      const float* p = rec + (size_t)min(s + i, s1 - 1) * 32 * REC;
+  for (int u = 0; u < RUNS; ++u) {
+    if (u > 0 && n_splits <= u * kFmRun * G) break;   // block-uniform
+#pragma unroll
+    for (int i = u * kFmRun; i < (u + 1) * kFmRun; ++i) {   // (the group's last record again where it has fewer, or none)
+      const float* p = rec + (size_t)max(min(s0 + i, s1 - 1), 0) * 32 * REC;
       ms[i] = p[32 * D + r];
       ls[i] = p[32 * D + 32 + r];
       x[i] = *reinterpret_cast<const f32x4*>(p + r * D + 4 * c4);
     }
-    __builtin_amdgcn_sched_barrier(0);   // all of them in flight
-    float m_new = m;
+  }
+  __builtin_amdgcn_sched_barrier(0);   // all of them in flight
+  float m = -INFINITY;
 #pragma unroll
-    for (int i = 0; i < kFmRun; ++i) m_new = fmaxf(m_new, ms[i]);
-    const float m_fin = m_new == -INFINITY ? 0.f : m_new;   // (a row that no split so far has seen a key for)
-    const float alpha = __builtin_amdgcn_exp2f(m - m_fin);
-    m = m_new;
-    l *= alpha;
-    acc *= alpha;
+  for (int i = 0; i < RUNS * kFmRun; ++i) m = s0 + i < s1 ? fmaxf(m, ms[i]) : m;
+  if constexpr (G > 1) {
+    ms_all[threadIdx.x] = m;
+    __syncthreads();
 #pragma unroll
-    for (int i = 0; i < kFmRun; ++i) {
-      const bool in = s + i < s1;
-      const float wgt = __builtin_amdgcn_exp2f(ms[i] - m_fin);
-      l += in ? wgt * ls[i] : 0.f;
+    for (int i = 0; i < G; ++i) m = fmaxf(m, ms_all[threadIdx.x + TPR * (i - grp)]);
+  }
+  float l = 0.f;
+  f32x4 acc = {0.f, 0.f, 0.f, 0.f};
 #pragma unroll
-      for (int e = 0; e < 4; ++e) acc[e] += in ? wgt * x[i][e] : 0.f;
+  for (int i = 0; i < RUNS * kFmRun; ++i) {
+    if (s0 + i < s1) {
+      const float wgt = __builtin_amdgcn_exp2f(ms[i] - m);   // (every row sees at least its own key: m is finite)
+      l += wgt * ls[i];
+#pragma unroll
+      for (int e = 0; e < 4; ++e) acc[e] += wgt * x[i][e];
     }
   }
   if constexpr (G > 1) {
     sum[threadIdx.x] = acc;
-    ml[threadIdx.x] = make_float2(m, l);
+    ls_all[threadIdx.x] = l;
     __syncthreads();
     if (grp > 0) return;
-    float m_all = m;
+    float lg[G];
+    f32x4 ag[G];
 #pragma unroll
-    for (int i = 1; i < G; ++i) m_all = fmaxf(m_all, ml[threadIdx.x + TPR * i].x);
-    const float m_fin = m_all == -INFINITY ? 0.f : m_all;
-    const float alpha = __builtin_amdgcn_exp2f(m - m_fin);
-    m = m_all;
-    l *= alpha;
-    acc *= alpha;
-#pragma unroll
-    for (int i = 1; i < G; ++i) {
-      const float2 o = ml[threadIdx.x + TPR * i];
-      const float wgt = __builtin_amdgcn_exp2f(o.x - m_fin);
-      l += wgt * o.y;
-      acc += wgt * sum[threadIdx.x + TPR * i];
+    for (int i = 0; i < G; ++i) {
+      lg[i] = ls_all[threadIdx.x + TPR * i];
+      ag[i] = sum[threadIdx.x + TPR * i];
     }
+#pragma unroll
+    for (int o = 1; o < G; o *= 2)   // in pairs
+#pragma unroll
+      for (int i = 0; i < G; i += 2 * o) {
+        lg[i] += lg[i + o];
+        ag[i] += ag[i + o];
+      }
+    l = lg[0];
+    acc = ag[0];
   }
   if (!row_on) return;
   const FaRow fr = fa_row(row, dm.g);
