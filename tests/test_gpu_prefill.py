@@ -194,6 +194,31 @@ def test_short_last_chunk_keeps_its_query_route():
         assert torch.equal(a, b)
 
 
+@pytest.mark.parametrize("d", [64, 128])
+@pytest.mark.parametrize("chunk,tail", [(1024, 65), (1024, 200), (1024, 256), (1024, 257), (700, 300), (2000, 512), (1024, 513)])
+def test_short_last_chunk_selects_alike_in_one_block_and_in_tiles(d, chunk, tail):
+    """Few heads, full chunks beyond one block per head: a last chunk of up to 512 tokens takes one block per head by itself and the
+    tiled launches among the others.  Cosines so close together that the last bits of the mean decide ranks: the same bits."""
+    import paper_2602_08722_amd as pk
+    pk.load_library()
+    L = 5 * chunk + tail
+    q, k, v = _prompt_on_device(1, 8, 2, d, L, seed=tail)
+    rng = torch.Generator(device="cuda").manual_seed(6)
+    lean = 30.0 * torch.randn(1, 8, 1, d, device="cuda", generator=rng)
+    q = (lean + q.float()).bfloat16()
+    got = []
+    for full in (False, True):
+        pb = pk.PrefillBuffers(q, k, v, chunk, 64, lambda t: t // 8)
+        if not full:
+            pb.workspace = pb.workspace[:pk.quoka_workspace_bytes(pb.shape)]
+        pb.q_idx.fill_(-1)
+        pb.run()
+        torch.cuda.synchronize()
+        got.append((pb.q_idx, pb.qbar, pb.k_cnt, pb.k_idx[:, :, :int(pb.k_cnt[0, 0])]))
+    for a, b in zip(*got):
+        assert torch.equal(a, b)
+
+
 @pytest.mark.parametrize("dtype,n_q,n_kv,L,chunk,sparse", [
     ("bf16", 4, 1, 300, 8, False),      # decode kernel
     ("bf16", 4, 1, 300, 8, True),

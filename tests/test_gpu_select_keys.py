@@ -337,3 +337,35 @@ def test_candidates_listed_in_memory(call, chunk, values):
         n = int(cnt[i, 0])
         want = O.topk_keys(gen.from_torch(sc)[i][:, :T], n)
         assert np.array_equal(gen.from_torch(idx)[i][:, :n], want) and np.array_equal(gen.from_torch(buf.k_idx)[i][:, :n], want)
+
+
+@pytest.mark.parametrize("left_out", [30000, 45, 3])
+@pytest.mark.parametrize("case", [dict(n_q=4, n_kv=1, chunk=40, n_retain=32), dict(n_q=8, n_kv=8, chunk=2, n_retain=16)], ids=["exact", "one-pass"])
+def test_keys_whose_scores_overflow(case, left_out):
+    """Keys so long that their squared norm is infinite (their score is then zero), and so long that the product is too (not a
+    number: below every other score, on every route of long caches).  The cut lies among ordinary scores, or among those without
+    a number, of which the lower positions are taken."""
+    pk = _pk()
+    T = 40000
+    w = gen.make_custom(dtype="bf16", d=128, kv_lens=[T], budgets=[T - left_out], batch=1, seed=52, **case)
+    buf = _buffers(pk, w)
+    buf.select_queries()
+    qbar = gen.from_torch(buf.qbar)[0]
+    rng = np.random.default_rng(9)
+    for kv in range(w.n_kv):
+        at = rng.choice(T, size=40, replace=False)
+        w.K[0, kv, at[:20]] *= 2.0 ** 90
+        w.K[0, kv, at[20:]] = np.where(qbar[kv, 0] > 0, 1.0, -1.0) * 255 / 256 * 2.0 ** 128   # (product with row 0: its 1-norm times that)
+        assert np.abs(qbar[kv, 0]).sum() > 1.1
+    buf = _buffers(pk, w)
+    exact = gen.from_torch(_staged(buf)[0])[0]
+    lists = []
+    for call in (buf.chunk_attn, buf.select_keys):
+        buf.k_idx.fill_(-1)
+        call()
+        torch.cuda.synchronize()
+        lists.append(gen.from_torch(buf.k_idx)[0])
+    assert np.array_equal(*lists)
+    nan = np.isnan(exact)
+    assert (nan.sum(axis=1) == 20).all()
+    assert np.array_equal(lists[0], O.topk_keys(np.where(nan, np.float32(-2.0), exact), T - left_out))

@@ -152,6 +152,28 @@ def test_select_queries_with_more_equal_cosines_than_are_listed(chunk, equal):
     assert np.array_equal(gen.from_torch(buf.q_idx)[0], np.tile(at[:100], (4, 1)))
 
 
+@pytest.mark.parametrize("dtype,d,chunk,n_retain", [("f32", 128, 300, 100), ("f32", 64, 512, 16), ("bf16", 128, 1500, 128), ("bf16", 64, 700, 5),
+                                                    ("bf16", 128, 129, 128)])
+def test_select_queries_with_a_cosine_that_overflows(dtype, d, chunk, n_retain):
+    """One row per head so long that its squared norm is infinite and its cosine is not a number, whose bits decide where it ranks:
+    the others keep their order."""
+    w = gen.make_custom(dtype=dtype, n_q=4, n_kv=2, d=d, chunk=chunk, n_retain=n_retain, kv_lens=[8], budgets=[2], seed=23)
+    rng = np.random.default_rng(8)
+    long = rng.integers(chunk, size=4)
+    for h in range(4):
+        w.Q[0][h, long[h]] = np.where(rng.standard_normal(d) > 0, 2.0 ** 66, -2.0 ** 66)
+    buf = _buffers(w)
+    buf.q_idx.fill_(-1)
+    buf.select_queries()
+    torch.cuda.synchronize()
+    q_idx, cos = gen.from_torch(buf.q_idx)[0], O.cos_to_mean(w.Q[0])
+    for h in range(4):
+        others = q_idx[h][q_idx[h] != long[h]]
+        assert len(others) >= n_retain - 1 and len(set(q_idx[h].tolist())) == n_retain
+        left = np.delete(np.arange(chunk), long[h])   # the others' positions
+        P.check_query_ranking(np.searchsorted(left, others), cos[h][left], len(others), what=f"h{h}")
+
+
 SCORE_CASES = [
     dict(dtype="f32", n_q=2, n_kv=1, d=64, chunk=128, n_retain=16, kv_lens=[1000]),
     dict(dtype="bf16", n_q=8, n_kv=2, d=128, chunk=256, n_retain=64, kv_lens=[1500]),          # ragged tail tile
