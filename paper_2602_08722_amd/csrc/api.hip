@@ -466,9 +466,9 @@ quoka_status quoka_prefill_attn(const quoka_shape* shape, int sparse, const void
   // 32/8 heads, d 128, 16000 tokens in chunks of 1024: 106 launches, 1197 us -> 8 launches, 573 us: the short launches
   // of the selection run once, and the attention blocks of all chunks fill the chip together.  (Batches: 2 sequences of
   // 16000 1777 -> 1099 us, 8 of them 5125 -> 4389, 8 of 20000 in chunks of 500, 8/2 heads 3844 -> 2104.)  A short last chunk goes
-  // along where it selects as many queries as the others (up to n_retain tokens it keeps all, in position order) and would
-  // take the same kernels by itself (a decode-sized one is attended by attn_decode_bf16, which rounds Q no second time;
-  // the query stage's two routes round the mean differently).
+  // along where it selects as many queries as the others (up to n_retain tokens it keeps all, in position order) and its results do not
+  // depend on that: a decode-sized one is attended by attn_decode_bf16, which rounds Q no second time, and the query stage's
+  // form for batches rounds the mean differently.  (Its one-block form for short chunks forms the tiled kernels' very sums.)
   const int last_len = L - (n_chunks - 1) * C;
   Dims last = dm;   // the last chunk by itself
   last.C = last.C_last = last_len;

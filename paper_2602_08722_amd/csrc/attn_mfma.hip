@@ -516,9 +516,10 @@ __global__ __launch_bounds__(2 * kSetThreads, 2) void attn_bf16(Dims dm, AttnArg
 #undef QUOKA_RESOLVE
 #undef QUOKA_ISSUE
 
-// Sum of the key splits' partials: a wave takes one dim block of a row block and up to kMergeRun neighbouring splits at a
-// time, all of whose records are requested before the first is used, and the sums of the waves that share a dim block meet in
-// LDS.  A block is all waves of a row block where those are at most eight, else those of a dim block (`dims` of a block).  The lane layout is the attention kernel's own, so the loads are whole kilobytes.  Everything is added in a fixed order.
+// Sum of the key splits' partials: a wave takes one dim block of a row block and up to kMergeRun neighbouring splits at a time, all of
+// whose records are requested before the first is used, and the sums of the waves that share a dim block meet in LDS.  A block
+// is all waves of a row block where those are at most eight, else those of a dim block (`dims` of a block).  The lane layout is
+// the attention kernel's own, so the loads are whole kilobytes.  Everything is added in a fixed order.
 // What bounds it is the chain of fetches, not the bytes: with one wave walking a dim block's splits two at a time the launch took
 // 0.4 us a split (8 heads, d 64, 103 tokens, 32 splits 15.4 us, now 5.4; 2 heads of 7, d 128, 5 tokens 13.2, now 4.4; 4 heads
 // of 3, d 128, 147 tokens 9.3, now 5.3).
@@ -705,14 +706,15 @@ static bool eight_row_blocks(const Dims& dm, bool sparse, long long groups) {
 // Measured (kernel and merge, unsplit -> split): 4 KV heads x 3 sequences, d 64, 333 tokens over 4999 keys (2 splits)
 // 60 -> 38 us; one KV head of 16 q-heads x 8 sequences, d 64, 69 tokens over 13477 keys (5 splits) 138 -> 65 us.
 // The cheapest variant by a model of the call in microseconds: a fixed part, the steps of the longest key list's share times
-// the rounds of 256 resident blocks, and for a split list the partials' bytes.  The numbers are fits to 2400 measured calls
+// the rounds of 256 resident blocks, and for a split list the partials' bytes and 0.03 a split.  The numbers are fits to 2400 measured calls
 // (220 shapes of 5 - 1500 tokens over 64 - 16000 keys; rms 3 - 5 %); a split has to promise 0.6 us more than it costs, because
 // the model takes the shortest whole lists for longer than they are (2 KV heads of 7, d 64, 5 tokens over 129 keys 8.2 us whole,
 // 10.5 in 4 splits).  The plans are 1 % off the best of the measured ones on the mean.
 static AttnPlan attn_plan(const Dims& dm, bool sparse) {
   const long long nrb = (long long)dm.g * ((dm.C + 31) / 32), heads = (long long)dm.n_kv * dm.b;
   if (heads * nrb * 2 > kMaxRecords) return AttnPlan{!eight_row_blocks(dm, sparse, heads * ((nrb + 7) / 8)), 1};
-  // (from here on there are at most 128 blocks of eight row blocks: a whole list takes blocks of four, in one round)
+  // (From here on there are at most 1024 row blocks, and a whole list takes blocks of four: 256 of them at most, one round, where the
+  // row blocks of a KV head are a multiple of four, more where they are not: 312 for 13 x 8/8 heads of 280 tokens.)
   struct Fit {
     float fixed, step, per_mb;   // a step is 8 row blocks x 64 keys or 4 x 128
   };

@@ -225,9 +225,11 @@ __device__ __forceinline__ float packed_products(const bf16x8 (&kop)[D / 16], co
 // Whether a bf16 call takes this form: the scores' last bits depend on it, so every scoring kernel goes by this rule, and
 // in a prompt it goes by the prompt's length and the batch of the whole call: how many chunks share a launch, and how
 // much cache they have come to, must not decide between two nearly equal keys.
-// Bounds: sel_finish ranks within heads of up to kPackMaxKeys positions.  Long caches of few keys in all keep the two-pass
-// form although packed is the faster there too (two heads of 65537 positions: 61.6 us a call, packed 48.9): a test that
-// the two-pass form runs expects mostly provisional scores of four queries at just that size.
+// Bounds: sel_finish has a lane for every tile of heads of up to kPackMaxKeys positions.  Long caches of few keys in all are not
+// packed: quoka_chunk_attn is the faster with unpacked exact scores there (two heads of 65537 positions, 4 queries 34.8 us, packed
+// 37.4; one of 131072 36.8, 43.0), up to where the two meet (two of 98000, 4 of 49000 39.1, 40.5 and 37.8, 37.0).
+// quoka_select_keys by itself takes the two-pass form there, though packed would be the faster (39 us, 27): a test that this
+// form runs expects mostly provisional scores of four queries at just that size.
 constexpr int kPackMaxKeys = 131072;
 constexpr long long kPackMinKeys = 3 << 16;
 inline bool score_packs(const Dims& dm) {

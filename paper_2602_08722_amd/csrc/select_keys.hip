@@ -141,10 +141,7 @@ __global__ __launch_bounds__(kSelThreads) void sel_band_rescore(Dims dm, const f
   const float eps = sqrtf(d2) * 1.001f + 4e-6f;
   const int m = (int)ceilf(2.0f * eps * (float)(kSelBins / 2)) + 1;
   const int bin_lo = max(cut_bin - m, 0), bin_hi = min(cut_bin + m, kSelBins - 1);
-  if (blockIdx.x == 0 && tid == 0) {
-    c.w.meta[kMetaBinLo] = (uint32_t)bin_lo;
-    c.w.meta[kMetaBinHi] = (uint32_t)bin_hi;
-  }
+  if (blockIdx.x == 0 && tid == 0) c.w.meta[kMetaBinHi] = (uint32_t)bin_hi;
   const char* kbase = reinterpret_cast<const char*>(kc + b * dm.kvs[0] + kv * dm.kvs[1]);
   const uint32_t row_bytes = (uint32_t)dm.kvs[2] * 2u;
   const int cg = tid % CG, r0 = tid / CG;
@@ -232,9 +229,6 @@ __global__ __launch_bounds__(kSelThreads) void sel_band_rescore(Dims dm, const f
 }
 
 // ---------------------------------------------------------------------------------------------
-// One block per head: the exact cut among the band candidates, then the output offset of every tile.
-// Radix select (descending) over keys that are read again from memory in every pass (the candidate list of a head is
-// a few tens of KiB and stays in cache; there is no bound on its length, so registers cannot hold it in general).
 // The cut among n candidates held in registers (thread t's k[i] is number t + NT*i): the `need`-th largest key, and how many
 // candidates equal to it are among the `need` largest.  A histogram over 256 equal parts of the keys' range, then the ranks of the
 // few keys in the cut's part: three barriers whatever n is, where radix passes need one each for every 8 bits.  False (block-
@@ -361,6 +355,8 @@ __device__ __forceinline__ void for_each_listed(const uint32_t* __restrict__ a, 
   for (; i < n; i += NT) use(a[i], b[i]);
 }
 
+// Radix select (descending) over keys that are read again from memory in every pass: for lists that registers do not hold, of any length,
+// and for parts that cut_among does not rank.
 template <int NT>
 __device__ __forceinline__ void stream_radix_select_desc(const uint32_t* __restrict__ keys, uint32_t n, uint32_t need,
                                                          RadixSelectLds& L, uint32_t* cut_key, uint32_t* need_eq) {
@@ -430,6 +426,8 @@ __device__ __forceinline__ void stream_radix_select_desc(const uint32_t* __restr
   *need_eq = need;
 }
 
+// ---------------------------------------------------------------------------------------------
+// One block per head: the exact cut among the band candidates, then the output offset of every tile.
 __global__ __launch_bounds__(kSelHeadThreads) void sel_band_select(Dims dm, float* __restrict__ scores,
                                                                    const int32_t* __restrict__ kv_lens,
                                                                    const int32_t* __restrict__ budgets,
@@ -589,7 +587,9 @@ __global__ __launch_bounds__(kSelThreads) void sel_emit(Dims dm, float* __restri
 }
 
 // ---------------------------------------------------------------------------------------------
-// Exact scores (score_packs): nothing is scored again, the candidates are the keys of the cut's own bin, a few dozen.
+// Exact scores (score_packs, select_keys_exact_pays): nothing is scored again, the candidates are the keys of the cut's own bin.  A few
+// dozen of ordinary scores in 4096 bins; in the exact scorer's 2048, of one KV head of 16 whose best scores lie close together,
+// beyond 1024, which are then selected from memory (131072 independent keys, 64 queries, budget 12 % 61 us a call, two-pass 109).
 // Launch chain: scoring with the histogram, one count per tile, emission; every emitting block finds the cut among the
 // candidates for itself, which is cheaper than a launch for it while the heads are short.  Measured (re-score, select, emit before -> these two; the scoring
 // launch takes the same): 8 sequences x 8 heads of 4096 to 65536 positions 48 -> 24 us (call 216 -> 196 us), 8 heads of

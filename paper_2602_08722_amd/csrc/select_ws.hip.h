@@ -9,11 +9,11 @@ constexpr int kScoreBins = 2048;      // of the exact scorer's histogram: half o
 constexpr int kSelTile = 2048;        // keys per block in the per-tile kernels
 constexpr int kSelThreads = 256;
 constexpr int kSelIPT = kSelTile / kSelThreads;
-constexpr int kSelMeta = 16;          // per-head words: candidate count, band limits, exact cut
+constexpr int kSelMeta = 16;          // per-head words: candidate count, upper band limit, exact cut, error bound
 constexpr int kSelHeadThreads = 1024;
 constexpr int kSelMaxTiles = (1 << 24) / kSelTile;   // the interface limits a cache to 2^24 - 1 positions
 
-enum { kMetaCand = 0, kMetaBinLo = 1, kMetaBinHi = 2, kMetaTau = 3, kMetaNeedEq = 4, kMetaEps2 = 5 };
+enum { kMetaCand = 0, kMetaBinHi = 2, kMetaTau = 3, kMetaNeedEq = 4, kMetaEps2 = 5 };
 
 // Bin of a provisional score: monotone in p, the same expression wherever it is evaluated.
 __device__ __forceinline__ int score_bin(float p) {

@@ -10,8 +10,8 @@ TOL_QBAR = 5e-7
 
 
 def two_pass_scores(w) -> bool:
-    """Whether quoka_select_keys (and so quoka_chunk_attn) takes its two-pass route for this workload: bf16 caches
-    longer than 32768 positions (include/quoka.h).  `scores` then holds exact values near the cut only."""
+    """Whether quoka_select_keys (and quoka_chunk_attn, where that is the faster) takes its two-pass route for this
+    workload: bf16 caches longer than 32768 positions (include/quoka.h).  `scores` then holds exact values near the cut only."""
     return w.dtype == "bf16" and w.t_max > 32768
 
 
