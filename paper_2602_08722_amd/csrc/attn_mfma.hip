@@ -706,10 +706,12 @@ static bool eight_row_blocks(const Dims& dm, bool sparse, long long groups) {
 // Measured (kernel and merge, unsplit -> split): 4 KV heads x 3 sequences, d 64, 333 tokens over 4999 keys (2 splits)
 // 60 -> 38 us; one KV head of 16 q-heads x 8 sequences, d 64, 69 tokens over 13477 keys (5 splits) 138 -> 65 us.
 // The cheapest variant by a model of the call in microseconds: a fixed part, the steps of the longest key list's share times
-// the rounds of 256 resident blocks, and for a split list the partials' bytes and 0.03 a split.  The numbers are fits to 2400 measured calls
-// (220 shapes of 5 - 1500 tokens over 64 - 16000 keys; rms 3 - 5 %); a split has to promise 0.6 us more than it costs, because
-// the model takes the shortest whole lists for longer than they are (2 KV heads of 7, d 64, 5 tokens over 129 keys 8.2 us whole,
-// 10.5 in 4 splits).  The plans are 1 % off the best of the measured ones on the mean.
+// the rounds of 256 resident blocks, and for a split list 6 for each further round, 0.03 a split and the partials' bytes.  The numbers
+// are fits to 2400 measured calls (220 shapes of 5 - 1500 tokens over 64 - 16000 keys; rms 3 - 5 %); a split has to promise 0.6 us more
+// than it costs, because the model takes the shortest whole lists for longer than they are (2 KV heads of 7, d 64, 5 tokens over
+// 129 keys 8.2 us whole, 10.5 in 4 splits).  Long lists of batches, bound by memory, are where further rounds cost time of their own (13 x 8
+// KV heads of 2, d 128, 17 tokens over 12000 keys: 2 splits, one round 117 us, 7 splits, three rounds 134).  The plans are 0.7 % off the
+// best of the measured ones on the mean of 760 other shapes, up to 60000 keys, and up to 6 % slower than another plan for single ones.
 static AttnPlan attn_plan(const Dims& dm, bool sparse) {
   const long long nrb = (long long)dm.g * ((dm.C + 31) / 32), heads = (long long)dm.n_kv * dm.b;
   if (heads * nrb * 2 > kMaxRecords) return AttnPlan{!eight_row_blocks(dm, sparse, heads * ((nrb + 7) / 8)), 1};
@@ -737,7 +739,7 @@ static AttnPlan attn_plan(const Dims& dm, bool sparse) {
       const Fit& f = kSplit[wide][mode];
       const long long rounds = (blocks * n + kComputeUnits - 1) / kComputeUnits, steps = (tiles + n - 1) / n;
       const float mb = (float)(heads * nrb * n) * (float)(dm.d + 2) * 128e-6f;
-      const float us = f.fixed + 0.6f + f.step * (float)(rounds * steps) + f.per_mb * mb + 0.03f * (float)n;
+      const float us = f.fixed + 0.6f + f.step * (float)(rounds * steps) + 6.f * (float)(rounds - 1) + f.per_mb * mb + 0.03f * (float)n;
       if (us < best_us) {
         best = AttnPlan{mode == 1, n};
         best_us = us;

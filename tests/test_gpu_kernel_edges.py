@@ -148,6 +148,12 @@ def test_bf16_attention_key_splits(case, scale_f32):
     check_attention(dict(case, dtype="bf16"), score_flags=16 if scale_f32 else 0)
 
 
+def test_bf16_attention_key_splits_of_a_batch_in_one_round():
+    # 104 blocks of two row blocks: two splits, one round of blocks, where seven would be three
+    check_attention(dict(dtype="bf16", n_q=16, n_kv=8, d=64, chunk=17, kv_lens=[3000 - 230 * i for i in range(13)],
+                         budgets=[700] * 13, batch=13), rows=[0, 8, 16])
+
+
 def test_bf16_attention_key_splits_of_eight_row_blocks():
     # 48 groups of eight row blocks on 256 compute units, which the plan splits five ways
     check_attention(dict(dtype="bf16", n_q=8, n_kv=8, d=128, chunk=1341, kv_lens=[5000], budgets=[3000]),
