@@ -86,8 +86,8 @@ struct AttnCfg {
 // a run-time switch it cost the unsplit launches 1.5-2 %.)
 // WHOLE (not KSPLIT): rows go out whole, 16 bytes a lane, through the wave's own piece of LDS; as the registers lie, a store covers
 // 16 bytes of each of 32 rows (32/8 heads, d 128, 1024 tokens over 983 keys 40.6 -> 39.2 us, 443 over 43 17.3 -> 16.6, 32 over 40
-// 10.9 -> 10.0).  Blocks of fewer than 64 rows in all are the faster without (2 KV heads of 2, d 64, 17 tokens 6.4 / 6.6 us), and so are
-// blocks of eight at d 64 (1 - 1.5 % in launches of many rounds).  (As a run-time choice it cost all others 2 - 5 %.)
+// 10.9 -> 10.0).  Launches of fewer than 64 rows a KV head are the faster without (2 KV heads of 2, d 64, 17 tokens 6.4 / 6.6 us), and so
+// are blocks of eight at d 64 (1 - 1.5 % in launches of many rounds).  (As a run-time choice it cost all others 2 - 5 %.)
 template <int D, bool SPLIT, bool XS, bool KSPLIT, bool WHOLE>
 __global__ __launch_bounds__(2 * kSetThreads, 2) void attn_bf16(Dims dm, AttnArgs a) {
   using Cfg = AttnCfg<D, SPLIT>;
@@ -656,7 +656,7 @@ template <int D, bool SPLIT, bool XS>
 static hipError_t launch_dsx(const Dims& dm, const AttnArgs& a, hipStream_t st) {
   if (a.n_splits > 1) return launch_variant<D, SPLIT, XS, true, false>(dm, a, st);
   if constexpr (SPLIT) {
-    if (dm.g * ((dm.C + 31) / 32) * (dm.C < 32 ? dm.C : 32) < 64) return launch_variant<D, SPLIT, XS, false, false>(dm, a, st);
+    if (dm.g * dm.C < 64) return launch_variant<D, SPLIT, XS, false, false>(dm, a, st);
   }
   return launch_variant<D, SPLIT, XS, false, SPLIT || D == 128>(dm, a, st);
 }
