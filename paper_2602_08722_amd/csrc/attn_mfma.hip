@@ -716,7 +716,8 @@ static AttnPlan attn_plan(const Dims& dm, bool sparse) {
   const long long nrb = (long long)dm.g * ((dm.C + 31) / 32), heads = (long long)dm.n_kv * dm.b;
   if (heads * nrb * 2 > kMaxRecords) return AttnPlan{!eight_row_blocks(dm, sparse, heads * ((nrb + 7) / 8)), 1};
   // (From here on there are at most 1024 row blocks, and a whole list takes blocks of four: 256 of them at most, one round, where the
-  // row blocks of a KV head are a multiple of four, more where they are not: 312 for 13 x 8/8 heads of 280 tokens.)
+  // row blocks of a KV head are a multiple of four, more where they are not: 312 for 13 x 8/8 heads of 280 tokens, which blocks of
+  // eight would take in one.)
   struct Fit {
     float fixed, step, per_mb;   // a step is 8 row blocks x 64 keys or 4 x 128
   };
