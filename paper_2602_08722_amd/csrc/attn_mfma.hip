@@ -22,12 +22,20 @@
 //     row0 .. row0+3: a quarter of an MFMA A operand, with no register shuffling.
 //     Accumulator block c, register v of lane li holds O[row li, dim 32*c + 8*(v/4) + 4*hf + v%4].
 //
-// Schedule: the two wave sets run half a step apart.  While one set forms S = K Q^T of a tile (matrix core only)
-// the other runs softmax and P V (exponentials interleaved with MFMAs), then they swap.  A SIMD hosts one wave of
-// each set, so its matrix core always has one wave that only feeds it and one whose vector work fills the gaps.
-// Two barriers per step keep the halves aligned and protect the double-buffered LDS stages.
+// Schedule: a wave works through its keys in units of 32 and keeps the matrix core and the vector unit busy at once: while the
+// products of unit u+1 (S = K Q^T) are formed, the scores of unit u become probabilities; while those of unit u (O += P V) are
+// formed, the maximum of unit u+1 is taken.  Operands are read from LDS half a unit before their product, and the next tiles are
+// stored and requested between products.  The order is written out, instruction group by instruction group, and held there.
+// One barrier per tile of 64 keys, K running one tile ahead of V.
+// What bounds it: the loop alone (operands from LDS, nothing staged) keeps the matrix core busy for 73 % of its clocks, at
+// 1.73 of 2.4 GHz, the clock that the power limit leaves (1.27 PFLOP/s; without the operand reads 1.44, without the conversion and sum
+// of the probabilities 1.44); staging costs 7 % of that.  Against two wave sets half a step apart, one forming S while the other ran
+// softmax and P V behind it (two barriers a tile), attention by itself, us: 32/8 heads, d 128, 4096 tokens over 8192 keys 645 -> 585,
+// 2048 over 3932 165 -> 155, 1024 over 983 37.7 -> 33.9, 1024 over all of 8192 157 -> 142; d 64, 1500 over 2400 70 -> 59.
 #include "common.hip.h"
 #include "kernels.h"
+
+#include <type_traits>
 
 namespace quoka {
 
@@ -144,13 +152,21 @@ __global__ __launch_bounds__(2 * kSetThreads, 2) void attn_bf16(Dims dm, AttnArg
     n_cache = min(a.n_cache[b * dm.ls], dm.T_max);
   }
   n_cache = max(n_cache, 0);
-  // Tile order: the chunk's own tiles first, then the cache tiles.  The online softmax does not care, and the first
-  // chunk tile needs no index look-up and no cache length, so its loads leave right at kernel start.
+  // Tile order: the chunk's own tiles first, the last one leading, then the cache tiles.  The online softmax does not care; the first
+  // chunk tile needs no index look-up and no cache length, so its loads leave right at kernel start; and what a wave can see is one
+  // run of tiles [w0, w1): a row block's causal range ends at the last of the chunk tiles and begins somewhere among them.
   const int n_cht = (c_end_blk + KT - 1) / KT;
   const int n_ct = (n_cache + KT - 1) / KT;
   const int n_tiles = n_cht + n_ct;
   const int t_begin = KSPLIT ? (int)((long long)n_tiles * split / a.n_splits) : 0;
   const int t_end = KSPLIT ? (int)((long long)n_tiles * (split + 1) / a.n_splits) : n_tiles;
+  // first key (in the tile's own numbering: cache slot or chunk position) of this set's share of tile t
+  auto share_base = [&](int t) { return (t >= n_cht ? t - n_cht : n_cht - 1 - t) * KT + sub; };
+  int w0 = n_cht - (tok0 + 31 >= sub ? (tok0 + 31 - sub) / KT + 1 : 0);
+  int w1 = n_ct > 0 && share_base(n_tiles - 1) >= n_cache ? n_tiles - 1 : n_tiles;   // (this set's share of the last tile may be empty)
+  w0 = max(w0, t_begin);
+  w1 = min(w1, t_end);
+  if (!wave_on || w0 >= w1) w0 = w1 = t_end + 1;   // sees nothing: stages its part of the tiles only
 
   const uint16_t* qg = static_cast<const uint16_t*>(a.q);
   // The tensor this set stages (set 0: K, set 1: V) for this (batch, KV head), as byte pointers: every row is
@@ -181,58 +197,69 @@ __global__ __launch_bounds__(2 * kSetThreads, 2) void attn_bf16(Dims dm, AttnArg
       for (int e = 0; e < 8; ++e) qreg[ks][e] = (__bf16)((float)qreg[ks][e] * qscale);
   }
 
+  // Staging.  Thread (r0, cg) carries chunk cg of rows r0 + RPI * k of this set's tensor, k < NLD, from memory through registers to LDS.
+  // Source rows of a tile are looked up a step ahead of the loads that use them, so the dependent index -> row fetch of the gather
+  // never sits on the critical path.  At d 128 the 16 lanes that carry a row look up NLD rows between them, one each, and take
+  // them from each other where they are used: one register instead of NLD.
+  constexpr bool kShare = CG == 16;
+  constexpr int NI = kShare ? 1 : NLD;
   const int cg = tid % CG, r0 = tid / CG;
   const uint32_t idx_max = (uint32_t)max(dm.T_max - 1, 0);
-  uint32_t rows[NLD];   // source rows of the tile to be issued next
-  u32x4 R[NLD];         // staging registers of the tile in flight
-
-  // Source rows of a tile are resolved one tile ahead of the loads that use them, so the dependent
-  // index -> row fetch of the gather never sits on the critical path: the fetched indices are first touched
-  // when the next tile's loads are issued, after the wait the LDS stores need anyway.  (Written as macros, not
-  // lambdas: the staging registers must stay in VGPRs.)
-#define QUOKA_RESOLVE(IT)                                                                          \
-  do {                                                                                             \
-    const int it_ = (IT);                                                                          \
-    if (it_ < t_end) {                                                                             \
-      const bool cache_ = it_ >= n_cht;                                                            \
-      const int base_ = cache_ ? (it_ - n_cht) * KT : it_ * KT;                                    \
-      const int last_ = cache_ ? n_cache - 1 : C - 1;                                              \
-      if (cache_ && sparse) {                                                                      \
-        _Pragma("unroll") for (int i = 0; i < NLD; ++i) {                                          \
-          const uint32_t n_ = (uint32_t)min(base_ + r0 + RPI * i, last_); /* tail slots repeat a real row */ \
-          rows[i] = *reinterpret_cast<const uint32_t*>(kidx + n_ * 4u); /* clamped where it is used */ \
-        }                                                                                          \
-      } else {                                                                                     \
-        _Pragma("unroll") for (int i = 0; i < NLD; ++i)                                            \
-          rows[i] = (uint32_t)min(base_ + r0 + RPI * i, last_);                                    \
-      }                                                                                            \
-    }                                                                                              \
-  } while (0)
-#define QUOKA_ISSUE(IT)                                                                            \
-  do {                                                                                             \
-    const bool cache_ = (IT) >= n_cht;                                                             \
-    const char* tb_ = cache_ ? cache_base : chunk_base;                                            \
-    const uint32_t rb_ = cache_ ? cache_row_bytes : chunk_row_bytes;                               \
-    /* Cache rows are clamped to the cache extent: a malformed list (negative or too large) cannot leave the tensor. \
-       The clamp sits here, not where the index is fetched: there it would make every wave wait for the fetch it \
-       has just issued. */                                                                          \
-    const uint32_t row_max_ = cache_ ? idx_max : 0xffffffffu;                                      \
-    _Pragma("unroll") for (int i = 0; i < NLD; ++i)                                                \
-      R[i] = *reinterpret_cast<const u32x4*>(tb_ + (min(rows[i], row_max_) * rb_ + (uint32_t)cg * 16u)); \
-  } while (0)
-
-  if (!KSPLIT || t_begin == 0) {
-    // tile 0 is the first chunk tile (the chunk is never empty): no index, no cache length
+  uint32_t src[NI];     // rows of the tile to be requested next, as looked up
+  uint32_t off[NI];     // the same as byte offsets, of the tile being requested
+  u32x4 R[NLD];         // the tile in flight
+  auto look_up = [&](int t) __attribute__((always_inline)) {
+    t = min(t, t_end - 1);   // (past the list's end the last tile is requested again, and nothing reads it)
+    const bool cache = t >= n_cht;
+    const int base = (cache ? t - n_cht : n_cht - 1 - t) * KT, last = cache ? n_cache - 1 : C - 1;
 #pragma unroll
-    for (int i = 0; i < NLD; ++i) {
-      rows[i] = (uint32_t)min(r0 + RPI * i, C - 1);
-      R[i] = *reinterpret_cast<const u32x4*>(chunk_base + (rows[i] * chunk_row_bytes + (uint32_t)cg * 16u));
+    for (int i = 0; i < NI; ++i)   // tail slots repeat a real row
+      src[i] = (uint32_t)min(base + r0 + RPI * (kShare ? lane % NLD : i), last);
+    if (cache && sparse) {
+#pragma unroll
+      for (int i = 0; i < NI; ++i) src[i] = *reinterpret_cast<const uint32_t*>(kidx + src[i] * 4u);
     }
-  } else if (t_begin < t_end) {
-    QUOKA_RESOLVE(t_begin);
-    QUOKA_ISSUE(t_begin);
+  };
+  const char* req_base = nullptr;   // of the tile being requested
+  auto address = [&](int t) __attribute__((always_inline)) {
+    const bool cache = min(t, t_end - 1) >= n_cht;
+    req_base = cache ? cache_base : chunk_base;
+    // Cache rows are clamped to the cache extent: a malformed list (negative or too large) cannot leave the tensor.
+    const uint32_t row_bytes = cache ? cache_row_bytes : chunk_row_bytes, row_max = cache ? idx_max : 0xffffffffu;
+#pragma unroll
+    for (int i = 0; i < NI; ++i) off[i] = min(src[i], row_max) * row_bytes + (kShare ? 0u : (uint32_t)cg * 16u);
+  };
+  auto request = [&](int k) __attribute__((always_inline)) {
+    const uint32_t o = kShare ? row16_lane(off[0], k) + (uint32_t)cg * 16u : off[k % NI];
+    R[k] = *reinterpret_cast<const u32x4*>(req_base + o);
+  };
+  uint16_t* const stage_dst = reinterpret_cast<uint16_t*>(smem + stage_off_mine) + r0 * ld_mine + cg * 8;
+  auto store = [&](int t, int k, u32x4 r) __attribute__((always_inline)) {
+    *reinterpret_cast<u32x4*>(stage_dst + (t & 1) * (int)(Cfg::kStageBytes / 2) + RPI * k * ld_mine) = r;
+  };
+  auto stage_step = [&](int t, int k) __attribute__((always_inline)) {   // chunk k of tile t is stored and that of the next requested
+    store(t, k, R[k]);
+    request(k);
+  };
+
+  if (t_begin < t_end) {   // (a split without tiles contributes the neutral partial)
+    look_up(t_begin);      // (tile 0 is a chunk tile, the chunk is never empty: no index, no cache length)
+    address(t_begin);
+    look_up(t_begin + 1);
+#pragma unroll
+    for (int k = 0; k < NLD; ++k) request(k);
+    if (set == 0) {   // K runs one tile ahead of V
+      u32x4 first[NLD];
+#pragma unroll
+      for (int k = 0; k < NLD; ++k) first[k] = R[k];
+      address(t_begin + 1);
+      look_up(t_begin + 2);
+#pragma unroll
+      for (int k = 0; k < NLD; ++k) request(k);
+#pragma unroll
+      for (int k = 0; k < NLD; ++k) store(t_begin, k, first[k]);
+    }
   }
-  QUOKA_RESOLVE(t_begin + 1);
 
   f32x16 o[DB];
 #pragma unroll
@@ -241,178 +268,205 @@ __global__ __launch_bounds__(2 * kSetThreads, 2) void attn_bf16(Dims dm, AttnArg
     for (int v = 0; v < 16; ++v) o[c][v] = 0.f;
   float m_run = -INFINITY;   // running row max, in the scaled log2 domain
   float l_run = 0.f;         // this half wave's share of the running row sum
-  // What the accumulator of K Q^T starts from.  !XS: -m_use in every entry, so the matrix core hands back s - m_use
+  // The reference point m_run only moves when a unit's maximum exceeds it by more than 2^kLazy: exp2(s - m_run) then stays below
+  // 2^kLazy, and rescaling the accumulators becomes rare.  `moves_above` is what a maximum is compared with (XS: in the scaled log2
+  // domain, else relative to the reference point): any score at all moves a row that has none yet.
+  constexpr float kLazy = 8.0f;
+  float moves_above = -INFINITY;
+  // What the accumulator of K Q^T starts from.  !XS: -m_run in every entry, so the matrix core hands back s - m_run
   // and the exponential needs no subtraction of its own; rewritten only when the reference point moves.  XS: zero.
   f32x16 cinit;
 #pragma unroll
   for (int v = 0; v < 16; ++v) cinit[v] = 0.f;
   const int tok = tok0 + li;
-  f32x16 s[2];               // S^T of the tile between its two halves
+  f32x16 s[2];          // S^T of a tile's two units of 32 keys
+  bf16x8 kop[KS];       // K operands of the unit whose S is formed next
+  s16x4 vop[2 * DB][2]; // V^T operands of the unit whose P V follows: block t2 * DB + c
+  bf16x8 p[2];          // P of that unit: k-slot e of this lane is key 16*t2 + 8*(e/4) + 4*hf + e%4
 
-  // first key (in the tile's own numbering: cache slot or chunk position) of this set's share of tile t
-  auto share_base = [&](int t) { return (t >= n_cht ? t - n_cht : t) * KT + sub; };
-  // whether this wave has anything visible in its share of tile t
-  auto computes = [&](int t) {
-    if (!wave_on) return false;
-    const int base = share_base(t);
-    return t < n_cht ? base <= tok0 + 31 : base < n_cache;
+  auto k_ptr = [&](int t, int u) __attribute__((always_inline)) {
+    return reinterpret_cast<const uint16_t*>(smem + (size_t)(t & 1) * Cfg::kStageBytes) + (sub + u * 32 + li) * LD + 8 * hf;
+  };
+  // lane's corner of every transposing read: key 4*hf + (lane%16)/4, dims 16*((lane/16)%2) + 4*(lane%4)
+  auto v_ptr = [&](int t, int u) __attribute__((always_inline)) {
+    return (tr_ptr)(reinterpret_cast<const uint16_t*>(smem + (size_t)(t & 1) * Cfg::kStageBytes + Cfg::kKTileBytes) +
+                    (sub + u * 32 + 4 * hf + ((lane & 15) >> 2)) * LDV + 16 * ((lane >> 4) & 1) + 4 * (lane & 3));
+  };
+  auto read_k = [&](const uint16_t* kp, int i) __attribute__((always_inline)) {
+    kop[i] = *reinterpret_cast<const bf16x8*>(kp + i * 16);
+  };
+  auto qk_step = [&](f32x16& sn, int i) __attribute__((always_inline)) {
+    sn = __builtin_amdgcn_mfma_f32_32x32x16_bf16(kop[i], qreg[i], i == 0 ? cinit : sn, 0, 0, 0);
+  };
+  // scores 2*e, 2*e+1 of a unit as probabilities: rounded to bf16, and added to the row sum as the matrix core sees them
+  auto to_p = [&](const f32x16& sc, int e, float psum) __attribute__((always_inline)) {
+    const bf16x2 pp = {(__bf16)sc[2 * e], (__bf16)sc[2 * e + 1]};
+    p[e / 4][2 * (e % 4)] = pp[0];
+    p[e / 4][2 * (e % 4) + 1] = pp[1];
+    return __builtin_amdgcn_fdot2_f32_bf16(pp, bf16x2{(__bf16)1.0f, (__bf16)1.0f}, psum, false);
   };
 
-  // ---- first half of a tile: S^T = K Q^T ---------------------------------------------------------
-  auto qk = [&](int t) __attribute__((always_inline)) {
-    const uint16_t* kt = reinterpret_cast<const uint16_t*>(smem + (size_t)(t & 1) * Cfg::kStageBytes);
+  // First half of a unit: S of the unit after it (`next`), and its own scores become probabilities meanwhile.
+  // The order of instructions is fixed: after every MFMA the operand reads of a step of the second half and 16 / KS exponentials.
+  auto half_qk = [&](auto next, f32x16& sn, f32x16& sc, tr_ptr vp, auto between) __attribute__((always_inline)) {
+    constexpr int E = 16 / KS;
+    const float neg_m = XS ? (m_run == -INFINITY ? 0.f : -m_run) : 0.f;   // (a row that has seen nothing yet: all its scores are -inf)
+    float psum = 0.f;
 #pragma unroll
-    for (int nb = 0; nb < 2; ++nb) {
-      const uint16_t* kp = kt + (sub + nb * 32 + li) * LD + 8 * hf;
-#pragma unroll
-      for (int ks = 0; ks < KS; ++ks) {
-        const bf16x8 kop = *reinterpret_cast<const bf16x8*>(kp + ks * 16);
-        s[nb] = __builtin_amdgcn_mfma_f32_32x32x16_bf16(kop, qreg[ks], ks == 0 ? cinit : s[nb], 0, 0, 0);
+    for (int i = 0; i < KS; ++i) {
+      if constexpr (decltype(next)::value) {
+        qk_step(sn, i);
+        __builtin_amdgcn_sched_barrier(0);
       }
+      const int e0 = (16 * (i / DB)) * LDV + (i % DB) * 32;   // elements past the lane's corner
+      vop[i][0] = __builtin_amdgcn_ds_read_tr16_b64_v4i16(vp + e0 / 4);
+      vop[i][1] = __builtin_amdgcn_ds_read_tr16_b64_v4i16(vp + (e0 + 8 * LDV) / 4);
+#pragma unroll
+      for (int e = E * i; e < E * i + E; ++e) sc[e] = __builtin_amdgcn_exp2f(XS ? fmaf(sc[e], qscale, neg_m) : sc[e]);
+      if (i > 0) {
+#pragma unroll
+        for (int e = E / 2 * (i - 1); e < E / 2 * i; ++e) psum = to_p(sc, e, psum);
+      }
+      between(i);
+      __builtin_amdgcn_sched_barrier(0);
     }
+#pragma unroll
+    for (int e = E / 2 * (KS - 1); e < 8; ++e) psum = to_p(sc, e, psum);
+    l_run += psum;
+    asm volatile("" : "+v"(p[0]), "+v"(p[1]), "+v"(l_run));   // (or the compiler moves all of it behind the next branch)
+    __builtin_amdgcn_sched_barrier(0);
   };
-
-  // ---- second half: mask, online softmax, O^T += V^T P^T ---------------------------------------
-  auto softmax_pv = [&](int t) __attribute__((always_inline)) {
-    const bool is_chunk = t < n_cht;
-    const int base = share_base(t);
-    const uint16_t* vt =
-        reinterpret_cast<const uint16_t*>(smem + (size_t)(t & 1) * Cfg::kStageBytes + Cfg::kKTileBytes) + sub * LDV;
-    const int limit = is_chunk ? (tok - base + 1) : (n_cache - base);   // keys kk < limit are visible
-    if (limit < kSub) {   // lane-varying for chunk tiles; only comparisons, no cross-lane traffic inside
-#pragma unroll
-      for (int nb = 0; nb < 2; ++nb)
-#pragma unroll
-        for (int v = 0; v < 16; ++v) {
-          const int kk = nb * 32 + 8 * (v / 4) + 4 * hf + (v % 4);
-          if (kk >= limit) s[nb][v] = -INFINITY;
-        }
-    }
-    // The reference point m_run only moves when the tile maximum exceeds it by more than 2^kLazy:
-    // exp2(s - m_run) then stays below 2^kLazy, and rescaling the accumulators becomes rare.
+  // Second half of a unit: O^T += V^T P^T; meanwhile the maximum of the next unit's scores, which it returns, and the K operands
+  // of the unit after that.
+  auto half_pv = [&](auto next, const f32x16& sn, const uint16_t* kp, auto between) __attribute__((always_inline)) {
+    constexpr int E = 16 / KS;
     float mx = -INFINITY;
 #pragma unroll
-    for (int nb = 0; nb < 2; ++nb)
+    for (int i = 0; i < KS; ++i) {
+      const s16x8 both = __builtin_shufflevector(vop[i][0], vop[i][1], 0, 1, 2, 3, 4, 5, 6, 7);
+      o[i % DB] = __builtin_amdgcn_mfma_f32_32x32x16_bf16(__builtin_bit_cast(bf16x8, both), p[i / DB], o[i % DB], 0, 0, 0);
+      __builtin_amdgcn_sched_barrier(0);
+      if constexpr (decltype(next)::value) {
+        read_k(kp, i);
 #pragma unroll
-      for (int v = 0; v < 16; ++v) mx = fmaxf(mx, s[nb][v]);
-    mx = fmaxf(mx, other_half(mx));
-    constexpr float kLazy = 8.0f;
-    if constexpr (XS) {
-      mx *= qscale;   // the row's largest score of this tile, scaled log2 domain (the products themselves are raw)
-      const bool moves = m_run == -INFINITY ? mx > -INFINITY : mx > m_run + kLazy;
-      if (__builtin_amdgcn_ballot_w64(moves) != 0) {   // wave-uniform branch
-        const float m_new = moves ? mx : m_run;
-        const float m_fin = (m_new == -INFINITY) ? 0.f : m_new;
-        const float alpha = __builtin_amdgcn_exp2f(m_run - m_fin);   // 0 for a row without a reference so far, 1 if unmoved
-        m_run = m_new;
-        l_run *= alpha;
-#pragma unroll
-        for (int c = 0; c < DB; ++c)
-#pragma unroll
-          for (int v = 0; v < 16; ++v) o[c][v] *= alpha;
+        for (int e = E * i; e < E * i + E; ++e) mx = fmaxf(mx, sn[e]);
+        asm volatile("" : "+v"(mx));   // (or all of it ends up behind the last product)
       }
-      const float neg_m = (m_run == -INFINITY) ? 0.f : -m_run;   // (a row that has seen nothing yet: all its scores are -inf)
+      between(KS + i);
+      __builtin_amdgcn_sched_barrier(0);
+    }
+    return mx;
+  };
+  // Keys of unit u of tile t that a row does not see (wave-uniform branch).
+  auto mask = [&](f32x16& sn, int t, int u) __attribute__((always_inline)) {
+    const bool is_chunk = t < n_cht;
+    const int base = share_base(t) + 32 * u;
+    if (base + 32 > (is_chunk ? tok0 + 1 : n_cache)) {
+      const int limit = (is_chunk ? tok + 1 : n_cache) - base - 4 * hf;   // register v is key 8*(v/4) + v%4 past the lane's first
 #pragma unroll
-      for (int nb = 0; nb < 2; ++nb)
+      for (int v = 0; v < 16; ++v)
+        if (8 * (v / 4) + v % 4 >= limit) sn[v] = -INFINITY;
+    }
+  };
+  // Moves the reference point where the maximum asks for it (wave-uniform branch, rare).
+  auto move_reference = [&](f32x16& sn, float mx) __attribute__((always_inline)) {
+    if constexpr (XS) mx *= qscale;   // (the products themselves are raw)
+    if (__builtin_amdgcn_ballot_w64(mx > moves_above) != 0) {
+      mx = fmaxf(mx, other_half(mx));   // of the row
+      const bool moves = mx > moves_above;
+      const float m_old = (m_run == -INFINITY) ? 0.f : m_run;    // !XS: what the scores are relative to
+      const float m_new = !moves ? m_run : XS ? mx : m_old + mx;
+      const float m_fin = (m_new == -INFINITY) ? 0.f : m_new;
+      const float alpha = __builtin_amdgcn_exp2f(m_run - m_fin);   // 0 for a row without a reference so far, 1 if unmoved
+      m_run = m_new;
+      moves_above = m_new == -INFINITY ? -INFINITY : XS ? m_new + kLazy : kLazy;
+      l_run *= alpha;
 #pragma unroll
-        for (int v = 0; v < 16; ++v) s[nb][v] = __builtin_amdgcn_exp2f(fmaf(s[nb][v], qscale, neg_m));
-    } else {
-      // (mx is relative to the reference point the tile was formed with)
-      const bool moves = m_run == -INFINITY ? mx > -INFINITY : mx > kLazy;
-      if (__builtin_amdgcn_ballot_w64(moves) != 0) {   // wave-uniform branch
-        const float m_old = (m_run == -INFINITY) ? 0.f : m_run;    // what the tile's scores are relative to
-        const float m_new = moves ? m_old + mx : m_run;
-        const float m_fin = (m_new == -INFINITY) ? 0.f : m_new;
-        const float alpha = __builtin_amdgcn_exp2f(m_run - m_fin);
+      for (int c = 0; c < DB; ++c)
+#pragma unroll
+        for (int v = 0; v < 16; ++v) o[c][v] *= alpha;
+      if constexpr (!XS) {
         const float shift = m_fin - m_old;
-        m_run = m_new;
-        l_run *= alpha;
 #pragma unroll
-        for (int c = 0; c < DB; ++c)
-#pragma unroll
-          for (int v = 0; v < 16; ++v) o[c][v] *= alpha;
-#pragma unroll
-        for (int nb = 0; nb < 2; ++nb)
-#pragma unroll
-          for (int v = 0; v < 16; ++v) s[nb][v] -= shift;
+        for (int v = 0; v < 16; ++v) sn[v] -= shift;
 #pragma unroll
         for (int v = 0; v < 16; ++v) cinit[v] = -m_fin;
       }
-#pragma unroll
-      for (int nb = 0; nb < 2; ++nb)
-#pragma unroll
-        for (int v = 0; v < 16; ++v) s[nb][v] = __builtin_amdgcn_exp2f(s[nb][v]);
     }
-    // lane's corner of every transposing read: key 4*hf + (lane%16)/4, dims 16*((lane/16)%2) + 4*(lane%4)
-    const tr_ptr vtr = (tr_ptr)(vt + (4 * hf + ((lane & 15) >> 2)) * LDV + 16 * ((lane >> 4) & 1) + 4 * (lane & 3));
-    float psum = 0.f;
-#pragma unroll
-    for (int nb = 0; nb < 2; ++nb) {
-#pragma unroll
-      for (int t2 = 0; t2 < 2; ++t2) {
-        // k-slot e of this lane is key 16*t2 + 8*(e/4) + 4*hf + e%4 of block nb
-        bf16x8 pb;
-#pragma unroll
-        for (int e = 0; e < 8; ++e) pb[e] = (__bf16)s[nb][8 * t2 + e];
-        // row sum of the probabilities as the matrix core sees them (rounded to bf16)
-#pragma unroll
-        for (int e = 0; e < 8; e += 2) {
-          const bf16x2 pp = {pb[e], pb[e + 1]};
-          psum = __builtin_amdgcn_fdot2_f32_bf16(pp, bf16x2{(__bf16)1.0f, (__bf16)1.0f}, psum, false);
-        }
-#pragma unroll
-        for (int c = 0; c < DB; ++c) {
-          const int e0 = (nb * 32 + 16 * t2) * LDV + c * 32;   // elements past the lane's corner
-          const s16x4 lo = __builtin_amdgcn_ds_read_tr16_b64_v4i16(vtr + e0 / 4);
-          const s16x4 hi = __builtin_amdgcn_ds_read_tr16_b64_v4i16(vtr + (e0 + 8 * LDV) / 4);
-          const s16x8 both = __builtin_shufflevector(lo, hi, 0, 1, 2, 3, 4, 5, 6, 7);
-          o[c] = __builtin_amdgcn_mfma_f32_32x32x16_bf16(__builtin_bit_cast(bf16x8, both), pb, o[c], 0, 0, 0);
-        }
-      }
-    }
-    l_run += psum;
   };
 
-  // Both sets run the same program -- per tile: barrier, stage the next tile and request the one after, S = K Q^T,
-  // barrier, softmax and P V -- but set 1 enters it one barrier late (and set 0 leaves it one barrier late), so the
-  // k-th barrier of set 0 is the (k-1)-th of set 1 and the sets stay half a step apart: while one forms S the other
-  // runs softmax and P V.  A set writes its tensor (set 0: K, set 1: V) of tile j+1 into LDS right after the first
-  // barrier of its step j, at the start of the half in which it only feeds the matrix core; the half that ends in
-  // softmax and P V, which sets the pace, carries no staging and no wait for global memory.
-  // Visibility: K of tile j+1 is stored by set 0 after block barrier 2j and is complete before block barrier 2j+2 (the
-  // fence of the storing waves' next first barrier), after which it is first read; V of tile j+1 is stored by set 1
-  // after block barrier 2j+1, complete before 2j+3 and first read, by set 0, after 2j+3.
-  // Reuse: the stage written in step j held tile j-1, whose last readers (both sets' S of that tile for K, both sets'
-  // P V for V) finished before the barrier the write follows.
-  auto stage_tile = [&](int t) __attribute__((always_inline)) {   // this set's tensor of tile t: registers -> LDS
-    uint16_t* dst = reinterpret_cast<uint16_t*>(smem + (size_t)(t & 1) * Cfg::kStageBytes + stage_off_mine);
-#pragma unroll
-    for (int i = 0; i < NLD; ++i) *reinterpret_cast<u32x4*>(dst + (r0 + RPI * i) * ld_mine + cg * 8) = R[i];
-  };
-  if (!KSPLIT || t_begin < t_end) stage_tile(t_begin);   // (a split without tiles contributes the neutral partial)
-  if (t_begin + 1 < t_end) {
-    QUOKA_ISSUE(t_begin + 1);
-    QUOKA_RESOLVE(t_begin + 2);
-  }
-  if (set == 1) __syncthreads();   // (with the fence: V of tile 0 is complete before set 0 passes its first barrier)
-  for (int j = t_begin; j < t_end; ++j) {
+  // Step j of the block: the next tiles go to LDS and those after them are requested (set 0: K, one tile ahead; set 1: V), then
+  // every wave works on tile j.  One barrier a step.  K of tile j+2 and V of tile j+1 are stored in step j and complete before the
+  // barrier of step j+1 (its fence), in which they are first read: the K operands of tile j+1 are read during tile j.  The places they
+  // take held K of tile j and V of tile j-1, whose last reads ended before the barrier of step j (the fence again).
+  auto begin_step = [&](int j) __attribute__((always_inline)) {
     __syncthreads();
-    if (j + 1 < t_end) {
-      stage_tile(j + 1);
-      if (j + 2 < t_end) {
-        QUOKA_ISSUE(j + 2);
-        QUOKA_RESOLVE(j + 3);
-      }
-    }
-    if (!computes(j)) {   // nothing visible for this wave in its share of the tile
-      __builtin_amdgcn_s_barrier();
-      continue;
-    }
-    qk(j);
-    __builtin_amdgcn_s_barrier();
-    softmax_pv(j);
+    address(j + 3 - set);
+    look_up(j + 4 - set);
+  };
+  auto stage_all = [&](int j) __attribute__((always_inline)) {
+#pragma unroll
+    for (int k = 0; k < NLD; ++k) stage_step(j + 2 - set, k);
+  };
+  using yes = std::integral_constant<bool, true>;
+  using no = std::integral_constant<bool, false>;
+  auto nothing = [](int) __attribute__((always_inline)) {};
+  int j = t_begin < t_end ? t_begin - 1 : t_end;
+  for (; j < min(w0 - 1, t_end); ++j) {
+    begin_step(j);
+    stage_all(j);
   }
-  if (set == 0) __builtin_amdgcn_s_barrier();
+  if (w0 < w1) {
+    // The staging of a step, a chunk at a time: between the products of the first unit's second half, or, where there are as many
+    // chunks as products in it (blocks of four row blocks, d 128), of both its halves.
+    auto staging = [&](int i) __attribute__((always_inline)) {
+      constexpr int first = NLD == KS ? 0 : KS, every = (2 * KS - first) / NLD;
+      if (i >= first && (i - first) % every == 0) stage_step(j + 2 - set, (i - first) / every);
+    };
+    begin_step(j);
+    {   // S of the first unit, the operands of the second
+      const uint16_t* kp = k_ptr(w0, 0);
+#pragma unroll
+      for (int i = 0; i < KS; ++i) read_k(kp, i);
+#pragma unroll
+      for (int i = 0; i < KS; ++i) qk_step(s[0], i);
+      const uint16_t* kp1 = k_ptr(w0, 1);
+#pragma unroll
+      for (int i = 0; i < KS; ++i) read_k(kp1, i);
+      mask(s[0], w0, 0);
+      float mx = -INFINITY;
+#pragma unroll
+      for (int v = 0; v < 16; ++v) mx = fmaxf(mx, s[0][v]);
+      move_reference(s[0], mx);
+    }
+    stage_all(j++);
+    for (; j + 1 < w1; ++j) {
+      begin_step(j);
+      half_qk(yes{}, s[1], s[0], v_ptr(j, 0), staging);
+      mask(s[1], j, 1);
+      float mx = half_pv(yes{}, s[1], k_ptr(j + 1, 0), staging);
+      move_reference(s[1], mx);
+      half_qk(yes{}, s[0], s[1], v_ptr(j, 1), nothing);
+      mask(s[0], j + 1, 0);
+      mx = half_pv(yes{}, s[0], k_ptr(j + 1, 1), nothing);
+      move_reference(s[0], mx);
+    }
+    begin_step(j);
+    half_qk(yes{}, s[1], s[0], v_ptr(j, 0), staging);
+    mask(s[1], j, 1);
+    float mx = -INFINITY;
+#pragma unroll
+    for (int v = 0; v < 16; ++v) mx = fmaxf(mx, s[1][v]);
+    half_pv(no{}, s[1], nullptr, staging);
+    move_reference(s[1], mx);
+    half_qk(no{}, s[0], s[1], v_ptr(j, 1), nothing);
+    half_pv(no{}, s[0], nullptr, nothing);
+    ++j;
+  }
+  for (; j < t_end; ++j) {
+    begin_step(j);
+    stage_all(j);
+  }
 
   // ---- merge of the two wave sets (SPLIT): set 1 hands (m, l, O) to set 0 through LDS ---------------------------
   if constexpr (SPLIT) {
@@ -512,9 +566,6 @@ __global__ __launch_bounds__(2 * kSetThreads, 2) void attn_bf16(Dims dm, AttnArg
     if (tok0 + r < C) *reinterpret_cast<u32x4*>(obase + (size_t)r * dm.os[2]) = rows_out[i];
   }
 }
-
-#undef QUOKA_RESOLVE
-#undef QUOKA_ISSUE
 
 // Sum of the key splits' partials: a wave takes one dim block of a row block and up to kMergeRun neighbouring splits at a time, all of
 // whose records are requested before the first is used, and the sums of the waves that share a dim block meet in LDS.  A block

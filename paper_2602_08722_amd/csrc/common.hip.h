@@ -119,6 +119,16 @@ __device__ __forceinline__ uint32_t dpp_take(uint32_t idle, uint32_t v) {
   return (uint32_t)__builtin_amdgcn_update_dpp((int)idle, (int)v, CTRL, ROW_MASK, 0xF, false);
 }
 
+// Value of lane `k` of the caller's 16-lane row (row_newbcast; k folds to a constant).
+__device__ __forceinline__ uint32_t row16_lane(uint32_t v, int k) {
+#define QUOKA_LANE(K) case K: return (uint32_t)__builtin_amdgcn_update_dpp(0, (int)v, 0x150 + K, 0xF, 0xF, true);
+  switch (k) {
+    QUOKA_LANE(0) QUOKA_LANE(1) QUOKA_LANE(2) QUOKA_LANE(3) QUOKA_LANE(4) QUOKA_LANE(5) QUOKA_LANE(6)
+    default: return (uint32_t)__builtin_amdgcn_update_dpp(0, (int)v, 0x157, 0xF, 0xF, true);
+  }
+#undef QUOKA_LANE
+}
+
 // Inclusive scan over the 64 lanes with OP (associative; IDLE its neutral element's bit pattern): four shifted steps
 // inside each row, then the row totals travel down.  Lane 63 ends with the reduction over the wave.
 #define QUOKA_WAVE_SCAN(x, OP, IDLE)                                   \

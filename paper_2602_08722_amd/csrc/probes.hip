@@ -6,8 +6,9 @@
 //   probe_attn_mix : the instruction mix of the attention kernel's step without its memory side -- per wave and
 //                step 16 MFMAs in two chains (S = K Q^T), then 32 exponentials and about 160 plain vector
 //                operations (scaling, max, conversion to bf16) interleaved with 16 MFMAs in four chains (O += P V);
-//                eight waves per compute unit, no LDS traffic, no barriers.  What it reaches is the ceiling of any
-//                kernel that keeps this work split (32 query rows per wave, two waves per SIMD).
+//                eight waves per compute unit, no LDS traffic, no barriers, in program order: what a kernel of this work
+//                split (32 query rows per wave, two waves per SIMD) reaches if it forms S, then softmax and O.  (The
+//                attention kernel forms the next S under the softmax.)
 #include "common.hip.h"
 #include "kernels.h"
 

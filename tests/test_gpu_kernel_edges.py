@@ -175,6 +175,20 @@ def test_bf16_attention_merge_of_splits(case):
     check_attention(dict(case, dtype="bf16"))
 
 
+# a wave works in units of 32 keys, the first of them formed ahead of the loop, the last without a successor: lists that end within and
+# at the end of the first and second unit of the first and second tile, chunks whose row blocks start in either unit of a tile;
+# blocks of four row blocks (chunk 97: the second wave set sees nothing of the first chunk tile) and of eight (batches of 32 heads)
+@pytest.mark.parametrize("scale_f32", [False, True], ids=["", "scale-f32"])
+@pytest.mark.parametrize("d", [64, 128])
+@pytest.mark.parametrize("case", [
+    dict(n_q=4, n_kv=2, chunk=97, kv_lens=[1, 33, 64, 65], budgets=[1, 33, 64, 65], batch=4),
+    dict(n_q=4, n_kv=2, chunk=128, kv_lens=[127, 128, 129, 0], budgets=[127, 128, 129, 0], batch=4),
+    dict(n_q=64, n_kv=16, chunk=289, kv_lens=[31, 32, 63, 130], budgets=[31, 32, 63, 130], batch=4),
+], ids=_id)
+def test_bf16_attention_units_and_runs_of_tiles(case, d, scale_f32):
+    check_attention(dict(case, dtype="bf16", d=d), score_flags=16 if scale_f32 else 0)
+
+
 # whole key lists of one sequence: one round of blocks of eight row blocks (130 of them, the last one not full; long lists
 # and none), and two rounds of blocks of four (264 of eight)
 @pytest.mark.parametrize("case", [
