@@ -29,9 +29,9 @@
 // One barrier per tile of 64 keys, K running one tile ahead of V.
 // What bounds it: the loop alone (operands from LDS, nothing staged) keeps the matrix core busy for 73 % of its clocks, at
 // 1.73 of 2.4 GHz, the clock that the power limit leaves (1.27 PFLOP/s; without the operand reads 1.44, without the conversion and sum
-// of the probabilities 1.44); staging costs 7 % of that.  Against two wave sets half a step apart, one forming S while the other ran
-// softmax and P V behind it (two barriers a tile), attention by itself, us: 32/8 heads, d 128, 4096 tokens over 8192 keys 645 -> 585,
-// 2048 over 3932 165 -> 155, 1024 over 983 37.7 -> 33.9, 1024 over all of 8192 157 -> 142; d 64, 1500 over 2400 70 -> 59.
+// of the probabilities 1.44).  Against two wave sets half a step apart, one forming S while the other ran softmax and P V behind
+// it (two barriers a tile, staging through registers), attention by itself, us: 32/8 heads, d 128, 4096 tokens over 8192 keys 627 -> 560
+// (1.23 PFLOP/s), 2048 over 3932 171 -> 148, 1024 over 983 37.2 -> 31.7, 1024 over all of 8192 159 -> 133; d 64, 1500 over 2400 70 -> 60.
 #include "common.hip.h"
 #include "kernels.h"
 
@@ -66,21 +66,44 @@ __device__ __forceinline__ int seq_of_rank(const int32_t* __restrict__ lens, int
   return hit ? (int)__builtin_ctzll(hit) : rank;
 }
 
+// LDS[m0 + lane * 16 .. + 16] <- 16 bytes at base + voff (per lane); completion is counted by vmcnt
+__device__ __forceinline__ void dma16(const char* base, uint32_t voff, uint32_t lds_addr) {
+  asm volatile("s_mov_b32 m0, %0\n\ts_nop 0\n\tglobal_load_lds_dwordx4 %1, %2" ::"s"(lds_addr), "v"(voff), "s"(base)
+               : "memory", "m0");
+}
+template <int N>
+__device__ __forceinline__ void wait_vmcnt() {
+  asm volatile("s_waitcnt vmcnt(%0)" ::"n"(N) : "memory");
+}
+template <int D>
+__device__ __forceinline__ int k_swizzle(int row) { return D == 128 ? row & 3 : (row >> 1) & 3; }
+template <int D>
+__device__ __forceinline__ int v_swizzle(int row) { return D == 128 ? 4 * (row & 3) : 4 * ((row >> 1) & 1); }
+
 template <int D, bool SPLIT>
 struct AttnCfg {
   static constexpr int KT = SPLIT ? 2 * kSub : kSub;  // keys per staged tile
   static constexpr int KS = D / 16;                   // k-steps of the QK^T product
-  static constexpr int LD = D + 8;                    // padded LDS row of the K tile (elements)
-  static constexpr int LDV = D + 32;                  // V tile: rows 64 bytes apart modulo 256, so the 8 rows x 64 bytes
-                                                      // one transposing read touches fall on distinct banks per half wave
   static constexpr int CG = D / 8;                    // 16-byte chunks per row
   static constexpr int RPI = kSetThreads / CG;        // rows per set-wide load
   static constexpr int NLD = KT / RPI;                // loads per thread per tile (set 0 loads K, set 1 loads V)
   static constexpr int DB = D / 32;                   // dim blocks of the PV product
   static constexpr int HW = SPLIT ? 2 : 4;            // front (= back) row blocks per block
-  static constexpr size_t kKTileBytes = (size_t)KT * LD * 2;
-  static constexpr size_t kStageBytes = kKTileBytes + (size_t)KT * LDV * 2;   // one K tile and one V tile
-  static constexpr size_t kLdsBytes = 2 * kStageBytes;                          // double buffered
+  // LDS: a wave-wide load fills a group of RPW rows, 1 KiB.  The 16-byte chunks of a row are permuted by the fetch (k_swizzle,
+  // v_swizzle), and K's groups lie 64 bytes apart modulo 256: the 16 rows that lanes read a chunk of at a time (K), and the four rows x
+  // 64 bytes of a transposing read by half a wave (V), are 256 bytes on distinct banks.
+  // Tiles go straight from memory to LDS, except with blocks of eight row blocks at d 64, whose steps are the shortest (1 us): through
+  // registers a load has two steps' time, not one (d 64, 333 tokens over 5000 keys 37.1 -> 36.0 us, 1500 over 2400 61.1 -> 59.9).
+  // Elsewhere the stores to LDS were what staging cost (by leaving them out, blocks of eight 7 %, of four 17 - 22 %), and direct loads take
+  // them off the waves: 32/8 heads, d 128, 1024 tokens over 8192 keys 140.7 -> 133.2 us, 1024 over 983 33.6 -> 31.7, 4096 over 8192
+  // 576 -> 560.  (Three stages, so that every load has two steps: 1 - 3 % slower throughout.)
+  static constexpr bool DMA = D == 128 || SPLIT;
+  static constexpr int RPW = 64 / CG, ROW = D * 2;
+  static constexpr int KG = 1024 + 64, VG = 1024;   // pitches of a group
+  static constexpr int kKTileBytes = KT / RPW * KG;
+  static constexpr int kStageBytes = kKTileBytes + KT / RPW * VG;   // one K tile and one V tile
+  static constexpr size_t kOutBytes = (size_t)8 * 32 * (D + 8) * 2;   // what the rows go out through
+  static constexpr size_t kLdsBytes = (size_t)2 * kStageBytes > kOutBytes ? (size_t)2 * kStageBytes : kOutBytes;
   static constexpr int kRecFloats = 32 * (D + 2);     // partial of a row block: O as the registers lie, m, l
 };
 
@@ -99,7 +122,8 @@ struct AttnCfg {
 template <int D, bool SPLIT, bool XS, bool KSPLIT, bool WHOLE>
 __global__ __launch_bounds__(2 * kSetThreads, 2) void attn_bf16(Dims dm, AttnArgs a) {
   using Cfg = AttnCfg<D, SPLIT>;
-  constexpr int KT = Cfg::KT, KS = Cfg::KS, LD = Cfg::LD, LDV = Cfg::LDV, CG = Cfg::CG, RPI = Cfg::RPI, NLD = Cfg::NLD,
+  constexpr bool DMA = Cfg::DMA;
+  constexpr int KT = Cfg::KT, KS = Cfg::KS, CG = Cfg::CG, RPI = Cfg::RPI, NLD = Cfg::NLD,
                 DB = Cfg::DB, HW = Cfg::HW;
   extern __shared__ __align__(16) unsigned char smem[];
 
@@ -177,16 +201,13 @@ __global__ __launch_bounds__(2 * kSetThreads, 2) void attn_bf16(Dims dm, AttnArg
   const char* chunk_base = reinterpret_cast<const char*>(static_cast<const uint16_t*>(chunk_t) + b * dm.cks[0] + kv * dm.cks[1]);
   const char* kidx = sparse ? reinterpret_cast<const char*>(a.k_idx + (size_t)(b * dm.n_kv + kv) * dm.B_max) : nullptr;
   const uint32_t cache_row_bytes = (uint32_t)dm.kvs[2] * 2u, chunk_row_bytes = (uint32_t)dm.cks[2] * 2u;
-  const int ld_mine = set == 0 ? LD : LDV;                              // LDS row pitch of the tensor this set stages
-  const size_t stage_off_mine = set == 0 ? 0 : Cfg::kKTileBytes;      // its place inside a stage
-
-  // Q operand: row tok0 + li, dims ks*16 + 8*hf .. +8
+  // Q operand: row tok0 + li, chunk ks + KS*hf of 8 dims
   bf16x8 qreg[KS];
   {
     const int tokq = min(tok0 + li, C - 1);
-    const uint16_t* qrow = qg + b * dm.qs[0] + h * dm.qs[1] + (size_t)tokq * dm.qs[2] + 8 * hf;
+    const uint16_t* qrow = qg + b * dm.qs[0] + h * dm.qs[1] + (size_t)tokq * dm.qs[2] + 8 * KS * hf;
 #pragma unroll
-    for (int ks = 0; ks < KS; ++ks) qreg[ks] = *reinterpret_cast<const bf16x8*>(qrow + ks * 16);
+    for (int ks = 0; ks < KS; ++ks) qreg[ks] = *reinterpret_cast<const bf16x8*>(qrow + ks * 8);
   }
   // the softmax scale and the change to base 2
   const float qscale = 1.4426950408889634f / sqrtf((float)D);
@@ -197,17 +218,18 @@ __global__ __launch_bounds__(2 * kSetThreads, 2) void attn_bf16(Dims dm, AttnArg
       for (int e = 0; e < 8; ++e) qreg[ks][e] = (__bf16)((float)qreg[ks][e] * qscale);
   }
 
-  // Staging.  Thread (r0, cg) carries chunk cg of rows r0 + RPI * k of this set's tensor, k < NLD, from memory through registers to LDS.
+  // Staging.  Thread (r0, cg) fetches slot cg of rows r0 + RPI * k of this set's tensor, k < NLD: a load of a wave fills a group.
   // Source rows of a tile are looked up a step ahead of the loads that use them, so the dependent index -> row fetch of the gather
   // never sits on the critical path.  At d 128 the 16 lanes that carry a row look up NLD rows between them, one each, and take
   // them from each other where they are used: one register instead of NLD.
   constexpr bool kShare = CG == 16;
   constexpr int NI = kShare ? 1 : NLD;
-  const int cg = tid % CG, r0 = tid / CG;
+  const int r0 = tid / CG;
+  const uint32_t cg_src = (uint32_t)(tid % CG ^ (set == 0 ? k_swizzle<D>(lane / CG) : v_swizzle<D>(lane / CG))) * 16u;
   const uint32_t idx_max = (uint32_t)max(dm.T_max - 1, 0);
   uint32_t src[NI];     // rows of the tile to be requested next, as looked up
   uint32_t off[NI];     // the same as byte offsets, of the tile being requested
-  u32x4 R[NLD];         // the tile in flight
+  u32x4 R[DMA ? 1 : NLD];   // the tile in flight (not DMA)
   auto look_up = [&](int t) __attribute__((always_inline)) {
     t = min(t, t_end - 1);   // (past the list's end the last tile is requested again, and nothing reads it)
     const bool cache = t >= n_cht;
@@ -227,19 +249,24 @@ __global__ __launch_bounds__(2 * kSetThreads, 2) void attn_bf16(Dims dm, AttnArg
     // Cache rows are clamped to the cache extent: a malformed list (negative or too large) cannot leave the tensor.
     const uint32_t row_bytes = cache ? cache_row_bytes : chunk_row_bytes, row_max = cache ? idx_max : 0xffffffffu;
 #pragma unroll
-    for (int i = 0; i < NI; ++i) off[i] = min(src[i], row_max) * row_bytes + (kShare ? 0u : (uint32_t)cg * 16u);
+    for (int i = 0; i < NI; ++i) off[i] = min(src[i], row_max) * row_bytes + (kShare ? 0u : cg_src);
   };
-  auto request = [&](int k) __attribute__((always_inline)) {
-    const uint32_t o = kShare ? row16_lane(off[0], k) + (uint32_t)cg * 16u : off[k % NI];
-    R[k] = *reinterpret_cast<const u32x4*>(req_base + o);
+  const uint32_t lds0 = (uint32_t)(uintptr_t)(__attribute__((address_space(3))) void*)smem;
+  const uint32_t group_mine = set == 0 ? Cfg::KG : Cfg::VG;
+  const uint32_t dst_mine = lds0 + (set == 0 ? 0u : (uint32_t)Cfg::kKTileBytes) + (uint32_t)w * group_mine;
+  auto stage_of = [&](int t) __attribute__((always_inline)) { return (t & 1) * Cfg::kStageBytes; };
+  auto request = [&](int t, int k) __attribute__((always_inline)) {   // chunk k of tile t
+    const uint32_t o = kShare ? row16_lane(off[0], k) + cg_src : off[k % NI];
+    if constexpr (DMA) dma16(req_base, o, dst_mine + (uint32_t)stage_of(t) + 4u * k * group_mine);
+    else R[k] = *reinterpret_cast<const u32x4*>(req_base + o);
   };
-  uint16_t* const stage_dst = reinterpret_cast<uint16_t*>(smem + stage_off_mine) + r0 * ld_mine + cg * 8;
-  auto store = [&](int t, int k, u32x4 r) __attribute__((always_inline)) {
-    *reinterpret_cast<u32x4*>(stage_dst + (t & 1) * (int)(Cfg::kStageBytes / 2) + RPI * k * ld_mine) = r;
+  auto store = [&](int t, int k, u32x4 r) __attribute__((always_inline)) {   // (not DMA)
+    *(u32x4 __attribute__((address_space(3)))*)(uintptr_t)(dst_mine + lane * 16u + (uint32_t)stage_of(t) + 4u * k * group_mine) = r;
   };
-  auto stage_step = [&](int t, int k) __attribute__((always_inline)) {   // chunk k of tile t is stored and that of the next requested
-    store(t, k, R[k]);
-    request(k);
+  // Step j takes chunk k of tile j+2 (K) or j+1 (V) to LDS; through registers it was requested a step earlier.
+  auto stage = [&](int j, int k) __attribute__((always_inline)) {
+    if constexpr (!DMA) store(j + 2 - set, k, R[k]);
+    request(DMA ? j + 2 - set : j + 3 - set, k);
   };
 
   if (t_begin < t_end) {   // (a split without tiles contributes the neutral partial)
@@ -247,17 +274,21 @@ __global__ __launch_bounds__(2 * kSetThreads, 2) void attn_bf16(Dims dm, AttnArg
     address(t_begin);
     look_up(t_begin + 1);
 #pragma unroll
-    for (int k = 0; k < NLD; ++k) request(k);
+    for (int k = 0; k < NLD; ++k) request(t_begin, k);
     if (set == 0) {   // K runs one tile ahead of V
-      u32x4 first[NLD];
+      u32x4 first[DMA ? 1 : NLD];
+      if constexpr (!DMA) {
 #pragma unroll
-      for (int k = 0; k < NLD; ++k) first[k] = R[k];
+        for (int k = 0; k < NLD; ++k) first[k] = R[k];
+      }
       address(t_begin + 1);
       look_up(t_begin + 2);
 #pragma unroll
-      for (int k = 0; k < NLD; ++k) request(k);
+      for (int k = 0; k < NLD; ++k) request(t_begin + 1, k);
+      if constexpr (!DMA) {
 #pragma unroll
-      for (int k = 0; k < NLD; ++k) store(t_begin, k, first[k]);
+        for (int k = 0; k < NLD; ++k) store(t_begin, k, first[k]);
+      }
     }
   }
 
@@ -284,16 +315,36 @@ __global__ __launch_bounds__(2 * kSetThreads, 2) void attn_bf16(Dims dm, AttnArg
   s16x4 vop[2 * DB][2]; // V^T operands of the unit whose P V follows: block t2 * DB + c
   bf16x8 p[2];          // P of that unit: k-slot e of this lane is key 16*t2 + 8*(e/4) + 4*hf + e%4
 
-  auto k_ptr = [&](int t, int u) __attribute__((always_inline)) {
-    return reinterpret_cast<const uint16_t*>(smem + (size_t)(t & 1) * Cfg::kStageBytes) + (sub + u * 32 + li) * LD + 8 * hf;
+  // Chunk c of row r of a group lies at slot c ^ k_swizzle(r) (K: the low two bits) or c ^ v_swizzle(r) (V: bit 2 and 3).
+  uint32_t ka[4];     // K: places of chunks ks % 4 (+ KS for the upper half wave) of row li
+#pragma unroll
+  for (int q = 0; q < 4; ++q)
+    ka[q] = lds0 + (uint32_t)(stage_of(w0) + (sub + li) / Cfg::RPW * Cfg::KG + li % Cfg::RPW * Cfg::ROW + ((q ^ k_swizzle<D>(li % Cfg::RPW)) + KS * hf) * 16);
+  uint32_t va[DB];    // V: the lane's corner of the transposing reads of dim block c: key 4*hf + (lane%16)/4, dims 16*((lane/16)%2) + 4*(lane%4)
+#pragma unroll
+  for (int c = 0; c < DB; ++c) {
+    const int r = 4 * hf + ((lane & 15) >> 2);
+    va[c] = lds0 + (uint32_t)(stage_of(w0) + Cfg::kKTileBytes + (sub + r) * Cfg::ROW + (((4 * c) ^ v_swizzle<D>(r % Cfg::RPW)) + 2 * ((lane >> 4) & 1) + ((lane & 3) >> 1)) * 16 + 8 * (lane & 1));
+  }
+  // (the places move between the two stages by one addition a tile each)
+  auto move_k = [&](int t) __attribute__((always_inline)) {   // from tile t to tile t + 1
+    const uint32_t by = (uint32_t)((t & 1) ? -Cfg::kStageBytes : Cfg::kStageBytes);
+#pragma unroll
+    for (int q = 0; q < 4; ++q) {
+      ka[q] += by;
+      asm volatile("" : "+v"(ka[q]));
+    }
   };
-  // lane's corner of every transposing read: key 4*hf + (lane%16)/4, dims 16*((lane/16)%2) + 4*(lane%4)
-  auto v_ptr = [&](int t, int u) __attribute__((always_inline)) {
-    return (tr_ptr)(reinterpret_cast<const uint16_t*>(smem + (size_t)(t & 1) * Cfg::kStageBytes + Cfg::kKTileBytes) +
-                    (sub + u * 32 + 4 * hf + ((lane & 15) >> 2)) * LDV + 16 * ((lane >> 4) & 1) + 4 * (lane & 3));
+  auto move_v = [&](int t) __attribute__((always_inline)) {
+    const uint32_t by = (uint32_t)((t & 1) ? -Cfg::kStageBytes : Cfg::kStageBytes);
+#pragma unroll
+    for (int c = 0; c < DB; ++c) {
+      va[c] += by;
+      asm volatile("" : "+v"(va[c]));
+    }
   };
-  auto read_k = [&](const uint16_t* kp, int i) __attribute__((always_inline)) {
-    kop[i] = *reinterpret_cast<const bf16x8*>(kp + i * 16);
+  auto read_k = [&](int u, int i) __attribute__((always_inline)) {
+    kop[i] = ((const bf16x8 __attribute__((address_space(3)))*)(uintptr_t)ka[i % 4])[i / 4 * 4 + u * (32 / Cfg::RPW * Cfg::KG / 16)];
   };
   auto qk_step = [&](f32x16& sn, int i) __attribute__((always_inline)) {
     sn = __builtin_amdgcn_mfma_f32_32x32x16_bf16(kop[i], qreg[i], i == 0 ? cinit : sn, 0, 0, 0);
@@ -308,7 +359,7 @@ __global__ __launch_bounds__(2 * kSetThreads, 2) void attn_bf16(Dims dm, AttnArg
 
   // First half of a unit: S of the unit after it (`next`), and its own scores become probabilities meanwhile.
   // The order of instructions is fixed: after every MFMA the operand reads of a step of the second half and 16 / KS exponentials.
-  auto half_qk = [&](auto next, f32x16& sn, f32x16& sc, tr_ptr vp, auto between) __attribute__((always_inline)) {
+  auto half_qk = [&](auto next, f32x16& sn, f32x16& sc, int u, auto between) __attribute__((always_inline)) {
     constexpr int E = 16 / KS;
     const float neg_m = XS ? (m_run == -INFINITY ? 0.f : -m_run) : 0.f;   // (a row that has seen nothing yet: all its scores are -inf)
     float psum = 0.f;
@@ -318,9 +369,9 @@ __global__ __launch_bounds__(2 * kSetThreads, 2) void attn_bf16(Dims dm, AttnArg
         qk_step(sn, i);
         __builtin_amdgcn_sched_barrier(0);
       }
-      const int e0 = (16 * (i / DB)) * LDV + (i % DB) * 32;   // elements past the lane's corner
-      vop[i][0] = __builtin_amdgcn_ds_read_tr16_b64_v4i16(vp + e0 / 4);
-      vop[i][1] = __builtin_amdgcn_ds_read_tr16_b64_v4i16(vp + (e0 + 8 * LDV) / 4);
+      const tr_ptr vp_c = (tr_ptr)(uintptr_t)va[i % DB] + (32 * u + 16 * (i / DB)) * Cfg::ROW / 8;
+      vop[i][0] = __builtin_amdgcn_ds_read_tr16_b64_v4i16(vp_c);
+      vop[i][1] = __builtin_amdgcn_ds_read_tr16_b64_v4i16(vp_c + Cfg::ROW);
 #pragma unroll
       for (int e = E * i; e < E * i + E; ++e) sc[e] = __builtin_amdgcn_exp2f(XS ? fmaf(sc[e], qscale, neg_m) : sc[e]);
       if (i > 0) {
@@ -338,7 +389,7 @@ __global__ __launch_bounds__(2 * kSetThreads, 2) void attn_bf16(Dims dm, AttnArg
   };
   // Second half of a unit: O^T += V^T P^T; meanwhile the maximum of the next unit's scores, which it returns, and the K operands
   // of the unit after that.
-  auto half_pv = [&](auto next, const f32x16& sn, const uint16_t* kp, auto between) __attribute__((always_inline)) {
+  auto half_pv = [&](auto next, const f32x16& sn, int u, auto between) __attribute__((always_inline)) {
     constexpr int E = 16 / KS;
     float mx = -INFINITY;
 #pragma unroll
@@ -347,7 +398,7 @@ __global__ __launch_bounds__(2 * kSetThreads, 2) void attn_bf16(Dims dm, AttnArg
       o[i % DB] = __builtin_amdgcn_mfma_f32_32x32x16_bf16(__builtin_bit_cast(bf16x8, both), p[i / DB], o[i % DB], 0, 0, 0);
       __builtin_amdgcn_sched_barrier(0);
       if constexpr (decltype(next)::value) {
-        read_k(kp, i);
+        read_k(u, i);
 #pragma unroll
         for (int e = E * i; e < E * i + E; ++e) mx = fmaxf(mx, sn[e]);
         asm volatile("" : "+v"(mx));   // (or all of it ends up behind the last product)
@@ -395,18 +446,27 @@ __global__ __launch_bounds__(2 * kSetThreads, 2) void attn_bf16(Dims dm, AttnArg
     }
   };
 
-  // Step j of the block: the next tiles go to LDS and those after them are requested (set 0: K, one tile ahead; set 1: V), then
-  // every wave works on tile j.  One barrier a step.  K of tile j+2 and V of tile j+1 are stored in step j and complete before the
-  // barrier of step j+1 (its fence), in which they are first read: the K operands of tile j+1 are read during tile j.  The places they
-  // take held K of tile j and V of tile j-1, whose last reads ended before the barrier of step j (the fence again).
+  // Step j of the block: K of tile j+2 and V of tile j+1 go to LDS (set 0: K, set 1: V) and every wave works on tile j.  One barrier a
+  // step.  What step j brings is complete before the barrier of step j+1 (the wait and the fence ahead of it), in which it is first
+  // read: the K operands of tile j+1 are read during tile j.  The places it takes held K of tile j and V of tile j-1, whose last reads
+  // ended before the barrier of step j (the fence again).  DMA: the first step's tiles are requested ahead of the loop.
   auto begin_step = [&](int j) __attribute__((always_inline)) {
+    if constexpr (DMA) {
+      if (j < t_begin) {   // (its tiles are on their way; K of the first one has to be there)
+        wait_vmcnt<NLD>();
+        __syncthreads();
+        return;
+      }
+      wait_vmcnt<0>();
+    }
     __syncthreads();
-    address(j + 3 - set);
-    look_up(j + 4 - set);
+    address(DMA ? j + 2 - set : j + 3 - set);
+    look_up(DMA ? j + 3 - set : j + 4 - set);
   };
   auto stage_all = [&](int j) __attribute__((always_inline)) {
+    if (DMA && (j < t_begin || j + 2 - set >= t_end)) return;
 #pragma unroll
-    for (int k = 0; k < NLD; ++k) stage_step(j + 2 - set, k);
+    for (int k = 0; k < NLD; ++k) stage(j, k);
   };
   using yes = std::integral_constant<bool, true>;
   using no = std::integral_constant<bool, false>;
@@ -417,22 +477,20 @@ __global__ __launch_bounds__(2 * kSetThreads, 2) void attn_bf16(Dims dm, AttnArg
     stage_all(j);
   }
   if (w0 < w1) {
-    // The staging of a step, a chunk at a time: between the products of the first unit's second half, or, where there are as many
+    // The staging of a step, a load at a time: between the products of the first unit's second half, or, where there are as many
     // chunks as products in it (blocks of four row blocks, d 128), of both its halves.
     auto staging = [&](int i) __attribute__((always_inline)) {
       constexpr int first = NLD == KS ? 0 : KS, every = (2 * KS - first) / NLD;
-      if (i >= first && (i - first) % every == 0) stage_step(j + 2 - set, (i - first) / every);
+      if (i >= first && (i - first) % every == 0) stage(j, (i - first) / every);
     };
     begin_step(j);
     {   // S of the first unit, the operands of the second
-      const uint16_t* kp = k_ptr(w0, 0);
 #pragma unroll
-      for (int i = 0; i < KS; ++i) read_k(kp, i);
+      for (int i = 0; i < KS; ++i) read_k(0, i);
 #pragma unroll
       for (int i = 0; i < KS; ++i) qk_step(s[0], i);
-      const uint16_t* kp1 = k_ptr(w0, 1);
 #pragma unroll
-      for (int i = 0; i < KS; ++i) read_k(kp1, i);
+      for (int i = 0; i < KS; ++i) read_k(1, i);
       mask(s[0], w0, 0);
       float mx = -INFINITY;
 #pragma unroll
@@ -442,31 +500,35 @@ __global__ __launch_bounds__(2 * kSetThreads, 2) void attn_bf16(Dims dm, AttnArg
     stage_all(j++);
     for (; j + 1 < w1; ++j) {
       begin_step(j);
-      half_qk(yes{}, s[1], s[0], v_ptr(j, 0), staging);
+      move_k(j);
+      half_qk(yes{}, s[1], s[0], 0, staging);
       mask(s[1], j, 1);
-      float mx = half_pv(yes{}, s[1], k_ptr(j + 1, 0), staging);
+      float mx = half_pv(yes{}, s[1], 0, staging);
       move_reference(s[1], mx);
-      half_qk(yes{}, s[0], s[1], v_ptr(j, 1), nothing);
+      half_qk(yes{}, s[0], s[1], 1, nothing);
+      move_v(j);
       mask(s[0], j + 1, 0);
-      mx = half_pv(yes{}, s[0], k_ptr(j + 1, 1), nothing);
+      mx = half_pv(yes{}, s[0], 1, nothing);
       move_reference(s[0], mx);
     }
     begin_step(j);
-    half_qk(yes{}, s[1], s[0], v_ptr(j, 0), staging);
+    stage_all(j);
+    half_qk(yes{}, s[1], s[0], 0, nothing);
     mask(s[1], j, 1);
     float mx = -INFINITY;
 #pragma unroll
     for (int v = 0; v < 16; ++v) mx = fmaxf(mx, s[1][v]);
-    half_pv(no{}, s[1], nullptr, staging);
+    half_pv(no{}, s[1], 0, nothing);
     move_reference(s[1], mx);
-    half_qk(no{}, s[0], s[1], v_ptr(j, 1), nothing);
-    half_pv(no{}, s[0], nullptr, nothing);
+    half_qk(no{}, s[0], s[1], 1, nothing);
+    half_pv(no{}, s[0], 0, nothing);
     ++j;
   }
   for (; j < t_end; ++j) {
     begin_step(j);
     stage_all(j);
   }
+  wait_vmcnt<0>();   // nothing may land in LDS from here on
 
   // ---- merge of the two wave sets (SPLIT): set 1 hands (m, l, O) to set 0 through LDS ---------------------------
   if constexpr (SPLIT) {
