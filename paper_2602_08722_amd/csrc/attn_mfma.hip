@@ -484,7 +484,7 @@ __global__ __launch_bounds__(2 * kSetThreads, 2) void attn_bf16(Dims dm, AttnArg
       if (i >= first && (i - first) % every == 0) stage(j, (i - first) / every);
     };
     begin_step(j);
-    {   // S of the first unit, the operands of the second
+    {   // S of the first unit, the operands of the second, the reference point
 #pragma unroll
       for (int i = 0; i < KS; ++i) read_k(0, i);
 #pragma unroll
@@ -495,6 +495,13 @@ __global__ __launch_bounds__(2 * kSetThreads, 2) void attn_bf16(Dims dm, AttnArg
       float mx = -INFINITY;
 #pragma unroll
       for (int v = 0; v < 16; ++v) mx = fmaxf(mx, s[0][v]);
+      // The reference point is the maximum over the whole tile, whose second unit is formed for it and again in its turn: where a row's
+      // largest probability is 1 it is not rounded (with the first unit's maximum alone outputs lay 0.5 % further from float64; 0.3 us).
+#pragma unroll
+      for (int i = 0; i < KS; ++i) qk_step(s[1], i);
+      mask(s[1], w0, 1);
+#pragma unroll
+      for (int v = 0; v < 16; ++v) mx = fmaxf(mx, s[1][v]);
       move_reference(s[0], mx);
     }
     stage_all(j++);
