@@ -361,7 +361,7 @@ static quoka_status select_keys_common(const Dims& dm, int dtype, const float* q
       return from_hip(quoka::launch_select_keys_exact(dm, qbar, k_cache, kv_lens, budgets, scores, k_idx, k_cnt, sel_ws, terms,
                                                       hs));
     return from_hip(quoka::launch_select_keys(dm, qbar, k_cache, kv_lens, budgets, scores, k_idx, k_cnt, sel_ws, hs,
-                                              sel_ws_is_zero));
+                                              sel_ws_is_zero, terms));
   }
   uint32_t* topk_ws = reinterpret_cast<uint32_t*>(static_cast<char*>(workspace) + l.topk_off);
   const bool fuse_clear = quoka::topk_uses_ws(dm);
@@ -410,11 +410,13 @@ static quoka_status chunk_common(const quoka_shape* shape, const CallInfo& info,
   if (st != QUOKA_OK) return st;
   hipStream_t hs = static_cast<hipStream_t>(stream);
   const bool two_pass = dm.T_max > 0 && quoka::select_keys_two_pass_applies(dm, shape->dtype);
-  const bool exact = two_pass && !info.of_prompt && quoka::select_keys_exact_pays(dm, shape->dtype);   // (the same lists)
+  // (the same lists, either way)
+  const bool streams_exact = two_pass && !info.of_prompt && quoka::select_keys_streams_exact(dm, shape->dtype);
+  const bool exact = two_pass && !info.of_prompt && !streams_exact && quoka::select_keys_exact_pays(dm, shape->dtype);
   uint32_t* sel_ws = reinterpret_cast<uint32_t*>(static_cast<char*>(workspace) + l.sel_off);
   float* sq_ws = reinterpret_cast<float*>(static_cast<char*>(workspace) + l.select_off);
   quoka::FusedQbar fq;
-  uint16_t* terms = (!two_pass || exact) && quoka::score_reads_terms(dm, shape->dtype)
+  uint16_t* terms = (!two_pass || exact || streams_exact) && quoka::score_reads_terms(dm, shape->dtype)
                         ? reinterpret_cast<uint16_t*>(static_cast<char*>(workspace) + l.terms_off)
                         : nullptr;
   if (!two_pass && quoka::score_forms_qbar(dm, shape->dtype)) {   // a few tokens: one launch less

@@ -61,8 +61,8 @@ hipError_t launch_topk_keys(const Dims& dm, const float* scores, const int32_t* 
 // Provisional one-term scores, exact re-scoring of the keys near the cut, ordered emission: the same index lists as
 // launch_score_keys followed by launch_topk_keys.  `ws_is_zero`: the first select_keys_zero_words words of the
 // workspace have already been cleared on this stream.
-hipError_t launch_score_stream(const Dims& dm, const float* qbar, const void* k_cache, const int32_t* kv_lens,
-                               float* scores, uint32_t* hist_ws, hipStream_t st);
+hipError_t launch_score_stream(const Dims& dm, const float* qbar, const uint16_t* terms, const void* k_cache,
+                               const int32_t* kv_lens, float* scores, uint32_t* hist_ws, hipStream_t st);
 bool select_keys_two_pass_applies(const Dims& dm, int dtype);
 // The same lists from exact scores and their histogram (launch_score_hist), which is the faster up to a size; `terms` as
 // launch_select_queries leaves them, the workspace cleared as for launch_select_keys.
@@ -76,7 +76,9 @@ size_t select_keys_ws_words(const Dims& dm);
 size_t select_keys_zero_words(const Dims& dm, bool exact);   // (`exact`: for launch_select_keys_exact)
 hipError_t launch_select_keys(const Dims& dm, const float* qbar, const void* k_cache, const int32_t* kv_lens,
                               const int32_t* budgets, float* scores, int32_t* k_idx, int32_t* k_cnt, uint32_t* ws,
-                              hipStream_t st, bool ws_is_zero = false);
+                              hipStream_t st, bool ws_is_zero = false, const uint16_t* terms = nullptr);
+// (`terms`, where select_keys_streams_exact: the streaming launch leaves exact scores and no key is scored again)
+bool select_keys_streams_exact(const Dims& dm, int dtype);
 
 // --- attention (attn_mfma.hip for bf16, attn_f32.hip for float32) ---------------------------------
 // Cache rows attended: sparse (k_idx != nullptr): k_idx[b,kv,0..k_cnt[b,kv]); dense: 0..kv_lens[b].  The kernels cut

@@ -1,7 +1,8 @@
-// Provisional key scores for long caches (Alg. 1: S = Qbar K^T with Qbar rounded to bf16, max over the query axis,
-// 1/||k||), streamed at memory speed, with the histogram of the scores that the selection stage needs.
+// Key scores for long caches (Alg. 1: S = Qbar K^T, max over the query axis, 1/||k||), streamed at memory speed, with the
+// histogram of the scores that the selection stage needs.  Provisional scores (Qbar rounded to bf16) of any number of queries, exact
+// ones of up to 64 (StreamForm).
 //
-// Structure (one block per compute unit, a fixed grid; eight consumer waves and two producer waves):
+// Structure (one block per compute unit, a fixed grid; eight consumer waves, four with exact scores, and two producer waves):
 //   * Work is the flat list of 256-key steps over (sequence, KV head, step); every block takes an equal contiguous
 //     share, worked out from the device-side cache lengths, so a ragged batch leaves no compute unit idle.
 //   * K travels from global memory straight into LDS (global_load_lds, 16 bytes per lane, no staging registers), one
@@ -14,7 +15,8 @@
 //   * MFMA operand plan as in the exact kernel (queries M side, keys N side), except that lane (li, hf) takes chunk
 //     ks + KS*hf of its key in k-step ks (the contraction index may be permuted freely as long as the query operand
 //     uses the same permutation); with the swizzle above this keeps every ds_read_b128 conflict-free.
-//   * A wave owns one query block and QB of the step's eight 32-key blocks; the operand reads of the next key block
+//     (Exact scores keep the exact kernel's chunks, whose reads the swizzle spreads as well: 16 rows, 16 columns.)
+//   * A wave owns one query block and QB (2 QB) of the step's eight 32-key blocks; the operand reads of the next key block
 //     are issued before the products of the current one, and every key block runs as two MFMA chains.
 //   * A step's scores are finished one step later, under the next step's barrier; each finished score is counted in a
 //     per-block LDS histogram (4096 equal bins of [-1, 1], two 16-bit counters per word) that is flushed with integer
@@ -26,17 +28,24 @@
 
 namespace quoka {
 
-constexpr int kStWaves = 8;           // consumer waves: products, maxima, norms, scores
+// What a launch leaves as scores: provisional ones, from one bf16 term of Qbar; the exact ones of at most kPackRows queries, whose three
+// terms fit one operand; the exact ones of up to 64, all three terms, in the very float32 operations of score_bf16.
+enum StreamForm { kProvisional, kPacked, kExact };
 constexpr int kStProducers = 2;       // producer waves: loads only
-constexpr int kStThreads = 64 * (kStWaves + kStProducers);
-constexpr int kStConsumerThreads = 64 * kStWaves;
+constexpr int stream_consumers(StreamForm f) { return f == kExact ? 4 : 8; }
+constexpr int stream_threads(StreamForm f) { return 64 * (stream_consumers(f) + kStProducers); }
 constexpr int kStKeys = 256;          // keys per step
 constexpr int kStRing = 2;            // step buffers
 constexpr int kStGrid = 256;          // one block per compute unit of an MI355X
 constexpr int kStFlushSteps = 255;    // 255 * 256 keys < 2^16: a 16-bit bin counter cannot overflow between flushes
 
-template <int D, int QB>
+template <int D, int QB, StreamForm F>
 struct StreamCfg {
+  // Consumer waves: products, maxima, norms, scores.  kExact: one a SIMD, which leaves it the registers for three terms (96 at d 128)
+  // beside the operands of two key blocks.  With up to 64 queries its products take half of a step's 3 us, and the launch takes 5 % longer
+  // than the provisional one (8 x 8 heads of 4096 to 64077 positions 137 -> 144 us, 4.5 TB/s); with 128 they are what it waits for (whole
+  // calls 5 - 15 % slower than with provisional scores, so there is no such form).
+  static constexpr int W = stream_consumers(F), kThreads = stream_threads(F);
   static constexpr int KS = D / 16;                    // MFMA k-steps
   static constexpr int CPR = D / 8;                    // 16-byte chunks per key row
   static constexpr int ROW_B = D * 2;                  // bytes per key row (dense in LDS)
@@ -46,8 +55,8 @@ struct StreamCfg {
   static constexpr int NP = 16 / RPI;                  // distinct swizzle patterns of a wave-wide load (by load % NP)
   static constexpr int FSH = CPR == 16 ? 0 : 1;        // swizzle f(r) = (r >> FSH) % CPR: 16 consecutive rows hit
                                                        // 16 different 16-byte columns of the 256-byte bank line
-  static constexpr int UPW = QB;                       // 32-key blocks per wave and step (QB * 8 units on 8 waves)
-  static constexpr int KB_STEP = kStWaves / QB;        // this wave's key blocks: w / QB + i * KB_STEP
+  static constexpr int UPW = QB * 8 / W;               // 32-key blocks per wave and step (QB * 8 units on W waves)
+  static constexpr int KB_STEP = W / QB;               // this wave's key blocks: w / QB + i * KB_STEP
   static constexpr int NKS = KS / QB;                  // k-steps whose squares this wave adds up for the norms
   static constexpr size_t kLdsBytes =
       (size_t)kStRing * STEP_B + (kSelBins / 2) * 4 + 2 * QB * kStKeys * 4 /*maxima*/ + 2 * QB * kStKeys * 4 /*norms*/;
@@ -63,14 +72,14 @@ __device__ __forceinline__ void wait_vmcnt() {
   asm volatile("s_waitcnt vmcnt(%0)" ::"n"(N) : "memory");
 }
 
-// PACK (QB = 1): at most kPackRows queries with all three terms in the one operand, so the scores are the exact ones.
-template <int D, int QB, bool PACK>
-__global__ __launch_bounds__(kStThreads, 1) void score_stream(Dims dm, const float* __restrict__ qbar,
+template <int D, int QB, StreamForm F>
+__global__ __launch_bounds__(stream_threads(F), 1) void score_stream(Dims dm, const float* __restrict__ qbar,
                                                              const uint16_t* __restrict__ kc,
                                                              const int32_t* __restrict__ kv_lens,
                                                              float* __restrict__ scores, uint32_t* __restrict__ hist_ws,
-                                                             int n_keep) {
-  using Cfg = StreamCfg<D, QB>;
+                                                             int n_keep, const uint16_t* __restrict__ terms) {
+  using Cfg = StreamCfg<D, QB, F>;
+  constexpr int kStWaves = Cfg::W, kStThreads = Cfg::kThreads;
   constexpr int KS = Cfg::KS, CPR = Cfg::CPR, ROW_B = Cfg::ROW_B, STEP_B = Cfg::STEP_B, RPI = Cfg::RPI, IPP = Cfg::IPP,
                 NP = Cfg::NP, FSH = Cfg::FSH, UPW = Cfg::UPW, KB_STEP = Cfg::KB_STEP, NKS = Cfg::NKS;
   extern __shared__ __align__(1024) unsigned char smem[];
@@ -120,9 +129,10 @@ __global__ __launch_bounds__(kStThreads, 1) void score_stream(Dims dm, const flo
   // operand reads: byte offset of this lane's chunk of key row li of a 32-key block, per k-step
   uint32_t rd_off[KS];
   {
-    const int y = (KS * hf) ^ ((li >> FSH) % CPR);   // rows of later 32-key blocks have the same f (32 % 16 == 0)
+    // (kExact: the chunk that score_bf16 has in that place, so that sums add up in its order)
+    const int y = (F == kExact ? hf : KS * hf) ^ ((li >> FSH) % CPR);   // rows of later 32-key blocks have the same f (32 % 16 == 0)
 #pragma unroll
-    for (int ks = 0; ks < KS; ++ks) rd_off[ks] = (uint32_t)(li * ROW_B + ((ks ^ y) * 16));
+    for (int ks = 0; ks < KS; ++ks) rd_off[ks] = (uint32_t)(li * ROW_B + (((F == kExact ? 2 * ks : ks) ^ y) * 16));
   }
 
   while (cur < end) {
@@ -183,8 +193,10 @@ __global__ __launch_bounds__(kStThreads, 1) void score_stream(Dims dm, const flo
     // query operand of this wave: rows qb*32 .. +32 of the head's Qbar, rounded to bf16, chunk ks + KS*hf per k-step
     bf16x8 qa[KS];
     PackedTerms<D> qp;
-    if (PACK && !producer) qp.load(qbar + (size_t)head * n_keep * D, n_keep, li, hf);
-    if (!PACK && !producer) {
+    QueryTerms<D, true> qt;
+    if (F == kPacked && !producer) qp.load(qbar + (size_t)head * n_keep * D, n_keep, li, hf);
+    if (F == kExact && !producer) qt.load_terms(terms + (size_t)head * TermsLayout<D>::head_elems(n_keep), n_keep, qb, li, hf);
+    if (F == kProvisional && !producer) {
       float d2 = 0.f;
       const int r = min(qb * 32 + li, n_keep - 1);   // padding rows repeat a real query: the max is unchanged
       const float* qrow = qbar + ((size_t)head * n_keep + r) * D;
@@ -218,7 +230,7 @@ __global__ __launch_bounds__(kStThreads, 1) void score_stream(Dims dm, const flo
 #pragma unroll
           for (int q = 1; q < QB; ++q) {
             m = fmaxf(m, sm[q * kStKeys + tid]);
-            s2 += sq[q * kStKeys + tid];
+            if (F == kProvisional) s2 += sq[q * kStKeys + tid];
           }
           const float v = m / fmaxf(sqrtf(s2), kNormEps) + 0.0f;
           sc[key] = v;
@@ -242,6 +254,58 @@ __global__ __launch_bounds__(kStThreads, 1) void score_stream(Dims dm, const flo
       }
     };
 
+    // kExact: two key blocks at a time, all three terms into one accumulator each, the operands of a k-step read two k-steps ahead.
+    auto compute_exact = [&](int j) __attribute__((always_inline)) {
+      const unsigned char* tl = ring + (size_t)(j % kStRing) * STEP_B;
+      float* smax_j = smax + (j & 1) * QB * kStKeys;
+      float* ssq_j = ssq + (j & 1) * QB * kStKeys;
+#pragma unroll
+      for (int u = 0; u < UPW; u += 2) {
+        const unsigned char* kp = tl + (kb0 + u * KB_STEP) * 32 * ROW_B;
+        const bool norm[2] = {u % QB == qb, (u + 1) % QB == qb};   // the waves of a key block share out its norms (wave-uniform)
+        bf16x8 kop[3][2];
+        auto read = [&](int ks) __attribute__((always_inline)) {
+#pragma unroll
+          for (int i = 0; i < 2; ++i) kop[ks % 3][i] = *reinterpret_cast<const bf16x8*>(kp + i * KB_STEP * 32 * ROW_B + rd_off[ks]);
+        };
+        read(0);
+        read(1);
+        f32x16 c[2] = {{0}, {0}};
+        float sq[2][KS];
+#pragma unroll
+        for (int ks = 0; ks < KS; ++ks) {
+          if (ks + 2 < KS) read(ks + 2);
+          __builtin_amdgcn_sched_barrier(0);
+#pragma unroll
+          for (int i = 0; i < 2; ++i) c[i] = __builtin_amdgcn_mfma_f32_32x32x16_bf16(qt.lo[ks], kop[ks % 3][i], c[i], 0, 0, 0);
+#pragma unroll
+          for (int i = 0; i < 2; ++i) c[i] = __builtin_amdgcn_mfma_f32_32x32x16_bf16(qt.mid[ks], kop[ks % 3][i], c[i], 0, 0, 0);
+#pragma unroll
+          for (int i = 0; i < 2; ++i) c[i] = __builtin_amdgcn_mfma_f32_32x32x16_bf16(qt.hi[ks], kop[ks % 3][i], c[i], 0, 0, 0);
+#pragma unroll
+          for (int i = 0; i < 2; ++i)
+            if (QB == 1 || norm[i]) sq[i][ks] = sumsq_bf16x8(__builtin_bit_cast(u32x4, kop[ks % 3][i]));
+        }
+#pragma unroll
+        for (int i = 0; i < 2; ++i) {
+          float m = -INFINITY;
+#pragma unroll
+          for (int v = 0; v < 16; ++v) m = fmaxf(m, c[i][v]);
+          m = fmaxf(m, other_half(m));
+          const int k = (kb0 + (u + i) * KB_STEP) * 32 + li;
+          if (hf == 0) smax_j[qb * kStKeys + k] = m;
+          if (QB == 1 || norm[i]) {   // added up as row_sumsq does: this half wave's chunks pair by pair, then the other's
+#pragma unroll
+            for (int o = KS / 2; o > 0; o /= 2)
+#pragma unroll
+              for (int ks = 0; ks < o; ++ks) sq[i][ks] += sq[i][ks + o];
+            const float ss = sq[i][0] + other_half(sq[i][0]);
+            if (hf == 0) ssq_j[k] = ss;
+          }
+        }
+      }
+    };
+
     auto compute = [&](int j) __attribute__((always_inline)) {
       const unsigned char* tl = ring + (size_t)(j % kStRing) * STEP_B;
       float* smax_g = smax + (j & 1) * QB * kStKeys + qb * kStKeys;
@@ -258,7 +322,7 @@ __global__ __launch_bounds__(kStThreads, 1) void score_stream(Dims dm, const flo
         // the next key block's operands are requested before this one's products are issued
         if (u + 1 < UPW) read_ops(u + 1, kop[(u + 1) & 1]);
         __builtin_amdgcn_sched_barrier(0);
-        if constexpr (PACK) {
+        if constexpr (F == kPacked) {
           float ss;
           const float m = packed_products<D>(kop[u & 1], qp, &ss);
           if (hf == 0) {
@@ -312,7 +376,8 @@ __global__ __launch_bounds__(kStThreads, 1) void score_stream(Dims dm, const flo
         if (j + 1 < n) issue_step(j + 1);
         wait_vmcnt<0>();
       } else {
-        compute(j);
+        if constexpr (F == kExact) compute_exact(j);
+        else compute(j);
         if (j > 0) finish(j - 1);
       }
       if (hist_ws != nullptr && ++since_flush >= kStFlushSteps) {   // block-uniform
@@ -329,37 +394,40 @@ __global__ __launch_bounds__(kStThreads, 1) void score_stream(Dims dm, const flo
   }
 }
 
-template <int D, int QB, bool PACK = false>
-static hipError_t launch_stream_q(const Dims& dm, const float* qbar, const void* kc, const int32_t* kv_lens,
+template <int D, int QB, StreamForm F>
+static hipError_t launch_stream_q(const Dims& dm, const float* qbar, const uint16_t* terms, const void* kc, const int32_t* kv_lens,
                                   float* scores, uint32_t* hist_ws, int n_keep, hipStream_t st) {
-  using Cfg = StreamCfg<D, QB>;
+  using Cfg = StreamCfg<D, QB, F>;
   static std::atomic<uint64_t> lds_done{0};
   const hipError_t e =
-      ensure_dynamic_lds(reinterpret_cast<const void*>(&score_stream<D, QB, PACK>), Cfg::kLdsBytes, lds_done);
+      ensure_dynamic_lds(reinterpret_cast<const void*>(&score_stream<D, QB, F>), Cfg::kLdsBytes, lds_done);
   if (e != hipSuccess) return e;
-  hipLaunchKernelGGL((score_stream<D, QB, PACK>), dim3(kStGrid), dim3(kStThreads), Cfg::kLdsBytes, st, dm, qbar,
-                     static_cast<const uint16_t*>(kc), kv_lens, scores, hist_ws, n_keep);
+  hipLaunchKernelGGL((score_stream<D, QB, F>), dim3(kStGrid), dim3(Cfg::kThreads), Cfg::kLdsBytes, st, dm, qbar,
+                     static_cast<const uint16_t*>(kc), kv_lens, scores, hist_ws, n_keep, terms);
   return hipGetLastError();
 }
 
 template <int D>
-static hipError_t launch_stream_d(const Dims& dm, const float* qbar, const void* kc, const int32_t* kv_lens,
+static hipError_t launch_stream_d(const Dims& dm, const float* qbar, const uint16_t* terms, const void* kc, const int32_t* kv_lens,
                                   float* scores, uint32_t* hist_ws, int n_keep, hipStream_t st) {
   const int qblocks = (n_keep + 31) / 32;
-  if (score_packs(dm)) return launch_stream_q<D, 1, true>(dm, qbar, kc, kv_lens, scores, hist_ws, n_keep, st);
-  if (qblocks <= 1) return launch_stream_q<D, 1>(dm, qbar, kc, kv_lens, scores, hist_ws, n_keep, st);
-  if (qblocks == 2) return launch_stream_q<D, 2>(dm, qbar, kc, kv_lens, scores, hist_ws, n_keep, st);
-  return launch_stream_q<D, 4>(dm, qbar, kc, kv_lens, scores, hist_ws, n_keep, st);
+  if (score_packs(dm)) return launch_stream_q<D, 1, kPacked>(dm, qbar, nullptr, kc, kv_lens, scores, hist_ws, n_keep, st);
+  if (terms != nullptr)
+    return qblocks <= 1 ? launch_stream_q<D, 1, kExact>(dm, qbar, terms, kc, kv_lens, scores, hist_ws, n_keep, st)
+                        : launch_stream_q<D, 2, kExact>(dm, qbar, terms, kc, kv_lens, scores, hist_ws, n_keep, st);
+  if (qblocks <= 1) return launch_stream_q<D, 1, kProvisional>(dm, qbar, nullptr, kc, kv_lens, scores, hist_ws, n_keep, st);
+  if (qblocks == 2) return launch_stream_q<D, 2, kProvisional>(dm, qbar, nullptr, kc, kv_lens, scores, hist_ws, n_keep, st);
+  return launch_stream_q<D, 4, kProvisional>(dm, qbar, nullptr, kc, kv_lens, scores, hist_ws, n_keep, st);
 }
 
-// Provisional (one bf16 term) cosine / max scores of every cached key; with `hist_ws` (the zeroed head of the
-// selection workspace) also their per-head histogram.
-hipError_t launch_score_stream(const Dims& dm, const float* qbar, const void* k_cache, const int32_t* kv_lens,
+// Cosine / max scores of every cached key, provisional (one bf16 term) or exact (score_packs, or from `terms`: up to 64 queries); with
+// `hist_ws` (the zeroed head of the selection workspace) also their per-head histogram.
+hipError_t launch_score_stream(const Dims& dm, const float* qbar, const uint16_t* terms, const void* k_cache, const int32_t* kv_lens,
                                float* scores, uint32_t* hist_ws, hipStream_t st) {
   if (dm.T_max <= 0) return hipSuccess;
   const int n_keep = dm.n_ret < dm.C ? dm.n_ret : dm.C;
-  return dm.d == 64 ? launch_stream_d<64>(dm, qbar, k_cache, kv_lens, scores, hist_ws, n_keep, st)
-                    : launch_stream_d<128>(dm, qbar, k_cache, kv_lens, scores, hist_ws, n_keep, st);
+  return dm.d == 64 ? launch_stream_d<64>(dm, qbar, terms, k_cache, kv_lens, scores, hist_ws, n_keep, st)
+                    : launch_stream_d<128>(dm, qbar, terms, k_cache, kv_lens, scores, hist_ws, n_keep, st);
 }
 
 }  // namespace quoka

@@ -16,7 +16,8 @@
 // produce it; the `scores` array ends up holding exact values inside the band and provisional values elsewhere.
 //
 // Up to a size the fused call takes a shorter way to the same lists: exact scores of every key with their histogram
-// (score_bf16), then sel_classify and sel_finish, see select_keys_exact_pays.
+// (score_bf16; for large caches and up to 64 queries score_stream with all three terms), then sel_classify and sel_finish, see
+// select_keys_exact_pays and select_keys_streams_exact.
 //
 // Launch chain (no block ever waits for another block of its launch): provisional scoring with the histogram
 // (score_stream.hip), band classification + exact re-scoring per 2048-key tile, one block per head that selects
@@ -587,7 +588,7 @@ __global__ __launch_bounds__(kSelThreads) void sel_emit(Dims dm, float* __restri
 }
 
 // ---------------------------------------------------------------------------------------------
-// Exact scores (score_packs, select_keys_exact_pays): nothing is scored again, the candidates are the keys of the cut's own bin.  A few
+// Exact scores (score_packs, select_keys_exact_pays, select_keys_streams_exact): nothing is scored again, the candidates are the keys of the cut's own bin.  A few
 // dozen of ordinary scores in 4096 bins; in the exact scorer's 2048, of one KV head of 16 whose best scores lie close together,
 // beyond 1024, which are then selected from memory (131072 independent keys, 64 queries, budget 12 % 61 us a call, two-pass 109).
 // Launch chain: scoring with the histogram, one count per tile, emission; every emitting block finds the cut among the
@@ -767,11 +768,22 @@ bool select_keys_two_pass_applies(const Dims& dm, int dtype) {
 // 8 x 8 of 36611, d 64 138 -> 156.  260 sizes measured; the lines lie where the two sides meet.  Packed calls score exactly either way and the
 // streaming launch is the faster for them; a prompt's chunks share one cache, 12 prompts 0.96 - 1.15 of the time, no line to draw.
 // (At these sizes a scoring block has far fewer than the 65536 keys that its 16-bit counters hold.)
-constexpr long long kExactBytes = 300'000'000, kExactBytesWide = 80'000'000;
+constexpr long long kExactBytes = 250'000'000, kExactBytesWide = 80'000'000;
 bool select_keys_exact_pays(const Dims& dm, int dtype) {
   if (!select_keys_two_pass_applies(dm, dtype) || dm.T_max > kPackMaxKeys || score_packs(dm)) return false;
   const int n_keep = dm.n_ret < dm.C ? dm.n_ret : dm.C;
   return (long long)dm.b * dm.n_kv * dm.T_cap * dm.d * 2 <= (n_keep <= 64 ? kExactBytes : kExactBytesWide);
+}
+
+// Beyond those sizes exact scores come from the streaming launch, as long as its products hide behind the keys' way from memory: up
+// to 64 queries.  Whole calls with a small attention part, us: against the two-pass form 8 x 8 heads of 4096 to 64077 positions, 64
+// queries 321 -> 310, 3 x 8 of 53300 144 -> 133, 13 x 4 of 7500 to 60000 187 -> 177, d 64 13 x 8 of 5000 to 40000 146 -> 131; against the
+// exact scores of the tiled launch 8 of 131072, 268 MB 115.6 -> 111.8, 32 queries 108.7 -> 104.4, 2 x 8 of 130000, d 64, 266 MB 132.5
+// -> 127.0, but 8 of 92109, 189 MB 97.7 -> 98.3, 8 of 130000, d 64, 133 MB 83.2 -> 86.2, 1 of 72294 48.7 -> 53.1.
+bool select_keys_streams_exact(const Dims& dm, int dtype) {
+  if (!select_keys_two_pass_applies(dm, dtype) || dm.T_max > kPackMaxKeys || score_packs(dm)) return false;
+  const int n_keep = dm.n_ret < dm.C ? dm.n_ret : dm.C;
+  return n_keep <= 64 && (long long)dm.b * dm.n_kv * dm.T_cap * dm.d * 2 > kExactBytes;
 }
 
 hipError_t launch_select_keys_exact(const Dims& dm, const float* qbar, const void* k_cache, const int32_t* kv_lens,
@@ -821,14 +833,14 @@ static void launch_rescore(const Dims& dm, const float* qbar, const void* kc, co
 
 hipError_t launch_select_keys(const Dims& dm, const float* qbar, const void* k_cache, const int32_t* kv_lens,
                               const int32_t* budgets, float* scores, int32_t* k_idx, int32_t* k_cnt, uint32_t* ws,
-                              hipStream_t st, bool ws_is_zero) {
+                              hipStream_t st, bool ws_is_zero, const uint16_t* terms) {
   const int n_keep = dm.n_ret < dm.C ? dm.n_ret : dm.C;
   if (!ws_is_zero) hipLaunchKernelGGL(sel_zero, dim3(64), dim3(256), 0, st, ws, select_keys_zero_words(dm, false));
   // provisional scores and their histogram in one streaming launch
-  hipError_t e = launch_score_stream(dm, qbar, k_cache, kv_lens, scores, ws, st);
+  hipError_t e = launch_score_stream(dm, qbar, terms, k_cache, kv_lens, scores, ws, st);
   if (e != hipSuccess) return e;
   const dim3 grid(sel_tiles(dm.T_cap), dm.n_kv, dm.b);
-  if (score_packs(dm)) {
+  if (score_packs(dm) || terms != nullptr) {
     hipLaunchKernelGGL((sel_classify<kSelBins>), grid, dim3(kSelThreads), 0, st, dm, scores, kv_lens, budgets, ws);
     hipLaunchKernelGGL((sel_finish<kSelBins>), grid, dim3(kSelThreads), 0, st, dm, scores, kv_lens, budgets, ws, k_idx, k_cnt);
     return hipGetLastError();

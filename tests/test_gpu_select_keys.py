@@ -314,6 +314,42 @@ def test_chunk_attn_of_caches_with_room_to_spare(n_kv, d, T_max, lens):
         assert torch.equal(buf.scores[i, :, :T], sc[i, :, :T]) and torch.equal(buf.k_idx[i, :, :n], idx[i, :, :n])
 
 
+# Beyond 250 MB of keys the streaming launch scores exactly (up to 64 queries): the scores and lists of the two separate calls bit for bit;
+# one query block and two, not full and full; steps of 256 keys just short of, at and past full, empty sequences, more than a wave has lanes
+@pytest.mark.parametrize("kind", ["normal", "pairs", "equal"])
+@pytest.mark.parametrize("n_kv,d,T_max,lens,n_retain", [
+    (4, 128, 33000, [33000, 0, 1, 255, 256, 257, 5000, 32768], 9),
+    (4, 128, 33000, [2, 511, 513, 0, 33000, 33000, 777, 12345], 64),
+    (8, 64, 33000, [33000, 0, 1, 255, 256, 257, 5000, 32768], 33),
+    (1, 128, 131072, [131072, 100001, 3, 65536, 0, 131071, 5, 90000], 32),
+    (1, 64, 32800, [32800 - 499 * (i % 65) for i in range(66)], 40),
+], ids=lambda v: f"{len(v)}x{v[0]}" if isinstance(v, list) else str(v))
+def test_chunk_attn_streams_exact_scores(kind, n_kv, d, T_max, lens, n_retain):
+    pk = _pk()
+    b, C = len(lens), 70
+    assert b * n_kv * T_max * d * 2 > 250_000_000
+    g = torch.Generator(device="cuda").manual_seed(53)
+    q, k, v, kc, vc = (torch.randn(b, n, t, d, device="cuda", generator=g, dtype=torch.float32).bfloat16()
+                       for n, t in ((2 * n_kv, C), (n_kv, T_max), (n_kv, T_max), (n_kv, C), (n_kv, C)))
+    if kind == "equal":
+        k[:] = k[:, :, :1].clone()
+    elif kind == "pairs":
+        n = T_max // 2 * 2
+        k[:, :, 1:n:2] = k[:, :, 0:n:2]
+    buf = pk.ChunkBuffers(q, k, v, kc, vc, lens, [t // 9 + 1 for t in lens], n_retain, max_budget=T_max // 8)
+    sc, idx, cnt = _staged(buf)
+    buf.scores.fill_(float("nan"))
+    buf.k_idx.fill_(-1)
+    buf.k_cnt.fill_(-1)
+    buf.workspace.fill_(0x5A)
+    buf.chunk_attn()
+    torch.cuda.synchronize()
+    assert torch.equal(buf.k_cnt, cnt)
+    for i, T in enumerate(lens):
+        n = int(cnt[i, 0])
+        assert torch.equal(buf.scores[i, :, :T], sc[i, :, :T]) and torch.equal(buf.k_idx[i, :, :n], idx[i, :, :n])
+
+
 # More candidates than a block holds in registers, listed in memory and fetched in runs of 2048 (8192 where one block selects for a
 # head): lists just short of, at and past whole runs; all scores equal, or eight values of which the cut's is an eighth
 @pytest.mark.parametrize("values", [1, 8])
