@@ -796,54 +796,43 @@ static int key_splits_limit(const Dims& dm, bool sparse, int keys_per_tile) {
   return (int)(tiles < kMaxKeySplits ? tiles : kMaxKeySplits);
 }
 
-struct AttnPlan {
-  bool split_tile;
-  int n_splits;
-};
-
-// Whole key lists: eight row blocks per block, or four.
+// Whole key lists of more than 1024 row blocks: eight row blocks per block, or four.
 // A batch: eight where that gives every compute unit a block.  (The lengths may differ, which the host cannot know, and then
-// smaller blocks fill up the second round where eight row blocks alone would be one: 2 sequences of 2153 tokens, 14/2
-// heads, 5546 and 2547 keys: 240 blocks of eight 255 us a call, 476 of four 235.)
-// One sequence: blocks of four take two rounds where eight take one, and each costs more per key, but in the second round
-// the blocks with the shortest causal ranges follow each other, so up to 128 groups of eight four is the faster, from
-// there on it depends on how much of the list is the chunk's own.  The bound is a fit of the two times' difference, in us,
-// to 172 measured pairs (groups 130 - 250, chunks 1056 - 4096, 0 - 4096 keys; rms 1.5 %), less 0.5 - 1 us.  Attention, eight
-// against four, d 128: 32/8 heads, 1312 tokens over 983 keys 62 / 72 us, over 3932 134 / 164; 12/4 heads, 3000 tokens over
-// 983 92 / 96, over none 66.9 / 65.4; d 64: 12/4 heads, 2752 tokens over none 43 / 37, over 2048 78.4 / 76.8.
-// Above 256 groups blocks of four take three rounds where those of eight take two, 32/8 heads, d 128, 2400 tokens over 983
-// keys, 304 groups 140 / 123 us; 3072 tokens, 384 groups 164 / 155.  From two full rounds on the longest ranges come first
-// and even the rounds out, whatever the rest: 4096 tokens, 512 groups 200 / 232; 6200, 776 groups 412 / 473.
-static bool eight_row_blocks(const Dims& dm, bool sparse, long long groups) {
-  if (dm.b > 1 || groups == kComputeUnits) return groups >= kComputeUnits;
-  if (groups > kComputeUnits) return 2 * groups > 3 * kComputeUnits;
-  if (groups <= kComputeUnits / 2) return false;
-  const float c = (float)attended_cap(dm, sparse) / kSub, r = (float)dm.C / kSub, n = (float)groups;
-  return dm.d == 128 ? 6.2f + 0.36f * c + r * (0.147f - 47.4f / n) > 0.f : 4.8f + 0.114f * c + r * (0.093f - 41.1f / n) > 0.f;
+// smaller blocks fill up the second round where eight row blocks alone would be one.)
+// One sequence: up to 256 groups of eight (one round) eight is the faster at d 128 in all 176 measured calls, at d 64 but for short
+// lists of the chunk's own keys (0.15 % on the mean of 100, 4 % at most): 32/8 heads, d 128, 1973 tokens over 1221 keys, 248 groups 79.6 us,
+// with four 89.1; d 64, 12/4 heads, 3305 tokens over 75 keys 47.0, 45.1.  Above that blocks of four take three rounds where those of eight
+// take two, up to 384 groups (d 64: 416) in less time, 0.87 of it at 257 - 320 groups, 0.91 at 321 - 384; from there on those of eight, whose
+// longest ranges come first, even the rounds out (385 - 448 groups 0.97, 449 - 512 0.94 of the time of four).
+static bool eight_row_blocks(const Dims& dm, long long groups) {
+  if (dm.b > 1 || groups <= kComputeUnits) return dm.b == 1 || groups >= kComputeUnits;
+  return groups > (dm.d == 128 ? 384 : 416);
 }
 
 // Few row blocks leave compute units idle whatever the tile mode; their key lists are split over blocks instead.
 // Measured (kernel and merge, unsplit -> split): 4 KV heads x 3 sequences, d 64, 333 tokens over 4999 keys (2 splits)
 // 60 -> 38 us; one KV head of 16 q-heads x 8 sequences, d 64, 69 tokens over 13477 keys (5 splits) 138 -> 65 us.
-// The cheapest variant by a model of the call in microseconds: a fixed part, the steps of the longest key list's share times
-// the rounds of 256 resident blocks, and for a split list 6 for each further round, 0.03 a split and the partials' bytes.  The numbers
-// are fits to 2400 measured calls (220 shapes of 5 - 1500 tokens over 64 - 16000 keys; rms 3 - 5 %); a split has to promise 0.6 us more
-// than it costs, because the model takes the shortest whole lists for longer than they are (2 KV heads of 7, d 64, 5 tokens over
-// 129 keys 8.2 us whole, 10.5 in 4 splits).  Long lists of batches, bound by memory, are where further rounds cost time of their own (13 x 8
-// KV heads of 2, d 128, 17 tokens over 12000 keys: 2 splits, one round 117 us, 7 splits, three rounds 134).  The plans are 0.7 % off the
-// best of the measured ones on the mean of 760 other shapes, up to 60000 keys, and up to 6 % slower than another plan for single ones.
+// The cheapest variant by a model of the call in microseconds: a fixed part, the steps of the longest key list's share times the rounds of
+// 256 resident blocks, a part for each further round, and for a split list one for each split and for the partials' bytes.  The numbers
+// are fits to half of 3800 measured calls (33 - 4096 tokens over 64 - 20000 keys, at most 1024 row blocks; rms 3 - 8 %); a split has to
+// promise 0.6 us more than it costs.  On the other half the plans are 0.5 % off the best of the measured ones on the mean (the fits
+// of the kernel before: 1.1 %), 10 % (d 64 20 %) for single ones.  Whole lists take blocks of eight where ragged row blocks make more
+// than 256 blocks of four: 13 x 4 heads of 3, d 128, 187 tokens over 454 keys 34.3 -> 24.8 us, 171 over 4688 130 -> 105.
+struct AttnPlan {
+  bool split_tile;
+  int n_splits;
+};
+
 static AttnPlan attn_plan(const Dims& dm, bool sparse) {
   const long long nrb = (long long)dm.g * ((dm.C + 31) / 32), heads = (long long)dm.n_kv * dm.b;
-  if (heads * nrb * 2 > kMaxRecords) return AttnPlan{!eight_row_blocks(dm, sparse, heads * ((nrb + 7) / 8)), 1};
-  // (From here on there are at most 1024 row blocks, and a whole list takes blocks of four: 256 of them at most, one round, where the
-  // row blocks of a KV head are a multiple of four, more where they are not: 312 for 13 x 8/8 heads of 280 tokens, which blocks of
-  // eight would take in one.)
+  if (heads * nrb * 2 > kMaxRecords) return AttnPlan{!eight_row_blocks(dm, heads * ((nrb + 7) / 8)), 1};
   struct Fit {
-    float fixed, step, per_mb;   // a step is 8 row blocks x 64 keys or 4 x 128
+    float fixed, step, round, per_mb, per_split;   // a step is 8 row blocks x 64 keys or 4 x 128
   };
-  constexpr Fit kWhole[2] = {{6.3f, 1.17f, 0.f}, {7.8f, 1.85f, 0.f}};   // d 64, d 128
-  constexpr Fit kSplit[2][2] = {{{8.1f, 1.10f, 0.58f}, {8.3f, 1.30f, 0.62f}},    // d 64: eight row blocks, four
-                                {{9.4f, 1.64f, 0.47f}, {9.8f, 1.95f, 0.56f}}};   // d 128
+  constexpr Fit kWhole[2][2] = {{{6.9f, 0.86f, 3.f, 0.f, 0.f}, {6.2f, 1.03f, 3.9f, 0.f, 0.f}},     // d 64: eight row blocks, four
+                                {{8.1f, 1.16f, 3.f, 0.f, 0.f}, {8.4f, 1.33f, 9.8f, 0.f, 0.f}}};    // d 128
+  constexpr Fit kSplit[2][2] = {{{8.5f, 0.90f, 0.8f, 0.52f, 0.03f}, {8.8f, 1.05f, 1.7f, 0.52f, 0.045f}},
+                                {{10.9f, 1.21f, 0.7f, 0.42f, 0.01f}, {11.2f, 1.35f, 1.7f, 0.51f, 0.01f}}};
   const int wide = dm.d == 128 ? 1 : 0;
   AttnPlan best{true, 1};
   float best_us = INFINITY;
@@ -852,15 +841,12 @@ static AttnPlan attn_plan(const Dims& dm, bool sparse) {
     const long long blocks = heads * ((nrb + per_block - 1) / per_block);
     const int limit = key_splits_limit(dm, sparse, kt);
     const long long tiles = ((long long)attended_cap(dm, sparse) + kt - 1) / kt + (dm.C + kt - 1) / kt;
-    if (mode == 1) {
-      const long long rounds = (blocks + kComputeUnits - 1) / kComputeUnits;
-      best_us = kWhole[wide].fixed + kWhole[wide].step * (float)(rounds * tiles);
-    }
-    for (int n = 2; n <= limit && heads * nrb * n <= kMaxRecords; ++n) {
-      const Fit& f = kSplit[wide][mode];
+    for (int n = 1; n == 1 || (n <= limit && heads * nrb * n <= kMaxRecords); ++n) {
+      const Fit& f = n == 1 ? kWhole[wide][mode] : kSplit[wide][mode];
       const long long rounds = (blocks * n + kComputeUnits - 1) / kComputeUnits, steps = (tiles + n - 1) / n;
       const float mb = (float)(heads * nrb * n) * (float)(dm.d + 2) * 128e-6f;
-      const float us = f.fixed + 0.6f + f.step * (float)(rounds * steps) + 6.f * (float)(rounds - 1) + f.per_mb * mb + 0.03f * (float)n;
+      const float us = f.fixed + (n > 1 ? 0.6f : 0.f) + f.step * (float)(rounds * steps) + f.round * (float)(rounds - 1) + f.per_mb * mb +
+                       f.per_split * (float)n;
       if (us < best_us) {
         best = AttnPlan{mode == 1, n};
         best_us = us;
