@@ -117,7 +117,7 @@ struct AttnCfg {
 // XS (QUOKA_ATTN_SCALE_F32): the softmax scale is applied to the float32 products, one fused multiply-add per score
 // together with the subtraction of the reference point.  Otherwise the factor log2(e)/sqrt(d) is folded into the bf16 Q
 // operand once and the accumulator of K Q^T starts from minus the reference point, so that the matrix core hands back
-// what the exponential takes and no vector instruction is spent on either -- 4-9 % faster, at the price of rounding Q a
+// what the exponential takes and no vector instruction is spent on either -- 2-9 % faster, at the price of rounding Q a
 // second time: an error of the logits of relative size 2^-9, which shows in the output once the logits are several
 // times those of unit-variance inputs (0.03 absolute at four times, 0.06 at eight).
 // KSPLIT: the key list is shared by a.n_splits blocks, each of which writes a partial result.  (A template parameter: as

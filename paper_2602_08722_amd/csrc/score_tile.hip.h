@@ -1,7 +1,8 @@
 // Tile arithmetic of the key scoring (Alg. 1: S = Qbar K^T, S-hat = max over the query axis; Sec. 3.2-3.3), shared
 // by the streaming scoring kernel and by the exact re-scoring of the keys near the provisional cut: both must give
 // the same float32 bits for the same key, so the split of Qbar, the order of the MFMA terms, the squared norm and
-// the final division live here once.
+// the final division live here once.  (The streaming kernel's exact form follows the orders of tile_products and row_sumsq on its own
+// layout.)
 //
 // Operand plan (v_mfma_f32_32x32x16_bf16; a lane is (li = lane % 32, hf = lane / 32)): queries are the M side, keys
 // the N side.  Lane (li, hf) holds, for k-step ks, dims ks*16 + 8*hf .. +8 of query row li (A) and of key li (B);
