@@ -26,6 +26,9 @@ struct Raw8;   // eight consecutive elements as loaded
 template <>
 struct Raw8<uint16_t> {
   u32x4 r;
+  // What was formed from the row before is formed again, not kept beside it (sq_head_select, d 128, 8 rows a thread: 94 -> 62 registers,
+  // 16 rows: 97 instead of 128 and spills).
+  __device__ __forceinline__ void pin() { asm volatile("" : "+v"(r)); }
   __device__ __forceinline__ void load(const uint16_t* p) { r = *reinterpret_cast<const u32x4*>(p); }
   __device__ __forceinline__ void widen(float (&v)[8]) const {
 #pragma unroll
@@ -351,7 +354,7 @@ __global__ __launch_bounds__(kSelThreads) void sq_head_select(Dims dm, const T* 
   __shared__ RankLds L;
   __shared__ __align__(16) float mean[D];
   __shared__ float mnorm;
-  __shared__ float buf[RPB * D];             // column partials, then the cosines (RPB * NR <= RPB * D of them)
+  __shared__ float buf[RPB * D];             // column partials, then products and squared norms (2 RPB NR <= RPB D)
   __shared__ float tsum[NT * D];
   const int h = blockIdx.x, b = blockIdx.y;
   const int C = dm.chunk(b);
@@ -423,10 +426,12 @@ __global__ __launch_bounds__(kSelThreads) void sq_head_select(Dims dm, const T* 
   float m[8];
 #pragma unroll
   for (int e = 0; e < 8; ++e) m[e] = mean[cg * 8 + e];
-  // ---- cosines of the rows held in registers (the norm of the mean is needed last) ----
-  float dots[NR], qn[NR];
+  // ---- cosines of the rows held in registers.  The norm of the mean is needed last: products and squared norms wait for it in LDS, and
+  // the root and the division are then taken once a token, not by every lane of its row.  (With the registers that this and pin()
+  // free: 32 heads of 423 tokens 12.0 -> 10.9 us, 256 of 512 17.1 -> 15.7, float32 32 of 512 13.8 -> 11.7.) ----
 #pragma unroll
   for (int u = 0; u < NR; ++u) {
+    if constexpr (sizeof(T) == 2) rows[u].pin();
     float v[8];
     rows[u].widen(v);
     float dot = 0.f, qq = 0.f;
@@ -442,23 +447,22 @@ __global__ __launch_bounds__(kSelThreads) void sq_head_select(Dims dm, const T* 
       dot = group_sum<CG>(dot);
       qq = group_sum<CG>(qq);
     }
-    dots[u] = dot;
-    qn[u] = fmaxf(sqrtf(qq), kNormEps);
-  }
-  __syncthreads();
-  const float mn = mnorm;
-#pragma unroll
-  for (int u = 0; u < NR; ++u) {
-    if (cg == 0 && token(u) < C) buf[token(u)] = dots[u] / (qn[u] * mn) + 0.0f;
+    if (cg == 0 && token(u) < C) {
+      buf[token(u)] = dot;
+      buf[RPB * NR + token(u)] = qq;
+    }
   }
   __syncthreads();
   const int lo = tid * IPT;
+  const float mn = mnorm;
   uint32_t key[IPT];
   uint32_t valid = 0u;
 #pragma unroll
   for (int j = 0; j < IPT; ++j) {
     const bool in = lo + j < C;
-    key[j] = in ? okey(buf[in ? lo + j : 0]) : 0xFFFFFFFFu;
+    const int t = in ? lo + j : 0;
+    const float qn = fmaxf(sqrtf(buf[RPB * NR + t]), kNormEps);
+    key[j] = in ? okey(buf[t] / (qn * mn) + 0.0f) : 0xFFFFFFFFu;
     valid |= (in ? 1u : 0u) << j;
   }
   select_lowest_ranked<IPT>(key, valid, lo, n_keep, L, q_idx + (size_t)(b * dm.n_q + h) * n_keep);
@@ -509,8 +513,8 @@ __global__ __launch_bounds__(64) void sq_qbar(Dims dm, const T* __restrict__ q, 
 // ---------------------------------------------------------------------------------------------
 // One block per head for everything where that is the faster, one launch instead of three.  Short chunks, whatever the heads, in
 // the sums of the tiled kernels: up to kHeadTokens tokens (query stage, bf16, d 128: 12 heads of 128 tokens 15.2 -> 10.2 us, 32 of
-// 423 15.8 -> 13.0; float32 8 of 464 15.3 -> 13.8).  From there on one compute unit per head pulls too little (32 heads of 1024
-// tokens 20.7 against 16.5 us, d 64 even), so single sequences spread the two reads of Q over the whole chip.
+// 423 15.8 -> 10.9; float32 32 of 512 11.7).  From there on one compute unit per head pulls too little (32 heads of 1024 tokens
+// 15.5 against 14.7 us), so calls of few heads spread the two reads of Q over the whole chip.
 // Batches, where the heads alone give half the compute units a block and the block can hold the head (8 rows of 8 elements per
 // thread): 256 heads of 512 tokens 14.8 us against 24 us.  Their sums differ in the last bits, and cosines that differ in theirs
 // only can change ranks, so that line stays where it is.  (It goes by the batch of the whole call and the chunk's own length; how
@@ -522,6 +526,15 @@ bool select_queries_one_block(const Dims& dm) {
   const int sequences = dm.prompt_chunks ? dm.ls : dm.b;   // (ls: the batch of the whole call)
   return dm.C <= rows_at_once * kRowsPerThread && sequences * dm.n_q >= 128;
 }
+
+// bf16 calls of 64 heads or more (sequences, and chunks of a prompt that share a launch, count alike: the sums are the tiled kernels')
+// up to kManyTokens tokens: Q is read once instead of twice, and that pays as soon as a good part of the compute units has a head.
+// Query stage, d 128: 64 heads of 1024 tokens 16.9 -> 16.0 us, 128 23.0 -> 18.3, 256 36.1 -> 24.3, 288 (two rounds) 40.8 -> 37.5, 512
+// 63.4 -> 47.8; d 64, 300 heads 27.9 -> 22.7.  Whole calls over 8192 keys: 8 x 32 heads 263 -> 251 us, 4 x 32 145 -> 140, 64 84.9 -> 84.1;
+// with 48 heads even, with 32, 16 and 8 1 to 3 % slower.  (Float32 heads of d 64 gain 2 to 3 % of the stage, of d 128 do not fit;
+// 2048 tokens of d 64 gain where the heads nearly fill the last round, 256 40 -> 31 us, and lose elsewhere: neither is built.)
+constexpr int kManyTokens = 1024;
+static bool select_queries_many_heads(const Dims& dm) { return dm.C <= kManyTokens && dm.n_q * dm.b >= 64; }
 
 template <typename T, int D, int RULE>
 static void launch_qbar(const Dims& dm, const T* q, int32_t* q_idx, float* qbar, int n_keep, hipStream_t st, uint32_t* zero,
@@ -559,6 +572,9 @@ static hipError_t launch_typed(const Dims& dm, const void* q, int32_t* q_idx, fl
     } else if (dm.C <= kHeadTokens) {
       hipLaunchKernelGGL((sq_head_select<T, D, kHeadTokens * D / 8 / kSelThreads, true>), sgrid, sblock, 0, st, dm, qp, q_idx,
                          n_keep);
+    } else if (sizeof(T) == 2 && select_queries_many_heads(dm)) {
+      hipLaunchKernelGGL((sq_head_select<uint16_t, D, kManyTokens * D / 8 / kSelThreads, true>), sgrid, sblock, 0, st, dm,
+                         static_cast<const uint16_t*>(q), q_idx, n_keep);
     } else {
       const int n_tiles = (dm.C + kSqTile - 1) / kSqTile;
       dim3 grid(n_tiles, dm.n_q, dm.b);

@@ -219,6 +219,32 @@ def test_short_last_chunk_selects_alike_in_one_block_and_in_tiles(d, chunk, tail
         assert torch.equal(a, b)
 
 
+# (what is compared is what the last chunk leaves; one of up to n_retain = 64 tokens runs by itself, keeps them all and writes no more
+# entries than it has, so the rest of the lists is then another chunk's: tails begin at 65)
+@pytest.mark.parametrize("d,chunk,tail", [(128, 1024, 1024), (128, 513, 65), (128, 1000, 577), (64, 1024, 1023), (64, 640, 66), (128, 1025, 700)])
+def test_queries_of_many_heads_are_selected_as_in_tiles(d, chunk, tail):
+    """Chunks that share a launch give it enough heads for one block per head and up to 1024 tokens; one chunk at a time takes the tiled
+    launches.  Query rows that lie apart, cosines so close together that the last bits of the mean decide ranks: the same bits."""
+    import paper_2602_08722_amd as pk
+    pk.load_library()
+    n_q, L = 16, 5 * chunk + tail
+    _, k, v = _prompt_on_device(1, n_q, 4, d, L, seed=tail)
+    rng = torch.Generator(device="cuda").manual_seed(7)
+    lean = 30.0 * torch.randn(1, 1, n_q, d, device="cuda", generator=rng)
+    q = (lean + torch.randn(1, L, n_q, d, device="cuda", generator=rng)).bfloat16().transpose(1, 2)
+    got = []
+    for full in (False, True):
+        pb = pk.PrefillBuffers(q, k, v, chunk, 64, lambda t: t // 8)
+        if not full:
+            pb.workspace = pb.workspace[:pk.quoka_workspace_bytes(pb.shape)]
+        pb.q_idx.fill_(-1)
+        pb.run()
+        torch.cuda.synchronize()
+        got.append((pb.q_idx, pb.qbar, pb.k_cnt, pb.k_idx[:, :, :int(pb.k_cnt[0, 0])]))
+    for a, b in zip(*got):
+        assert torch.equal(a, b)
+
+
 @pytest.mark.parametrize("dtype,n_q,n_kv,L,chunk,sparse", [
     ("bf16", 4, 1, 300, 8, False),      # decode kernel
     ("bf16", 4, 1, 300, 8, True),
