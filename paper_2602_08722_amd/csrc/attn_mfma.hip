@@ -827,7 +827,8 @@ static bool eight_row_blocks(const Dims& dm, long long groups) {
 // 256 resident blocks, a part for each further round, and for a split list one for each split and for the partials' bytes.  The numbers
 // are fits to half of 3800 measured calls (33 - 4096 tokens over 64 - 20000 keys, at most 1024 row blocks; rms 3 - 8 %); a split has to
 // promise 0.6 us more than it costs.  On the other half the plans are 0.5 % off the best of the measured ones on the mean (the fits
-// of the kernel before: 1.1 %), 10 % (d 64 20 %) for single ones.  Whole lists take blocks of eight where ragged row blocks make more
+// of the kernel before: 1.1 %), 10 % (d 64 20 %) for single ones; on 1800 calls of 3 - 64 tokens, most of them shorter than the fits have
+// seen, 0.8 % (d 64) and 1.2 % (those before: 1.3 and 2.3 %).  Whole lists take blocks of eight where ragged row blocks make more
 // than 256 blocks of four: 13 x 4 heads of 3, d 128, 187 tokens over 454 keys 34.3 -> 24.8 us, 171 over 4688 130 -> 105.
 struct AttnPlan {
   bool split_tile;
