@@ -8,7 +8,7 @@ import gen
 from oracle import quoka_oracle as O
 from tests import parity as P
 from tests.bf16_round import round_to_bf16
-from tests.test_gpu_stages import _buffers
+from tests.test_gpu_stages import _buffers, _pk
 
 pytestmark = pytest.mark.gpu
 
@@ -183,10 +183,51 @@ def test_bf16_attention_merge_of_splits(case):
 @pytest.mark.parametrize("case", [
     dict(n_q=4, n_kv=2, chunk=97, kv_lens=[1, 33, 64, 65], budgets=[1, 33, 64, 65], batch=4),
     dict(n_q=4, n_kv=2, chunk=128, kv_lens=[127, 128, 129, 0], budgets=[127, 128, 129, 0], batch=4),
+    dict(n_q=4, n_kv=2, chunk=289, kv_lens=[1, 64, 130, 0], budgets=[1, 64, 130, 0], batch=4),   # nothing for the second set in the last cache tile
     dict(n_q=64, n_kv=16, chunk=289, kv_lens=[31, 32, 63, 130], budgets=[31, 32, 63, 130], batch=4),
 ], ids=_id)
 def test_bf16_attention_units_and_runs_of_tiles(case, d, scale_f32):
     check_attention(dict(case, dtype="bf16", d=d), score_flags=16 if scale_f32 else 0)
+
+
+# bf16 rounds every probability but 1: those of the keys that hold a row's largest score are exact where that score is the row's
+# reference point.  Chunks whose first 64 keys are all that counts (half of them at probability 1, half at 3/4, whose values cancel) and
+# whose other keys, a few octaves below, have values of zero: a sum of exact probabilities is exactly zero, while a reference point taken
+# from another tile first scales both by 2^4.55, which rounds the one up and the other down and leaves up to 1e-3.
+@pytest.mark.parametrize("score_flags", [0, 16])
+@pytest.mark.parametrize("d", [64, 128])
+@pytest.mark.parametrize("chunk,kv_len", [(1100, 0), (1100, 100), (2240, 0), (2240, 257)])   # blocks of eight row blocks, of four
+def test_bf16_attention_takes_the_reference_point_from_the_first_keys(chunk, kv_len, d, score_flags):
+    n_q, n_kv = 32, 8
+    r = np.float32(1.4426950408889634) / np.sqrt(np.float32(d))
+    if not score_flags:
+        r = round_to_bf16(np.array([r]))[0]
+    shift = 4.55
+
+    def key(log2p):   # q = (1, 2^-8, 2^-16): the score in three pieces of eight bits
+        rest, pieces = log2p / float(r), []
+        for i in range(3):
+            piece = float(round_to_bf16(np.array([rest * 256.0 ** i], dtype=np.float32))[0])
+            pieces.append(piece)
+            rest -= piece / 256.0 ** i
+        return torch.tensor(pieces)
+
+    for p in (2.0 ** shift, 0.75 * 2.0 ** shift):   # (what the shifted probabilities round to)
+        assert abs(float(round_to_bf16(np.array([p], dtype=np.float32))[0]) / p - 1) > 1e-3
+    q = torch.zeros(1, n_q, chunk, d)
+    q[..., :3] = torch.tensor([1.0, 2.0 ** -8, 2.0 ** -16])
+    kc = torch.zeros(1, n_kv, chunk, d)
+    kc[..., 1:64:2, :3] = key(np.log2(0.75))
+    kc[..., 64:, :3] = key(-shift)
+    vc = torch.zeros(1, n_kv, chunk, d)
+    vc[..., 0:64:2, :], vc[..., 1:64:2, :] = 0.75, -1.0
+    k = torch.zeros(1, n_kv, max(kv_len, 1), d)
+    k[..., :3] = key(-shift)
+    dev = lambda t: t.to("cuda:0", torch.bfloat16)
+    buf = _pk().ChunkBuffers(dev(q), dev(k), dev(torch.zeros_like(k)), dev(kc), dev(vc), [kv_len], [0], 8, score_flags=score_flags)
+    buf.dense_attn()
+    torch.cuda.synchronize()
+    assert bool((buf.out[:, :, 64:] == 0).all()), float(buf.out[:, :, 64:].abs().max())
 
 
 # whole key lists of one sequence: one round of blocks of eight row blocks (130 of them, the last one not full; long lists
