@@ -303,10 +303,12 @@ __global__ __launch_bounds__(2 * kSetThreads, 2) void attn_bf16(Dims dm, AttnArg
 #pragma unroll
         for (int k = 0; k < NLD; ++k) first[k] = R[k];
       }
-      address(t_begin + 1);
-      look_up(t_begin + 2);
+      if (t_begin + 1 < t_end) {
+        address(t_begin + 1);
+        look_up(t_begin + 2);
 #pragma unroll
-      for (int k = 0; k < NLD; ++k) request(t_begin + 1, k);
+        for (int k = 0; k < NLD; ++k) request(t_begin + 1, k);
+      }
       if constexpr (!DMA) {
 #pragma unroll
         for (int k = 0; k < NLD; ++k) store(t_begin, k, first[k]);
@@ -474,14 +476,19 @@ __global__ __launch_bounds__(2 * kSetThreads, 2) void attn_bf16(Dims dm, AttnArg
     }
   };
 
+  using yes = std::integral_constant<bool, true>;
+  using no = std::integral_constant<bool, false>;
   // Step j of the block: K of tile j+2 and V of tile j+1 go to LDS (set 0: K, set 1: V) and every wave works on tile j.  One barrier a
   // step.  What step j brings is complete before the barrier of step j+1 (the wait and the fence ahead of it), in which it is first
   // read: the K operands of tile j+1 are read during tile j.  The places it takes held K of tile j and V of tile j-1, whose last reads
-  // ended before the barrier of step j (the fence again).  DMA: the first step's tiles are requested ahead of the loop.
-  auto begin_step = [&](int j) __attribute__((always_inline)) {
+  // ended before the barrier of step j (the fence again).  DMA: the first step's tiles are requested ahead of the loop.  (Whether a step
+  // can be the first is settled when it is compiled: asked in every step, and with a second tile requested and waited for where a block has
+  // only one, d 64 was 2 % slower on the mean of 2000 calls, d 128 1 %; 8 KV heads of 4, d 128, 1074 tokens over 3487 keys 96.1 -> 92.8 us.)
+  auto begin_step = [&](int j, auto can_be_first) __attribute__((always_inline)) {
     if constexpr (DMA) {
-      if (j < t_begin) {   // (its tiles are on their way; K of the first one has to be there)
-        wait_vmcnt<NLD>();
+      if (decltype(can_be_first)::value && j < t_begin) {   // (its tiles are on their way; K of the first one has to be there)
+        if (t_begin + 1 < t_end) wait_vmcnt<NLD>();
+        else wait_vmcnt<0>();
         __syncthreads();
         return;
       }
@@ -491,18 +498,16 @@ __global__ __launch_bounds__(2 * kSetThreads, 2) void attn_bf16(Dims dm, AttnArg
     address(DMA ? j + 2 - set : j + 3 - set);
     look_up(DMA ? j + 3 - set : j + 4 - set);
   };
-  auto stage_all = [&](int j) __attribute__((always_inline)) {
-    if (DMA && (j < t_begin || j + 2 - set >= t_end)) return;
+  auto stage_all = [&](int j, auto can_be_first) __attribute__((always_inline)) {
+    if (DMA && ((decltype(can_be_first)::value && j < t_begin) || j + 2 - set >= t_end)) return;
 #pragma unroll
     for (int k = 0; k < NLD; ++k) stage(j, k);
   };
-  using yes = std::integral_constant<bool, true>;
-  using no = std::integral_constant<bool, false>;
   auto nothing = [](int) __attribute__((always_inline)) {};
   int j = t_begin < t_end ? t_begin - 1 : t_end;
   for (; j < min(w0 - 1, t_end); ++j) {
-    begin_step(j);
-    stage_all(j);
+    begin_step(j, yes{});
+    stage_all(j, yes{});
   }
   if (w0 < w1) {
     // The staging of a step, a load at a time: between the products of the first unit's second half, or, where there are as many
@@ -511,7 +516,7 @@ __global__ __launch_bounds__(2 * kSetThreads, 2) void attn_bf16(Dims dm, AttnArg
       constexpr int first = NLD == KS ? 0 : KS, every = (2 * KS - first) / NLD;
       if (i >= first && (i - first) % every == 0) stage(j, (i - first) / every);
     };
-    begin_step(j);
+    begin_step(j, yes{});
     {   // S of the first unit, the operands of the second, the reference point
 #pragma unroll
       for (int i = 0; i < KS; ++i) read_k(0, i);
@@ -534,9 +539,9 @@ __global__ __launch_bounds__(2 * kSetThreads, 2) void attn_bf16(Dims dm, AttnArg
       }
       move_reference(s[0], mx);
     }
-    stage_all(j++);
+    stage_all(j++, yes{});
     for (; j + 1 < w1; ++j) {
-      begin_step(j);
+      begin_step(j, no{});
       move_k(j);
       half_qk(yes{}, s[1], s[0], 0, staging);
       mask(s[1], j, 1);
@@ -548,8 +553,8 @@ __global__ __launch_bounds__(2 * kSetThreads, 2) void attn_bf16(Dims dm, AttnArg
       mx = half_pv(yes{}, s[0], 1, nothing);
       move_reference(s[0], mx);
     }
-    begin_step(j);
-    stage_all(j);
+    begin_step(j, no{});
+    stage_all(j, no{});
     if (both_units(j)) {
       half_qk(yes{}, s[1], s[0], 0, nothing);
       mask(s[1], j, 1);
@@ -569,10 +574,10 @@ __global__ __launch_bounds__(2 * kSetThreads, 2) void attn_bf16(Dims dm, AttnArg
     ++j;
   }
   for (; j < t_end; ++j) {
-    begin_step(j);
-    stage_all(j);
+    begin_step(j, no{});
+    stage_all(j, no{});
   }
-  wait_vmcnt<0>();   // nothing may land in LDS from here on
+  if constexpr (DMA) wait_vmcnt<0>();   // nothing may land in LDS from here on
 
   // ---- merge of the two wave sets (SPLIT): set 1 hands (m, l, O) to set 0 through LDS ---------------------------
   if constexpr (SPLIT) {
