@@ -844,26 +844,34 @@ static int key_splits_limit(const Dims& dm, bool sparse, int keys_per_tile) {
 // Whole key lists of more than 1024 row blocks: eight row blocks per block, or four.
 // A batch: eight where that gives every compute unit a block.  (The lengths may differ, which the host cannot know, and then
 // smaller blocks fill up the second round where eight row blocks alone would be one.)
-// One sequence: up to 256 groups of eight (one round) eight is the faster at d 128 in all 176 measured calls, at d 64 but for short
-// lists of the chunk's own keys (0.15 % on the mean of 100, 4 % at most): 32/8 heads, d 128, 1973 tokens over 1221 keys, 248 groups 79.6 us,
-// with four 89.1; d 64, 12/4 heads, 3305 tokens over 75 keys 47.0, 45.1.  Above that blocks of four take three rounds where those of eight
-// take two, up to 384 groups (d 64: 416) in less time, 0.87 of it at 257 - 320 groups, 0.91 at 321 - 384; from there on those of eight, whose
-// longest ranges come first, even the rounds out (385 - 448 groups 0.97, 449 - 512 0.94 of the time of four).
-static bool eight_row_blocks(const Dims& dm, long long groups) {
-  if (dm.b > 1 || groups <= kComputeUnits) return dm.b == 1 || groups >= kComputeUnits;
-  return groups > (dm.d == 128 ? 384 : 416);
+// One sequence, d 128: up to 256 groups of eight (one round) eight is the faster in all but one of 1050 measured calls (blocks of four
+// take 0.99 - 1.36 of its time); above that blocks of four take three rounds where those of eight take two, up to 384 groups in
+// less time (0.84 of it at 257 - 288 groups, 0.97 at 353 - 384); from there on those of eight, whose longest ranges come first, even
+// the rounds out (four: 1.03 at 385 - 416 groups, 1.08 - 1.13 beyond).
+// d 64: up to 256 groups it depends on how much of the list is the chunk's own, whose causal ranges blocks of four follow more closely; the
+// bound is a fit of the two times' difference, in us, to half of 1040 measured calls (0 - 6000 keys; with it they take 0.1 % more than the better
+// form, with eight throughout 2.8 %): 12/4 heads, 3203 tokens alone, eight 42.9, four 39.9; 32/8, 1064 over 3000 tokens 62
+// and 71.  Up to 384 groups four (0.74 - 0.88), up to 512 where the chunk is more than three fifths of the list (0.90 - 0.96; else
+// 1.01 - 1.07), beyond that eight.
+static bool eight_row_blocks(const Dims& dm, bool sparse, long long groups) {
+  if (dm.b > 1) return groups >= kComputeUnits;
+  const float c = (float)attended_cap(dm, sparse) / kSub, r = (float)dm.C / kSub;
+  if (groups <= kComputeUnits) return dm.d == 128 || 4.35f + 0.103f * c - r * (0.078f + 9.0f / (float)groups) > 0.f;
+  if (dm.d == 64 && 3.f * c < 2.f * r) return groups > 512;
+  return groups > 384;
 }
 
 // Few row blocks leave compute units idle whatever the tile mode; their key lists are split over blocks instead.
 // Measured (kernel and merge, unsplit -> split): 4 KV heads x 3 sequences, d 64, 333 tokens over 4999 keys (2 splits)
 // 60 -> 38 us; one KV head of 16 q-heads x 8 sequences, d 64, 69 tokens over 13477 keys (5 splits) 138 -> 65 us.
 // The cheapest variant by a model of the call in microseconds: a fixed part, the steps of the longest key list's share times the rounds of
-// 256 resident blocks, a part for each further round, and for a split list one for each split and for the partials' bytes.  The numbers
-// are fits to half of 3800 measured calls (33 - 4096 tokens over 64 - 20000 keys, at most 1024 row blocks; rms 3 - 8 %); a split has to
-// promise 0.6 us more than it costs.  On the other half the plans are 0.5 % off the best of the measured ones on the mean (the fits
-// of the kernel before: 1.1 %), 10 % (d 64 20 %) for single ones; on 1800 calls of 3 - 64 tokens, most of them shorter than the fits have
-// seen, 0.8 % (d 64) and 1.2 % (those before: 1.3 and 2.3 %).  Whole lists take blocks of eight where ragged row blocks make more
-// than 256 blocks of four: 13 x 4 heads of 3, d 128, 187 tokens over 454 keys 34.3 -> 24.8 us, 171 over 4688 130 -> 105.
+// 256 resident blocks, a part for each further round, and for a split list one for each split, one for the partials' bytes and one where
+// there are more than four, whose merge's waves hand their sums to each other.  The numbers are fits to half of 13300 measured calls (2 - 3000
+// tokens over 0 - 20000 keys, at most 1024 row blocks).  On the other half the plans are behind the best of the measured ones, on the mean, by
+// 0.4 % (d 64) and 0.8 % (d 128) for 2 - 64 tokens, by 0.4 % for 33 - 3000 tokens and by 0.15 and 0.3 % for one sequence over few keys; 12 % for
+// single ones.  (Without the part beyond four splits, fitted to 33 tokens and more: 0.6, 1.1, 0.6 and 0.6 %, 20 %.)  Whole lists take blocks of
+// eight where ragged row blocks make more than 256 blocks of four: 13 x 4 heads of 3, d 128, 187 tokens over 454 keys 34.3 -> 24.8 us, 171 over
+// 4688 130 -> 105.
 struct AttnPlan {
   bool split_tile;
   int n_splits;
@@ -871,14 +879,14 @@ struct AttnPlan {
 
 static AttnPlan attn_plan(const Dims& dm, bool sparse) {
   const long long nrb = (long long)dm.g * ((dm.C + 31) / 32), heads = (long long)dm.n_kv * dm.b;
-  if (heads * nrb * 2 > kMaxRecords) return AttnPlan{!eight_row_blocks(dm, heads * ((nrb + 7) / 8)), 1};
+  if (heads * nrb * 2 > kMaxRecords) return AttnPlan{!eight_row_blocks(dm, sparse, heads * ((nrb + 7) / 8)), 1};
   struct Fit {
-    float fixed, step, round, per_mb, per_split;   // a step is 8 row blocks x 64 keys or 4 x 128
+    float fixed, step, round, per_mb, per_split, beyond_four;   // a step is 8 row blocks x 64 keys or 4 x 128
   };
-  constexpr Fit kWhole[2][2] = {{{6.9f, 0.86f, 3.f, 0.f, 0.f}, {6.2f, 1.03f, 3.9f, 0.f, 0.f}},     // d 64: eight row blocks, four
-                                {{8.1f, 1.16f, 3.f, 0.f, 0.f}, {8.4f, 1.33f, 9.8f, 0.f, 0.f}}};    // d 128
-  constexpr Fit kSplit[2][2] = {{{8.5f, 0.90f, 0.8f, 0.52f, 0.03f}, {8.8f, 1.05f, 1.7f, 0.52f, 0.045f}},
-                                {{10.9f, 1.21f, 0.7f, 0.42f, 0.01f}, {11.2f, 1.35f, 1.7f, 0.51f, 0.01f}}};
+  constexpr Fit kWhole[2][2] = {{{6.6f, 0.91f, 3.4f, 0.f, 0.f, 0.f}, {4.7f, 0.955f, 6.1f, 0.f, 0.f, 0.f}},    // d 64: eight row blocks, four
+                                {{6.9f, 1.14f, 2.f, 0.f, 0.f, 0.f}, {7.2f, 1.26f, 6.7f, 0.f, 0.f, 0.f}}};     // d 128
+  constexpr Fit kSplit[2][2] = {{{9.3f, 0.83f, 1.1f, 0.59f, 0.067f, 0.42f}, {7.35f, 1.015f, 0.f, 0.65f, 0.009f, 0.48f}},
+                                {{9.8f, 1.2f, 1.45f, 0.45f, 0.017f, 0.6f}, {9.8f, 1.48f, 0.85f, 0.51f, 0.01f, 1.1f}}};
   const int wide = dm.d == 128 ? 1 : 0;
   AttnPlan best{true, 1};
   float best_us = INFINITY;
@@ -891,8 +899,8 @@ static AttnPlan attn_plan(const Dims& dm, bool sparse) {
       const Fit& f = n == 1 ? kWhole[wide][mode] : kSplit[wide][mode];
       const long long rounds = (blocks * n + kComputeUnits - 1) / kComputeUnits, steps = (tiles + n - 1) / n;
       const float mb = (float)(heads * nrb * n) * (float)(dm.d + 2) * 128e-6f;
-      const float us = f.fixed + (n > 1 ? 0.6f : 0.f) + f.step * (float)(rounds * steps) + f.round * (float)(rounds - 1) + f.per_mb * mb +
-                       f.per_split * (float)n;
+      const float us = f.fixed + f.step * (float)(rounds * steps) + f.round * (float)(rounds - 1) + f.per_mb * mb + f.per_split * (float)n +
+                       (n > 4 ? f.beyond_four : 0.f);
       if (us < best_us) {
         best = AttnPlan{mode == 1, n};
         best_us = us;
