@@ -529,12 +529,22 @@ bool select_queries_one_block(const Dims& dm) {
 
 // bf16 calls of 64 heads or more (sequences, and chunks of a prompt that share a launch, count alike: the sums are the tiled kernels')
 // up to kManyTokens tokens: Q is read once instead of twice, and that pays as soon as a good part of the compute units has a head.
-// Query stage, d 128: 64 heads of 1024 tokens 16.9 -> 16.0 us, 128 23.0 -> 18.3, 256 36.1 -> 24.3, 288 (two rounds) 40.8 -> 37.5, 512
-// 63.4 -> 47.8; d 64, 300 heads 27.9 -> 22.7.  Whole calls over 8192 keys: 8 x 32 heads 263 -> 251 us, 4 x 32 145 -> 140, 64 84.9 -> 84.1;
-// with 48 heads even, with 32, 16 and 8 1 to 3 % slower.  (Float32 heads of d 64 gain 2 to 3 % of the stage, of d 128 do not fit;
-// 2048 tokens of d 64 gain where the heads nearly fill the last round, 256 40 -> 31 us, and lose elsewhere: neither is built.)
-constexpr int kManyTokens = 1024;
-static bool select_queries_many_heads(const Dims& dm) { return dm.C <= kManyTokens && dm.n_q * dm.b >= 64; }
+// Query stage, d 128: 64 heads of 1024 tokens 16.9 -> 16.0 us, 128 23.0 -> 18.3, 256 36.1 -> 24.3, 512 63.4 -> 47.8; d 64 0.97 - 0.99 of the
+// time for 64 heads, 0.90 - 0.96 for 112 to 256, 0.63 - 0.82 beyond, wherever it was measured (513 - 1024 tokens, up to 4096 heads).
+// At d 128 a head takes its compute unit long enough that the last round of blocks counts: 260 heads of 513 tokens 24.9 -> 28.3, 520 of
+// 513 43.9 -> 46.2, and 64 of 513 14.5 -> 14.6.  The line there is a fit of both times, in us, to 2810 calls of up to 768 heads (with it they
+// take 0.01 % more than the better route on the mean, 2.6 % at most; one block throughout 1 and 14 %); beyond that, rounds are many and one
+// block is the faster, 0.66 - 0.98.
+// Whole calls over 8192 keys, 1024 tokens: 8 x 32 heads 263 -> 251 us, 4 x 32 145 -> 140, 64 84.9 -> 84.1; with 48 heads even, with 32, 16
+// and 8 1 to 3 % slower.  (Float32 heads of d 64 gain 2 to 3 % of the stage, of d 128 do not fit; 2048 tokens of d 64 gain where the heads
+// nearly fill the last round, 256 40 -> 31 us, and lose elsewhere: neither is built.)
+constexpr int kManyTokens = 1024, kComputeUnits = 256;
+static bool select_queries_many_heads(const Dims& dm) {
+  const int heads = dm.n_q * dm.b, rounds = (heads + kComputeUnits - 1) / kComputeUnits;
+  if (dm.C > kManyTokens || heads < 64) return false;
+  const float c = (float)dm.C / 1024.f;
+  return dm.d == 64 || rounds > 3 || (float)rounds * (7.8f + 2.0f * c) < 6.5f + (float)heads * c * (4.0f / 64.f);
+}
 
 template <typename T, int D, int RULE>
 static void launch_qbar(const Dims& dm, const T* q, int32_t* q_idx, float* qbar, int n_keep, hipStream_t st, uint32_t* zero,
