@@ -768,22 +768,25 @@ bool select_keys_two_pass_applies(const Dims& dm, int dtype) {
 // 8 x 8 of 36611, d 64 138 -> 156.  260 sizes measured; the lines lie where the two sides meet.  Packed calls score exactly either way and the
 // streaming launch is the faster for them; a prompt's chunks share one cache, 12 prompts 0.96 - 1.15 of the time, no line to draw.
 // (At these sizes a scoring block has far fewer than the 65536 keys that its 16-bit counters hold.)
-constexpr long long kExactBytes = 250'000'000, kExactBytesWide = 80'000'000;
+constexpr long long kExactBytesFew = 300'000'000, kExactBytes = 250'000'000, kExactBytesWide = 80'000'000;
+static long long exact_bytes(int n_keep) { return n_keep <= 32 ? kExactBytesFew : n_keep <= 64 ? kExactBytes : kExactBytesWide; }
 bool select_keys_exact_pays(const Dims& dm, int dtype) {
   if (!select_keys_two_pass_applies(dm, dtype) || dm.T_max > kPackMaxKeys || score_packs(dm)) return false;
   const int n_keep = dm.n_ret < dm.C ? dm.n_ret : dm.C;
-  return (long long)dm.b * dm.n_kv * dm.T_cap * dm.d * 2 <= (n_keep <= 64 ? kExactBytes : kExactBytesWide);
+  return (long long)dm.b * dm.n_kv * dm.T_cap * dm.d * 2 <= exact_bytes(n_keep);
 }
 
 // Beyond those sizes exact scores come from the streaming launch, as long as its products hide behind the keys' way from memory: up
 // to 64 queries.  Whole calls with a small attention part, us: against the two-pass form 8 x 8 heads of 4096 to 64077 positions, 64
 // queries 321 -> 310, 3 x 8 of 53300 144 -> 133, 13 x 4 of 7500 to 60000 187 -> 177, d 64 13 x 8 of 5000 to 40000 146 -> 131; against the
-// exact scores of the tiled launch 8 of 131072, 268 MB 115.6 -> 111.8, 32 queries 108.7 -> 104.4, 2 x 8 of 130000, d 64, 266 MB 132.5
-// -> 127.0, but 8 of 92109, 189 MB 97.7 -> 98.3, 8 of 130000, d 64, 133 MB 83.2 -> 86.2, 1 of 72294 48.7 -> 53.1.
+// exact scores of the tiled launch 8 of 131072, 268 MB 115.6 -> 111.8, 2 x 8 of 130000, d 64, 266 MB 132.5 -> 127.0 (33 to 64 queries over 250
+// to 300 MB 0.95 of the time at d 64, 0.98 at d 128), but 8 of 92109, 189 MB 97.7 -> 98.3, 8 of 130000, d 64, 133 MB 83.2 -> 86.2, 1 of 72294
+// 48.7 -> 53.1.  With up to 32 queries the tiled launch has little to compute, and from 250 to 300 MB the streaming one is 1 % slower (333
+// calls; d 64, 4 x 8 heads of 67939 94 and 98 us); two-pass, which it replaces beyond, takes 1.10 to 1.17 of its time.
 bool select_keys_streams_exact(const Dims& dm, int dtype) {
   if (!select_keys_two_pass_applies(dm, dtype) || dm.T_max > kPackMaxKeys || score_packs(dm)) return false;
   const int n_keep = dm.n_ret < dm.C ? dm.n_ret : dm.C;
-  return n_keep <= 64 && (long long)dm.b * dm.n_kv * dm.T_cap * dm.d * 2 > kExactBytes;
+  return n_keep <= 64 && (long long)dm.b * dm.n_kv * dm.T_cap * dm.d * 2 > exact_bytes(n_keep);
 }
 
 hipError_t launch_select_keys_exact(const Dims& dm, const float* qbar, const void* k_cache, const int32_t* kv_lens,

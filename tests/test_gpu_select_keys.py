@@ -314,7 +314,7 @@ def test_chunk_attn_of_caches_with_room_to_spare(n_kv, d, T_max, lens):
         assert torch.equal(buf.scores[i, :, :T], sc[i, :, :T]) and torch.equal(buf.k_idx[i, :, :n], idx[i, :, :n])
 
 
-# Beyond 250 MB of keys the streaming launch scores exactly (up to 64 queries): the scores and lists of the two separate calls bit for bit;
+# Beyond 250 MB of keys (up to 32 queries: 300 MB) the streaming launch scores exactly (up to 64 queries): the scores and lists of the two separate calls bit for bit;
 # one query block and two, not full and full; steps of 256 keys just short of, at and past full, empty sequences, more than a wave has lanes
 @pytest.mark.parametrize("kind", ["normal", "pairs", "equal"])
 @pytest.mark.parametrize("n_kv,d,T_max,lens,n_retain", [
@@ -323,6 +323,8 @@ def test_chunk_attn_of_caches_with_room_to_spare(n_kv, d, T_max, lens):
     (8, 64, 33000, [33000, 0, 1, 255, 256, 257, 5000, 32768], 33),
     (1, 128, 131072, [131072, 100001, 3, 65536, 0, 131071, 5, 90000], 32),
     (1, 64, 32800, [32800 - 499 * (i % 65) for i in range(66)], 40),
+    (4, 128, 40000, [40000, 0, 1, 255, 256, 257, 5000, 32768], 9),
+    (1, 128, 131072, [131072, 100001, 3, 65536, 0, 131071, 5, 90000, 777], 32),
 ], ids=lambda v: f"{len(v)}x{v[0]}" if isinstance(v, list) else str(v))
 def test_chunk_attn_streams_exact_scores(kind, n_kv, d, T_max, lens, n_retain):
     pk = _pk()
