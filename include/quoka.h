@@ -227,7 +227,11 @@ quoka_status quoka_topk_keys_noalloc(const quoka_shape* shape, const float* scor
  *                     16-byte loads and writes nothing.
  *   quoka_probe_attn_mix  `blocks` blocks of 8 waves, each wave running `steps` steps of the bf16 attention kernel's
  *                     instruction mix without its memory side: 32 MFMAs (32768 flop each), 32 exponentials and about
- *                     160 plain vector operations per step, S first, then softmax and O.                         */
+ *                     160 plain vector operations per step, S first, then softmax and O.
+ *   quoka_probe_attn_plan  (host only, launches nothing) how quoka_sparse_attn (sparse != 0) or quoka_dense_attn would lay out the bf16
+ *                     attention of this shape: row blocks of 32 query rows per block (8 or 4) and blocks that share a row block's
+ *                     key list (1: none).  Both 0 where another kernel takes the call (float32; decode-sized chunks). */
+quoka_status quoka_probe_attn_plan(const quoka_shape* shape, int sparse, int32_t* row_blocks, int32_t* n_splits);
 quoka_status quoka_probe_attn_mix(int blocks, int steps, float* sink, void* stream);
 quoka_status quoka_probe_mfma(int blocks, int iters, float* sink, void* stream);
 quoka_status quoka_probe_read(const void* src, size_t bytes, float* sink, void* stream);

@@ -23,7 +23,7 @@ EXPORTS = (
     "quoka_workspace_bytes", "quoka_select_queries", "quoka_score_keys", "quoka_topk_keys", "quoka_select_keys",
     "quoka_sparse_attn", "quoka_dense_attn", "quoka_chunk_attn", "quoka_prefill_workspace_bytes", "quoka_prefill_attn",
     "quoka_topk_keys_noalloc",
-    "quoka_probe_mfma", "quoka_probe_read", "quoka_probe_attn_mix", "quoka_status_string", "quoka_version",
+    "quoka_probe_mfma", "quoka_probe_read", "quoka_probe_attn_mix", "quoka_probe_attn_plan", "quoka_status_string", "quoka_version",
 )
 _STATUS_EXPORTS = EXPORTS[:-2]   # everything that returns a quoka_status
 
@@ -187,6 +187,14 @@ def quoka_probe_mfma(blocks: int, iters: int, sink, stream=None) -> None:
 def quoka_probe_attn_mix(blocks: int, steps: int, sink, stream=None) -> None:
     _check("quoka_probe_attn_mix", load_library().quoka_probe_attn_mix(int(blocks), int(steps), _ptr(sink),
                                                                        _stream(stream)))
+
+
+def quoka_probe_attn_plan(shape: QuokaShape, sparse: bool):
+    """(row blocks per block, blocks that share a key list) of the bf16 attention kernel for this shape; (0, 0) where another takes it."""
+    rows, splits = ctypes.c_int32(0), ctypes.c_int32(0)
+    _check("quoka_probe_attn_plan", load_library().quoka_probe_attn_plan(
+        ctypes.byref(shape), int(bool(sparse)), ctypes.byref(rows), ctypes.byref(splits)))
+    return rows.value, splits.value
 
 
 def quoka_probe_read(src, nbytes: int, sink, stream=None) -> None:

@@ -593,6 +593,16 @@ quoka_status quoka_probe_mfma(int blocks, int iters, float* sink, void* stream) 
   return from_hip(quoka::launch_probe_mfma(blocks, iters, sink, static_cast<hipStream_t>(stream)));
 }
 
+quoka_status quoka_probe_attn_plan(const quoka_shape* shape, int sparse, int32_t* row_blocks, int32_t* n_splits) {
+  Dims dm;
+  const quoka_status st = check_shape(shape, &dm);
+  if (st != QUOKA_OK) return st;
+  if (row_blocks == nullptr || n_splits == nullptr) return QUOKA_EINVAL;
+  *row_blocks = *n_splits = 0;
+  if (shape->dtype == QUOKA_BF16 && !quoka::attn_decode_applies(dm)) quoka::attn_bf16_plan(dm, sparse != 0, row_blocks, n_splits);
+  return QUOKA_OK;
+}
+
 quoka_status quoka_probe_attn_mix(int blocks, int steps, float* sink, void* stream) {
   if (blocks < 1 || blocks > 65535 || steps < 1 || sink == nullptr) return QUOKA_EINVAL;
   return from_hip(quoka::launch_probe_attn_mix(blocks, steps, sink, static_cast<hipStream_t>(stream)));

@@ -930,6 +930,12 @@ static hipError_t launch_d(const Dims& dm, const AttnArgs& a, hipStream_t st) {
   return p.split_tile ? launch_ds<D, true>(dm, aa, st) : launch_ds<D, false>(dm, aa, st);
 }
 
+void attn_bf16_plan(const Dims& dm, bool sparse, int32_t* row_blocks, int32_t* n_splits) {
+  const AttnPlan p = attn_plan(dm, sparse);
+  *row_blocks = p.split_tile ? 4 : 8;
+  *n_splits = p.n_splits;
+}
+
 hipError_t launch_attn_bf16(const Dims& dm, const AttnArgs& a, float* part, hipStream_t st) {
   AttnArgs aa = a;
   aa.part = part;

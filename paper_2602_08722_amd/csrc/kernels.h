@@ -99,6 +99,7 @@ struct AttnArgs {
 inline int attended_cap(const Dims& dm, bool sparse) { return sparse && dm.B_max < dm.T_cap ? dm.B_max : dm.T_cap; }
 size_t attn_bf16_ws_floats(const Dims& dm);
 hipError_t launch_attn_bf16(const Dims& dm, const AttnArgs& a, float* part, hipStream_t st);
+void attn_bf16_plan(const Dims& dm, bool sparse, int32_t* row_blocks, int32_t* n_splits);   // what that launch would choose
 // decode-sized chunks (g * C <= 32 query rows per KV head): split-KV kernel + merge, partials in `part`
 bool attn_decode_applies(const Dims& dm);
 size_t attn_decode_ws_floats(const Dims& dm);

@@ -21,9 +21,14 @@ def check_attention(case, rows=None, score_flags=0, tol=None):
     """Sparse attention over seeded random index lists of the stated budgets, then dense attention, each with its
     softmax normaliser, against the oracle (every row, or the chunk positions `rows`)."""
     case = dict(case)
+    plan, dense_plan = case.pop("plan", None), case.pop("dense_plan", None)
     batch = case.setdefault("batch", 1)
     w = gen.make_custom(n_retain=8, seed=21, **case)
     buf = _buffers(w, score_flags=score_flags)
+    if plan is not None:
+        assert _pk().quoka_probe_attn_plan(buf.shape, True) == plan
+    if dense_plan is not None:
+        assert _pk().quoka_probe_attn_plan(buf.shape, False) == dense_plan
     tol = tol or P.TOL_OUT[w.dtype]
     tol_lse = 1e-4 if w.dtype == "f32" else 2e-2
     rng = np.random.default_rng(3)
@@ -132,13 +137,17 @@ def test_float32_scores_of_few_queries(n_q, n_retain, kv_lens, d, score_flags):
         assert not np.isnan(got).any() and (not got.size or P.max_abs(got, want) <= P.TOL_SCORE * (np.sqrt(d) * 1.5 if score_flags & 1 else 1))
 
 
-# bf16 prefill kernel with the key list split over blocks (few row blocks); the second sequence of a batch has fewer
-# tiles than there are splits, so some blocks get none
+# The bf16 prefill kernel chooses blocks of eight or four row blocks and how many of them share a key list by a model of the call.
+# `plan` says what a case is meant to run, (row blocks per block, splits) of the sparse call: a change of the model that takes a case
+# elsewhere fails (tests/test_attn_plan.py, without a GPU), and the case is to be chosen anew.
+# Key lists split over blocks (few row blocks); the second sequence of a batch has fewer tiles than there are splits, so some blocks
+# get none
 BF16_SPLIT_CASES = [
-    dict(n_q=8, n_kv=2, d=128, chunk=9, kv_lens=[6000, 3], budgets=[1500, 3], batch=2),
-    dict(n_q=2, n_kv=1, d=64, chunk=33, kv_lens=[4097], budgets=[640]),
-    dict(n_q=7, n_kv=1, d=128, chunk=65, kv_lens=[2500], budgets=[2500]),
-    dict(n_q=2, n_kv=2, d=128, chunk=129, kv_lens=[1, 5000, 0], budgets=[1, 1100, 9], batch=3),
+    dict(n_q=8, n_kv=2, d=128, chunk=9, kv_lens=[6000, 3], budgets=[1500, 3], batch=2, plan=(4, 13)),
+    dict(n_q=2, n_kv=1, d=64, chunk=33, kv_lens=[4097], budgets=[640], plan=(4, 6)),
+    dict(n_q=7, n_kv=1, d=128, chunk=65, kv_lens=[2500], budgets=[2500], plan=(4, 11)),
+    dict(n_q=2, n_kv=2, d=128, chunk=129, kv_lens=[1, 5000, 0], budgets=[1, 1100, 9], batch=3, plan=(4, 11)),
+    dict(n_q=2, n_kv=1, d=128, chunk=33, kv_lens=[1000], budgets=[640], plan=(8, 11)),   # a tile each
 ]
 
 
@@ -149,43 +158,73 @@ def test_bf16_attention_key_splits(case, scale_f32):
 
 
 def test_bf16_attention_key_splits_of_a_batch_in_one_round():
-    # 104 blocks of two row blocks: two splits, one round of blocks, where seven would be three
+    # 104 blocks of two row blocks: the dense call's lists are shared by two blocks, one round
     check_attention(dict(dtype="bf16", n_q=16, n_kv=8, d=64, chunk=17, kv_lens=[3000 - 230 * i for i in range(13)],
-                         budgets=[700] * 13, batch=13), rows=[0, 8, 16])
+                         budgets=[700] * 13, batch=13, plan=(4, 1), dense_plan=(4, 2)), rows=[0, 8, 16])
 
 
 def test_bf16_attention_key_splits_of_eight_row_blocks():
     # 48 groups of eight row blocks on 256 compute units, which the plan splits five ways
-    check_attention(dict(dtype="bf16", n_q=8, n_kv=8, d=128, chunk=1341, kv_lens=[5000], budgets=[3000]),
+    check_attention(dict(dtype="bf16", n_q=8, n_kv=8, d=128, chunk=1341, kv_lens=[5000], budgets=[3000], plan=(8, 5)),
                     rows=[0, 1, 31, 32, 700, 1311, 1312, 1340])
 
 
-# the merge of key splits takes four records at a time and up to eight waves: 2 to 5 splits, 8 and 9, and the most there are
-@pytest.mark.parametrize("case", [
-    dict(n_q=32, n_kv=8, d=64, chunk=333, kv_lens=[2000], budgets=[1990]),       # 2
-    dict(n_q=7, n_kv=1, d=128, chunk=333, kv_lens=[300], budgets=[299]),         # 3
-    dict(n_q=14, n_kv=2, d=128, chunk=65, kv_lens=[300], budgets=[290]),         # 4
-    dict(n_q=2, n_kv=1, d=64, chunk=333, kv_lens=[150], budgets=[150]),          # 5
-    dict(n_q=4, n_kv=1, d=128, chunk=130, kv_lens=[700], budgets=[640]),         # 8
-    dict(n_q=1, n_kv=1, d=64, chunk=333, kv_lens=[700], budgets=[690]),          # 9
-    dict(n_q=1, n_kv=1, d=128, chunk=33, kv_lens=[20000], budgets=[19000]),      # 32, one token in the second row block
-    dict(n_q=3, n_kv=1, d=64, chunk=33, kv_lens=[9000, 2, 0, 4000], budgets=[8000, 2, 1, 40], batch=4),   # neutral records
-], ids=_id)
+# the merge of key splits takes four records at a time and up to eight waves: 2 to 5 splits, 7 to 9, and the most there are
+MERGE_CASES = [
+    dict(n_q=32, n_kv=8, d=64, chunk=333, kv_lens=[2000], budgets=[1990], plan=(4, 2)),
+    dict(n_q=7, n_kv=1, d=128, chunk=333, kv_lens=[300], budgets=[299], plan=(4, 3)),
+    dict(n_q=14, n_kv=2, d=128, chunk=65, kv_lens=[300], budgets=[290], plan=(4, 1)),
+    dict(n_q=2, n_kv=1, d=64, chunk=333, kv_lens=[150], budgets=[150], plan=(4, 1)),
+    dict(n_q=4, n_kv=1, d=128, chunk=130, kv_lens=[700], budgets=[640], plan=(4, 4)),
+    dict(n_q=1, n_kv=1, d=64, chunk=33, kv_lens=[300], budgets=[290], plan=(4, 4)),
+    dict(n_q=4, n_kv=1, d=128, chunk=130, kv_lens=[300], budgets=[290], plan=(8, 4)),
+    dict(n_q=1, n_kv=1, d=64, chunk=130, kv_lens=[300], budgets=[290], plan=(4, 5)),
+    dict(n_q=7, n_kv=1, d=128, chunk=130, kv_lens=[1000], budgets=[1000], plan=(4, 5)),
+    dict(n_q=1, n_kv=1, d=64, chunk=33, kv_lens=[700], budgets=[700], plan=(4, 7)),
+    dict(n_q=1, n_kv=1, d=64, chunk=130, kv_lens=[700], budgets=[700], plan=(4, 8)),
+    dict(n_q=1, n_kv=1, d=128, chunk=130, kv_lens=[300], budgets=[290], plan=(8, 8)),
+    dict(n_q=1, n_kv=1, d=64, chunk=333, kv_lens=[700], budgets=[690], plan=(4, 9)),
+    dict(n_q=1, n_kv=1, d=128, chunk=333, kv_lens=[200], budgets=[129], plan=(8, 9)),
+    dict(n_q=1, n_kv=1, d=128, chunk=33, kv_lens=[20000], budgets=[19000], plan=(4, 30)),      # one token in the second row block
+    dict(n_q=1, n_kv=1, d=64, chunk=1000, kv_lens=[19000], budgets=[19000], plan=(4, 32)),
+    dict(n_q=3, n_kv=1, d=64, chunk=33, kv_lens=[9000, 2, 0, 4000], budgets=[8000, 2, 1, 40], batch=4, plan=(4, 22)),   # neutral records
+]
+
+
+@pytest.mark.parametrize("case", MERGE_CASES, ids=_id)
 def test_bf16_attention_merge_of_splits(case):
-    check_attention(dict(case, dtype="bf16"))
+    check_attention(dict(case, dtype="bf16"), rows=[0, 31, 32, 500, 999] if case["chunk"] == 1000 else None)
+
+
+# shares of many tiles in blocks of eight row blocks, at d 64 staged through registers: 131 tiles over four blocks, whose shares begin
+# at tiles of either stage; a sequence whose shares differ by a tile and one with fewer tiles than blocks
+MANY_TILES_CASES = [
+    dict(n_q=12, n_kv=4, d=64, chunk=333, kv_lens=[8000, 5003, 64], budgets=[8000, 5003, 64], batch=3, plan=(8, 4)),
+    dict(n_q=32, n_kv=8, d=128, chunk=333, kv_lens=[5000], budgets=[5000], plan=(8, 5)),
+]
+
+
+@pytest.mark.parametrize("scale_f32", [False, True], ids=["", "scale-f32"])
+@pytest.mark.parametrize("case", MANY_TILES_CASES, ids=_id)
+def test_bf16_attention_shares_of_many_tiles(case, scale_f32):
+    check_attention(dict(case, dtype="bf16"), rows=[0, 31, 32, 63, 64, 100, 200, 320, 332], score_flags=16 if scale_f32 else 0)
 
 
 # a wave works in units of 32 keys, the first of them formed ahead of the loop, the last without a successor: lists that end within and
 # at the end of the first and second unit of the first and second tile, chunks whose row blocks start in either unit of a tile;
 # blocks of four row blocks (chunk 97: the second wave set sees nothing of the first chunk tile) and of eight (batches of 32 heads)
+UNIT_CASES = [
+    dict(n_q=4, n_kv=2, chunk=97, kv_lens=[1, 33, 64, 65], budgets=[1, 33, 64, 65], batch=4, plan=(4, 1)),
+    dict(n_q=4, n_kv=2, chunk=128, kv_lens=[127, 128, 129, 0], budgets=[127, 128, 129, 0], batch=4, plan=(4, 1)),
+    # nothing for the second set in the last cache tile
+    dict(n_q=4, n_kv=2, chunk=289, kv_lens=[1, 64, 130, 0], budgets=[1, 64, 130, 0], batch=4, plan=(4, 1)),
+    dict(n_q=64, n_kv=16, chunk=289, kv_lens=[31, 32, 63, 130], budgets=[31, 32, 63, 130], batch=4, plan=(8, 1)),
+]
+
+
 @pytest.mark.parametrize("scale_f32", [False, True], ids=["", "scale-f32"])
 @pytest.mark.parametrize("d", [64, 128])
-@pytest.mark.parametrize("case", [
-    dict(n_q=4, n_kv=2, chunk=97, kv_lens=[1, 33, 64, 65], budgets=[1, 33, 64, 65], batch=4),
-    dict(n_q=4, n_kv=2, chunk=128, kv_lens=[127, 128, 129, 0], budgets=[127, 128, 129, 0], batch=4),
-    dict(n_q=4, n_kv=2, chunk=289, kv_lens=[1, 64, 130, 0], budgets=[1, 64, 130, 0], batch=4),   # nothing for the second set in the last cache tile
-    dict(n_q=64, n_kv=16, chunk=289, kv_lens=[31, 32, 63, 130], budgets=[31, 32, 63, 130], batch=4),
-], ids=_id)
+@pytest.mark.parametrize("case", UNIT_CASES, ids=_id)
 def test_bf16_attention_units_and_runs_of_tiles(case, d, scale_f32):
     check_attention(dict(case, dtype="bf16", d=d), score_flags=16 if scale_f32 else 0)
 
@@ -196,7 +235,7 @@ def test_bf16_attention_units_and_runs_of_tiles(case, d, scale_f32):
 # from another tile first scales both by 2^4.55, which rounds the one up and the other down and leaves up to 1e-3.
 @pytest.mark.parametrize("score_flags", [0, 16])
 @pytest.mark.parametrize("d", [64, 128])
-@pytest.mark.parametrize("chunk,kv_len", [(1100, 0), (1100, 100), (2240, 0), (2240, 257)])   # blocks of eight row blocks, of four
+@pytest.mark.parametrize("chunk,kv_len", [(1100, 0), (1100, 100), (2240, 0), (2240, 257)])
 def test_bf16_attention_takes_the_reference_point_from_the_first_keys(chunk, kv_len, d, score_flags):
     n_q, n_kv = 32, 8
     r = np.float32(1.4426950408889634) / np.sqrt(np.float32(d))
@@ -225,39 +264,55 @@ def test_bf16_attention_takes_the_reference_point_from_the_first_keys(chunk, kv_
     k[..., :3] = key(-shift)
     dev = lambda t: t.to("cuda:0", torch.bfloat16)
     buf = _pk().ChunkBuffers(dev(q), dev(k), dev(torch.zeros_like(k)), dev(kc), dev(vc), [kv_len], [0], 8, score_flags=score_flags)
+    four = chunk == 2240   # blocks of four row blocks, of eight
+    assert _pk().quoka_probe_attn_plan(buf.shape, False) == (4 if four else 8, 1)
     buf.dense_attn()
     torch.cuda.synchronize()
     assert bool((buf.out[:, :, 64:] == 0).all()), float(buf.out[:, :, 64:].abs().max())
 
 
-# whole key lists of one sequence: one round of blocks of eight row blocks (130 of them, the last one not full; long lists
-# and none), and two rounds of blocks of four (264 of eight)
-@pytest.mark.parametrize("case", [
-    dict(n_q=16, n_kv=1, d=64, chunk=2070, kv_lens=[3000], budgets=[2500]),
-    dict(n_q=16, n_kv=1, d=64, chunk=2070, kv_lens=[0], budgets=[1]),
-    dict(n_q=7, n_kv=1, d=128, chunk=4803, kv_lens=[700], budgets=[129]),
-    dict(n_q=32, n_kv=8, d=64, chunk=2081, kv_lens=[100], budgets=[65]),
-], ids=_id)
+# whole key lists of one sequence: one round of blocks of eight row blocks (130 of them, the last one not full), two rounds of
+# blocks of four at d 64 (lists of the chunk's own keys), three at either head size (264 groups of eight), two rounds of blocks of eight
+WHOLE_CASES = [
+    dict(n_q=16, n_kv=1, d=64, chunk=2070, kv_lens=[3000], budgets=[2500], plan=(8, 1)),
+    dict(n_q=16, n_kv=1, d=64, chunk=2070, kv_lens=[0], budgets=[1], plan=(4, 1)),
+    dict(n_q=7, n_kv=1, d=128, chunk=4803, kv_lens=[700], budgets=[129], plan=(8, 1)),
+    dict(n_q=32, n_kv=8, d=64, chunk=2081, kv_lens=[100], budgets=[65], plan=(4, 1)),
+    dict(n_q=28, n_kv=4, d=128, chunk=2400, kv_lens=[300], budgets=[65], plan=(4, 1)),
+    dict(n_q=28, n_kv=4, d=64, chunk=2400, kv_lens=[300], budgets=[129], plan=(4, 1)),
+    dict(n_q=64, n_kv=4, d=128, chunk=1569, kv_lens=[130], budgets=[100], plan=(8, 1)),
+]
+
+
+@pytest.mark.parametrize("case", WHOLE_CASES, ids=_id)
 def test_bf16_attention_whole_lists_of_one_sequence(case):
     check_attention(dict(case, dtype="bf16"), rows=[0, 31, 32, 1000, case["chunk"] - 33, case["chunk"] - 1])
 
 
 # rows go out through LDS, which the waves' hand-over records (blocks of four) or the tiles (blocks of eight) held before: every row,
 # the last row block not full, into contiguous outputs and into rows that lie apart, whose gaps stay as they are
+ROW_CASES = [
+    dict(n_q=16, n_kv=2, d=128, chunk=2070, kv_lens=[50], budgets=[40], plan=(8, 1)),
+    dict(n_q=16, n_kv=2, d=64, chunk=2070, kv_lens=[50], budgets=[40], plan=(4, 1)),
+    dict(n_q=28, n_kv=4, d=128, chunk=2400, kv_lens=[50], budgets=[40], plan=(4, 1)),      # rounds of blocks of four
+    dict(n_q=14, n_kv=2, d=64, chunk=5, kv_lens=[129], budgets=[129], plan=(4, 1)),        # few rows: stored as the registers lie; 63 of
+    dict(n_q=14, n_kv=2, d=128, chunk=9, kv_lens=[130], budgets=[129], plan=(4, 1)),       # them, and 64, which go out whole
+    dict(n_q=16, n_kv=2, d=128, chunk=8, kv_lens=[130], budgets=[129], plan=(4, 1)),
+    dict(n_q=4, n_kv=2, d=64, chunk=31, kv_lens=[60], budgets=[50], plan=(4, 1)),          # 62, one head a row block
+    dict(n_q=4, n_kv=2, d=64, chunk=97, kv_lens=[70], budgets=[65], plan=(4, 1)),
+    dict(n_q=14, n_kv=2, d=128, chunk=9, kv_lens=[60], budgets=[50], plan=(8, 1)),         # blocks of eight: whole, however few
+    dict(n_q=16, n_kv=2, d=128, chunk=8, kv_lens=[60], budgets=[50], plan=(8, 1)),
+    dict(n_q=16, n_kv=2, d=128, chunk=2070, kv_lens=[3000], budgets=[2500], plan=(8, 1)),
+    dict(n_q=16, n_kv=2, d=64, chunk=2070, kv_lens=[3000], budgets=[2500], plan=(8, 1)),   # (as the registers lie)
+]
+
+
 @pytest.mark.parametrize("scale_f32", [False, True], ids=["", "scale-f32"])
-@pytest.mark.parametrize("case", [
-    dict(n_q=16, n_kv=2, d=128, chunk=2070, kv_lens=[50], budgets=[40]),        # blocks of four
-    dict(n_q=16, n_kv=2, d=64, chunk=2070, kv_lens=[50], budgets=[40]),
-    dict(n_q=14, n_kv=2, d=64, chunk=5, kv_lens=[129], budgets=[129]),          # few rows: stored as the registers lie; 63 of them,
-    dict(n_q=14, n_kv=2, d=128, chunk=9, kv_lens=[60], budgets=[50]),           # and 64, which go out whole
-    dict(n_q=16, n_kv=2, d=128, chunk=8, kv_lens=[60], budgets=[50]),
-    dict(n_q=4, n_kv=2, d=64, chunk=31, kv_lens=[60], budgets=[50]),            # 62, one head a row block
-    dict(n_q=16, n_kv=2, d=128, chunk=2070, kv_lens=[3000], budgets=[2500]),    # blocks of eight
-], ids=_id)
+@pytest.mark.parametrize("case", ROW_CASES, ids=_id)
 def test_bf16_attention_rows_of_whole_lists(case, scale_f32):
     flags, rows = 16 if scale_f32 else 0, sorted({0, 1, case["chunk"] // 2, case["chunk"] - 2, case["chunk"] - 1})
     check_attention(dict(case, dtype="bf16"), rows=rows, score_flags=flags)
-    w = gen.make_custom(dtype="bf16", n_retain=8, seed=22, batch=1, **case)
+    w = gen.make_custom(dtype="bf16", n_retain=8, seed=22, batch=1, **{k: v for k, v in case.items() if k != "plan"})
     buf = _buffers(w, score_flags=flags)
     n, d = w.budgets[0], w.d
     buf.k_idx.copy_(torch.arange(n, dtype=torch.int32).expand(1, w.n_kv, n))
