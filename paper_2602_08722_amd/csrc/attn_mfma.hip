@@ -73,15 +73,6 @@ __device__ __forceinline__ uint32_t bf16_pair(float lo, float hi) {
   return __builtin_bit_cast(uint32_t, p);
 }
 
-// LDS[m0 + lane * 16 .. + 16] <- 16 bytes at base + voff (per lane); completion is counted by vmcnt
-__device__ __forceinline__ void dma16(const char* base, uint32_t voff, uint32_t lds_addr) {
-  asm volatile("s_mov_b32 m0, %0\n\ts_nop 0\n\tglobal_load_lds_dwordx4 %1, %2" ::"s"(lds_addr), "v"(voff), "s"(base)
-               : "memory", "m0");
-}
-template <int N>
-__device__ __forceinline__ void wait_vmcnt() {
-  asm volatile("s_waitcnt vmcnt(%0)" ::"n"(N) : "memory");
-}
 template <int D>
 __device__ __forceinline__ int k_swizzle(int row) { return D == 128 ? row & 3 : (row >> 1) & 3; }
 template <int D>
@@ -323,7 +314,7 @@ __global__ __launch_bounds__(2 * kSetThreads, 2) void attn_bf16(Dims dm, AttnArg
     for (int v = 0; v < 16; ++v) o[c][v] = 0.f;
   float m_run = -INFINITY;   // running row max, in the scaled log2 domain
   float l_run = 0.f;         // this half wave's share of the running row sum
-  // The reference point m_run only moves when a unit's maximum exceeds it by more than 2^kLazy: exp2(s - m_run) then stays below
+  // The reference point m_run only moves when a unit's maximum exceeds it by more than kLazy (in the log2 domain): exp2(s - m_run) then stays below
   // 2^kLazy, and rescaling the accumulators becomes rare.  `moves_above` is what a maximum is compared with (XS: in the scaled log2
   // domain, else relative to the reference point): any score at all moves a row that has none yet.
   constexpr float kLazy = 8.0f;

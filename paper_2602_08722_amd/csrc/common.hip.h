@@ -189,6 +189,16 @@ __device__ __forceinline__ void wave_fence() {
   __builtin_amdgcn_fence(__ATOMIC_ACQ_REL, "wavefront");
 }
 
+// LDS[m0 + lane * 16 .. + 16] <- 16 bytes at base + voff (per lane); completion is counted by vmcnt
+__device__ __forceinline__ void dma16(const char* base, uint32_t voff, uint32_t lds_addr) {
+  asm volatile("s_mov_b32 m0, %0\n\ts_nop 0\n\tglobal_load_lds_dwordx4 %1, %2" ::"s"(lds_addr), "v"(voff), "s"(base)
+               : "memory", "m0");
+}
+template <int N>
+__device__ __forceinline__ void wait_vmcnt() {
+  asm volatile("s_waitcnt vmcnt(%0)" ::"n"(N) : "memory");
+}
+
 // Exclusive prefix sum of one uint per thread over a block of NT threads (NT multiple of 64, <= 1024).
 // `wsum` is LDS scratch of at least NT/64 + 1 uints.  Returns the exclusive prefix; *total gets the block sum.
 template <int NT>

@@ -62,16 +62,6 @@ struct StreamCfg {
       (size_t)kStRing * STEP_B + (kSelBins / 2) * 4 + 2 * QB * kStKeys * 4 /*maxima*/ + 2 * QB * kStKeys * 4 /*norms*/;
 };
 
-// LDS[m0 + lane * 16 .. + 16] <- 16 bytes at base + voff (per lane); completion is counted by vmcnt
-__device__ __forceinline__ void dma16(const char* base, uint32_t voff, uint32_t lds_addr) {
-  asm volatile("s_mov_b32 m0, %0\n\ts_nop 0\n\tglobal_load_lds_dwordx4 %1, %2" ::"s"(lds_addr), "v"(voff), "s"(base)
-               : "memory", "m0");
-}
-template <int N>
-__device__ __forceinline__ void wait_vmcnt() {
-  asm volatile("s_waitcnt vmcnt(%0)" ::"n"(N) : "memory");
-}
-
 template <int D, int QB, StreamForm F>
 __global__ __launch_bounds__(stream_threads(F), 1) void score_stream(Dims dm, const float* __restrict__ qbar,
                                                              const uint16_t* __restrict__ kc,
