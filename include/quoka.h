@@ -225,9 +225,10 @@ quoka_status quoka_topk_keys_noalloc(const quoka_shape* shape, const float* scor
  *                     v_mfma_f32_32x32x16_bf16 (32768 flop each); sink: device float, never written in practice.
  *   quoka_probe_read  reads `bytes` (multiple of 16; src 16-byte aligned, device memory) once with coalesced
  *                     16-byte loads and writes nothing.
- *   quoka_probe_attn_mix  `blocks` blocks of 8 waves, each wave running `steps` steps of the bf16 attention kernel's
- *                     instruction mix without its memory side: 32 MFMAs (32768 flop each), 32 exponentials and about
- *                     160 plain vector operations per step, S first, then softmax and O.
+ *   quoka_probe_attn_mix  `blocks` blocks of 8 waves, each wave running `steps` steps of a plain flash-attention kernel on 32 rows
+ *                     without its memory side: 32 MFMAs (32768 flop each), 32 exponentials and about 160 plain vector
+ *                     operations per step, S first, then softmax and O.  (quoka_sparse_attn has about 105 and interleaves them:
+ *                     this is a rate to compare with, no bound.)
  *   quoka_probe_attn_plan  (host only, launches nothing) how quoka_sparse_attn (sparse != 0) or quoka_dense_attn would lay out the bf16
  *                     attention of this shape: row blocks of 32 query rows per block (8 or 4) and blocks that share a row block's
  *                     key list (1: none).  Both 0 where another kernel takes the call (float32; decode-sized chunks). */

@@ -861,7 +861,9 @@ static bool eight_row_blocks(const Dims& dm, bool sparse, long long groups) {
 // tokens over 0 - 20000 keys, at most 1024 row blocks).  On the other half the plans are behind the best of the measured ones, on the mean, by
 // 0.4 % (d 64) and 0.8 % (d 128) for 2 - 64 tokens, by 0.4 % for 33 - 3000 tokens and by 0.15 and 0.3 % for one sequence over few keys; 12 % for
 // single ones.  (Without the part beyond four splits, fitted to 33 tokens and more: 0.6, 1.1, 0.6 and 0.6 %, 20 %.)  Whole lists may take blocks of
-// eight where ragged row blocks make more than 256 blocks of four: 13 x 4 heads of 3, d 128, 187 tokens over 454 keys 34.3 -> 24.8 us.  But not
+// eight only where ragged row blocks make more than 256 blocks of four: 13 x 4 heads of 3, d 128, 187 tokens over 454 keys 34.3 -> 24.8 us.
+// (Elsewhere they gain up to 5 % on the shortest lists and cost precision: in blocks of four each wave set takes its own reference point, so that
+// two probabilities of a row are 1 and not rounded; 65 tokens over 130 keys lie 2.6 % further from float64 in blocks of eight.)  And not
 // in a batch with room for more than kRaggedKeys keys: its sequences may have fewer, and then the blocks beyond 256 are short ones that fill
 // gaps (13 x 4 heads of 3, without and with whole lists in blocks of eight: d 64, 174 tokens over 512 to 2616 keys 40 and 50 us, over 1868 each
 // 43 and 40; d 128, 171 tokens over 586 to 4688 keys 66 and 105, over 4688 each 133 and 108).
@@ -889,8 +891,8 @@ static AttnPlan attn_plan(const Dims& dm, bool sparse) {
     const long long blocks = heads * ((nrb + per_block - 1) / per_block);
     const int limit = key_splits_limit(dm, sparse, kt);
     const long long tiles = ((long long)attended_cap(dm, sparse) + kt - 1) / kt + (dm.C + kt - 1) / kt;
-    const bool no_whole = mode == 0 && dm.b > 1 && attended_cap(dm, sparse) > kRaggedKeys && heads * ((nrb + 3) / 4) > kComputeUnits;
-    for (int n = no_whole ? 2 : 1; n == 1 || (n <= limit && heads * nrb * n <= kMaxRecords); ++n) {
+    const bool whole = mode == 1 || (heads * ((nrb + 3) / 4) > kComputeUnits && (dm.b == 1 || attended_cap(dm, sparse) <= kRaggedKeys));
+    for (int n = whole ? 1 : 2; n == 1 || (n <= limit && heads * nrb * n <= kMaxRecords); ++n) {
       const Fit& f = n == 1 ? kWhole[wide][mode] : kSplit[wide][mode];
       const long long rounds = (blocks * n + kComputeUnits - 1) / kComputeUnits, steps = (tiles + n - 1) / n;
       const float mb = (float)(heads * nrb * n) * (float)(dm.d + 2) * 128e-6f;

@@ -3,12 +3,12 @@
 // against the published peaks.
 //   probe_mfma : register-only chains of v_mfma_f32_32x32x16_bf16, two waves per SIMD, no memory traffic.
 //   probe_read : every byte of a buffer read once with coalesced 16-byte loads, nothing written.
-//   probe_attn_mix : the instruction mix of the attention kernel's step without its memory side -- per wave and
+//   probe_attn_mix : a step of a plain flash-attention kernel without its memory side -- per wave and
 //                step 16 MFMAs in two chains (S = K Q^T), then 32 exponentials and about 160 plain vector
 //                operations (scaling, max, conversion to bf16) interleaved with 16 MFMAs in four chains (O += P V);
 //                eight waves per compute unit, no LDS traffic, no barriers, in program order: what a kernel of this work
 //                split (32 query rows per wave, two waves per SIMD) reaches if it forms S, then softmax and O.  (The
-//                attention kernel forms the next S under the softmax.)
+//                attention kernel forms the next S under the softmax and has about 105 vector operations: no bound on it.)
 #include "common.hip.h"
 #include "kernels.h"
 

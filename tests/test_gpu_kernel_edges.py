@@ -300,8 +300,8 @@ ROW_CASES = [
     dict(n_q=16, n_kv=2, d=128, chunk=8, kv_lens=[130], budgets=[129], plan=(4, 1)),
     dict(n_q=4, n_kv=2, d=64, chunk=31, kv_lens=[60], budgets=[50], plan=(4, 1)),          # 62, one head a row block
     dict(n_q=4, n_kv=2, d=64, chunk=97, kv_lens=[70], budgets=[65], plan=(4, 1)),
-    dict(n_q=14, n_kv=2, d=128, chunk=9, kv_lens=[60], budgets=[50], plan=(8, 1)),         # blocks of eight: whole, however few
-    dict(n_q=16, n_kv=2, d=128, chunk=8, kv_lens=[60], budgets=[50], plan=(8, 1)),
+    dict(n_q=14, n_kv=2, d=128, chunk=9, kv_lens=[60], budgets=[50], plan=(4, 1)),
+    dict(n_q=16, n_kv=2, d=128, chunk=8, kv_lens=[60], budgets=[50], plan=(4, 1)),
     dict(n_q=16, n_kv=2, d=128, chunk=2070, kv_lens=[3000], budgets=[2500], plan=(8, 1)),
     dict(n_q=16, n_kv=2, d=64, chunk=2070, kv_lens=[3000], budgets=[2500], plan=(8, 1)),   # (as the registers lie)
 ]
