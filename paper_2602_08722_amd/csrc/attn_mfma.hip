@@ -30,8 +30,8 @@
 // What bounds it: the loop alone (operands from LDS, nothing staged) keeps the matrix core busy for 73 % of its clocks, at
 // 1.73 of 2.4 GHz, the clock that the power limit leaves (1.27 PFLOP/s; without the operand reads 1.44, without the conversion and sum
 // of the probabilities 1.44).  Against two wave sets half a step apart, one forming S while the other ran softmax and P V behind
-// it (two barriers a tile, staging through registers), attention by itself, us: 32/8 heads, d 128, 4096 tokens over 8192 keys 627 -> 560
-// (1.23 PFLOP/s), 2048 over 3932 171 -> 148, 1024 over 983 37.2 -> 31.7, 1024 over all of 8192 159 -> 133; d 64, 1500 over 2400 70 -> 60.
+// it (two barriers a tile, staging through registers), attention by itself, us: 32/8 heads, d 128, 4096 tokens over 8192 keys 622 -> 551
+// (1.25 PFLOP/s), 2048 over 3932 172 -> 147, 1024 over 983 38.1 -> 31.7, 1024 over 8192 161 -> 135; d 64, 1500 over 2400 70 -> 59.
 #include "common.hip.h"
 #include "kernels.h"
 
@@ -108,7 +108,7 @@ struct AttnCfg {
 // XS (QUOKA_ATTN_SCALE_F32): the softmax scale is applied to the float32 products, one fused multiply-add per score
 // together with the subtraction of the reference point.  Otherwise the factor log2(e)/sqrt(d) is folded into the bf16 Q
 // operand once and the accumulator of K Q^T starts from minus the reference point, so that the matrix core hands back
-// what the exponential takes and no vector instruction is spent on either -- 2-9 % faster, at the price of rounding Q a
+// what the exponential takes and no vector instruction is spent on either -- 3-13 % faster, at the price of rounding Q a
 // second time: an error of the logits of relative size 2^-9, which shows in the output once the logits are several
 // times those of unit-variance inputs (0.03 absolute at four times, 0.06 at eight).
 // KSPLIT: the key list is shared by a.n_splits blocks, each of which writes a partial result.  (A template parameter: as
