@@ -314,9 +314,9 @@ __global__ __launch_bounds__(2 * kSetThreads, 2) void attn_bf16(Dims dm, AttnArg
     for (int v = 0; v < 16; ++v) o[c][v] = 0.f;
   float m_run = -INFINITY;   // running row max, in the scaled log2 domain
   float l_run = 0.f;         // this half wave's share of the running row sum
-  // The reference point m_run only moves when a unit's maximum exceeds it by more than kLazy (in the log2 domain): exp2(s - m_run) then stays below
-  // 2^kLazy, and rescaling the accumulators becomes rare.  `moves_above` is what a maximum is compared with (XS: in the scaled log2
-  // domain, else relative to the reference point): any score at all moves a row that has none yet.
+  // The reference point m_run only moves when a unit's maximum exceeds it by more than kLazy (in the log2 domain): exp2(s - m_run)
+  // then stays below 2^kLazy, and rescaling the accumulators becomes rare.  `moves_above` is what a maximum is compared with (XS: in the
+  // scaled log2 domain, else relative to the reference point): any score at all moves a row that has none yet.
   constexpr float kLazy = 8.0f;
   float moves_above = -INFINITY;
   // What the accumulator of K Q^T starts from.  !XS: -m_run in every entry, so the matrix core hands back s - m_run
@@ -433,8 +433,8 @@ __global__ __launch_bounds__(2 * kSetThreads, 2) void attn_bf16(Dims dm, AttnArg
     }
   };
   // Whether any row sees a key of the second unit of tile t: half of all row blocks end in the first unit of their last tile, and so do
-  // lists of up to 32 keys (32 heads, 20 tokens over 30 keys: d 64 7.3 -> 6.8 us, d 128 9.3 -> 8.3; 260 tokens alone, d 64 8.0 -> 7.6).  (Not asked where the list is shared: the time
-  // is that of a block whose tiles are full, and the question cost it 1 %.)
+  // lists of up to 32 keys (32 heads, 20 tokens over 30 keys: d 64 7.3 -> 6.8 us, d 128 9.3 -> 8.3; 260 tokens alone, d 64 8.0 -> 7.6).
+  // (Not asked where the list is shared: the time is that of a block whose tiles are full, and the question cost it 1 %.)
   auto both_units = [&](int t) __attribute__((always_inline)) {
     if constexpr (KSPLIT) return true;
     const int base = tile_base(t) + sub + 32;
@@ -841,8 +841,7 @@ static int key_splits_limit(const Dims& dm, bool sparse, int keys_per_tile) {
 // the rounds out (four: 1.03 at 385 - 416 groups, 1.08 - 1.13 beyond).
 // d 64: up to 256 groups it depends on how much of the list is the chunk's own, whose causal ranges blocks of four follow more closely; the
 // bound is a fit of the two times' difference, in us, to half of 1040 measured calls (0 - 6000 keys; with it they take 0.1 % more than the better
-// form, with eight throughout 2.8 %): 12/4 heads, 3203 tokens alone, eight 42.9, four 39.9; 32/8, 1064 over 3000 tokens 62
-// and 71.  Up to 384 groups four (0.74 - 0.88), up to 512 where the chunk is more than three fifths of the list (0.90 - 0.96; else
+// form, with eight throughout 2.8 %): 12/4 heads, 3203 tokens alone, eight 42.9, four 39.9; 32/8, 1064 tokens over 3000 keys 62 and 71.  Up to 384 groups four (0.74 - 0.88), up to 512 where the chunk is more than three fifths of the list (0.90 - 0.96; else
 // 1.01 - 1.07), beyond that eight.
 static bool eight_row_blocks(const Dims& dm, bool sparse, long long groups) {
   if (dm.b > 1) return groups >= kComputeUnits;
