@@ -63,3 +63,23 @@ def test_partials_fit_the_workspace_over_the_range_of_shapes():
                 longer = _shape(pk, batch=batch, n_q_heads=n_kv * g, n_kv_heads=n_kv, head_dim=d, chunk_len=min(8192, 2 * chunk),
                                 max_kv_len=t_max, max_budget=cap)
                 assert records * 32 * (d + 2) * 4 <= pk.quoka_workspace_bytes(longer)
+
+
+def _plan(n_q, n_kv, d, chunk, cap, batch=1):
+    return pk.quoka_probe_attn_plan(_shape(pk, batch=batch, n_q_heads=n_q, n_kv_heads=n_kv, head_dim=d, chunk_len=chunk, max_kv_len=cap,
+                                           max_budget=cap), False)
+
+
+@pytest.mark.parametrize("d", [64, 128])
+def test_whole_lists_take_the_block_form_of_their_size(d):
+    # few row blocks: four; eight only where blocks of four are more than 256 (260 and 312 here), and in a batch only with room for few keys
+    assert _plan(8, 2, d, 65, 130) == (4, 1) and _plan(14, 2, d, 9, 60) == (4, 1)
+    assert _plan(12, 4, d, 187, 454, batch=13) == (8, 1)
+    assert _plan(12, 4, d, 174, 2616, batch=13)[0] == 4 and _plan(8, 8, d, 279, 2251, batch=13)[0] == 4
+    # more than 1024 row blocks: a batch by the number of its groups of eight, one sequence by theirs and, at d 64, by whose keys they are
+    assert _plan(32, 8, d, 257, 3000, batch=7) == (8, 1) and _plan(32, 8, d, 160, 3000, batch=8) == (4, 1)
+    assert _plan(32, 8, d, 1064, 3000) == (8, 1)
+    assert _plan(12, 4, d, 3203, 1) == ((4 if d == 64 else 8), 1)
+    assert _plan(32, 8, d, 2240, 3000) == (4, 1)                                   # 280 groups
+    assert _plan(32, 8, d, 3500, 1) == ((4 if d == 64 else 8), 1)                  # 440 groups, the chunk's own keys
+    assert _plan(32, 8, d, 3500, 9000) == (8, 1) and _plan(32, 8, d, 4800, 1) == (8, 1)
