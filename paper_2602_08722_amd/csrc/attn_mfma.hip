@@ -78,6 +78,9 @@ __device__ __forceinline__ int k_swizzle(int row) { return D == 128 ? row & 3 : 
 template <int D>
 __device__ __forceinline__ int v_swizzle(int row) { return D == 128 ? 4 * (row & 3) : 4 * ((row >> 1) & 1); }
 
+template <int D>
+__device__ __forceinline__ int q_swizzle(int row) { return D == 128 ? row & 15 : (row >> 1) & 7; }
+
 template <int D, bool SPLIT>
 struct AttnCfg {
   static constexpr int KT = SPLIT ? 2 * kSub : kSub;  // keys per staged tile
@@ -101,7 +104,10 @@ struct AttnCfg {
   static constexpr int kKTileBytes = KT / RPW * KG;
   static constexpr int kStageBytes = kKTileBytes + KT / RPW * VG;   // one K tile and one V tile
   static constexpr size_t kOutBytes = (size_t)8 * 32 * (D + 8) * 2;   // what the rows go out through
-  static constexpr size_t kLdsBytes = (size_t)2 * kStageBytes > kOutBytes ? (size_t)2 * kStageBytes : kOutBytes;
+  static constexpr size_t kQBytes = SPLIT ? 0 : (size_t)8 * 32 * ROW;   // (SPLIT: in the place of a V tile)
+  static constexpr size_t kInBytes = (size_t)2 * kStageBytes + kQBytes;
+  static constexpr size_t kLdsBytes = kInBytes > kOutBytes ? kInBytes : kOutBytes;
+  static_assert(!SPLIT || KT / RPW * VG == 4 * 32 * ROW, "the rows of four row blocks in the place of a V tile");
   static constexpr int kRecFloats = 32 * (D + 2);     // partial of a row block: O as the registers lie, m, l
 };
 
@@ -134,6 +140,13 @@ __global__ __launch_bounds__(2 * kSetThreads, 2) void attn_bf16(Dims dm, AttnArg
   int b = dm.prompt_chunks ? dm.b - 1 - (int)blockIdx.z : (int)blockIdx.z;
   if (dm.b > 1 && dm.b <= kWave && !dm.prompt_chunks)
     b = seq_of_rank(sparse ? a.n_cache + kv : a.n_cache, sparse ? dm.n_kv : dm.ls, dm.b, blockIdx.z);
+  // The list's length and the arguments that the start needs, fetched together: one by one, where each is first used, they are four fetches
+  // in a row.
+  const int n_given = a.n_cache[sparse ? b * dm.n_kv + kv : b * dm.ls];
+  asm volatile("" ::"s"(dm.g), "s"(dm.C), "s"(dm.T_max), "s"(dm.B_max), "s"(dm.C_last),
+               "s"(dm.qs[0]), "s"(dm.qs[1]), "s"(dm.qs[2]), "s"(dm.kvs[0]), "s"(dm.kvs[1]), "s"(dm.kvs[2]), "s"(dm.cks[0]), "s"(dm.cks[1]),
+               "s"(dm.cks[2]), "s"(a.q), "s"(a.k_cache), "s"(a.v_cache), "s"(a.k_chunk), "s"(a.v_chunk), "s"(a.k_idx), "s"(a.n_cache), "s"(a.adjacent),
+               "s"(a.inv_g));
   const int tid = threadIdx.x % kSetThreads, lane = tid & 63;                 // position inside the wave set
   // wave-uniform values are pinned to scalar registers so that everything derived from them (tile kind, base
   // pointers, branches) stays scalar too
@@ -148,7 +161,7 @@ __global__ __launch_bounds__(2 * kSetThreads, 2) void attn_bf16(Dims dm, AttnArg
   // row block.  Otherwise set 0 is front, set 1 back.
   const int slot = SPLIT ? (w + 2 * set) % 4 : w + 4 * set;
   const bool back = SPLIT ? slot >= 2 : set == 1;
-  const int yb = KSPLIT ? (int)blockIdx.y / a.n_splits : (int)blockIdx.y;   // group of row blocks
+  const int yb = KSPLIT ? (int)((blockIdx.y * a.inv_splits) >> 16) : (int)blockIdx.y;   // group of row blocks
   const int split = KSPLIT ? (int)blockIdx.y - yb * a.n_splits : 0;                               // share of its key list
   const int kf = yb * HW + slot % HW;
   // Row blocks of a block.  Paired (a launch of one round): half from the front of the list, half from the back, so all
@@ -158,23 +171,82 @@ __global__ __launch_bounds__(2 * kSetThreads, 2) void attn_bf16(Dims dm, AttnArg
   const bool adjacent = a.adjacent != 0;
   const int x = adjacent ? nrb - 1 - (yb * 2 * HW + slot) : (back ? nrb - 1 - kf : kf);
   const bool wave_on = adjacent ? x >= 0 : (back ? (x >= half) : (x < half));
-  const int xj = wave_on ? x % g : 0;
-  const int tok0 = wave_on ? (x / g) * 32 : 0;
+  const int xt = wave_on ? (int)((uint32_t)x * a.inv_g >> 16) : 0;   // x / g
+  const int xj = wave_on ? x - xt * g : 0;
+  const int tok0 = xt * 32;
   const int h = kv * g + xj;
   const int xb_hi = nrb - 1 - yb * HW;                                     // the block's last row block
   const int x_hi = adjacent ? nrb - 1 - yb * 2 * HW
                             : (xb_hi >= half ? xb_hi : min(yb * HW + HW - 1, half - 1));
   if (adjacent ? x_hi < 0 : yb * HW >= half) return;   // a short chunk has no row blocks here (block-uniform)
-  const int c_end_blk = min((x_hi / g) * 32 + 32, C);   // chunk keys any wave of this block can see
+  const int c_end_blk = min((int)((uint32_t)x_hi * a.inv_g >> 16) * 32 + 32, C);   // chunk keys any wave of this block can see
   const int sub = SPLIT ? set * kSub : 0;               // first key of this set's share of a staged tile
 
-  int n_cache;
-  if (sparse) {
-    n_cache = min(a.n_cache[b * dm.n_kv + kv], dm.B_max);
-  } else {
-    n_cache = min(a.n_cache[b * dm.ls], dm.T_max);
+  // The tensor this set stages (set 0: K, set 1: V) for this (batch, KV head), as byte pointers: every row is
+  // addressed as base + 32-bit byte offset (the host checks that a head's rows span less than 4 GiB).
+  const void* cache_t = set == 0 ? a.k_cache : a.v_cache;
+  const void* chunk_t = set == 0 ? a.k_chunk : a.v_chunk;
+  const char* cache_base = reinterpret_cast<const char*>(static_cast<const uint16_t*>(cache_t) + b * dm.kvs[0] + kv * dm.kvs[1]);
+  const char* chunk_base = reinterpret_cast<const char*>(static_cast<const uint16_t*>(chunk_t) + b * dm.cks[0] + kv * dm.cks[1]);
+  const char* kidx = sparse ? reinterpret_cast<const char*>(a.k_idx + (size_t)(b * dm.n_kv + kv) * dm.B_max) : nullptr;
+  const uint32_t cache_row_bytes = (uint32_t)dm.kvs[2] * 2u, chunk_row_bytes = (uint32_t)dm.cks[2] * 2u;
+  // Staging.  Thread (r0, cg) fetches slot cg of rows r0 + RPI * k of this set's tensor, k < NLD: a load of a wave fills a group.
+  // Source rows of a tile are looked up a step ahead of the loads that use them, so the dependent index -> row fetch of the gather
+  // never sits on the critical path.  At d 128 the 16 lanes that carry a row look up NLD rows between them, one each, and take
+  // them from each other where they are used: one register instead of NLD.
+  constexpr bool kShare = CG == 16;
+  constexpr int NI = kShare ? 1 : NLD;
+  const int r0 = tid / CG;
+  const uint32_t cg_src = (uint32_t)(tid % CG ^ (set == 0 ? k_swizzle<D>(lane / CG) : v_swizzle<D>(lane / CG))) * 16u;
+  const uint32_t idx_max = (uint32_t)max(dm.T_max - 1, 0);
+  uint32_t src[NI];     // rows of the tile to be requested next, as looked up
+  uint32_t off[NI];     // the same as byte offsets, of the tile being requested
+  u32x4 R[DMA ? 1 : NLD];   // the tile in flight (not DMA)
+  const char* req_base = nullptr;   // of the tile being requested
+  const uint32_t lds0 = (uint32_t)(uintptr_t)(__attribute__((address_space(3))) void*)smem;
+  const uint32_t group_mine = set == 0 ? Cfg::KG : Cfg::VG;
+  const uint32_t dst_mine = lds0 + (set == 0 ? 0u : (uint32_t)Cfg::kKTileBytes) + (uint32_t)w * group_mine;
+  auto stage_of = [&](int t) __attribute__((always_inline)) { return (t & 1) * Cfg::kStageBytes; };
+  auto request = [&](int t, int k) __attribute__((always_inline)) {   // chunk k of tile t
+    const uint32_t o = kShare ? row16_lane(off[0], k) + cg_src : off[k % NI];
+    if constexpr (DMA) dma16(req_base, o, dst_mine + (uint32_t)stage_of(t) + 4u * k * group_mine);
+    else R[k] = *reinterpret_cast<const u32x4*>(req_base + o);
+  };
+  auto q_area = [&](int t_first) __attribute__((always_inline)) {
+    return lds0 + (uint32_t)(SPLIT ? stage_of(t_first + 1) + Cfg::kKTileBytes : 2 * Cfg::kStageBytes);
+  };
+  // A block's start is a chain of fetches, in a launch of many rounds one for every round, so what does not wait for the list's length
+  // leaves at once: the list's first entries, the chunk's first tile and the queries.  The entries are looked up for a list that fills its
+  // first tile, and again where it does not.  (Length, queries, entries and tile one after the other took 5.2 us to the first product in 32/8 heads,
+  // 1024 tokens over 983 keys, now 3.8, of which 1.3 until the arguments are there.  Attention by itself, 200 random calls of 2 - 4096 tokens:
+  // 0.95 of the time, d 128 0.96 - 0.92, d 64 0.99 - 0.96; 54 tokens over 132 keys 10.8 -> 9.5 us, 573 over 2084 37.6 -> 35.4.)
+  if constexpr (!KSPLIT) {
+    if (sparse) {
+#pragma unroll
+      for (int i = 0; i < NI; ++i)
+        src[i] = *reinterpret_cast<const uint32_t*>(kidx + (uint32_t)min(r0 + RPI * (kShare ? lane % NLD : i), max(dm.B_max - 1, 0)) * 4u);
+    }
+    req_base = chunk_base;
+#pragma unroll
+    for (int i = 0; i < NI; ++i)
+      off[i] = (uint32_t)min(r0 + RPI * (kShare ? lane % NLD : i), C - 1) * chunk_row_bytes + (kShare ? 0u : cg_src);
+#pragma unroll
+    for (int k = 0; k < NLD; ++k) request(-1, k);
   }
-  n_cache = max(n_cache, 0);
+  // Q goes through LDS too, in whole rows.  (As operands a load takes 16 bytes of each of 64 lines: 1.7 us for a block's.)
+  // SPLIT: the two waves of a slot fetch half of its rows each, to where V of the second tile goes later.
+  auto request_q = [&](uint32_t area) __attribute__((always_inline)) {
+    constexpr int N = 32 / Cfg::RPW / (SPLIT ? 2 : 1);
+    const uint16_t* qhead = static_cast<const uint16_t*>(a.q) + b * dm.qs[0] + h * dm.qs[1];
+#pragma unroll
+    for (int i = 0; i < N; ++i) {
+      const int r = ((SPLIT ? set * N : 0) + i) * Cfg::RPW + lane / CG;
+      const uint16_t* p = qhead + (size_t)min(tok0 + r, C - 1) * dm.qs[2] + (lane % CG ^ q_swizzle<D>(r)) * 8;
+      dma16(p, area + slot * (32 * Cfg::ROW) + (uint32_t)((SPLIT ? set * N : 0) + i) * 1024u);
+    }
+  };
+  if constexpr (!KSPLIT) request_q(q_area(-1));
+  const int n_cache = max(min(n_given, sparse ? dm.B_max : dm.T_max), 0);
   // Tile order: the chunk's first tile, the cache tiles, the chunk's other tiles.  What a wave can see is one run of tiles [w0, w1), whose
   // end is where its causal range ends; the first tile needs no index look-up, so its loads leave right at kernel start; and every row
   // of a chunk sees all of it, but for the first rows, so that the reference point taken from it (below) is a maximum over as many keys
@@ -185,8 +257,8 @@ __global__ __launch_bounds__(2 * kSetThreads, 2) void attn_bf16(Dims dm, AttnArg
   const int n_ct = (n_cache + KT - 1) / KT;
   const int n_tiles = n_cht + n_ct;
   // Tiles are numbered from -1, so that the cache tiles are 0 .. n_ct - 1.
-  const int t_begin = (KSPLIT ? (int)((long long)n_tiles * split / a.n_splits) : 0) - 1;
-  const int t_end = (KSPLIT ? (int)((long long)n_tiles * (split + 1) / a.n_splits) : n_tiles) - 1;
+  const int t_begin = (KSPLIT ? (int)((uint32_t)n_tiles * (uint32_t)split / (uint32_t)a.n_splits) : 0) - 1;   // (at most 2^19 tiles, 32 shares)
+  const int t_end = (KSPLIT ? (int)((uint32_t)n_tiles * (uint32_t)(split + 1) / (uint32_t)a.n_splits) : n_tiles) - 1;
   auto is_cache = [&](int t) __attribute__((always_inline)) { return (uint32_t)t < (uint32_t)n_ct; };
   // first key (cache slot or chunk position) of tile t
   auto tile_base = [&](int t) __attribute__((always_inline)) { return (is_cache(t) ? t : max(t - (n_ct - 1), 0)) * KT; };
@@ -205,73 +277,43 @@ __global__ __launch_bounds__(2 * kSetThreads, 2) void attn_bf16(Dims dm, AttnArg
   w1 = min(w1, t_end);
   if (!wave_on || w0 >= w1) w0 = w1 = t_end + 1;   // sees nothing: stages its part of the tiles only
 
-  const uint16_t* qg = static_cast<const uint16_t*>(a.q);
-  // The tensor this set stages (set 0: K, set 1: V) for this (batch, KV head), as byte pointers: every row is
-  // addressed as base + 32-bit byte offset (the host checks that a head's rows span less than 4 GiB).
-  const void* cache_t = set == 0 ? a.k_cache : a.v_cache;
-  const void* chunk_t = set == 0 ? a.k_chunk : a.v_chunk;
-  const char* cache_base = reinterpret_cast<const char*>(static_cast<const uint16_t*>(cache_t) + b * dm.kvs[0] + kv * dm.kvs[1]);
-  const char* chunk_base = reinterpret_cast<const char*>(static_cast<const uint16_t*>(chunk_t) + b * dm.cks[0] + kv * dm.cks[1]);
-  const char* kidx = sparse ? reinterpret_cast<const char*>(a.k_idx + (size_t)(b * dm.n_kv + kv) * dm.B_max) : nullptr;
-  const uint32_t cache_row_bytes = (uint32_t)dm.kvs[2] * 2u, chunk_row_bytes = (uint32_t)dm.cks[2] * 2u;
-  // Q operand: row tok0 + li, chunk ks + KS*hf of 8 dims
-  bf16x8 qreg[KS];
-  {
-    const int tokq = min(tok0 + li, C - 1);
-    const uint16_t* qrow = qg + b * dm.qs[0] + h * dm.qs[1] + (size_t)tokq * dm.qs[2] + 8 * KS * hf;
-#pragma unroll
-    for (int ks = 0; ks < KS; ++ks) qreg[ks] = *reinterpret_cast<const bf16x8*>(qrow + ks * 8);
-  }
-  // the softmax scale and the change to base 2
-  const float qscale = 1.4426950408889634f / sqrtf((float)D);
-  if constexpr (!XS) {   // into Q once, so K Q^T arrives in the exponent's own units
-#pragma unroll
-    for (int ks = 0; ks < KS; ++ks)
-#pragma unroll
-      for (int e = 0; e < 8; ++e) qreg[ks][e] = (__bf16)((float)qreg[ks][e] * qscale);
-  }
-
-  // Staging.  Thread (r0, cg) fetches slot cg of rows r0 + RPI * k of this set's tensor, k < NLD: a load of a wave fills a group.
-  // Source rows of a tile are looked up a step ahead of the loads that use them, so the dependent index -> row fetch of the gather
-  // never sits on the critical path.  At d 128 the 16 lanes that carry a row look up NLD rows between them, one each, and take
-  // them from each other where they are used: one register instead of NLD.
-  constexpr bool kShare = CG == 16;
-  constexpr int NI = kShare ? 1 : NLD;
-  const int r0 = tid / CG;
-  const uint32_t cg_src = (uint32_t)(tid % CG ^ (set == 0 ? k_swizzle<D>(lane / CG) : v_swizzle<D>(lane / CG))) * 16u;
-  const uint32_t idx_max = (uint32_t)max(dm.T_max - 1, 0);
-  uint32_t src[NI];     // rows of the tile to be requested next, as looked up
-  uint32_t off[NI];     // the same as byte offsets, of the tile being requested
-  u32x4 R[DMA ? 1 : NLD];   // the tile in flight (not DMA)
+  // Source rows of tile t.  kShare: only entries of the list are fetched, for a chunk tile too (some entry, which is not used), and other
+  // rows are worked out where they are requested: as a choice between a fetch and a number the value changes registers, and the step
+  // that asks for an entry waits for it.  (d 64 keeps either: the vector unit sets the pace there.)
+  const int list_last = max(n_cache - 1, 0);
+  auto row_of = [&](int t, int i) __attribute__((always_inline)) {   // tail slots repeat a real row
+    return (uint32_t)min(tile_base(t) + r0 + RPI * (kShare ? lane % NLD : i), (is_cache(t) ? n_cache : C) - 1);
+  };
   auto look_up = [&](int t) __attribute__((always_inline)) {
     t = min(t, t_end - 1);   // (past the list's end the last tile is requested again, and nothing reads it)
-    const bool cache = is_cache(t);
-    const int base = tile_base(t), last = cache ? n_cache - 1 : C - 1;
+    if constexpr (kShare) {
+      if (!sparse) return;
+      src[0] = *reinterpret_cast<const uint32_t*>(kidx + (uint32_t)min(max(t, 0) * KT + r0 + RPI * (lane % NLD), list_last) * 4u);
+    } else {
+      const bool cache = is_cache(t);
+      const int base = tile_base(t), last = cache ? n_cache - 1 : C - 1;
 #pragma unroll
-    for (int i = 0; i < NI; ++i)   // tail slots repeat a real row
-      src[i] = (uint32_t)min(base + r0 + RPI * (kShare ? lane % NLD : i), last);
-    if (cache && sparse) {
+      for (int i = 0; i < NI; ++i) src[i] = (uint32_t)min(base + r0 + RPI * i, last);
+      if (cache && sparse) {
 #pragma unroll
-      for (int i = 0; i < NI; ++i) src[i] = *reinterpret_cast<const uint32_t*>(kidx + src[i] * 4u);
+        for (int i = 0; i < NI; ++i) src[i] = *reinterpret_cast<const uint32_t*>(kidx + src[i] * 4u);
+      }
     }
   };
-  const char* req_base = nullptr;   // of the tile being requested
+  // (the clamp to the cache extent: a malformed list, negative or too large, cannot leave the tensor)
   auto address = [&](int t) __attribute__((always_inline)) {
-    const bool cache = is_cache(min(t, t_end - 1));
+    t = min(t, t_end - 1);
+    const bool cache = is_cache(t);
     req_base = cache ? cache_base : chunk_base;
-    // Cache rows are clamped to the cache extent: a malformed list (negative or too large) cannot leave the tensor.
-    const uint32_t row_bytes = cache ? cache_row_bytes : chunk_row_bytes, row_max = cache ? idx_max : 0xffffffffu;
+    const uint32_t row_bytes = cache ? cache_row_bytes : chunk_row_bytes;
+    if constexpr (kShare) {
+      if (cache && sparse) off[0] = min(src[0], idx_max) * cache_row_bytes;
+      else off[0] = row_of(t, 0) * row_bytes;
+    } else {
+      const uint32_t row_max = cache ? idx_max : 0xffffffffu;
 #pragma unroll
-    for (int i = 0; i < NI; ++i) off[i] = min(src[i], row_max) * row_bytes + (kShare ? 0u : cg_src);
-  };
-  const uint32_t lds0 = (uint32_t)(uintptr_t)(__attribute__((address_space(3))) void*)smem;
-  const uint32_t group_mine = set == 0 ? Cfg::KG : Cfg::VG;
-  const uint32_t dst_mine = lds0 + (set == 0 ? 0u : (uint32_t)Cfg::kKTileBytes) + (uint32_t)w * group_mine;
-  auto stage_of = [&](int t) __attribute__((always_inline)) { return (t & 1) * Cfg::kStageBytes; };
-  auto request = [&](int t, int k) __attribute__((always_inline)) {   // chunk k of tile t
-    const uint32_t o = kShare ? row16_lane(off[0], k) + cg_src : off[k % NI];
-    if constexpr (DMA) dma16(req_base, o, dst_mine + (uint32_t)stage_of(t) + 4u * k * group_mine);
-    else R[k] = *reinterpret_cast<const u32x4*>(req_base + o);
+      for (int i = 0; i < NI; ++i) off[i] = min(src[i], row_max) * row_bytes + cg_src;
+    }
   };
   auto store = [&](int t, int k, u32x4 r) __attribute__((always_inline)) {   // (not DMA)
     *(u32x4 __attribute__((address_space(3)))*)(uintptr_t)(dst_mine + lane * 16u + (uint32_t)stage_of(t) + 4u * k * group_mine) = r;
@@ -282,30 +324,51 @@ __global__ __launch_bounds__(2 * kSetThreads, 2) void attn_bf16(Dims dm, AttnArg
     request(DMA ? j + 2 - set : j + 3 - set, k);
   };
 
-  if (t_begin < t_end) {   // (a split without tiles contributes the neutral partial)
-    look_up(t_begin);      // (the first one is a chunk tile, the chunk is never empty: no index, no cache length)
+  if constexpr (!KSPLIT) {
+    if (n_cache < KT || (!kShare && !sparse)) look_up(0);
+  } else if (t_begin < t_end) {   // (a split without tiles contributes the neutral partial)
+    request_q(q_area(t_begin));
+    look_up(t_begin);
     address(t_begin);
     look_up(t_begin + 1);
 #pragma unroll
     for (int k = 0; k < NLD; ++k) request(t_begin, k);
-    if (set == 0) {   // K runs one tile ahead of V
-      u32x4 first[DMA ? 1 : NLD];
-      if constexpr (!DMA) {
+  }
+  if (t_begin < t_end && set == 0) {   // K runs one tile ahead of V
+    u32x4 first[DMA ? 1 : NLD];
+    if constexpr (!DMA) {
 #pragma unroll
-        for (int k = 0; k < NLD; ++k) first[k] = R[k];
-      }
-      if (t_begin + 1 < t_end) {
-        address(t_begin + 1);
-        look_up(t_begin + 2);
+      for (int k = 0; k < NLD; ++k) first[k] = R[k];
+    }
+    if (t_begin + 1 < t_end) {
+      address(t_begin + 1);
+      look_up(t_begin + 2);
 #pragma unroll
-        for (int k = 0; k < NLD; ++k) request(t_begin + 1, k);
-      }
-      if constexpr (!DMA) {
+      for (int k = 0; k < NLD; ++k) request(t_begin + 1, k);
+    }
+    if constexpr (!DMA) {
 #pragma unroll
-        for (int k = 0; k < NLD; ++k) store(t_begin, k, first[k]);
-      }
+      for (int k = 0; k < NLD; ++k) store(t_begin, k, first[k]);
     }
   }
+  // the first tile and the queries have arrived (K of the second tile may be on its way)
+  if (set == 0 && t_begin + 1 < t_end) wait_vmcnt<NLD>();
+  else wait_vmcnt<0>();
+  __syncthreads();
+  // Q operand: row tok0 + li, chunk ks + KS*hf of 8 dims
+  bf16x8 qreg[KS];
+#pragma unroll
+  for (int ks = 0; ks < KS; ++ks)
+    qreg[ks] = *(const bf16x8 __attribute__((address_space(3)))*)(uintptr_t)(q_area(t_begin) + slot * (32 * Cfg::ROW) + li * Cfg::ROW + ((ks + KS * hf) ^ q_swizzle<D>(li)) * 16);
+  // the softmax scale and the change to base 2
+  const float qscale = 1.4426950408889634f / sqrtf((float)D);
+  if constexpr (!XS) {   // into Q once, so K Q^T arrives in the exponent's own units
+#pragma unroll
+    for (int ks = 0; ks < KS; ++ks)
+#pragma unroll
+      for (int e = 0; e < 8; ++e) qreg[ks][e] = (__bf16)((float)qreg[ks][e] * qscale);
+  }
+
 
   f32x16 o[DB];
 #pragma unroll
@@ -476,16 +539,16 @@ __global__ __launch_bounds__(2 * kSetThreads, 2) void attn_bf16(Dims dm, AttnArg
   // can be the first is settled when it is compiled: asked in every step, and with a second tile requested and waited for where a block has
   // only one, d 64 was 2 % slower on the mean of 2000 calls, d 128 1 %; 8 KV heads of 4, d 128, 1074 tokens over 3487 keys 96.1 -> 92.8 us.)
   auto begin_step = [&](int j, auto can_be_first) __attribute__((always_inline)) {
+    const bool first = decltype(can_be_first)::value && j < t_begin;   // (its barrier is the one above)
     if constexpr (DMA) {
-      if (decltype(can_be_first)::value && j < t_begin) {   // (its tiles are on their way; K of the first one has to be there)
-        if (t_begin + 1 < t_end) wait_vmcnt<NLD>();
-        else wait_vmcnt<0>();
-        __syncthreads();
-        return;
-      }
+      if (first) return;
       wait_vmcnt<0>();
     }
-    __syncthreads();
+    if (!first) __syncthreads();
+    if constexpr (!kShare) {   // (or the new entries are waited for, to be moved to where these are)
+#pragma unroll
+      for (int i = 0; i < NI; ++i) asm volatile("" : "+v"(src[i]));
+    }
     address(DMA ? j + 2 - set : j + 3 - set);
     look_up(DMA ? j + 3 - set : j + 4 - set);
   };
@@ -798,6 +861,8 @@ static hipError_t launch_variant(const Dims& dm, const AttnArgs& a, hipStream_t 
   // one block is resident per compute unit: from two rounds on, neighbouring row blocks and longest ranges first
   // (measured at 512 blocks, 4096-token chunk over 131072 cached tokens: 3.5 % faster than pairing; a launch of one
   // round needs the pairing, or its last block sets the time alone)
+  aa.inv_g = (65536u + dm.g - 1) / dm.g;
+  aa.inv_splits = (65536u + a.n_splits - 1) / a.n_splits;
   aa.adjacent = (long long)grid.x * grid.y * grid.z >= 2 * kComputeUnits ? 1 : 0;
   hipLaunchKernelGGL((attn_bf16<D, SPLIT, XS, KSPLIT, WHOLE>), grid, dim3(2 * kSetThreads), lds, st, dm, aa);
   if (KSPLIT) {

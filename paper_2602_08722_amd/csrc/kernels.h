@@ -93,6 +93,8 @@ struct AttnArgs {
   // set by the launcher of the bf16 kernel:
   int adjacent = 0;        // row-block assignment (paired or adjacent)
   int n_splits = 1;        // blocks that share a row block's key list
+  // 2^16 / g and 2^16 / n_splits, rounded up: x * inv >> 16 is the quotient for x < 4096 (row blocks, g <= 16) and x < 2048 (blocks, n_splits <= 32)
+  uint32_t inv_g = 0, inv_splits = 0;
   float* part = nullptr;   // their partial results
 };
 // the most cache rows any sequence of the call attends

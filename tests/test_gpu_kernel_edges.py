@@ -325,6 +325,45 @@ def test_bf16_attention_rows_of_whole_lists(case, scale_f32):
     assert torch.equal(wide[..., :d], buf.out) and bool((wide[..., d:] == 7.0).all())
 
 
+# a block's first fetches leave before the list's length is known: lists that fill their first tile, one short of it, and empty, in
+# arrays whose unused entries are out of range, in every form of the kernel and with queries whose tokens lie apart
+@pytest.mark.parametrize("scale_f32", [False, True], ids=["", "scale-f32"])
+@pytest.mark.parametrize("d", [64, 128])
+@pytest.mark.parametrize("case,counts", [
+    (dict(n_q=16, n_kv=2, chunk=9, kv_lens=[200], budgets=[129], plan=(4, 1)), [129, 128, 127, 65, 1, 0]),
+    (dict(n_q=16, n_kv=2, chunk=2070, kv_lens=[3000], budgets=[2500], plan=(8, 1)), [2500, 65, 64, 63, 1, 0]),
+    (dict(n_q=14, n_kv=2, chunk=40, kv_lens=[3000], budgets=[2500], plan=None), [2500, 129, 127, 64, 1, 0]),   # shared lists
+], ids=["four", "eight", "shared"])
+def test_bf16_attention_lists_shorter_than_their_array(case, counts, d, scale_f32):
+    case = dict(case)
+    plan, chunk = case.pop("plan"), case["chunk"]
+    w = gen.make_custom(dtype="bf16", d=d, n_retain=8, batch=1, seed=4, **case)
+    buf = _buffers(w, score_flags=16 if scale_f32 else 0)
+    got = _pk().quoka_probe_attn_plan(buf.shape, True)
+    assert got == plan if plan else got[1] > 1, got
+    apart = torch.full((1, w.n_q, chunk, d + 8), float("nan"), dtype=torch.bfloat16, device="cuda:0")
+    apart[..., :d] = buf.q
+    buf.q = apart[..., :d]
+    buf.shape.q_stride[:] = buf.q.stride()[:3]
+    rows = sorted({0, 1, chunk // 2, chunk - 1})
+    rng = np.random.default_rng(d)
+    n_most, n_keys = w.budgets[0], w.kv_lens[0]
+    for n in counts:
+        lists = np.stack([np.sort(rng.choice(n_keys, size=n, replace=False)) for _ in range(w.n_kv)]).astype(np.int32)
+        host = np.full(tuple(buf.k_idx.shape), 0x7FFFFFFF, dtype=np.int32)
+        host[0, :, n:n_most:2] = -1
+        host[0, :, :n] = lists
+        buf.k_idx.copy_(torch.from_numpy(host))
+        buf.k_cnt.fill_(n)
+        buf.out.fill_(float("nan"))
+        buf.sparse_attn()
+        torch.cuda.synchronize()
+        out = gen.from_torch(buf.out[0])
+        assert not np.isnan(out).any()
+        want = O.sparse_attn(w.Q[0], w.K[0], w.V[0], lists, w.Kc[0], w.Vc[0], rows=rows)
+        assert P.max_abs(out[:, rows], want) <= P.TOL_OUT["bf16"], n
+
+
 # decode kernel: single slots, tiles of 32 short of and past full, fewer tiles than waves or blocks, batches whose shares
 # of the blocks differ, batches beyond one wave's lanes
 DECODE_CASES = [
