@@ -16,6 +16,8 @@ import torch
 QUOKA_F32 = 0
 QUOKA_BF16 = 1
 
+_raw_stream = getattr(torch._C, "_cuda_getCurrentRawStream", None)
+
 _LIB_NAME = "libquoka.so"
 _lib: Optional[ctypes.CDLL] = None
 
@@ -93,13 +95,18 @@ def _check(fn: str, status: int) -> None:
         raise QuokaError(fn, status, load_library().quoka_status_string(status).decode())
 
 
+# A call marshals up to 17 arguments, which is a third of what enqueuing four launches takes: plain integers (the entry points'
+# argtypes turn them into pointers) and the current stream's handle without a Stream object around it.
 def _ptr(t: Optional[torch.Tensor]):
-    return None if t is None else ctypes.c_void_p(t.data_ptr())
+    return None if t is None else t.data_ptr()
 
 
-def _stream(stream) -> ctypes.c_void_p:
-    s = torch.cuda.current_stream() if stream is None else stream
-    return ctypes.c_void_p(s.cuda_stream)
+def _stream(stream):
+    if stream is not None:
+        return stream.cuda_stream
+    if _raw_stream is None:
+        return torch.cuda.current_stream().cuda_stream
+    return _raw_stream(torch.cuda.current_device())
 
 
 def _strides3(t: torch.Tensor):

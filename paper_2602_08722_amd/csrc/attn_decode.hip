@@ -134,8 +134,9 @@ __global__ __launch_bounds__(kDcThreads, 2) void attn_decode_bf16(Dims dm, AttnA
     n_keys = n + C;
     const int tiles = (n_keys + kDcTile - 1) / kDcTile;
     if constexpr (ONE) work.n_splits = decode_splits_of_one(tiles, n_slots);
-    t_end = (int)((long long)tiles * (work.split + 1) / work.n_splits);
-    t = ONE && work.split >= work.n_splits ? t_end : (int)((long long)tiles * work.split / work.n_splits) + w;
+    // (at most 2^20 tiles and 64 shares; as 64-bit quotients they took 260 instructions ahead of the first fetch)
+    t_end = (int)((uint32_t)tiles * (uint32_t)(work.split + 1) / (uint32_t)work.n_splits);
+    t = ONE && work.split >= work.n_splits ? t_end : (int)((uint32_t)tiles * (uint32_t)work.split / (uint32_t)work.n_splits) + w;
   };
   const int n_given = decode_cache(dm, a, b, kv), n_most = min(dm.B_max, dm.T_max);
   share_out(ONE ? n_most : n_given);
@@ -153,26 +154,27 @@ __global__ __launch_bounds__(kDcThreads, 2) void attn_decode_bf16(Dims dm, AttnA
   const int cg = lane % CG, r0 = lane / CG;
   uint32_t src[NLD];        // list entries of the tile whose rows are fetched next
   u32x4 RK[NLD], RV[NLD];   // rows on the way
+  // (Every slot fetches an entry, also where it is a chunk row and has none: with a choice between an entry and the slot's own number, the
+  // fetches of a tile waited for each other two by two.)
   auto resolve = [&](int tt) __attribute__((always_inline)) {
+    if (!sparse) return;
 #pragma unroll
-    for (int i = 0; i < NLD; ++i) {
-      const int n = min(tt * kDcTile + r0 + RPI * i, n_keys - 1);   // tail slots repeat a real row; they are masked below
-      src[i] = (uint32_t)n;
-      if (sparse && n < n_cache) src[i] = (uint32_t)kidx[n];
-    }
+    for (int i = 0; i < NLD; ++i) src[i] = (uint32_t)kidx[max(min(tt * kDcTile + r0 + RPI * i, n_cache - 1), 0)];
   };
   auto issue = [&](int tt) __attribute__((always_inline)) {
 #pragma unroll
     for (int i = 0; i < NLD; ++i) {
       // addresses as integers (cache base, plus the distance to the chunk tensor for chunk rows): a per-lane choice
       // between two pointers would be kept as a table in scratch memory
-      const int n = min(tt * kDcTile + r0 + RPI * i, n_keys - 1);
+      const int n = min(tt * kDcTile + r0 + RPI * i, n_keys - 1);   // tail slots repeat a real row; they are masked below
       const bool from_cache = n < n_cache;
       // (the clamp: a malformed list cannot leave the cache)
-      const uint32_t row = from_cache ? min(src[i], (uint32_t)(dm.T_max - 1)) : (uint32_t)(n - n_cache);
+      const uint32_t row = from_cache ? (sparse ? min(src[i], (uint32_t)(dm.T_max - 1)) : (uint32_t)n) : (uint32_t)(n - n_cache);
       const uint64_t off = (uint64_t)(row * (from_cache ? cache_row_bytes : chunk_row_bytes) + (uint32_t)cg * 16u);
-      RK[i] = *reinterpret_cast<const u32x4*>(k_cache_u + (from_cache ? 0ull : k_chunk_delta) + off);
-      RV[i] = *reinterpret_cast<const u32x4*>(v_cache_u + (from_cache ? 0ull : v_chunk_delta) + off);
+      // (named as global memory: through generic pointers the products' LDS operands waited for the rows of the tile after)
+      typedef const u32x4 __attribute__((address_space(1))) * global_rows;
+      RK[i] = *(global_rows)(k_cache_u + (from_cache ? 0ull : k_chunk_delta) + off);
+      RV[i] = *(global_rows)(v_cache_u + (from_cache ? 0ull : v_chunk_delta) + off);
     }
   };
   if (t < t_end) resolve(t);

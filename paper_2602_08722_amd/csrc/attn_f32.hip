@@ -100,13 +100,16 @@ __global__ __launch_bounds__(kFaThreads, 2) void attn_f32(Dims dm, AttnArgs a, f
   const char* vchunk = reinterpret_cast<const char*>(static_cast<const float*>(a.v_chunk) + b * dm.cks[0] + kv * dm.cks[1]);
   const uint32_t cache_rb = (uint32_t)dm.kvs[2] * 4u, chunk_rb = (uint32_t)dm.cks[2] * 4u;
 
+  // The list's entry for slot li of unit u: fetched a unit ahead, before the unit's V rows (fetches arrive in order), and first used, and so
+  // waited for, behind the unit's first product.  (Looked up and turned into an offset in one place, the wave waited for it, and for all
+  // of its V rows, ahead of that product.)  A chunk unit and a dense call find some number, which is not used.
+  const int32_t* list = sparse ? kidx : a.n_cache;
+  const int list_last = sparse ? max(n_cache - 1, 0) : 0;
+  auto look_up = [&](int u) __attribute__((always_inline)) { return (uint32_t)list[min(u * 32 + li, list_last)]; };
   // byte offset of the row that slot li of unit u names (slots past the list repeat its last row; they are masked)
-  auto row_offset = [&](int u) -> uint32_t {
-    if (u < cache_units) {
-      const int n = min(u * 32 + li, n_cache - 1);
-      const uint32_t src = sparse ? min((uint32_t)kidx[n], (uint32_t)(dm.T_max - 1)) : (uint32_t)n;   // a malformed list cannot leave the cache
-      return src * cache_rb;
-    }
+  auto row_offset = [&](int u, uint32_t entry) __attribute__((always_inline)) -> uint32_t {
+    if (u < cache_units)   // (the clamp: a malformed list cannot leave the cache)
+      return (sparse ? min(entry, (uint32_t)(dm.T_max - 1)) : (uint32_t)min(u * 32 + li, n_cache - 1)) * cache_rb;
     return (uint32_t)min((u - cache_units) * 32 + li, n_chunk - 1) * chunk_rb;
   };
   f32x4 kreg[NI];
@@ -128,7 +131,7 @@ __global__ __launch_bounds__(kFaThreads, 2) void attn_f32(Dims dm, AttnArgs a, f
   int u = u_begin + w;
   uint32_t off = 0;
   if (u < u_end) {
-    off = row_offset(u);
+    off = row_offset(u, look_up(u));
     load_k(u, off);
   }
   __syncthreads();   // Q rows are in LDS
@@ -147,12 +150,12 @@ __global__ __launch_bounds__(kFaThreads, 2) void attn_f32(Dims dm, AttnArgs a, f
 #pragma unroll
       for (int e = 0; e < 4; ++e) voff[4 * q4 + e] = t[e];
     }
+    const uint32_t entry_next = look_up(u + kFaWaves);
     vrow vreg[16];   // in flight during the first product
     const char* vbase = (is_chunk ? vchunk : vcache) + (DB * 4) * li;
 #pragma unroll
     for (int v = 0; v < 16; ++v) vreg[v] = *reinterpret_cast<const vrow*>(vbase + voff[v]);
-    uint32_t off_next = 0;
-    if (u + kFaWaves < u_end) off_next = row_offset(u + kFaWaves);
+    __builtin_amdgcn_sched_barrier(0);   // (or they leave behind the product)
 
     f32x16 s;
 #pragma unroll
@@ -163,8 +166,10 @@ __global__ __launch_bounds__(kFaThreads, 2) void attn_f32(Dims dm, AttnArgs a, f
 #pragma unroll
       for (int e = 0; e < 4; ++e) s = __builtin_amdgcn_mfma_f32_32x32x2f32(kreg[i][e], qv[e], s, 0, 0, 0);
     }
-    off = off_next;
-    if (u + kFaWaves < u_end) load_k(u + kFaWaves, off);   // travels during the softmax and the second product
+    if (u + kFaWaves < u_end) {   // travels during the softmax and the second product
+      off = row_offset(u + kFaWaves, entry_next);
+      load_k(u + kFaWaves, off);
+    }
 
     const int limit = is_chunk ? tok + 1 - (u - cache_units) * 32 : n_cache - u * 32;   // slots kk < limit are visible
     float mx = -INFINITY;

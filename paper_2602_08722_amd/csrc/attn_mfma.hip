@@ -545,7 +545,7 @@ __global__ __launch_bounds__(2 * kSetThreads, 2) void attn_bf16(Dims dm, AttnArg
       wait_vmcnt<0>();
     }
     if (!first) __syncthreads();
-    if constexpr (!kShare) {   // (or the new entries are waited for, to be moved to where these are)
+    if constexpr (!kShare && DMA) {   // (or the new entries are waited for, to be moved to where these are)
 #pragma unroll
       for (int i = 0; i < NI; ++i) asm volatile("" : "+v"(src[i]));
     }

@@ -181,6 +181,16 @@ __device__ __forceinline__ float other_half(float x) {
   return __uint_as_float((threadIdx.x & 32) ? lo : hi);
 }
 
+// A pointer (the same in all lanes) of which the compiler no longer knows what it is based on: fetches through a `__restrict__` one are
+// moved behind the next branch that does not need them, whatever stands between.
+template <typename T>
+__device__ __forceinline__ void opaque(T*& p) {
+  typedef T __attribute__((address_space(1))) * global_ptr;   // (what a generic pointer is fetched through waits for LDS as well)
+  global_ptr g = (global_ptr)p;
+  asm("" : "+s"(g));
+  p = (T*)g;
+}
+
 // Orders the memory accesses of one wave's lanes to each other: none is moved across it by the compiler.  (LDS accesses of a wave
 // are carried out in the order they are issued in.)
 __device__ __forceinline__ void wave_fence() {

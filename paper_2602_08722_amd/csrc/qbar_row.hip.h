@@ -2,6 +2,8 @@
 // head of the group, unit-normalised, and averaged.  Lanes own D/64 consecutive elements each.  The group's rows are all
 // requested before any is used, so this pays one index latency and one row latency, not g of each.
 #pragma once
+#include <type_traits>
+
 #include "common.hip.h"
 
 namespace quoka {
@@ -14,9 +16,22 @@ namespace quoka {
 // block does this, groups of more than four go one head after the other (24 x 8 KV heads of 7, d 64, 8 tokens over 1500 keys, whole
 // calls 36.2 / 37.4 us; one sequence 19.2 / 18.9).  The same bits.
 enum { kFromIndex = 0, kIdentity = 1, kUniform = 2 };
+// `first` (bf16): the rows of the group's first eight heads, as the caller has requested them.
+template <int D>
+struct QbarRows {
+  typedef typename std::conditional<D == 128, uint32_t, uint16_t>::type elems;   // a lane's D / 64 elements
+  elems v[8];
+  __device__ __forceinline__ void load(const Dims& dm, const uint16_t* q, int tok, int kv, int b, int lane) {
+#pragma unroll
+    for (int j = 0; j < 8; ++j)
+      v[j] = *reinterpret_cast<const elems*>(q + b * dm.qs[0] + (size_t)(kv * dm.g + min(j, dm.g - 1)) * dm.qs[1] + (size_t)tok * dm.qs[2] + lane * (D / 64));
+  }
+  __device__ __forceinline__ float at(int j, int e) const { return __uint_as_float(e == 0 ? (uint32_t)v[j] << 16 : (uint32_t)v[j] & 0xFFFF0000u); }
+};
 template <typename T, int D, int RULE, int GU, bool SIDE>
 __device__ __forceinline__ void qbar_row(const Dims& dm, const T* __restrict__ q, int32_t* __restrict__ q_idx, int n_keep,
-                                         int r, int kv, int b, int lane, bool write_idx, float (&row)[D / 64]) {
+                                         int r, int kv, int b, int lane, bool write_idx, float (&row)[D / 64],
+                                         const QbarRows<D>* first = nullptr) {
   constexpr int EPL = D / 64;
   float acc[EPL];
 #pragma unroll
@@ -38,7 +53,10 @@ __device__ __forceinline__ void qbar_row(const Dims& dm, const T* __restrict__ q
       const int tok = RULE == kFromIndex ? __builtin_amdgcn_readlane(my_tok, j) : my_tok;
       const T* src = q + b * dm.qs[0] + (size_t)(kv * dm.g + j) * dm.qs[1] + (size_t)tok * dm.qs[2];
 #pragma unroll
-      for (int e = 0; e < EPL; ++e) v[jj][e] = Elem<T>::load1(src + lane * EPL + e);
+      for (int e = 0; e < EPL; ++e) {
+        if (GU <= 8 && first != nullptr && j0 == 0) v[jj][e] = first->at(jj % 8, e);
+        else v[jj][e] = Elem<T>::load1(src + lane * EPL + e);
+      }
     }
     if constexpr (SIDE) {
       // (a row beyond the group is made zero, and adds zero; without normalisation (dot-product ablation) every norm is made one)

@@ -43,7 +43,7 @@ __global__ __launch_bounds__(kScThreads, 2) void score_bf16(Dims dm, const float
                                                            FusedQbar fq, const uint16_t* __restrict__ terms,
                                                            uint32_t* __restrict__ hist_ws) {
   using Cfg = ScoreCfg<D, QB>;
-  if constexpr (!HIST) clear_words(zero, zero_words);
+  const int len = HIST ? 0 : kv_lens[blockIdx.z * dm.ls];
   constexpr int LD = Cfg::LD, CG = Cfg::CG, RPI = Cfg::RPI, NLD = Cfg::NLD;
   extern __shared__ __align__(16) unsigned char smem[];
   uint16_t* tile0p = reinterpret_cast<uint16_t*>(smem);
@@ -82,6 +82,7 @@ __global__ __launch_bounds__(kScThreads, 2) void score_bf16(Dims dm, const float
 
   // rows of this (batch, KV head) are addressed as base + 32-bit byte offset (the host checks the 4 GiB span)
   const char* kbase = reinterpret_cast<const char*>(kc + b * dm.kvs[0] + kv * dm.kvs[1]);
+  opaque(kbase);
   const uint32_t row_bytes = (uint32_t)dm.kvs[2] * 2u;
   float* sc = scores + (size_t)(b * dm.n_kv + kv) * dm.T_max;
   const int cg = tid % CG, r0 = tid / CG;
@@ -98,8 +99,15 @@ __global__ __launch_bounds__(kScThreads, 2) void score_bf16(Dims dm, const float
       R[i] = *reinterpret_cast<const u32x4*>(kbase + ((uint32_t)row * row_bytes + (uint32_t)cg * 16u));
     }
   };
-  if constexpr (!HIST) issue(0, RA);   // the first K tile is in flight while the length arrives and the query operands are prepared
-  const int T = min(kv_lens[b * dm.ls], dm.T_cap);
+  // FUSE: the queries of the wave's first row, ahead of the keys (fetches arrive in order, and these are few)
+  QbarRows<D> q_first;
+  if constexpr (FUSE) q_first.load(dm, static_cast<const uint16_t*>(fq.q), min(w, n_keep - 1), kv, b, lane);
+  if constexpr (!HIST) {   // the first K tile is in flight while the length arrives and the query operands are prepared
+    issue(0, RA);
+    asm volatile("" ::: "memory");   // (or the compiler moves these fetches behind the length's arrival)
+    clear_words(zero, zero_words);
+  }
+  const int T = min(HIST ? kv_lens[b * dm.ls] : len, dm.T_cap);
   if constexpr (HIST) {
     if (!shared && T != dm.T_cap) {   // the cache is not full
       tiles_per_wg = (max(T, 0) + kScTile * blocks - 1) / (kScTile * blocks);
@@ -116,10 +124,11 @@ __global__ __launch_bounds__(kScThreads, 2) void score_bf16(Dims dm, const float
     for (int r = w; r < n_keep; r += kScThreads / 64) {
       float row[EPL];
       const uint16_t* q = static_cast<const uint16_t*>(fq.q);
+      if (r != w) q_first.load(dm, q, r, kv, b, lane);
       if (dm.g <= 4) {
-        qbar_row<uint16_t, D, kIdentity, 4, true>(dm, q, fq.q_idx, n_keep, r, kv, b, lane, blockIdx.x == 0, row);
+        qbar_row<uint16_t, D, kIdentity, 4, true>(dm, q, fq.q_idx, n_keep, r, kv, b, lane, blockIdx.x == 0, row, &q_first);
       } else {
-        qbar_row<uint16_t, D, kIdentity, 8, false>(dm, q, fq.q_idx, n_keep, r, kv, b, lane, blockIdx.x == 0, row);
+        qbar_row<uint16_t, D, kIdentity, 8, false>(dm, q, fq.q_idx, n_keep, r, kv, b, lane, blockIdx.x == 0, row, &q_first);
       }
 #pragma unroll
       for (int e = 0; e < EPL; ++e) {
@@ -132,7 +141,9 @@ __global__ __launch_bounds__(kScThreads, 2) void score_bf16(Dims dm, const float
   }
   if (t_begin >= T) return;  // block-uniform
   const int n_tiles = min(tiles_per_wg, (T - t_begin + kScTile - 1) / kScTile);
-  if (n_tiles > 1) issue(1, RB);
+  // The second K tile: ahead of operands that are converted here, and so waited for; behind those that lie ready, which the first tile's
+  // products need.
+  if (!TERMS && n_tiles > 1) issue(1, RB);
 
   const bool dot_mode = (dm.flags & 1) != 0, mean_mode = (dm.flags & 2) != 0;   // ablation scorers
   typename std::conditional<PACK, PackedTerms<D>, QueryTerms<D, EXACT>>::type qt;   // this wave's 32 query rows
@@ -143,6 +154,7 @@ __global__ __launch_bounds__(kScThreads, 2) void score_bf16(Dims dm, const float
   } else {
     qt.load(qhead, n_keep, qb, li, hf, mean_mode);
   }
+  if (TERMS && n_tiles > 1) issue(1, RB);
 
   // scores of tile `it` from the maxima and squared norms of generation it % 3
   auto finish = [&](int it) {
@@ -229,14 +241,16 @@ __global__ __launch_bounds__(kScThreads) void score_f32(Dims dm, const float* __
   constexpr int KPB = 32 * (4 / QB);   // keys per block and step
   typedef float f32x4 __attribute__((ext_vector_type(4)));
   __shared__ float smax[2][QB][KPB];
-  clear_words(zero, zero_words);
   const int kv = blockIdx.y, b = blockIdx.z;
   const int tid = threadIdx.x, lane = tid & 63;
   const int w = __builtin_amdgcn_readfirstlane(tid >> 6);
   const int qb = w % QB, kb = w / QB;
   const int li = lane & 31, hf = lane >> 5;
   const bool dot_mode = (dm.flags & 1) != 0, mean_mode = (dm.flags & 2) != 0;   // ablation scorers
-  const char* kbase = reinterpret_cast<const char*>(kc + b * dm.kvs[0] + kv * dm.kvs[1]) + 16 * hf;
+  const int len = kv_lens[b * dm.ls];
+  const char* khead = reinterpret_cast<const char*>(kc + b * dm.kvs[0] + kv * dm.kvs[1]);
+  opaque(khead);
+  const char* kbase = khead + 16 * hf;
   const uint32_t row_bytes = (uint32_t)dm.kvs[2] * 4u;
   f32x4 kreg[NI];
   auto load_k = [&](int t0) __attribute__((always_inline)) {   // clamped to the cache extent: no wait for the length
@@ -246,18 +260,26 @@ __global__ __launch_bounds__(kScThreads) void score_f32(Dims dm, const float* __
   };
   int t0 = blockIdx.x * KPB;
   load_k(t0);
-  const int T = min(kv_lens[b * dm.ls], dm.T_cap);
-  if (t0 >= T) return;   // block-uniform
-  // query operand: row qb*32 + li (rows past n_keep repeat a real query, or are zero where a mean is taken)
+  // query operand: row qb*32 + li (rows past n_keep repeat a real query, or are zero where a mean is taken), fetched beside the keys
+  // and the length
   f32x4 qreg[NI];
+  const int r = qb * 32 + li;
+  const bool pad = r >= n_keep;
   {
-    int r = qb * 32 + li;
-    const bool pad = r >= n_keep;
-    const float* qrow = qbar + ((size_t)(b * dm.n_kv + kv) * n_keep + (pad ? n_keep - 1 : r)) * D + 4 * hf;
-    const bool round_q = (dm.flags & QUOKA_SCORE_QBAR_BF16) != 0;   // reduced-precision scorer: Qbar as bf16 values
+    const float* qhead = qbar + (size_t)(b * dm.n_kv + kv) * n_keep * D;
+    opaque(qhead);
+    const float* qrow = qhead + (pad ? n_keep - 1 : r) * D + 4 * hf;
+#pragma unroll
+    for (int i = 0; i < NI; ++i) qreg[i] = *reinterpret_cast<const f32x4*>(qrow + 8 * i);
+  }
+  asm volatile("" ::: "memory");   // (or the compiler moves all of these fetches behind the length's arrival)
+  clear_words(zero, zero_words);
+  const int T = min(len, dm.T_cap);
+  if (t0 >= T) return;   // block-uniform
+  const bool round_q = (dm.flags & QUOKA_SCORE_QBAR_BF16) != 0;   // reduced-precision scorer: Qbar as bf16 values
+  if (round_q || mean_mode) {   // (kernel-uniform)
 #pragma unroll
     for (int i = 0; i < NI; ++i) {
-      qreg[i] = *reinterpret_cast<const f32x4*>(qrow + 8 * i);
 #pragma unroll
       for (int e = 0; e < 4; ++e) {
         if (round_q) qreg[i][e] = bf16_bits_to_f32(f32_to_bf16_bits(qreg[i][e]));

@@ -408,6 +408,30 @@ def test_decode_attention_lists_of_one_sequence_shorter_than_their_array(d, chun
         assert P.max_abs(gen.from_torch(buf.lse[0]), want_lse) <= 2e-2
 
 
+# entries are fetched a unit or a tile ahead, for slots that hold a chunk row or nothing too: float32 units and decode tiles of a batch, lists
+# around whole units, of one entry and empty, in arrays whose unused entries are out of range
+@pytest.mark.parametrize("dtype,d,chunk", [("f32", 64, 40), ("f32", 128, 7), ("bf16", 128, 3), ("bf16", 64, 8)])
+def test_entries_fetched_ahead_of_their_use(dtype, d, chunk):
+    w = gen.make_custom(dtype=dtype, n_q=4, n_kv=2, d=d, chunk=chunk, n_retain=8, kv_lens=[700, 650], budgets=[600, 600], batch=2, seed=5)
+    buf = _buffers(w)
+    rng = np.random.default_rng(d)
+    for counts in ((600, 257), (256, 0), (1, 255), (0, 33)):
+        host = np.full(tuple(buf.k_idx.shape), 0x7FFFFFFF, dtype=np.int32)
+        host[:, :, 1::2] = -1
+        lists = []
+        for b, n in enumerate(counts):
+            lists.append(np.stack([np.sort(rng.choice(w.kv_lens[b], size=n, replace=False)) for _ in range(w.n_kv)]).astype(np.int32))
+            host[b, :, :n] = lists[b]
+        buf.k_idx.copy_(torch.from_numpy(host))
+        buf.k_cnt.copy_(torch.tensor([[n] * w.n_kv for n in counts], dtype=torch.int32))
+        buf.out.fill_(float("nan"))
+        buf.sparse_attn()
+        torch.cuda.synchronize()
+        for b in range(2):
+            want = O.sparse_attn(w.Q[b], w.K[b], w.V[b], lists[b], w.Kc[b], w.Vc[b])
+            assert P.max_abs(gen.from_torch(buf.out[b]), want) <= P.TOL_OUT[dtype], (b, counts)
+
+
 # top-B: the fused call and the stage calls against a sort of the same scores, bit for bit, whatever the scores look
 # like (ties at the cut, one score only, more keys in the cut bin than LDS takes, edges of the keys held per thread)
 BINNED_CASES = [
