@@ -3,15 +3,15 @@
 // sparse path (cache rows through k_idx) and the dense baseline.
 //
 // What bounds it: the float32 matrix rate (64 clocks for 32x32x2, twice the rate of plain FMAs); a 32-row, 32-key unit
-// takes D such instructions and reads only 2 * 32 * D floats, so operands come straight from global memory (the cache
-// rows of one KV head stay in L2) and no key tile is staged in LDS.
+// takes D such instructions and reads only 2 * 32 * D floats, so V, and K of short lists and at d 64, come straight from global
+// memory (the cache rows of one KV head stay in L2); no key tile is shared by waves.
 //
 // Rows: the C * g query rows of a KV head are numbered r = token * g + head-in-group, so the 32 rows of a block span few
 // tokens and decode-sized chunks of all heads fill one row block.  Keys: the cache list and the chunk are cut into
 // units of 32 keys.  A block of eight waves owns one row block; its waves take the units in turn, each with its own
 // running (m, l, O), and are merged through LDS.  Row blocks that leave compute units idle are also split over the grid
 // along the key list: such blocks write partial (m, l, O) and attn_f32_merge adds them up.
-// Measured (8/2 heads, d 128, 512 tokens over 491 + 512 keys): 423 us for one wave per row with plain FMAs, 30 + 4 us here;
+// Measured (8/2 heads, d 128, 512 tokens over 491 + 512 keys): 423 us for one wave per row with plain FMAs, 27 + 4 us here;
 // (2/1 heads, d 64, 128 tokens over 128 + 128 keys): 47 us and 10 us.
 //
 // Short lists of a few tokens keep one wave per row (attn_f32_short).
@@ -21,6 +21,8 @@
 //     Register v of the result holds key 8*(v/4) + 4*hf + v%4 of the unit for query row li.
 //   O^T[dim, row]: step v contracts exactly the two keys that register v holds, so B = P is that register; A = V of the
 //     lane's key, M index m of block c standing for dim DB*m + c, so one contiguous load gives all DB blocks.
+#include <type_traits>
+
 #include "common.hip.h"
 #include "kernels.h"
 
@@ -57,10 +59,16 @@ struct FaRow {
 };
 __device__ __forceinline__ FaRow fa_row(int r, int g) { return {r / g, r % g}; }
 
-template <int D>
+// STAGED: K rows go to the wave's own piece of LDS (where its output rows go in the end), whole.  As operands straight from memory a load
+// takes 32 bytes of each of 32 rows, eight waves' rows do not fit the first-level cache, and every line is fetched four times (8/2 heads, d 128,
+// 512 tokens over 491 + 512 keys: the launches 31.5 -> 27.8 us; dense over 4096 101 -> 89).  Where few
+// waves have a unit their lines stay, and the way through LDS costs 0.5 us (5 tokens over 45 keys 8.9 / 9.4; eight waves of one unit, 60 tokens
+// over 360 keys 18.2 / 16.7), and at d 64, with half the lines, 4 - 7 % throughout: those take the operands as they come.
+template <int D, bool STAGED>
 __global__ __launch_bounds__(kFaThreads, 2) void attn_f32(Dims dm, AttnArgs a, float* __restrict__ part, int n_splits) {
   using Cfg = FaCfg<D>;
   constexpr int NI = Cfg::NI, DB = Cfg::DB, QLD = Cfg::QLD, OLD = Cfg::OLD, REC = Cfg::REC;
+  static_assert(OLD >= D, "a unit's K rows in the place of a wave's output rows");
   typedef typename FaVec<DB>::type vrow;
   typedef float f32x4 __attribute__((ext_vector_type(4)));
   extern __shared__ __align__(16) unsigned char smem[];
@@ -112,11 +120,26 @@ __global__ __launch_bounds__(kFaThreads, 2) void attn_f32(Dims dm, AttnArgs a, f
       return (sparse ? min(entry, (uint32_t)(dm.T_max - 1)) : (uint32_t)min(u * 32 + li, n_cache - 1)) * cache_rb;
     return (uint32_t)min((u - cache_units) * 32 + li, n_chunk - 1) * chunk_rb;
   };
-  f32x4 kreg[NI];
-  auto load_k = [&](int u, uint32_t off) __attribute__((always_inline)) {
-    const char* base = (u < cache_units ? kcache : kchunk) + 16 * hf;
+  // Slot c of row r holds chunk c ^ (r & 15), so that 16 lanes read a chunk of 16 rows without conflicts.
+  constexpr int CG = D / 4, RPL = 64 / CG;   // 16-byte chunks of a row, rows of a load
+  const float* kt = os + (size_t)w * 32 * OLD;
+  const uint32_t kt_lds = (uint32_t)(uintptr_t)(const __attribute__((address_space(3))) void*)kt;
+  f32x4 kreg[STAGED ? 1 : NI];
+  auto request_k = [&](int u, uint32_t off) __attribute__((always_inline)) {
+    const char* base = u < cache_units ? kcache : kchunk;
+    if constexpr (!STAGED) {
 #pragma unroll
-    for (int i = 0; i < NI; ++i) kreg[i] = *reinterpret_cast<const f32x4*>(base + off + 32 * i);
+      for (int i = 0; i < NI; ++i) kreg[i] = *reinterpret_cast<const f32x4*>(base + 16 * hf + off + 32 * i);
+      return;
+    }
+#pragma unroll
+    for (int i = 0; i < 32 / RPL; ++i) {
+      const int r = i * RPL + lane / CG;
+      uint32_t row = (uint32_t)__builtin_amdgcn_readlane((int)off, i * RPL);   // (lane r has the offset of row r)
+#pragma unroll
+      for (int j = 1; j < RPL; ++j) row = lane / CG == j ? (uint32_t)__builtin_amdgcn_readlane((int)off, i * RPL + j) : row;
+      dma16(base, row + (uint32_t)(lane % CG ^ (r & 15)) * 16u, kt_lds + (uint32_t)i * 1024u);
+    }
   };
 
   f32x16 o[DB];
@@ -131,13 +154,14 @@ __global__ __launch_bounds__(kFaThreads, 2) void attn_f32(Dims dm, AttnArgs a, f
   int u = u_begin + w;
   uint32_t off = 0;
   if (u < u_end) {
-    off = row_offset(u, look_up(u));
-    load_k(u, off);
+    off = row_offset(u, sparse ? look_up(u) : 0u);
+    request_k(u, off);
   }
   __syncthreads();   // Q rows are in LDS
   uint32_t* my_offs = offs + w * 32;
   const float* qrow = qs + li * QLD + 4 * hf;
   for (; u < u_end; u += kFaWaves) {
+    if constexpr (STAGED) wait_vmcnt<0>();   // K of this unit is there
     const bool is_chunk = u >= cache_units;
     // the rows of the unit's 16 V loads: slot 8*(v/4) + 4*hf + v%4 belongs to another lane (only this wave uses its row
     // of `offs`, and a wave's LDS accesses stay in order)
@@ -160,15 +184,29 @@ __global__ __launch_bounds__(kFaThreads, 2) void attn_f32(Dims dm, AttnArgs a, f
     f32x16 s;
 #pragma unroll
     for (int v = 0; v < 16; ++v) s[v] = 0.f;
+    // (Q, read a step ahead of its products.  With K in LDS too that is the slower: 512 tokens over 491 + 512 keys 27.8 / 29.4 us.)
+    f32x4 qv[2];
+    auto read_q = [&](int i) __attribute__((always_inline)) { qv[i % 2] = *reinterpret_cast<const f32x4*>(qrow + 8 * i); };
+    if constexpr (!STAGED) read_q(0);
 #pragma unroll
     for (int i = 0; i < NI; ++i) {
-      const f32x4 qv = *reinterpret_cast<const f32x4*>(qrow + 8 * i);
+      f32x4 kop;
+      if constexpr (STAGED) {
+        read_q(i);
+        kop = *reinterpret_cast<const f32x4*>(kt + li * D + ((2 * i + hf) ^ (li & 15)) * 4);
+      } else {
+        if (i + 1 < NI) read_q(i + 1);
+        kop = kreg[i];
+        __builtin_amdgcn_sched_barrier(0);
+      }
 #pragma unroll
-      for (int e = 0; e < 4; ++e) s = __builtin_amdgcn_mfma_f32_32x32x2f32(kreg[i][e], qv[e], s, 0, 0, 0);
+      for (int e = 0; e < 4; ++e) s = __builtin_amdgcn_mfma_f32_32x32x2f32(kop[e], qv[i % 2][e], s, 0, 0, 0);
+      if constexpr (!STAGED) __builtin_amdgcn_sched_barrier(0);
     }
     if (u + kFaWaves < u_end) {   // travels during the softmax and the second product
       off = row_offset(u + kFaWaves, entry_next);
-      load_k(u + kFaWaves, off);
+      if constexpr (STAGED) asm volatile("s_waitcnt lgkmcnt(0)" ::: "memory");   // (K of this unit has been read)
+      request_k(u + kFaWaves, off);
     }
 
     const int limit = is_chunk ? tok + 1 - (u - cache_units) * 32 : n_cache - u * 32;   // slots kk < limit are visible
@@ -441,9 +479,11 @@ static bool attn_f32_is_short(const Dims& dm, bool sparse) {
 // Splits of the key list: as many as give every compute unit a block, but at least one unit of 32 keys for every wave
 // of a block (a split costs 16 KiB of partials and a share of the merge launch).
 static long long f32_blocks(const Dims& dm) { return (long long)dm.b * dm.n_kv * ((dm.C * dm.g + 31) / 32); }
+static long long f32_units(const Dims& dm, bool sparse) {   // of the longest key list
+  return ((long long)attended_cap(dm, sparse) + 31) / 32 + (dm.C + 31) / 32;
+}
 static int f32_most_splits(const Dims& dm, bool sparse) {
-  const long long units = ((long long)attended_cap(dm, sparse) + 31) / 32 + (dm.C + 31) / 32;
-  const long long n = (units + kFaWaves - 1) / kFaWaves;
+  const long long n = (f32_units(dm, sparse) + kFaWaves - 1) / kFaWaves;
   return (int)(n > kFaMaxSplits ? kFaMaxSplits : n);
 }
 static int f32_splits(const Dims& dm, bool sparse) {
@@ -466,12 +506,24 @@ static hipError_t launch_f32_d(const Dims& dm, const AttnArgs& a, float* part, h
     hipLaunchKernelGGL((attn_f32_short<D>), grid, dim3(kFsThreads), 0, st, dm, a);
     return hipGetLastError();
   }
-  static std::atomic<uint64_t> lds_done{0};
-  const hipError_t e = ensure_dynamic_lds(reinterpret_cast<const void*>(&attn_f32<D>), FaCfg<D>::kLdsBytes, lds_done);
-  if (e != hipSuccess) return e;
   const int n_splits = f32_splits(dm, a.k_idx != nullptr), n_rb = (dm.C * dm.g + 31) / 32;
-  hipLaunchKernelGGL((attn_f32<D>), dim3(n_rb, n_splits, dm.b * dm.n_kv), dim3(kFaThreads), FaCfg<D>::kLdsBytes, st, dm,
-                     a, part, n_splits);
+  auto launch = [&](auto staged) -> hipError_t {
+    constexpr bool kStaged = decltype(staged)::value;
+    static std::atomic<uint64_t> lds_done{0};
+    const hipError_t e = ensure_dynamic_lds(reinterpret_cast<const void*>(&attn_f32<D, kStaged>), FaCfg<D>::kLdsBytes, lds_done);
+    if (e != hipSuccess) return e;
+    hipLaunchKernelGGL((attn_f32<D, kStaged>), dim3(n_rb, n_splits, dm.b * dm.n_kv), dim3(kFaThreads), FaCfg<D>::kLdsBytes, st, dm,
+                       a, part, n_splits);
+    return hipSuccess;
+  };
+  hipError_t e;
+  if constexpr (D == 128) {
+    const bool few = f32_units(dm, a.k_idx != nullptr) <= 4LL * n_splits;   // at most four waves of a block have a unit
+    e = few ? launch(std::false_type{}) : launch(std::true_type{});
+  } else {
+    e = launch(std::false_type{});
+  }
+  if (e != hipSuccess) return e;
   if (n_splits > 1) {
     const int rows = dm.C * dm.g;
     auto merge = [&](auto kernel, int rows_per_block) {
