@@ -320,9 +320,9 @@ static quoka_status attn_common(const quoka_shape* shape, const CallInfo& info, 
   a.k_chunk = k_chunk;
   a.v_chunk = v_chunk;
   if (!sparse) dm.T_max = dm.T_cap;   // what the kernels cut a cache length at: the launch is sized for that
-  // a null k_idx selects the dense kernel path, so a sparse call with B_max == 0 still needs a non-null marker:
-  // n_cache is then 0 everywhere and k_idx is never dereferenced.
-  a.k_idx = sparse ? (k_idx != nullptr ? k_idx : n_cache) : nullptr;
+  // A null k_idx selects the dense kernel path, so a sparse call with B_max == 0 still needs a non-null one: n_cache, not the
+  // caller's pointer to an array without entries, because the kernels fetch entry 0 before they know a list's length (and do not use it).
+  a.k_idx = !sparse ? nullptr : dm.B_max > 0 ? k_idx : n_cache;
   a.n_cache = n_cache;
   a.out = out;
   a.lse = lse;

@@ -378,6 +378,22 @@ def test_bf16_attention_lists_shorter_than_their_array(case, counts, d, scale_f3
         assert P.max_abs(out[:, rows], want) <= P.TOL_OUT["bf16"], n
 
 
+# no room for selected keys at all: the entry that the kernels fetch ahead is none of a list's, in units and a wave a row (float32), decode of one
+# sequence and of a batch, blocks of four and of eight
+@pytest.mark.parametrize("case", [
+    dict(dtype="f32", n_q=4, n_kv=2, d=64, chunk=40, kv_lens=[70], budgets=[0]),
+    dict(dtype="f32", n_q=4, n_kv=2, d=128, chunk=200, kv_lens=[70], budgets=[0]),
+    dict(dtype="f32", n_q=4, n_kv=2, d=128, chunk=2, kv_lens=[70], budgets=[0]),
+    dict(dtype="bf16", n_q=4, n_kv=2, d=128, chunk=1, kv_lens=[70], budgets=[0]),
+    dict(dtype="bf16", n_q=4, n_kv=2, d=64, chunk=8, kv_lens=[70, 9], budgets=[0, 0], batch=2),
+    dict(dtype="bf16", n_q=14, n_kv=2, d=64, chunk=9, kv_lens=[70], budgets=[0]),
+    dict(dtype="bf16", n_q=14, n_kv=2, d=128, chunk=300, kv_lens=[70], budgets=[0]),
+    dict(dtype="bf16", n_q=52, n_kv=52, d=128, chunk=700, kv_lens=[70], budgets=[0]),
+], ids=_id)
+def test_attention_without_room_for_selected_keys(case):
+    check_attention(case, rows=sorted({0, case["chunk"] // 2, case["chunk"] - 1}))
+
+
 # decode kernel: single slots, tiles of 32 short of and past full, fewer tiles than waves or blocks, batches whose shares
 # of the blocks differ, batches beyond one wave's lanes
 DECODE_CASES = [
