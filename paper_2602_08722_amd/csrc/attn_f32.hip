@@ -61,9 +61,9 @@ __device__ __forceinline__ FaRow fa_row(int r, int g) { return {r / g, r % g}; }
 
 // STAGED: K rows go to the wave's own piece of LDS (where its output rows go in the end), whole.  As operands straight from memory a load
 // takes 32 bytes of each of 32 rows, eight waves' rows do not fit the first-level cache, and every line is fetched four times (8/2 heads, d 128,
-// 512 tokens over 491 + 512 keys: the launches 31.5 -> 27.8 us; dense over 4096 101 -> 89).  Where few
-// waves have a unit their lines stay, and the way through LDS costs 0.5 us (5 tokens over 45 keys 8.9 / 9.4; eight waves of one unit, 60 tokens
-// over 360 keys 18.2 / 16.7), and at d 64, with half the lines, 4 - 7 % throughout: those take the operands as they come.
+// 512 tokens over 491 + 512 keys: the launches 31.5 -> 27.8 us; dense over 4096 101 -> 89).  Up to four units their waves' lines
+// stay, and the way through LDS costs 0.5 us (5 tokens over 45 keys 8.9 / 9.4; eight waves of one unit, 60 tokens over 360 keys 18.2 / 16.7), and at
+// d 64, with half the lines, 4 - 7 % throughout: those take the operands as they come.
 template <int D, bool STAGED>
 __global__ __launch_bounds__(kFaThreads, 2) void attn_f32(Dims dm, AttnArgs a, float* __restrict__ part, int n_splits) {
   using Cfg = FaCfg<D>;
@@ -518,8 +518,8 @@ static hipError_t launch_f32_d(const Dims& dm, const AttnArgs& a, float* part, h
   };
   hipError_t e;
   if constexpr (D == 128) {
-    const bool few = f32_units(dm, a.k_idx != nullptr) <= 4LL * n_splits;   // at most four waves of a block have a unit
-    e = few ? launch(std::false_type{}) : launch(std::true_type{});
+    // at most four waves of the block have a unit (a list of so few is never split)
+    e = f32_units(dm, a.k_idx != nullptr) <= 4 ? launch(std::false_type{}) : launch(std::true_type{});
   } else {
     e = launch(std::false_type{});
   }

@@ -82,14 +82,15 @@ def test_float32_attention_units_rows_and_splits(case):
     check_attention(dict(case, dtype="f32"))
 
 
-# K rows of float32 units at d 128 go through LDS where more than four waves of a block have a unit: four and five units, the last one of a
-# single key, eight and nine (a wave has two), split lists on both sides of the line, and d 64, where none do
+# K rows of float32 units at d 128 go through LDS beyond four units: four, and five, the last one of a single key; eight, and nine and ten, of
+# which one and two waves have a second one; a split list (seven units a share, and one where the sequence has but four); and d 64, where none do
 @pytest.mark.parametrize("d", [128, 64])
 @pytest.mark.parametrize("case", [
     dict(n_q=2, n_kv=1, chunk=16, kv_lens=[300], budgets=[96]),
     dict(n_q=2, n_kv=1, chunk=16, kv_lens=[300], budgets=[97]),
     dict(n_q=3, n_kv=1, chunk=33, kv_lens=[300], budgets=[192]),
-    dict(n_q=300, n_kv=300, chunk=33, kv_lens=[300], budgets=[225]),     # (more row blocks than compute units: not split)
+    dict(n_q=300, n_kv=300, chunk=33, kv_lens=[300], budgets=[224]),     # (more row blocks than compute units: not split)
+    dict(n_q=300, n_kv=300, chunk=33, kv_lens=[300], budgets=[225]),
     dict(n_q=4, n_kv=2, chunk=70, kv_lens=[900, 31], budgets=[800, 31], batch=2),
 ], ids=_id)
 def test_float32_attention_keys_through_lds(case, d):
