@@ -12,10 +12,11 @@ namespace {
 
 using quoka::Dims;
 
+using quoka::kMaxChunk;
+using quoka::kMaxGroup;
+using quoka::kMaxKv;
+
 constexpr int kMaxRetain = 128;
-constexpr int kMaxGroup = 16;   // q-heads per KV head
-constexpr int kMaxChunk = 8192;
-constexpr int kMaxKv = 1 << 24;
 constexpr size_t kAlign = 256;
 
 size_t round_up(size_t x, size_t a) { return (x + a - 1) / a * a; }

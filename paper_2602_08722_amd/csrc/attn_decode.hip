@@ -32,6 +32,7 @@ constexpr int kDcWaves = 4;
 constexpr int kDcThreads = 64 * kDcWaves;
 constexpr int kDcTile = 32;       // list slots a wave handles at a time
 constexpr int kMaxSplits = 64;    // blocks per (sequence, KV head)
+static_assert(((long long)kMaxKv / kDcTile + 2) * kMaxSplits < 1ll << 32, "tiles times shares in 32 bits");   // (at most 32 rows of the chunk's own)
 
 template <int D>
 struct DecodeCfg {
@@ -134,7 +135,7 @@ __global__ __launch_bounds__(kDcThreads, 2) void attn_decode_bf16(Dims dm, AttnA
     n_keys = n + C;
     const int tiles = (n_keys + kDcTile - 1) / kDcTile;
     if constexpr (ONE) work.n_splits = decode_splits_of_one(tiles, n_slots);
-    // (at most 2^20 tiles and 64 shares; as 64-bit quotients they took 260 instructions ahead of the first fetch)
+    // (as 64-bit quotients they took 260 instructions ahead of the first fetch)
     t_end = (int)((uint32_t)tiles * (uint32_t)(work.split + 1) / (uint32_t)work.n_splits);
     t = ONE && work.split >= work.n_splits ? t_end : (int)((uint32_t)tiles * (uint32_t)work.split / (uint32_t)work.n_splits) + w;
   };

@@ -47,6 +47,13 @@ typedef s16x4 __attribute__((address_space(3))) * tr_ptr;   // LDS address of on
 constexpr int kComputeUnits = 256;   // MI355X
 constexpr int kSetThreads = 256;   // four waves
 constexpr int kSub = 64;           // keys a wave set consumes per step
+constexpr int kMaxKeySplits = 32;          // blocks that share a key list,
+constexpr long long kMaxRecords = 2048;   // and their partials of 32 rows (16.6 KiB each at d = 128)
+// What attn_bf16 divides without a division: row blocks of a KV head by the group, blocks by the shares of a list (of which there are no more
+// than partials); and its tiles times shares stay within 32 bits.
+static_assert(quotients_hold(kMaxGroup, kMaxGroup * ((kMaxChunk + 31) / 32) - 1), "row blocks by the group");
+static_assert(quotients_hold(kMaxKeySplits, kMaxRecords - 1), "blocks by the shares");
+static_assert(((long long)kMaxKv / kSub + kMaxChunk / kSub + 2) * kMaxKeySplits < 1ll << 32, "tiles times shares");
 
 // SPLIT = false: the sets own different row blocks (8 per block) and both consume every 64-key tile.
 // SPLIT = true:  both sets own the same 4 row blocks; a staged tile has 128 keys, set s consumes keys 64*s..64*s+63,
@@ -257,7 +264,7 @@ __global__ __launch_bounds__(2 * kSetThreads, 2) void attn_bf16(Dims dm, AttnArg
   const int n_ct = (n_cache + KT - 1) / KT;
   const int n_tiles = n_cht + n_ct;
   // Tiles are numbered from -1, so that the cache tiles are 0 .. n_ct - 1.
-  const int t_begin = (KSPLIT ? (int)((uint32_t)n_tiles * (uint32_t)split / (uint32_t)a.n_splits) : 0) - 1;   // (at most 2^19 tiles, 32 shares)
+  const int t_begin = (KSPLIT ? (int)((uint32_t)n_tiles * (uint32_t)split / (uint32_t)a.n_splits) : 0) - 1;
   const int t_end = (KSPLIT ? (int)((uint32_t)n_tiles * (uint32_t)(split + 1) / (uint32_t)a.n_splits) : n_tiles) - 1;
   auto is_cache = [&](int t) __attribute__((always_inline)) { return (uint32_t)t < (uint32_t)n_ct; };
   // first key (cache slot or chunk position) of tile t
@@ -858,11 +865,11 @@ static hipError_t launch_variant(const Dims& dm, const AttnArgs& a, hipStream_t 
   const int half = (nrb + 1) / 2;
   dim3 grid(dm.n_kv, (half + Cfg::HW - 1) / Cfg::HW * a.n_splits, dm.b);
   AttnArgs aa = a;
+  aa.inv_g = quotient_factor(dm.g);
+  aa.inv_splits = quotient_factor(a.n_splits);
   // one block is resident per compute unit: from two rounds on, neighbouring row blocks and longest ranges first
   // (measured at 512 blocks, 4096-token chunk over 131072 cached tokens: 3.5 % faster than pairing; a launch of one
   // round needs the pairing, or its last block sets the time alone)
-  aa.inv_g = (65536u + dm.g - 1) / dm.g;
-  aa.inv_splits = (65536u + a.n_splits - 1) / a.n_splits;
   aa.adjacent = (long long)grid.x * grid.y * grid.z >= 2 * kComputeUnits ? 1 : 0;
   hipLaunchKernelGGL((attn_bf16<D, SPLIT, XS, KSPLIT, WHOLE>), grid, dim3(2 * kSetThreads), lds, st, dm, aa);
   if (KSPLIT) {
@@ -888,8 +895,6 @@ static hipError_t launch_ds(const Dims& dm, const AttnArgs& a, hipStream_t st) {
 }
 
 // ---- which variant: 8 row blocks per block or 4 (SPLIT), and over how many blocks the key list is split -----------
-constexpr int kMaxKeySplits = 32;
-constexpr long long kMaxRecords = 2048;   // partials of 32 rows (16.6 KiB each at d = 128)
 
 static int key_splits_limit(const Dims& dm, bool sparse, int keys_per_tile) {
   const long long tiles = ((long long)attended_cap(dm, sparse) + keys_per_tile - 1) / keys_per_tile +

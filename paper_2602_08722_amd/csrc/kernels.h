@@ -9,6 +9,20 @@
 
 namespace quoka {
 
+// Sizes that every call is checked against, and that kernels count on
+constexpr int kMaxGroup = 16;   // q-heads per KV head
+constexpr int kMaxChunk = 8192;
+constexpr int kMaxKv = 1 << 24;   // (cache lengths are below it)
+
+// x / n as x * quotient_factor(n) >> 16.  The product is x / n + x * (n * factor - 2^16) / (n * 2^16) before the shift, so the quotient is
+// right as long as x * (n * factor - 2^16) < 2^16, and the product fits 32 bits for x <= 2^16 - 1.
+constexpr uint32_t quotient_factor(uint32_t n) { return (65536u + n - 1) / n; }
+constexpr bool quotients_hold(uint32_t n_most, uint32_t x_most) {   // for every n up to n_most and x up to x_most
+  for (uint32_t n = 1; n <= n_most; ++n)
+    if (x_most * (n * quotient_factor(n) - 65536u) >= 65536u) return false;
+  return x_most < 65536u;
+}
+
 // Kernels that use more than 64 KiB of dynamic LDS need the limit raised once per function and device.  `done` is a
 // per-function bit mask over device ordinals (a function-local static of the caller); the attribute call is
 // idempotent, so two threads racing through it are harmless, and the mask itself is atomic.
@@ -93,7 +107,7 @@ struct AttnArgs {
   // set by the launcher of the bf16 kernel:
   int adjacent = 0;        // row-block assignment (paired or adjacent)
   int n_splits = 1;        // blocks that share a row block's key list
-  // 2^16 / g and 2^16 / n_splits, rounded up: x * inv >> 16 is the quotient for x < 4096 (row blocks, g <= 16) and x < 2048 (blocks, n_splits <= 32)
+  // quotient_factor of g and of n_splits
   uint32_t inv_g = 0, inv_splits = 0;
   float* part = nullptr;   // their partial results
 };
