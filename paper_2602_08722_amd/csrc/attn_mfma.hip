@@ -350,6 +350,9 @@ __global__ __launch_bounds__(2 * kSetThreads, 2) void attn_bf16(Dims dm, AttnArg
     if (t_begin + 1 < t_end) {
       address(t_begin + 1);
       look_up(t_begin + 2);
+      // Not DMA: the queries have arrived before the second tile is requested, into registers, by loads whose number is the compiler's choice.
+      // (It waits here for the entries anyway.  KSPLIT: the queries come ahead of the first tile, which is stored below.)
+      if constexpr (!DMA && !KSPLIT) wait_vmcnt<0>();
 #pragma unroll
       for (int k = 0; k < NLD; ++k) request(t_begin + 1, k);
     }
@@ -359,8 +362,11 @@ __global__ __launch_bounds__(2 * kSetThreads, 2) void attn_bf16(Dims dm, AttnArg
     }
   }
   // the first tile and the queries have arrived (K of the second tile may be on its way)
-  if (set == 0 && t_begin + 1 < t_end) wait_vmcnt<NLD>();
-  else wait_vmcnt<0>();
+  if (set == 0 && t_begin + 1 < t_end) {
+    if constexpr (DMA) wait_vmcnt<NLD>();
+  } else {
+    wait_vmcnt<0>();
+  }
   __syncthreads();
   // Q operand: row tok0 + li, chunk ks + KS*hf of 8 dims
   bf16x8 qreg[KS];
