@@ -340,22 +340,24 @@ def test_bf16_attention_rows_of_whole_lists(case, scale_f32):
     assert torch.equal(wide[..., :d], buf.out) and bool((wide[..., d:] == 7.0).all())
 
 
-# a block's first fetches leave before the list's length is known: lists that fill their first tile, one short of it, and empty, in
+# the first fetches of a block with a whole list leave before its length is known: lists that fill their first tile, one short of it, and empty, in
 # arrays whose unused entries are out of range, in every form of the kernel and with queries whose tokens lie apart
 @pytest.mark.parametrize("scale_f32", [False, True], ids=["", "scale-f32"])
 @pytest.mark.parametrize("d", [64, 128])
 @pytest.mark.parametrize("case,counts", [
     (dict(n_q=16, n_kv=2, chunk=9, kv_lens=[200], budgets=[129], plan=(4, 1)), [129, 128, 127, 65, 1, 0]),
     (dict(n_q=16, n_kv=2, chunk=2070, kv_lens=[3000], budgets=[2500], plan=(8, 1)), [2500, 65, 64, 63, 1, 0]),
-    (dict(n_q=14, n_kv=2, chunk=40, kv_lens=[3000], budgets=[2500], plan=None), [2500, 129, 127, 64, 1, 0]),   # shared lists
-], ids=["four", "eight", "shared"])
+    (dict(n_q=14, n_kv=2, chunk=5, kv_lens=[200], budgets=[129], plan=(4, 1)), [129, 128, 127, 65, 1, 0]),     # rows stored as the registers lie
+    (dict(n_q=14, n_kv=2, chunk=40, kv_lens=[3000], budgets=[2500], plan=(4, 11)), [2500, 129, 127, 64, 1, 0]),   # shared lists
+    (dict(n_q=12, n_kv=4, chunk=1421, kv_lens=[3000], budgets=[2500], plan=(8, 3)), [2500, 65, 64, 63, 1, 0]),
+], ids=["four", "eight", "four-few-rows", "four-shared", "eight-shared"])
 def test_bf16_attention_lists_shorter_than_their_array(case, counts, d, scale_f32):
     case = dict(case)
     plan, chunk = case.pop("plan"), case["chunk"]
     w = gen.make_custom(dtype="bf16", d=d, n_retain=8, batch=1, seed=4, **case)
     buf = _buffers(w, score_flags=16 if scale_f32 else 0)
     got = _pk().quoka_probe_attn_plan(buf.shape, True)
-    assert got == plan if plan else got[1] > 1, got
+    assert got == plan, got
     apart = torch.full((1, w.n_q, chunk, d + 8), float("nan"), dtype=torch.bfloat16, device="cuda:0")
     apart[..., :d] = buf.q
     buf.q = apart[..., :d]
