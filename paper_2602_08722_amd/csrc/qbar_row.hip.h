@@ -16,7 +16,9 @@ namespace quoka {
 // block does this, groups of more than four go one head after the other (24 x 8 KV heads of 7, d 64, 8 tokens over 1500 keys, whole
 // calls 36.2 / 37.4 us; one sequence 19.2 / 18.9).  The same bits.
 enum { kFromIndex = 0, kIdentity = 1, kUniform = 2 };
-// `first` (bf16): the rows of the group's first eight heads, as the caller has requested them.
+// `first` (bf16): the rows of the group's first eight heads, as the caller has requested them.  A smaller group's last row is requested again for
+// the places beyond it: a choice by the group's size stands ahead of the first fetch and costs more than the fetches (scoring launch of 8 heads of
+// 4, 8192 keys, 1 token 9.3 -> 9.9 us; asked for a wave's later rows only, 1 token 9.25 -> 9.4, 13 x 8 heads, 8 tokens over 1500 keys 14.0 -> 13.7).
 template <int D>
 struct QbarRows {
   typedef typename std::conditional<D == 128, uint32_t, uint16_t>::type elems;   // a lane's D / 64 elements
