@@ -32,7 +32,8 @@ constexpr int kDcWaves = 4;
 constexpr int kDcThreads = 64 * kDcWaves;
 constexpr int kDcTile = 32;       // list slots a wave handles at a time
 constexpr int kMaxSplits = 64;    // blocks per (sequence, KV head)
-static_assert(((long long)kMaxKv / kDcTile + 2) * kMaxSplits < 1ll << 32, "tiles times shares in 32 bits");   // (at most 32 rows of the chunk's own)
+// (at most 32 rows of the chunk's own)
+static_assert(((long long)kMaxKv / kDcTile + 2) * kMaxSplits < 1ll << 32, "tiles times shares in 32 bits");
 
 template <int D>
 struct DecodeCfg {

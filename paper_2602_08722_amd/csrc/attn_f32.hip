@@ -60,10 +60,10 @@ struct FaRow {
 __device__ __forceinline__ FaRow fa_row(int r, int g) { return {r / g, r % g}; }
 
 // STAGED: K rows go to the wave's own piece of LDS (where its output rows go in the end), whole.  As operands straight from memory a load
-// takes 32 bytes of each of 32 rows, eight waves' rows do not fit the first-level cache, and every line is fetched four times (8/2 heads, d 128,
-// 512 tokens over 491 + 512 keys: the launches 31.5 -> 27.8 us; dense over 4096 101 -> 89).  Up to four units their waves' lines
-// stay, and the way through LDS costs 0.5 us (5 tokens over 45 keys 8.9 / 9.4; eight waves of one unit, 60 tokens over 360 keys 18.2 / 16.7), and at
-// d 64, with half the lines, 4 - 7 % throughout: those take the operands as they come.
+// takes 32 bytes of each of 32 rows, eight waves' rows do not fit the first-level cache, and every line is fetched four times (8/2 heads, d
+// 128, 512 tokens over 491 + 512 keys: the launches 31.5 -> 27.8 us; dense over 4096 101 -> 89).  Up to four units their waves' lines
+// stay, and the way through LDS costs 0.5 us (5 tokens over 45 keys 8.9 / 9.4; eight waves of one unit, 60 tokens over 360 keys 18.2 /
+// 16.7), and at d 64, with half the lines, 4 - 7 % throughout: those take the operands as they come.
 template <int D, bool STAGED>
 __global__ __launch_bounds__(kFaThreads, 2) void attn_f32(Dims dm, AttnArgs a, float* __restrict__ part, int n_splits) {
   using Cfg = FaCfg<D>;
@@ -108,8 +108,8 @@ __global__ __launch_bounds__(kFaThreads, 2) void attn_f32(Dims dm, AttnArgs a, f
   const char* vchunk = reinterpret_cast<const char*>(static_cast<const float*>(a.v_chunk) + b * dm.cks[0] + kv * dm.cks[1]);
   const uint32_t cache_rb = (uint32_t)dm.kvs[2] * 4u, chunk_rb = (uint32_t)dm.cks[2] * 4u;
 
-  // The list's entry for slot li of unit u: fetched a unit ahead, before the unit's V rows (fetches arrive in order), and first used, and so
-  // waited for, behind the unit's first product.  (Looked up and turned into an offset in one place, the wave waited for it, and for all
+  // The list's entry for slot li of unit u: fetched a unit ahead, before the unit's V rows (fetches arrive in order), and first used, and
+  // so waited for, behind the unit's first product.  (Looked up and turned into an offset in one place, the wave waited for it, and for all
   // of its V rows, ahead of that product.)  A chunk unit and a dense call find some number, which is not used.
   const int32_t* list = sparse ? kidx : a.n_cache;
   const int list_last = sparse ? max(n_cache - 1, 0) : 0;

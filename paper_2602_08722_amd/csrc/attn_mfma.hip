@@ -49,8 +49,8 @@ constexpr int kSetThreads = 256;   // four waves
 constexpr int kSub = 64;           // keys a wave set consumes per step
 constexpr int kMaxKeySplits = 32;          // blocks that share a key list,
 constexpr long long kMaxRecords = 2048;   // and their partials of 32 rows (16.6 KiB each at d = 128)
-// What attn_bf16 divides without a division: row blocks of a KV head by the group, blocks by the shares of a list (of which there are no more
-// than partials); and its tiles times shares stay within 32 bits.
+// What attn_bf16 divides without a division: row blocks of a KV head by the group, blocks by the shares of a list (of which there are no
+// more than partials); and its tiles times shares stay within 32 bits.
 static_assert(quotients_hold(kMaxGroup, kMaxGroup * ((kMaxChunk + 31) / 32) - 1), "row blocks by the group");
 static_assert(quotients_hold(kMaxKeySplits, kMaxRecords - 1), "blocks by the shares");
 static_assert(((long long)kMaxKv / kSub + kMaxChunk / kSub + 2) * kMaxKeySplits < 1ll << 32, "tiles times shares");
@@ -73,8 +73,8 @@ __device__ __forceinline__ int seq_of_rank(const int32_t* __restrict__ lens, int
   return hit ? (int)__builtin_ctzll(hit) : rank;
 }
 
-// Two floats as bf16, rounded to nearest even by one instruction.  (In integer arithmetic the rows' way out takes 300 more: 32/8 heads, d 128,
-// 300 tokens over 1080 keys 23.9 -> 23.6 us, 3000 over 2400 200.5 -> 199.4.)
+// Two floats as bf16, rounded to nearest even by one instruction.  (In integer arithmetic the rows' way out takes 300 more: 32/8 heads, d
+// 128, 300 tokens over 1080 keys 23.9 -> 23.6 us, 3000 over 2400 200.5 -> 199.4.)
 __device__ __forceinline__ uint32_t bf16_pair(float lo, float hi) {
   const bf16x2 p = {(__bf16)lo, (__bf16)hi};
   return __builtin_bit_cast(uint32_t, p);
@@ -152,8 +152,8 @@ __global__ __launch_bounds__(2 * kSetThreads, 2) void attn_bf16(Dims dm, AttnArg
   const int n_given = a.n_cache[sparse ? b * dm.n_kv + kv : b * dm.ls];
   asm volatile("" ::"s"(dm.g), "s"(dm.C), "s"(dm.T_max), "s"(dm.B_max), "s"(dm.C_last),
                "s"(dm.qs[0]), "s"(dm.qs[1]), "s"(dm.qs[2]), "s"(dm.kvs[0]), "s"(dm.kvs[1]), "s"(dm.kvs[2]), "s"(dm.cks[0]), "s"(dm.cks[1]),
-               "s"(dm.cks[2]), "s"(a.q), "s"(a.k_cache), "s"(a.v_cache), "s"(a.k_chunk), "s"(a.v_chunk), "s"(a.k_idx), "s"(a.n_cache), "s"(a.adjacent),
-               "s"(a.inv_g));
+               "s"(dm.cks[2]), "s"(a.q), "s"(a.k_cache), "s"(a.v_cache), "s"(a.k_chunk), "s"(a.v_chunk), "s"(a.k_idx),
+               "s"(a.n_cache), "s"(a.adjacent), "s"(a.inv_g));
   const int tid = threadIdx.x % kSetThreads, lane = tid & 63;                 // position inside the wave set
   // wave-uniform values are pinned to scalar registers so that everything derived from them (tile kind, base
   // pointers, branches) stays scalar too
@@ -224,9 +224,10 @@ __global__ __launch_bounds__(2 * kSetThreads, 2) void attn_bf16(Dims dm, AttnArg
   };
   // A block's start is a chain of fetches, in a launch of many rounds one for every round, so what does not wait for the list's length
   // leaves at once: the list's first entries, the chunk's first tile and the queries.  The entries are looked up for a list that fills its
-  // first tile, and again where it does not.  (Length, queries, entries and tile one after the other took 5.2 us to the first product in 32/8 heads,
-  // 1024 tokens over 983 keys, now 3.8, of which 1.3 until the arguments are there.  Attention by itself, 200 random calls of 2 - 4096 tokens:
-  // 0.95 of the time, d 128 0.96 - 0.92, d 64 0.99 - 0.96; 54 tokens over 132 keys 10.8 -> 9.5 us, 573 over 2084 37.6 -> 35.4.)
+  // first tile, and again where it does not.  (Length, queries, entries and tile one after the other took 5.2 us to the first product in
+  // 32/8 heads, 1024 tokens over 983 keys, now 3.8, of which 1.3 until the arguments are there.  Attention by itself, 200 random calls of
+  // 2 - 4096 tokens: 0.95 of the time, d 128 0.96 - 0.92, d 64 0.99 - 0.96; 54 tokens over 132 keys 10.8 -> 9.5 us, 573 over 2084
+  // 37.6 -> 35.4.)
   if constexpr (!KSPLIT) {
     if (sparse) {
 #pragma unroll
@@ -350,8 +351,8 @@ __global__ __launch_bounds__(2 * kSetThreads, 2) void attn_bf16(Dims dm, AttnArg
     if (t_begin + 1 < t_end) {
       address(t_begin + 1);
       look_up(t_begin + 2);
-      // Not DMA: the queries have arrived before the second tile is requested, into registers, by loads whose number is the compiler's choice.
-      // (It waits here for the entries anyway.  KSPLIT: the queries come ahead of the first tile, which is stored below.)
+      // Not DMA: the queries have arrived before the second tile is requested, into registers, by loads whose number is the compiler's
+      // choice.  (It waits here for the entries anyway.  KSPLIT: the queries come ahead of the first tile, which is stored below.)
       if constexpr (!DMA && !KSPLIT) wait_vmcnt<0>();
 #pragma unroll
       for (int k = 0; k < NLD; ++k) request(t_begin + 1, k);
@@ -372,7 +373,8 @@ __global__ __launch_bounds__(2 * kSetThreads, 2) void attn_bf16(Dims dm, AttnArg
   bf16x8 qreg[KS];
 #pragma unroll
   for (int ks = 0; ks < KS; ++ks)
-    qreg[ks] = *(const bf16x8 __attribute__((address_space(3)))*)(uintptr_t)(q_area(t_begin) + slot * (32 * Cfg::ROW) + li * Cfg::ROW + ((ks + KS * hf) ^ q_swizzle<D>(li)) * 16);
+    qreg[ks] = *(const bf16x8 __attribute__((address_space(3)))*)(uintptr_t)(q_area(t_begin) + slot * (32 * Cfg::ROW) + li * Cfg::ROW +
+                                                                             ((ks + KS * hf) ^ q_swizzle<D>(li)) * 16);
   // the softmax scale and the change to base 2
   const float qscale = 1.4426950408889634f / sqrtf((float)D);
   if constexpr (!XS) {   // into Q once, so K Q^T arrives in the exponent's own units
@@ -381,7 +383,6 @@ __global__ __launch_bounds__(2 * kSetThreads, 2) void attn_bf16(Dims dm, AttnArg
 #pragma unroll
       for (int e = 0; e < 8; ++e) qreg[ks][e] = (__bf16)((float)qreg[ks][e] * qscale);
   }
-
 
   f32x16 o[DB];
 #pragma unroll
@@ -410,12 +411,15 @@ __global__ __launch_bounds__(2 * kSetThreads, 2) void attn_bf16(Dims dm, AttnArg
   uint32_t ka[4];     // K: places of chunks ks % 4 (+ KS for the upper half wave) of row li
 #pragma unroll
   for (int q = 0; q < 4; ++q)
-    ka[q] = lds0 + (uint32_t)(stage_of(w0) + (sub + li) / Cfg::RPW * Cfg::KG + li % Cfg::RPW * Cfg::ROW + ((q ^ k_swizzle<D>(li % Cfg::RPW)) + KS * hf) * 16);
-  uint32_t va[DB];    // V: the lane's corner of the transposing reads of dim block c: key 4*hf + (lane%16)/4, dims 16*((lane/16)%2) + 4*(lane%4)
+    ka[q] = lds0 + (uint32_t)(stage_of(w0) + (sub + li) / Cfg::RPW * Cfg::KG + li % Cfg::RPW * Cfg::ROW +
+                              ((q ^ k_swizzle<D>(li % Cfg::RPW)) + KS * hf) * 16);
+  // V: the lane's corner of the transposing reads of dim block c: key 4*hf + (lane%16)/4, dims 16*((lane/16)%2) + 4*(lane%4)
+  uint32_t va[DB];
 #pragma unroll
   for (int c = 0; c < DB; ++c) {
     const int r = 4 * hf + ((lane & 15) >> 2);
-    va[c] = lds0 + (uint32_t)(stage_of(w0) + Cfg::kKTileBytes + (sub + r) * Cfg::ROW + (((4 * c) ^ v_swizzle<D>(r % Cfg::RPW)) + 2 * ((lane >> 4) & 1) + ((lane & 3) >> 1)) * 16 + 8 * (lane & 1));
+    va[c] = lds0 + (uint32_t)(stage_of(w0) + Cfg::kKTileBytes + (sub + r) * Cfg::ROW +
+                              (((4 * c) ^ v_swizzle<D>(r % Cfg::RPW)) + 2 * ((lane >> 4) & 1) + ((lane & 3) >> 1)) * 16 + 8 * (lane & 1));
   }
   // (the places move between the two stages by one addition a tile each)
   auto move_k = [&](int t) __attribute__((always_inline)) {   // from tile t to tile t + 1
@@ -502,7 +506,8 @@ __global__ __launch_bounds__(2 * kSetThreads, 2) void attn_bf16(Dims dm, AttnArg
   // Keys of unit u of tile t that a row does not see (wave-uniform branch).
   auto mask = [&](f32x16& sn, int t, int u) __attribute__((always_inline)) {
     if (t == tail_tile[u] || t == diag_tile[u]) {
-      const int limit = (is_cache(t) ? n_cache : tok + 1) - (tile_base(t) + sub + 32 * u) - 4 * hf;   // register v is key 8*(v/4) + v%4 past the lane's first
+      // register v is key 8*(v/4) + v%4 past the lane's first
+      const int limit = (is_cache(t) ? n_cache : tok + 1) - (tile_base(t) + sub + 32 * u) - 4 * hf;
 #pragma unroll
       for (int v = 0; v < 16; ++v)
         if (8 * (v / 4) + v % 4 >= limit) sn[v] = -INFINITY;
@@ -550,7 +555,8 @@ __global__ __launch_bounds__(2 * kSetThreads, 2) void attn_bf16(Dims dm, AttnArg
   // read: the K operands of tile j+1 are read during tile j.  The places it takes held K of tile j and V of tile j-1, whose last reads
   // ended before the barrier of step j (the fence again).  DMA: the first step's tiles are requested ahead of the loop.  (Whether a step
   // can be the first is settled when it is compiled: asked in every step, and with a second tile requested and waited for where a block has
-  // only one, d 64 was 2 % slower on the mean of 2000 calls, d 128 1 %; 8 KV heads of 4, d 128, 1074 tokens over 3487 keys 96.1 -> 92.8 us.)
+  // only one, d 64 was 2 % slower on the mean of 2000 calls, d 128 1 %; 8 KV heads of 4, d 128, 1074 tokens over 3487 keys
+  // 96.1 -> 92.8 us.)
   auto begin_step = [&](int j, auto can_be_first) __attribute__((always_inline)) {
     const bool first = decltype(can_be_first)::value && j < t_begin;   // (its barrier is the one above)
     if constexpr (DMA) {
@@ -916,9 +922,10 @@ static int key_splits_limit(const Dims& dm, bool sparse, int keys_per_tile) {
 // less time (0.84 of it at 257 - 288 groups, 0.97 at 353 - 384); from there on those of eight, whose longest ranges come first, even
 // the rounds out (four: 1.03 at 385 - 416 groups, 1.08 - 1.13 beyond).
 // d 64: up to 256 groups it depends on how much of the list is the chunk's own, whose causal ranges blocks of four follow more closely; the
-// bound is a fit of the two times' difference, in us, to half of 1040 measured calls (0 - 6000 keys; with it they take 0.1 % more than the better
-// form, with eight throughout 2.8 %): 12/4 heads, 3203 tokens alone, eight 42.9, four 39.9; 32/8, 1064 tokens over 3000 keys 62 and 71.  Up to 384 groups four (0.74 - 0.88), up to 512 where the chunk is more than three fifths of the list (0.90 - 0.96; else
-// 1.01 - 1.07), beyond that eight.
+// bound is a fit of the two times' difference, in us, to half of 1040 measured calls (0 - 6000 keys; with it they take 0.1 % more than the
+// better form, with eight throughout 2.8 %): 12/4 heads, 3203 tokens alone, eight 42.9, four 39.9; 32/8, 1064 tokens over 3000 keys 62 and
+// 71.  Up to 384 groups four (0.74 - 0.88), up to 512 where the chunk is more than three fifths of the list (0.90 - 0.96; else 1.01 -
+// 1.07), beyond that eight.
 static bool eight_row_blocks(const Dims& dm, bool sparse, long long groups) {
   if (dm.b > 1) return groups >= kComputeUnits;
   const float c = (float)attended_cap(dm, sparse) / kSub, r = (float)dm.C / kSub;
@@ -932,16 +939,16 @@ static bool eight_row_blocks(const Dims& dm, bool sparse, long long groups) {
 // 60 -> 38 us; one KV head of 16 q-heads x 8 sequences, d 64, 69 tokens over 13477 keys (5 splits) 138 -> 65 us.
 // The cheapest variant by a model of the call in microseconds: a fixed part, the steps of the longest key list's share times the rounds of
 // 256 resident blocks, a part for each further round, and for a split list one for each split, one for the partials' bytes and one where
-// there are more than four, whose merge's waves hand their sums to each other.  The numbers are fits to half of 13300 measured calls (2 - 3000
-// tokens over 0 - 20000 keys, at most 1024 row blocks).  On the other half the plans are behind the best of the measured ones, on the mean, by
-// 0.4 % (d 64) and 0.8 % (d 128) for 2 - 64 tokens, by 0.4 % for 33 - 3000 tokens and by 0.15 and 0.3 % for one sequence over few keys; 12 % for
-// single ones.  (Without the part beyond four splits, fitted to 33 tokens and more: 0.6, 1.1, 0.6 and 0.6 %, 20 %.)  Whole lists may take blocks of
-// eight only where ragged row blocks make more than 256 blocks of four: 13 x 4 heads of 3, d 128, 187 tokens over 454 keys 34.3 -> 24.8 us.
-// (Elsewhere they gain up to 5 % on the shortest lists and cost precision: in blocks of four each wave set takes its own reference point, so that
-// two probabilities of a row are 1 and not rounded; 65 tokens over 130 keys lie 2.6 % further from float64 in blocks of eight.)  And not
-// in a batch with room for more than kRaggedKeys keys: its sequences may have fewer, and then the blocks beyond 256 are short ones that fill
-// gaps (13 x 4 heads of 3, without and with whole lists in blocks of eight: d 64, 174 tokens over 512 to 2616 keys 40 and 50 us, over 1868 each
-// 43 and 40; d 128, 171 tokens over 586 to 4688 keys 66 and 105, over 4688 each 133 and 108).
+// there are more than four, whose merge's waves hand their sums to each other.  The numbers are fits to half of 13300 measured calls (2 -
+// 3000 tokens over 0 - 20000 keys, at most 1024 row blocks).  On the other half the plans are behind the best of the measured ones, on the
+// mean, by 0.4 % (d 64) and 0.8 % (d 128) for 2 - 64 tokens, by 0.4 % for 33 - 3000 tokens and by 0.15 and 0.3 % for one sequence over few
+// keys; 12 % for single ones.  (Without the part beyond four splits, fitted to 33 tokens and more: 0.6, 1.1, 0.6 and 0.6 %, 20 %.)  Whole
+// lists may take blocks of eight only where ragged row blocks make more than 256 blocks of four: 13 x 4 heads of 3, d 128, 187 tokens over
+// 454 keys 34.3 -> 24.8 us.  (Elsewhere they gain up to 5 % on the shortest lists and cost precision: in blocks of four each wave set takes
+// its own reference point, so that two probabilities of a row are 1 and not rounded; 65 tokens over 130 keys lie 2.6 % further from float64
+// in blocks of eight.)  And not in a batch with room for more than kRaggedKeys keys: its sequences may have fewer, and then the blocks
+// beyond 256 are short ones that fill gaps (13 x 4 heads of 3, without and with whole lists in blocks of eight: d 64, 174 tokens over 512
+// to 2616 keys 40 and 50 us, over 1868 each 43 and 40; d 128, 171 tokens over 586 to 4688 keys 66 and 105, over 4688 each 133 and 108).
 constexpr int kRaggedKeys = 1024;
 struct AttnPlan {
   bool split_tile;

@@ -16,9 +16,10 @@ namespace quoka {
 // block does this, groups of more than four go one head after the other (24 x 8 KV heads of 7, d 64, 8 tokens over 1500 keys, whole
 // calls 36.2 / 37.4 us; one sequence 19.2 / 18.9).  The same bits.
 enum { kFromIndex = 0, kIdentity = 1, kUniform = 2 };
-// `first` (bf16): the rows of the group's first eight heads, as the caller has requested them.  A smaller group's last row is requested again for
-// the places beyond it: a choice by the group's size stands ahead of the first fetch and costs more than the fetches (scoring launch of 8 heads of
-// 4, 8192 keys, 1 token 9.3 -> 9.9 us; asked for a wave's later rows only, 1 token 9.25 -> 9.4, 13 x 8 heads, 8 tokens over 1500 keys 14.0 -> 13.7).
+// `first` (bf16): the rows of the group's first eight heads, as the caller has requested them.  A smaller group's last row is requested
+// again for the places beyond it: a choice by the group's size stands ahead of the first fetch and costs more than the fetches (scoring
+// launch of 8 heads of 4, 8192 keys, 1 token 9.3 -> 9.9 us; asked for a wave's later rows only, 1 token 9.25 -> 9.4, 13 x 8 heads, 8 tokens
+// over 1500 keys 14.0 -> 13.7).
 template <int D>
 struct QbarRows {
   typedef typename std::conditional<D == 128, uint32_t, uint16_t>::type elems;   // a lane's D / 64 elements
@@ -26,9 +27,12 @@ struct QbarRows {
   __device__ __forceinline__ void load(const Dims& dm, const uint16_t* q, int tok, int kv, int b, int lane) {
 #pragma unroll
     for (int j = 0; j < 8; ++j)
-      v[j] = *reinterpret_cast<const elems*>(q + b * dm.qs[0] + (size_t)(kv * dm.g + min(j, dm.g - 1)) * dm.qs[1] + (size_t)tok * dm.qs[2] + lane * (D / 64));
+      v[j] = *reinterpret_cast<const elems*>(q + b * dm.qs[0] + (size_t)(kv * dm.g + min(j, dm.g - 1)) * dm.qs[1] +
+                                             (size_t)tok * dm.qs[2] + lane * (D / 64));
   }
-  __device__ __forceinline__ float at(int j, int e) const { return __uint_as_float(e == 0 ? (uint32_t)v[j] << 16 : (uint32_t)v[j] & 0xFFFF0000u); }
+  __device__ __forceinline__ float at(int j, int e) const {
+    return __uint_as_float(e == 0 ? (uint32_t)v[j] << 16 : (uint32_t)v[j] & 0xFFFF0000u);
+  }
 };
 template <typename T, int D, int RULE, int GU, bool SIDE>
 __device__ __forceinline__ void qbar_row(const Dims& dm, const T* __restrict__ q, int32_t* __restrict__ q_idx, int n_keep,
