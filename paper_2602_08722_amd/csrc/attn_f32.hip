@@ -110,7 +110,8 @@ __global__ __launch_bounds__(kFaThreads, 2) void attn_f32(Dims dm, AttnArgs a, f
 
   // The list's entry for slot li of unit u: fetched a unit ahead, before the unit's V rows (fetches arrive in order), and first used, and
   // so waited for, behind the unit's first product.  (Looked up and turned into an offset in one place, the wave waited for it, and for all
-  // of its V rows, ahead of that product.)  A chunk unit and a dense call find some number, which is not used.
+  // of its V rows, ahead of that product.)  A chunk unit and a dense call find some number, which is not used: asked for lists only, the
+  // launch over 491 + 512 keys takes 29.8 us instead of 27.5, at d 64 19.3 and 18.8, and a dense one over 4096 the same 88.8.
   const int32_t* list = sparse ? kidx : a.n_cache;
   const int list_last = sparse ? max(n_cache - 1, 0) : 0;
   auto look_up = [&](int u) __attribute__((always_inline)) { return (uint32_t)list[min(u * 32 + li, list_last)]; };
