@@ -18,6 +18,8 @@
 // one sequence, 983 keys: 10.1 -> 6.1 us.
 // MFMA operand plan as in the prefill kernel: S^T = K Q^T (query rows on lanes), O^T += V^T P^T with V^T fetched
 // by the transposing LDS read.
+#include <type_traits>
+
 #include "common.hip.h"
 #include "kernels.h"
 
@@ -110,7 +112,11 @@ __device__ __forceinline__ DecodeWork decode_work(const Dims& dm, const AttnArgs
 // looked up while the list's length travels: one fetch less in the chain, here and in the merge (32/8 heads, d 128, whole calls: 1 token
 // over 983 keys 23.6 -> 22.6 us, this kernel alone 22.7; 5 over 4000 75.4 -> 74.5; batches, whose shares go by all the lengths,
 // lost 1.4 % to it and stay as they were).
-template <int D, bool ONE>
+// LONG: waves with more than two tiles.  The queries have arrived before a tile's successor is requested.  Otherwise they count as on
+// their way wherever the loop is entered again, and every tile's products wait for all that was requested after them, which is the next
+// tile.  With two tiles and fewer that wait is the shorter one: the second tile leaves before the queries are there.  (32/8 heads, d 128, 1
+// token: 8 sequences, 12 % of 16384 keys each 18.7 -> 17.3 us, of 4096 - 65536 33.1 -> 32.3; one, 12 % of 131072 18.3 -> 17.0; both launches.)
+template <int D, bool ONE, bool LONG>
 __global__ __launch_bounds__(kDcThreads, 2) void attn_decode_bf16(Dims dm, AttnArgs a, float* __restrict__ part,
                                                                   int n_slots) {
   using Cfg = DecodeCfg<D>;
@@ -173,7 +179,7 @@ __global__ __launch_bounds__(kDcThreads, 2) void attn_decode_bf16(Dims dm, AttnA
       // (the clamp: a malformed list cannot leave the cache)
       const uint32_t row = from_cache ? (sparse ? min(src[i], (uint32_t)(dm.T_max - 1)) : (uint32_t)n) : (uint32_t)(n - n_cache);
       const uint64_t off = (uint64_t)(row * (from_cache ? cache_row_bytes : chunk_row_bytes) + (uint32_t)cg * 16u);
-      // (named as global memory: through generic pointers the products' LDS operands waited for the rows of the tile after)
+      // (named as global memory: through generic pointers the products' LDS operands wait for the rows of the tile after)
       typedef const u32x4 __attribute__((address_space(1))) * global_rows;
       RK[i] = *(global_rows)(k_cache_u + (from_cache ? 0ull : k_chunk_delta) + off);
       RV[i] = *(global_rows)(v_cache_u + (from_cache ? 0ull : v_chunk_delta) + off);
@@ -222,6 +228,10 @@ __global__ __launch_bounds__(kDcThreads, 2) void attn_decode_bf16(Dims dm, AttnA
       *reinterpret_cast<u32x4*>(vt + rl * LDV + cg * 8) = RV[i];
     }
     __builtin_amdgcn_wave_barrier();
+    if constexpr (LONG) {   // (named as changed, so that they are waited for here, where the tile's entries are waited for next)
+#pragma unroll
+      for (int ks = 0; ks < KS; ++ks) asm volatile("" : "+v"(qreg[ks]));
+    }
     if (t + kDcWaves < t_end) {
       issue(t + kDcWaves);
       if (t + 2 * kDcWaves < t_end) resolve(t + 2 * kDcWaves);
@@ -461,15 +471,23 @@ size_t attn_decode_ws_floats(const Dims& dm) {
 template <int D, bool ONE>
 static hipError_t launch_decode_d(const Dims& dm, const AttnArgs& a, float* part, hipStream_t st) {
   using Cfg = DecodeCfg<D>;
-  static std::atomic<uint64_t> lds_done{0};
-  const hipError_t e = ensure_dynamic_lds(reinterpret_cast<const void*>(&attn_decode_bf16<D, ONE>), Cfg::kLdsBytes, lds_done);
-  if (e != hipSuccess) return e;
   const int n_slots = decode_launch_slots(dm, a.k_idx != nullptr);
   // blocks that a short list leaves without work are not launched where the host can tell
   const long long tiles = ((long long)attended_cap(dm, a.k_idx != nullptr) + dm.C + kDcTile - 1) / kDcTile;
   const long long most = dm.b > 64 ? n_slots : dm.b * ((tiles + kDcWaves - 1) / kDcWaves);
-  hipLaunchKernelGGL((attn_decode_bf16<D, ONE>), dim3(n_slots < most ? n_slots : (int)most, dm.n_kv), dim3(kDcThreads),
-                     Cfg::kLdsBytes, st, dm, a, part, n_slots);
+  auto launch = [&](auto is_long) -> hipError_t {
+    constexpr bool kLong = decltype(is_long)::value;
+    static std::atomic<uint64_t> lds_done{0};
+    const hipError_t e = ensure_dynamic_lds(reinterpret_cast<const void*>(&attn_decode_bf16<D, ONE, kLong>), Cfg::kLdsBytes, lds_done);
+    if (e != hipSuccess) return e;
+    hipLaunchKernelGGL((attn_decode_bf16<D, ONE, kLong>), dim3(n_slots < most ? n_slots : (int)most, dm.n_kv), dim3(kDcThreads),
+                       Cfg::kLdsBytes, st, dm, a, part, n_slots);
+    return hipSuccess;
+  };
+  // More than two tiles a wave.  (160 random calls, both launches: LONG takes 0.93 - 1.00 of the time above the line, 0.97 on the mean,
+  // and 1.00 - 1.03 at it and below, 1.01 with more than eight rows.)
+  const hipError_t e = tiles * dm.b > 2LL * kDcWaves * n_slots ? launch(std::true_type{}) : launch(std::false_type{});
+  if (e != hipSuccess) return e;
   hipLaunchKernelGGL((attn_decode_merge<D, ONE>), dim3(dm.C * dm.g, dm.n_kv, dm.b), dim3(kDcThreads), 0, st, dm, a, part,
                      n_slots);
   return hipGetLastError();

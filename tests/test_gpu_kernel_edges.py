@@ -417,6 +417,19 @@ def test_decode_attention_tiles_and_shares(case):
     check_attention(dict(case, dtype="bf16"))
 
 
+# more than two tiles a wave have a form of their own: two, and one tile more, of one sequence (two blocks a head) and of a ragged batch (six)
+@pytest.mark.parametrize("d", [64, 128])
+@pytest.mark.parametrize("case", [
+    dict(n_q=256, n_kv=256, chunk=1, kv_lens=[520], budgets=[511]),
+    dict(n_q=256, n_kv=256, chunk=1, kv_lens=[511], budgets=[511]),
+    dict(n_q=256, n_kv=256, chunk=1, kv_lens=[520], budgets=[512]),
+    dict(n_q=512, n_kv=128, chunk=2, kv_lens=[766, 95], budgets=[766, 40], batch=2),
+    dict(n_q=512, n_kv=128, chunk=2, kv_lens=[780, 95], budgets=[767, 40], batch=2),
+], ids=_id)
+def test_decode_attention_two_tiles_a_wave_and_more(case, d):
+    check_attention(dict(case, dtype="bf16", d=d))
+
+
 # one sequence: the kernels look a full list up before they know its length; lists that are full, one short of it, of fewer tiles or
 # splits, and empty, in arrays whose unused entries are out of range, and partials left by a longer list
 @pytest.mark.parametrize("count", [1600, 1599, 1500, 400, 127, 32, 1, 0])
