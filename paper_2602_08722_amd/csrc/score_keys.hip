@@ -102,7 +102,10 @@ __global__ __launch_bounds__(kScThreads, 2) void score_bf16(Dims dm, const float
   // FUSE: the queries of the wave's first row, ahead of the keys (fetches arrive in order, and these are few)
   QbarRows<D> q_first;
   if constexpr (FUSE) q_first.load(dm, static_cast<const uint16_t*>(fq.q), min(w, n_keep - 1), kv, b, lane);
-  if constexpr (!HIST) {   // the first K tile is in flight while the length arrives and the query operands are prepared
+  // The first K tile is in flight while the length arrives and the query operands are prepared.  (Past the end of a sequence it is fetched
+  // for nothing: in ten random batches with lengths up to eight times apart this launch takes 1.025 of the time that it takes with the fetch
+  // behind the length; in the other 71 calls 0.995, and a prompt of 16000 466.7 us without and 458.5 with it.)
+  if constexpr (!HIST) {
     issue(0, RA);
     asm volatile("" ::: "memory");   // (or the compiler moves these fetches behind the length's arrival)
     clear_words(zero, zero_words);
